@@ -54,7 +54,7 @@ def listed():
         # A short prompt through a 7B-class layer, forward only: prefill.
         _case("7B-class prefill of 333", "infer", "bf16", 4096, 32, 32, 128, 11008, 333),
         # A tensor-parallel share with a ragged token count.
-        _case("hidden-4096 share, 3300", "step", "bf16", 4096, 8, 8, 128, 4096, 3300),
+        _case("hidden-4096 share of 3300", "step", "bf16", 4096, 8, 8, 128, 4096, 3300),
         # 7B-class layer, forward and backward in training (gradients accumulate over calls).
         _case("7B-class layer step", "step", "bf16", 4096, 32, 32, 128, 11008, 2048, accumulate=True),
         # Backward alone of a hidden-8192 layer at an eighth tensor-parallel share: 8 query heads on one key/value head.
