@@ -1,0 +1,215 @@
+// k_gemm_ring: bf16 GEMM for problems on which 256x256 tiles would leave most of the chip idle.
+//
+// One workgroup computes one BM x BN tile of C, or one share of its k range, through a ring of NS LDS stages of
+// DK = 64 k values that are filled straight from global memory.  WM x WN waves, each a (BM/WM) x (BN/WN) block of
+// 32x32x16 MFMAs.  One barrier per stage, placed before its last k step: by then every wave holds its last fragments
+// of the stage, so its slot can be refilled (NS stages of lookahead) and the first fragments of the next stage are
+// fetched in the shadow of the last MFMAs.
+#pragma once
+#include "gemm_tile.h"
+#include "kernels.h"
+
+namespace hh {
+
+template <int KIND, int BM, int BN, int WM, int WN, int NS, bool OUT_F32>
+__global__ __launch_bounds__(WM * WN * 64) void k_gemm_ring(const bf16_t* __restrict__ A, int lda, uint32_t a_bytes,
+                                                            const bf16_t* __restrict__ B, int ldb, uint32_t b_bytes,
+                                                            void* __restrict__ Cv, int ldc, const bf16_t* R, int ldr,
+                                                            int M, int N, int K, int accumulate, int tiles, int ksplit,
+                                                            float* __restrict__ partial) {
+    constexpr int NW = WM * WN;
+    using DA = DmaTile<(KIND != GEMM_TN), BM, NW>;
+    using DB = DmaTile<(KIND == GEMM_NT), BN, NW>;
+    constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+    constexpr int STAGE = DA::BYTES + DB::BYTES;
+    constexpr int PW = DA::PER_WAVE + DB::PER_WAVE;       // DMA instructions per wave and stage
+    static_assert(NS * STAGE >= NW * 4096, "the epilogue patches reuse the ring");
+    extern __shared__ __attribute__((aligned(1024))) char smem[];   // [stage][A | B]
+
+    const int share = blockIdx.x / tiles, tix = blockIdx.x - share * tiles;
+    const int tiles_n = (N + BN - 1) / BN;
+    int tm, tn;
+    tile_of_index(tix, (M + BM - 1) / BM, tiles_n, tm, tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int nk_all = (K + DK - 1) / DK;
+    const int kbeg = (int)((long)share * nk_all / ksplit), nk = (int)((long)(share + 1) * nk_all / ksplit) - kbeg;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, hf = lane >> 5;
+    const int wm = (wave / WN) * (BM / WM), wn = (wave % WN) * (BN / WN);
+
+    const uint64_t pa = (uint64_t)A, pb = (uint64_t)B;
+    const i32x4 rsA = {(int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), (int)a_bytes, 0x00020000};
+    const i32x4 rsB = {(int)(uint32_t)pb, (int)(uint32_t)(pb >> 32), (int)b_bytes, 0x00020000};
+    const uint32_t stepA = DA::kstep_bytes(lda), stepB = DB::kstep_bytes(ldb);
+    uint32_t voA[DA::PER_WAVE], voB[DB::PER_WAVE];
+#pragma unroll
+    for (int i = 0; i < DA::PER_WAVE; i++) voA[i] = DA::voff(wave, i, m0, lda) + kbeg * stepA;
+#pragma unroll
+    for (int i = 0; i < DB::PER_WAVE; i++) voB[i] = DB::voff(wave, i, n0, ldb) + kbeg * stepB;
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
+    auto issue = [&](int slot) {
+        const uint32_t base = lds0 + slot * STAGE;
+#pragma unroll
+        for (int i = 0; i < DA::PER_WAVE; i++) { dma16(base + (wave * DA::PER_WAVE + i) * 1024, voA[i], rsA); voA[i] += stepA; }
+#pragma unroll
+        for (int i = 0; i < DB::PER_WAVE; i++) { dma16(base + DA::BYTES + (wave * DB::PER_WAVE + i) * 1024, voB[i], rsB); voB[i] += stepB; }
+    };
+#pragma unroll
+    for (int s = 0; s < NS; s++)
+        if (s < nk) issue(s);
+
+    f32x16 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+        for (int j = 0; j < TN; j++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
+
+    bf16x8 fa[2][TM], fb[2][TN];
+    auto fetch = [&](int set, int slot, int kk) {
+        const char* cA = smem + slot * STAGE;
+        const char* cB = cA + DA::BYTES;
+#pragma unroll
+        for (int i = 0; i < TM; i++) fa[set][i] = DA::frag(cA, wm + 32 * i, kk);
+#pragma unroll
+        for (int j = 0; j < TN; j++) fb[set][j] = DB::frag(cB, wn + 32 * j, kk);
+    };
+    auto mma = [&](int set) {
+#pragma unroll
+        for (int i = 0; i < TM; i++)
+#pragma unroll
+            for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0);
+    };
+    // k tile 0 has landed
+    if (nk >= NS) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * PW) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    fetch(0, 0, 0);
+    int slot = 0;
+    for (int kt = 0; kt < nk; kt++) {
+        const int next = slot + 1 == NS ? 0 : slot + 1;
+#pragma unroll
+        for (int kk = 0; kk < 3; kk++) {
+            fetch((kk + 1) & 1, slot, kk + 1);
+            mma(kk & 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // Every wave holds its last fragments of k tile kt, so its slot is free once all waves are here; k tile kt + 1
+        // must have landed for everyone, the NS - 2 tiles after it may still be on their way.
+        if (kt + NS <= nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * PW) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        if (kt + NS < nk) issue(slot);
+        if (kt + 1 < nk) fetch(0, next, 0);
+        mma(1);
+        __builtin_amdgcn_sched_barrier(0);
+        slot = next;
+    }
+
+    if (ksplit > 1) {   // a share of the k range: raw fp32 sums, finished by k_splitk_reduce
+        float* pt = partial + ((size_t)(tm * tiles_n + tn) * ksplit + share) * (BM * BN);
+#pragma unroll
+        for (int i = 0; i < TM; i++)
+#pragma unroll
+            for (int j = 0; j < TN; j++)
+#pragma unroll
+                for (int g = 0; g < 4; g++)
+                    *reinterpret_cast<float4*>(pt + (wm + 32 * i + (lane & 31)) * BN + wn + 32 * j + 8 * g + 4 * hf) =
+                        make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+        return;
+    }
+
+    // Epilogue as in k_gemm_dma: every 32x32 block goes through a wave-private LDS patch, so that loads of what is
+    // added and stores cover whole row segments.
+    constexpr uint32_t CES = OUT_F32 ? 4u : 2u;
+    constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
+    const __amdgpu_buffer_rsrc_t rsC = make_rsrc(Cv, (uint32_t)(((size_t)(M - 1) * ldc + N) * CES));
+    const __amdgpu_buffer_rsrc_t rsR = make_rsrc(R ? (const void*)R : (const void*)Cv, R ? (uint32_t)(((size_t)(M - 1) * ldr + N) * 2u) : 0u);
+    __syncthreads();   // nobody reads the ring any more: each wave takes 4 KB of it as its patch
+    char* const patch = smem + wave * 4096;
+    const int r_w = lane & 31;                       // row written, chunks 2g + hf
+    const int r_r = lane >> 3, c_r = lane & 7;       // row (+ 8t) and chunk read back
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+        for (int j = 0; j < TN; j++) {
+            const int col = n0 + wn + 32 * j + 4 * c_r;
+            float4 add[4];
+            uint32_t off_c[4];
+#pragma unroll
+            for (int t = 0; t < 4; t++) {
+                const uint32_t row = (uint32_t)(m0 + wm + 32 * i + r_r + 8 * t);
+                off_c[t] = col < N ? (row * (uint32_t)ldc + (uint32_t)col) * CES : OUT_OF_RANGE;
+                add[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (OUT_F32) {
+                    if (accumulate) {
+                        const i32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsC, off_c[t], 0, 0);
+                        add[t] = make_float4(__int_as_float(v[0]), __int_as_float(v[1]), __int_as_float(v[2]), __int_as_float(v[3]));
+                    }
+                } else if (R) {
+                    const uint32_t off_r = col < N ? (row * (uint32_t)ldr + (uint32_t)col) * 2u : OUT_OF_RANGE;
+                    const i32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsR, off_r, 0, 0);
+                    add[t] = make_float4(lo_bf((uint32_t)v[0]), hi_bf((uint32_t)v[0]), lo_bf((uint32_t)v[1]), hi_bf((uint32_t)v[1]));
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < 4; g++)
+                *reinterpret_cast<float4*>(patch + r_w * 128 + (((2 * g + hf) ^ ((r_w >> 1) & 7)) << 4)) =
+                    make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+#pragma unroll
+            for (int t = 0; t < 4; t++) {
+                const int rr = 8 * t + r_r;
+                float4 v = *reinterpret_cast<const float4*>(patch + rr * 128 + ((c_r ^ ((rr >> 1) & 7)) << 4));
+                v.x += add[t].x; v.y += add[t].y; v.z += add[t].z; v.w += add[t].w;
+                if (OUT_F32) {
+                    const i32x4 o = {__float_as_int(v.x), __float_as_int(v.y), __float_as_int(v.z), __float_as_int(v.w)};
+                    __builtin_amdgcn_raw_buffer_store_b128(o, rsC, off_c[t], 0, 0);
+                } else {
+                    const i32x2 o = {(int)pack_bf2(v.x, v.y), (int)pack_bf2(v.z, v.w)};
+                    __builtin_amdgcn_raw_buffer_store_b64(o, rsC, off_c[t], 0, 0);
+                }
+            }
+        }
+}
+
+// Sums the ksplit fp32 shares of every BM x BN tile in a fixed order and applies the epilogue.  A thread owns 4
+// consecutive columns of one row of C.
+template <bool OUT_F32>
+__global__ __launch_bounds__(256) void k_ring_reduce(const float* __restrict__ partial, int ksplit, int bm, int bn,
+                                                     void* __restrict__ Cv, int ldc, const bf16_t* R, int ldr,
+                                                     int M, int N, int accumulate) {
+    const int vpr = N / 4;
+    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= (long)M * vpr) return;
+    const int m = (int)(idx / vpr), n = (int)(idx - (long)m * vpr) * 4;
+    const int tiles_n = (N + bn - 1) / bn;
+    const int tm = m / bm, tn = n / bn;
+    const float* p = partial + (size_t)(tm * tiles_n + tn) * ksplit * (bm * bn) + (m - tm * bm) * bn + (n - tn * bn);
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < ksplit; c++) {
+        const float4 t = *reinterpret_cast<const float4*>(p + (size_t)c * (bm * bn));
+        v[0] += t.x; v[1] += t.y; v[2] += t.z; v[3] += t.w;
+    }
+    if (OUT_F32) {
+        float* c = reinterpret_cast<float*>(Cv) + (size_t)m * ldc + n;
+        if (accumulate) {
+            const float4 old = *reinterpret_cast<const float4*>(c);
+            v[0] += old.x; v[1] += old.y; v[2] += old.z; v[3] += old.w;
+        }
+        *reinterpret_cast<float4*>(c) = make_float4(v[0], v[1], v[2], v[3]);
+    } else {
+        if (R) {
+            const uint2 rr = *reinterpret_cast<const uint2*>(R + (size_t)m * ldr + n);
+            v[0] += lo_bf(rr.x); v[1] += hi_bf(rr.x); v[2] += lo_bf(rr.y); v[3] += hi_bf(rr.y);
+        }
+        uint2 o;
+        o.x = pack_bf2(v[0], v[1]);
+        o.y = pack_bf2(v[2], v[3]);
+        *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(Cv) + (size_t)m * ldc + n) = o;
+    }
+}
+
+}  // namespace hh

@@ -1,0 +1,35 @@
+"""Layers whose twelve projections take every tile and k split of the GEMM dispatch, with ragged token counts.
+
+Tolerances are those of every bf16 layer test (storage rounding 2^-9 per tensor, fp32 sums); the shapes were chosen by
+evaluating the dispatch rule for each of their projections.
+"""
+import pytest
+
+from paper_2405_16256_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2405_16256_amd import binding as hh
+    c = hh.hh_ctx_create(0)
+    yield c
+    hh.hh_ctx_destroy(c)
+
+
+@pytest.mark.parametrize("shape,packed", [
+    # 64x64 (whole and 4 shares of k), 64x128 (whole and 8 shares), 128x128 two per CU
+    (I.LayerShape(1024, 4, 128, 2816, 150, 1), True),
+    # the same with 70 tokens over grouped heads: single projections of 64 and 128 columns, k of 70 in the weight gradients
+    (I.LayerShape(1024, 8, 64, 2816, 35, 2, n_kv_heads=1), False),
+    # 128x256 whole, 128x128 (one per CU) whole and 3 shares
+    (I.LayerShape(2048, 4, 128, 4096, 520, 1), True),
+    # 128x256 in 4 shares, 64x128 in 4 shares, 256x256 on problems of one or two rows of tiles
+    (I.LayerShape(4096, 8, 128, 5632, 333, 1), True),
+    # one token: a single row of C, a single k value in the weight gradients
+    (I.LayerShape(2048, 2, 128, 1024, 1, 1), True),
+])
+def test_every_tile_of_the_gemm_dispatch(ctx, shape, packed):
+    from tests.test_gpu_parity import check_layer
+    check_layer(ctx, shape, True, 301, packed=packed, label="tiles")
