@@ -1,88 +1,208 @@
-// fp32 GEMM for the fp32 reference-precision path (tiny shapes, any sizes):
-// LDS-tiled FMA kernel, 64x64 output tile, fully guarded edges, fp32 throughout.
-#include "common.h"
+// fp32 GEMM of the fp32 path on the matrix cores (v_mfma_f32_32x32x2_f32: fp32 operands, products and sums), any
+// sizes that are multiples of 8 in N and in a contiguous K.
+//
+//   NT  C[M,N] = A[M,K] B[N,K]^T     NN  C[M,N] = A[M,K] B[K,N]     TN  C[M,N] = A[K,M]^T B[K,N]
+//
+// A workgroup of 4 waves computes a BM x BN tile; k advances FK = 32 at a time through a ring of NS LDS stages filled
+// straight from global memory.  Tile 64x64: each wave a 32x32 block over the whole stage.  Tile 32x32: all four waves
+// on the one block, each taking 8 of the stage's 32 k values, their sums added through LDS in wave order.
+//
+// What bounds it: one wave needs 16 MFMAs of 64 cycles per 32x32 block and stage, so the small problems of this path
+// (a few dozen blocks, k up to a few thousand) are bound by how many waves share that chain: the 32x32 tile spreads a
+// problem over 16 times the waves of a 64x64 one at twice the LDS traffic, and is taken until 64x64 tiles fill the
+// chip.  Measured against the 64x64 FMA tile kernel with scalar loads before it, per call: 128x256x1376 NN 189 -> 12.7
+// us, 700x1024x1536 NN 285 -> 27 us (82 TFLOP/s), 1024x2048x700 TN 98 -> 30 us, 2048x8192x1024 NT 536 -> 287 us (120).
+// Eight stages instead of four are 5 to 20 % slower: the smaller ring lets five workgroups share a CU.
+#include "gemm_tile.h"
 #include "kernels.h"
 
 namespace hh {
 
-constexpr int FT = 64;   // tile edge
-constexpr int FK = 16;   // k step
+constexpr int FK = 32;   // k values per stage
 
-// A(m,k) = A[m*sam + k*sak], B(n,k) = B[n*sbn + k*sbk]; AK/BK: k is the contiguous index.
-template <bool AK, bool BK>
-__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, long sam, long sak,
-                                                  const float* __restrict__ B, long sbn, long sbk,
-                                                  float* __restrict__ C, int ldc, const float* __restrict__ R, int ldr,
-                                                  int M, int N, int K, int accumulate) {
-    __shared__ float As[FK][FT + 4];
-    __shared__ float Bs[FK][FT + 4];
-    const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-    const int m0 = blockIdx.y * FT, n0 = blockIdx.x * FT;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += FK) {
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const int idx = tid + 256 * i;
-            {
-                const int mm = AK ? idx / FK : idx % FT, kk = AK ? idx % FK : idx / FT;
-                const int gm = m0 + mm, gk = k0 + kk;
-                As[kk][mm] = (gm < M && gk < K) ? A[gm * sam + gk * sak] : 0.f;
-            }
-            {
-                const int nn = BK ? idx / FK : idx % FT, kk = BK ? idx % FK : idx / FT;
-                const int gn = n0 + nn, gk = k0 + kk;
-                Bs[kk][nn] = (gn < N && gk < K) ? B[gn * sbn + gk * sbk] : 0.f;
-            }
+// One operand's tile of ROWS rows of C's dimension x FK values of k.
+//   KC (k contiguous): LDS [row][k], 128 bytes a row, 16-byte chunks XOR-swizzled by the row index.
+//   otherwise:         LDS [k][row], bit 7 of the byte address flipped for k rows with bit 2 set, so that the two half
+//                      waves of a fragment read (k and k + 4) fall into different banks.
+template <bool KC, int ROWS>
+struct FTile {
+    static constexpr int BYTES = ROWS * FK * 4;
+    static constexpr int PER_WAVE = BYTES / 1024 / 4;
+    static constexpr int PITCH = ROWS * 4;
+    struct Src { uint32_t off; int k; };   // byte offset at k tile 0; first k value the lane fetches there
+    __device__ static __forceinline__ Src src(int wave, int i, int row0, int ld) {
+        const int idx = wave * PER_WAVE + i, L = threadIdx.x & 63;
+        if (KC) {
+            const int r = 8 * idx + (L >> 3), c = (L & 7) ^ ((r >> 1) & 7);
+            return {((uint32_t)(row0 + r) * (uint32_t)ld + (uint32_t)(4 * c)) * 4u, 4 * c};
         }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < FK; kk++) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; i++) { a[i] = As[kk][ty * 4 + i]; b[i] = Bs[kk][tx * 4 + i]; }
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-#pragma unroll
-                for (int j = 0; j < 4; j++) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
+        const int p = idx * 1024 + L * 16;
+        const int lb = p ^ ((((p / PITCH) >> 2) & 1) << 7);
+        const int k = lb / PITCH;
+        return {((uint32_t)k * (uint32_t)ld + (uint32_t)row0) * 4u + (uint32_t)(lb % PITCH), k};
     }
+    __device__ static __forceinline__ uint32_t kstep_bytes(int ld) { return KC ? FK * 4u : (uint32_t)FK * (uint32_t)ld * 4u; }
+    // the lane's 4 values of k step kk (8 k values): row rb + lane%32, k = 8kk + 4(lane/32) + e
+    __device__ static __forceinline__ f32x4 frag(const char* lds, int rb, int kk) {
+        const int l = threadIdx.x & 63, r = rb + (l & 31), hf = l >> 5;
+        if (KC) return *reinterpret_cast<const f32x4*>(lds + r * 128 + (((2 * kk + hf) ^ ((r >> 1) & 7)) << 4));
+        f32x4 v;
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-        const int gm = m0 + ty * 4 + i;
-        if (gm >= M) continue;
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            const int gn = n0 + tx * 4 + j;
-            if (gn >= N) continue;
-            float v = acc[i][j];
-            if (R) v += R[(size_t)gm * ldr + gn];
-            float* c = C + (size_t)gm * ldc + gn;
-            *c = accumulate ? *c + v : v;
+        for (int e = 0; e < 4; e++) {
+            const int k = 8 * kk + 4 * hf + e;
+            v[e] = *reinterpret_cast<const float*>(lds + ((k * PITCH + r * 4) ^ (hf << 7)));   // (k >> 2) & 1 == hf
         }
+        return v;
+    }
+};
+
+template <int KIND, int BT, int NS>
+__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, int lda, uint32_t a_bytes,
+                                                  const float* __restrict__ B, int ldb, uint32_t b_bytes,
+                                                  float* __restrict__ C, int ldc, const float* R, int ldr,
+                                                  int M, int N, int K, int accumulate) {
+    constexpr bool A_KC = KIND != GEMM_TN, B_KC = KIND == GEMM_NT;
+    using TA = FTile<A_KC, BT>;
+    using TB = FTile<B_KC, BT>;
+    constexpr int KG = BT == 32 ? 4 : 1;                  // waves that share a block along k
+    constexpr int STAGE = TA::BYTES + TB::BYTES, PW = TA::PER_WAVE + TB::PER_WAVE;
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int tiles_n = (N + BT - 1) / BT;
+    int tm, tn;
+    tile_of_index(blockIdx.x, (M + BT - 1) / BT, tiles_n, tm, tn);
+    const int m0 = tm * BT, n0 = tn * BT;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, hf = lane >> 5;
+    const int wm = KG == 1 ? (wave >> 1) * 32 : 0, wn = KG == 1 ? (wave & 1) * 32 : 0;
+    const int nk = (K + FK - 1) / FK;
+
+    const uint64_t pa = (uint64_t)A, pb = (uint64_t)B;
+    const i32x4 rsA = {(int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), (int)a_bytes, 0x00020000};
+    const i32x4 rsB = {(int)(uint32_t)pb, (int)(uint32_t)(pb >> 32), (int)b_bytes, 0x00020000};
+    const uint32_t stepA = TA::kstep_bytes(lda), stepB = TB::kstep_bytes(ldb);
+    typename TA::Src sa[TA::PER_WAVE];
+    typename TB::Src sb[TB::PER_WAVE];
+#pragma unroll
+    for (int i = 0; i < TA::PER_WAVE; i++) sa[i] = TA::src(wave, i, m0, lda);
+#pragma unroll
+    for (int i = 0; i < TB::PER_WAVE; i++) sb[i] = TB::src(wave, i, n0, ldb);
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
+    auto issue = [&](int slot, int kt) {
+        const uint32_t base = lds0 + slot * STAGE;
+        // k values at or past K read as zero: they lie past the end of a k-strided operand by themselves, in a
+        // k-contiguous one (4 values per lane, K a multiple of 8) the lane's offset is put out of range
+        const int k0 = kt * FK;
+#pragma unroll
+        for (int i = 0; i < TA::PER_WAVE; i++) {
+            const uint32_t off = sa[i].off + (uint32_t)kt * stepA;
+            dma16(base + (wave * TA::PER_WAVE + i) * 1024, A_KC && k0 + sa[i].k >= K ? a_bytes : off, rsA);
+        }
+#pragma unroll
+        for (int i = 0; i < TB::PER_WAVE; i++) {
+            const uint32_t off = sb[i].off + (uint32_t)kt * stepB;
+            dma16(base + TA::BYTES + (wave * TB::PER_WAVE + i) * 1024, B_KC && k0 + sb[i].k >= K ? b_bytes : off, rsB);
+        }
+    };
+#pragma unroll
+    for (int s = 0; s < NS - 1; s++)
+        if (s < nk) issue(s, s);
+
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; r++) acc[r] = 0.f;
+    int slot = 0, fill = NS - 1;
+    for (int kt = 0; kt < nk; kt++) {
+        // k tile kt has landed, and everyone has read k tile kt - 1, whose slot is filled next
+        if (nk - 1 - kt >= NS - 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * PW) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (kt + NS - 1 < nk) issue(fill, kt + NS - 1);
+        const char* cA = smem + slot * STAGE;
+        const char* cB = cA + TA::BYTES;
+#pragma unroll
+        for (int q = 0; q < 4 / KG; q++) {
+            const int kk = KG == 1 ? q : wave;
+            const f32x4 fa = TA::frag(cA, wm, kk), fb = TB::frag(cB, wn, kk);
+#pragma unroll
+            for (int e = 0; e < 4; e++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[e], fa[e], acc, 0, 0, 0);
+        }
+        slot = slot + 1 == NS ? 0 : slot + 1;
+        fill = fill + 1 == NS ? 0 : fill + 1;
+    }
+    __syncthreads();   // nobody reads the ring any more
+    // A lane owns row lane%32 of its block and runs of 4 columns 8g + 4hf; through an LDS patch of 4 KB per block the
+    // stores cover 128-byte row segments.  With KG = 4 the four waves' patches are the four partial sums.
+    char* const patch = smem + wave * 4096;
+    const int r_w = lane & 31;
+#pragma unroll
+    for (int g = 0; g < 4; g++)
+        *reinterpret_cast<float4*>(patch + r_w * 128 + (((2 * g + hf) ^ ((r_w >> 1) & 7)) << 4)) =
+            make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
+    if (KG > 1) __syncthreads();
+    const int r_r = lane >> 3, c_r = lane & 7;
+#pragma unroll
+    for (int t = 0; t < 4 / KG; t++) {
+        const int rr = 8 * (KG == 1 ? t : wave) + r_r;
+        const int at = rr * 128 + ((c_r ^ ((rr >> 1) & 7)) << 4);
+        float4 v = *reinterpret_cast<const float4*>((KG == 1 ? patch : smem) + at);
+#pragma unroll
+        for (int q = 1; q < KG; q++) {
+            const float4 u = *reinterpret_cast<const float4*>(smem + q * 4096 + at);
+            v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+        }
+        const int m = m0 + wm + rr, n = n0 + wn + 4 * c_r;
+        if (m >= M || n >= N) continue;
+        if (R) {
+            const float4 u = *reinterpret_cast<const float4*>(R + (size_t)m * ldr + n);
+            v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+        }
+        float4* c = reinterpret_cast<float4*>(C + (size_t)m * ldc + n);
+        if (accumulate) {
+            const float4 u = *c;
+            v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+        }
+        *c = v;
     }
 }
 
-hipError_t gemm_f32(const GemmDesc& g, hipStream_t st) {
-    dim3 grid((g.N + FT - 1) / FT, (g.M + FT - 1) / FT);
-    const float* A = (const float*)g.A;
-    const float* B = (const float*)g.B;
-    float* C = (float*)g.C;
-    const float* R = (const float*)g.R;
-    switch (g.kind) {
-        case GEMM_NT:
-            k_gemm_f32<true, true><<<grid, 256, 0, st>>>(A, g.lda, 1, B, g.ldb, 1, C, g.ldc, R, g.ldr, g.M, g.N, g.K, g.accumulate);
-            break;
-        case GEMM_NN:
-            k_gemm_f32<true, false><<<grid, 256, 0, st>>>(A, g.lda, 1, B, 1, g.ldb, C, g.ldc, R, g.ldr, g.M, g.N, g.K, g.accumulate);
-            break;
-        case GEMM_TN:
-            k_gemm_f32<false, false><<<grid, 256, 0, st>>>(A, 1, g.lda, B, 1, g.ldb, C, g.ldc, R, g.ldr, g.M, g.N, g.K, g.accumulate);
-            break;
-        default:
-            return hipErrorInvalidValue;
-    }
+template <int KIND, int BT, int NS>
+static hipError_t launch(const GemmDesc& g, uint32_t a_bytes, uint32_t b_bytes, hipStream_t st) {
+    constexpr int LDS = NS * 2 * BT * FK * 4;
+    static_assert(LDS >= 4 * 4096, "the epilogue patches reuse the ring");
+    static std::atomic<uint64_t> lds_ok{0};
+    auto kern = k_gemm_f32<KIND, BT, NS>;
+    const hipError_t e = allow_lds((const void*)kern, LDS, lds_ok);
+    if (e != hipSuccess) return e;
+    const int tiles = ((g.M + BT - 1) / BT) * ((g.N + BT - 1) / BT);
+    kern<<<tiles, 256, LDS, st>>>((const float*)g.A, g.lda, a_bytes, (const float*)g.B, g.ldb, b_bytes, (float*)g.C, g.ldc, (const float*)g.R, g.ldr,
+                                  g.M, g.N, g.K, g.accumulate);
     return hipGetLastError();
+}
+
+template <int KIND>
+static hipError_t pick(const GemmDesc& g, uint32_t a_bytes, uint32_t b_bytes, hipStream_t st) {
+    // 64x64 tiles once they fill the chip (about 2.5 per CU): 700x4096x1024 NT, 704 of them: 60 us against 62.5 with
+    // 32x32 tiles; 2048x8192x1024: 287 against 355; 700x1536x1024, 264 of them: 38.6 against 31.5
+    const long tiles = (long)((g.M + 63) / 64) * ((g.N + 63) / 64);
+    if (tiles >= 640) return launch<KIND, 64, 4>(g, a_bytes, b_bytes, st);
+    return launch<KIND, 32, 4>(g, a_bytes, b_bytes, st);
+}
+
+hipError_t gemm_f32(const GemmDesc& g, hipStream_t st) {
+    if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipSuccess;
+    const long a_rows = (g.kind == GEMM_TN) ? g.K : g.M, a_cols = (g.kind == GEMM_TN) ? g.M : g.K;
+    const long b_rows = (g.kind == GEMM_NT) ? g.N : g.K, b_cols = (g.kind == GEMM_NT) ? g.K : g.N;
+    const long a_bytes = ((a_rows - 1) * g.lda + a_cols) * 4, b_bytes = ((b_rows - 1) * g.ldb + b_cols) * 4;
+    // 32-bit byte offsets with room for a tile of rows past the end
+    if (a_bytes >= (1L << 32) - (1L << 25) || b_bytes >= (1L << 32) - (1L << 25)) return hipErrorInvalidValue;
+    if (g.lda > 65535 || g.ldb > 65535 || g.N % 4 != 0) return hipErrorInvalidValue;
+    if (g.kind != GEMM_TN && g.K % 4 != 0) return hipErrorInvalidValue;
+    switch (g.kind) {
+        case GEMM_NT: return pick<GEMM_NT>(g, (uint32_t)a_bytes, (uint32_t)b_bytes, st);
+        case GEMM_NN: return pick<GEMM_NN>(g, (uint32_t)a_bytes, (uint32_t)b_bytes, st);
+        case GEMM_TN: return pick<GEMM_TN>(g, (uint32_t)a_bytes, (uint32_t)b_bytes, st);
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace hh

@@ -33,3 +33,15 @@ def ctx():
 def test_every_tile_of_the_gemm_dispatch(ctx, shape, packed):
     from tests.test_gpu_parity import check_layer
     check_layer(ctx, shape, True, 301, packed=packed, label="tiles")
+
+
+@pytest.mark.parametrize("shape,packed", [
+    # 64x64 tiles in the gate|up projection, k of 1000 and 700 (neither a multiple of the 32-wide stage)
+    (I.LayerShape(1000, 4, 64, 2040, 700, 1), True),
+    # 32x32 tiles with k of 8, 72 and 40: shorter than one stage, and a tail of a quarter stage
+    (I.LayerShape(72, 1, 64, 40, 5, 2), False),
+    (I.LayerShape(8, 1, 64, 8, 33, 1), True),
+])
+def test_both_tiles_of_the_fp32_gemm(ctx, shape, packed):
+    from tests.test_gpu_parity import check_layer
+    check_layer(ctx, shape, False, 302, packed=packed, label="f32 tiles")
