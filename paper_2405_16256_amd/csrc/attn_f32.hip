@@ -1,179 +1,442 @@
-// fp32 causal attention for the fp32 reference-precision path (small shapes).
-// One wave per query row (forward, dq) or per key row (dk, dv): lanes span keys
-// (resp. queries) for the scores and span head channels for the weighted sums.
-// Deterministic: no atomics.
+// fp32 causal attention of the fp32 path, forward and backward, on the fp32 matrix instructions
+// (v_mfma_f32_16x16x4_f32: fp32 operands, products and sums).  The S x S scores are never written out.
+//
+// A workgroup of 4 waves owns 16 queries (forward, dq) or 16 keys (dk, dv) of one head and its waves take the 16-row
+// tiles of the other side in turn; their partial results are added through LDS in wave order (no atomics).  Tiles of
+// 16 and not of 32 because this path serves small launches: it is bound by the longest chain of tiles one wave walks
+// (64 to 128 MFMAs of 32 cycles per pair of tiles at head_dim 128), so it needs many short chains.
+//
+// Operands go from global memory (L2 for all but the first reader) straight to registers, in two layouts:
+//   rows: lane l holds row l%16 and the channels 16j + 4(l/16) + e: 16-byte loads; as both operands of a product over
+//         the channels carry the same lane -> channel map, the order in which channels are summed does not matter.
+//   cols: lane l holds the rows 4(l/16) + r and the channels 64q + 4(l%16) + e: the transposed first operand of a
+//         product over the tile's rows, whose second operand is then exactly the accumulator of the scores
+//         (lane l: column l%16, rows 4(l/16) + r).
+// The next tile of each operand is requested as soon as its registers are free.
+//
+// Measured on one MI355X against one wave per row with scalar dot products (us per call, 8 query heads on 2 key/value
+// heads of 128, 700 tokens): forward 401 -> 28, dq 424 -> 42, dk|dv 1246 -> 53; 4 heads of 64, 128 tokens: 39.7 -> 6.4,
+// 26.3 -> 7.6, 33.3 -> 8.9.
 #include "common.h"
 #include "kernels.h"
 
 namespace hh {
 
-constexpr int AW = 4;  // waves per workgroup
+constexpr int AW = 4;     // waves per workgroup
+constexpr int AT = 16;    // rows of a tile
+constexpr uint32_t A_OUT = 0xFFFFFFF0u;   // byte offset past the end of every buffer: reads as zero
 
-__device__ __forceinline__ float dot_row(const float* __restrict__ a_lds, const float* __restrict__ row, int d) {
-    float acc = 0.f;
-    for (int i = 0; i < d; i += 4) {
-        const float4 r = *reinterpret_cast<const float4*>(row + i);
-        acc = fmaf(a_lds[i], r.x, acc); acc = fmaf(a_lds[i + 1], r.y, acc);
-        acc = fmaf(a_lds[i + 2], r.z, acc); acc = fmaf(a_lds[i + 3], r.w, acc);
-    }
-    return acc;
+template <int D> struct RowsF { f32x4 v[D / 16]; };
+template <int D> struct ColsF { f32x4 v[4][D / 64]; };
+
+__device__ __forceinline__ f32x4 load4(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+    const i32x4 u = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+    return f32x4{__int_as_float(u[0]), __int_as_float(u[1]), __int_as_float(u[2]), __int_as_float(u[3])};
 }
 
-__global__ __launch_bounds__(AW* WAVE) void k_attn_f32_fwd(const float* __restrict__ qkv, int ld, float* __restrict__ o,
-                                                           float* __restrict__ lse, int B, int S, int nh, int nkv, int d) {
-    __shared__ float qs[AW][128];
-    const int wv = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
-    const long w = (long)blockIdx.x * AW + wv;
-    if (w >= (long)B * nh * S) return;  // whole wave leaves together; no block-wide barrier below
-    const int s = (int)(w % S), h = (int)((w / S) % nh), b = (int)(w / ((long)S * nh));
-    const int A = nh * d;
-    const float* qrow = qkv + ((size_t)b * S + s) * ld + h * d;
-    const float* kb = qkv + (size_t)b * S * ld + A + (h / (nh / nkv)) * d;   // the query head's key/value head
-    const float* vb = kb + nkv * d;
-    for (int i = lane; i < d; i += WAVE) qs[wv][i] = qrow[i];
-    __builtin_amdgcn_wave_barrier();
-    const float scale = 1.0f / sqrtf((float)d);
-    float m = -INFINITY, l = 0.f, acc0 = 0.f, acc1 = 0.f;
-    for (int t0 = 0; t0 <= s; t0 += WAVE) {
-        const int t = t0 + lane;
-        float z = -INFINITY;
-        if (t <= s) z = dot_row(qs[wv], kb + (size_t)t * ld, d) * scale;
-        const float mn = fmaxf(m, wave_max(z));
-        const float alpha = expf(m - mn);
-        const float p = (t <= s) ? expf(z - mn) : 0.f;
-        l = l * alpha + wave_sum(p);
-        acc0 *= alpha; acc1 *= alpha;
-        const int nk = min(WAVE, s - t0 + 1);
-        for (int j = 0; j < nk; j++) {
-            const float pj = __shfl(p, j, WAVE);
-            const float* vr = vb + (size_t)(t0 + j) * ld;
-            if (lane < d) acc0 = fmaf(pj, vr[lane], acc0);
-            if (lane + WAVE < d) acc1 = fmaf(pj, vr[lane + WAVE], acc1);
+// One operand of one head: rows [0, S) of `ld` elements each, the head's channels at the base.  Rows at or past S read
+// as zero (the rows behind them may belong to the next sample).
+struct Operand {
+    __amdgpu_buffer_rsrc_t rs;
+    uint32_t base, ld4;   // bytes
+    int S;
+    __device__ __forceinline__ uint32_t at(int row, int channel) const {
+        return row < S ? base + (uint32_t)row * ld4 + (uint32_t)channel * 4u : A_OUT;
+    }
+    template <int D> __device__ __forceinline__ void rows(RowsF<D>& f, int row0) const {
+        const int l = threadIdx.x & 63;
+        const uint32_t o = at(row0 + (l & 15), 4 * (l >> 4));
+#pragma unroll
+        for (int j = 0; j < D / 16; j++) f.v[j] = load4(rs, o + (o == A_OUT ? 0u : 64u * j));
+    }
+    template <int D> __device__ __forceinline__ void cols(ColsF<D>& f, int row0) const {
+        const int l = threadIdx.x & 63;
+#pragma unroll
+        for (int r = 0; r < 4; r++)
+#pragma unroll
+            for (int q = 0; q < D / 64; q++) f.v[r][q] = load4(rs, at(row0 + 4 * (l >> 4) + r, 64 * q + 4 * (l & 15)));
+    }
+};
+// `origin` is the array, `elems` its extent, `first` the element of row 0, channel 0
+__device__ __forceinline__ Operand operand(const float* origin, size_t elems, size_t first, int ld, int S) {
+    return Operand{make_rsrc(origin, (uint32_t)(elems * 4)), (uint32_t)(first * 4), (uint32_t)ld * 4u, S};
+}
+
+// a b^T over the channels: lane l gets column l%16 (row of b), rows 4(l/16) + r (rows of a)
+template <int D>
+__device__ __forceinline__ f32x4 dot_tiles(const RowsF<D>& a, const RowsF<D>& b) {
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;   // two chains: one alone would wait for its own results
+#pragma unroll
+    for (int j = 0; j < D / 16; j += 2)
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[j][e], b.v[j][e], s0, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[j + 1][e], b.v[j + 1][e], s1, 0, 0, 0);
         }
+    return s0 + s1;
+}
+
+// acc[4q+e] += c^T w over the tile's rows; w as dot_tiles gives it.  Accumulator register r of block 4q+e is channel
+// 64q + 16(l/16) + 4r + e of column l%16.
+template <int D>
+__device__ __forceinline__ void add_cols(f32x4 (&acc)[D / 16], const ColsF<D>& c, f32x4 w) {
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+#pragma unroll
+        for (int q = 0; q < D / 64; q++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) acc[4 * q + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(c.v[r][q][e], w[r], acc[4 * q + e], 0, 0, 0);
+}
+
+// On the diagonal some weights are zero because the pair is masked, and a product of such a zero with an infinity or
+// NaN must not reach the sum: a tile that holds one goes through the allowed pairs alone.
+template <int D>
+__device__ __forceinline__ bool all_finite(const ColsF<D>& c) {
+    float t = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+#pragma unroll
+        for (int q = 0; q < D / 64; q++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) t = fmaf(c.v[r][q][e], 0.f, t);
+    return !__any(t != 0.f);
+}
+// rows_are_keys: pair allowed where tile row <= column; else where tile row >= column (both count from the diagonal)
+template <int D, bool ROWS_ARE_KEYS>
+__device__ __forceinline__ void add_cols_masked(f32x4 (&acc)[D / 16], const Operand& op, int row0, f32x4 w) {
+    const int l = threadIdx.x & 63, col = l & 15, g = l >> 4;
+    for (int row = 0; row < AT; row++) {
+        float wr = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const float t = __shfl(w[r], ((row >> 2) << 4) | col, WAVE);
+            if (r == (row & 3)) wr = t;
+        }
+        if (row0 + row >= op.S || (ROWS_ARE_KEYS ? row > col : row < col)) continue;
+#pragma unroll
+        for (int q = 0; q < D / 64; q++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                const f32x4 v = load4(op.rs, op.at(row0 + row, 64 * q + 16 * g + 4 * r));
+#pragma unroll
+                for (int e = 0; e < 4; e++) acc[4 * q + e][r] = fmaf(wr, v[e], acc[4 * q + e][r]);
+            }
+    }
+}
+
+// Partial sums of the 4 waves: [wave][column][channel], rows padded by one 16-byte chunk against bank conflicts.
+template <int D> struct Merge {
+    static constexpr int PITCH = D + 4;
+    static constexpr int FLOATS = AW * AT * PITCH;
+    __device__ static __forceinline__ void put(float* buf, int wave, const f32x4 (&acc)[D / 16]) {
+        const int l = threadIdx.x & 63;
+        float* p = buf + (wave * AT + (l & 15)) * PITCH + 16 * (l >> 4);
+#pragma unroll
+        for (int q = 0; q < D / 64; q++)
+#pragma unroll
+            for (int r = 0; r < 4; r++)
+                *reinterpret_cast<f32x4*>(p + 64 * q + 4 * r) = f32x4{acc[4 * q][r], acc[4 * q + 1][r], acc[4 * q + 2][r], acc[4 * q + 3][r]};
+    }
+    __device__ static __forceinline__ f32x4 get(const float* buf, int wave, int column, int channel) {
+        return *reinterpret_cast<const f32x4*>(buf + (wave * AT + column) * PITCH + channel);
+    }
+    __device__ static __forceinline__ f32x4 sum(const float* buf, int column, int channel) {
+        f32x4 s = get(buf, 0, column, channel);
+#pragma unroll
+        for (int w = 1; w < AW; w++) s += get(buf, w, column, channel);
+        return s;
+    }
+    // the workgroup writes the sums of its 16 columns, times `scale`, to rows tok0.. of `out`; with a rotary table the
+    // pairs (i, i + D/2) are rotated by minus the angle of their position on the way
+    __device__ static __forceinline__ void write(const float* buf, float* out, int ld, int pos0, int S, float scale,
+                                                 const float* table, int table_seq) {
+        constexpr int HALF = D / 2;
+        const int column = threadIdx.x >> 4, c = (threadIdx.x & 15) * 4;
+        if (pos0 + column >= S || c >= HALF) return;
+        f32x4 a = sum(buf, column, c) * scale, b = sum(buf, column, c + HALF) * scale;
+        if (table) {
+            const f32x4 cs = *reinterpret_cast<const f32x4*>(table + (size_t)(pos0 + column) * HALF + c);
+            const f32x4 sn = *reinterpret_cast<const f32x4*>(table + (size_t)(table_seq + pos0 + column) * HALF + c);
+            const f32x4 ra = a * cs + b * sn, rb = b * cs - a * sn;
+            a = ra; b = rb;
+        }
+        float* p = out + (size_t)column * ld + c;
+        *reinterpret_cast<f32x4*>(p) = a;
+        *reinterpret_cast<f32x4*>(p + HALF) = b;
+    }
+};
+
+// reductions over the four lanes that share a column
+__device__ __forceinline__ float col_max(float v) { v = fmaxf(v, __shfl_xor(v, 16, WAVE)); return fmaxf(v, __shfl_xor(v, 32, WAVE)); }
+__device__ __forceinline__ float col_sum(float v) { v += __shfl_xor(v, 16, WAVE); return v + __shfl_xor(v, 32, WAVE); }
+
+template <int D>
+__global__ __launch_bounds__(AW* WAVE, 2) void k_attn_f32_fwd(const float* __restrict__ qkv, int ld, float* __restrict__ o,
+                                                              float* __restrict__ lse, int B, int S, int nh, int nkv) {
+    __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
+    __shared__ float ms[AW][AT], ls[AW][AT];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4;
+    const int nhb = nh * B, tiles = (S + AT - 1) / AT;
+    const int qt = tiles - 1 - (int)blockIdx.x / nhb, h = (blockIdx.x % nhb) % nh, b = (blockIdx.x % nhb) / nh;   // longest first
+    const int A = nh * D, kcol = A + (h / (nh / nkv)) * D;
+    const size_t extent = (size_t)B * S * ld, row0 = (size_t)b * S * ld;
+    const Operand oq = operand(qkv, extent, row0 + h * D, ld, S), ok = operand(qkv, extent, row0 + kcol, ld, S),
+                  ov = operand(qkv, extent, row0 + kcol + nkv * D, ld, S);
+    RowsF<D> qf, kf;
+    ColsF<D> vf;
+    oq.rows(qf, qt * AT);
+    f32x4 acc[D / 16];
+#pragma unroll
+    for (int i = 0; i < D / 16; i++) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;
+    const float scale = 1.0f / sqrtf((float)D);
+    if (wave <= qt) { ok.rows(kf, wave * AT); ov.cols(vf, wave * AT); }
+    for (int t = wave; t <= qt; t += AW) {
+        f32x4 z = dot_tiles<D>(kf, qf) * scale;   // row = key, column = query
+        if (t + AW <= qt) ok.rows(kf, (t + AW) * AT);
+        if (t == qt)
+#pragma unroll
+            for (int r = 0; r < 4; r++)
+                if (4 * g + r > (lane & 15)) z[r] = -INFINITY;
+        const float mn = fmaxf(m, col_max(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]))));
+        const float ref = mn == -INFINITY ? 0.f : mn;   // no finite score yet: all weights are zero, not NaN
+        const float alpha = expf(m - ref);
+        f32x4 p;
+#pragma unroll
+        for (int r = 0; r < 4; r++) p[r] = expf(z[r] - ref);
+        l = l * alpha + col_sum((p[0] + p[1]) + (p[2] + p[3]));
+#pragma unroll
+        for (int i = 0; i < D / 16; i++) acc[i] *= alpha;
+        if (t == qt && !all_finite<D>(vf)) add_cols_masked<D, true>(acc, ov, t * AT, p);
+        else add_cols<D>(acc, vf, p);
+        if (t + AW <= qt) ov.cols(vf, (t + AW) * AT);
         m = mn;
     }
-    float* orow = o + ((size_t)b * S + s) * A + h * d;
-    if (lane < d) orow[lane] = acc0 / l;
-    if (lane + WAVE < d) orow[lane + WAVE] = acc1 / l;
-    if (lane == 0) lse[((size_t)b * nh + h) * S + s] = m + logf(l);
+    Merge<D>::put(buf, wave, acc);
+    if (g == 0) { ms[wave][lane] = m; ls[wave][lane] = l; }
+    __syncthreads();
+    const int column = threadIdx.x >> 4, s = qt * AT + column;
+    if (s >= S) return;
+    float M = ms[0][column], f[AW], L = 0.f;
+#pragma unroll
+    for (int w = 1; w < AW; w++) M = fmaxf(M, ms[w][column]);
+#pragma unroll
+    for (int w = 0; w < AW; w++) {
+        f[w] = ms[w][column] == -INFINITY ? 0.f : expf(ms[w][column] - M);
+        L += f[w] * ls[w][column];
+    }
+    float* orow = o + ((size_t)b * S + s) * A + h * D;
+    for (int c = (threadIdx.x & 15) * 4; c < D; c += 64) {
+        f32x4 v = Merge<D>::get(buf, 0, column, c) * f[0];
+#pragma unroll
+        for (int w = 1; w < AW; w++) v += Merge<D>::get(buf, w, column, c) * f[w];
+        *reinterpret_cast<f32x4*>(orow + c) = v / L;
+    }
+    if ((threadIdx.x & 15) == 0) lse[((size_t)b * nh + h) * S + s] = M + logf(L);
 }
 
-// Per query row: D = <do, o>, and dq = sum_t dZ[s,t] k[t] / sqrt(d).
-__global__ __launch_bounds__(AW* WAVE) void k_attn_f32_bwd_q(const float* __restrict__ qkv, int ld,
-                                                             const float* __restrict__ o, const float* __restrict__ dout,
-                                                             const float* __restrict__ lse, float* __restrict__ dvec,
-                                                             float* __restrict__ dqkv, int B, int S, int nh, int nkv, int d) {
-    __shared__ float qs[AW][128];
-    __shared__ float dos[AW][128];
-    const int wv = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
-    const long w = (long)blockIdx.x * AW + wv;
-    if (w >= (long)B * nh * S) return;
-    const int s = (int)(w % S), h = (int)((w / S) % nh), b = (int)(w / ((long)S * nh));
-    const int A = nh * d;
-    const size_t tok = (size_t)b * S + s;
-    const float* qrow = qkv + tok * ld + h * d;
-    const float* kb = qkv + (size_t)b * S * ld + A + (h / (nh / nkv)) * d;
-    const float* vb = kb + nkv * d;
-    const float* dorow = dout + tok * A + h * d;
-    const float* orow = o + tok * A + h * d;
-    float dd = 0.f;
-    for (int i = lane; i < d; i += WAVE) {
-        qs[wv][i] = qrow[i];
-        const float g = dorow[i];
-        dos[wv][i] = g;
-        dd = fmaf(g, orow[i], dd);
+// Per 16 queries: delta = <do, o>, and dq = sum_t dZ[s,t] k[t] / sqrt(d).
+template <int D>
+__global__ __launch_bounds__(AW* WAVE, 2) void k_attn_f32_bwd_q(const float* __restrict__ qkv, int ld,
+                                                                const float* __restrict__ o, const float* __restrict__ dout,
+                                                                const float* __restrict__ lse, float* __restrict__ dvec,
+                                                                float* __restrict__ dqkv, int B, int S, int nh, int nkv,
+                                                                const float* __restrict__ table, int table_seq) {
+    __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4;
+    const int nhb = nh * B, tiles = (S + AT - 1) / AT;
+    const int qt = tiles - 1 - (int)blockIdx.x / nhb, h = (blockIdx.x % nhb) % nh, b = (blockIdx.x % nhb) / nh;
+    const int A = nh * D, kcol = A + (h / (nh / nkv)) * D;
+    const size_t extent = (size_t)B * S * ld, row0 = (size_t)b * S * ld;
+    const size_t extent_o = (size_t)B * S * A, row0_o = (size_t)b * S * A;
+    const Operand oq = operand(qkv, extent, row0 + h * D, ld, S), ok = operand(qkv, extent, row0 + kcol, ld, S),
+                  ov = operand(qkv, extent, row0 + kcol + nkv * D, ld, S);
+    const Operand od = operand(dout, extent_o, row0_o + h * D, A, S), oo = operand(o, extent_o, row0_o + h * D, A, S);
+    RowsF<D> qf, df, kf, vf;
+    ColsF<D> kc;
+    od.rows(df, qt * AT);
+    oo.rows(kf, qt * AT);
+    oq.rows(qf, qt * AT);
+    float delta = 0.f;
+#pragma unroll
+    for (int j = 0; j < D / 16; j++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) delta = fmaf(df.v[j][e], kf.v[j][e], delta);
+    delta = col_sum(delta);
+    const int s = qt * AT + (lane & 15);
+    const size_t at_s = ((size_t)b * nh + h) * S + s;
+    const float L = s < S ? lse[at_s] : 0.f;
+    if (wave == 0 && g == 0 && s < S) dvec[at_s] = delta;
+    const float scale = 1.0f / sqrtf((float)D);
+    f32x4 acc[D / 16];
+#pragma unroll
+    for (int i = 0; i < D / 16; i++) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (wave <= qt) { ok.rows(kf, wave * AT); ov.rows(vf, wave * AT); ok.cols(kc, wave * AT); }
+    for (int t = wave; t <= qt; t += AW) {
+        const f32x4 z = dot_tiles<D>(kf, qf) * scale;   // row = key, column = query
+        const bool more = t + AW <= qt;
+        if (more) ok.rows(kf, (t + AW) * AT);
+        const f32x4 dp = dot_tiles<D>(vf, df);
+        if (more) ov.rows(vf, (t + AW) * AT);
+        f32x4 dz;
+#pragma unroll
+        for (int r = 0; r < 4; r++) dz[r] = t == qt && 4 * g + r > (lane & 15) ? 0.f : expf(z[r] - L) * (dp[r] - delta);
+        if (t == qt && !all_finite<D>(kc)) add_cols_masked<D, true>(acc, ok, t * AT, dz);
+        else add_cols<D>(acc, kc, dz);
+        if (more) ok.cols(kc, (t + AW) * AT);
     }
-    const float D = wave_sum(dd);
-    __builtin_amdgcn_wave_barrier();
-    const float L = lse[((size_t)b * nh + h) * S + s];
-    if (lane == 0) dvec[((size_t)b * nh + h) * S + s] = D;
-    const float scale = 1.0f / sqrtf((float)d);
-    float acc0 = 0.f, acc1 = 0.f;
-    for (int t0 = 0; t0 <= s; t0 += WAVE) {
-        const int t = t0 + lane;
-        float dz = 0.f;
-        if (t <= s) {
-            const float p = expf(dot_row(qs[wv], kb + (size_t)t * ld, d) * scale - L);
-            const float dp = dot_row(dos[wv], vb + (size_t)t * ld, d);
-            dz = p * (dp - D);
-        }
-        const int nk = min(WAVE, s - t0 + 1);
-        for (int j = 0; j < nk; j++) {
-            const float zj = __shfl(dz, j, WAVE);
-            const float* kr = kb + (size_t)(t0 + j) * ld;
-            if (lane < d) acc0 = fmaf(zj, kr[lane], acc0);
-            if (lane + WAVE < d) acc1 = fmaf(zj, kr[lane + WAVE], acc1);
-        }
-    }
-    float* dq = dqkv + tok * ld + h * d;
-    if (lane < d) dq[lane] = acc0 * scale;
-    if (lane + WAVE < d) dq[lane + WAVE] = acc1 * scale;
+    Merge<D>::put(buf, wave, acc);
+    __syncthreads();
+    Merge<D>::write(buf, dqkv + ((size_t)b * S + qt * AT) * ld + h * D, ld, qt * AT, S, scale, table, table_seq);
 }
 
-// Per key row t of key/value head hk: dv[t] = sum over its query heads and s>=t of P[s,t] do[s];
-// dk[t] = the same sum of dZ[s,t] q[s] / sqrt(d).
-__global__ __launch_bounds__(AW* WAVE) void k_attn_f32_bwd_kv(const float* __restrict__ qkv, int ld,
-                                                              const float* __restrict__ dout, const float* __restrict__ lse,
-                                                              const float* __restrict__ dvec, float* __restrict__ dqkv,
-                                                              int B, int S, int nh, int nkv, int d) {
-    __shared__ float ks[AW][128];
-    __shared__ float vs[AW][128];
-    const int wv = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
-    const long w = (long)blockIdx.x * AW + wv;
-    if (w >= (long)B * nkv * S) return;
-    const int t = (int)(w % S), hk = (int)((w / S) % nkv), b = (int)(w / ((long)S * nkv));
-    const int A = nh * d, G = nh / nkv;
-    const size_t tok = (size_t)b * S + t;
-    const float* krow = qkv + tok * ld + A + hk * d;
-    const float* vrow = krow + nkv * d;
-    for (int i = lane; i < d; i += WAVE) { ks[wv][i] = krow[i]; vs[wv][i] = vrow[i]; }
-    __builtin_amdgcn_wave_barrier();
-    const float scale = 1.0f / sqrtf((float)d);
-    float dk0 = 0.f, dk1 = 0.f, dv0 = 0.f, dv1 = 0.f;
-    for (int g = 0; g < G; g++) {
-        const int h = hk * G + g;
-        const float* qb = qkv + (size_t)b * S * ld + h * d;
-        const float* dob = dout + (size_t)b * S * A + h * d;
-        const float* Lb = lse + ((size_t)b * nh + h) * S;
-        const float* Db = dvec + ((size_t)b * nh + h) * S;
-        for (int s0 = t; s0 < S; s0 += WAVE) {
-            const int s = s0 + lane;
-            float p = 0.f, dz = 0.f;
-            if (s < S) {
-                p = expf(dot_row(ks[wv], qb + (size_t)s * ld, d) * scale - Lb[s]);
-                const float dp = dot_row(vs[wv], dob + (size_t)s * A, d);
-                dz = p * (dp - Db[s]);
-            }
-            const int nq = min(WAVE, S - s0);
-            for (int j = 0; j < nq; j++) {
-                const float pj = __shfl(p, j, WAVE), zj = __shfl(dz, j, WAVE);
-                const float* qr = qb + (size_t)(s0 + j) * ld;
-                const float* dr = dob + (size_t)(s0 + j) * A;
-                if (lane < d) { dv0 = fmaf(pj, dr[lane], dv0); dk0 = fmaf(zj, qr[lane], dk0); }
-                if (lane + WAVE < d) { dv1 = fmaf(pj, dr[lane + WAVE], dv1); dk1 = fmaf(zj, qr[lane + WAVE], dk1); }
-            }
-        }
+// Per 16 keys of one key/value head: dv[t] = sum over its query heads and s >= t of P[s,t] do[s]; dk[t] = the same sum
+// of dZ[s,t] q[s] / sqrt(d).  With parts > 1 the query heads are dealt out to `parts` workgroups, whose sums go to
+// partial[part][token][dk | dv of every key/value head] and are finished by k_attn_f32_kv_reduce.
+template <int D>
+__global__ __launch_bounds__(AW* WAVE, 1) void k_attn_f32_bwd_kv(const float* __restrict__ qkv, int ld,
+                                                                 const float* __restrict__ dout, const float* __restrict__ lse,
+                                                                 const float* __restrict__ dvec, float* __restrict__ dqkv,
+                                                                 float* __restrict__ partial, int parts, int B, int S, int nh, int nkv,
+                                                                 const float* __restrict__ table, int table_seq) {
+    __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4;
+    const int tiles = (S + AT - 1) / AT, jobs = B * nkv * parts;
+    const int kt = (int)blockIdx.x / jobs, rest = blockIdx.x % jobs;   // the first keys see the most queries: longest first
+    const int part = rest % parts, hk = (rest / parts) % nkv, b = rest / (parts * nkv);
+    const int A = nh * D, kcol = A + hk * D, heads = nh / nkv / parts, h0 = hk * (nh / nkv) + part * heads;
+    const size_t extent = (size_t)B * S * ld, row0 = (size_t)b * S * ld;
+    const size_t extent_o = (size_t)B * S * A, row0_o = (size_t)b * S * A;
+    Operand oq = operand(qkv, extent, row0 + (size_t)h0 * D, ld, S), od = operand(dout, extent_o, row0_o + (size_t)h0 * D, A, S);
+    const uint32_t base_q = oq.base, base_d = od.base;
+    RowsF<D> kf, vf, qf, df;
+    ColsF<D> qc, dc;
+    operand(qkv, extent, row0 + kcol, ld, S).rows(kf, kt * AT);
+    operand(qkv, extent, row0 + kcol + nkv * D, ld, S).rows(vf, kt * AT);
+    f32x4 dk[D / 16], dv[D / 16];
+#pragma unroll
+    for (int i = 0; i < D / 16; i++) dk[i] = dv[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const float scale = 1.0f / sqrtf((float)D);
+    const int per_head = tiles - kt, n = heads * per_head;   // (head, query tile) pairs, dealt out to the waves in turn
+    auto point = [&](int i) {   // the operands' head of pair i; its query tile
+        const int hd = i / per_head;
+        oq.base = base_q + (uint32_t)(hd * D) * 4u;
+        od.base = base_d + (uint32_t)(hd * D) * 4u;
+        return kt + i - hd * per_head;
+    };
+    if (wave < n) {
+        const int t = point(wave);
+        oq.rows(qf, t * AT); od.rows(df, t * AT); od.cols(dc, t * AT); oq.cols(qc, t * AT);
     }
-    float* dk = dqkv + tok * ld + A + hk * d;
-    float* dv = dk + nkv * d;
-    if (lane < d) { dk[lane] = dk0 * scale; dv[lane] = dv0; }
-    if (lane + WAVE < d) { dk[lane + WAVE] = dk1 * scale; dv[lane + WAVE] = dv1; }
+    for (int i = wave; i < n; i += AW) {
+        const int qt = point(i), hd = h0 + i / per_head;
+        const Operand cq = oq, cd = od;
+        const size_t stat = ((size_t)b * nh + hd) * S;
+        float L[4], dl[4];
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int s = min(qt * AT + 4 * g + r, S - 1);
+            L[r] = lse[stat + s];
+            dl[r] = dvec[stat + s];
+        }
+        const bool more = i + AW < n;
+        const int nt = more ? point(i + AW) : 0;
+        const f32x4 z = dot_tiles<D>(qf, kf) * scale;   // row = query, column = key
+        if (more) oq.rows(qf, nt * AT);
+        const f32x4 dp = dot_tiles<D>(df, vf);
+        if (more) od.rows(df, nt * AT);
+        f32x4 p, dz;
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const bool off = (qt == kt && 4 * g + r < (lane & 15)) || qt * AT + 4 * g + r >= S;
+            p[r] = off ? 0.f : expf(z[r] - L[r]);
+            dz[r] = off ? 0.f : p[r] * (dp[r] - dl[r]);
+        }
+        if (qt == kt && !all_finite<D>(dc)) add_cols_masked<D, false>(dv, cd, qt * AT, p);
+        else add_cols<D>(dv, dc, p);
+        if (more) od.cols(dc, nt * AT);
+        if (qt == kt && !all_finite<D>(qc)) add_cols_masked<D, false>(dk, cq, qt * AT, dz);
+        else add_cols<D>(dk, qc, dz);
+        if (more) oq.cols(qc, nt * AT);
+    }
+    const size_t tok = (size_t)b * S + kt * AT;
+    float* out = parts > 1 ? partial + ((size_t)part * B * S + tok) * (2 * nkv * D) + hk * D : dqkv + tok * ld + kcol;
+    const int ldo = parts > 1 ? 2 * nkv * D : ld;
+    Merge<D>::put(buf, wave, dk);
+    __syncthreads();
+    Merge<D>::write(buf, out, ldo, kt * AT, S, scale, parts > 1 ? nullptr : table, table_seq);
+    __syncthreads();
+    Merge<D>::put(buf, wave, dv);
+    __syncthreads();
+    Merge<D>::write(buf, out + nkv * D, ldo, kt * AT, S, 1.0f, nullptr, 0);
+}
+
+// dk | dv of a token = the sum of its `parts` partial rows in order, dk rotated back.  A thread owns 4 channel pairs.
+template <int D>
+__global__ __launch_bounds__(256) void k_attn_f32_kv_reduce(const float* __restrict__ partial, int parts, float* __restrict__ dqkv, int ld,
+                                                            int T, int S, int nh, int nkv, const float* __restrict__ table, int table_seq) {
+    constexpr int HALF = D / 2, VPH = HALF / 4;
+    const int per_row = 2 * nkv * VPH;
+    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= (long)T * per_row) return;
+    const int t = (int)(idx / per_row), w = (int)(idx % per_row), head = w / VPH, c = (w % VPH) * 4, pos = t % S;
+    const int width = 2 * nkv * D;
+    const float* p = partial + (size_t)t * width + head * D + c;
+    f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+    for (int i = 0; i < parts; i++, p += (size_t)T * width) {
+        a += *reinterpret_cast<const f32x4*>(p);
+        b += *reinterpret_cast<const f32x4*>(p + HALF);
+    }
+    if (table && head < nkv) {
+        const f32x4 cs = *reinterpret_cast<const f32x4*>(table + (size_t)pos * HALF + c);
+        const f32x4 sn = *reinterpret_cast<const f32x4*>(table + (size_t)(table_seq + pos) * HALF + c);
+        const f32x4 ra = a * cs + b * sn, rb = b * cs - a * sn;
+        a = ra; b = rb;
+    }
+    float* out = dqkv + (size_t)t * ld + nh * D + head * D + c;
+    *reinterpret_cast<f32x4*>(out) = a;
+    *reinterpret_cast<f32x4*>(out + HALF) = b;
+}
+
+template <int D>
+static hipError_t launch_bwd(const float* qkv, int ld, const float* o, const float* dout, const float* lse, float* dvec, float* dqkv,
+                             float* scratch, size_t scratch_bytes, int B, int S, int nh, int nkv, const float* table, int table_seq,
+                             hipStream_t st) {
+    const int tiles = (S + AT - 1) / AT, G = nh / nkv;
+    // The query heads that share a key/value head run one after the other in a workgroup, unless that leaves fewer than
+    // two workgroups per CU and the scratch holds their partial sums.  dq, dk and dv together, kept together -> dealt
+    // out: 8 heads of 128 on 2, 700 tokens, 202 -> 92 us; 350 tokens 101 -> 50; 16 heads of 64 on 2, 2 x 1024 tokens,
+    // 349 -> 261; 4 heads of 64 on 1, 128 tokens, 27 -> 30 (the reduction's launch).
+    int parts = 1;
+    const size_t part_bytes = (size_t)B * S * 2 * nkv * D * sizeof(float);
+    for (int p = 2; p <= G; p++)
+        if (G % p == 0 && (long)tiles * B * nkv * parts < 512 && p * part_bytes <= scratch_bytes) parts = p;
+    k_attn_f32_bwd_q<D><<<tiles * B * nh, AW * WAVE, 0, st>>>(qkv, ld, o, dout, lse, dvec, dqkv, B, S, nh, nkv, table, table_seq);
+    k_attn_f32_bwd_kv<D><<<tiles * B * nkv * parts, AW * WAVE, 0, st>>>(qkv, ld, dout, lse, dvec, dqkv, scratch, parts, B, S, nh, nkv,
+                                                                       table, table_seq);
+    if (parts > 1) {
+        const long n = (long)B * S * 2 * nkv * (D / 8);
+        k_attn_f32_kv_reduce<D><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(scratch, parts, dqkv, ld, B * S, S, nh, nkv, table, table_seq);
+    }
+    return hipGetLastError();
 }
 
 hipError_t attn_f32_fwd(const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, hipStream_t st) {
-    const long rows = (long)B * nh * S;
-    k_attn_f32_fwd<<<(unsigned)((rows + AW - 1) / AW), AW * WAVE, 0, st>>>((const float*)qkv, ld, (float*)o, lse, B, S, nh, nkv, d);
+    const int grid = (S + AT - 1) / AT * B * nh;
+    if (d == 64) k_attn_f32_fwd<64><<<grid, AW * WAVE, 0, st>>>((const float*)qkv, ld, (float*)o, lse, B, S, nh, nkv);
+    else if (d == 128) k_attn_f32_fwd<128><<<grid, AW * WAVE, 0, st>>>((const float*)qkv, ld, (float*)o, lse, B, S, nh, nkv);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
 hipError_t attn_f32_bwd(const void* qkv, int ld, const void* o, const void* dout, const float* lse, float* dvec,
-                        void* dqkv, int B, int S, int nh, int nkv, int d, hipStream_t st) {
-    const long rows = (long)B * nh * S, rows_kv = (long)B * nkv * S;
-    k_attn_f32_bwd_q<<<(unsigned)((rows + AW - 1) / AW), AW * WAVE, 0, st>>>((const float*)qkv, ld, (const float*)o, (const float*)dout,
-                                                                             lse, dvec, (float*)dqkv, B, S, nh, nkv, d);
-    k_attn_f32_bwd_kv<<<(unsigned)((rows_kv + AW - 1) / AW), AW * WAVE, 0, st>>>((const float*)qkv, ld, (const float*)dout, lse, dvec,
-                                                                                 (float*)dqkv, B, S, nh, nkv, d);
-    return hipGetLastError();
+                        void* dqkv, float* scratch, size_t scratch_bytes, int B, int S, int nh, int nkv, int d,
+                        const float* table, int table_seq, hipStream_t st) {
+    if (d == 64) return launch_bwd<64>((const float*)qkv, ld, (const float*)o, (const float*)dout, lse, dvec, (float*)dqkv, scratch,
+                                       scratch_bytes, B, S, nh, nkv, table, table_seq, st);
+    if (d == 128) return launch_bwd<128>((const float*)qkv, ld, (const float*)o, (const float*)dout, lse, dvec, (float*)dqkv, scratch,
+                                         scratch_bytes, B, S, nh, nkv, table, table_seq, st);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace hh

@@ -62,13 +62,14 @@ hipError_t swiglu_bwd(int dtype, const void* dm, const void* gu, void* dgu, void
 hipError_t attn_fwd(int dtype, const void* qkv, int ld, void* o, float* lse,
                     int B, int S, int nh, int nkv, int d, hipStream_t st);
 // dqkv [T, ld] receives dq | dk | dv in the same layout.  dvec: scratch [B, nh, S] floats.  scratch: device
-// memory of attn_bwd_scratch_bytes() bytes (partial dK, dV sums when the query heads that share a key/value head
-// are spread over several workgroups; may be null when that size is 0).  rope_table (as for rope(), rope_seq >= S;
+// memory of scratch_bytes, at least attn_bwd_scratch_bytes() (partial dK, dV sums when the query heads that share a
+// key/value head are spread over several workgroups; may be null when it has no bytes; the fp32 path needs none and
+// spreads the heads as far as what it is given reaches).  rope_table (as for rope(), rope_seq >= S;
 // null: none): q and k were rotated before the forward call, and dq, dk are written as gradients of the
 // unrotated q, k (the backward rotation applied before the one rounding to the storage type).
 size_t attn_bwd_scratch_bytes(int dtype, int B, int S, int nh, int nkv, int d);
 hipError_t attn_bwd(int dtype, const void* qkv, int ld, const void* o, const void* dout, const float* lse,
-                    float* dvec, void* dqkv, void* scratch, int B, int S, int nh, int nkv, int d,
+                    float* dvec, void* dqkv, void* scratch, size_t scratch_bytes, int B, int S, int nh, int nkv, int d,
                     const float* rope_table, int rope_seq, hipStream_t st);
 
 }  // namespace hh
