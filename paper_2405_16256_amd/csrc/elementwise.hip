@@ -2,6 +2,8 @@
 // residual gradient folded in), rotary embedding, SwiGLU forward/backward and
 // the column-sum reduction for the gain gradients.  All global accesses are
 // 16-byte vectors along the contiguous feature dimension; math is fp32.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -73,15 +75,14 @@ __global__ __launch_bounds__(TPB) void k_rmsnorm_fwd(const T* __restrict__ x, co
     }
 }
 
-// One workgroup walks `rpb` consecutive rows.  Column j is always handled by the
-// same thread, so the per-column sums of dxn*u live in LDS without atomics.
+// RMSNorm backward, rows too long for registers: one workgroup walks `rpb` consecutive rows and reads each twice.
+// Column j is always handled by the same thread, so the per-column sums of dxn*u live in LDS without atomics.
 template <typename T>
 __global__ __launch_bounds__(TPB) void k_rmsnorm_bwd(const T* __restrict__ dxn, const T* __restrict__ x,
                                                      const float* __restrict__ r, const T* __restrict__ g,
                                                      const T* __restrict__ dres, T* __restrict__ dx,
                                                      float* __restrict__ partial, int T_rows, int H, int rpb) {
     constexpr int V = Vec<T>::N;
-    typedef typename Vec<T>::Raw Raw;
     extern __shared__ float colacc[];  // [H]
     __shared__ float red[NWAVES];
     for (int c = threadIdx.x * V; c < H; c += TPB * V)
@@ -90,70 +91,32 @@ __global__ __launch_bounds__(TPB) void k_rmsnorm_bwd(const T* __restrict__ dxn, 
     const int row0 = blockIdx.x * rpb;
     const int row1 = min(T_rows, row0 + rpb);
     const float invH = 1.0f / (float)H;
-    const bool cached = H <= RC * TPB * V;
     for (int row = row0; row < row1; row++) {
         const size_t base = (size_t)row * H;
         const float rs = r[row];
         float s = 0.f;
-        if (cached) {
-            Raw kd[RC], kx[RC];
+        for (int c = threadIdx.x * V; c < H; c += TPB * V) {
+            float d[V], xx[V], gg[V];
+            Vec<T>::load(dxn + base + c, d);
+            Vec<T>::load(x + base + c, xx);
+            Vec<T>::load(g + c, gg);
 #pragma unroll
-            for (int i = 0; i < RC; i++) {
-                const int c = (threadIdx.x + i * TPB) * V;
-                if (c < H) {
-                    kd[i] = Vec<T>::raw(dxn + base + c);
-                    kx[i] = Vec<T>::raw(x + base + c);
-                    float d[V], xx[V], gg[V];
-                    Vec<T>::widen(kd[i], d);
-                    Vec<T>::widen(kx[i], xx);
-                    Vec<T>::load(g + c, gg);
+            for (int e = 0; e < V; e++) s += d[e] * gg[e] * xx[e];
+        }
+        const float c1 = block_sum<NWAVES>(s, red) * rs * invH;  // mean_j(w_j u_j)
+        for (int c = threadIdx.x * V; c < H; c += TPB * V) {
+            float d[V], xx[V], gg[V], rr[V], o[V];
+            Vec<T>::load(dxn + base + c, d);
+            Vec<T>::load(x + base + c, xx);
+            Vec<T>::load(g + c, gg);
+            Vec<T>::load(dres + base + c, rr);
 #pragma unroll
-                    for (int e = 0; e < V; e++) s += d[e] * gg[e] * xx[e];
-                }
+            for (int e = 0; e < V; e++) {
+                const float u = xx[e] * rs;
+                colacc[c + e] += d[e] * u;
+                o[e] = rr[e] + rs * (d[e] * gg[e] - u * c1);
             }
-            const float c1 = block_sum<NWAVES>(s, red) * rs * invH;  // mean_j(w_j u_j)
-#pragma unroll
-            for (int i = 0; i < RC; i++) {
-                const int c = (threadIdx.x + i * TPB) * V;
-                if (c < H) {
-                    float d[V], xx[V], gg[V], rr[V], o[V];
-                    Vec<T>::widen(kd[i], d);
-                    Vec<T>::widen(kx[i], xx);
-                    Vec<T>::load(g + c, gg);
-                    Vec<T>::load(dres + base + c, rr);
-#pragma unroll
-                    for (int e = 0; e < V; e++) {
-                        const float u = xx[e] * rs;
-                        colacc[c + e] += d[e] * u;
-                        o[e] = rr[e] + rs * (d[e] * gg[e] - u * c1);
-                    }
-                    Vec<T>::store(dx + base + c, o);
-                }
-            }
-        } else {
-            for (int c = threadIdx.x * V; c < H; c += TPB * V) {
-                float d[V], xx[V], gg[V];
-                Vec<T>::load(dxn + base + c, d);
-                Vec<T>::load(x + base + c, xx);
-                Vec<T>::load(g + c, gg);
-#pragma unroll
-                for (int e = 0; e < V; e++) s += d[e] * gg[e] * xx[e];
-            }
-            const float c1 = block_sum<NWAVES>(s, red) * rs * invH;
-            for (int c = threadIdx.x * V; c < H; c += TPB * V) {
-                float d[V], xx[V], gg[V], rr[V], o[V];
-                Vec<T>::load(dxn + base + c, d);
-                Vec<T>::load(x + base + c, xx);
-                Vec<T>::load(g + c, gg);
-                Vec<T>::load(dres + base + c, rr);
-#pragma unroll
-                for (int e = 0; e < V; e++) {
-                    const float u = xx[e] * rs;
-                    colacc[c + e] += d[e] * u;
-                    o[e] = rr[e] + rs * (d[e] * gg[e] - u * c1);
-                }
-                Vec<T>::store(dx + base + c, o);
-            }
+            Vec<T>::store(dx + base + c, o);
         }
     }
     float* out = partial + (size_t)blockIdx.x * H;
@@ -162,29 +125,110 @@ __global__ __launch_bounds__(TPB) void k_rmsnorm_bwd(const T* __restrict__ dxn, 
         for (int e = 0; e < V; e++) out[c + e] = colacc[c + e];
 }
 
-// out[j] (=|+=) sum_b partial[b][j].  A workgroup covers 256 columns (one float4 per thread column
-// group) with 4 row groups that are combined through LDS in a fixed order.
-__global__ __launch_bounds__(TPB) void k_colsum_reduce(const float* __restrict__ partial, int nblk, int H,
-                                                       float* __restrict__ out, int accumulate) {
-    __shared__ float4 red[NWAVES][WAVE];
-    const int cx = threadIdx.x % WAVE, ry = threadIdx.x / WAVE;
-    const int col = (blockIdx.x * WAVE + cx) * 4;
+// RMSNorm backward, short rows (at most NV * 64 * V elements): one wave per row, no barrier until the end; a lane's
+// columns are the same in every row, so their sums stay in registers and the waves' sums meet in LDS once, in a fixed
+// order.  Bound by latency: one row at a time per workgroup of 256 threads, most of them idle, took 9.6-11.3 us for
+// 128 rows of 256 and 20.8 us for 2200 rows of 512 (bf16); this kernel with one to nine rows a workgroup takes
+// 3.0-4.2 and 4.8 us.
+constexpr int RW = 8;   // waves per workgroup
+template <typename T, int NV>
+__global__ __launch_bounds__(RW * WAVE) void k_rmsnorm_bwd_wave(const T* __restrict__ dxn, const T* __restrict__ x,
+                                                                const float* __restrict__ r, const T* __restrict__ g,
+                                                                const T* __restrict__ dres, T* __restrict__ dx,
+                                                                float* __restrict__ partial, int T_rows, int H, int rpb) {
+    constexpr int V = Vec<T>::N;
+    extern __shared__ float colsum[];  // [RW][H]
+    const int wave = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
+    const int row0 = blockIdx.x * rpb, row1 = min(T_rows, row0 + rpb);
+    const float invH = 1.0f / (float)H;
+    float gg[NV][V], acc[NV][V];
+#pragma unroll
+    for (int i = 0; i < NV; i++) {
+        const int c = (lane + i * WAVE) * V;
+        if (c < H) Vec<T>::load(g + c, gg[i]);
+#pragma unroll
+        for (int e = 0; e < V; e++) acc[i][e] = 0.f;
+    }
+    for (int row = row0 + wave; row < row1; row += RW) {
+        const size_t base = (size_t)row * H;
+        const float rs = r[row];
+        float d[NV][V], xx[NV][V], rr[NV][V];
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < NV; i++) {
+            const int c = (lane + i * WAVE) * V;
+            if (c < H) {
+                Vec<T>::load(dxn + base + c, d[i]);
+                Vec<T>::load(x + base + c, xx[i]);
+                Vec<T>::load(dres + base + c, rr[i]);
+#pragma unroll
+                for (int e = 0; e < V; e++) s += d[i][e] * gg[i][e] * xx[i][e];
+            }
+        }
+        const float c1 = wave_sum(s) * rs * invH;  // mean_j(w_j u_j)
+#pragma unroll
+        for (int i = 0; i < NV; i++) {
+            const int c = (lane + i * WAVE) * V;
+            if (c < H) {
+                float o[V];
+#pragma unroll
+                for (int e = 0; e < V; e++) {
+                    const float u = xx[i][e] * rs;
+                    acc[i][e] += d[i][e] * u;
+                    o[e] = rr[i][e] + rs * (d[i][e] * gg[i][e] - u * c1);
+                }
+                Vec<T>::store(dx + base + c, o);
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NV; i++) {
+        const int c = (lane + i * WAVE) * V;
+        if (c < H)
+#pragma unroll
+            for (int e = 0; e < V; e += 4)
+                *reinterpret_cast<float4*>(colsum + wave * H + c + e) = make_float4(acc[i][e], acc[i][e + 1], acc[i][e + 2], acc[i][e + 3]);
+    }
+    __syncthreads();
+    const int waves = min(RW, row1 - row0);   // waves that had a row
+    for (int c = threadIdx.x; c < H; c += RW * WAVE) {
+        float s = 0.f;
+        for (int w = 0; w < waves; w++) s += colsum[w * H + c];
+        partial[(size_t)blockIdx.x * H + c] = s;
+    }
+}
+
+// out[j] (=|+=) sum_b partial[b][j] of one or two gain gradients (blockIdx.y).  A workgroup covers 64 columns (a float4
+// per lane, 16 lanes a row) with 64 row groups, combined by shuffles and through LDS in a fixed order: at most 256
+// partial rows are then one batch of loads per thread, and a row of 4096 is spread over 64 CUs.  Both sums at 256 x 12288
+// and at 254 x 4096: 12.8 and 11.8 us as two launches of 256 columns a workgroup, 7.6 and 6.0 us as this one.
+constexpr int CSW = 16;   // waves of a workgroup
+__global__ __launch_bounds__(CSW * WAVE) void k_colsum_reduce(ColSum a, ColSum b, int H, int accumulate) {
+    __shared__ float4 red[CSW][16];
+    const ColSum& j = blockIdx.y ? b : a;
+    const int cx = threadIdx.x % 16, wave = threadIdx.x / WAVE;
+    const int col = (blockIdx.x * 16 + cx) * 4;
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
     if (col < H) {
-        const float* p = partial + col;
-#pragma unroll 8
-        for (int b = ry; b < nblk; b += NWAVES) {
-            const float4 v = *reinterpret_cast<const float4*>(p + (size_t)b * H);
+        const float* p = j.partial + col;
+#pragma unroll 4
+        for (int i = threadIdx.x / 16; i < j.rows; i += CSW * WAVE / 16) {
+            const float4 v = *reinterpret_cast<const float4*>(p + (size_t)i * H);
             s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
         }
     }
-    red[ry][cx] = s;
+#pragma unroll
+    for (int o = 16; o < WAVE; o *= 2) {
+        s.x += __shfl_xor(s.x, o, WAVE); s.y += __shfl_xor(s.y, o, WAVE);
+        s.z += __shfl_xor(s.z, o, WAVE); s.w += __shfl_xor(s.w, o, WAVE);
+    }
+    if ((threadIdx.x & (WAVE - 1)) < 16) red[wave][cx] = s;
     __syncthreads();
-    if (ry == 0 && col < H) {
+    if (threadIdx.x < 16 && col < H) {
         float4 t = red[0][cx];
 #pragma unroll
-        for (int i = 1; i < NWAVES; i++) { t.x += red[i][cx].x; t.y += red[i][cx].y; t.z += red[i][cx].z; t.w += red[i][cx].w; }
-        float4* o = reinterpret_cast<float4*>(out + col);
+        for (int i = 1; i < CSW; i++) { t.x += red[i][cx].x; t.y += red[i][cx].y; t.z += red[i][cx].z; t.w += red[i][cx].w; }
+        float4* o = reinterpret_cast<float4*>(j.out + col);
         if (accumulate) { const float4 old = *o; t.x += old.x; t.y += old.y; t.z += old.z; t.w += old.w; }
         *o = t;
     }
@@ -276,19 +320,19 @@ hipError_t rmsnorm_fwd(int dtype, const void* x, const void* g, void* xn, float*
     return hipGetLastError();
 }
 
-// Rows of exactly NV * TPB * V elements: the three input rows of row r + 1 are requested before row r is
+// Rows of up to NV * TPB * V elements (exactly that many unless GUARD): the three input rows of row r + 1 are requested before row r is
 // reduced and written, each in its own registers, so the memory queue never drains between rows.  The one
 // barrier per row waits for LDS only (a full workgroup fence would also wait for the loads in flight).
 __device__ __forceinline__ void keep_raw(uint4& v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
 __device__ __forceinline__ void keep_raw(float4& v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
 
-template <typename T, int NV>
+template <typename T, int NV, bool GUARD>
 __global__ __launch_bounds__(TPB, 2) void k_rmsnorm_bwd_rows(const T* __restrict__ dxn, const T* __restrict__ x,
                                                           const float* __restrict__ r, const T* __restrict__ g,
                                                           const T* __restrict__ dres, T* __restrict__ dx,
-                                                          float* __restrict__ partial, int T_rows, int rpb) {
+                                                          float* __restrict__ partial, int T_rows, int H_, int rpb) {
     constexpr int V = Vec<T>::N;
-    constexpr int H = NV * TPB * V;
+    const int H = GUARD ? H_ : NV * TPB * V;
     typedef typename Vec<T>::Raw Raw;
     extern __shared__ float colacc[];  // [H]
     __shared__ float red[2][NWAVES];
@@ -298,6 +342,7 @@ __global__ __launch_bounds__(TPB, 2) void k_rmsnorm_bwd_rows(const T* __restrict
 #pragma unroll
         for (int i = 0; i < NV; i++) {
             const int c = (threadIdx.x + i * TPB) * V;
+            if (GUARD && c >= H) break;
             w.d[i] = Vec<T>::raw(dxn + base + c);
             w.x[i] = Vec<T>::raw(x + base + c);
             w.res[i] = Vec<T>::raw(dres + base + c);
@@ -308,6 +353,7 @@ __global__ __launch_bounds__(TPB, 2) void k_rmsnorm_bwd_rows(const T* __restrict
 #pragma unroll
     for (int i = 0; i < NV; i++) {
         const int c = (threadIdx.x + i * TPB) * V;
+        if (GUARD && c >= H) break;
         gain[i] = Vec<T>::raw(g + c);
 #pragma unroll
         for (int e = 0; e < V; e++) colacc[c + e] = 0.f;   // only this thread ever touches these columns
@@ -320,6 +366,7 @@ __global__ __launch_bounds__(TPB, 2) void k_rmsnorm_bwd_rows(const T* __restrict
         float s = 0.f;
 #pragma unroll
         for (int i = 0; i < NV; i++) {
+            if (GUARD && (threadIdx.x + i * TPB) * V >= H) break;
             float d[V], xx[V], gg[V];
             Vec<T>::widen(w.d[i], d);
             Vec<T>::widen(w.x[i], xx);
@@ -346,6 +393,7 @@ __global__ __launch_bounds__(TPB, 2) void k_rmsnorm_bwd_rows(const T* __restrict
 #pragma unroll
         for (int i = 0; i < NV; i++) {
             const int c = (threadIdx.x + i * TPB) * V;
+            if (GUARD && c >= H) break;
             float d[V], xx[V], gg[V], rr[V], o[V];
             Vec<T>::widen(w.d[i], d);
             Vec<T>::widen(w.x[i], xx);
@@ -374,69 +422,77 @@ __global__ __launch_bounds__(TPB, 2) void k_rmsnorm_bwd_rows(const T* __restrict
 #pragma unroll
     for (int i = 0; i < NV; i++) {
         const int c = (threadIdx.x + i * TPB) * V;
+        if (GUARD && c >= H) break;
 #pragma unroll
         for (int e = 0; e < V; e++) partial[(size_t)blockIdx.x * H + c + e] = colacc[c + e];
     }
 }
 
+struct NormBwd {
+    const void* dxn; const void* x; const float* r; const void* g; const void* dres; void* dx; float* partial;
+    int T, H, rpb, nblk;
+};
+template <typename T, int NV, bool GUARD>
+static hipError_t launch_rows(const NormBwd& a, hipStream_t st) {
+    const int lds = a.H * (int)sizeof(float);   // at most 48 KB
+    k_rmsnorm_bwd_rows<T, NV, GUARD><<<a.nblk, TPB, lds, st>>>((const T*)a.dxn, (const T*)a.x, a.r, (const T*)a.g, (const T*)a.dres,
+                                                               (T*)a.dx, a.partial, a.T, a.H, a.rpb);
+    return hipGetLastError();
+}
 template <typename T, int NV>
-static hipError_t launch_rmsnorm_bwd_rows(const void* dxn, const void* x, const float* r, const void* g, const void* dres,
-                                          void* dx, float* partial, int T_rows, int rpb, int nblk, hipStream_t st) {
-    constexpr int lds = NV * TPB * Vec<T>::N * (int)sizeof(float);
-    static std::atomic<uint64_t> lds_ok{0};
-    const hipError_t e = allow_lds((const void*)k_rmsnorm_bwd_rows<T, NV>, lds, lds_ok);
-    if (e != hipSuccess) return e;
-    k_rmsnorm_bwd_rows<T, NV><<<nblk, TPB, lds, st>>>((const T*)dxn, (const T*)x, r, (const T*)g, (const T*)dres, (T*)dx,
-                                                      partial, T_rows, rpb);
+static hipError_t launch_wave(const NormBwd& a, hipStream_t st) {
+    const int lds = RW * a.H * (int)sizeof(float);   // at most 32 KB
+    k_rmsnorm_bwd_wave<T, NV><<<a.nblk, RW * WAVE, lds, st>>>((const T*)a.dxn, (const T*)a.x, a.r, (const T*)a.g, (const T*)a.dres,
+                                                              (T*)a.dx, a.partial, a.T, a.H, a.rpb);
     return hipGetLastError();
 }
 
-static inline int rms_rows_per_block(int T) {
-    int rpb = 8;
-    while ((T + rpb - 1) / rpb > 256) rpb *= 2;
-    return rpb;
+// Workgroups (= rows of `partial`) of rmsnorm_bwd: as few rows each as 256 of them leave, so that neither a short
+// batch nor a ragged one idles CUs (700 rows: 234 workgroups of 3, 3300 rows: 254 of 13), and no more of them than
+// `partial` has room for.
+static inline int rms_rows_per_block(int T, int H, size_t partial_bytes) {
+    const size_t room = partial_bytes / ((size_t)H * sizeof(float));
+    const int most = (int)std::max<size_t>(1, std::min<size_t>(256, room));
+    return (T + most - 1) / most;
 }
-int rmsnorm_bwd_blocks(int T) {
-    const int rpb = rms_rows_per_block(T);
+int rmsnorm_bwd_blocks(int T, int H, size_t partial_bytes) {
+    const int rpb = rms_rows_per_block(T, H, partial_bytes);
     return (T + rpb - 1) / rpb;
 }
 
-hipError_t rmsnorm_bwd(int dtype, const void* dxn, const void* x, const float* r, const void* g, const void* dres,
-                       void* dx, float* partial, int T, int H, hipStream_t st) {
-    const int rpb = rms_rows_per_block(T);
-    const int nblk = (T + rpb - 1) / rpb;
-    const size_t lds = (size_t)H * sizeof(float);
-    hipError_t e;
-    if (dtype == DT_BF16 && H % (TPB * 8) == 0 && H / (TPB * 8) <= RC) {
-        switch (H / (TPB * 8)) {   // row length as a compile-time multiple of the workgroup's 16-byte vectors
-            case 1: return launch_rmsnorm_bwd_rows<bf16_t, 1>(dxn, x, r, g, dres, dx, partial, T, rpb, nblk, st);
-            case 2: return launch_rmsnorm_bwd_rows<bf16_t, 2>(dxn, x, r, g, dres, dx, partial, T, rpb, nblk, st);
-            case 3: return launch_rmsnorm_bwd_rows<bf16_t, 3>(dxn, x, r, g, dres, dx, partial, T, rpb, nblk, st);
-            case 4: return launch_rmsnorm_bwd_rows<bf16_t, 4>(dxn, x, r, g, dres, dx, partial, T, rpb, nblk, st);
-            case 5: return launch_rmsnorm_bwd_rows<bf16_t, 5>(dxn, x, r, g, dres, dx, partial, T, rpb, nblk, st);
-            default: return launch_rmsnorm_bwd_rows<bf16_t, 6>(dxn, x, r, g, dres, dx, partial, T, rpb, nblk, st);
-        }
+template <typename T>
+static hipError_t rmsnorm_bwd_t(const NormBwd& a, hipStream_t st) {
+    constexpr int V = Vec<T>::N;
+    // a wave per row up to two vectors a lane, a workgroup per row beyond (four times the threads at work on a row)
+    if (a.H <= WAVE * V) return launch_wave<T, 1>(a, st);
+    if (a.H <= 2 * WAVE * V) return launch_wave<T, 2>(a, st);
+    const bool whole = a.H % (TPB * V) == 0;   // row length as a compile-time multiple of the workgroup's 16-byte vectors
+    switch ((a.H + TPB * V - 1) / (TPB * V)) {
+        case 1: return whole ? launch_rows<T, 1, false>(a, st) : launch_rows<T, 1, true>(a, st);
+        case 2: return whole ? launch_rows<T, 2, false>(a, st) : launch_rows<T, 2, true>(a, st);
+        case 3: return whole ? launch_rows<T, 3, false>(a, st) : launch_rows<T, 3, true>(a, st);
+        case 4: return whole ? launch_rows<T, 4, false>(a, st) : launch_rows<T, 4, true>(a, st);
+        case 5: return whole ? launch_rows<T, 5, false>(a, st) : launch_rows<T, 5, true>(a, st);
+        case 6: return whole ? launch_rows<T, 6, false>(a, st) : launch_rows<T, 6, true>(a, st);
     }
-    if (dtype == DT_BF16) {
-        if (lds > 48 * 1024) {
-            e = hipFuncSetAttribute((const void*)k_rmsnorm_bwd<bf16_t>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-        }
-        k_rmsnorm_bwd<bf16_t><<<nblk, TPB, lds, st>>>((const bf16_t*)dxn, (const bf16_t*)x, r, (const bf16_t*)g,
-                                                      (const bf16_t*)dres, (bf16_t*)dx, partial, T, H, rpb);
-    } else {
-        if (lds > 48 * 1024) {
-            e = hipFuncSetAttribute((const void*)k_rmsnorm_bwd<float>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-        }
-        k_rmsnorm_bwd<float><<<nblk, TPB, lds, st>>>((const float*)dxn, (const float*)x, r, (const float*)g,
-                                                     (const float*)dres, (float*)dx, partial, T, H, rpb);
-    }
+    const int lds = a.H * (int)sizeof(float);
+    static std::atomic<uint64_t> lds_ok{0};
+    const hipError_t e = allow_lds((const void*)k_rmsnorm_bwd<T>, 32768 * (int)sizeof(float), lds_ok);
+    if (e != hipSuccess) return e;
+    k_rmsnorm_bwd<T><<<a.nblk, TPB, lds, st>>>((const T*)a.dxn, (const T*)a.x, a.r, (const T*)a.g, (const T*)a.dres, (T*)a.dx,
+                                               a.partial, a.T, a.H, a.rpb);
     return hipGetLastError();
 }
 
-hipError_t colsum_reduce(const float* partial, int nblk, int H, float* out, int accumulate, hipStream_t st) {
-    k_colsum_reduce<<<(H + 4 * WAVE - 1) / (4 * WAVE), TPB, 0, st>>>(partial, nblk, H, out, accumulate);
+hipError_t rmsnorm_bwd(int dtype, const void* dxn, const void* x, const float* r, const void* g, const void* dres,
+                       void* dx, float* partial, size_t partial_bytes, int T, int H, hipStream_t st) {
+    NormBwd a{dxn, x, r, g, dres, dx, partial, T, H, rms_rows_per_block(T, H, partial_bytes), 0};
+    a.nblk = (T + a.rpb - 1) / a.rpb;
+    return dtype == DT_BF16 ? rmsnorm_bwd_t<bf16_t>(a, st) : rmsnorm_bwd_t<float>(a, st);
+}
+
+hipError_t colsum_reduce(const ColSum* jobs, int n, int H, int accumulate, hipStream_t st) {
+    k_colsum_reduce<<<dim3((H + 63) / 64, n), CSW * WAVE, 0, st>>>(jobs[0], jobs[n - 1], H, accumulate);
     return hipGetLastError();
 }
 

@@ -232,7 +232,9 @@ static WorkLayout work_layout(const Dims& d) {
     w.dqkv = take(T * d.Q3 * d.es);
     w.dvec = take((size_t)d.B * d.nh * d.S * 4);
     w.dkv_part = take(attn_bwd_scratch_bytes(d.dt, d.B, d.S, d.nh, d.nkv, d.d));   // partial dK, dV of grouped heads
-    w.partial = take((size_t)rmsnorm_bwd_blocks(d.T) * d.H * 4);
+    int rows = 8;                          // gain-gradient partials: one row per `rows` tokens, at most 256
+    while ((d.T + rows - 1) / rows > 256) rows *= 2;
+    w.partial = take((size_t)((d.T + rows - 1) / rows) * d.H * 4);
     w.gemm_ws = take(d.dt == DT_BF16 ? GEMM_WS_BYTES : 0);
     w.total = off;
     return w;
@@ -479,8 +481,18 @@ static int layer_bwd_impl(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, c
     const float* r1 = (const float*)at(saved, sl.r1); const float* r2 = (const float*)at(saved, sl.r2);
     void* m = at(ws, wl.m); void* dgu = at(ws, wl.dgu); void* dhn = at(ws, wl.dhn); void* dh = at(ws, wl.dh);
     void* da = at(ws, wl.da); void* dqkv = at(ws, wl.dqkv);
-    float* dvec = (float*)at(ws, wl.dvec); float* partial = (float*)at(ws, wl.partial);
-    const int nblk = rmsnorm_bwd_blocks(T);
+    float* dvec = (float*)at(ws, wl.dvec);
+    // Partial column sums of the two gain gradients, kept until one launch at the end reduces both.  Those of the MLP norm
+    // go to the front of the m | dgate|dup stretch, which nobody needs by then, if that holds a row per workgroup, those
+    // of the attention norm behind them or to `partial`, whichever has more room.
+    const size_t want = (size_t)std::min(T, 256) * H * 4, stretch = wl.dhn - wl.m;
+    const bool in_stretch = stretch >= want;
+    float* part2 = (float*)at(ws, in_stretch ? wl.m : wl.partial);
+    const size_t part2_b = in_stretch ? up256(want) : wl.gemm_ws - wl.partial;
+    const bool both_in = in_stretch && stretch - part2_b >= want;
+    float* part1 = (float*)at(ws, both_in ? wl.m + part2_b : wl.partial);
+    const size_t part1_b = both_in ? want : wl.gemm_ws - wl.partial;
+    const ColSum sums[2] = {{part2, rmsnorm_bwd_blocks(T, H, part2_b), g->g_mlp}, {part1, rmsnorm_bwd_blocks(T, H, part1_b), g->g_attn}};
     acc = acc ? 1 : 0;
     ctx->gemm_ws = d.dt == DT_BF16 ? at(ws, wl.gemm_ws) : nullptr;
 
@@ -502,8 +514,8 @@ static int layer_bwd_impl(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, c
         HIP_TRY(tgemm(ctx, dt, desc(GEMM_NN, T, H, F, dgu, 2 * F, w->w_gate, H, dhn, H), st));
         HIP_TRY(tgemm(ctx, dt, desc(GEMM_NN, T, H, F, at(dgu, (size_t)F * es), 2 * F, w->w_up, H, dhn, H, dhn, H), st));
     }
-    TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dhn, h, r2, w->g_mlp, dy, dh, partial, T, H, st));                // dh = dy + norm-bwd
-    TR(HH_TRACE_ELEMENTWISE, 4.0 * nblk * H, colsum_reduce(partial, nblk, H, g->g_mlp, acc, st));
+    TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dhn, h, r2, w->g_mlp, dy, dh, part2, part2_b, T, H, st));          // dh = dy + norm-bwd
+    if (!in_stretch) TR(HH_TRACE_ELEMENTWISE, 4.0 * sums[0].rows * H, colsum_reduce(sums, 1, H, acc, st));
 
     // attention branch: h = x + a Wo^T
     HIP_TRY(tgemm(ctx, dt, desc(GEMM_TN, H, A, T, dh, H, a, A, g->wo, A, nullptr, 0, 1, acc), st));
@@ -511,8 +523,9 @@ static int layer_bwd_impl(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, c
     const int Akv = d.Akv, Q3 = d.Q3;
     const int part_w[3] = {A, Akv, Akv}, part_c[3] = {0, A, A + Akv};
     // dq | dk | dv of the rotated q, k and of v, with the rotary embedding taken back out of dq and dk.  The fp32 path's
-    // scratch is the m | dgate|dup | dhn stretch of the workspace, whose contents nobody needs any more by now.
-    const size_t part_at = dt == DT_BF16 ? wl.dkv_part : wl.m, part_end = dt == DT_BF16 ? wl.partial : wl.dh;
+    // scratch is the m | dgate|dup | dhn stretch of the workspace behind the partial sums above, whose contents nobody
+    // needs any more by now.
+    const size_t part_at = dt == DT_BF16 ? wl.dkv_part : wl.m + (in_stretch ? part2_b : 0), part_end = dt == DT_BF16 ? wl.partial : wl.dh;
     TR(HH_TRACE_ATTN_BWD, 2.0 * attn_flop(d), attn_bwd(dt, qkv, Q3, a, da, lse, dvec, dqkv, at(ws, part_at), part_end - part_at, d.B, d.S,
                                                        d.nh, d.nkv, d.d, ctx->rope_table, ctx->rope_seq, st));
     const bool qkv_packed = (const char*)w->wk == (const char*)w->wq + (size_t)A * H * es &&
@@ -535,8 +548,9 @@ static int layer_bwd_impl(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, c
             HIP_TRY(tgemm(ctx, dt, desc(GEMM_NN, T, H, part_w[i], at(dqkv, (size_t)part_c[i] * es), Q3, ws3[i], H, dxn, H,
                                   i ? dxn : nullptr, H), st));
     }
-    TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dxn, x, r1, w->g_attn, dh, dx, partial, T, H, st));              // dx = dh + norm-bwd
-    TR(HH_TRACE_ELEMENTWISE, 4.0 * nblk * H, colsum_reduce(partial, nblk, H, g->g_attn, acc, st));
+    TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dxn, x, r1, w->g_attn, dh, dx, part1, part1_b, T, H, st));         // dx = dh + norm-bwd
+    if (in_stretch) TR(HH_TRACE_ELEMENTWISE, 4.0 * (sums[0].rows + sums[1].rows) * H, colsum_reduce(sums, 2, H, acc, st));
+    else TR(HH_TRACE_ELEMENTWISE, 4.0 * sums[1].rows * H, colsum_reduce(sums + 1, 1, H, acc, st));
     return HH_OK;
 }
 

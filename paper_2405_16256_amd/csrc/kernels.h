@@ -39,11 +39,13 @@ hipError_t gemm(int dtype, const GemmDesc& g, hipStream_t st);
 hipError_t rmsnorm_fwd(int dtype, const void* x, const void* g, void* xn, float* r,
                        int T, int H, float eps, hipStream_t st);
 // dx = dres + r*(w - u*mean(w*u)), u = x*r, w = dxn*g; per-workgroup column sums of
-// dxn*u go to partial[rmsnorm_bwd_blocks(T), H].
-int rmsnorm_bwd_blocks(int T);
+// dxn*u go to partial[rmsnorm_bwd_blocks(T, H, partial_bytes)][H].
+int rmsnorm_bwd_blocks(int T, int H, size_t partial_bytes);
 hipError_t rmsnorm_bwd(int dtype, const void* dxn, const void* x, const float* r, const void* g,
-                       const void* dres, void* dx, float* partial, int T, int H, hipStream_t st);
-hipError_t colsum_reduce(const float* partial, int nblk, int H, float* out, int accumulate, hipStream_t st);
+                       const void* dres, void* dx, float* partial, size_t partial_bytes, int T, int H, hipStream_t st);
+// out[H] (=|+=) column sums of partial[rows][H], one or two of them in one launch
+struct ColSum { const float* partial; int rows; float* out; };
+hipError_t colsum_reduce(const ColSum* jobs, int n, int H, int accumulate, hipStream_t st);
 
 // In-place rotary embedding of the first nrot heads (query heads, then key heads) of every row of a
 // [T, ld] buffer.  table = cos[table_seq][d/2] followed by sin[table_seq][d/2], table_seq >= S.
