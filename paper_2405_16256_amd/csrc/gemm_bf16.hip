@@ -15,7 +15,7 @@
 //     the stage after that are issued.
 //   * k_gemm_ring (gemm_ring.h): tiles of 64x64 to 128x256 with rings of 2 to 4 stages, for
 //     problems that 256x256 tiles would leave most of the chip idle on.
-// choose() picks kernel, tile and k split by a cost model fitted to measured times.
+// plan() picks kernel, tile and k split, and whether problems share a launch, by a cost model fitted to measured times.
 //
 // Operand tiles in LDS keep the layout they have in memory, so global->LDS traffic is
 // 16 bytes per lane with no transposition:
@@ -30,6 +30,10 @@
 // The MFMA takes the B-side fragment as its first operand, so each accumulator lane owns
 // one row m of C and runs of 4 consecutive columns n: stores are 8-byte (bf16) or 16-byte
 // (fp32) vectors along the contiguous dimension of C.
+#include <algorithm>
+#include <climits>
+#include <cstring>
+
 #include "gemm_ring.h"
 #include "gemm_tile.h"
 #include "kernels.h"
@@ -369,21 +373,54 @@ static hipError_t launch_dma(const GemmDesc& g, uint32_t a_bytes, uint32_t b_byt
     return hipGetLastError();
 }
 
-template <int KIND, int BM, int BN, int WM, int WN, int NS, bool OUT_F32>
-static hipError_t launch_ring(const GemmDesc& g, uint32_t a_bytes, uint32_t b_bytes, int ksplit, hipStream_t st) {
+// extent in bytes of each operand as laid out in memory (rows x ld), for the buffer bounds
+static long extent_a(const GemmDesc& g) {
+    const long rows = (g.kind == GEMM_TN) ? g.K : g.M, cols = (g.kind == GEMM_TN) ? g.M : g.K;
+    return ((rows - 1) * g.lda + cols) * 2;
+}
+static long extent_b(const GemmDesc& g, int K) {
+    const long rows = (g.kind == GEMM_NT) ? g.N : K, cols = (g.kind == GEMM_NT) ? K : g.N;
+    return ((rows - 1) * g.ldb + cols) * 2;
+}
+
+template <bool BWD, int BM, int BN, int WM, int WN, int NS>
+static hipError_t launch_ring(const GemmDesc* g, const int* order, const int* ksplit, int n, hipStream_t st) {
     constexpr int LDS = NS * (BM + BN) * DK * 2;
     static std::atomic<uint64_t> lds_ok{0};
-    auto kern = k_gemm_ring<KIND, BM, BN, WM, WN, NS, OUT_F32>;
+    auto kern = k_gemm_ring<BWD, BM, BN, WM, WN, NS>;
     const hipError_t e = allow_lds((const void*)kern, LDS, lds_ok);
     if (e != hipSuccess) return e;
-    const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
-    kern<<<tiles * ksplit, WM * WN * 64, LDS, st>>>((const bf16_t*)g.A, g.lda, a_bytes, (const bf16_t*)g.B, g.ldb, b_bytes, g.C, g.ldc,
-                                                    (const bf16_t*)g.R, g.ldr, g.M, g.N, g.K, g.accumulate, tiles, ksplit, (float*)g.ws);
-    if (ksplit > 1) {
-        const long n = (long)g.M * (g.N / 4);
-        k_ring_reduce<OUT_F32><<<(unsigned)((n + 255) / 256), 256, 0, st>>>((const float*)g.ws, ksplit, BM, BN, g.C, g.ldc, (const bf16_t*)g.R,
-                                                                           g.ldr, g.M, g.N, g.accumulate);
+    RingGroup grp{};
+    RingReduce red{};
+    grp.n = n;
+    red.bm = BM; red.bn = BN;
+    int first = 0, red_first = 0;
+    float* partial = (float*)g[0].ws;
+    for (int i = 0; i < n; i++) {
+        const GemmDesc& q = g[order[i]];
+        const int s = ksplit[order[i]];
+        RingProblem& p = grp.p[i];
+        const int nk = (q.K + DK - 1) / DK;
+        p.A = (const bf16_t*)q.A; p.B = (const bf16_t*)q.B; p.C = q.C; p.R = (const bf16_t*)q.R;
+        p.kseg[0] = q.k1 ? q.k1 / DK : INT_MAX; p.kseg[1] = q.k2 ? q.k2 / DK : INT_MAX;
+        p.Bseg[0] = (const bf16_t*)q.B1; p.Bseg[1] = (const bf16_t*)q.B2;
+        p.a_bytes = (uint32_t)extent_a(q); p.b_bytes = (uint32_t)extent_b(q, q.k1 ? q.k1 : q.K);
+        p.kind = q.kind; p.lda = q.lda; p.ldb = q.ldb; p.ldc = q.ldc; p.ldr = q.ldr; p.M = q.M; p.N = q.N; p.K = q.K;
+        p.accumulate = q.accumulate;
+        p.tiles = ((q.M + BM - 1) / BM) * ((q.N + BN - 1) / BN);
+        p.ksplit = s;
+        p.first = first;
+        first += p.tiles * s;
+        if (s > 1) {
+            if (nk < s) return hipErrorInvalidValue;
+            p.partial = partial;
+            partial += (size_t)p.tiles * s * BM * BN;
+            red.j[red.n++] = RingReduce::Job{p.partial, q.C, p.R, s, q.ldc, q.ldr, q.M, q.N, q.accumulate, q.out_f32, red_first};
+            red_first += (int)(((long)q.M * (q.N / 4) + 255) / 256);
+        }
     }
+    kern<<<first, WM * WN * 64, LDS, st>>>(grp);
+    if (red.n) k_ring_reduce<<<red_first, 256, 0, st>>>(red);
     return hipGetLastError();
 }
 
@@ -402,65 +439,169 @@ static constexpr Variant VARIANTS[V_COUNT] = {
     {64, 64, 2, 2.4, 2.0, 0.23, 0.38},   {64, 128, 2, 1.9, 2.5, 0.325, 0.59}, {128, 128, 1, 2.4, 2.4, 0.43, 0.59},
     {128, 128, 2, 0.6, 3.9, 0.56, 0.875}, {128, 256, 1, 1.8, 4.0, 0.72, 0.92}, {256, 256, 1, 3.0, 5.5, 1.45, 1.45},
 };
-struct Choice { int v, ksplit; };
+// Plan of one problem or of a group: the kernel variant, k splits, the order of the problems (longest k loop first) and
+// the predicted time.
+struct Plan { int v, ksplit[RING_MAX], order[RING_MAX]; double t; };
+static constexpr int SPLITS[] = {1, 2, 3, 4, 6, 8};
 
-static Choice choose(const GemmDesc& g) {
+static double out_bytes(const GemmDesc& g) { return (double)g.M * g.N * (g.out_f32 ? 8 : 2); }
+static double floor_us(const GemmDesc& g) { return (2.0 * g.K * ((double)g.M + g.N) + out_bytes(g)) / 5.0e6; }
+static long tiles_of(const GemmDesc& g, const Variant& q) { return (long)((g.M + q.bm - 1) / q.bm) * ((g.N + q.bn - 1) / q.bn); }
+static bool may_split(const GemmDesc& g, const Variant& q, int s) {
+    const long tiles = tiles_of(g, q);
+    return s == 1 || (g.ws && (g.K + DK - 1) / DK / s >= 2 && tiles * (s - 1) <= 700 &&
+                      (size_t)tiles * s * q.bm * q.bn * sizeof(float) <= g.ws_bytes);
+}
+static double reduce_us(const GemmDesc& g, const Variant& q, int s) {
+    return s > 1 ? ((double)tiles_of(g, q) * q.bm * q.bn * 8.0 * s + out_bytes(g)) / 6.5e6 : 0.0;
+}
+
+// One problem.  whole_only: it has to run as one piece (B in several segments), which the 256x256 kernel cannot.
+static Plan plan_one(const GemmDesc& g, bool whole_only) {
     const int nk = (g.K + DK - 1) / DK;
-    const double out_bytes = (double)g.M * g.N * (g.out_f32 ? 8 : 2);
-    const double floor_us = (2.0 * g.K * ((double)g.M + g.N) + out_bytes) / 5.0e6;
-    Choice best{V_DMA, 1};
-    double best_t = 1e30;
+    const double floor = floor_us(g);
+    Plan best{V_DMA, {1}, {0}, 1e30};
     for (int v = 0; v < V_COUNT; v++) {
         const Variant& q = VARIANTS[v];
-        const long tiles = (long)((g.M + q.bm - 1) / q.bm) * ((g.N + q.bn - 1) / q.bn);
-        if (v == V_DMA && tiles < 64) continue;
+        const long tiles = tiles_of(g, q);
+        if (v == V_DMA && (whole_only || tiles < 64)) continue;
         const long cap = 256L * q.per_cu;
         if (v == V_DMA) {   // launch_dma splits the last round itself
             const long full = tiles / cap, rem = tiles % cap;
             int s = rem > 0 && rem <= cap / 2 && g.ws ? (int)(cap / rem > 8 ? 8 : cap / rem) : 1;
             while (s > 1 && nk / s < 4) s--;
             double t = full * (q.e + nk * q.t_full) + (rem ? q.e + (double)nk / s * q.t_one : 0.0);
-            if (t < floor_us) t = floor_us;
+            if (t < floor) t = floor;
             if (s > 1) t += 2.0 + rem * s * 0.05;
             t = 0.95 * (t + q.t0);   // another kernel has to promise more than the model's bias at these sizes
-            if (t < best_t) { best_t = t; best = Choice{v, 1}; }
+            if (t < best.t) best = Plan{V_DMA, {1}, {0}, t};
             continue;
         }
-        static constexpr int SPLITS[] = {1, 2, 3, 4, 6, 8};
         for (const int s : SPLITS) {
-            if (s > 1 && (!g.ws || nk / s < 2 || tiles * (s - 1) > 700 ||
-                          (size_t)tiles * s * q.bm * q.bn * sizeof(float) > g.ws_bytes)) break;
+            if (!may_split(g, q, s)) break;
             const long w = tiles * s, full = w / cap, rem = w % cap;
             const double ks = (double)nk / s;
             double t = full * (q.e + ks * q.t_full) + (rem ? q.e + ks * (rem <= 256 ? q.t_one : q.t_full) : 0.0);
-            if (t < floor_us) t = floor_us;
-            if (s > 1) t += 3.0 + ((double)tiles * q.bm * q.bn * 8.0 * s + out_bytes) / 6.5e6;
+            if (t < floor) t = floor;
+            if (s > 1) t += 3.0 + reduce_us(g, q, s);
             t += q.t0;
-            if (t < best_t) { best_t = t; best = Choice{v, s}; }
+            if (t < best.t) best = Plan{v, {s}, {0}, t};
         }
     }
     return best;
 }
 
-template <int KIND, bool OUT_F32>
-static hipError_t launch_chosen(const GemmDesc& g, uint32_t a_bytes, uint32_t b_bytes, hipStream_t st) {
-    const Choice c = choose(g);
-    switch (c.v) {
-        case V_64x64: return launch_ring<KIND, 64, 64, 2, 2, 4, OUT_F32>(g, a_bytes, b_bytes, c.ksplit, st);
-        case V_64x128: return launch_ring<KIND, 64, 128, 2, 2, 3, OUT_F32>(g, a_bytes, b_bytes, c.ksplit, st);
-        case V_128x128: return launch_ring<KIND, 128, 128, 2, 4, 4, OUT_F32>(g, a_bytes, b_bytes, c.ksplit, st);
-        case V_128x128_2: return launch_ring<KIND, 128, 128, 2, 2, 2, OUT_F32>(g, a_bytes, b_bytes, c.ksplit, st);
-        case V_128x256: return launch_ring<KIND, 128, 256, 2, 4, 3, OUT_F32>(g, a_bytes, b_bytes, c.ksplit, st);
-        default: return launch_dma<KIND, OUT_F32>(g, a_bytes, b_bytes, st);
+// Several problems in one launch of one variant.  Its workgroups are handed out longest first; the launch ends with the
+// longest of them if all fit the chip at once, otherwise when the work is spent, give or take half a short one.  The
+// splits tried are those that bring every problem's k loop below a common length.
+static Plan plan_group(const GemmDesc* g, int n) {
+    double floor = 0.0;
+    for (int i = 0; i < n; i++) floor += floor_us(g[i]);
+    Plan best{V_DMA, {1, 1, 1, 1}, {0, 1, 2, 3}, 1e30};
+    for (int v = 0; v < V_DMA; v++) {
+        const Variant& q = VARIANTS[v];
+        for (int lead = 0; lead < n; lead++)
+            for (const int ls : SPLITS) {
+                if (!may_split(g[lead], q, ls)) break;
+                const double len = (double)((g[lead].K + DK - 1) / DK) / ls;
+                Plan p{v, {1, 1, 1, 1}, {0, 1, 2, 3}, 0.0};
+                long w = 0;
+                size_t ws = 0;
+                double reduce = 0.0, most = 0.0, least = 1e30, sum = 0.0;
+                for (int i = 0; i < n; i++) {
+                    const int nk = (g[i].K + DK - 1) / DK;
+                    int s = 1;
+                    for (const int c : SPLITS) {
+                        if (!may_split(g[i], q, c)) break;
+                        s = c;
+                        if ((double)nk / c <= len) break;
+                    }
+                    p.ksplit[i] = s;
+                    const long tiles = tiles_of(g[i], q);
+                    w += tiles * s;
+                    if (s > 1) ws += (size_t)tiles * s * q.bm * q.bn * sizeof(float);
+                    reduce += reduce_us(g[i], q, s);
+                    const double ks = (double)nk / s;
+                    most = std::max(most, ks); least = std::min(least, ks); sum += tiles * s * ks;
+                }
+                if (ws > g[0].ws_bytes) continue;
+                const double slots = 256.0 * q.per_cu;
+                double t;
+                if (w <= 256) t = q.e + most * q.t_one;
+                else if (w <= slots) t = q.e + most * q.t_full;
+                else t = std::max(q.e + most * q.t_full, (w * q.e + sum * q.t_full) / slots + 0.5 * (q.e + least * q.t_full));
+                t = std::max(t, floor) + q.t0 + (ws ? 3.0 + reduce : 0.0);
+                p.t = t;
+                if (t < best.t) best = p;
+            }
     }
+    auto len = [&](int i) { return (double)g[i].K / best.ksplit[i]; };
+    for (int i = 1; i < n; i++)   // longest first
+        for (int j = i; j > 0 && len(best.order[j]) > len(best.order[j - 1]); j--) std::swap(best.order[j], best.order[j - 1]);
+    return best;
 }
 
-hipError_t gemm_bf16(const GemmDesc& g, hipStream_t st) {
-    if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipSuccess;
-    // extent in bytes of each operand as laid out in memory (rows x ld), for the buffer bounds
-    const long a_rows = (g.kind == GEMM_TN) ? g.K : g.M, a_cols = (g.kind == GEMM_TN) ? g.M : g.K;
-    const long b_rows = (g.kind == GEMM_NT) ? g.N : g.K, b_cols = (g.kind == GEMM_NT) ? g.K : g.N;
-    const long a_bytes = ((a_rows - 1) * g.lda + a_cols) * 2, b_bytes = ((b_rows - 1) * g.ldb + b_cols) * 2;
+// A plan depends on sizes alone, and a program asks for the same few again and again: each thread remembers the last one
+// of each of 64 hash slots (a group costs 5 to 10 us to plan).
+struct PlanKey {
+    int n, whole, sizes[RING_MAX][4];
+    size_t ws;
+    bool operator==(const PlanKey& o) const { return n == o.n && whole == o.whole && ws == o.ws && !memcmp(sizes, o.sizes, sizeof sizes); }
+};
+static Plan plan(const GemmDesc* g, int n, bool whole_only) {
+    struct Slot { PlanKey key; Plan plan; };
+    static thread_local Slot slots[64];
+    PlanKey k{};
+    k.n = n; k.whole = whole_only; k.ws = g[0].ws ? g[0].ws_bytes : 0;
+    uint32_t h = (uint32_t)n * 2u + whole_only;
+    for (int i = 0; i < n; i++) {
+        const int v[4] = {g[i].kind, g[i].M, g[i].N, g[i].K};
+        for (int j = 0; j < 4; j++) { k.sizes[i][j] = v[j]; h = (h ^ (uint32_t)v[j]) * 0x9E3779B1u; h ^= h >> 15; }
+    }
+    Slot& s = slots[h & 63];
+    if (!(s.key == k)) s = Slot{k, n == 1 ? plan_one(g[0], whole_only) : plan_group(g, n)};   // key.n is 0 in an empty slot
+    return s.plan;
+}
+
+template <bool BWD>
+static hipError_t launch_variant(const GemmDesc* g, int n, const Plan& p, hipStream_t st) {
+    switch (p.v) {
+        case V_64x64: return launch_ring<BWD, 64, 64, 2, 2, 4>(g, p.order, p.ksplit, n, st);
+        case V_64x128: return launch_ring<BWD, 64, 128, 2, 2, 3>(g, p.order, p.ksplit, n, st);
+        case V_128x128: return launch_ring<BWD, 128, 128, 2, 4, 4>(g, p.order, p.ksplit, n, st);
+        case V_128x128_2: return launch_ring<BWD, 128, 128, 2, 2, 2>(g, p.order, p.ksplit, n, st);
+        case V_128x256: return launch_ring<BWD, 128, 256, 2, 4, 3>(g, p.order, p.ksplit, n, st);
+    }
+    const uint32_t a = (uint32_t)extent_a(g[0]), b = (uint32_t)extent_b(g[0], g[0].K);
+    switch (g[0].kind) {
+        case GEMM_NT: return launch_dma<GEMM_NT, false>(g[0], a, b, st);
+        case GEMM_NN: return launch_dma<GEMM_NN, false>(g[0], a, b, st);
+        default: return launch_dma<GEMM_TN, true>(g[0], a, b, st);
+    }
+}
+static hipError_t launch_planned(const GemmDesc* g, int n, const Plan& p, hipStream_t st) {
+    return g[0].kind == GEMM_NT ? launch_variant<false>(g, n, p, st) : launch_variant<true>(g, n, p, st);
+}
+
+// The segments of a segmented problem one after the other, each adding to what the ones before it have left in C.
+static int segments(const GemmDesc& g, GemmDesc out[3]) {
+    const int at[4] = {0, g.k1 ? g.k1 : g.K, g.k2 ? g.k2 : g.K, g.K};
+    const void* const b[3] = {g.B, g.B1, g.B2};
+    int n = 0;
+    for (int i = 0; i < 3 && at[i] < g.K; i++) {
+        GemmDesc& o = out[n++];
+        o = g;
+        o.k1 = o.k2 = 0; o.B1 = o.B2 = nullptr;
+        o.A = (const bf16_t*)g.A + at[i];
+        o.B = b[i];
+        o.K = at[i + 1] - at[i];
+        if (i) { o.R = g.C; o.ldr = g.ldc; }
+    }
+    return n;
+}
+
+static hipError_t check(const GemmDesc& g) {
+    const long a_bytes = extent_a(g), b_bytes = extent_b(g, g.K);
     if (a_bytes >= (1L << 32) - (1L << 25) || b_bytes >= (1L << 32) - (1L << 25)) return hipErrorInvalidValue;
     if (g.lda > 65535 || g.ldb > 65535) return hipErrorInvalidValue;
     // C (and the residual) are addressed with 32-bit byte offsets below 2 GB
@@ -471,12 +612,47 @@ hipError_t gemm_bf16(const GemmDesc& g, hipStream_t st) {
     if (g.N % 4 != 0) return hipErrorInvalidValue;   // the epilogues move 4 columns at a time
     // activations come out in bf16 (NT, NN), parameter gradients in fp32 (TN)
     if ((g.out_f32 != 0) != (g.kind == GEMM_TN) || (g.out_f32 && g.R)) return hipErrorInvalidValue;
-    switch (g.kind) {
-        case GEMM_NT: return launch_chosen<GEMM_NT, false>(g, (uint32_t)a_bytes, (uint32_t)b_bytes, st);
-        case GEMM_NN: return launch_chosen<GEMM_NN, false>(g, (uint32_t)a_bytes, (uint32_t)b_bytes, st);
-        case GEMM_TN: return launch_chosen<GEMM_TN, true>(g, (uint32_t)a_bytes, (uint32_t)b_bytes, st);
+    // segments of B: rows of an NN problem, in order, each a whole number of k tiles
+    if (g.k1 && (g.kind != GEMM_NN || !g.B1 || g.k1 % DK || g.k1 >= g.K)) return hipErrorInvalidValue;
+    if (g.k2 && (!g.k1 || !g.B2 || g.k2 % DK || g.k2 <= g.k1 || g.k2 >= g.K)) return hipErrorInvalidValue;
+    return hipSuccess;
+}
+
+hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st) {
+    if (n < 1 || n > RING_MAX) return hipErrorInvalidValue;
+    Plan each[RING_MAX];
+    double apart = 0.0;
+    for (int i = 0; i < n; i++) {
+        if (g[i].M <= 0 || g[i].N <= 0 || g[i].K <= 0) return hipErrorInvalidValue;
+        const hipError_t e = check(g[i]);
+        if (e != hipSuccess) return e;
+        if ((g[i].kind == GEMM_NT) != (g[0].kind == GEMM_NT)) return hipErrorInvalidValue;
+        each[i] = plan(g + i, 1, false);
+        if (g[i].k1) {   // in one piece on the ring kernel, or segment by segment
+            GemmDesc seg[3];
+            const int m = segments(g[i], seg);
+            double t = 0.0;
+            for (int j = 0; j < m; j++) t += plan(seg + j, 1, false).t;
+            const Plan whole = plan(g + i, 1, true);
+            each[i] = whole;
+            if (t < whole.t) { each[i].v = V_COUNT; each[i].t = t; }
+        }
+        apart += each[i].t;
     }
-    return hipErrorInvalidValue;
+    if (n > 1) {
+        const Plan p = plan(g, n, false);
+        if (p.t < apart) return launch_planned(g, n, p, st);
+    }
+    for (int i = 0; i < n; i++) {
+        hipError_t e = hipSuccess;
+        if (each[i].v == V_COUNT) {
+            GemmDesc seg[3];
+            const int m = segments(g[i], seg);
+            for (int j = 0; j < m && e == hipSuccess; j++) e = launch_planned(seg + j, 1, plan(seg + j, 1, false), st);
+        } else e = launch_planned(g + i, 1, each[i], st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace hh

@@ -11,12 +11,33 @@
 
 namespace hh {
 
-template <int KIND, int BM, int BN, int WM, int WN, int NS, bool OUT_F32>
-__global__ __launch_bounds__(WM * WN * 64) void k_gemm_ring(const bf16_t* __restrict__ A, int lda, uint32_t a_bytes,
-                                                            const bf16_t* __restrict__ B, int ldb, uint32_t b_bytes,
-                                                            void* __restrict__ Cv, int ldc, const bf16_t* R, int ldr,
-                                                            int M, int N, int K, int accumulate, int tiles, int ksplit,
-                                                            float* __restrict__ partial) {
+// A launch takes a group of up to RING_MAX independent problems, each with its own operands, kind and k split: the
+// weight gradients of a layer's backward pass beside the input gradient that uses the same operand, or projections
+// whose weights are separate allocations.  Problem p owns the workgroups first .. first + tiles * ksplit - 1.
+//
+// Why groups: alone, each of these problems leaves most of the chip idle and costs a launch.  Measured: dWdown | dWgate |
+// dWup | d(hn) of hidden 512, ffn 768 and 2200 tokens in five launches 52 us, in one 23 us; dWo | da of hidden 4096,
+// width 1024 and 3300 tokens 101 -> 77 us; a 4-layer, 8 micro-batch stage of hidden 256 and 128 tokens 3.22 -> 2.88 ms.
+constexpr int RING_MAX = 4;
+struct RingProblem {
+    const bf16_t* A;
+    const bf16_t* B;
+    void* C;
+    const bf16_t* R;
+    const bf16_t* Bseg[2];     // NN: where the rows of B from k tile kseg[0] (kseg[1]) on are; INT_MAX: no such segment
+    float* partial;            // k shares: [tile][share][BM*BN] fp32 sums
+    uint32_t a_bytes, b_bytes; // extent of A, and of B up to the first segment's end
+    int kseg[2];
+    int kind, lda, ldb, ldc, ldr, M, N, K, accumulate, tiles, ksplit, first;
+};
+struct RingGroup {
+    int n;
+    RingProblem p[RING_MAX];
+};
+
+template <int KIND, int BM, int BN, int WM, int WN, int NS>
+__device__ __forceinline__ void ring_body(const RingProblem& g) {
+    constexpr bool OUT_F32 = KIND == GEMM_TN;
     constexpr int NW = WM * WN;
     using DA = DmaTile<(KIND != GEMM_TN), BM, NW>;
     using DB = DmaTile<(KIND == GEMM_NT), BN, NW>;
@@ -25,8 +46,13 @@ __global__ __launch_bounds__(WM * WN * 64) void k_gemm_ring(const bf16_t* __rest
     constexpr int PW = DA::PER_WAVE + DB::PER_WAVE;       // DMA instructions per wave and stage
     static_assert(NS * STAGE >= NW * 4096, "the epilogue patches reuse the ring");
     extern __shared__ __attribute__((aligned(1024))) char smem[];   // [stage][A | B]
+    const int M = g.M, N = g.N, K = g.K, lda = g.lda, ldb = g.ldb, ldc = g.ldc, ldr = g.ldr, tiles = g.tiles, ksplit = g.ksplit;
+    const bf16_t* const R = g.R;
+    void* const Cv = g.C;
+    const bool accumulate = g.accumulate != 0;
 
-    const int share = blockIdx.x / tiles, tix = blockIdx.x - share * tiles;
+    const int item = (int)blockIdx.x - g.first;
+    const int share = item / tiles, tix = item - share * tiles;
     const int tiles_n = (N + BN - 1) / BN;
     int tm, tn;
     tile_of_index(tix, (M + BM - 1) / BM, tiles_n, tm, tn);
@@ -36,18 +62,35 @@ __global__ __launch_bounds__(WM * WN * 64) void k_gemm_ring(const bf16_t* __rest
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, hf = lane >> 5;
     const int wm = (wave / WN) * (BM / WM), wn = (wave % WN) * (BN / WN);
 
-    const uint64_t pa = (uint64_t)A, pb = (uint64_t)B;
-    const i32x4 rsA = {(int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), (int)a_bytes, 0x00020000};
-    const i32x4 rsB = {(int)(uint32_t)pb, (int)(uint32_t)(pb >> 32), (int)b_bytes, 0x00020000};
+    const uint64_t pa = (uint64_t)g.A;
+    const i32x4 rsA = {(int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), (int)g.a_bytes, 0x00020000};
     const uint32_t stepA = DA::kstep_bytes(lda), stepB = DB::kstep_bytes(ldb);
+    // B's rows may lie in up to three allocations.  Offsets run on over the segments: segment s is addressed from a base
+    // moved back by the rows before it, and its last row ends its extent.
+    auto rsrc_b = [&](int kt) {
+        uint64_t pb = (uint64_t)g.B;
+        uint32_t bytes = g.b_bytes;
+        if (KIND == GEMM_NN && kt >= g.kseg[0]) {
+            const int s = kt >= g.kseg[1] ? 1 : 0;
+            pb = (uint64_t)g.Bseg[s] - (uint64_t)(uint32_t)g.kseg[s] * stepB;
+            const int end = s == 0 && g.kseg[1] < nk_all ? g.kseg[1] * DK : K;
+            bytes = ((uint32_t)(end - 1) * (uint32_t)ldb + (uint32_t)N) * 2u;
+        }
+        return i32x4{(int)(uint32_t)pb, (int)(uint32_t)(pb >> 32), (int)bytes, 0x00020000};
+    };
+    i32x4 rsB = rsrc_b(kbeg);
     uint32_t voA[DA::PER_WAVE], voB[DB::PER_WAVE];
 #pragma unroll
     for (int i = 0; i < DA::PER_WAVE; i++) voA[i] = DA::voff(wave, i, m0, lda) + kbeg * stepA;
 #pragma unroll
     for (int i = 0; i < DB::PER_WAVE; i++) voB[i] = DB::voff(wave, i, n0, ldb) + kbeg * stepB;
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
+    const int kseg0 = g.kseg[0], kseg1 = g.kseg[1];
+    int kissue = kbeg;   // k tile that `issue` fetches next
     auto issue = [&](int slot) {
         const uint32_t base = lds0 + slot * STAGE;
+        if (KIND == GEMM_NN && (kissue == kseg0 || kissue == kseg1)) rsB = rsrc_b(kissue);
+        kissue++;
 #pragma unroll
         for (int i = 0; i < DA::PER_WAVE; i++) { dma16(base + (wave * DA::PER_WAVE + i) * 1024, voA[i], rsA); voA[i] += stepA; }
 #pragma unroll
@@ -109,16 +152,16 @@ __global__ __launch_bounds__(WM * WN * 64) void k_gemm_ring(const bf16_t* __rest
         slot = next;
     }
 
-    if (ksplit > 1) {   // a share of the k range: raw fp32 sums, finished by k_splitk_reduce
-        float* pt = partial + ((size_t)(tm * tiles_n + tn) * ksplit + share) * (BM * BN);
+    if (ksplit > 1) {   // a share of the k range: raw fp32 sums, finished by k_ring_reduce
+        float* pt = g.partial + ((size_t)(tm * tiles_n + tn) * ksplit + share) * (BM * BN);
 #pragma unroll
         for (int i = 0; i < TM; i++)
 #pragma unroll
             for (int j = 0; j < TN; j++)
 #pragma unroll
-                for (int g = 0; g < 4; g++)
-                    *reinterpret_cast<float4*>(pt + (wm + 32 * i + (lane & 31)) * BN + wn + 32 * j + 8 * g + 4 * hf) =
-                        make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+                for (int q = 0; q < 4; q++)
+                    *reinterpret_cast<float4*>(pt + (wm + 32 * i + (lane & 31)) * BN + wn + 32 * j + 8 * q + 4 * hf) =
+                        make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
         return;
     }
 
@@ -156,9 +199,9 @@ __global__ __launch_bounds__(WM * WN * 64) void k_gemm_ring(const bf16_t* __rest
                 }
             }
 #pragma unroll
-            for (int g = 0; g < 4; g++)
-                *reinterpret_cast<float4*>(patch + r_w * 128 + (((2 * g + hf) ^ ((r_w >> 1) & 7)) << 4)) =
-                    make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+            for (int q = 0; q < 4; q++)
+                *reinterpret_cast<float4*>(patch + r_w * 128 + (((2 * q + hf) ^ ((r_w >> 1) & 7)) << 4)) =
+                    make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
 #pragma unroll
             for (int t = 0; t < 4; t++) {
                 const int rr = 8 * t + r_r;
@@ -175,40 +218,60 @@ __global__ __launch_bounds__(WM * WN * 64) void k_gemm_ring(const bf16_t* __rest
         }
 }
 
-// Sums the ksplit fp32 shares of every BM x BN tile in a fixed order and applies the epilogue.  A thread owns 4
-// consecutive columns of one row of C.
-template <bool OUT_F32>
-__global__ __launch_bounds__(256) void k_ring_reduce(const float* __restrict__ partial, int ksplit, int bm, int bn,
-                                                     void* __restrict__ Cv, int ldc, const bf16_t* R, int ldr,
-                                                     int M, int N, int accumulate) {
-    const int vpr = N / 4;
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (long)M * vpr) return;
+// BWD: NN and TN problems, otherwise NT
+template <bool BWD, int BM, int BN, int WM, int WN, int NS>
+__global__ __launch_bounds__(WM * WN * 64) void k_gemm_ring(RingGroup grp) {
+    int i = 0;
+    while (i + 1 < grp.n && (int)blockIdx.x >= grp.p[i + 1].first) i++;
+    const RingProblem& g = grp.p[i];
+    if (!BWD) ring_body<GEMM_NT, BM, BN, WM, WN, NS>(g);
+    else if (g.kind == GEMM_NN) ring_body<GEMM_NN, BM, BN, WM, WN, NS>(g);
+    else ring_body<GEMM_TN, BM, BN, WM, WN, NS>(g);
+}
+
+// Sums the ksplit fp32 shares of every BM x BN tile of the group's split problems in a fixed order and applies the
+// epilogue.  A thread owns 4 consecutive columns of one row of C.
+struct RingReduce {
+    struct Job {
+        const float* partial;
+        void* C;
+        const bf16_t* R;
+        int ksplit, ldc, ldr, M, N, accumulate, out_f32, first;
+    } j[RING_MAX];
+    int n, bm, bn;
+};
+__global__ __launch_bounds__(256) void k_ring_reduce(RingReduce grp) {
+    int i = 0;
+    while (i + 1 < grp.n && (int)blockIdx.x >= grp.j[i + 1].first) i++;
+    const RingReduce::Job& j = grp.j[i];
+    const int bm = grp.bm, bn = grp.bn, vpr = j.N / 4;
+    const long idx = (long)((int)blockIdx.x - j.first) * 256 + threadIdx.x;
+    if (idx >= (long)j.M * vpr) return;
     const int m = (int)(idx / vpr), n = (int)(idx - (long)m * vpr) * 4;
-    const int tiles_n = (N + bn - 1) / bn;
+    const int tiles_n = (j.N + bn - 1) / bn;
     const int tm = m / bm, tn = n / bn;
-    const float* p = partial + (size_t)(tm * tiles_n + tn) * ksplit * (bm * bn) + (m - tm * bm) * bn + (n - tn * bn);
+    const float* p = j.partial + (size_t)(tm * tiles_n + tn) * j.ksplit * (bm * bn) + (m - tm * bm) * bn + (n - tn * bn);
     float v[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int c = 0; c < ksplit; c++) {
+    for (int c = 0; c < j.ksplit; c++) {
         const float4 t = *reinterpret_cast<const float4*>(p + (size_t)c * (bm * bn));
         v[0] += t.x; v[1] += t.y; v[2] += t.z; v[3] += t.w;
     }
-    if (OUT_F32) {
-        float* c = reinterpret_cast<float*>(Cv) + (size_t)m * ldc + n;
-        if (accumulate) {
+    if (j.out_f32) {
+        float* c = reinterpret_cast<float*>(j.C) + (size_t)m * j.ldc + n;
+        if (j.accumulate) {
             const float4 old = *reinterpret_cast<const float4*>(c);
             v[0] += old.x; v[1] += old.y; v[2] += old.z; v[3] += old.w;
         }
         *reinterpret_cast<float4*>(c) = make_float4(v[0], v[1], v[2], v[3]);
     } else {
-        if (R) {
-            const uint2 rr = *reinterpret_cast<const uint2*>(R + (size_t)m * ldr + n);
+        if (j.R) {
+            const uint2 rr = *reinterpret_cast<const uint2*>(j.R + (size_t)m * j.ldr + n);
             v[0] += lo_bf(rr.x); v[1] += hi_bf(rr.x); v[2] += lo_bf(rr.y); v[3] += hi_bf(rr.y);
         }
         uint2 o;
         o.x = pack_bf2(v[0], v[1]);
         o.y = pack_bf2(v[2], v[3]);
-        *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(Cv) + (size_t)m * ldc + n) = o;
+        *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(j.C) + (size_t)m * j.ldc + n) = o;
     }
 }
 

@@ -16,7 +16,7 @@
 #include "kernels.h"
 
 namespace hh {
-hipError_t gemm_bf16(const GemmDesc& g, hipStream_t st);
+hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st);
 hipError_t gemm_f32(const GemmDesc& g, hipStream_t st);
 hipError_t attn_bf16_fwd(const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, hipStream_t st);
 hipError_t attn_bf16_bwd(const void* qkv, int ld, const void* o, const void* dout, const float* lse, float* dvec,
@@ -28,8 +28,21 @@ hipError_t attn_f32_bwd(const void* qkv, int ld, const void* o, const void* dout
                         void* dqkv, float* scratch, size_t scratch_bytes, int B, int S, int nh, int nkv, int d,
                         const float* rope, int rope_seq, hipStream_t st);
 
-hipError_t gemm(int dtype, const GemmDesc& g, hipStream_t st) {
-    return dtype == DT_BF16 ? gemm_bf16(g, st) : gemm_f32(g, st);
+hipError_t gemm(int dtype, const GemmDesc* g, int n, hipStream_t st) {
+    if (dtype == DT_BF16) return gemm_bf16(g, n, st);
+    for (int i = 0; i < n; i++) {
+        // the segments of B one after the other, each adding to what the ones before it have left in C
+        const int at[4] = {0, g[i].k1 ? g[i].k1 : g[i].K, g[i].k2 ? g[i].k2 : g[i].K, g[i].K};
+        const void* const b[3] = {g[i].B, g[i].B1, g[i].B2};
+        for (int s = 0; s < 3 && at[s] < g[i].K; s++) {
+            GemmDesc q = g[i];
+            q.B = b[s]; q.K = at[s + 1] - at[s]; q.A = (const float*)q.A + at[s];
+            if (s) { q.R = q.C; q.ldr = q.ldc; }
+            const hipError_t e = gemm_f32(q, st);
+            if (e != hipSuccess) return e;
+        }
+    }
+    return hipSuccess;
 }
 hipError_t attn_fwd(int dtype, const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, hipStream_t st) {
     return dtype == DT_BF16 ? attn_bf16_fwd(qkv, ld, o, lse, B, S, nh, nkv, d, st) : attn_f32_fwd(qkv, ld, o, lse, B, S, nh, nkv, d, st);
@@ -78,6 +91,7 @@ struct TraceRec {
     hipEvent_t a, b;
     int kind;
     double work;
+    double share;   // of the time between the events that is this family's
 };
 struct hh_ctx {
     int device;
@@ -321,7 +335,7 @@ struct Traced {
     Traced(hh_ctx* c, hipStream_t s, int kind, double work) : ctx(c), st(s), rec(nullptr) {
         if (c->trace_on && ((c->trace_mask >> kind) & 1u) && c->trace_used < c->trace.size()) {
             rec = &c->trace[c->trace_used++];
-            rec->kind = kind; rec->work = work;
+            rec->kind = kind; rec->work = work; rec->share = 1.0;
             (void)hipEventRecord(rec->a, st);
         }
     }
@@ -334,18 +348,33 @@ struct Traced {
     } while (0)
 static double attn_flop(const Dims& d) { return 4.0 * d.d * d.B * d.nh * ((double)d.S * (d.S + 1) / 2); }
 static double gemm_flop(const GemmDesc& g) { return 2.0 * g.M * g.N * g.K; }
-static hipError_t tgemm(hh_ctx* ctx, int dt, GemmDesc g, hipStream_t st) {
-    Traced t(ctx, st, g.kind, gemm_flop(g));
-    g.ws = ctx->gemm_ws; g.ws_bytes = ctx->gemm_ws ? GEMM_WS_BYTES : 0;
-    return gemm(dt, g, st);
+// A group of GEMMs in one call.  Its time is shared out to the members by their flops, so that every member is one
+// launch of its family whether or not they share one.
+static hipError_t tgemm(hh_ctx* ctx, int dt, GemmDesc* g, int n, hipStream_t st) {
+    double total = 0.0;
+    for (int i = 0; i < n; i++) {
+        g[i].ws = ctx->gemm_ws; g[i].ws_bytes = ctx->gemm_ws ? GEMM_WS_BYTES : 0;
+        total += gemm_flop(g[i]);
+    }
+    const size_t first = ctx->trace_used;
+    for (int i = 0; i < n; i++) {
+        if (!(ctx->trace_on && ((ctx->trace_mask >> g[i].kind) & 1u) && ctx->trace_used < ctx->trace.size())) continue;
+        TraceRec& r = ctx->trace[ctx->trace_used++];
+        r.kind = g[i].kind; r.work = gemm_flop(g[i]); r.share = r.work / total;
+        (void)hipEventRecord(r.a, st);
+    }
+    const hipError_t e = gemm(dt, g, n, st);
+    for (size_t i = first; i < ctx->trace_used; i++) (void)hipEventRecord(ctx->trace[i].b, st);
+    return e;
 }
+static hipError_t tgemm(hh_ctx* ctx, int dt, GemmDesc g, hipStream_t st) { return tgemm(ctx, dt, &g, 1, st); }
 
 extern "C" int hh_trace_begin(hh_ctx* ctx, int max_launches, uint32_t kind_mask) {
     if (!ctx) return fail(HH_ERR_INVALID_ARG, "ctx is NULL");
     if (max_launches <= 0) return fail(HH_ERR_INVALID_ARG, "max_launches must be positive");
     HIP_TRY(hipSetDevice(ctx->device));
     while ((int)ctx->trace.size() < max_launches) {
-        TraceRec r{nullptr, nullptr, 0, 0.0};
+        TraceRec r{nullptr, nullptr, 0, 0.0, 1.0};
         HIP_TRY(hipEventCreate(&r.a));
         hipError_t e = hipEventCreate(&r.b);
         if (e != hipSuccess) { (void)hipEventDestroy(r.a); return hip_fail(e, "hipEventCreate"); }
@@ -367,7 +396,7 @@ extern "C" int hh_trace_end(hh_ctx* ctx, hh_trace_sum* out, int n_kinds) {
         HIP_TRY(hipEventSynchronize(r.b));
         float ms = 0.f;
         HIP_TRY(hipEventElapsedTime(&ms, r.a, r.b));
-        if (r.kind < n_kinds) { out[r.kind].launches++; out[r.kind].ms += ms; out[r.kind].work += r.work; }
+        if (r.kind < n_kinds) { out[r.kind].launches++; out[r.kind].ms += ms * r.share; out[r.kind].work += r.work; }
     }
     ctx->trace_used = 0;
     return HH_OK;
@@ -382,6 +411,7 @@ static GemmDesc desc(int kind, int M, int N, int K, const void* A, int lda, cons
     GemmDesc g;
     g.kind = kind; g.M = M; g.N = N; g.K = K; g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc;
     g.R = R; g.ldr = ldr; g.out_f32 = out_f32; g.accumulate = acc; g.ws = nullptr; g.ws_bytes = 0;
+    g.B1 = g.B2 = nullptr; g.k1 = g.k2 = 0;
     return g;
 }
 
@@ -407,8 +437,9 @@ static int layer_fwd_impl(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, c
         HIP_TRY(tgemm(ctx, dt, desc(GEMM_NT, T, Q3, H, xn, H, w->wq, H, qkv, Q3), st));
     } else {
         const void* ws3[3] = {w->wq, w->wk, w->wv};
-        for (int i = 0; i < 3; i++)
-            HIP_TRY(tgemm(ctx, dt, desc(GEMM_NT, T, part_w[i], H, xn, H, ws3[i], H, at(qkv, (size_t)part_c[i] * es), Q3), st));
+        GemmDesc q[3];
+        for (int i = 0; i < 3; i++) q[i] = desc(GEMM_NT, T, part_w[i], H, xn, H, ws3[i], H, at(qkv, (size_t)part_c[i] * es), Q3);
+        HIP_TRY(tgemm(ctx, dt, q, 3, st));
     }
     TR(HH_TRACE_ELEMENTWISE, 2.0 * T * (A + Akv) * es, rope(dt, qkv, Q3, T, d.S, d.nh + d.nkv, d.d, ctx->rope_table, ctx->rope_seq, 0, st));
     TR(HH_TRACE_ATTN_FWD, attn_flop(d), attn_fwd(dt, qkv, Q3, a, lse, d.B, d.S, d.nh, d.nkv, d.d, st));
@@ -418,8 +449,9 @@ static int layer_fwd_impl(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, c
     if (gu_packed) {
         HIP_TRY(tgemm(ctx, dt, desc(GEMM_NT, T, 2 * F, H, hn, H, w->w_gate, H, gu, 2 * F), st));
     } else {
-        HIP_TRY(tgemm(ctx, dt, desc(GEMM_NT, T, F, H, hn, H, w->w_gate, H, gu, 2 * F), st));
-        HIP_TRY(tgemm(ctx, dt, desc(GEMM_NT, T, F, H, hn, H, w->w_up, H, at(gu, (size_t)F * es), 2 * F), st));
+        GemmDesc q[2] = {desc(GEMM_NT, T, F, H, hn, H, w->w_gate, H, gu, 2 * F),
+                         desc(GEMM_NT, T, F, H, hn, H, w->w_up, H, at(gu, (size_t)F * es), 2 * F)};
+        HIP_TRY(tgemm(ctx, dt, q, 2, st));
     }
     TR(HH_TRACE_ELEMENTWISE, 3.0 * T * F * es, swiglu_fwd(dt, gu, m, T, F, st));
     HIP_TRY(tgemm(ctx, dt, desc(GEMM_NT, T, H, F, m, F, w->w_down, F, y, H, h, H), st));
@@ -499,27 +531,27 @@ static int layer_bwd_impl(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, c
     // MLP branch: y = h + m Wd^T
     HIP_TRY(tgemm(ctx, dt, desc(GEMM_NN, T, F, H, dy, H, w->w_down, F, m, F), st));                 // dm (in the m buffer)
     TR(HH_TRACE_ELEMENTWISE, 6.0 * T * F * es, swiglu_bwd(dt, m, gu, dgu, m, T, F, st));                                          // dgate|dup, m
-    HIP_TRY(tgemm(ctx, dt, desc(GEMM_TN, H, F, T, dy, H, m, F, g->w_down, F, nullptr, 0, 1, acc), st));
     const bool gu_packed = (const char*)w->w_up == (const char*)w->w_gate + (size_t)F * H * es;
     const bool dgu_packed = (char*)g->w_up == (char*)g->w_gate + (size_t)F * H * 4 && (size_t)2 * F * H * 4 < ((size_t)1 << 31);
+    GemmDesc q[4];
+    int n = 0;
+    q[n++] = desc(GEMM_TN, H, F, T, dy, H, m, F, g->w_down, F, nullptr, 0, 1, acc);
     if (dgu_packed) {
-        HIP_TRY(tgemm(ctx, dt, desc(GEMM_TN, 2 * F, H, T, dgu, 2 * F, hn, H, g->w_gate, H, nullptr, 0, 1, acc), st));
+        q[n++] = desc(GEMM_TN, 2 * F, H, T, dgu, 2 * F, hn, H, g->w_gate, H, nullptr, 0, 1, acc);
     } else {
-        HIP_TRY(tgemm(ctx, dt, desc(GEMM_TN, F, H, T, dgu, 2 * F, hn, H, g->w_gate, H, nullptr, 0, 1, acc), st));
-        HIP_TRY(tgemm(ctx, dt, desc(GEMM_TN, F, H, T, at(dgu, (size_t)F * es), 2 * F, hn, H, g->w_up, H, nullptr, 0, 1, acc), st));
+        q[n++] = desc(GEMM_TN, F, H, T, dgu, 2 * F, hn, H, g->w_gate, H, nullptr, 0, 1, acc);
+        q[n++] = desc(GEMM_TN, F, H, T, at(dgu, (size_t)F * es), 2 * F, hn, H, g->w_up, H, nullptr, 0, 1, acc);
     }
-    if (gu_packed) {
-        HIP_TRY(tgemm(ctx, dt, desc(GEMM_NN, T, H, 2 * F, dgu, 2 * F, w->w_gate, H, dhn, H), st));
-    } else {
-        HIP_TRY(tgemm(ctx, dt, desc(GEMM_NN, T, H, F, dgu, 2 * F, w->w_gate, H, dhn, H), st));
-        HIP_TRY(tgemm(ctx, dt, desc(GEMM_NN, T, H, F, at(dgu, (size_t)F * es), 2 * F, w->w_up, H, dhn, H, dhn, H), st));
-    }
+    q[n] = desc(GEMM_NN, T, H, 2 * F, dgu, 2 * F, w->w_gate, H, dhn, H);
+    if (!gu_packed) { q[n].B1 = w->w_up; q[n].k1 = F; }
+    HIP_TRY(tgemm(ctx, dt, q, n + 1, st));
     TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dhn, h, r2, w->g_mlp, dy, dh, part2, part2_b, T, H, st));          // dh = dy + norm-bwd
     if (!in_stretch) TR(HH_TRACE_ELEMENTWISE, 4.0 * sums[0].rows * H, colsum_reduce(sums, 1, H, acc, st));
 
     // attention branch: h = x + a Wo^T
-    HIP_TRY(tgemm(ctx, dt, desc(GEMM_TN, H, A, T, dh, H, a, A, g->wo, A, nullptr, 0, 1, acc), st));
-    HIP_TRY(tgemm(ctx, dt, desc(GEMM_NN, T, A, H, dh, H, w->wo, A, da, A), st));
+    q[0] = desc(GEMM_TN, H, A, T, dh, H, a, A, g->wo, A, nullptr, 0, 1, acc);
+    q[1] = desc(GEMM_NN, T, A, H, dh, H, w->wo, A, da, A);
+    HIP_TRY(tgemm(ctx, dt, q, 2, st));
     const int Akv = d.Akv, Q3 = d.Q3;
     const int part_w[3] = {A, Akv, Akv}, part_c[3] = {0, A, A + Akv};
     // dq | dk | dv of the rotated q, k and of v, with the rotary embedding taken back out of dq and dk.  The fp32 path's
@@ -532,22 +564,18 @@ static int layer_bwd_impl(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, c
                             (const char*)w->wv == (const char*)w->wk + (size_t)Akv * H * es;
     const bool dqkv_packed = (char*)g->wk == (char*)g->wq + (size_t)A * H * 4 && (char*)g->wv == (char*)g->wk + (size_t)Akv * H * 4 &&
                              (size_t)Q3 * H * 4 < ((size_t)1 << 31);
+    n = 0;
     if (dqkv_packed) {
-        HIP_TRY(tgemm(ctx, dt, desc(GEMM_TN, Q3, H, T, dqkv, Q3, xn, H, g->wq, H, nullptr, 0, 1, acc), st));
+        q[n++] = desc(GEMM_TN, Q3, H, T, dqkv, Q3, xn, H, g->wq, H, nullptr, 0, 1, acc);
     } else {
         float* gs[3] = {g->wq, g->wk, g->wv};
         for (int i = 0; i < 3; i++)
-            HIP_TRY(tgemm(ctx, dt, desc(GEMM_TN, part_w[i], H, T, at(dqkv, (size_t)part_c[i] * es), Q3, xn, H, gs[i], H, nullptr, 0, 1, acc), st));
+            q[n++] = desc(GEMM_TN, part_w[i], H, T, at(dqkv, (size_t)part_c[i] * es), Q3, xn, H, gs[i], H, nullptr, 0, 1, acc);
     }
     void* dxn = dhn;
-    if (qkv_packed) {
-        HIP_TRY(tgemm(ctx, dt, desc(GEMM_NN, T, H, Q3, dqkv, Q3, w->wq, H, dxn, H), st));
-    } else {
-        const void* ws3[3] = {w->wq, w->wk, w->wv};
-        for (int i = 0; i < 3; i++)
-            HIP_TRY(tgemm(ctx, dt, desc(GEMM_NN, T, H, part_w[i], at(dqkv, (size_t)part_c[i] * es), Q3, ws3[i], H, dxn, H,
-                                  i ? dxn : nullptr, H), st));
-    }
+    q[n] = desc(GEMM_NN, T, H, Q3, dqkv, Q3, w->wq, H, dxn, H);
+    if (!qkv_packed) { q[n].B1 = w->wk; q[n].k1 = A; q[n].B2 = w->wv; q[n].k2 = A + Akv; }
+    HIP_TRY(tgemm(ctx, dt, q, n + 1, st));
     TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dxn, x, r1, w->g_attn, dh, dx, part1, part1_b, T, H, st));         // dx = dh + norm-bwd
     if (in_stretch) TR(HH_TRACE_ELEMENTWISE, 4.0 * (sums[0].rows + sums[1].rows) * H, colsum_reduce(sums, 2, H, acc, st));
     else TR(HH_TRACE_ELEMENTWISE, 4.0 * sums[1].rows * H, colsum_reduce(sums + 1, 1, H, acc, st));

@@ -24,6 +24,9 @@ struct GemmDesc {
     const void* R; int ldr;  // optional residual in the storage dtype, added before rounding (NULL: none)
     int out_f32;             // 1: C is fp32 regardless of the storage dtype (parameter gradients)
     int accumulate;          // 1: C += result
+    // B of an NN problem in up to three allocations: rows k1.. at B1, rows k2.. at B2 (0: no such segment)
+    const void* B1; int k1;
+    const void* B2; int k2;
     void* ws;                // optional scratch for k-split partial sums (bf16 path), may be NULL
     size_t ws_bytes;
 };
@@ -33,7 +36,9 @@ constexpr size_t GEMM_WS_BYTES = (size_t)64 << 20;   // enough for 256 partial t
 constexpr size_t STATIC_SCRATCH_BYTES = (size_t)128 << 20;
 hipError_t static_scratch_init(int device);   // `device` must be current; looks the array's address up once
 void* static_scratch(int device);             // that address (null before a successful init)
-hipError_t gemm(int dtype, const GemmDesc& g, hipStream_t st);
+// Up to 4 problems of which none reads what another writes, either all NT or none; they share launches where that is
+// predicted to be faster.
+hipError_t gemm(int dtype, const GemmDesc* g, int n, hipStream_t st);
 
 // xn = x * r * g, r = 1/sqrt(mean(x^2)+eps) per row.
 hipError_t rmsnorm_fwd(int dtype, const void* x, const void* g, void* xn, float* r,

@@ -45,3 +45,15 @@ def test_every_tile_of_the_gemm_dispatch(ctx, shape, packed):
 def test_both_tiles_of_the_fp32_gemm(ctx, shape, packed):
     from tests.test_gpu_parity import check_layer
     check_layer(ctx, shape, False, 302, packed=packed, label="f32 tiles")
+
+
+@pytest.mark.parametrize("shape,packed", [
+    # groups with and without k shares, B in two and three segments, some of them a single k tile wide
+    (I.LayerShape(256, 4, 64, 704, 128, 1), True),
+    (I.LayerShape(512, 8, 64, 64, 550, 2, n_kv_heads=2), False),
+    (I.LayerShape(512, 3, 128, 1216, 77, 3, n_kv_heads=1), False),
+    (I.LayerShape(4096, 8, 128, 256, 700, 1), True),
+])
+def test_problems_that_share_a_launch(ctx, shape, packed):
+    from tests.test_gpu_parity import check_layer
+    check_layer(ctx, shape, True, 303, packed=packed, label="groups")
