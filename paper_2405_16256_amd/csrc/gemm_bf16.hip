@@ -13,7 +13,7 @@
 //     interleaved with the LDS fragment reads of the next, one barrier per stage placed
 //     before its last k step, after which the other stage's first fragments and the DMA of
 //     the stage after that are issued.
-//   * k_gemm_ring (gemm_ring.h): tiles of 64x64 to 128x256 with rings of 2 to 4 stages, for
+//   * k_gemm_ring (gemm_ring.h): tiles of 64x64 to 192x256 with rings of 2 to 4 stages, for
 //     problems that 256x256 tiles would leave most of the chip idle on.
 // plan() picks kernel, tile and k split, and whether problems share a launch, by a cost model fitted to measured times.
 //
@@ -428,16 +428,21 @@ static hipError_t launch_ring(const GemmDesc* g, const int* order, const int* ks
 // as rounds of 256 (one workgroup per CU) or 512 (two per CU); a round takes e + (k stages) * t, with t = t_full when
 // the round fills every slot and t_one when the last round leaves each CU one workgroup at most; never less than the
 // operands and the result take at 5 TB/s.  A k split adds a reduction kernel: 3 us and its traffic at 6.5 TB/s.
-// The constants (microseconds) are a least-squares fit to 6700 measured launches of 419 random problems (M 17..8192,
-// N, K 64..16384, all three kinds) on one MI355X: 9 % rms error (14 % for 256x256), the choice costs 3 % over the best
-// variant of each problem.  Against one 128x128 register-staged kernel for everything below 64 tiles of 256x256 the
-// problems of that class take half the time (geometric mean; 333x4096x11008 NT: 152 -> 54 us, 36x8384x25152 NN:
-// 336 -> 93 us, 128x512x2200 TN: 29 -> 8.5 us), the larger ones 0.88.
-struct Variant { int bm, bn, per_cu; double t0, e, t_one, t_full; };
-enum { V_64x64, V_64x128, V_128x128, V_128x128_2, V_128x256, V_DMA, V_COUNT };
+// The constants (microseconds) are a least-squares fit to 100000 measured launches of 5600 random problems (M 17..8192,
+// N 64..28672, K 64..16384, all three kinds, weights read cold) on one MI355X: 7 to 11 % rms error (14 % for 256x256),
+// the choice costs 1.6 % over the best variant of each problem.  Against one 128x128 register-staged kernel for
+// everything below 64 tiles of 256x256 the problems of that class take half the time (333x4096x11008 NT: 152 -> 50 us,
+// 36x8384x25152 NN: 336 -> 93 us, 128x512x2200 TN: 29 -> 8.5 us).
+// Tiles of 192 rows or columns only take operands with contiguous k (a k row of a strided operand must be a power of two
+// of 16-byte chunks), i.e. NT problems: 333x12288x4096 60 -> 51 us, 333x22016x4096 95 -> 78, 3300x3072x4096 89 -> 83.
+struct Variant { int bm, bn, per_cu; bool nt_only; double t0, e, t_one, t_full; };
+enum { V_64x64, V_64x128, V_128x128, V_128x128_2, V_128x256, V_192x128, V_192x192, V_192x256, V_DMA, V_COUNT };
 static constexpr Variant VARIANTS[V_COUNT] = {
-    {64, 64, 2, 2.4, 2.0, 0.23, 0.38},   {64, 128, 2, 1.9, 2.5, 0.325, 0.59}, {128, 128, 1, 2.4, 2.4, 0.43, 0.59},
-    {128, 128, 2, 0.6, 3.9, 0.56, 0.875}, {128, 256, 1, 1.8, 4.0, 0.72, 0.92}, {256, 256, 1, 3.0, 5.5, 1.45, 1.45},
+    {64, 64, 2, false, 1.76, 1.83, 0.256, 0.464},   {64, 128, 2, false, 1.69, 2.15, 0.372, 0.690},
+    {128, 128, 1, false, 1.88, 2.65, 0.467, 0.589}, {128, 128, 2, false, 1.13, 3.10, 0.639, 0.997},
+    {128, 256, 1, false, 2.10, 3.76, 0.741, 0.947}, {192, 128, 1, true, 2.34, 2.97, 0.619, 0.778},
+    {192, 192, 1, true, 1.81, 4.58, 0.960, 1.067},  {192, 256, 1, true, 2.07, 4.57, 1.085, 1.305},
+    {256, 256, 1, false, 0.97, 5.44, 1.587, 1.639},
 };
 // Plan of one problem or of a group: the kernel variant, k splits, the order of the problems (longest k loop first) and
 // the predicted time.
@@ -464,7 +469,7 @@ static Plan plan_one(const GemmDesc& g, bool whole_only) {
     for (int v = 0; v < V_COUNT; v++) {
         const Variant& q = VARIANTS[v];
         const long tiles = tiles_of(g, q);
-        if (v == V_DMA && (whole_only || tiles < 64)) continue;
+        if ((v == V_DMA && (whole_only || tiles < 64)) || (q.nt_only && g.kind != GEMM_NT)) continue;
         const long cap = 256L * q.per_cu;
         if (v == V_DMA) {   // launch_dma splits the last round itself
             const long full = tiles / cap, rem = tiles % cap;
@@ -500,6 +505,7 @@ static Plan plan_group(const GemmDesc* g, int n) {
     Plan best{V_DMA, {1, 1, 1, 1}, {0, 1, 2, 3}, 1e30};
     for (int v = 0; v < V_DMA; v++) {
         const Variant& q = VARIANTS[v];
+        if (q.nt_only && g[0].kind != GEMM_NT) continue;
         for (int lead = 0; lead < n; lead++)
             for (const int ls : SPLITS) {
                 if (!may_split(g[lead], q, ls)) break;
@@ -571,6 +577,13 @@ static hipError_t launch_variant(const GemmDesc* g, int n, const Plan& p, hipStr
         case V_128x128: return launch_ring<BWD, 128, 128, 2, 4, 4>(g, p.order, p.ksplit, n, st);
         case V_128x128_2: return launch_ring<BWD, 128, 128, 2, 2, 2>(g, p.order, p.ksplit, n, st);
         case V_128x256: return launch_ring<BWD, 128, 256, 2, 4, 3>(g, p.order, p.ksplit, n, st);
+    }
+    if constexpr (!BWD) {
+        switch (p.v) {
+            case V_192x128: return launch_ring<false, 192, 128, 2, 4, 4>(g, p.order, p.ksplit, n, st);
+            case V_192x192: return launch_ring<false, 192, 192, 2, 2, 3>(g, p.order, p.ksplit, n, st);
+            case V_192x256: return launch_ring<false, 192, 256, 2, 4, 2>(g, p.order, p.ksplit, n, st);
+        }
     }
     const uint32_t a = (uint32_t)extent_a(g[0]), b = (uint32_t)extent_b(g[0], g[0].K);
     switch (g[0].kind) {

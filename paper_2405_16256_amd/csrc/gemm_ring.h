@@ -6,6 +6,8 @@
 // of the stage, so its slot can be refilled (NS stages of lookahead) and the first fragments of the next stage are
 // fetched in the shadow of the last MFMAs.
 #pragma once
+#include <type_traits>
+
 #include "gemm_tile.h"
 #include "kernels.h"
 
@@ -108,48 +110,95 @@ __device__ __forceinline__ void ring_body(const RingProblem& g) {
 #pragma unroll
             for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
 
-    bf16x8 fa[2][TM], fb[2][TN];
-    auto fetch = [&](int set, int slot, int kk) {
-        const char* cA = smem + slot * STAGE;
-        const char* cB = cA + DA::BYTES;
-#pragma unroll
-        for (int i = 0; i < TM; i++) fa[set][i] = DA::frag(cA, wm + 32 * i, kk);
-#pragma unroll
-        for (int j = 0; j < TN; j++) fb[set][j] = DB::frag(cB, wn + 32 * j, kk);
-    };
-    auto mma = [&](int set) {
-#pragma unroll
-        for (int i = 0; i < TM; i++)
-#pragma unroll
-            for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0);
-    };
     // k tile 0 has landed
     if (nk >= NS) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * PW) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    fetch(0, 0, 0);
-    int slot = 0;
-    for (int kt = 0; kt < nk; kt++) {
-        const int next = slot + 1 == NS ? 0 : slot + 1;
+    if constexpr (TM * TN == 1) {
+        // One MFMA per k step: a whole k tile of fragments ahead, so that LDS latency is met once per stage and not once
+        // per k step (128x256x1408 NN, eight tiles: 12.3 -> 9.0 us; 700x1024x1024 NT 7.5 -> 7.2).  With more MFMAs per k
+        // step the loop is bound by its loads from L2 and the registers of a second k tile only cost (64x128 tiles 3 %
+        // slower, 192x192 ones 20 %).
+        bf16x8 fa[2][4][TM], fb[2][4][TN];
+        auto fetch = [&](int set, int slot, int kk) {
+            const char* cA = smem + slot * STAGE;
+            const char* cB = cA + DA::BYTES;
 #pragma unroll
-        for (int kk = 0; kk < 3; kk++) {
-            fetch((kk + 1) & 1, slot, kk + 1);
-            mma(kk & 1);
+            for (int i = 0; i < TM; i++) fa[set][kk][i] = DA::frag(cA, wm + 32 * i, kk);
+#pragma unroll
+            for (int j = 0; j < TN; j++) fb[set][kk][j] = DB::frag(cB, wn + 32 * j, kk);
+        };
+        int slot = 0;
+        auto step = [&](auto parity, int kt) {
+            constexpr int P = decltype(parity)::value, Q = P ^ 1;
+            const int next = slot + 1 == NS ? 0 : slot + 1;
+            // Every wave holds its fragments of k tile kt, so its slot is free once all waves are here; k tile kt + 1 must
+            // have landed for everyone, the NS - 2 tiles after it may still be on their way.
+            if (kt + NS <= nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * PW) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
             __builtin_amdgcn_sched_barrier(0);
+            if (kt + NS < nk) issue(slot);
+            const bool more = kt + 1 < nk;
+#pragma unroll
+            for (int kk = 0; kk < 4; kk++) {
+                if (more) fetch(Q, next, kk);
+#pragma unroll
+                for (int i = 0; i < TM; i++)
+#pragma unroll
+                    for (int j = 0; j < TN; j++)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[P][kk][j], fa[P][kk][i], acc[i][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            slot = next;
+        };
+#pragma unroll
+        for (int kk = 0; kk < 4; kk++) fetch(0, 0, kk);
+        for (int kt = 0; kt < nk; kt += 2) {
+            step(std::integral_constant<int, 0>{}, kt);
+            if (kt + 1 < nk) step(std::integral_constant<int, 1>{}, kt + 1);
         }
-        // Every wave holds its last fragments of k tile kt, so its slot is free once all waves are here; k tile kt + 1
-        // must have landed for everyone, the NS - 2 tiles after it may still be on their way.
-        if (kt + NS <= nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * PW) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-        if (kt + NS < nk) issue(slot);
-        if (kt + 1 < nk) fetch(0, next, 0);
-        mma(1);
-        __builtin_amdgcn_sched_barrier(0);
-        slot = next;
+    } else {
+        bf16x8 fa[2][TM], fb[2][TN];
+        auto fetch = [&](int set, int slot, int kk) {
+            const char* cA = smem + slot * STAGE;
+            const char* cB = cA + DA::BYTES;
+#pragma unroll
+            for (int i = 0; i < TM; i++) fa[set][i] = DA::frag(cA, wm + 32 * i, kk);
+#pragma unroll
+            for (int j = 0; j < TN; j++) fb[set][j] = DB::frag(cB, wn + 32 * j, kk);
+        };
+        auto mma = [&](int set) {
+#pragma unroll
+            for (int i = 0; i < TM; i++)
+#pragma unroll
+                for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0);
+        };
+        fetch(0, 0, 0);
+        int slot = 0;
+        for (int kt = 0; kt < nk; kt++) {
+            const int next = slot + 1 == NS ? 0 : slot + 1;
+#pragma unroll
+            for (int kk = 0; kk < 3; kk++) {
+                fetch((kk + 1) & 1, slot, kk + 1);
+                mma(kk & 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // Every wave holds its last fragments of k tile kt, so its slot is free once all waves are here; k tile kt + 1
+            // must have landed for everyone, the NS - 2 tiles after it may still be on their way.
+            if (kt + NS <= nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * PW) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            if (kt + NS < nk) issue(slot);
+            if (kt + 1 < nk) fetch(0, next, 0);
+            mma(1);
+            __builtin_amdgcn_sched_barrier(0);
+            slot = next;
+        }
     }
 
     if (ksplit > 1) {   // a share of the k range: raw fp32 sums, finished by k_ring_reduce
@@ -220,7 +269,7 @@ __device__ __forceinline__ void ring_body(const RingProblem& g) {
 
 // BWD: NN and TN problems, otherwise NT
 template <bool BWD, int BM, int BN, int WM, int WN, int NS>
-__global__ __launch_bounds__(WM * WN * 64) void k_gemm_ring(RingGroup grp) {
+__global__ __launch_bounds__(WM * WN * 64, BM * BN / (WM * WN) > 64 * 128 ? 1 : 2) void k_gemm_ring(RingGroup grp) {
     int i = 0;
     while (i + 1 < grp.n && (int)blockIdx.x >= grp.p[i + 1].first) i++;
     const RingProblem& g = grp.p[i];

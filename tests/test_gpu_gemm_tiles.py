@@ -57,3 +57,14 @@ def test_both_tiles_of_the_fp32_gemm(ctx, shape, packed):
 def test_problems_that_share_a_launch(ctx, shape, packed):
     from tests.test_gpu_parity import check_layer
     check_layer(ctx, shape, True, 303, packed=packed, label="groups")
+
+
+@pytest.mark.parametrize("shape", [
+    # 192x128, 192x192 and 192x256 in the forward projections: 333 and 385 rows, one row into a third tile
+    I.LayerShape(2048, 32, 128, 11008, 333, 1, n_kv_heads=32),
+    I.LayerShape(1024, 24, 128, 5632, 385, 1, n_kv_heads=24),
+    I.LayerShape(512, 24, 128, 4096, 1153, 1),
+])
+def test_tiles_of_192_rows(ctx, shape):
+    from tests.test_gpu_parity import check_layer
+    check_layer(ctx, shape, True, 304, label="192 rows")
