@@ -11,8 +11,12 @@
 // (a few dozen blocks, k up to a few thousand) are bound by how many waves share that chain: the 32x32 tile spreads a
 // problem over 16 times the waves of a 64x64 one at twice the LDS traffic, and is taken until 64x64 tiles fill the
 // chip.  Measured against the 64x64 FMA tile kernel with scalar loads before it, per call: 128x256x1376 NN 189 -> 12.7
-// us, 700x1024x1536 NN 285 -> 27 us (82 TFLOP/s), 1024x2048x700 TN 98 -> 30 us, 2048x8192x1024 NT 536 -> 287 us (120).
-// Eight stages instead of four are 5 to 20 % slower: the smaller ring lets five workgroups share a CU.
+// us, 700x1024x1536 NN 285 -> 27 us (82 TFLOP/s), 1024x2048x700 TN 98 -> 30 us, 2048x8192x1024 NT 536 -> 270 us (127).
+// Rings of two stages on full launches, so that ten workgroups of 32x32 (five of 64x64) share a CU and their barriers and loads overlap:
+// 700x1536x1024 NT 30.0 us with four stages, 27.7 with two; 2048x8192x1024 329 and 270; eight are slower still.
+#include <algorithm>
+#include <utility>
+
 #include "gemm_tile.h"
 #include "kernels.h"
 
@@ -56,26 +60,45 @@ struct FTile {
     }
 };
 
+// A launch takes a group of up to F32_MAX independent problems (weight gradients beside an input gradient, projections
+// with separate weights), each owning the workgroups first .. first + tiles - 1: alone they are bound by their chain of
+// k stages on a few dozen workgroups.  dWdown | dWgate|up | d(hn) of hidden 256, ffn 688 and 128 tokens in three launches
+// 22.3 us, in one 14; of hidden 1024, ffn 2048 and 700 tokens 171 -> 137; dWo | da there 39.5 -> 30.5.
+constexpr int F32_MAX = 4;
+struct F32Problem {
+    const float* A;
+    const float* B;
+    float* C;
+    const float* R;
+    uint32_t a_bytes, b_bytes;
+    int kind, lda, ldb, ldc, ldr, M, N, K, accumulate, tiles, first;
+};
+struct F32Group {
+    int n;
+    F32Problem p[F32_MAX];
+};
+
 template <int KIND, int BT, int NS>
-__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, int lda, uint32_t a_bytes,
-                                                  const float* __restrict__ B, int ldb, uint32_t b_bytes,
-                                                  float* __restrict__ C, int ldc, const float* R, int ldr,
-                                                  int M, int N, int K, int accumulate) {
+__device__ __forceinline__ void f32_body(const F32Problem& g) {
     constexpr bool A_KC = KIND != GEMM_TN, B_KC = KIND == GEMM_NT;
     using TA = FTile<A_KC, BT>;
     using TB = FTile<B_KC, BT>;
     constexpr int KG = BT == 32 ? 4 : 1;                  // waves that share a block along k
     constexpr int STAGE = TA::BYTES + TB::BYTES, PW = TA::PER_WAVE + TB::PER_WAVE;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int M = g.M, N = g.N, K = g.K, lda = g.lda, ldb = g.ldb, ldc = g.ldc, ldr = g.ldr, accumulate = g.accumulate;
+    const uint32_t a_bytes = g.a_bytes, b_bytes = g.b_bytes;
+    const float* const R = g.R;
+    float* const C = g.C;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, hf = lane >> 5;
     const int tiles_n = (N + BT - 1) / BT;
     int tm, tn;
-    tile_of_index(blockIdx.x, (M + BT - 1) / BT, tiles_n, tm, tn);
+    tile_of_index((int)blockIdx.x - g.first, (M + BT - 1) / BT, tiles_n, tm, tn);
     const int m0 = tm * BT, n0 = tn * BT;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, hf = lane >> 5;
     const int wm = KG == 1 ? (wave >> 1) * 32 : 0, wn = KG == 1 ? (wave & 1) * 32 : 0;
     const int nk = (K + FK - 1) / FK;
 
-    const uint64_t pa = (uint64_t)A, pb = (uint64_t)B;
+    const uint64_t pa = (uint64_t)g.A, pb = (uint64_t)g.B;
     const i32x4 rsA = {(int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), (int)a_bytes, 0x00020000};
     const i32x4 rsB = {(int)(uint32_t)pb, (int)(uint32_t)(pb >> 32), (int)b_bytes, 0x00020000};
     const uint32_t stepA = TA::kstep_bytes(lda), stepB = TB::kstep_bytes(ldb);
@@ -131,7 +154,7 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, i
     }
     __syncthreads();   // nobody reads the ring any more
     // A lane owns row lane%32 of its block and runs of 4 columns 8g + 4hf; through an LDS patch of 4 KB per block the
-    // stores cover 128-byte row segments.  With KG = 4 the four waves' patches are the four partial sums.
+    // stores cover 128-byte row segments.  With KG = 4 the patches of the waves that share a block are its partial sums.
     char* const patch = smem + wave * 4096;
     const int r_w = lane & 31;
 #pragma unroll
@@ -165,44 +188,76 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, i
     }
 }
 
-template <int KIND, int BT, int NS>
-static hipError_t launch(const GemmDesc& g, uint32_t a_bytes, uint32_t b_bytes, hipStream_t st) {
+// BWD: NN and TN problems, otherwise NT
+template <bool BWD, int BT, int NS>
+__global__ __launch_bounds__(256) void k_gemm_f32(F32Group grp) {
+    int i = 0;
+    while (i + 1 < grp.n && (int)blockIdx.x >= grp.p[i + 1].first) i++;
+    const F32Problem& g = grp.p[i];
+    if (!BWD) f32_body<GEMM_NT, BT, NS>(g);
+    else if (g.kind == GEMM_NN) f32_body<GEMM_NN, BT, NS>(g);
+    else f32_body<GEMM_TN, BT, NS>(g);
+}
+
+template <bool BWD, int BT, int NS>
+static hipError_t launch(F32Group& grp, hipStream_t st) {
     constexpr int LDS = NS * 2 * BT * FK * 4;
     static_assert(LDS >= 4 * 4096, "the epilogue patches reuse the ring");
-    static std::atomic<uint64_t> lds_ok{0};
-    auto kern = k_gemm_f32<KIND, BT, NS>;
-    const hipError_t e = allow_lds((const void*)kern, LDS, lds_ok);
-    if (e != hipSuccess) return e;
-    const int tiles = ((g.M + BT - 1) / BT) * ((g.N + BT - 1) / BT);
-    kern<<<tiles, 256, LDS, st>>>((const float*)g.A, g.lda, a_bytes, (const float*)g.B, g.ldb, b_bytes, (float*)g.C, g.ldc, (const float*)g.R, g.ldr,
-                                  g.M, g.N, g.K, g.accumulate);
+    static_assert(LDS <= 48 * 1024, "no raised LDS limit");
+    int first = 0;
+    for (int i = 0; i < grp.n; i++) {
+        F32Problem& p = grp.p[i];
+        p.tiles = ((p.M + BT - 1) / BT) * ((p.N + BT - 1) / BT);
+        p.first = first;
+        first += p.tiles;
+    }
+    k_gemm_f32<BWD, BT, NS><<<first, 256, LDS, st>>>(grp);
     return hipGetLastError();
 }
 
-template <int KIND>
-static hipError_t pick(const GemmDesc& g, uint32_t a_bytes, uint32_t b_bytes, hipStream_t st) {
-    // 64x64 tiles once they fill the chip (about 2.5 per CU): 700x4096x1024 NT, 704 of them: 60 us against 62.5 with
-    // 32x32 tiles; 2048x8192x1024: 287 against 355; 700x1536x1024, 264 of them: 38.6 against 31.5
-    const long tiles = (long)((g.M + 63) / 64) * ((g.N + 63) / 64);
-    if (tiles >= 640) return launch<KIND, 64, 4>(g, a_bytes, b_bytes, st);
-    return launch<KIND, 32, 4>(g, a_bytes, b_bytes, st);
+// 64x64 tiles (half the loads per product) once two of them per CU are kept busy to the end: their k stages, dealt to 512
+// places, have to last a quarter longer than the longest tile.  700x4096x1024 NT, 704 tiles: 53.6 us against 55.3 with
+// 32x32 tiles; 2048x8192x1024: 270 against 302; 700x1536x1024, 264 of them: 39.0 against 27.7; dWdown | dWgate|up | d(hn)
+// of hidden 1024, 700 tokens, 1712 tiles of which 176 six times as long as the others: 149 against 137.
+template <bool BWD>
+static hipError_t pick(F32Group& grp, hipStream_t st) {
+    long stages = 0, longest = 0, small = 0;
+    for (int i = 0; i < grp.n; i++) {
+        const F32Problem& p = grp.p[i];
+        const long nk = (p.K + FK - 1) / FK;
+        stages += (long)((p.M + 63) / 64) * ((p.N + 63) / 64) * nk;
+        longest = std::max(longest, nk);
+        small += (long)((p.M + 31) / 32) * ((p.N + 31) / 32);
+    }
+    // longest k loop first: the launch then ends with the short ones
+    for (int i = 1; i < grp.n; i++)
+        for (int j = i; j > 0 && grp.p[j].K > grp.p[j - 1].K; j--) std::swap(grp.p[j], grp.p[j - 1]);
+    if (stages >= 640 * longest) return launch<BWD, 64, 2>(grp, st);
+    // Up to three 32x32 tiles per CU: six stages, because few workgroups hide little of the latency of operands that
+    // another kernel has just written.  128x256x688 NT of a step of hidden 256
+    // and 128 tokens: 11.3 us with two stages, 8.0 with six (704 tiles: alike).
+    if (small <= 768) return launch<BWD, 32, 6>(grp, st);
+    return launch<BWD, 32, 2>(grp, st);
 }
 
-hipError_t gemm_f32(const GemmDesc& g, hipStream_t st) {
-    if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipSuccess;
-    const long a_rows = (g.kind == GEMM_TN) ? g.K : g.M, a_cols = (g.kind == GEMM_TN) ? g.M : g.K;
-    const long b_rows = (g.kind == GEMM_NT) ? g.N : g.K, b_cols = (g.kind == GEMM_NT) ? g.K : g.N;
-    const long a_bytes = ((a_rows - 1) * g.lda + a_cols) * 4, b_bytes = ((b_rows - 1) * g.ldb + b_cols) * 4;
-    // 32-bit byte offsets with room for a tile of rows past the end
-    if (a_bytes >= (1L << 32) - (1L << 25) || b_bytes >= (1L << 32) - (1L << 25)) return hipErrorInvalidValue;
-    if (g.lda > 65535 || g.ldb > 65535 || g.N % 4 != 0) return hipErrorInvalidValue;
-    if (g.kind != GEMM_TN && g.K % 4 != 0) return hipErrorInvalidValue;
-    switch (g.kind) {
-        case GEMM_NT: return pick<GEMM_NT>(g, (uint32_t)a_bytes, (uint32_t)b_bytes, st);
-        case GEMM_NN: return pick<GEMM_NN>(g, (uint32_t)a_bytes, (uint32_t)b_bytes, st);
-        case GEMM_TN: return pick<GEMM_TN>(g, (uint32_t)a_bytes, (uint32_t)b_bytes, st);
+hipError_t gemm_f32(const GemmDesc* d, int n, hipStream_t st) {
+    if (n < 1 || n > F32_MAX) return hipErrorInvalidValue;
+    F32Group grp{};
+    grp.n = n;
+    for (int i = 0; i < n; i++) {
+        const GemmDesc& g = d[i];
+        if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.k1 || (g.kind == GEMM_NT) != (d[0].kind == GEMM_NT)) return hipErrorInvalidValue;
+        const long a_rows = (g.kind == GEMM_TN) ? g.K : g.M, a_cols = (g.kind == GEMM_TN) ? g.M : g.K;
+        const long b_rows = (g.kind == GEMM_NT) ? g.N : g.K, b_cols = (g.kind == GEMM_NT) ? g.K : g.N;
+        const long a_bytes = ((a_rows - 1) * g.lda + a_cols) * 4, b_bytes = ((b_rows - 1) * g.ldb + b_cols) * 4;
+        // 32-bit byte offsets with room for a tile of rows, past the end
+        if (a_bytes >= (1L << 32) - (1L << 25) || b_bytes >= (1L << 32) - (1L << 25)) return hipErrorInvalidValue;
+        if (g.lda > 65535 || g.ldb > 65535 || g.N % 4 != 0) return hipErrorInvalidValue;
+        if (g.kind != GEMM_TN && g.K % 4 != 0) return hipErrorInvalidValue;
+        grp.p[i] = F32Problem{(const float*)g.A, (const float*)g.B, (float*)g.C, (const float*)g.R, (uint32_t)a_bytes, (uint32_t)b_bytes,
+                              g.kind, g.lda, g.ldb, g.ldc, g.ldr, g.M, g.N, g.K, g.accumulate, 0, 0};
     }
-    return hipErrorInvalidValue;
+    return d[0].kind == GEMM_NT ? pick<false>(grp, st) : pick<true>(grp, st);
 }
 
 }  // namespace hh

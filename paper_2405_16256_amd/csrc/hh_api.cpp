@@ -17,7 +17,7 @@
 
 namespace hh {
 hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st);
-hipError_t gemm_f32(const GemmDesc& g, hipStream_t st);
+hipError_t gemm_f32(const GemmDesc* g, int n, hipStream_t st);
 hipError_t attn_bf16_fwd(const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, hipStream_t st);
 hipError_t attn_bf16_bwd(const void* qkv, int ld, const void* o, const void* dout, const float* lse, float* dvec,
                          void* dqkv, float* scratch, int B, int S, int nh, int nkv, int d,
@@ -30,19 +30,27 @@ hipError_t attn_f32_bwd(const void* qkv, int ld, const void* o, const void* dout
 
 hipError_t gemm(int dtype, const GemmDesc* g, int n, hipStream_t st) {
     if (dtype == DT_BF16) return gemm_bf16(g, n, st);
+    // the later segments of B one after the other behind the group, each adding to what the ones before it have left in C
+    GemmDesc q[4];
+    if (n < 1 || n > 4) return hipErrorInvalidValue;
     for (int i = 0; i < n; i++) {
-        // the segments of B one after the other, each adding to what the ones before it have left in C
-        const int at[4] = {0, g[i].k1 ? g[i].k1 : g[i].K, g[i].k2 ? g[i].k2 : g[i].K, g[i].K};
-        const void* const b[3] = {g[i].B, g[i].B1, g[i].B2};
-        for (int s = 0; s < 3 && at[s] < g[i].K; s++) {
-            GemmDesc q = g[i];
-            q.B = b[s]; q.K = at[s + 1] - at[s]; q.A = (const float*)q.A + at[s];
-            if (s) { q.R = q.C; q.ldr = q.ldc; }
-            const hipError_t e = gemm_f32(q, st);
-            if (e != hipSuccess) return e;
+        q[i] = g[i];
+        if (q[i].k1) q[i].K = q[i].k1;
+        q[i].k1 = q[i].k2 = 0;
+    }
+    hipError_t e = gemm_f32(q, n, st);
+    for (int i = 0; i < n; i++) {
+        const int at[3] = {g[i].k1, g[i].k2 ? g[i].k2 : g[i].K, g[i].K};
+        const void* const b[2] = {g[i].B1, g[i].B2};
+        for (int s = 0; s < 2 && g[i].k1 && at[s] < g[i].K && e == hipSuccess; s++) {
+            q[i].A = (const float*)g[i].A + at[s];
+            q[i].B = b[s];
+            q[i].K = at[s + 1] - at[s];
+            q[i].R = g[i].C; q[i].ldr = g[i].ldc;
+            e = gemm_f32(q + i, 1, st);
         }
     }
-    return hipSuccess;
+    return e;
 }
 hipError_t attn_fwd(int dtype, const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, hipStream_t st) {
     return dtype == DT_BF16 ? attn_bf16_fwd(qkv, ld, o, lse, B, S, nh, nkv, d, st) : attn_f32_fwd(qkv, ld, o, lse, B, S, nh, nkv, d, st);

@@ -68,3 +68,16 @@ def test_problems_that_share_a_launch(ctx, shape, packed):
 def test_tiles_of_192_rows(ctx, shape):
     from tests.test_gpu_parity import check_layer
     check_layer(ctx, shape, True, 304, label="192 rows")
+
+
+@pytest.mark.parametrize("shape,packed", [
+    # k loops of 4 to 87 stages of 32 side by side, ragged ones among them, separate weights
+    (I.LayerShape(256, 4, 64, 688, 128, 1), True),
+    (I.LayerShape(296, 3, 64, 1384, 37, 1), False),
+    (I.LayerShape(64, 2, 64, 264, 500, 2, n_kv_heads=1), False),
+    # 64x64 tiles for a whole group
+    (I.LayerShape(1000, 4, 64, 2040, 1500, 1), True),
+])
+def test_fp32_problems_that_share_a_launch(ctx, shape, packed):
+    from tests.test_gpu_parity import check_layer
+    check_layer(ctx, shape, False, 305, packed=packed, label="f32 groups")
