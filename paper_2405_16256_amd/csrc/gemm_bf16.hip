@@ -53,12 +53,29 @@ constexpr int DSTAGE_BYTES = DTILE * DK * 2;   // one operand, one stage: 32 KB
 // requests measured 1.2 % faster on a whole layer than issuing all 8 during k step 3; more, or later, was slower.
 constexpr int DMA_LATE = 3;
 
+// A launch takes one problem or up to DMA_MAX of one kind and one k (the weight gradients of a layer): their tiles are
+// numbered on, problem p from `first` on.
+constexpr int DMA_MAX = 8;
+struct DmaProblem {
+    const bf16_t* A;
+    const bf16_t* B;
+    void* C;
+    const bf16_t* R;
+    uint32_t a_bytes, b_bytes;
+    int lda, ldb, ldc, ldr, M, N, accumulate, first;
+};
+struct DmaGroup {
+    int n, K;
+    DmaProblem p[DMA_MAX];
+    __device__ __forceinline__ int problem_of(int tile) const {
+        int i = 0;
+        while (i + 1 < n && tile >= p[i + 1].first) i++;
+        return i;
+    }
+};
+
 template <int KIND, bool OUT_F32>
-__global__ __launch_bounds__(512) void k_gemm_dma(const bf16_t* __restrict__ A, int lda, uint32_t a_bytes,
-                                                  const bf16_t* __restrict__ B, int ldb, uint32_t b_bytes,
-                                                  void* __restrict__ Cv, int ldc, const bf16_t* R, int ldr,
-                                                  int M, int N, int K, int accumulate,
-                                                  int full, int n_items, int ksplit, float* __restrict__ partial) {
+__global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_items, int ksplit, float* __restrict__ partial) {
     // The workgroup walks work items blockIdx.x, + gridDim.x, ... < n_items.  Items below `full` are whole tiles
     // (all of k, written out through the epilogue).  Item full + q is the (q % ksplit)-th share of the k range of
     // tile full + q / ksplit; its fp32 sums go to partial[q][256][256] and k_splitk_reduce finishes those tiles.
@@ -70,13 +87,15 @@ __global__ __launch_bounds__(512) void k_gemm_dma(const bf16_t* __restrict__ A, 
     constexpr int TM = 4, TN = 2;
     extern __shared__ __attribute__((aligned(1024))) char smem[];   // [stage][A 32 KB | B 32 KB]
 
-    const int tiles_m = (M + DTILE - 1) / DTILE, tiles_n = (N + DTILE - 1) / DTILE;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, hf = lane >> 5;
     const int wm = (wave >> 2) * 128, wn = (wave & 3) * 64;
-    const int nk_all = (K + DK - 1) / DK;
-    // work item -> tile index, first k tile, number of k tiles, slot in `partial` (-1: whole tile)
-    int tix, kbeg, nk, slot;
+    const int nk_all = (grp.K + DK - 1) / DK;
+    // work item -> problem, first row and column of its tile, first k tile, number of k tiles, slot in `partial` (-1: whole tile)
+    int prob, m0, n0, kbeg, nk, slot;
+    i32x4 rsA, rsB;
+    uint32_t stepA, stepB;
     auto decode = [&](int item) {
+        int tix;
         if (item < full) { tix = item; kbeg = 0; nk = nk_all; slot = -1; }
         else {
             const int q = item - full, chunk = q % ksplit;
@@ -85,22 +104,25 @@ __global__ __launch_bounds__(512) void k_gemm_dma(const bf16_t* __restrict__ A, 
             nk = (int)((long)(chunk + 1) * nk_all / ksplit) - kbeg;
             slot = q;
         }
+        prob = grp.problem_of(tix);
+        const DmaProblem& g = grp.p[prob];
+        int tm, tn;
+        tile_of_index(tix - g.first, (g.M + DTILE - 1) / DTILE, (g.N + DTILE - 1) / DTILE, tm, tn);
+        m0 = tm * DTILE; n0 = tn * DTILE;
+        const uint64_t pa = (uint64_t)g.A, pb = (uint64_t)g.B;
+        rsA = i32x4{(int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), (int)g.a_bytes, 0x00020000};
+        rsB = i32x4{(int)(uint32_t)pb, (int)(uint32_t)(pb >> 32), (int)g.b_bytes, 0x00020000};
+        stepA = DA::kstep_bytes(g.lda); stepB = DB::kstep_bytes(g.ldb);
     };
     int item = (int)blockIdx.x;
     decode(item);
 
-    const uint64_t pa = (uint64_t)A, pb = (uint64_t)B;
-    const i32x4 rsA = {(int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), (int)a_bytes, 0x00020000};
-    const i32x4 rsB = {(int)(uint32_t)pb, (int)(uint32_t)(pb >> 32), (int)b_bytes, 0x00020000};
     uint32_t voA[4], voB[4];
-    const uint32_t stepA = DA::kstep_bytes(lda), stepB = DB::kstep_bytes(ldb);
     const uint32_t lds0 = (uint32_t)(uintptr_t)smem;   // LDS byte address of the dynamic segment
     const uint32_t wave_lds = __builtin_amdgcn_readfirstlane(lds0 + wave * 4096);
 
     constexpr uint32_t CES = OUT_F32 ? 4u : 2u;
     constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
-    const __amdgpu_buffer_rsrc_t rsC = make_rsrc(Cv, (uint32_t)(((size_t)(M - 1) * ldc + N) * CES));
-    const __amdgpu_buffer_rsrc_t rsR = make_rsrc(R ? (const void*)R : (const void*)Cv, R ? (uint32_t)(((size_t)(M - 1) * ldr + N) * 2u) : 0u);
 
 #define SB() __builtin_amdgcn_sched_barrier(0)
     // one DMA instruction of the k tile being issued (i < 4: A part i, else B part i-4) into stage st
@@ -109,8 +131,9 @@ __global__ __launch_bounds__(512) void k_gemm_dma(const bf16_t* __restrict__ A, 
         if (i < 4) { dma16(base + i * 1024, voA[i], rsA); voA[i] += stepA; }
         else { dma16(base + DSTAGE_BYTES + (i - 4) * 1024, voB[i - 4], rsB); voB[i - 4] += stepB; }
     };
-    // point the DMA offsets at tile (m0, n0) and put its first two k tiles on their way
-    auto start_tile = [&](int m0, int n0) {
+    // point the DMA offsets at the decoded tile and put its first two k tiles on their way
+    auto start_tile = [&]() {
+        const int lda = grp.p[prob].lda, ldb = grp.p[prob].ldb;
 #pragma unroll
         for (int i = 0; i < 4; i++) { voA[i] = DA::voff(wave, i, m0, lda) + kbeg * stepA; voB[i] = DB::voff(wave, i, n0, ldb) + kbeg * stepB; }
 #pragma unroll
@@ -121,10 +144,7 @@ __global__ __launch_bounds__(512) void k_gemm_dma(const bf16_t* __restrict__ A, 
             }
     };
 
-    int tm, tn;
-    tile_of_index(tix, tiles_m, tiles_n, tm, tn);
-    int m0 = tm * DTILE, n0 = tn * DTILE;
-    start_tile(m0, n0);
+    start_tile();
     bool fresh = true;   // no stores of an earlier tile are in flight behind the DMAs
 
     for (;;) {
@@ -197,15 +217,13 @@ __global__ __launch_bounds__(512) void k_gemm_dma(const bf16_t* __restrict__ A, 
         }
 
         // next piece of work of this workgroup: start its loads before writing this one out
-        const int cm0 = m0, cn0 = n0, cacc = accumulate, cslot = slot;
+        const int cm0 = m0, cn0 = n0, cslot = slot, cprob = prob;
         item += (int)gridDim.x;
         const bool has_next = item < n_items;
         if (has_next) {
             decode(item);
-            tile_of_index(tix, tiles_m, tiles_n, tm, tn);
-            m0 = tm * DTILE; n0 = tn * DTILE;
             __syncthreads();   // every wave has finished reading the LDS stages
-            start_tile(m0, n0);
+            start_tile();
             fresh = false;
         }
 
@@ -230,6 +248,13 @@ __global__ __launch_bounds__(512) void k_gemm_dma(const bf16_t* __restrict__ A, 
         // whole 128-byte (fp32) or 64-byte (bf16) row segments.  C and R are reached through bounds-checked
         // buffers: rows past M fall behind the buffer's end, columns past N get an out-of-range offset.
         {
+            const DmaProblem& g = grp.p[cprob];
+            const int M = g.M, N = g.N, ldc = g.ldc, ldr = g.ldr;
+            const bool cacc = g.accumulate != 0;
+            void* const Cv = g.C;
+            const bf16_t* const R = g.R;
+            const __amdgpu_buffer_rsrc_t rsC = make_rsrc(Cv, (uint32_t)(((size_t)(M - 1) * ldc + N) * CES));
+            const __amdgpu_buffer_rsrc_t rsR = make_rsrc(R ? (const void*)R : (const void*)Cv, R ? (uint32_t)(((size_t)(M - 1) * ldr + N) * 2u) : 0u);
             char* const patch = smem + DSTAGES * 2 * DSTAGE_BYTES + wave * 4096;
             const int r_w = lane & 31;                       // row written, chunks 2g + hf
             const int r_r = lane >> 3, c_r = lane & 7;       // row (+ 8t) and chunk read back
@@ -288,12 +313,14 @@ __global__ __launch_bounds__(512) void k_gemm_dma(const bf16_t* __restrict__ A, 
 // Sums the ksplit fp32 partial tiles of each split tile in a fixed order and applies the epilogue.
 // 64 workgroups per tile; a thread owns 4 consecutive columns of one row.
 template <bool OUT_F32>
-__global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__ partial, int ksplit, int block0,
-                                                       void* __restrict__ Cv, int ldc, const bf16_t* R, int ldr,
-                                                       int M, int N, int accumulate) {
+__global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__ partial, int ksplit, int block0, DmaGroup grp) {
     const int r = blockIdx.x >> 6, sub = blockIdx.x & 63;
+    const DmaProblem& g = grp.p[grp.problem_of(block0 + r)];
+    const int M = g.M, N = g.N, ldc = g.ldc, ldr = g.ldr, accumulate = g.accumulate;
+    void* const Cv = g.C;
+    const bf16_t* const R = g.R;
     int tm, tn;
-    tile_of_index(block0 + r, (M + DTILE - 1) / DTILE, (N + DTILE - 1) / DTILE, tm, tn);
+    tile_of_index(block0 + r - g.first, (M + DTILE - 1) / DTILE, (N + DTILE - 1) / DTILE, tm, tn);
     const int q = sub * 256 + threadIdx.x;
     const int row = q >> 6, col = (q & 63) * 4;
     const float* p = partial + (size_t)r * ksplit * (DTILE * DTILE) + row * DTILE + col;
@@ -323,6 +350,16 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__
     }
 }
 
+// extent in bytes of each operand as laid out in memory (rows x ld), for the buffer bounds
+static long extent_a(const GemmDesc& g) {
+    const long rows = (g.kind == GEMM_TN) ? g.K : g.M, cols = (g.kind == GEMM_TN) ? g.M : g.K;
+    return ((rows - 1) * g.lda + cols) * 2;
+}
+static long extent_b(const GemmDesc& g, int K) {
+    const long rows = (g.kind == GEMM_NT) ? g.N : K, cols = (g.kind == GEMM_NT) ? K : g.N;
+    return ((rows - 1) * g.ldb + cols) * 2;
+}
+
 // Compute units of the current device (one persistent workgroup each), asked once per device.
 static int device_cus(hipError_t& err) {
     static std::atomic<int> cached[64];
@@ -343,7 +380,7 @@ static int device_cus(hipError_t& err) {
 // tiles would leave most units idle, so it is cut along k into floor(units / R) shares per tile, which the same
 // workgroups take up after their whole tiles (fp32 partials in `ws`, summed in a fixed order by a small second kernel).
 template <int KIND, bool OUT_F32>
-static hipError_t launch_dma(const GemmDesc& g, uint32_t a_bytes, uint32_t b_bytes, hipStream_t st) {
+static hipError_t launch_dma(const GemmDesc* g, int n, hipStream_t st) {
     constexpr int LDS = DSTAGES * 2 * DSTAGE_BYTES + 8 * 4096;   // two stages + the epilogue patches of the 8 waves
     static std::atomic<uint64_t> lds_ok{0};
     auto kern = k_gemm_dma<KIND, OUT_F32>;
@@ -352,35 +389,29 @@ static hipError_t launch_dma(const GemmDesc& g, uint32_t a_bytes, uint32_t b_byt
     hipError_t ce = hipSuccess;
     const int NUM_CU = device_cus(ce);
     if (ce != hipSuccess) return ce;
-    const int tiles = ((g.M + DTILE - 1) / DTILE) * ((g.N + DTILE - 1) / DTILE);
-    const int nk = (g.K + DK - 1) / DK;
+    DmaGroup grp{};
+    grp.n = n; grp.K = g[0].K;
+    int tiles = 0;
+    for (int i = 0; i < n; i++) {
+        const GemmDesc& q = g[i];
+        grp.p[i] = DmaProblem{(const bf16_t*)q.A, (const bf16_t*)q.B, q.C, (const bf16_t*)q.R, (uint32_t)extent_a(q), (uint32_t)extent_b(q, q.K),
+                              q.lda, q.ldb, q.ldc, q.ldr, q.M, q.N, q.accumulate, tiles};
+        tiles += ((q.M + DTILE - 1) / DTILE) * ((q.N + DTILE - 1) / DTILE);
+    }
+    const int nk = (g[0].K + DK - 1) / DK;
     int full = tiles, tail = 0, ksplit = 1;
     const int rem = tiles % NUM_CU;
-    if (rem > 0 && rem <= NUM_CU / 2 && g.ws) {
+    if (rem > 0 && rem <= NUM_CU / 2 && g[0].ws) {
         int s = NUM_CU / rem;
         if (s > 8) s = 8;
-        while (s > 1 && (nk / s < 4 || (size_t)rem * s * DTILE * DTILE * sizeof(float) > g.ws_bytes)) s--;
+        while (s > 1 && (nk / s < 4 || (size_t)rem * s * DTILE * DTILE * sizeof(float) > g[0].ws_bytes)) s--;
         if (s > 1) { full = tiles - rem; tail = rem; ksplit = s; }
     }
     // one launch: a persistent workgroup per CU walks the whole tiles and then the k shares of the tail tiles
     const int n_items = full + tail * ksplit;
-    kern<<<n_items < NUM_CU ? n_items : NUM_CU, 512, LDS, st>>>((const bf16_t*)g.A, g.lda, a_bytes, (const bf16_t*)g.B, g.ldb, b_bytes,
-                                                                 g.C, g.ldc, (const bf16_t*)g.R, g.ldr, g.M, g.N, g.K, g.accumulate,
-                                                                 full, n_items, ksplit, (float*)g.ws);
-    if (tail > 0)
-        k_splitk_reduce<OUT_F32><<<tail * 64, 256, 0, st>>>((const float*)g.ws, ksplit, full, g.C, g.ldc, (const bf16_t*)g.R,
-                                                            g.ldr, g.M, g.N, g.accumulate);
+    kern<<<n_items < NUM_CU ? n_items : NUM_CU, 512, LDS, st>>>(grp, full, n_items, ksplit, (float*)g[0].ws);
+    if (tail > 0) k_splitk_reduce<OUT_F32><<<tail * 64, 256, 0, st>>>((const float*)g[0].ws, ksplit, full, grp);
     return hipGetLastError();
-}
-
-// extent in bytes of each operand as laid out in memory (rows x ld), for the buffer bounds
-static long extent_a(const GemmDesc& g) {
-    const long rows = (g.kind == GEMM_TN) ? g.K : g.M, cols = (g.kind == GEMM_TN) ? g.M : g.K;
-    return ((rows - 1) * g.lda + cols) * 2;
-}
-static long extent_b(const GemmDesc& g, int K) {
-    const long rows = (g.kind == GEMM_NT) ? g.N : K, cols = (g.kind == GEMM_NT) ? K : g.N;
-    return ((rows - 1) * g.ldb + cols) * 2;
 }
 
 template <bool BWD, int BM, int BN, int WM, int WN, int NS>
@@ -461,6 +492,18 @@ static double reduce_us(const GemmDesc& g, const Variant& q, int s) {
     return s > 1 ? ((double)tiles_of(g, q) * q.bm * q.bn * 8.0 * s + out_bytes(g)) / 6.5e6 : 0.0;
 }
 
+// `tiles` tiles of 256x256 in one launch, which splits its last round itself.
+static double dma_us(long tiles, int nk, double floor, bool ws) {
+    const Variant& q = VARIANTS[V_DMA];
+    const long full = tiles / 256, rem = tiles % 256;
+    int s = rem > 0 && rem <= 128 && ws ? (int)(256 / rem > 8 ? 8 : 256 / rem) : 1;
+    while (s > 1 && nk / s < 4) s--;
+    double t = full * (q.e + nk * q.t_full) + (rem ? q.e + (double)nk / s * q.t_one : 0.0);
+    if (t < floor) t = floor;
+    if (s > 1) t += 2.0 + rem * s * 0.05;
+    return 0.95 * (t + q.t0);   // another kernel has to promise more than the model's bias at these sizes
+}
+
 // One problem.  whole_only: it has to run as one piece (B in several segments), which the 256x256 kernel cannot.
 static Plan plan_one(const GemmDesc& g, bool whole_only) {
     const int nk = (g.K + DK - 1) / DK;
@@ -471,14 +514,8 @@ static Plan plan_one(const GemmDesc& g, bool whole_only) {
         const long tiles = tiles_of(g, q);
         if ((v == V_DMA && (whole_only || tiles < 64)) || (q.nt_only && g.kind != GEMM_NT)) continue;
         const long cap = 256L * q.per_cu;
-        if (v == V_DMA) {   // launch_dma splits the last round itself
-            const long full = tiles / cap, rem = tiles % cap;
-            int s = rem > 0 && rem <= cap / 2 && g.ws ? (int)(cap / rem > 8 ? 8 : cap / rem) : 1;
-            while (s > 1 && nk / s < 4) s--;
-            double t = full * (q.e + nk * q.t_full) + (rem ? q.e + (double)nk / s * q.t_one : 0.0);
-            if (t < floor) t = floor;
-            if (s > 1) t += 2.0 + rem * s * 0.05;
-            t = 0.95 * (t + q.t0);   // another kernel has to promise more than the model's bias at these sizes
+        if (v == V_DMA) {
+            const double t = dma_us(tiles, nk, floor, g.ws != nullptr);
             if (t < best.t) best = Plan{V_DMA, {1}, {0}, t};
             continue;
         }
@@ -548,7 +585,7 @@ static Plan plan_group(const GemmDesc* g, int n) {
 }
 
 // A plan depends on sizes alone, and a program asks for the same few again and again: each thread remembers the last one
-// of each of 64 hash slots (a group costs 5 to 10 us to plan).
+// of each of 256 hash slots (a group costs 5 to 10 us to plan).
 struct PlanKey {
     int n, whole, sizes[RING_MAX][4];
     size_t ws;
@@ -556,7 +593,7 @@ struct PlanKey {
 };
 static Plan plan(const GemmDesc* g, int n, bool whole_only) {
     struct Slot { PlanKey key; Plan plan; };
-    static thread_local Slot slots[64];
+    static thread_local Slot slots[256];
     PlanKey k{};
     k.n = n; k.whole = whole_only; k.ws = g[0].ws ? g[0].ws_bytes : 0;
     uint32_t h = (uint32_t)n * 2u + whole_only;
@@ -564,11 +601,18 @@ static Plan plan(const GemmDesc* g, int n, bool whole_only) {
         const int v[4] = {g[i].kind, g[i].M, g[i].N, g[i].K};
         for (int j = 0; j < 4; j++) { k.sizes[i][j] = v[j]; h = (h ^ (uint32_t)v[j]) * 0x9E3779B1u; h ^= h >> 15; }
     }
-    Slot& s = slots[h & 63];
+    Slot& s = slots[h & 255];
     if (!(s.key == k)) s = Slot{k, n == 1 ? plan_one(g[0], whole_only) : plan_group(g, n)};   // key.n is 0 in an empty slot
     return s.plan;
 }
 
+static hipError_t launch_tiles256(const GemmDesc* g, int n, hipStream_t st) {
+    switch (g[0].kind) {
+        case GEMM_NT: return launch_dma<GEMM_NT, false>(g, n, st);
+        case GEMM_NN: return launch_dma<GEMM_NN, false>(g, n, st);
+        default: return launch_dma<GEMM_TN, true>(g, n, st);
+    }
+}
 template <bool BWD>
 static hipError_t launch_variant(const GemmDesc* g, int n, const Plan& p, hipStream_t st) {
     switch (p.v) {
@@ -585,12 +629,7 @@ static hipError_t launch_variant(const GemmDesc* g, int n, const Plan& p, hipStr
             case V_192x256: return launch_ring<false, 192, 256, 2, 4, 2>(g, p.order, p.ksplit, n, st);
         }
     }
-    const uint32_t a = (uint32_t)extent_a(g[0]), b = (uint32_t)extent_b(g[0], g[0].K);
-    switch (g[0].kind) {
-        case GEMM_NT: return launch_dma<GEMM_NT, false>(g[0], a, b, st);
-        case GEMM_NN: return launch_dma<GEMM_NN, false>(g[0], a, b, st);
-        default: return launch_dma<GEMM_TN, true>(g[0], a, b, st);
-    }
+    return launch_tiles256(g, n, st);
 }
 static hipError_t launch_planned(const GemmDesc* g, int n, const Plan& p, hipStream_t st) {
     return g[0].kind == GEMM_NT ? launch_variant<false>(g, n, p, st) : launch_variant<true>(g, n, p, st);
@@ -631,38 +670,84 @@ static hipError_t check(const GemmDesc& g) {
     return hipSuccess;
 }
 
-hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st) {
-    if (n < 1 || n > RING_MAX) return hipErrorInvalidValue;
-    Plan each[RING_MAX];
-    double apart = 0.0;
+// How a list of problems is launched, and the predicted time.
+struct Route {
+    enum { APART, RING, TILES256 } how;
+    Plan group, each[DMA_MAX];   // each[i].v == V_COUNT: segment by segment
+    double t;
+};
+static void route(const GemmDesc* g, int n, Route& r) {
+    r.how = Route::APART;
+    r.t = 0.0;
     for (int i = 0; i < n; i++) {
-        if (g[i].M <= 0 || g[i].N <= 0 || g[i].K <= 0) return hipErrorInvalidValue;
-        const hipError_t e = check(g[i]);
-        if (e != hipSuccess) return e;
-        if ((g[i].kind == GEMM_NT) != (g[0].kind == GEMM_NT)) return hipErrorInvalidValue;
-        each[i] = plan(g + i, 1, false);
+        r.each[i] = plan(g + i, 1, false);
         if (g[i].k1) {   // in one piece on the ring kernel, or segment by segment
             GemmDesc seg[3];
             const int m = segments(g[i], seg);
             double t = 0.0;
             for (int j = 0; j < m; j++) t += plan(seg + j, 1, false).t;
-            const Plan whole = plan(g + i, 1, true);
-            each[i] = whole;
-            if (t < whole.t) { each[i].v = V_COUNT; each[i].t = t; }
+            r.each[i] = plan(g + i, 1, true);
+            if (t < r.each[i].t) { r.each[i].v = V_COUNT; r.each[i].t = t; }
         }
-        apart += each[i].t;
+        r.t += r.each[i].t;
     }
-    if (n > 1) {
-        const Plan p = plan(g, n, false);
-        if (p.t < apart) return launch_planned(g, n, p, st);
+    if (n == 1) return;
+    if (n <= RING_MAX) {
+        r.group = plan(g, n, false);
+        if (r.group.t < r.t) { r.how = Route::RING; r.t = r.group.t; }
     }
+    bool alike = true;
+    double floor = 0.0;
+    long tiles = 0;
+    for (int i = 0; i < n; i++) {
+        alike = alike && g[i].kind == g[0].kind && g[i].K == g[0].K && !g[i].k1;
+        floor += floor_us(g[i]);
+        tiles += tiles_of(g[i], VARIANTS[V_DMA]);
+    }
+    if (alike && tiles >= 64) {
+        const double t = dma_us(tiles, (g[0].K + DK - 1) / DK, floor, g[0].ws != nullptr);
+        if (t < r.t) { r.how = Route::TILES256; r.t = t; }
+    }
+}
+
+// Whether the weight gradients of a layer (dw, one k) are better left to one launch at the end than launched with the
+// input gradients (groups[i] holds n[i] problems of which the last is the input gradient): 256x256 tiles of all of them
+// fill the rounds of the chip that the projections one by one leave ragged, but then the small ones cannot fill up the
+// input gradients' rounds.
+bool gemm_bf16_defer(const GemmDesc* dw, int n_dw, const GemmDesc* const groups[3], const int n[3]) {
+    if (n_dw > DMA_MAX) return false;
+    Route r;
+    route(dw, n_dw, r);
+    if (r.how != Route::TILES256) return false;
+    double last = r.t, with = 0.0;
+    for (int i = 0; i < 3; i++) {
+        route(groups[i], n[i], r);
+        with += r.t;
+        route(groups[i] + n[i] - 1, 1, r);
+        last += r.t;
+    }
+    return last < 0.99 * with;
+}
+
+hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st) {
+    if (n < 1 || n > DMA_MAX) return hipErrorInvalidValue;
+    for (int i = 0; i < n; i++) {
+        if (g[i].M <= 0 || g[i].N <= 0 || g[i].K <= 0) return hipErrorInvalidValue;
+        const hipError_t e = check(g[i]);
+        if (e != hipSuccess) return e;
+        if ((g[i].kind == GEMM_NT) != (g[0].kind == GEMM_NT)) return hipErrorInvalidValue;
+    }
+    Route r;
+    route(g, n, r);
+    if (r.how == Route::RING) return launch_planned(g, n, r.group, st);
+    if (r.how == Route::TILES256) return launch_tiles256(g, n, st);
     for (int i = 0; i < n; i++) {
         hipError_t e = hipSuccess;
-        if (each[i].v == V_COUNT) {
+        if (r.each[i].v == V_COUNT) {
             GemmDesc seg[3];
             const int m = segments(g[i], seg);
             for (int j = 0; j < m && e == hipSuccess; j++) e = launch_planned(seg + j, 1, plan(seg + j, 1, false), st);
-        } else e = launch_planned(g + i, 1, each[i], st);
+        } else e = launch_planned(g + i, 1, r.each[i], st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -17,6 +17,7 @@
 
 namespace hh {
 hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st);
+bool gemm_bf16_defer(const GemmDesc* dw, int n_dw, const GemmDesc* const groups[3], const int n[3]);
 hipError_t gemm_f32(const GemmDesc* g, int n, hipStream_t st);
 hipError_t attn_bf16_fwd(const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, hipStream_t st);
 hipError_t attn_bf16_bwd(const void* qkv, int ld, const void* o, const void* dout, const float* lse, float* dvec,
@@ -356,12 +357,13 @@ struct Traced {
     } while (0)
 static double attn_flop(const Dims& d) { return 4.0 * d.d * d.B * d.nh * ((double)d.S * (d.S + 1) / 2); }
 static double gemm_flop(const GemmDesc& g) { return 2.0 * g.M * g.N * g.K; }
+static void gemm_scratch(const hh_ctx* ctx, GemmDesc& g) { g.ws = ctx->gemm_ws; g.ws_bytes = ctx->gemm_ws ? GEMM_WS_BYTES : 0; }
 // A group of GEMMs in one call.  Its time is shared out to the members by their flops, so that every member is one
 // launch of its family whether or not they share one.
 static hipError_t tgemm(hh_ctx* ctx, int dt, GemmDesc* g, int n, hipStream_t st) {
     double total = 0.0;
     for (int i = 0; i < n; i++) {
-        g[i].ws = ctx->gemm_ws; g[i].ws_bytes = ctx->gemm_ws ? GEMM_WS_BYTES : 0;
+        gemm_scratch(ctx, g[i]);
         total += gemm_flop(g[i]);
     }
     const size_t first = ctx->trace_used;
@@ -522,70 +524,87 @@ static int layer_bwd_impl(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, c
     void* m = at(ws, wl.m); void* dgu = at(ws, wl.dgu); void* dhn = at(ws, wl.dhn); void* dh = at(ws, wl.dh);
     void* da = at(ws, wl.da); void* dqkv = at(ws, wl.dqkv);
     float* dvec = (float*)at(ws, wl.dvec);
-    // Partial column sums of the two gain gradients, kept until one launch at the end reduces both.  Those of the MLP norm
-    // go to the front of the m | dgate|dup stretch, which nobody needs by then, if that holds a row per workgroup, those
-    // of the attention norm behind them or to `partial`, whichever has more room.
-    const size_t want = (size_t)std::min(T, 256) * H * 4, stretch = wl.dhn - wl.m;
-    const bool in_stretch = stretch >= want;
-    float* part2 = (float*)at(ws, in_stretch ? wl.m : wl.partial);
-    const size_t part2_b = in_stretch ? up256(want) : wl.gemm_ws - wl.partial;
-    const bool both_in = in_stretch && stretch - part2_b >= want;
-    float* part1 = (float*)at(ws, both_in ? wl.m + part2_b : wl.partial);
-    const size_t part1_b = both_in ? want : wl.gemm_ws - wl.partial;
-    const ColSum sums[2] = {{part2, rmsnorm_bwd_blocks(T, H, part2_b), g->g_mlp}, {part1, rmsnorm_bwd_blocks(T, H, part1_b), g->g_attn}};
     acc = acc ? 1 : 0;
     ctx->gemm_ws = d.dt == DT_BF16 ? at(ws, wl.gemm_ws) : nullptr;
+    void* dxn = dhn;
 
-    // MLP branch: y = h + m Wd^T
-    HIP_TRY(tgemm(ctx, dt, desc(GEMM_NN, T, F, H, dy, H, w->w_down, F, m, F), st));                 // dm (in the m buffer)
-    TR(HH_TRACE_ELEMENTWISE, 6.0 * T * F * es, swiglu_bwd(dt, m, gu, dgu, m, T, F, st));                                          // dgate|dup, m
-    const bool gu_packed = (const char*)w->w_up == (const char*)w->w_gate + (size_t)F * H * es;
-    const bool dgu_packed = (char*)g->w_up == (char*)g->w_gate + (size_t)F * H * 4 && (size_t)2 * F * H * 4 < ((size_t)1 << 31);
-    GemmDesc q[4];
-    int n = 0;
-    q[n++] = desc(GEMM_TN, H, F, T, dy, H, m, F, g->w_down, F, nullptr, 0, 1, acc);
-    if (dgu_packed) {
-        q[n++] = desc(GEMM_TN, 2 * F, H, T, dgu, 2 * F, hn, H, g->w_gate, H, nullptr, 0, 1, acc);
-    } else {
-        q[n++] = desc(GEMM_TN, F, H, T, dgu, 2 * F, hn, H, g->w_gate, H, nullptr, 0, 1, acc);
-        q[n++] = desc(GEMM_TN, F, H, T, at(dgu, (size_t)F * es), 2 * F, hn, H, g->w_up, H, nullptr, 0, 1, acc);
-    }
-    q[n] = desc(GEMM_NN, T, H, 2 * F, dgu, 2 * F, w->w_gate, H, dhn, H);
-    if (!gu_packed) { q[n].B1 = w->w_up; q[n].k1 = F; }
-    HIP_TRY(tgemm(ctx, dt, q, n + 1, st));
-    TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dhn, h, r2, w->g_mlp, dy, dh, part2, part2_b, T, H, st));          // dh = dy + norm-bwd
-    if (!in_stretch) TR(HH_TRACE_ELEMENTWISE, 4.0 * sums[0].rows * H, colsum_reduce(sums, 1, H, acc, st));
-
-    // attention branch: h = x + a Wo^T
-    q[0] = desc(GEMM_TN, H, A, T, dh, H, a, A, g->wo, A, nullptr, 0, 1, acc);
-    q[1] = desc(GEMM_NN, T, A, H, dh, H, w->wo, A, da, A);
-    HIP_TRY(tgemm(ctx, dt, q, 2, st));
+    // The GEMMs after dm, in three groups of independent ones: the weight gradients that use an operand of an input
+    // gradient, and that input gradient last.
     const int Akv = d.Akv, Q3 = d.Q3;
     const int part_w[3] = {A, Akv, Akv}, part_c[3] = {0, A, A + Akv};
-    // dq | dk | dv of the rotated q, k and of v, with the rotary embedding taken back out of dq and dk.  The fp32 path's
-    // scratch is the m | dgate|dup | dhn stretch of the workspace behind the partial sums above, whose contents nobody
-    // needs any more by now.
-    const size_t part_at = dt == DT_BF16 ? wl.dkv_part : wl.m + (in_stretch ? part2_b : 0), part_end = dt == DT_BF16 ? wl.partial : wl.dh;
-    TR(HH_TRACE_ATTN_BWD, 2.0 * attn_flop(d), attn_bwd(dt, qkv, Q3, a, da, lse, dvec, dqkv, at(ws, part_at), part_end - part_at, d.B, d.S,
-                                                       d.nh, d.nkv, d.d, ctx->rope_table, ctx->rope_seq, st));
+    const bool gu_packed = (const char*)w->w_up == (const char*)w->w_gate + (size_t)F * H * es;
+    const bool dgu_packed = (char*)g->w_up == (char*)g->w_gate + (size_t)F * H * 4 && (size_t)2 * F * H * 4 < ((size_t)1 << 31);
     const bool qkv_packed = (const char*)w->wk == (const char*)w->wq + (size_t)A * H * es &&
                             (const char*)w->wv == (const char*)w->wk + (size_t)Akv * H * es;
     const bool dqkv_packed = (char*)g->wk == (char*)g->wq + (size_t)A * H * 4 && (char*)g->wv == (char*)g->wk + (size_t)Akv * H * 4 &&
                              (size_t)Q3 * H * 4 < ((size_t)1 << 31);
-    n = 0;
+    GemmDesc group[3][4];
+    int n[3] = {0, 0, 0};
+    group[0][n[0]++] = desc(GEMM_TN, H, F, T, dy, H, m, F, g->w_down, F, nullptr, 0, 1, acc);
+    if (dgu_packed) {
+        group[0][n[0]++] = desc(GEMM_TN, 2 * F, H, T, dgu, 2 * F, hn, H, g->w_gate, H, nullptr, 0, 1, acc);
+    } else {
+        group[0][n[0]++] = desc(GEMM_TN, F, H, T, dgu, 2 * F, hn, H, g->w_gate, H, nullptr, 0, 1, acc);
+        group[0][n[0]++] = desc(GEMM_TN, F, H, T, at(dgu, (size_t)F * es), 2 * F, hn, H, g->w_up, H, nullptr, 0, 1, acc);
+    }
+    GemmDesc& to_hn = group[0][n[0]++] = desc(GEMM_NN, T, H, 2 * F, dgu, 2 * F, w->w_gate, H, dhn, H);
+    if (!gu_packed) { to_hn.B1 = w->w_up; to_hn.k1 = F; }
+    group[1][n[1]++] = desc(GEMM_TN, H, A, T, dh, H, a, A, g->wo, A, nullptr, 0, 1, acc);
+    group[1][n[1]++] = desc(GEMM_NN, T, A, H, dh, H, w->wo, A, da, A);
     if (dqkv_packed) {
-        q[n++] = desc(GEMM_TN, Q3, H, T, dqkv, Q3, xn, H, g->wq, H, nullptr, 0, 1, acc);
+        group[2][n[2]++] = desc(GEMM_TN, Q3, H, T, dqkv, Q3, xn, H, g->wq, H, nullptr, 0, 1, acc);
     } else {
         float* gs[3] = {g->wq, g->wk, g->wv};
         for (int i = 0; i < 3; i++)
-            q[n++] = desc(GEMM_TN, part_w[i], H, T, at(dqkv, (size_t)part_c[i] * es), Q3, xn, H, gs[i], H, nullptr, 0, 1, acc);
+            group[2][n[2]++] = desc(GEMM_TN, part_w[i], H, T, at(dqkv, (size_t)part_c[i] * es), Q3, xn, H, gs[i], H, nullptr, 0, 1, acc);
     }
-    void* dxn = dhn;
-    q[n] = desc(GEMM_NN, T, H, Q3, dqkv, Q3, w->wq, H, dxn, H);
-    if (!qkv_packed) { q[n].B1 = w->wk; q[n].k1 = A; q[n].B2 = w->wv; q[n].k2 = A + Akv; }
-    HIP_TRY(tgemm(ctx, dt, q, n + 1, st));
+    GemmDesc& to_xn = group[2][n[2]++] = desc(GEMM_NN, T, H, Q3, dqkv, Q3, w->wq, H, dxn, H);
+    if (!qkv_packed) { to_xn.B1 = w->wk; to_xn.k1 = A; to_xn.B2 = w->wv; to_xn.k2 = A + Akv; }
+    // Or all the weight gradients in one launch after the last input gradient, where that is predicted to be faster.
+    GemmDesc dw[7];
+    int n_dw = 0;
+    for (int i = 0; i < 3; i++)
+        for (int j = 0; j < n[i]; j++) {
+            gemm_scratch(ctx, group[i][j]);
+            if (j + 1 < n[i]) dw[n_dw++] = group[i][j];
+        }
+    const GemmDesc* const groups[3] = {group[0], group[1], group[2]};
+    const bool defer = dt == DT_BF16 && gemm_bf16_defer(dw, n_dw, groups, n);
+    auto run_group = [&](int i) { return defer ? tgemm(ctx, dt, &group[i][n[i] - 1], 1, st) : tgemm(ctx, dt, group[i], n[i], st); };
+
+    // Partial column sums of the two gain gradients.  Those of the MLP norm go to the front of the m | dgate|dup stretch
+    // if nobody needs that any more by then and it holds a row per workgroup, otherwise to `partial`; those of the
+    // attention norm to the stretch (behind the others) or to `partial` likewise.  Unless both have to take `partial`,
+    // one launch at the end reduces both.
+    const size_t want = (size_t)std::min(T, 256) * H * 4, stretch = wl.dhn - wl.m, partial_b = wl.gemm_ws - wl.partial;
+    const bool mlp_in = !defer && stretch >= want;
+    const size_t taken = mlp_in ? up256(want) : 0;
+    const bool attn_in = stretch - taken >= want;
+    float* part2 = (float*)at(ws, mlp_in ? wl.m : wl.partial);
+    float* part1 = (float*)at(ws, attn_in ? wl.m + taken : wl.partial);
+    const size_t part2_b = mlp_in ? want : partial_b, part1_b = attn_in ? want : partial_b;
+    const ColSum sums[2] = {{part2, rmsnorm_bwd_blocks(T, H, part2_b), g->g_mlp}, {part1, rmsnorm_bwd_blocks(T, H, part1_b), g->g_attn}};
+    const bool sum_both = part1 != part2;
+
+    // MLP branch: y = h + m Wd^T
+    HIP_TRY(tgemm(ctx, dt, desc(GEMM_NN, T, F, H, dy, H, w->w_down, F, m, F), st));                 // dm (in the m buffer)
+    TR(HH_TRACE_ELEMENTWISE, 6.0 * T * F * es, swiglu_bwd(dt, m, gu, dgu, m, T, F, st));                                          // dgate|dup, m
+    HIP_TRY(run_group(0));
+    TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dhn, h, r2, w->g_mlp, dy, dh, part2, part2_b, T, H, st));          // dh = dy + norm-bwd
+    if (!sum_both) TR(HH_TRACE_ELEMENTWISE, 4.0 * sums[0].rows * H, colsum_reduce(sums, 1, H, acc, st));
+
+    // attention branch: h = x + a Wo^T
+    HIP_TRY(run_group(1));
+    // dq | dk | dv of the rotated q, k and of v, with the rotary embedding taken back out of dq and dk.  The fp32 path's
+    // scratch is the m | dgate|dup | dhn stretch of the workspace behind the partial sums above, whose contents nobody
+    // needs any more by now.
+    const size_t part_at = dt == DT_BF16 ? wl.dkv_part : wl.m + taken, part_end = dt == DT_BF16 ? wl.partial : wl.dh;
+    TR(HH_TRACE_ATTN_BWD, 2.0 * attn_flop(d), attn_bwd(dt, qkv, Q3, a, da, lse, dvec, dqkv, at(ws, part_at), part_end - part_at, d.B, d.S,
+                                                       d.nh, d.nkv, d.d, ctx->rope_table, ctx->rope_seq, st));
+    HIP_TRY(run_group(2));
+    if (defer) HIP_TRY(tgemm(ctx, dt, dw, n_dw, st));
     TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dxn, x, r1, w->g_attn, dh, dx, part1, part1_b, T, H, st));         // dx = dh + norm-bwd
-    if (in_stretch) TR(HH_TRACE_ELEMENTWISE, 4.0 * (sums[0].rows + sums[1].rows) * H, colsum_reduce(sums, 2, H, acc, st));
+    if (sum_both) TR(HH_TRACE_ELEMENTWISE, 4.0 * (sums[0].rows + sums[1].rows) * H, colsum_reduce(sums, 2, H, acc, st));
     else TR(HH_TRACE_ELEMENTWISE, 4.0 * sums[1].rows * H, colsum_reduce(sums + 1, 1, H, acc, st));
     return HH_OK;
 }

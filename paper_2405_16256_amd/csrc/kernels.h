@@ -36,7 +36,7 @@ constexpr size_t GEMM_WS_BYTES = (size_t)64 << 20;   // enough for 256 partial t
 constexpr size_t STATIC_SCRATCH_BYTES = (size_t)128 << 20;
 hipError_t static_scratch_init(int device);   // `device` must be current; looks the array's address up once
 void* static_scratch(int device);             // that address (null before a successful init)
-// Up to 4 problems of which none reads what another writes, either all NT or none; they share launches where that is
+// Up to 4 problems (8 weight gradients in bf16) of which none reads what another writes, either all NT or none; they share launches where that is
 // predicted to be faster.
 hipError_t gemm(int dtype, const GemmDesc* g, int n, hipStream_t st);
 

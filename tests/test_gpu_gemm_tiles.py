@@ -81,3 +81,14 @@ def test_tiles_of_192_rows(ctx, shape):
 def test_fp32_problems_that_share_a_launch(ctx, shape, packed):
     from tests.test_gpu_parity import check_layer
     check_layer(ctx, shape, False, 305, packed=packed, label="f32 groups")
+
+
+@pytest.mark.parametrize("shape,packed", [
+    # all weight gradients in one launch of 256x256 tiles, with a split last round, from four and from seven problems
+    (I.LayerShape(2048, 4, 128, 2048, 1100, 1, n_kv_heads=1), True),
+    (I.LayerShape(2048, 4, 128, 2048, 750, 2, n_kv_heads=1), False),
+    (I.LayerShape(2048, 16, 128, 2048, 1500, 1, n_kv_heads=4), False),
+])
+def test_weight_gradients_in_one_launch(ctx, shape, packed):
+    from tests.test_gpu_parity import check_layer
+    check_layer(ctx, shape, True, 306, packed=packed, label="dW together")
