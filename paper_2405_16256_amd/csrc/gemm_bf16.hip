@@ -480,6 +480,15 @@ static constexpr Variant VARIANTS[V_COUNT] = {
 struct Plan { int v, ksplit[RING_MAX], order[RING_MAX]; double t; };
 static constexpr int SPLITS[] = {1, 2, 3, 4, 6, 8};
 
+// Time of a k stage in a last round of `busy` workgroups, one per CU.  Where each CU holds one workgroup at most anyway,
+// loops of more than 64 stages run the longer towards t_full the more CUs are busy (the power limit and the traffic
+// behind L2 catch up with them): 4096x1536x12288 NN, 192 tiles of 128x256, 180 us where t_one alone predicts 148 and
+// 256x256 tiles in two shares of k take 159.  On 130 random problems with 40 to 520 tiles of 256x256 the choice costs
+// 1.25 % over the best variant of each, 1.6 % with t_one alone; the same ramp for shorter loops gains nothing.
+static double stage_us(const Variant& q, long busy, double ks) {
+    if (q.per_cu > 1 || ks <= 64.0) return q.t_one;
+    return q.t_one + (q.t_full - q.t_one) * (busy / 256.0) * std::min(1.0, ks / 64.0 - 1.0);
+}
 static double out_bytes(const GemmDesc& g) { return (double)g.M * g.N * (g.out_f32 ? 8 : 2); }
 static double floor_us(const GemmDesc& g) { return (2.0 * g.K * ((double)g.M + g.N) + out_bytes(g)) / 5.0e6; }
 static long tiles_of(const GemmDesc& g, const Variant& q) { return (long)((g.M + q.bm - 1) / q.bm) * ((g.N + q.bn - 1) / q.bn); }
@@ -523,7 +532,7 @@ static Plan plan_one(const GemmDesc& g, bool whole_only) {
             if (!may_split(g, q, s)) break;
             const long w = tiles * s, full = w / cap, rem = w % cap;
             const double ks = (double)nk / s;
-            double t = full * (q.e + ks * q.t_full) + (rem ? q.e + ks * (rem <= 256 ? q.t_one : q.t_full) : 0.0);
+            double t = full * (q.e + ks * q.t_full) + (rem ? q.e + ks * (rem <= 256 ? stage_us(q, rem, ks) : q.t_full) : 0.0);
             if (t < floor) t = floor;
             if (s > 1) t += 3.0 + reduce_us(g, q, s);
             t += q.t0;
@@ -570,7 +579,7 @@ static Plan plan_group(const GemmDesc* g, int n) {
                 if (ws > g[0].ws_bytes) continue;
                 const double slots = 256.0 * q.per_cu;
                 double t;
-                if (w <= 256) t = q.e + most * q.t_one;
+                if (w <= 256) t = q.e + most * stage_us(q, w, most);
                 else if (w <= slots) t = q.e + most * q.t_full;
                 else t = std::max(q.e + most * q.t_full, (w * q.e + sum * q.t_full) / slots + 0.5 * (q.e + least * q.t_full));
                 t = std::max(t, floor) + q.t0 + (ws ? 3.0 + reduce : 0.0);
