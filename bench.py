@@ -21,7 +21,7 @@ if ROOT not in sys.path:
 
 PEAK_BF16_TFLOPS = 2500.0   # dense bf16 MFMA, MI355X
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "cfg3_layer_hbm_traffic_counters.txt")
-KERNEL_SOURCES = ("gemm_bf16.hip", "common.h")      # what the roofline kernel is built from
+KERNEL_SOURCES = ("gemm_bf16.hip", "gemm_tile.h", "gemm_ring.h", "common.h")      # what the roofline kernels are built from
 
 
 def kernel_sources_sha256():
@@ -137,7 +137,7 @@ def main():
         del src, dst
     # Warm-up steps run with every kernel family bracketed by events: this gives the per-family breakdown and
     # names the dominant GEMM family.  In the timed region only that family is bracketed, because each event
-    # between two kernels costs a few microseconds (28 launches per layer pass).
+    # between two kernels costs a few microseconds (23 launches per layer pass).
     fam_all = {}
     traced_warm = a.warmup - 1 if not a.no_trace else 0     # the very first step pays one-time costs: not traced
     for i in range(a.warmup):
