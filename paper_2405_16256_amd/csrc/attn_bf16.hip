@@ -288,7 +288,7 @@ __global__ __launch_bounds__(QW * NPAR * WAVE, QW * NPAR == 8 ? 1 : 2) void k_at
         // rescale of the output accumulators is skipped for almost every tile.
         if (__any(tmax > m + 8.0f)) {
             const float mn = fmaxf(m, tmax);
-            const float alpha = __builtin_amdgcn_exp2f(m - mn);
+            const float alpha = NPAR > 1 && mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - mn);
             lsum *= alpha;
             m = mn;
 #pragma unroll
@@ -296,12 +296,15 @@ __global__ __launch_bounds__(QW * NPAR * WAVE, QW * NPAR == 8 ? 1 : 2) void k_at
 #pragma unroll
                 for (int r = 0; r < 16; r++) oacc[i][r] *= alpha;
         }
+        // A group whose keys so far all score -inf (products past the fp32 range) has no reference yet: its weights are
+        // zero, not NaN, because another group may hold finite scores of the same query.
+        const float ref = NPAR > 1 && m == -INFINITY ? 0.f : m;
         float psum = 0.f;
 #pragma unroll
         for (int tl = 0; tl < 2; tl++)
 #pragma unroll
             for (int r = 0; r < 16; r++) {
-                const float p = __builtin_amdgcn_exp2f(fmaf(sacc[tl][r], c, -m));
+                const float p = __builtin_amdgcn_exp2f(fmaf(sacc[tl][r], c, -ref));
                 sacc[tl][r] = p;
                 psum += p;
             }
