@@ -235,7 +235,13 @@ int hh_layer_profile(hh_ctx *ctx, const hh_layer_cfg *cfg, int n_layers, const h
  * the events (not a hot call); hh_trace_end waits for them and fills
  * out[0..n_kinds-1] (HOST) with launch count, summed milliseconds and summed
  * work: model flops for GEMM and attention families, algorithmic bytes for the
- * elementwise family. */
+ * elementwise family.
+ * A GEMM counts as one launch, with the reduction kernel it may need: each
+ * forward projection and weight gradient (q|k|v and gate|up as one where they
+ * are one allocation) and each input gradient (that of q|k|v or gate|up as one
+ * also where the weights are separate allocations).  GEMMs of small layers may
+ * share a launch, also with one of another family: it is bracketed once and
+ * its time shared out by flops, so that such families show one rate there. */
 typedef enum {
     HH_TRACE_GEMM_NT = 0,      /* forward projections       y  = x W^T   */
     HH_TRACE_GEMM_NN = 1,      /* input gradients           dX = dY W    */

@@ -738,6 +738,13 @@ bool gemm_bf16_defer(const GemmDesc* dw, int n_dw, const GemmDesc* const groups[
     return last < 0.99 * with;
 }
 
+bool gemm_bf16_shares_launch(const GemmDesc* g, int n) {
+    if (n < 2 || n > DMA_MAX) return false;
+    Route r;
+    route(g, n, r);
+    return r.how != Route::APART;
+}
+
 hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st) {
     if (n < 1 || n > DMA_MAX) return hipErrorInvalidValue;
     for (int i = 0; i < n; i++) {

@@ -17,6 +17,7 @@
 
 namespace hh {
 hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st);
+bool gemm_bf16_shares_launch(const GemmDesc* g, int n);
 bool gemm_bf16_defer(const GemmDesc* dw, int n_dw, const GemmDesc* const groups[3], const int n[3]);
 hipError_t gemm_f32(const GemmDesc* g, int n, hipStream_t st);
 hipError_t attn_bf16_fwd(const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, hipStream_t st);
@@ -53,6 +54,7 @@ hipError_t gemm(int dtype, const GemmDesc* g, int n, hipStream_t st) {
     }
     return e;
 }
+bool gemm_shares_launch(int dtype, const GemmDesc* g, int n) { return dtype == DT_BF16 ? gemm_bf16_shares_launch(g, n) : n > 1; }
 hipError_t attn_fwd(int dtype, const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, hipStream_t st) {
     return dtype == DT_BF16 ? attn_bf16_fwd(qkv, ld, o, lse, B, S, nh, nkv, d, st) : attn_f32_fwd(qkv, ld, o, lse, B, S, nh, nkv, d, st);
 }
@@ -100,7 +102,8 @@ struct TraceRec {
     hipEvent_t a, b;
     int kind;
     double work;
-    double share;   // of the time between the events that is this family's
+    size_t events;  // the record whose events bracket the launch (its own, unless GEMMs share one)
+    double share;   // of the time between them that is this family's
 };
 struct hh_ctx {
     int device;
@@ -344,7 +347,7 @@ struct Traced {
     Traced(hh_ctx* c, hipStream_t s, int kind, double work) : ctx(c), st(s), rec(nullptr) {
         if (c->trace_on && ((c->trace_mask >> kind) & 1u) && c->trace_used < c->trace.size()) {
             rec = &c->trace[c->trace_used++];
-            rec->kind = kind; rec->work = work; rec->share = 1.0;
+            rec->kind = kind; rec->work = work; rec->events = ctx->trace_used - 1; rec->share = 1.0;
             (void)hipEventRecord(rec->a, st);
         }
     }
@@ -358,23 +361,29 @@ struct Traced {
 static double attn_flop(const Dims& d) { return 4.0 * d.d * d.B * d.nh * ((double)d.S * (d.S + 1) / 2); }
 static double gemm_flop(const GemmDesc& g) { return 2.0 * g.M * g.N * g.K; }
 static void gemm_scratch(const hh_ctx* ctx, GemmDesc& g) { g.ws = ctx->gemm_ws; g.ws_bytes = ctx->gemm_ws ? GEMM_WS_BYTES : 0; }
-// A group of GEMMs in one call.  Its time is shared out to the members by their flops, so that every member is one
-// launch of its family whether or not they share one.
+// A group of GEMMs in one call.  Where they share a launch it is bracketed once and its time shared out to the members by
+// their flops; members with launches of their own are traced (and launched, in the same way) one by one.
 static hipError_t tgemm(hh_ctx* ctx, int dt, GemmDesc* g, int n, hipStream_t st) {
     double total = 0.0;
     for (int i = 0; i < n; i++) {
         gemm_scratch(ctx, g[i]);
         total += gemm_flop(g[i]);
     }
+    if (n > 1 && ctx->trace_on && !gemm_shares_launch(dt, g, n)) {
+        hipError_t e = hipSuccess;
+        for (int i = 0; i < n && e == hipSuccess; i++) e = tgemm(ctx, dt, g + i, 1, st);
+        return e;
+    }
     const size_t first = ctx->trace_used;
     for (int i = 0; i < n; i++) {
         if (!(ctx->trace_on && ((ctx->trace_mask >> g[i].kind) & 1u) && ctx->trace_used < ctx->trace.size())) continue;
         TraceRec& r = ctx->trace[ctx->trace_used++];
-        r.kind = g[i].kind; r.work = gemm_flop(g[i]); r.share = r.work / total;
-        (void)hipEventRecord(r.a, st);
+        r.kind = g[i].kind; r.work = gemm_flop(g[i]); r.events = first; r.share = r.work / total;
     }
+    const bool traced = ctx->trace_used > first;
+    if (traced) (void)hipEventRecord(ctx->trace[first].a, st);
     const hipError_t e = gemm(dt, g, n, st);
-    for (size_t i = first; i < ctx->trace_used; i++) (void)hipEventRecord(ctx->trace[i].b, st);
+    if (traced) (void)hipEventRecord(ctx->trace[first].b, st);
     return e;
 }
 static hipError_t tgemm(hh_ctx* ctx, int dt, GemmDesc g, hipStream_t st) { return tgemm(ctx, dt, &g, 1, st); }
@@ -384,7 +393,7 @@ extern "C" int hh_trace_begin(hh_ctx* ctx, int max_launches, uint32_t kind_mask)
     if (max_launches <= 0) return fail(HH_ERR_INVALID_ARG, "max_launches must be positive");
     HIP_TRY(hipSetDevice(ctx->device));
     while ((int)ctx->trace.size() < max_launches) {
-        TraceRec r{nullptr, nullptr, 0, 0.0, 1.0};
+        TraceRec r{nullptr, nullptr, 0, 0.0, 0, 1.0};
         HIP_TRY(hipEventCreate(&r.a));
         hipError_t e = hipEventCreate(&r.b);
         if (e != hipSuccess) { (void)hipEventDestroy(r.a); return hip_fail(e, "hipEventCreate"); }
@@ -403,9 +412,10 @@ extern "C" int hh_trace_end(hh_ctx* ctx, hh_trace_sum* out, int n_kinds) {
     for (int k = 0; k < n_kinds; k++) { out[k].kind = k; out[k].launches = 0; out[k].ms = 0.0; out[k].work = 0.0; }
     for (size_t i = 0; i < ctx->trace_used; i++) {
         const TraceRec& r = ctx->trace[i];
-        HIP_TRY(hipEventSynchronize(r.b));
+        const TraceRec& ev = ctx->trace[r.events];
+        HIP_TRY(hipEventSynchronize(ev.b));
         float ms = 0.f;
-        HIP_TRY(hipEventElapsedTime(&ms, r.a, r.b));
+        HIP_TRY(hipEventElapsedTime(&ms, ev.a, ev.b));
         if (r.kind < n_kinds) { out[r.kind].launches++; out[r.kind].ms += ms * r.share; out[r.kind].work += r.work; }
     }
     ctx->trace_used = 0;

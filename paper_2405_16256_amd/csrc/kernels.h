@@ -39,6 +39,8 @@ void* static_scratch(int device);             // that address (null before a suc
 // Up to 4 problems (8 weight gradients in bf16) of which none reads what another writes, either all NT or none; they share launches where that is
 // predicted to be faster.
 hipError_t gemm(int dtype, const GemmDesc* g, int n, hipStream_t st);
+// Whether they do; if not, gemm() on each of them alone launches the same.
+bool gemm_shares_launch(int dtype, const GemmDesc* g, int n);
 
 // xn = x * r * g, r = 1/sqrt(mean(x^2)+eps) per row.
 hipError_t rmsnorm_fwd(int dtype, const void* x, const void* g, void* xn, float* r,

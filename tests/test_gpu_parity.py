@@ -557,6 +557,61 @@ def test_trace_counts_launches_per_family_and_honours_the_mask(ctx):
     assert all(v[0] == 0 for v in fam.values())
 
 
+def test_trace_times_gemms_with_launches_of_their_own_one_by_one(ctx):
+    # 64 tokens, hidden 4096, 64 heads of 128: the weight gradient of q|k|v (0.8 GB of fp32 sums read and written) and the
+    # input gradient beside it (0.2 GB of weights read) have launches of their own and the same flops; they are most of the
+    # time of their families.  Timed together and shared out by flops both families would show the same time.
+    H, nh, d, F, S = 4096, 64, 128, 64, 64
+    cfg = hh.make_cfg(H, nh, d, F, S, 1)
+    A = nh * d
+    gen = torch.Generator(device=L.DEV)
+    gen.manual_seed(53)
+
+    def normal(*shape):
+        return torch.empty(*shape, device=L.DEV).normal_(0.0, 0.02, generator=gen)
+
+    qkv, gu = normal(3 * A, H), normal(2 * F, H)
+    g = {"g_attn": normal(H), "wq": qkv[:A], "wk": qkv[A:2 * A], "wv": qkv[2 * A:], "wo": normal(H, A), "g_mlp": normal(H),
+         "w_gate": gu[:F], "w_up": gu[F:], "w_down": normal(H, F)}
+    qkv_b, gu_b = qkv.bfloat16(), gu.bfloat16()
+    w = {n: t.bfloat16() for n, t in g.items() if n in ("g_attn", "wo", "g_mlp", "w_down")}
+    w.update(wq=qkv_b[:A], wk=qkv_b[A:2 * A], wv=qkv_b[2 * A:], w_gate=gu_b[:F], w_up=gu_b[F:])
+    ws, gs = hh.make_weights(w), hh.make_grads(g)
+    x, dy = normal(1, S, H).bfloat16(), normal(1, S, H).bfloat16()
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+    saved_b, ws_b = hh.hh_layer_sizes(cfg)
+    saved = torch.empty(saved_b, dtype=torch.uint8, device=L.DEV)
+    wsp = torch.empty(ws_b, dtype=torch.uint8, device=L.DEV)
+    hh.hh_layer_fwd(ctx, cfg, ws, x, y, saved, wsp, L.stream_ptr())
+
+    def bwd():
+        hh.hh_layer_bwd(ctx, cfg, ws, x, saved, dy, dx, gs, 1, wsp, L.stream_ptr())
+
+    bwd()
+    hh.hh_trace_begin(ctx, 200)
+    for _ in range(5):
+        bwd()
+    fam = hh.hh_trace_end(ctx)
+    say("  trace: " + ", ".join("%s %d launches %.3f ms" % (n, v[0], v[1]) for n, v in fam.items()))
+    assert [fam[n][0] for n in ("gemm_nn", "gemm_tn")] == [20, 20]
+    assert fam["gemm_tn"][1] > 1.3 * fam["gemm_nn"][1]
+    # tracing changes neither launches nor results
+    a = torch.empty_like(dx)
+    for traced in (False, True):
+        for t in g.values():
+            t.zero_()
+        if traced:
+            hh.hh_trace_begin(ctx, 200)
+        bwd()
+        if traced:
+            hh.hh_trace_end(ctx)
+        torch.cuda.synchronize()
+        if not traced:
+            a.copy_(dx)
+            b = {n: t.clone() for n, t in g.items()}
+    assert torch.equal(a, dx) and all(torch.equal(b[n], t) for n, t in g.items())
+
+
 def test_profile_records_feed_the_pipeline_predictor(ctx):
     """Section 3.2: the per-layer times measured on this accelerator (and a second, hypothetical type that is 1.5x
     slower) drive the simulator and the layer split."""
