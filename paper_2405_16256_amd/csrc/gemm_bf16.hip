@@ -32,6 +32,7 @@
 // (fp32) vectors along the contiguous dimension of C.
 #include <algorithm>
 #include <climits>
+#include <cstdio>
 #include <cstring>
 
 #include "gemm_ring.h"
@@ -376,6 +377,15 @@ static int device_cus(hipError_t& err) {
     return n;
 }
 
+// k shares of each tile of the last, partial round of `tiles` (1: it is not cut)
+static int tail_shares(const GemmDesc& g, int tiles, int cus) {
+    const int rem = tiles % cus, nk = (g.K + DK - 1) / DK;
+    if (rem == 0 || rem > cus / 2 || !g.ws) return 1;
+    int s = std::min(cus / rem, 8);
+    while (s > 1 && (nk / s < 4 || (size_t)rem * s * DTILE * DTILE * sizeof(float) > g.ws_bytes)) s--;
+    return s;
+}
+
 // Full rounds of one tile per compute unit run as one persistent workgroup per unit.  A last, partial round of R
 // tiles would leave most units idle, so it is cut along k into floor(units / R) shares per tile, which the same
 // workgroups take up after their whole tiles (fp32 partials in `ws`, summed in a fixed order by a small second kernel).
@@ -398,15 +408,8 @@ static hipError_t launch_dma(const GemmDesc* g, int n, hipStream_t st) {
                               q.lda, q.ldb, q.ldc, q.ldr, q.M, q.N, q.accumulate, tiles};
         tiles += ((q.M + DTILE - 1) / DTILE) * ((q.N + DTILE - 1) / DTILE);
     }
-    const int nk = (g[0].K + DK - 1) / DK;
-    int full = tiles, tail = 0, ksplit = 1;
-    const int rem = tiles % NUM_CU;
-    if (rem > 0 && rem <= NUM_CU / 2 && g[0].ws) {
-        int s = NUM_CU / rem;
-        if (s > 8) s = 8;
-        while (s > 1 && (nk / s < 4 || (size_t)rem * s * DTILE * DTILE * sizeof(float) > g[0].ws_bytes)) s--;
-        if (s > 1) { full = tiles - rem; tail = rem; ksplit = s; }
-    }
+    const int ksplit = tail_shares(g[0], tiles, NUM_CU);
+    const int tail = ksplit > 1 ? tiles % NUM_CU : 0, full = tiles - tail;
     // one launch: a persistent workgroup per CU walks the whole tiles and then the k shares of the tail tiles
     const int n_items = full + tail * ksplit;
     kern<<<n_items < NUM_CU ? n_items : NUM_CU, 512, LDS, st>>>(grp, full, n_items, ksplit, (float*)g[0].ws);
@@ -770,3 +773,58 @@ hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st) {
 }
 
 }  // namespace hh
+
+// For tests, not part of the public interface: how problems of these sizes are launched, without launching them.  A problem
+// is kind, M, N, K and the first k of B's second and third segment (0: none).  Writes a line for each of the n problems
+// of a call: "<how> <tile> <k shares>", where <how> is `alone`, `ring` or `tiles256` (together, on that kernel) or
+// `segments` (one after the other, no tile); of 256x256 tiles the shares are those of the last round on 256 CUs.
+static hh::GemmDesc sizes_of(const int* q) {
+    hh::GemmDesc g{};
+    static char somewhere[16];
+    g.kind = q[0]; g.M = q[1]; g.N = q[2]; g.K = q[3]; g.k1 = q[4]; g.k2 = q[5];
+    g.B1 = g.B2 = somewhere;
+    g.out_f32 = g.kind == hh::GEMM_TN;
+    g.ws = somewhere; g.ws_bytes = hh::GEMM_WS_BYTES;
+    return g;
+}
+extern "C" int hh_internal_gemm_plan(const int* problems, int n, char* out, size_t size) {
+    using namespace hh;
+    if (n < 1 || n > DMA_MAX) return -1;
+    GemmDesc g[DMA_MAX];
+    long tiles = 0;
+    for (int i = 0; i < n; i++) {
+        g[i] = sizes_of(problems + 6 * i);
+        tiles += tiles_of(g[i], VARIANTS[V_DMA]);
+    }
+    Route r;
+    route(g, n, r);
+    size_t at = 0;
+    for (int i = 0; i < n; i++) {
+        const bool ring = r.how == Route::RING, together = r.how == Route::TILES256;
+        const int v = ring ? r.group.v : together ? (int)V_DMA : r.each[i].v;
+        const int shares = v == V_DMA ? tail_shares(g[i], (int)(together ? tiles : tiles_of(g[i], VARIANTS[V_DMA])), 256)
+                         : v == V_COUNT ? 1 : ring ? r.group.ksplit[i] : r.each[i].ksplit[0];
+        char tile[32] = "-";
+        if (v < V_COUNT) snprintf(tile, sizeof tile, "%dx%d%s", VARIANTS[v].bm, VARIANTS[v].bn, v == V_128x128_2 ? "/2" : "");
+        const int w = snprintf(out + at, size - at, "%s %s %d\n", ring ? "ring" : together ? "tiles256" : v == V_COUNT ? "segments" : "alone",
+                               tile, shares);
+        if (w < 0 || (size_t)w >= size - at) return -1;
+        at += (size_t)w;
+    }
+    return 0;
+}
+// Whether the weight gradients of a layer are left to one launch at the end: the problems of its three groups, n of each.
+extern "C" int hh_internal_gemm_defer(const int* problems, const int* n) {
+    using namespace hh;
+    GemmDesc g[3][RING_MAX], dw[DMA_MAX];
+    const GemmDesc* const groups[3] = {g[0], g[1], g[2]};
+    int n_dw = 0;
+    for (int i = 0; i < 3; i++) {
+        if (n[i] < 1 || n[i] > RING_MAX) return -1;
+        for (int j = 0; j < n[i]; j++, problems += 6) {
+            g[i][j] = sizes_of(problems);
+            if (j + 1 < n[i] && n_dw < DMA_MAX) dw[n_dw++] = g[i][j];
+        }
+    }
+    return gemm_bf16_defer(dw, n_dw, groups, n);
+}

@@ -1,7 +1,7 @@
-"""Layers whose twelve projections take every tile and k split of the GEMM dispatch, with ragged token counts.
+"""Layers whose projections take many of the tiles and k splits of the GEMM dispatch, with ragged token counts.
 
-Tolerances are those of every bf16 layer test (storage rounding 2^-9 per tensor, fp32 sums); the shapes were chosen by
-evaluating the dispatch rule for each of their projections.
+Tolerances are those of every bf16 layer test (storage rounding 2^-9 per tensor, fp32 sums).  Which launches the bf16 shapes
+take is asked of the library in test_gemm_dispatch.py, which adds layers for those that none of them takes.
 """
 import pytest
 
@@ -19,13 +19,13 @@ def ctx():
 
 
 @pytest.mark.parametrize("shape,packed", [
-    # 64x64 (whole and 4 shares of k), 64x128 (whole and 8 shares), 128x128 two per CU
+    # 64x64 tiles (whole and 4 shares of k) and 64x128 (whole, 4 and 8 shares)
     (I.LayerShape(1024, 4, 128, 2816, 150, 1), True),
     # the same with 70 tokens over grouped heads: single projections of 64 and 128 columns, k of 70 in the weight gradients
     (I.LayerShape(1024, 8, 64, 2816, 35, 2, n_kv_heads=1), False),
-    # 128x256 whole, 128x128 (one per CU) whole and 3 shares
+    # 192x128, 128x128 (one per CU: whole and 3 shares; two per CU: grouped, whole and 3 shares)
     (I.LayerShape(2048, 4, 128, 4096, 520, 1), True),
-    # 128x256 in 4 shares, 64x128 in 4 shares, 256x256 on problems of one or two rows of tiles
+    # 128x128 in 2 and 3 shares, 128x256 in 3 shares and, in a group, whole and in 8
     (I.LayerShape(4096, 8, 128, 5632, 333, 1), True),
     # one token: a single row of C, a single k value in the weight gradients
     (I.LayerShape(2048, 2, 128, 1024, 1, 1), True),
@@ -60,7 +60,8 @@ def test_problems_that_share_a_launch(ctx, shape, packed):
 
 
 @pytest.mark.parametrize("shape", [
-    # 192x128, 192x192 and 192x256 in the forward projections: 333 and 385 rows, one row into a third tile
+    # 192x128 (q|k|v) and 192x192 (gate|up) on 333 rows; 192x256 (both) one row into a seventh tile.  The second layer, 385
+    # rows, takes tiles of 64 and 128 rows.
     I.LayerShape(2048, 32, 128, 11008, 333, 1, n_kv_heads=32),
     I.LayerShape(1024, 24, 128, 5632, 385, 1, n_kv_heads=24),
     I.LayerShape(512, 24, 128, 4096, 1153, 1),
@@ -84,7 +85,7 @@ def test_fp32_problems_that_share_a_launch(ctx, shape, packed):
 
 
 @pytest.mark.parametrize("shape,packed", [
-    # all weight gradients in one launch of 256x256 tiles, with a split last round, from four and from seven problems
+    # all weight gradients in one launch of 256x256 tiles, from four and from seven problems, the last one's in two k shares
     (I.LayerShape(2048, 4, 128, 2048, 1100, 1, n_kv_heads=1), True),
     (I.LayerShape(2048, 4, 128, 2048, 750, 2, n_kv_heads=1), False),
     (I.LayerShape(2048, 16, 128, 2048, 1500, 1, n_kv_heads=4), False),
@@ -92,3 +93,9 @@ def test_fp32_problems_that_share_a_launch(ctx, shape, packed):
 def test_weight_gradients_in_one_launch(ctx, shape, packed):
     from tests.test_gpu_parity import check_layer
     check_layer(ctx, shape, True, 306, packed=packed, label="dW together")
+
+
+# the bf16 layers above
+SHAPES = [(p if isinstance(p, tuple) else (p, True)) for f in (test_every_tile_of_the_gemm_dispatch, test_problems_that_share_a_launch,
+                                                               test_tiles_of_192_rows, test_weight_gradients_in_one_launch)
+          for m in f.pytestmark if m.name == "parametrize" for p in m.args[1]]
