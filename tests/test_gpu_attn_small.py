@@ -28,7 +28,7 @@ def test_edges(ctx, heads, kv_heads, head_dim, seq, batch):
 
 
 def test_more_workgroups_than_cus(ctx):
-    # 257 workgroups of at most 512 queries: one group of waves per query block, two kernels backward
+    # 257 workgroups, each of the 100 queries of a sample: one group of waves per query block, two kernels backward
     from tests.test_gpu_parity import check_layer
     check_layer(ctx, I.LayerShape(64, 1, 64, 64, 100, 257), True, 702, label="attn 257")
 
