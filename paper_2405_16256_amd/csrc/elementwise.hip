@@ -239,7 +239,7 @@ __global__ __launch_bounds__(CSW * WAVE) void k_colsum_reduce(ColSum a, ColSum b
 // (the query heads followed by the key heads).
 template <typename T>
 __global__ __launch_bounds__(TPB) void k_rope(T* __restrict__ qkv, int ld, int Ttok, int S, int nrot, int d,
-                                              const float* __restrict__ table, int table_seq, float sin_sign) {
+                                              const float* __restrict__ table, int table_seq) {
     constexpr int V = Vec<T>::N;
     const int half = d / 2;
     const int vph = half / V;               // vectors per head-half
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(TPB) void k_rope(T* __restrict__ qkv, int ld, int T
     Vec<T>::load(p + half, b);
 #pragma unroll
     for (int e = 0; e < V; e++) {
-        const float c = cs[e], s = sin_sign * sn[e];
+        const float c = cs[e], s = sn[e];
         oa[e] = a[e] * c - b[e] * s;
         ob[e] = b[e] * c + a[e] * s;
     }
@@ -497,14 +497,13 @@ hipError_t colsum_reduce(const ColSum* jobs, int n, int H, int accumulate, hipSt
 }
 
 hipError_t rope(int dtype, void* qkv, int ld, int T, int S, int nrot, int d, const float* table, int table_seq,
-                int backward, hipStream_t st) {
-    const float sgn = backward ? -1.0f : 1.0f;
+                hipStream_t st) {
     if (dtype == DT_BF16) {
         const long n = (long)T * nrot * (d / 2 / Vec<bf16_t>::N);
-        k_rope<bf16_t><<<nblocks(n), TPB, 0, st>>>((bf16_t*)qkv, ld, T, S, nrot, d, table, table_seq, sgn);
+        k_rope<bf16_t><<<nblocks(n), TPB, 0, st>>>((bf16_t*)qkv, ld, T, S, nrot, d, table, table_seq);
     } else {
         const long n = (long)T * nrot * (d / 2 / Vec<float>::N);
-        k_rope<float><<<nblocks(n), TPB, 0, st>>>((float*)qkv, ld, T, S, nrot, d, table, table_seq, sgn);
+        k_rope<float><<<nblocks(n), TPB, 0, st>>>((float*)qkv, ld, T, S, nrot, d, table, table_seq);
     }
     return hipGetLastError();
 }

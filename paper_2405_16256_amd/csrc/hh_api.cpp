@@ -461,7 +461,7 @@ static int layer_fwd_impl(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, c
         for (int i = 0; i < 3; i++) q[i] = desc(GEMM_NT, T, part_w[i], H, xn, H, ws3[i], H, at(qkv, (size_t)part_c[i] * es), Q3);
         HIP_TRY(tgemm(ctx, dt, q, 3, st));
     }
-    TR(HH_TRACE_ELEMENTWISE, 2.0 * T * (A + Akv) * es, rope(dt, qkv, Q3, T, d.S, d.nh + d.nkv, d.d, ctx->rope_table, ctx->rope_seq, 0, st));
+    TR(HH_TRACE_ELEMENTWISE, 2.0 * T * (A + Akv) * es, rope(dt, qkv, Q3, T, d.S, d.nh + d.nkv, d.d, ctx->rope_table, ctx->rope_seq, st));
     TR(HH_TRACE_ATTN_FWD, attn_flop(d), attn_fwd(dt, qkv, Q3, a, lse, d.B, d.S, d.nh, d.nkv, d.d, st));
     HIP_TRY(tgemm(ctx, dt, desc(GEMM_NT, T, H, A, a, A, w->wo, A, h, H, x, H), st));
     TR(HH_TRACE_ELEMENTWISE, 2.0 * T * H * es, rmsnorm_fwd(dt, h, w->g_mlp, hn, r2, T, H, cfg->rms_eps, st));

@@ -55,10 +55,10 @@ struct ColSum { const float* partial; int rows; float* out; };
 hipError_t colsum_reduce(const ColSum* jobs, int n, int H, int accumulate, hipStream_t st);
 
 // In-place rotary embedding of the first nrot heads (query heads, then key heads) of every row of a
-// [T, ld] buffer.  table = cos[table_seq][d/2] followed by sin[table_seq][d/2], table_seq >= S.
-// backward: rotate by -angle.
+// [T, ld] buffer.  table = cos[table_seq][d/2] followed by sin[table_seq][d/2], table_seq >= S.  (The backward rotation is
+// part of attn_bwd.)
 hipError_t rope(int dtype, void* qkv, int ld, int T, int S, int nrot, int d, const float* table, int table_seq,
-                int backward, hipStream_t st);
+                hipStream_t st);
 
 // gu[T,2F] = (gate | up);  m = silu(gate)*up
 hipError_t swiglu_fwd(int dtype, const void* gu, void* m, int T, int F, hipStream_t st);
