@@ -17,8 +17,9 @@
 // for dQ and a key-stationary pass for dK, dV, both recomputing P from the
 // saved log-sum-exp.  On large launches they are two kernels and the dQ pass forms
 // delta[s] = <dO[s], O[s]> for the dK/dV pass; on launches of few workgroups, where
-// each pass alone is bound by its longest job, a small kernel forms delta and one
-// launch deals out the jobs of both passes together.
+// each pass alone is bound by its longest job, one launch deals out the jobs of both
+// passes together: up to 1024 tokens every job forms the delta it needs, above that a
+// small kernel before the launch does.
 //
 // The loops are bound by instruction issue, not by the matrix pipes, so the vector
 // work per tile is kept to the softmax arithmetic itself: LDS addresses are per-lane

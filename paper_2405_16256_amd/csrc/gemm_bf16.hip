@@ -467,8 +467,11 @@ static hipError_t launch_ring(const GemmDesc* g, const int* order, const int* ks
 // the choice costs 1.6 % over the best variant of each problem.  Against one 128x128 register-staged kernel for
 // everything below 64 tiles of 256x256 the problems of that class take half the time (333x4096x11008 NT: 152 -> 50 us,
 // 36x8384x25152 NN: 336 -> 93 us, 128x512x2200 TN: 29 -> 8.5 us).
-// Tiles of 192 rows or columns only take operands with contiguous k (a k row of a strided operand must be a power of two
-// of 16-byte chunks), i.e. NT problems: 333x12288x4096 60 -> 51 us, 333x22016x4096 95 -> 78, 3300x3072x4096 89 -> 83.
+// Tiles of 192 rows are built for NT problems: 333x12288x4096 60 -> 51 us, 333x22016x4096 95 -> 78, 3300x3072x4096 89 -> 83.
+// 192 rows or columns of a k-strided operand cannot be (its k row must be a power of two of 16-byte chunks): that rules
+// out TN, and 192 columns of an NN problem.  192x128 and 192x256 would fit an NN problem; they were never measured there.
+// A round is 256 workgroups here, the CUs of the card in its default partition, where the constants were measured; on fewer
+// the choice is still correct, and only the 256x256 kernel adapts (its workgroups and its split follow the device's CUs).
 struct Variant { int bm, bn, per_cu; bool nt_only; double t0, e, t_one, t_full; };
 enum { V_64x64, V_64x128, V_128x128, V_128x128_2, V_128x256, V_192x128, V_192x192, V_192x256, V_DMA, V_COUNT };
 static constexpr Variant VARIANTS[V_COUNT] = {

@@ -63,7 +63,7 @@ struct FTile {
 // A launch takes a group of up to F32_MAX independent problems (weight gradients beside an input gradient, projections
 // with separate weights), each owning the workgroups first .. first + tiles - 1: alone they are bound by their chain of
 // k stages on a few dozen workgroups.  dWdown | dWgate|up | d(hn) of hidden 256, ffn 688 and 128 tokens in three launches
-// 22.3 us, in one 14; of hidden 1024, ffn 2048 and 700 tokens 171 -> 137; dWo | da there 39.5 -> 30.5.
+// 22.3 us, in one 15.5; of hidden 1024, ffn 2048 and 700 tokens 171 -> 137; dWo | da there 39.5 -> 32.
 constexpr int F32_MAX = 4;
 struct F32Problem {
     const float* A;
