@@ -192,6 +192,12 @@ __device__ __forceinline__ void mfma_stream(L load, M mma, W side) {
     }
 }
 
+// The operand of micro-batch m (blockIdx.y) where consecutive ones lie `stride` bytes apart.
+template <typename T>
+__device__ __forceinline__ T* micro_at(T* p, size_t stride) {
+    return (T*)((uintptr_t)p + blockIdx.y * stride);
+}
+
 // ------------------------------------------------------------------ forward
 // QW waves, each 32 queries of the block's 32 * QW, walk the key tiles; NPAR groups of them repeat the same queries and
 // take every NPAR-th tile each (NPAR tiles per step), so the longest job of the launch -- the last query block -- is
@@ -201,7 +207,9 @@ __device__ __forceinline__ void mfma_stream(L load, M mma, W side) {
 //   QW 2, NPAR 2: one wave per SIMD, for launches that would leave CUs without a workgroup.
 template <int D, int QW, int NPAR>
 __global__ __launch_bounds__(QW * NPAR * WAVE, QW * NPAR == 8 ? 1 : 2) void k_attn_fwd(const bf16_t* __restrict__ qkv, int ld, uint32_t qkv_bytes,
-                                                       bf16_t* __restrict__ o, float* __restrict__ lse, int S, int nh, int nkv, int B) {
+                                                       bf16_t* __restrict__ o, float* __restrict__ lse, int S, int nh, int nkv, int B,
+                                                       MicroStride micro) {
+    qkv = micro_at(qkv, micro.saved); o = micro_at(o, micro.saved); lse = micro_at(lse, micro.saved);
     using TL = Tile<D>;
     constexpr int NW = QW * NPAR;
     constexpr int STAGE = 2 * TL::BYTES;                              // K tile | V tile
@@ -864,7 +872,9 @@ __global__ __launch_bounds__(ATHREADS * NPAR, NPAR == 1 ? 2 : 1) void k_attn_bwd
                                                           const bf16_t* __restrict__ o, const bf16_t* __restrict__ dout, uint32_t do_bytes,
                                                           const float* __restrict__ lse, float* __restrict__ dvec,
                                                           bf16_t* __restrict__ dqkv, int S, int nh, int nkv, int B,
-                                                          const float* __restrict__ rope, int rope_seq) {
+                                                          const float* __restrict__ rope, int rope_seq, MicroStride micro) {
+    qkv = micro_at(qkv, micro.saved); o = micro_at(o, micro.saved); lse = micro_at(lse, micro.saved);
+    dout = micro_at(dout, micro.ws); dvec = micro_at(dvec, micro.ws); dqkv = micro_at(dqkv, micro.ws);
     const int nhb = nh * B;
     attn_bwd_dq_body<D, NPAR, false>((int)(gridDim.x / nhb) - 1 - (int)(blockIdx.x / nhb), blockIdx.x % nhb, qkv, ld, qkv_bytes, o, dout, do_bytes,
                                      lse, dvec, dqkv, S, nh, nkv, B, rope, rope_seq);
@@ -877,7 +887,10 @@ __global__ __launch_bounds__(KVTHREADS) void k_attn_bwd_dkv(const bf16_t* __rest
                                                             const bf16_t* __restrict__ dout, uint32_t do_bytes,
                                                             const float* __restrict__ lse, const float* __restrict__ dvec,
                                                             bf16_t* __restrict__ dqkv, int S, int nh, int nkv, int B,
-                                                            int hs, float* __restrict__ part, const float* __restrict__ rope, int rope_seq) {
+                                                            int hs, float* __restrict__ part, const float* __restrict__ rope, int rope_seq,
+                                                            MicroStride micro) {
+    qkv = micro_at(qkv, micro.saved); lse = micro_at(lse, micro.saved);
+    dout = micro_at(dout, micro.ws); dvec = micro_at(dvec, micro.ws); dqkv = micro_at(dqkv, micro.ws); part = micro_at(part, micro.ws);
     const int nkb = nkv * hs * B;
     attn_bwd_dkv_body<D, true>(blockIdx.x / nkb, blockIdx.x % nkb, qkv, ld, qkv_bytes, nullptr, dout, do_bytes, lse, dvec, dqkv, S, nh, nkv, B, hs, part,
                          rope, rope_seq);
@@ -893,7 +906,10 @@ __global__ __launch_bounds__(KVTHREADS) void k_attn_bwd_both(const bf16_t* __res
                                                              const bf16_t* __restrict__ o, const bf16_t* __restrict__ dout, uint32_t do_bytes,
                                                              const float* __restrict__ lse, float* __restrict__ dvec,
                                                              bf16_t* __restrict__ dqkv, int S, int nh, int nkv, int B,
-                                                             int hs, float* __restrict__ part, const float* __restrict__ rope, int rope_seq) {
+                                                             int hs, float* __restrict__ part, const float* __restrict__ rope, int rope_seq,
+                                                             MicroStride micro) {
+    qkv = micro_at(qkv, micro.saved); o = micro_at(o, micro.saved); lse = micro_at(lse, micro.saved);
+    dout = micro_at(dout, micro.ws); dvec = micro_at(dvec, micro.ws); dqkv = micro_at(dqkv, micro.ws); part = micro_at(part, micro.ws);
     const int nkvj = nkv * hs * B, nqj = nh * B, per = nkvj + nqj;
     const int level = blockIdx.x / per, nblk = gridDim.x / per;
     const int r = blockIdx.x % per;
@@ -907,7 +923,8 @@ __global__ __launch_bounds__(KVTHREADS) void k_attn_bwd_both(const bf16_t* __res
 // 16kk + 8hf .. of the row, in the order and with the arithmetic of the dQ kernel's own delta.
 template <int D>
 __global__ __launch_bounds__(256) void k_attn_delta(const bf16_t* __restrict__ o, const bf16_t* __restrict__ dout, float* __restrict__ dvec,
-                                                    int S, int nh, long rows) {
+                                                    int S, int nh, long rows, MicroStride micro) {
+    o = micro_at(o, micro.saved); dout = micro_at(dout, micro.ws); dvec = micro_at(dvec, micro.ws);
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     const long row = i >> 1;                    // token * nh + head
     const int hf = (int)(i & 1);
@@ -940,7 +957,8 @@ __global__ __launch_bounds__(256) void k_attn_delta(const bf16_t* __restrict__ o
 // out of dK (rope != null: rotation by minus the token's angle; table as in store_rope_bwd).
 __global__ __launch_bounds__(256) void k_attn_dkv_reduce(const float* __restrict__ part, int hs, long tokens, int Akv, int D, int S,
                                                          bf16_t* __restrict__ dqkv, int ld, int A,
-                                                         const float* __restrict__ rope, int rope_seq) {
+                                                         const float* __restrict__ rope, int rope_seq, MicroStride micro) {
+    part = micro_at(part, micro.ws); dqkv = micro_at(dqkv, micro.ws);
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     const int per_tok = Akv / 8, half = D / 2;
     if (i >= tokens * per_tok) return;
@@ -1001,11 +1019,6 @@ size_t attn_bf16_bwd_scratch_bytes(int B, int S, int nh, int nkv, int d) {
     return hs > 1 ? (size_t)hs * 2 * B * S * nkv * d * sizeof(float) : 0;
 }
 
-template <typename K>
-static hipError_t set_lds(K kern, int bytes) {
-    return bytes > 48 * 1024 ? hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) : hipSuccess;
-}
-
 // Longest sequence for which the joint backward launch forms delta itself.
 constexpr int DELTA_MAX = 1024;
 
@@ -1016,12 +1029,14 @@ constexpr int DELTA_MAX = 1024;
 static bool joint_backward(unsigned grid, int S) { return grid <= 256 || (S >= 1024 && grid <= 2 * 256); }
 
 template <int D, int QW, int NPAR>
-static hipError_t launch_fwd(const void* qkv, int ld, uint32_t bytes, void* o, float* lse, int B, int S, int nh, int nkv, hipStream_t st) {
+static hipError_t launch_fwd(const void* qkv, int ld, uint32_t bytes, void* o, float* lse, int B, int S, int nh, int nkv, const MicroStride& micro,
+                             hipStream_t st) {
     constexpr int LDS = 4 * NPAR * Tile<D>::BYTES;
-    hipError_t e = set_lds(k_attn_fwd<D, QW, NPAR>, LDS);
+    static std::atomic<uint64_t> lds_ok{0};
+    const hipError_t e = allow_lds((const void*)k_attn_fwd<D, QW, NPAR>, LDS, lds_ok);
     if (e != hipSuccess) return e;
     const unsigned grid = (unsigned)((S + 32 * QW - 1) / (32 * QW)) * nh * B;
-    k_attn_fwd<D, QW, NPAR><<<grid, QW * NPAR * WAVE, LDS, st>>>((const bf16_t*)qkv, ld, bytes, (bf16_t*)o, lse, S, nh, nkv, B);
+    k_attn_fwd<D, QW, NPAR><<<dim3(grid, micro.n), QW * NPAR * WAVE, LDS, st>>>((const bf16_t*)qkv, ld, bytes, (bf16_t*)o, lse, S, nh, nkv, B, micro);
     return hipGetLastError();
 }
 
@@ -1030,19 +1045,21 @@ static hipError_t launch_fwd(const void* qkv, int ld, uint32_t bytes, void* o, f
 // and values of a head arriving at each CU, 55 KB a microsecond).  With at most four key tiles the merge costs more than
 // the steps: 4 heads x 128 tokens 5.2 us one by one, 6.1 in two groups, 5.7 in four.
 template <int D>
-static hipError_t fwd_d(const void* qkv, int ld, uint32_t bytes, void* o, float* lse, int B, int S, int nh, int nkv, hipStream_t st) {
+static hipError_t fwd_d(const void* qkv, int ld, uint32_t bytes, void* o, float* lse, int B, int S, int nh, int nkv, const MicroStride& micro,
+                        hipStream_t st) {
     const unsigned heads = (unsigned)(nh * B);
-    if (S > 256 && (unsigned)((S + 63) / 64) * heads <= 256) return launch_fwd<D, 2, 2>(qkv, ld, bytes, o, lse, B, S, nh, nkv, st);
-    if (S >= 1024 && (unsigned)((S + 127) / 128) * heads <= 512) return launch_fwd<D, 4, 2>(qkv, ld, bytes, o, lse, B, S, nh, nkv, st);
-    return launch_fwd<D, 4, 1>(qkv, ld, bytes, o, lse, B, S, nh, nkv, st);
+    if (S > 256 && (unsigned)((S + 63) / 64) * heads <= 256) return launch_fwd<D, 2, 2>(qkv, ld, bytes, o, lse, B, S, nh, nkv, micro, st);
+    if (S >= 1024 && (unsigned)((S + 127) / 128) * heads <= 512) return launch_fwd<D, 4, 2>(qkv, ld, bytes, o, lse, B, S, nh, nkv, micro, st);
+    return launch_fwd<D, 4, 1>(qkv, ld, bytes, o, lse, B, S, nh, nkv, micro, st);
 }
 
 template <int D>
 static hipError_t bwd_d(const void* qkv, int ld, uint32_t bytes, const void* o, const void* dout, uint32_t do_bytes,
                         const float* lse, float* dvec, void* dqkv, float* scratch, int B, int S, int nh, int nkv,
-                        const float* rope, int rope_seq, hipStream_t st) {
+                        const float* rope, int rope_seq, const MicroStride& micro, hipStream_t st) {
     constexpr int LDS_KV = 8 * Tile<D>::BYTES + 1024;
-    hipError_t e = set_lds(k_attn_bwd_dkv<D>, LDS_KV);
+    static std::atomic<uint64_t> dkv_ok{0}, both_ok[2], dq_ok{0};
+    hipError_t e = allow_lds((const void*)k_attn_bwd_dkv<D>, LDS_KV, dkv_ok);
     if (e != hipSuccess) return e;
     const unsigned grid = (unsigned)((S + 127) / 128) * nh * B;
     const int hs = dkv_head_slices(B, S, nh, nkv);
@@ -1052,46 +1069,48 @@ static hipError_t bwd_d(const void* qkv, int ld, uint32_t bytes, const void* o, 
         // a launch of its own for delta costs 3 to 4 us; formed in the jobs it is read once per key block (at most 8 here)
         const bool given = S > DELTA_MAX;
         auto kern = given ? k_attn_bwd_both<D, true> : k_attn_bwd_both<D, false>;
-        e = set_lds(kern, LDS_KV);
+        e = allow_lds((const void*)kern, LDS_KV, both_ok[given]);
         if (e != hipSuccess) return e;
         const long rows = (long)B * S * nh;
-        if (given) k_attn_delta<D><<<(unsigned)((2 * rows + 255) / 256), 256, 0, st>>>((const bf16_t*)o, (const bf16_t*)dout, dvec, S, nh, rows);
-        kern<<<grid + grid_kv, KVTHREADS, LDS_KV, st>>>((const bf16_t*)qkv, ld, bytes, (const bf16_t*)o, (const bf16_t*)dout, do_bytes, lse, dvec,
-                                                        (bf16_t*)dqkv, S, nh, nkv, B, hs, scratch, rope, rope_seq);
+        if (given) k_attn_delta<D><<<dim3((unsigned)((2 * rows + 255) / 256), micro.n), 256, 0, st>>>((const bf16_t*)o, (const bf16_t*)dout, dvec, S, nh, rows,
+                                                                                                      micro);
+        kern<<<dim3(grid + grid_kv, micro.n), KVTHREADS, LDS_KV, st>>>((const bf16_t*)qkv, ld, bytes, (const bf16_t*)o, (const bf16_t*)dout, do_bytes, lse, dvec,
+                                                        (bf16_t*)dqkv, S, nh, nkv, B, hs, scratch, rope, rope_seq, micro);
     } else {
         constexpr int LDS = 4 * Tile<D>::BYTES;
-        e = set_lds(k_attn_bwd_dq<D, 1>, LDS);
+        e = allow_lds((const void*)k_attn_bwd_dq<D, 1>, LDS, dq_ok);
         if (e != hipSuccess) return e;
-        k_attn_bwd_dq<D, 1><<<grid, ATHREADS, LDS, st>>>((const bf16_t*)qkv, ld, bytes, (const bf16_t*)o, (const bf16_t*)dout, do_bytes, lse, dvec,
-                                                         (bf16_t*)dqkv, S, nh, nkv, B, rope, rope_seq);
-        k_attn_bwd_dkv<D><<<grid_kv, KVTHREADS, LDS_KV, st>>>((const bf16_t*)qkv, ld, bytes, (const bf16_t*)dout, do_bytes, lse,
-                                                              dvec, (bf16_t*)dqkv, S, nh, nkv, B, hs, scratch, rope, rope_seq);
+        k_attn_bwd_dq<D, 1><<<dim3(grid, micro.n), ATHREADS, LDS, st>>>((const bf16_t*)qkv, ld, bytes, (const bf16_t*)o, (const bf16_t*)dout, do_bytes, lse, dvec,
+                                                         (bf16_t*)dqkv, S, nh, nkv, B, rope, rope_seq, micro);
+        k_attn_bwd_dkv<D><<<dim3(grid_kv, micro.n), KVTHREADS, LDS_KV, st>>>((const bf16_t*)qkv, ld, bytes, (const bf16_t*)dout, do_bytes, lse,
+                                                              dvec, (bf16_t*)dqkv, S, nh, nkv, B, hs, scratch, rope, rope_seq, micro);
     }
     if (hs > 1) {
         const long n = (long)B * S * (nkv * D / 8);
-        k_attn_dkv_reduce<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(scratch, hs, (long)B * S, nkv * D, D, S, (bf16_t*)dqkv, ld, nh * D,
-                                                                       rope, rope_seq);
+        k_attn_dkv_reduce<<<dim3((unsigned)((n + 255) / 256), micro.n), 256, 0, st>>>(scratch, hs, (long)B * S, nkv * D, D, S, (bf16_t*)dqkv, ld, nh * D,
+                                                                       rope, rope_seq, micro);
     }
     return hipGetLastError();
 }
 
-hipError_t attn_bf16_fwd(const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, hipStream_t st) {
+hipError_t attn_bf16_fwd(const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, const MicroStride& micro,
+                         hipStream_t st) {
     const long bytes = (long)B * S * ld * 2;
     if (bytes >= (1L << 32) - (1L << 25)) return hipErrorInvalidValue;
-    if (d == 128) return fwd_d<128>(qkv, ld, (uint32_t)bytes, o, lse, B, S, nh, nkv, st);
-    if (d == 64) return fwd_d<64>(qkv, ld, (uint32_t)bytes, o, lse, B, S, nh, nkv, st);
+    if (d == 128) return fwd_d<128>(qkv, ld, (uint32_t)bytes, o, lse, B, S, nh, nkv, micro, st);
+    if (d == 64) return fwd_d<64>(qkv, ld, (uint32_t)bytes, o, lse, B, S, nh, nkv, micro, st);
     return hipErrorInvalidValue;
 }
 
 hipError_t attn_bf16_bwd(const void* qkv, int ld, const void* o, const void* dout, const float* lse, float* dvec,
                          void* dqkv, float* scratch, int B, int S, int nh, int nkv, int d,
-                         const float* rope, int rope_seq, hipStream_t st) {
+                         const float* rope, int rope_seq, const MicroStride& micro, hipStream_t st) {
     const long bytes = (long)B * S * ld * 2;
     const long do_bytes = (long)B * S * nh * d * 2;
     if (bytes >= (1L << 32) - (1L << 25)) return hipErrorInvalidValue;
     if (rope && rope_seq < S) return hipErrorInvalidValue;
-    if (d == 128) return bwd_d<128>(qkv, ld, (uint32_t)bytes, o, dout, (uint32_t)do_bytes, lse, dvec, dqkv, scratch, B, S, nh, nkv, rope, rope_seq, st);
-    if (d == 64) return bwd_d<64>(qkv, ld, (uint32_t)bytes, o, dout, (uint32_t)do_bytes, lse, dvec, dqkv, scratch, B, S, nh, nkv, rope, rope_seq, st);
+    if (d == 128) return bwd_d<128>(qkv, ld, (uint32_t)bytes, o, dout, (uint32_t)do_bytes, lse, dvec, dqkv, scratch, B, S, nh, nkv, rope, rope_seq, micro, st);
+    if (d == 64) return bwd_d<64>(qkv, ld, (uint32_t)bytes, o, dout, (uint32_t)do_bytes, lse, dvec, dqkv, scratch, B, S, nh, nkv, rope, rope_seq, micro, st);
     return hipErrorInvalidValue;
 }
 

@@ -70,6 +70,15 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
 }
 
+// ---- an operand's address in each of up to N micro-batches, as a kernel argument ----
+// N is 1 for a launch of one micro-batch: a table of one, whose entry is asked for with the other arguments, where an index
+// would have to be formed first (nine launches of a small layer's forward pass: 67.7 us, 70.7 with tables of 8).
+template <int N>
+struct Ops {
+    void* p[N];
+    __device__ __forceinline__ void* at(int m) const { return p[N == 1 ? 0 : m]; }
+};
+
 // ---- dynamic LDS above the 48 KB default -------------------------------------
 // The limit is an attribute of the (kernel, device) pair.  `done` is the calling launcher's own record (one
 // bit per device, one record per kernel instantiation) of where it has been raised already.

@@ -18,8 +18,8 @@ constexpr int NWAVES = TPB / WAVE;
 constexpr int RC = 6;
 
 template <typename T>
-__global__ __launch_bounds__(TPB) void k_rmsnorm_fwd(const T* __restrict__ x, const T* __restrict__ g,
-                                                     T* __restrict__ xn, float* __restrict__ r, int H, float eps) {
+__device__ __forceinline__ void rmsnorm_fwd_body(const T* __restrict__ x, const T* __restrict__ g, T* __restrict__ xn,
+                                                 float* __restrict__ r, int H, float eps) {
     constexpr int V = Vec<T>::N;
     typedef typename Vec<T>::Raw Raw;
     __shared__ float red[NWAVES];
@@ -75,13 +75,33 @@ __global__ __launch_bounds__(TPB) void k_rmsnorm_fwd(const T* __restrict__ x, co
     }
 }
 
+// Micro-batches side by side: blockIdx.y.
+template <int N>
+static Ops<N> ops(const Each& e) {
+    Ops<N> o;
+    for (int m = 0; m < N; m++) o.p[m] = e.p[m];
+    return o;
+}
+template <typename T, int N>
+__global__ __launch_bounds__(TPB) void k_rmsnorm_fwd(Ops<N> x, const T* g, Ops<N> xn, Ops<N> r, int H, float eps) {
+    const int m = blockIdx.y;
+    rmsnorm_fwd_body<T>((const T*)x.at(m), g, (T*)xn.at(m), (float*)r.at(m), H, eps);
+}
+
+// The operands of the backward kernels, one per micro-batch but for the gain.
+template <int N>
+struct NormBwd {
+    Ops<N> dxn, x, r, dres, dx, partial;
+    const void* g;
+    int T, H, rpb, nblk, n;
+};
+
 // RMSNorm backward, rows too long for registers: one workgroup walks `rpb` consecutive rows and reads each twice.
 // Column j is always handled by the same thread, so the per-column sums of dxn*u live in LDS without atomics.
 template <typename T>
-__global__ __launch_bounds__(TPB) void k_rmsnorm_bwd(const T* __restrict__ dxn, const T* __restrict__ x,
-                                                     const float* __restrict__ r, const T* __restrict__ g,
-                                                     const T* __restrict__ dres, T* __restrict__ dx,
-                                                     float* __restrict__ partial, int T_rows, int H, int rpb) {
+__device__ __forceinline__ void rmsnorm_bwd_body(const T* __restrict__ dxn, const T* __restrict__ x, const float* __restrict__ r, const T* __restrict__ g,
+                                                 const T* __restrict__ dres, T* __restrict__ dx, float* __restrict__ partial,
+                                                 int T_rows, int H, int rpb) {
     constexpr int V = Vec<T>::N;
     extern __shared__ float colacc[];  // [H]
     __shared__ float red[NWAVES];
@@ -125,6 +145,13 @@ __global__ __launch_bounds__(TPB) void k_rmsnorm_bwd(const T* __restrict__ dxn, 
         for (int e = 0; e < V; e++) out[c + e] = colacc[c + e];
 }
 
+template <typename T, int N>
+__global__ __launch_bounds__(TPB) void k_rmsnorm_bwd(NormBwd<N> a) {
+    const int m = blockIdx.y;
+    rmsnorm_bwd_body<T>((const T*)a.dxn.at(m), (const T*)a.x.at(m), (const float*)a.r.at(m), (const T*)a.g, (const T*)a.dres.at(m),
+                        (T*)a.dx.at(m), (float*)a.partial.at(m), a.T, a.H, a.rpb);
+}
+
 // RMSNorm backward, short rows (at most NV * 64 * V elements): one wave per row, no barrier until the end; a lane's
 // columns are the same in every row, so their sums stay in registers and the waves' sums meet in LDS once, in a fixed
 // order.  Bound by latency: one row at a time per workgroup of 256 threads, most of them idle, took 9.6-11.3 us for
@@ -132,10 +159,9 @@ __global__ __launch_bounds__(TPB) void k_rmsnorm_bwd(const T* __restrict__ dxn, 
 // 3.0-4.2 and 4.8 us.
 constexpr int RW = 8;   // waves per workgroup
 template <typename T, int NV>
-__global__ __launch_bounds__(RW * WAVE) void k_rmsnorm_bwd_wave(const T* __restrict__ dxn, const T* __restrict__ x,
-                                                                const float* __restrict__ r, const T* __restrict__ g,
-                                                                const T* __restrict__ dres, T* __restrict__ dx,
-                                                                float* __restrict__ partial, int T_rows, int H, int rpb) {
+__device__ __forceinline__ void rmsnorm_bwd_wave_body(const T* __restrict__ dxn, const T* __restrict__ x, const float* __restrict__ r, const T* __restrict__ g,
+                                                      const T* __restrict__ dres, T* __restrict__ dx, float* __restrict__ partial,
+                                                      int T_rows, int H, int rpb) {
     constexpr int V = Vec<T>::N;
     extern __shared__ float colsum[];  // [RW][H]
     const int wave = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
@@ -198,47 +224,68 @@ __global__ __launch_bounds__(RW * WAVE) void k_rmsnorm_bwd_wave(const T* __restr
     }
 }
 
+template <typename T, int NV, int N>
+__global__ __launch_bounds__(RW * WAVE) void k_rmsnorm_bwd_wave(NormBwd<N> a) {
+    const int m = blockIdx.y;
+    rmsnorm_bwd_wave_body<T, NV>((const T*)a.dxn.at(m), (const T*)a.x.at(m), (const float*)a.r.at(m), (const T*)a.g, (const T*)a.dres.at(m),
+                                 (T*)a.dx.at(m), (float*)a.partial.at(m), a.T, a.H, a.rpb);
+}
+
 // out[j] (=|+=) sum_b partial[b][j] of one or two gain gradients (blockIdx.y).  A workgroup covers 64 columns (a float4
 // per lane, 16 lanes a row) with 64 row groups, combined by shuffles and through LDS in a fixed order: at most 256
 // partial rows are then one batch of loads per thread, and a row of 4096 is spread over 64 CUs.  Both sums at 256 x 12288
 // and at 254 x 4096: 12.8 and 11.8 us as two launches of 256 columns a workgroup, 7.6 and 6.0 us as this one.
 constexpr int CSW = 16;   // waves of a workgroup
-__global__ __launch_bounds__(CSW * WAVE) void k_colsum_reduce(ColSum a, ColSum b, int H, int accumulate) {
-    __shared__ float4 red[CSW][16];
-    const ColSum& j = blockIdx.y ? b : a;
+template <int N>
+struct ColSums {
+    struct { Ops<N> partial; int rows; float* out; } j[2];
+};
+template <int N>
+__global__ __launch_bounds__(CSW * WAVE) void k_colsum_reduce(ColSums<N> sums, int n, int H, int accumulate) {
+    __shared__ float4 red[2][CSW][16];
+    const auto& j = sums.j[blockIdx.y];
     const int cx = threadIdx.x % 16, wave = threadIdx.x / WAVE;
     const int col = (blockIdx.x * 16 + cx) * 4;
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (col < H) {
-        const float* p = j.partial + col;
+    const bool owner = threadIdx.x < 16 && col < H;
+    float4* const out = reinterpret_cast<float4*>(j.out + col);
+    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (owner && accumulate) sum = *out;
+    for (int m = 0; m < (N == 1 ? 1 : n); m++) {   // each micro-batch's sum is added to those before it, as n calls would
+        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (col < H) {
+            const float* p = (const float*)j.partial.at(m) + col;
 #pragma unroll 4
-        for (int i = threadIdx.x / 16; i < j.rows; i += CSW * WAVE / 16) {
-            const float4 v = *reinterpret_cast<const float4*>(p + (size_t)i * H);
-            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+            for (int i = threadIdx.x / 16; i < j.rows; i += CSW * WAVE / 16) {
+                const float4 v = *reinterpret_cast<const float4*>(p + (size_t)i * H);
+                s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+            }
+        }
+#pragma unroll
+        for (int o = 16; o < WAVE; o *= 2) {
+            s.x += __shfl_xor(s.x, o, WAVE); s.y += __shfl_xor(s.y, o, WAVE);
+            s.z += __shfl_xor(s.z, o, WAVE); s.w += __shfl_xor(s.w, o, WAVE);
+        }
+        if ((threadIdx.x & (WAVE - 1)) < 16) red[m & 1][wave][cx] = s;
+        __syncthreads();   // red[m & 1] is written again two barriers after its readers
+        if (owner) {
+            float4 t = red[m & 1][0][cx];
+#pragma unroll
+            for (int i = 1; i < CSW; i++) {
+                const float4 v = red[m & 1][i][cx];
+                t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w;
+            }
+            if (accumulate || m) { sum.x = t.x + sum.x; sum.y = t.y + sum.y; sum.z = t.z + sum.z; sum.w = t.w + sum.w; }
+            else sum = t;
         }
     }
-#pragma unroll
-    for (int o = 16; o < WAVE; o *= 2) {
-        s.x += __shfl_xor(s.x, o, WAVE); s.y += __shfl_xor(s.y, o, WAVE);
-        s.z += __shfl_xor(s.z, o, WAVE); s.w += __shfl_xor(s.w, o, WAVE);
-    }
-    if ((threadIdx.x & (WAVE - 1)) < 16) red[wave][cx] = s;
-    __syncthreads();
-    if (threadIdx.x < 16 && col < H) {
-        float4 t = red[0][cx];
-#pragma unroll
-        for (int i = 1; i < CSW; i++) { t.x += red[i][cx].x; t.y += red[i][cx].y; t.z += red[i][cx].z; t.w += red[i][cx].w; }
-        float4* o = reinterpret_cast<float4*>(j.out + col);
-        if (accumulate) { const float4 old = *o; t.x += old.x; t.y += old.y; t.z += old.z; t.w += old.w; }
-        *o = t;
-    }
+    if (owner) *out = sum;
 }
 
 // --------------------------------------------------------------------- RoPE
 // One thread rotates V pairs (i, i + d/2) of one of the nrot heads that start at column 0 of a token's row
 // (the query heads followed by the key heads).
-template <typename T>
-__global__ __launch_bounds__(TPB) void k_rope(T* __restrict__ qkv, int ld, int Ttok, int S, int nrot, int d,
+template <typename T, int N>
+__global__ __launch_bounds__(TPB) void k_rope(Ops<N> qkv, int ld, int Ttok, int S, int nrot, int d,
                                               const float* __restrict__ table, int table_seq) {
     constexpr int V = Vec<T>::N;
     const int half = d / 2;
@@ -251,7 +298,7 @@ __global__ __launch_bounds__(TPB) void k_rope(T* __restrict__ qkv, int ld, int T
     const int head = (int)(rest % nrot);
     const int t = (int)(rest / nrot);
     const int pos = t % S;
-    T* p = qkv + (size_t)t * ld + (size_t)head * d + iv * V;
+    T* p = (T*)qkv.at(blockIdx.y) + (size_t)t * ld + (size_t)head * d + iv * V;
     const float* cs = table + ((size_t)pos * half + iv * V);
     const float* sn = cs + (size_t)table_seq * half;
     float a[V], b[V], oa[V], ob[V];
@@ -268,9 +315,11 @@ __global__ __launch_bounds__(TPB) void k_rope(T* __restrict__ qkv, int ld, int T
 }
 
 // ------------------------------------------------------------------- SwiGLU
-template <typename T>
-__global__ __launch_bounds__(TPB) void k_swiglu_fwd(const T* __restrict__ gu, T* __restrict__ m, int Ttok, int F) {
+template <typename T, int N>
+__global__ __launch_bounds__(TPB) void k_swiglu_fwd(Ops<N> gu_, Ops<N> m_, int Ttok, int F) {
     constexpr int V = Vec<T>::N;
+    const T* gu = (const T*)gu_.at(blockIdx.y);
+    T* m = (T*)m_.at(blockIdx.y);
     const int vpr = F / V;
     const long idx = (long)blockIdx.x * TPB + threadIdx.x;
     if (idx >= (long)Ttok * vpr) return;
@@ -283,10 +332,11 @@ __global__ __launch_bounds__(TPB) void k_swiglu_fwd(const T* __restrict__ gu, T*
     Vec<T>::store(m + (size_t)t * F + c, o);
 }
 
-template <typename T>
-__global__ __launch_bounds__(TPB) void k_swiglu_bwd(const T* __restrict__ dm, const T* __restrict__ gu,
-                                                    T* __restrict__ dgu, T* __restrict__ m, int Ttok, int F) {
+template <typename T, int N>
+__global__ __launch_bounds__(TPB) void k_swiglu_bwd(Ops<N> dm_, Ops<N> gu_, Ops<N> dgu_, Ops<N> m_, int Ttok, int F) {
     constexpr int V = Vec<T>::N;
+    const T *dm = (const T*)dm_.at(blockIdx.y), *gu = (const T*)gu_.at(blockIdx.y);
+    T *dgu = (T*)dgu_.at(blockIdx.y), *m = (T*)m_.at(blockIdx.y);
     const int vpr = F / V;
     const long idx = (long)blockIdx.x * TPB + threadIdx.x;
     if (idx >= (long)Ttok * vpr) return;
@@ -311,12 +361,16 @@ __global__ __launch_bounds__(TPB) void k_swiglu_bwd(const T* __restrict__ dm, co
 // ---------------------------------------------------------------- launchers
 static inline unsigned nblocks(long n) { return (unsigned)((n + TPB - 1) / TPB); }
 
-hipError_t rmsnorm_fwd(int dtype, const void* x, const void* g, void* xn, float* r, int T, int H, float eps,
+template <typename T>
+static void rmsnorm_fwd_t(const Each& x, const void* g, const Each& xn, const Each& r, int n, int T_, int H, float eps, hipStream_t st) {
+    if (n == 1) k_rmsnorm_fwd<T, 1><<<T_, TPB, 0, st>>>(ops<1>(x), (const T*)g, ops<1>(xn), ops<1>(r), H, eps);
+    else if constexpr (sizeof(T) == 2)   // fp32 micro-batches come one by one
+        k_rmsnorm_fwd<T, MICRO_MAX><<<dim3(T_, n), TPB, 0, st>>>(ops<MICRO_MAX>(x), (const T*)g, ops<MICRO_MAX>(xn), ops<MICRO_MAX>(r), H, eps);
+}
+hipError_t rmsnorm_fwd(int dtype, const Each& x, const void* g, const Each& xn, const Each& r, int n, int T, int H, float eps,
                        hipStream_t st) {
-    if (dtype == DT_BF16)
-        k_rmsnorm_fwd<bf16_t><<<T, TPB, 0, st>>>((const bf16_t*)x, (const bf16_t*)g, (bf16_t*)xn, r, H, eps);
-    else
-        k_rmsnorm_fwd<float><<<T, TPB, 0, st>>>((const float*)x, (const float*)g, (float*)xn, r, H, eps);
+    if (dtype == DT_BF16) rmsnorm_fwd_t<bf16_t>(x, g, xn, r, n, T, H, eps, st);
+    else rmsnorm_fwd_t<float>(x, g, xn, r, n, T, H, eps, st);
     return hipGetLastError();
 }
 
@@ -327,10 +381,9 @@ __device__ __forceinline__ void keep_raw(uint4& v) { asm volatile("" : "+v"(v.x)
 __device__ __forceinline__ void keep_raw(float4& v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
 
 template <typename T, int NV, bool GUARD>
-__global__ __launch_bounds__(TPB, 2) void k_rmsnorm_bwd_rows(const T* __restrict__ dxn, const T* __restrict__ x,
-                                                          const float* __restrict__ r, const T* __restrict__ g,
-                                                          const T* __restrict__ dres, T* __restrict__ dx,
-                                                          float* __restrict__ partial, int T_rows, int H_, int rpb) {
+__device__ __forceinline__ void rmsnorm_bwd_rows_body(const T* __restrict__ dxn, const T* __restrict__ x, const float* __restrict__ r, const T* __restrict__ g,
+                                                      const T* __restrict__ dres, T* __restrict__ dx, float* __restrict__ partial,
+                                                      int T_rows, int H_, int rpb) {
     constexpr int V = Vec<T>::N;
     const int H = GUARD ? H_ : NV * TPB * V;
     typedef typename Vec<T>::Raw Raw;
@@ -428,22 +481,23 @@ __global__ __launch_bounds__(TPB, 2) void k_rmsnorm_bwd_rows(const T* __restrict
     }
 }
 
-struct NormBwd {
-    const void* dxn; const void* x; const float* r; const void* g; const void* dres; void* dx; float* partial;
-    int T, H, rpb, nblk;
-};
-template <typename T, int NV, bool GUARD>
-static hipError_t launch_rows(const NormBwd& a, hipStream_t st) {
+template <typename T, int NV, bool GUARD, int N>
+__global__ __launch_bounds__(TPB, 2) void k_rmsnorm_bwd_rows(NormBwd<N> a) {
+    const int m = blockIdx.y;
+    rmsnorm_bwd_rows_body<T, NV, GUARD>((const T*)a.dxn.at(m), (const T*)a.x.at(m), (const float*)a.r.at(m), (const T*)a.g, (const T*)a.dres.at(m),
+                                        (T*)a.dx.at(m), (float*)a.partial.at(m), a.T, a.H, a.rpb);
+}
+
+template <typename T, int NV, bool GUARD, int N>
+static hipError_t launch_rows(const NormBwd<N>& a, hipStream_t st) {
     const int lds = a.H * (int)sizeof(float);   // at most 48 KB
-    k_rmsnorm_bwd_rows<T, NV, GUARD><<<a.nblk, TPB, lds, st>>>((const T*)a.dxn, (const T*)a.x, a.r, (const T*)a.g, (const T*)a.dres,
-                                                               (T*)a.dx, a.partial, a.T, a.H, a.rpb);
+    k_rmsnorm_bwd_rows<T, NV, GUARD, N><<<dim3(a.nblk, a.n), TPB, lds, st>>>(a);
     return hipGetLastError();
 }
-template <typename T, int NV>
-static hipError_t launch_wave(const NormBwd& a, hipStream_t st) {
+template <typename T, int NV, int N>
+static hipError_t launch_wave(const NormBwd<N>& a, hipStream_t st) {
     const int lds = RW * a.H * (int)sizeof(float);   // at most 32 KB
-    k_rmsnorm_bwd_wave<T, NV><<<a.nblk, RW * WAVE, lds, st>>>((const T*)a.dxn, (const T*)a.x, a.r, (const T*)a.g, (const T*)a.dres,
-                                                              (T*)a.dx, a.partial, a.T, a.H, a.rpb);
+    k_rmsnorm_bwd_wave<T, NV, N><<<dim3(a.nblk, a.n), RW * WAVE, lds, st>>>(a);
     return hipGetLastError();
 }
 
@@ -460,8 +514,8 @@ int rmsnorm_bwd_blocks(int T, int H, size_t partial_bytes) {
     return (T + rpb - 1) / rpb;
 }
 
-template <typename T>
-static hipError_t rmsnorm_bwd_t(const NormBwd& a, hipStream_t st) {
+template <typename T, int N>
+static hipError_t rmsnorm_bwd_t(const NormBwd<N>& a, hipStream_t st) {
     constexpr int V = Vec<T>::N;
     // a wave per row up to two vectors a lane, a workgroup per row beyond (four times the threads at work on a row)
     if (a.H <= WAVE * V) return launch_wave<T, 1>(a, st);
@@ -477,52 +531,74 @@ static hipError_t rmsnorm_bwd_t(const NormBwd& a, hipStream_t st) {
     }
     const int lds = a.H * (int)sizeof(float);
     static std::atomic<uint64_t> lds_ok{0};
-    const hipError_t e = allow_lds((const void*)k_rmsnorm_bwd<T>, 32768 * (int)sizeof(float), lds_ok);
+    const hipError_t e = allow_lds((const void*)k_rmsnorm_bwd<T, N>, 32768 * (int)sizeof(float), lds_ok);
     if (e != hipSuccess) return e;
-    k_rmsnorm_bwd<T><<<a.nblk, TPB, lds, st>>>((const T*)a.dxn, (const T*)a.x, a.r, (const T*)a.g, (const T*)a.dres, (T*)a.dx,
-                                               a.partial, a.T, a.H, a.rpb);
+    k_rmsnorm_bwd<T, N><<<dim3(a.nblk, a.n), TPB, lds, st>>>(a);
     return hipGetLastError();
 }
 
-hipError_t rmsnorm_bwd(int dtype, const void* dxn, const void* x, const float* r, const void* g, const void* dres,
-                       void* dx, float* partial, size_t partial_bytes, int T, int H, hipStream_t st) {
-    NormBwd a{dxn, x, r, g, dres, dx, partial, T, H, rms_rows_per_block(T, H, partial_bytes), 0};
+template <int N>
+static hipError_t rmsnorm_bwd_n(int dtype, const Each& dxn, const Each& x, const Each& r, const void* g, const Each& dres,
+                                const Each& dx, const Each& partial, size_t partial_bytes, int n, int T, int H, hipStream_t st) {
+    NormBwd<N> a{ops<N>(dxn), ops<N>(x), ops<N>(r), ops<N>(dres), ops<N>(dx), ops<N>(partial), g, T, H, rms_rows_per_block(T, H, partial_bytes),
+                 0, n};
     a.nblk = (T + a.rpb - 1) / a.rpb;
-    return dtype == DT_BF16 ? rmsnorm_bwd_t<bf16_t>(a, st) : rmsnorm_bwd_t<float>(a, st);
+    if constexpr (N == 1) if (dtype != DT_BF16) return rmsnorm_bwd_t<float>(a, st);
+    return rmsnorm_bwd_t<bf16_t>(a, st);
+}
+hipError_t rmsnorm_bwd(int dtype, const Each& dxn, const Each& x, const Each& r, const void* g, const Each& dres,
+                       const Each& dx, const Each& partial, size_t partial_bytes, int n, int T, int H, hipStream_t st) {
+    return n == 1 ? rmsnorm_bwd_n<1>(dtype, dxn, x, r, g, dres, dx, partial, partial_bytes, n, T, H, st)
+                  : rmsnorm_bwd_n<MICRO_MAX>(dtype, dxn, x, r, g, dres, dx, partial, partial_bytes, n, T, H, st);
 }
 
-hipError_t colsum_reduce(const ColSum* jobs, int n, int H, int accumulate, hipStream_t st) {
-    k_colsum_reduce<<<dim3((H + 63) / 64, n), CSW * WAVE, 0, st>>>(jobs[0], jobs[n - 1], H, accumulate);
-    return hipGetLastError();
-}
-
-hipError_t rope(int dtype, void* qkv, int ld, int T, int S, int nrot, int d, const float* table, int table_seq,
-                hipStream_t st) {
-    if (dtype == DT_BF16) {
-        const long n = (long)T * nrot * (d / 2 / Vec<bf16_t>::N);
-        k_rope<bf16_t><<<nblocks(n), TPB, 0, st>>>((bf16_t*)qkv, ld, T, S, nrot, d, table, table_seq);
-    } else {
-        const long n = (long)T * nrot * (d / 2 / Vec<float>::N);
-        k_rope<float><<<nblocks(n), TPB, 0, st>>>((float*)qkv, ld, T, S, nrot, d, table, table_seq);
+template <int N>
+static void colsum_n(const ColSum* jobs, int n_jobs, int n, int H, int accumulate, hipStream_t st) {
+    ColSums<N> s;
+    for (int i = 0; i < 2; i++) {
+        const ColSum& q = jobs[std::min(i, n_jobs - 1)];
+        s.j[i] = {ops<N>(q.partial), q.rows, q.out};
     }
+    k_colsum_reduce<N><<<dim3((H + 63) / 64, n_jobs), CSW * WAVE, 0, st>>>(s, n, H, accumulate);
+}
+hipError_t colsum_reduce(const ColSum* jobs, int n_jobs, int n, int H, int accumulate, hipStream_t st) {
+    if (n == 1) colsum_n<1>(jobs, n_jobs, n, H, accumulate, st);
+    else colsum_n<MICRO_MAX>(jobs, n_jobs, n, H, accumulate, st);
     return hipGetLastError();
 }
 
-hipError_t swiglu_fwd(int dtype, const void* gu, void* m, int T, int F, hipStream_t st) {
-    if (dtype == DT_BF16)
-        k_swiglu_fwd<bf16_t><<<nblocks((long)T * (F / 8)), TPB, 0, st>>>((const bf16_t*)gu, (bf16_t*)m, T, F);
-    else
-        k_swiglu_fwd<float><<<nblocks((long)T * (F / 4)), TPB, 0, st>>>((const float*)gu, (float*)m, T, F);
+template <typename T, int N>
+static void rope_t(const Each& qkv, int ld, int n, int Ttok, int S, int nrot, int d, const float* table, int table_seq, hipStream_t st) {
+    const long vecs = (long)Ttok * nrot * (d / 2 / Vec<T>::N);
+    k_rope<T, N><<<dim3(nblocks(vecs), n), TPB, 0, st>>>(ops<N>(qkv), ld, Ttok, S, nrot, d, table, table_seq);
+}
+hipError_t rope(int dtype, const Each& qkv, int ld, int n, int T, int S, int nrot, int d, const float* table, int table_seq,
+                hipStream_t st) {
+    if (dtype != DT_BF16) rope_t<float, 1>(qkv, ld, 1, T, S, nrot, d, table, table_seq, st);
+    else if (n == 1) rope_t<bf16_t, 1>(qkv, ld, n, T, S, nrot, d, table, table_seq, st);
+    else rope_t<bf16_t, MICRO_MAX>(qkv, ld, n, T, S, nrot, d, table, table_seq, st);
     return hipGetLastError();
 }
 
-hipError_t swiglu_bwd(int dtype, const void* dm, const void* gu, void* dgu, void* m, int T, int F, hipStream_t st) {
-    if (dtype == DT_BF16)
-        k_swiglu_bwd<bf16_t><<<nblocks((long)T * (F / 8)), TPB, 0, st>>>((const bf16_t*)dm, (const bf16_t*)gu,
-                                                                          (bf16_t*)dgu, (bf16_t*)m, T, F);
-    else
-        k_swiglu_bwd<float><<<nblocks((long)T * (F / 4)), TPB, 0, st>>>((const float*)dm, (const float*)gu,
-                                                                         (float*)dgu, (float*)m, T, F);
+template <typename T, int N>
+static void swiglu_fwd_t(const Each& gu, const Each& m, int n, int Ttok, int F, hipStream_t st) {
+    k_swiglu_fwd<T, N><<<dim3(nblocks((long)Ttok * (F / Vec<T>::N)), n), TPB, 0, st>>>(ops<N>(gu), ops<N>(m), Ttok, F);
+}
+hipError_t swiglu_fwd(int dtype, const Each& gu, const Each& m, int n, int T, int F, hipStream_t st) {
+    if (dtype != DT_BF16) swiglu_fwd_t<float, 1>(gu, m, 1, T, F, st);
+    else if (n == 1) swiglu_fwd_t<bf16_t, 1>(gu, m, n, T, F, st);
+    else swiglu_fwd_t<bf16_t, MICRO_MAX>(gu, m, n, T, F, st);
+    return hipGetLastError();
+}
+
+template <typename T, int N>
+static void swiglu_bwd_t(const Each& dm, const Each& gu, const Each& dgu, const Each& m, int n, int Ttok, int F, hipStream_t st) {
+    k_swiglu_bwd<T, N><<<dim3(nblocks((long)Ttok * (F / Vec<T>::N)), n), TPB, 0, st>>>(ops<N>(dm), ops<N>(gu), ops<N>(dgu), ops<N>(m), Ttok, F);
+}
+hipError_t swiglu_bwd(int dtype, const Each& dm, const Each& gu, const Each& dgu, const Each& m, int n, int T, int F, hipStream_t st) {
+    if (dtype != DT_BF16) swiglu_bwd_t<float, 1>(dm, gu, dgu, m, 1, T, F, st);
+    else if (n == 1) swiglu_bwd_t<bf16_t, 1>(dm, gu, dgu, m, n, T, F, st);
+    else swiglu_bwd_t<bf16_t, MICRO_MAX>(dm, gu, dgu, m, n, T, F, st);
     return hipGetLastError();
 }
 

@@ -417,15 +417,15 @@ static hipError_t launch_dma(const GemmDesc* g, int n, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <bool BWD, int BM, int BN, int WM, int WN, int NS>
-static hipError_t launch_ring(const GemmDesc* g, const int* order, const int* ksplit, int n, hipStream_t st) {
+template <bool BWD, int MB, int BM, int BN, int WM, int WN, int NS>
+static hipError_t launch_ring_n(const GemmDesc* g, const int* order, const int* ksplit, int n, hipStream_t st) {
     constexpr int LDS = NS * (BM + BN) * DK * 2;
     static std::atomic<uint64_t> lds_ok{0};
-    auto kern = k_gemm_ring<BWD, BM, BN, WM, WN, NS>;
+    auto kern = k_gemm_ring<BWD, MB, BM, BN, WM, WN, NS>;
     const hipError_t e = allow_lds((const void*)kern, LDS, lds_ok);
     if (e != hipSuccess) return e;
-    RingGroup grp{};
-    RingReduce red{};
+    RingGroup<MB> grp{};
+    RingReduce<MB> red{};
     grp.n = n;
     red.bm = BM; red.bn = BN;
     int first = 0, red_first = 0;
@@ -433,9 +433,15 @@ static hipError_t launch_ring(const GemmDesc* g, const int* order, const int* ks
     for (int i = 0; i < n; i++) {
         const GemmDesc& q = g[order[i]];
         const int s = ksplit[order[i]];
-        RingProblem& p = grp.p[i];
+        RingProblem<MB>& p = grp.p[i];
         const int nk = (q.K + DK - 1) / DK;
-        p.A = (const bf16_t*)q.A; p.B = (const bf16_t*)q.B; p.C = q.C; p.R = (const bf16_t*)q.R;
+        if constexpr (MB == 1) {
+            p.A.p[0] = const_cast<void*>(q.A); p.B.p[0] = const_cast<void*>(q.B); p.C.p[0] = q.C; p.R.p[0] = const_cast<void*>(q.R);
+        } else {
+            for (int m = 0; m < MB; m++) {
+                p.A.p[m] = q.each->A.p[m]; p.B.p[m] = q.each->B.p[m]; p.C.p[m] = q.each->C.p[m]; p.R.p[m] = q.each->R.p[m];
+            }
+        }
         p.kseg[0] = q.k1 ? q.k1 / DK : INT_MAX; p.kseg[1] = q.k2 ? q.k2 / DK : INT_MAX;
         p.Bseg[0] = (const bf16_t*)q.B1; p.Bseg[1] = (const bf16_t*)q.B2;
         p.a_bytes = (uint32_t)extent_a(q); p.b_bytes = (uint32_t)extent_b(q, q.k1 ? q.k1 : q.K);
@@ -444,18 +450,27 @@ static hipError_t launch_ring(const GemmDesc* g, const int* order, const int* ks
         p.tiles = ((q.M + BM - 1) / BM) * ((q.N + BN - 1) / BN);
         p.ksplit = s;
         p.first = first;
-        first += p.tiles * s;
+        p.micro = q.micro;
+        p.seq = q.kind == GEMM_TN && s == 1 ? q.micro : 1;
+        first += p.tiles * s * (q.micro / p.seq);
         if (s > 1) {
             if (nk < s) return hipErrorInvalidValue;
             p.partial = partial;
-            partial += (size_t)p.tiles * s * BM * BN;
-            red.j[red.n++] = RingReduce::Job{p.partial, q.C, p.R, s, q.ldc, q.ldr, q.M, q.N, q.accumulate, q.out_f32, red_first};
-            red_first += (int)(((long)q.M * (q.N / 4) + 255) / 256);
+            partial += (size_t)p.tiles * s * q.micro * BM * BN;
+            const int blocks = (int)(((long)q.M * (q.N / 4) + 255) / 256);
+            red.j[red.n++] = typename RingReduce<MB>::Job{p.C, p.R, p.partial, s, q.ldc, q.ldr, q.M, q.N, q.accumulate, q.out_f32, red_first, q.micro, blocks};
+            red_first += blocks * (q.out_f32 ? 1 : q.micro);
         }
     }
     kern<<<first, WM * WN * 64, LDS, st>>>(grp);
-    if (red.n) k_ring_reduce<<<red_first, 256, 0, st>>>(red);
+    if (red.n) k_ring_reduce<MB><<<red_first, 256, 0, st>>>(red);
     return hipGetLastError();
+}
+
+template <bool BWD, int BM, int BN, int WM, int WN, int NS>
+static hipError_t launch_ring(const GemmDesc* g, const int* order, const int* ksplit, int n, hipStream_t st) {
+    return g[0].micro == 1 ? launch_ring_n<BWD, 1, BM, BN, WM, WN, NS>(g, order, ksplit, n, st)
+                           : launch_ring_n<BWD, MICRO_MAX, BM, BN, WM, WN, NS>(g, order, ksplit, n, st);
 }
 
 // Which kernel, tile and k split: the smallest predicted time over the variants below.  A launch of W workgroups runs
@@ -751,6 +766,25 @@ bool gemm_bf16_shares_launch(const GemmDesc* g, int n) {
     return r.how != Route::APART;
 }
 
+// Whether the launches that `n` problems take can take them for several micro-batches at once (only the ring kernel does),
+// and what partial sums those launches keep for each micro-batch.
+bool gemm_bf16_micro_bytes(const GemmDesc* g, int n, size_t* bytes) {
+    if (n < 1 || n > RING_MAX) return false;
+    Route r;
+    route(g, n, r);
+    if (r.how == Route::TILES256 || (r.how == Route::RING && r.group.v >= V_DMA)) return false;
+    size_t total = 0;
+    for (int i = 0; i < n; i++) {
+        const Plan& p = r.how == Route::RING ? r.group : r.each[i];
+        if (p.v >= V_DMA) return false;
+        const int s = p.ksplit[r.how == Route::RING ? i : 0];
+        const size_t b = s > 1 ? (size_t)tiles_of(g[i], VARIANTS[p.v]) * s * VARIANTS[p.v].bm * VARIANTS[p.v].bn * sizeof(float) : 0;
+        total = r.how == Route::RING ? total + b : std::max(total, b);
+    }
+    *bytes = total;
+    return true;
+}
+
 hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st) {
     if (n < 1 || n > DMA_MAX) return hipErrorInvalidValue;
     for (int i = 0; i < n; i++) {
@@ -761,6 +795,9 @@ hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st) {
     }
     Route r;
     route(g, n, r);
+    for (int i = 0; i < n; i++)   // several micro-batches: what gemm_bf16_micro_bytes allows
+        if (g[i].micro < 1 || g[i].micro > MICRO_MAX || g[i].micro != g[0].micro || (g[i].micro > 1 && (!g[i].each || r.how == Route::TILES256 || (r.how == Route::RING ? r.group.v : r.each[i].v) >= V_DMA)))
+            return hipErrorInvalidValue;
     if (r.how == Route::RING) return launch_planned(g, n, r.group, st);
     if (r.how == Route::TILES256) return launch_tiles256(g, n, st);
     for (int i = 0; i < n; i++) {
@@ -788,6 +825,7 @@ static hh::GemmDesc sizes_of(const int* q) {
     g.B1 = g.B2 = somewhere;
     g.out_f32 = g.kind == hh::GEMM_TN;
     g.ws = somewhere; g.ws_bytes = hh::GEMM_WS_BYTES;
+    g.micro = 1;
     return g;
 }
 extern "C" int hh_internal_gemm_plan(const int* problems, int n, char* out, size_t size) {

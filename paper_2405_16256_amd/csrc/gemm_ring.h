@@ -20,25 +20,31 @@ namespace hh {
 // Why groups: alone, each of these problems leaves most of the chip idle and costs a launch.  Measured: dWdown | dWgate |
 // dWup | d(hn) of hidden 512, ffn 768 and 2200 tokens in five launches 52 us, in one 23 us; dWo | da of hidden 4096,
 // width 1024 and 3300 tokens 101 -> 77 us; a 4-layer, 8 micro-batch stage of hidden 256 and 128 tokens 3.22 -> 2.88 ms.
+//
+// A problem may stand for the same product in `micro` micro-batches.  NT, NN and split TN ones then own that many times the
+// workgroups; a workgroup of an unsplit TN problem walks the k loops of all of them, in order, and adds each product to the
+// sum of those before it (`seq` of them), so that the gradient is read and written once.  Tile and split are those of a
+// micro-batch by itself, so every result is what a launch per micro-batch gives, bit for bit.  Bound as before by one
+// workgroup's chain and by launch latency, of which there are fewer: a 4-layer stage of hidden 256, 128 tokens and 8
+// micro-batches, two at a time, 2671 -> 1485 us; 2 layers of hidden 512, 2200 tokens, 3 micro-batches, two and one, 1092 -> 899 us.
 constexpr int RING_MAX = 4;
+template <int MB>             // how many micro-batches a launch may stand for: 1 or MICRO_MAX
 struct RingProblem {
-    const bf16_t* A;
-    const bf16_t* B;
-    void* C;
-    const bf16_t* R;
+    Ops<MB> A, B, C, R;
     const bf16_t* Bseg[2];     // NN: where the rows of B from k tile kseg[0] (kseg[1]) on are; INT_MAX: no such segment
-    float* partial;            // k shares: [tile][share][BM*BN] fp32 sums
+    float* partial;            // k shares: [tile][micro-batch][share][BM*BN] fp32 sums
     uint32_t a_bytes, b_bytes; // extent of A, and of B up to the first segment's end
     int kseg[2];
-    int kind, lda, ldb, ldc, ldr, M, N, K, accumulate, tiles, ksplit, first;
+    int kind, lda, ldb, ldc, ldr, M, N, K, accumulate, tiles, ksplit, first, micro, seq;
 };
+template <int MB>
 struct RingGroup {
     int n;
-    RingProblem p[RING_MAX];
+    RingProblem<MB> p[RING_MAX];
 };
 
-template <int KIND, int BM, int BN, int WM, int WN, int NS>
-__device__ __forceinline__ void ring_body(const RingProblem& g) {
+template <int KIND, int MB, int BM, int BN, int WM, int WN, int NS>
+__device__ __forceinline__ void ring_body(const RingProblem<MB>& g) {
     constexpr bool OUT_F32 = KIND == GEMM_TN;
     constexpr int NW = WM * WN;
     using DA = DmaTile<(KIND != GEMM_TN), BM, NW>;
@@ -49,28 +55,35 @@ __device__ __forceinline__ void ring_body(const RingProblem& g) {
     static_assert(NS * STAGE >= NW * 4096, "the epilogue patches reuse the ring");
     extern __shared__ __attribute__((aligned(1024))) char smem[];   // [stage][A | B]
     const int M = g.M, N = g.N, K = g.K, lda = g.lda, ldb = g.ldb, ldc = g.ldc, ldr = g.ldr, tiles = g.tiles, ksplit = g.ksplit;
-    const bf16_t* const R = g.R;
-    void* const Cv = g.C;
-    const bool accumulate = g.accumulate != 0;
+    bool accumulate = g.accumulate != 0;
 
     const int item = (int)blockIdx.x - g.first;
-    const int share = item / tiles, tix = item - share * tiles;
+    const int micro = MB == 1 ? 0 : item / (tiles * ksplit), rest = item - micro * (tiles * ksplit);
+    const int share = rest / tiles, tix = rest - share * tiles;
+    const bf16_t* const R = (const bf16_t*)g.R.at(micro);
+    void* const Cv = g.C.at(micro);
+    constexpr bool SUMS = KIND == GEMM_TN && MB > 1;
+    const int seq = SUMS ? g.seq : 1;   // products summed here
     const int tiles_n = (N + BN - 1) / BN;
     int tm, tn;
     tile_of_index(tix, (M + BM - 1) / BM, tiles_n, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
     const int nk_all = (K + DK - 1) / DK;
     const int kbeg = (int)((long)share * nk_all / ksplit), nk = (int)((long)(share + 1) * nk_all / ksplit) - kbeg;
+    const int nt = nk * seq;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, hf = lane >> 5;
     const int wm = (wave / WN) * (BM / WM), wn = (wave % WN) * (BN / WN);
 
-    const uint64_t pa = (uint64_t)g.A;
-    const i32x4 rsA = {(int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), (int)g.a_bytes, 0x00020000};
+    auto rsrc_a = [&](int m) {
+        const uint64_t pa = (uint64_t)g.A.at(m);
+        return i32x4{(int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), (int)g.a_bytes, 0x00020000};
+    };
+    i32x4 rsA = rsrc_a(micro);
     const uint32_t stepA = DA::kstep_bytes(lda), stepB = DB::kstep_bytes(ldb);
     // B's rows may lie in up to three allocations.  Offsets run on over the segments: segment s is addressed from a base
     // moved back by the rows before it, and its last row ends its extent.
-    auto rsrc_b = [&](int kt) {
-        uint64_t pb = (uint64_t)g.B;
+    auto rsrc_b = [&](int m, int kt) {
+        uint64_t pb = (uint64_t)g.B.at(m);
         uint32_t bytes = g.b_bytes;
         if (KIND == GEMM_NN && kt >= g.kseg[0]) {
             const int s = kt >= g.kseg[1] ? 1 : 0;
@@ -80,7 +93,7 @@ __device__ __forceinline__ void ring_body(const RingProblem& g) {
         }
         return i32x4{(int)(uint32_t)pb, (int)(uint32_t)(pb >> 32), (int)bytes, 0x00020000};
     };
-    i32x4 rsB = rsrc_b(kbeg);
+    i32x4 rsB = rsrc_b(micro, kbeg);
     uint32_t voA[DA::PER_WAVE], voB[DB::PER_WAVE];
 #pragma unroll
     for (int i = 0; i < DA::PER_WAVE; i++) voA[i] = DA::voff(wave, i, m0, lda) + kbeg * stepA;
@@ -88,10 +101,20 @@ __device__ __forceinline__ void ring_body(const RingProblem& g) {
     for (int i = 0; i < DB::PER_WAVE; i++) voB[i] = DB::voff(wave, i, n0, ldb) + kbeg * stepB;
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
     const int kseg0 = g.kseg[0], kseg1 = g.kseg[1];
-    int kissue = kbeg;   // k tile that `issue` fetches next
+    int kissue = kbeg, missue = micro;   // k tile and micro-batch that `issue` fetches next
     auto issue = [&](int slot) {
         const uint32_t base = lds0 + slot * STAGE;
-        if (KIND == GEMM_NN && (kissue == kseg0 || kissue == kseg1)) rsB = rsrc_b(kissue);
+        if (KIND == GEMM_NN && (kissue == kseg0 || kissue == kseg1)) rsB = rsrc_b(micro, kissue);
+        if (SUMS && kissue == kbeg + nk) {   // the next micro-batch's product
+            kissue = kbeg;
+            missue++;
+            rsA = rsrc_a(missue);
+            rsB = rsrc_b(missue, kbeg);
+#pragma unroll
+            for (int i = 0; i < DA::PER_WAVE; i++) voA[i] -= (uint32_t)nk * stepA;
+#pragma unroll
+            for (int i = 0; i < DB::PER_WAVE; i++) voB[i] -= (uint32_t)nk * stepB;
+        }
         kissue++;
 #pragma unroll
         for (int i = 0; i < DA::PER_WAVE; i++) { dma16(base + (wave * DA::PER_WAVE + i) * 1024, voA[i], rsA); voA[i] += stepA; }
@@ -100,7 +123,7 @@ __device__ __forceinline__ void ring_body(const RingProblem& g) {
     };
 #pragma unroll
     for (int s = 0; s < NS; s++)
-        if (s < nk) issue(s);
+        if (s < nt) issue(s);
 
     f32x16 acc[TM][TN];
 #pragma unroll
@@ -110,8 +133,48 @@ __device__ __forceinline__ void ring_body(const RingProblem& g) {
 #pragma unroll
             for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
 
+    // The sum of the products of the micro-batches before the one at work; a lane owns 4 consecutive columns of a row.
+    constexpr int RM = SUMS ? TM : 1, RN = SUMS ? TN : 1;
+    f32x16 sum[RM][RN];
+    int left = nk;   // k tiles up to the end of the product at work
+    bool first = true;
+    if (SUMS && seq > 1 && accumulate) {
+        const __amdgpu_buffer_rsrc_t rsC = make_rsrc(Cv, (uint32_t)(((size_t)(M - 1) * ldc + N) * 4u));
+#pragma unroll
+        for (int i = 0; i < RM; i++)
+#pragma unroll
+            for (int j = 0; j < RN; j++)
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    const uint32_t row = (uint32_t)(m0 + wm + 32 * i + (lane & 31)), col = (uint32_t)(n0 + wn + 32 * j + 8 * q + 4 * hf);
+                    const i32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsC, (int)col < N ? (row * (uint32_t)ldc + col) * 4u : 0x80000000u, 0, 0);
+#pragma unroll
+                    for (int e = 0; e < 4; e++) sum[i][j][4 * q + e] = __int_as_float(v[e]);
+                }
+        // the loads end here, as far as the compiler's wait counters go: the loop must not wait for them
+#pragma unroll
+        for (int i = 0; i < RM; i++)
+#pragma unroll
+            for (int j = 0; j < RN; j++) asm volatile("" : "+v"(sum[i][j]));
+        first = false;
+    }
+    auto fold = [&]() {
+        if (!SUMS || seq == 1 || --left) return;
+        left = nk;
+#pragma unroll
+        for (int i = 0; i < RM; i++)
+#pragma unroll
+            for (int j = 0; j < RN; j++)
+#pragma unroll
+                for (int r = 0; r < 16; r++) {
+                    sum[i][j][r] = first ? acc[i][j][r] : acc[i][j][r] + sum[i][j][r];
+                    acc[i][j][r] = 0.f;
+                }
+        first = false;
+    };
+
     // k tile 0 has landed
-    if (nk >= NS) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * PW) : "memory");
+    if (nt >= NS) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * PW) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -135,13 +198,13 @@ __device__ __forceinline__ void ring_body(const RingProblem& g) {
             const int next = slot + 1 == NS ? 0 : slot + 1;
             // Every wave holds its fragments of k tile kt, so its slot is free once all waves are here; k tile kt + 1 must
             // have landed for everyone, the NS - 2 tiles after it may still be on their way.
-            if (kt + NS <= nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * PW) : "memory");
+            if (kt + NS <= nt) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * PW) : "memory");
             else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             __builtin_amdgcn_sched_barrier(0);
-            if (kt + NS < nk) issue(slot);
-            const bool more = kt + 1 < nk;
+            if (kt + NS < nt) issue(slot);
+            const bool more = kt + 1 < nt;
 #pragma unroll
             for (int kk = 0; kk < 4; kk++) {
                 if (more) fetch(Q, next, kk);
@@ -152,13 +215,14 @@ __device__ __forceinline__ void ring_body(const RingProblem& g) {
                         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[P][kk][j], fa[P][kk][i], acc[i][j], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
+            fold();
             slot = next;
         };
 #pragma unroll
         for (int kk = 0; kk < 4; kk++) fetch(0, 0, kk);
-        for (int kt = 0; kt < nk; kt += 2) {
+        for (int kt = 0; kt < nt; kt += 2) {
             step(std::integral_constant<int, 0>{}, kt);
-            if (kt + 1 < nk) step(std::integral_constant<int, 1>{}, kt + 1);
+            if (kt + 1 < nt) step(std::integral_constant<int, 1>{}, kt + 1);
         }
     } else {
         bf16x8 fa[2][TM], fb[2][TN];
@@ -178,7 +242,7 @@ __device__ __forceinline__ void ring_body(const RingProblem& g) {
         };
         fetch(0, 0, 0);
         int slot = 0;
-        for (int kt = 0; kt < nk; kt++) {
+        for (int kt = 0; kt < nt; kt++) {
             const int next = slot + 1 == NS ? 0 : slot + 1;
 #pragma unroll
             for (int kk = 0; kk < 3; kk++) {
@@ -188,21 +252,22 @@ __device__ __forceinline__ void ring_body(const RingProblem& g) {
             }
             // Every wave holds its last fragments of k tile kt, so its slot is free once all waves are here; k tile kt + 1
             // must have landed for everyone, the NS - 2 tiles after it may still be on their way.
-            if (kt + NS <= nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * PW) : "memory");
+            if (kt + NS <= nt) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * PW) : "memory");
             else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             __builtin_amdgcn_sched_barrier(0);
-            if (kt + NS < nk) issue(slot);
-            if (kt + 1 < nk) fetch(0, next, 0);
+            if (kt + NS < nt) issue(slot);
+            if (kt + 1 < nt) fetch(0, next, 0);
             mma(1);
             __builtin_amdgcn_sched_barrier(0);
+            fold();
             slot = next;
         }
     }
 
     if (ksplit > 1) {   // a share of the k range: raw fp32 sums, finished by k_ring_reduce
-        float* pt = g.partial + ((size_t)(tm * tiles_n + tn) * ksplit + share) * (BM * BN);
+        float* pt = g.partial + (((size_t)(tm * tiles_n + tn) * (MB == 1 ? 1 : g.micro) + micro) * ksplit + share) * (BM * BN);
 #pragma unroll
         for (int i = 0; i < TM; i++)
 #pragma unroll
@@ -212,6 +277,14 @@ __device__ __forceinline__ void ring_body(const RingProblem& g) {
                     *reinterpret_cast<float4*>(pt + (wm + 32 * i + (lane & 31)) * BN + wn + 32 * j + 8 * q + 4 * hf) =
                         make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
         return;
+    }
+
+    if (SUMS && seq > 1) {
+#pragma unroll
+        for (int i = 0; i < RM; i++)
+#pragma unroll
+            for (int j = 0; j < RN; j++) acc[i][j] = sum[i][j];
+        accumulate = false;   // what the buffer held is in the sum
     }
 
     // Epilogue as in k_gemm_dma: every 32x32 block goes through a wave-private LDS patch, so that loads of what is
@@ -268,59 +341,70 @@ __device__ __forceinline__ void ring_body(const RingProblem& g) {
 }
 
 // BWD: NN and TN problems, otherwise NT
-template <bool BWD, int BM, int BN, int WM, int WN, int NS>
-__global__ __launch_bounds__(WM * WN * 64, BM * BN / (WM * WN) > 64 * 128 ? 1 : 2) void k_gemm_ring(RingGroup grp) {
+template <bool BWD, int MB, int BM, int BN, int WM, int WN, int NS>
+__global__ __launch_bounds__(WM * WN * 64, BM * BN / (WM * WN) > 64 * 128 ? 1 : 2) void k_gemm_ring(RingGroup<MB> grp) {
     int i = 0;
     while (i + 1 < grp.n && (int)blockIdx.x >= grp.p[i + 1].first) i++;
-    const RingProblem& g = grp.p[i];
-    if (!BWD) ring_body<GEMM_NT, BM, BN, WM, WN, NS>(g);
-    else if (g.kind == GEMM_NN) ring_body<GEMM_NN, BM, BN, WM, WN, NS>(g);
-    else ring_body<GEMM_TN, BM, BN, WM, WN, NS>(g);
+    const RingProblem<MB>& g = grp.p[i];
+    if (!BWD) ring_body<GEMM_NT, MB, BM, BN, WM, WN, NS>(g);
+    else if (g.kind == GEMM_NN) ring_body<GEMM_NN, MB, BM, BN, WM, WN, NS>(g);
+    else ring_body<GEMM_TN, MB, BM, BN, WM, WN, NS>(g);
 }
 
 // Sums the ksplit fp32 shares of every BM x BN tile of the group's split problems in a fixed order and applies the
-// epilogue.  A thread owns 4 consecutive columns of one row of C.
+// epilogue.  A thread owns 4 consecutive columns of one row of C: of one micro-batch's (NT, NN), or of the gradient, to
+// which it adds the micro-batches' products one after the other.
+template <int MB>
 struct RingReduce {
     struct Job {
+        Ops<MB> C, R;
         const float* partial;
-        void* C;
-        const bf16_t* R;
-        int ksplit, ldc, ldr, M, N, accumulate, out_f32, first;
+        int ksplit, ldc, ldr, M, N, accumulate, out_f32, first, micro, blocks;   // blocks: workgroups of one micro-batch
     } j[RING_MAX];
     int n, bm, bn;
 };
-__global__ __launch_bounds__(256) void k_ring_reduce(RingReduce grp) {
+template <int MB>
+__global__ __launch_bounds__(256) void k_ring_reduce(RingReduce<MB> grp) {
     int i = 0;
     while (i + 1 < grp.n && (int)blockIdx.x >= grp.j[i + 1].first) i++;
-    const RingReduce::Job& j = grp.j[i];
+    const typename RingReduce<MB>::Job& j = grp.j[i];
     const int bm = grp.bm, bn = grp.bn, vpr = j.N / 4;
-    const long idx = (long)((int)blockIdx.x - j.first) * 256 + threadIdx.x;
+    const int micro = MB == 1 ? 0 : ((int)blockIdx.x - j.first) / j.blocks, micros = MB == 1 ? 1 : j.micro;
+    const long idx = (long)((int)blockIdx.x - j.first - micro * j.blocks) * 256 + threadIdx.x;
     if (idx >= (long)j.M * vpr) return;
     const int m = (int)(idx / vpr), n = (int)(idx - (long)m * vpr) * 4;
     const int tiles_n = (j.N + bn - 1) / bn;
     const int tm = m / bm, tn = n / bn;
-    const float* p = j.partial + (size_t)(tm * tiles_n + tn) * j.ksplit * (bm * bn) + (m - tm * bm) * bn + (n - tn * bn);
-    float v[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int c = 0; c < j.ksplit; c++) {
-        const float4 t = *reinterpret_cast<const float4*>(p + (size_t)c * (bm * bn));
-        v[0] += t.x; v[1] += t.y; v[2] += t.z; v[3] += t.w;
-    }
-    if (j.out_f32) {
-        float* c = reinterpret_cast<float*>(j.C) + (size_t)m * j.ldc + n;
-        if (j.accumulate) {
-            const float4 old = *reinterpret_cast<const float4*>(c);
-            v[0] += old.x; v[1] += old.y; v[2] += old.z; v[3] += old.w;
+    const float* p = j.partial + ((size_t)(tm * tiles_n + tn) * micros + micro) * j.ksplit * (bm * bn) + (m - tm * bm) * bn + (n - tn * bn);
+    auto shares = [&](float (&v)[4]) {   // the next ksplit shares
+        for (int c = 0; c < j.ksplit; c++, p += bm * bn) {
+            const float4 t = *reinterpret_cast<const float4*>(p);
+            v[0] += t.x; v[1] += t.y; v[2] += t.z; v[3] += t.w;
         }
-        *reinterpret_cast<float4*>(c) = make_float4(v[0], v[1], v[2], v[3]);
+    };
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    if (j.out_f32) {
+        float* c = reinterpret_cast<float*>(j.C.at(0)) + (size_t)m * j.ldc + n;
+        float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (j.accumulate) sum = *reinterpret_cast<const float4*>(c);
+        for (int k = 0; k < micros; k++) {
+            v[0] = v[1] = v[2] = v[3] = 0.f;
+            shares(v);
+            if (j.accumulate || k) { v[0] += sum.x; v[1] += sum.y; v[2] += sum.z; v[3] += sum.w; }
+            sum = make_float4(v[0], v[1], v[2], v[3]);
+        }
+        *reinterpret_cast<float4*>(c) = sum;
     } else {
-        if (j.R) {
-            const uint2 rr = *reinterpret_cast<const uint2*>(j.R + (size_t)m * j.ldr + n);
+        shares(v);
+        const bf16_t* R = (const bf16_t*)j.R.at(micro);
+        if (R) {
+            const uint2 rr = *reinterpret_cast<const uint2*>(R + (size_t)m * j.ldr + n);
             v[0] += lo_bf(rr.x); v[1] += hi_bf(rr.x); v[2] += lo_bf(rr.y); v[3] += hi_bf(rr.y);
         }
         uint2 o;
         o.x = pack_bf2(v[0], v[1]);
         o.y = pack_bf2(v[2], v[3]);
-        *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(j.C) + (size_t)m * j.ldc + n) = o;
+        *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(j.C.at(micro)) + (size_t)m * j.ldc + n) = o;
     }
 }
 

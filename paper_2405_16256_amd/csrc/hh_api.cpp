@@ -19,11 +19,13 @@ namespace hh {
 hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st);
 bool gemm_bf16_shares_launch(const GemmDesc* g, int n);
 bool gemm_bf16_defer(const GemmDesc* dw, int n_dw, const GemmDesc* const groups[3], const int n[3]);
+bool gemm_bf16_micro_bytes(const GemmDesc* g, int n, size_t* bytes);
 hipError_t gemm_f32(const GemmDesc* g, int n, hipStream_t st);
-hipError_t attn_bf16_fwd(const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, hipStream_t st);
+hipError_t attn_bf16_fwd(const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, const MicroStride& micro,
+                         hipStream_t st);
 hipError_t attn_bf16_bwd(const void* qkv, int ld, const void* o, const void* dout, const float* lse, float* dvec,
                          void* dqkv, float* scratch, int B, int S, int nh, int nkv, int d,
-                         const float* rope, int rope_seq, hipStream_t st);
+                         const float* rope, int rope_seq, const MicroStride& micro, hipStream_t st);
 size_t attn_bf16_bwd_scratch_bytes(int B, int S, int nh, int nkv, int d);
 hipError_t attn_f32_fwd(const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, hipStream_t st);
 hipError_t attn_f32_bwd(const void* qkv, int ld, const void* o, const void* dout, const float* lse, float* dvec,
@@ -55,16 +57,17 @@ hipError_t gemm(int dtype, const GemmDesc* g, int n, hipStream_t st) {
     return e;
 }
 bool gemm_shares_launch(int dtype, const GemmDesc* g, int n) { return dtype == DT_BF16 ? gemm_bf16_shares_launch(g, n) : n > 1; }
-hipError_t attn_fwd(int dtype, const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, hipStream_t st) {
-    return dtype == DT_BF16 ? attn_bf16_fwd(qkv, ld, o, lse, B, S, nh, nkv, d, st) : attn_f32_fwd(qkv, ld, o, lse, B, S, nh, nkv, d, st);
+hipError_t attn_fwd(int dtype, const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, const MicroStride& micro,
+                    hipStream_t st) {
+    return dtype == DT_BF16 ? attn_bf16_fwd(qkv, ld, o, lse, B, S, nh, nkv, d, micro, st) : attn_f32_fwd(qkv, ld, o, lse, B, S, nh, nkv, d, st);
 }
 size_t attn_bwd_scratch_bytes(int dtype, int B, int S, int nh, int nkv, int d) {
     return dtype == DT_BF16 ? attn_bf16_bwd_scratch_bytes(B, S, nh, nkv, d) : 0;
 }
 hipError_t attn_bwd(int dtype, const void* qkv, int ld, const void* o, const void* dout, const float* lse, float* dvec,
                     void* dqkv, void* scratch, size_t scratch_bytes, int B, int S, int nh, int nkv, int d,
-                    const float* rope_table, int rope_seq, hipStream_t st) {
-    if (dtype == DT_BF16) return attn_bf16_bwd(qkv, ld, o, dout, lse, dvec, dqkv, (float*)scratch, B, S, nh, nkv, d, rope_table, rope_seq, st);
+                    const float* rope_table, int rope_seq, const MicroStride& micro, hipStream_t st) {
+    if (dtype == DT_BF16) return attn_bf16_bwd(qkv, ld, o, dout, lse, dvec, dqkv, (float*)scratch, B, S, nh, nkv, d, rope_table, rope_seq, micro, st);
     return attn_f32_bwd(qkv, ld, o, dout, lse, dvec, dqkv, (float*)scratch, scratch_bytes, B, S, nh, nkv, d, rope_table, rope_seq, st);
 }
 }  // namespace hh
@@ -104,6 +107,7 @@ struct TraceRec {
     double work;
     size_t events;  // the record whose events bracket the launch (its own, unless GEMMs share one)
     double share;   // of the time between them that is this family's
+    int count;      // micro-batches that the launch takes side by side: it stands for a launch of each
 };
 struct hh_ctx {
     int device;
@@ -344,10 +348,10 @@ extern "C" int hh_ctx_reserve(hh_ctx* ctx, const hh_layer_cfg* cfg) {
 // launch stream; hh_trace_end turns them into per-family time and work sums.
 struct Traced {
     hh_ctx* ctx; hipStream_t st; TraceRec* rec;
-    Traced(hh_ctx* c, hipStream_t s, int kind, double work) : ctx(c), st(s), rec(nullptr) {
+    Traced(hh_ctx* c, hipStream_t s, int kind, int count, double work) : ctx(c), st(s), rec(nullptr) {
         if (c->trace_on && ((c->trace_mask >> kind) & 1u) && c->trace_used < c->trace.size()) {
             rec = &c->trace[c->trace_used++];
-            rec->kind = kind; rec->work = work; rec->events = ctx->trace_used - 1; rec->share = 1.0;
+            rec->kind = kind; rec->work = work * count; rec->events = ctx->trace_used - 1; rec->share = 1.0; rec->count = count;
             (void)hipEventRecord(rec->a, st);
         }
     }
@@ -355,11 +359,11 @@ struct Traced {
 };
 #define TR(kind, work, call)                     \
     do {                                         \
-        Traced t_(ctx, st, (kind), (double)(work)); \
+        Traced t_(ctx, st, (kind), p.n, (double)(work)); \
         HIP_TRY(call);                           \
     } while (0)
 static double attn_flop(const Dims& d) { return 4.0 * d.d * d.B * d.nh * ((double)d.S * (d.S + 1) / 2); }
-static double gemm_flop(const GemmDesc& g) { return 2.0 * g.M * g.N * g.K; }
+static double gemm_flop(const GemmDesc& g) { return 2.0 * g.M * g.N * g.K * g.micro; }
 static void gemm_scratch(const hh_ctx* ctx, GemmDesc& g) { g.ws = ctx->gemm_ws; g.ws_bytes = ctx->gemm_ws ? GEMM_WS_BYTES : 0; }
 // A group of GEMMs in one call.  Where they share a launch it is bracketed once and its time shared out to the members by
 // their flops; members with launches of their own are traced (and launched, in the same way) one by one.
@@ -378,7 +382,7 @@ static hipError_t tgemm(hh_ctx* ctx, int dt, GemmDesc* g, int n, hipStream_t st)
     for (int i = 0; i < n; i++) {
         if (!(ctx->trace_on && ((ctx->trace_mask >> g[i].kind) & 1u) && ctx->trace_used < ctx->trace.size())) continue;
         TraceRec& r = ctx->trace[ctx->trace_used++];
-        r.kind = g[i].kind; r.work = gemm_flop(g[i]); r.events = first; r.share = r.work / total;
+        r.kind = g[i].kind; r.work = gemm_flop(g[i]); r.events = first; r.share = r.work / total; r.count = g[i].micro;
     }
     const bool traced = ctx->trace_used > first;
     if (traced) (void)hipEventRecord(ctx->trace[first].a, st);
@@ -393,7 +397,7 @@ extern "C" int hh_trace_begin(hh_ctx* ctx, int max_launches, uint32_t kind_mask)
     if (max_launches <= 0) return fail(HH_ERR_INVALID_ARG, "max_launches must be positive");
     HIP_TRY(hipSetDevice(ctx->device));
     while ((int)ctx->trace.size() < max_launches) {
-        TraceRec r{nullptr, nullptr, 0, 0.0, 0, 1.0};
+        TraceRec r{nullptr, nullptr, 0, 0.0, 0, 1.0, 1};
         HIP_TRY(hipEventCreate(&r.a));
         hipError_t e = hipEventCreate(&r.b);
         if (e != hipSuccess) { (void)hipEventDestroy(r.a); return hip_fail(e, "hipEventCreate"); }
@@ -416,7 +420,7 @@ extern "C" int hh_trace_end(hh_ctx* ctx, hh_trace_sum* out, int n_kinds) {
         HIP_TRY(hipEventSynchronize(ev.b));
         float ms = 0.f;
         HIP_TRY(hipEventElapsedTime(&ms, ev.a, ev.b));
-        if (r.kind < n_kinds) { out[r.kind].launches++; out[r.kind].ms += ms * r.share; out[r.kind].work += r.work; }
+        if (r.kind < n_kinds) { out[r.kind].launches += r.count; out[r.kind].ms += ms * r.share; out[r.kind].work += r.work; }
     }
     ctx->trace_used = 0;
     return HH_OK;
@@ -432,49 +436,109 @@ static GemmDesc desc(int kind, int M, int N, int K, const void* A, int lda, cons
     g.kind = kind; g.M = M; g.N = N; g.K = K; g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc;
     g.R = R; g.ldr = ldr; g.out_f32 = out_f32; g.accumulate = acc; g.ws = nullptr; g.ws_bytes = 0;
     g.B1 = g.B2 = nullptr; g.k1 = g.k2 = 0;
+    g.micro = 1; g.each = nullptr;
     return g;
 }
 
-static int layer_fwd_impl(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, const hh_layer_weights* w, const void* x,
-                          void* y, void* saved, void* ws, hipStream_t st) {
+// The micro-batches that a pass takes through its launches side by side.  Their pool slots lie `pool_stride` bytes apart and
+// their workspaces `ws_stride`; the boundary tensors are wherever the caller has them.  The code below names the addresses of
+// the first micro-batch; at() gives those of the others.
+struct Pass {
+    int n;
+    const char* pool; size_t pool_stride;
+    const char* ws; size_t ws_stride;
+    const void* const* x; void* const* y;
+    const void* const* dy; void* const* dx;
+    void* at(const void* p, int m) const {
+        const char* c = (const char*)p;
+        if (m == 0 || !c) return const_cast<char*>(c);
+        if (c >= pool && c < pool + pool_stride) return const_cast<char*>(c) + m * pool_stride;
+        if (c >= ws && c < ws + ws_stride) return const_cast<char*>(c) + m * ws_stride;
+        if (c == x[0]) return const_cast<void*>(x[m]);
+        if (c == y[0]) return y[m];
+        if (c == dy[0]) return const_cast<void*>(dy[m]);   // dx[m] too where it is the same buffer
+        if (c == dx[0]) return dx[m];
+        return const_cast<char*>(c);   // parameters and their gradients
+    }
+    Each each(const void* p) const {
+        Each e{};
+        for (int m = 0; m < n; m++) e.p[m] = at(p, m);
+        return e;
+    }
+    MicroStride stride() const { return MicroStride{n, pool_stride, ws_stride}; }
+};
+static const Pass ONE{1, nullptr, 0, nullptr, 0, nullptr, nullptr, nullptr, nullptr};
+
+// GEMMs of a pass: in every micro-batch of it.
+static hipError_t pgemm(hh_ctx* ctx, const Pass& p, int dt, GemmDesc* g, int n, hipStream_t st) {
+    GemmMicro ops[8];
+    if (n > 8) return hipErrorInvalidValue;
+    if (p.n > 1)
+        for (int i = 0; i < n; i++) {
+            ops[i] = GemmMicro{p.each(g[i].A), p.each(g[i].B), p.each(g[i].C), p.each(g[i].R)};
+            g[i].micro = p.n; g[i].each = ops + i;
+        }
+    return tgemm(ctx, dt, g, n, st);
+}
+static hipError_t pgemm(hh_ctx* ctx, const Pass& p, int dt, GemmDesc g, hipStream_t st) { return pgemm(ctx, p, dt, &g, 1, st); }
+
+static bool qkv_in_one(const Dims& d, const hh_layer_weights* w) {
+    return (const char*)w->wk == (const char*)w->wq + (size_t)d.A * d.H * d.es && (const char*)w->wv == (const char*)w->wk + (size_t)d.Akv * d.H * d.es;
+}
+static bool gate_up_in_one(const Dims& d, const hh_layer_weights* w) { return (const char*)w->w_up == (const char*)w->w_gate + (size_t)d.F * d.H * d.es; }
+
+// The projections of a forward pass: q|k|v (one problem or three), out, gate|up (one or two), down.
+struct FwdGemms {
+    GemmDesc qkv[3], out, gu[2], down;
+    int n_qkv, n_gu;
+};
+static void fwd_gemms(const Dims& d, const hh_layer_weights* w, const void* x, void* y, void* saved, void* m, FwdGemms& f) {
     const SavedLayout sl = saved_layout(d);
-    const WorkLayout wl = work_layout(d);
-    const int T = d.T, H = d.H, A = d.A, F = d.F, dt = d.dt;
+    const int T = d.T, H = d.H, A = d.A, F = d.F, Akv = d.Akv, Q3 = d.Q3;
     const size_t es = d.es;
     void* xn = at(saved, sl.xn); void* qkv = at(saved, sl.qkv); void* a = at(saved, sl.a); void* h = at(saved, sl.h);
     void* hn = at(saved, sl.hn); void* gu = at(saved, sl.gu);
-    float* lse = (float*)at(saved, sl.lse); float* r1 = (float*)at(saved, sl.r1); float* r2 = (float*)at(saved, sl.r2);
-    void* m = at(ws, wl.m);
-    ctx->gemm_ws = d.dt == DT_BF16 ? at(ws, wl.gemm_ws) : nullptr;
-
-    TR(HH_TRACE_ELEMENTWISE, 2.0 * T * H * es, rmsnorm_fwd(dt, x, w->g_attn, xn, r1, T, H, cfg->rms_eps, st));
     // q | k | v rows of width A, Akv, Akv (Akv < A with grouped-query attention)
-    const int Akv = d.Akv, Q3 = d.Q3;
     const int part_w[3] = {A, Akv, Akv}, part_c[3] = {0, A, A + Akv};
-    const bool qkv_packed = (const char*)w->wk == (const char*)w->wq + (size_t)A * H * es &&
-                            (const char*)w->wv == (const char*)w->wk + (size_t)Akv * H * es;
-    if (qkv_packed) {
-        HIP_TRY(tgemm(ctx, dt, desc(GEMM_NT, T, Q3, H, xn, H, w->wq, H, qkv, Q3), st));
+    const void* ws3[3] = {w->wq, w->wk, w->wv};
+    f.n_qkv = qkv_in_one(d, w) ? 1 : 3;
+    if (f.n_qkv == 1) f.qkv[0] = desc(GEMM_NT, T, Q3, H, xn, H, w->wq, H, qkv, Q3);
+    else for (int i = 0; i < 3; i++) f.qkv[i] = desc(GEMM_NT, T, part_w[i], H, xn, H, ws3[i], H, at(qkv, (size_t)part_c[i] * es), Q3);
+    f.out = desc(GEMM_NT, T, H, A, a, A, w->wo, A, h, H, x, H);
+    f.n_gu = gate_up_in_one(d, w) ? 1 : 2;
+    if (f.n_gu == 1) {
+        f.gu[0] = desc(GEMM_NT, T, 2 * F, H, hn, H, w->w_gate, H, gu, 2 * F);
     } else {
-        const void* ws3[3] = {w->wq, w->wk, w->wv};
-        GemmDesc q[3];
-        for (int i = 0; i < 3; i++) q[i] = desc(GEMM_NT, T, part_w[i], H, xn, H, ws3[i], H, at(qkv, (size_t)part_c[i] * es), Q3);
-        HIP_TRY(tgemm(ctx, dt, q, 3, st));
+        f.gu[0] = desc(GEMM_NT, T, F, H, hn, H, w->w_gate, H, gu, 2 * F);
+        f.gu[1] = desc(GEMM_NT, T, F, H, hn, H, w->w_up, H, at(gu, (size_t)F * es), 2 * F);
     }
-    TR(HH_TRACE_ELEMENTWISE, 2.0 * T * (A + Akv) * es, rope(dt, qkv, Q3, T, d.S, d.nh + d.nkv, d.d, ctx->rope_table, ctx->rope_seq, st));
-    TR(HH_TRACE_ATTN_FWD, attn_flop(d), attn_fwd(dt, qkv, Q3, a, lse, d.B, d.S, d.nh, d.nkv, d.d, st));
-    HIP_TRY(tgemm(ctx, dt, desc(GEMM_NT, T, H, A, a, A, w->wo, A, h, H, x, H), st));
-    TR(HH_TRACE_ELEMENTWISE, 2.0 * T * H * es, rmsnorm_fwd(dt, h, w->g_mlp, hn, r2, T, H, cfg->rms_eps, st));
-    const bool gu_packed = (const char*)w->w_up == (const char*)w->w_gate + (size_t)F * H * es;
-    if (gu_packed) {
-        HIP_TRY(tgemm(ctx, dt, desc(GEMM_NT, T, 2 * F, H, hn, H, w->w_gate, H, gu, 2 * F), st));
-    } else {
-        GemmDesc q[2] = {desc(GEMM_NT, T, F, H, hn, H, w->w_gate, H, gu, 2 * F),
-                         desc(GEMM_NT, T, F, H, hn, H, w->w_up, H, at(gu, (size_t)F * es), 2 * F)};
-        HIP_TRY(tgemm(ctx, dt, q, 2, st));
-    }
-    TR(HH_TRACE_ELEMENTWISE, 3.0 * T * F * es, swiglu_fwd(dt, gu, m, T, F, st));
-    HIP_TRY(tgemm(ctx, dt, desc(GEMM_NT, T, H, F, m, F, w->w_down, F, y, H, h, H), st));
+    f.down = desc(GEMM_NT, T, H, F, m, F, w->w_down, F, y, H, h, H);
+}
+
+// Addresses are those of the pass's first micro-batch.  gemm_ws: the GEMMs' scratch (null: in its place in the workspace).
+static int layer_fwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_layer_cfg* cfg, const hh_layer_weights* w, const void* x,
+                          void* y, void* saved, void* ws, void* gemm_ws, hipStream_t st) {
+    const SavedLayout sl = saved_layout(d);
+    const WorkLayout wl = work_layout(d);
+    const int T = d.T, H = d.H, A = d.A, F = d.F, dt = d.dt, Akv = d.Akv, Q3 = d.Q3;
+    const size_t es = d.es;
+    const Each qkv = p.each(at(saved, sl.qkv)), h = p.each(at(saved, sl.h)), m = p.each(at(ws, wl.m));
+    ctx->gemm_ws = d.dt != DT_BF16 ? nullptr : gemm_ws ? gemm_ws : at(ws, wl.gemm_ws);
+    FwdGemms f;
+    fwd_gemms(d, w, x, y, saved, m.p[0], f);
+
+    TR(HH_TRACE_ELEMENTWISE, 2.0 * T * H * es, rmsnorm_fwd(dt, p.each(x), w->g_attn, p.each(at(saved, sl.xn)), p.each(at(saved, sl.r1)), p.n, T, H,
+                                                           cfg->rms_eps, st));
+    HIP_TRY(pgemm(ctx, p, dt, f.qkv, f.n_qkv, st));
+    TR(HH_TRACE_ELEMENTWISE, 2.0 * T * (A + Akv) * es, rope(dt, qkv, Q3, p.n, T, d.S, d.nh + d.nkv, d.d, ctx->rope_table, ctx->rope_seq, st));
+    TR(HH_TRACE_ATTN_FWD, attn_flop(d), attn_fwd(dt, qkv.p[0], Q3, at(saved, sl.a), (float*)at(saved, sl.lse), d.B, d.S, d.nh, d.nkv, d.d,
+                                                 p.stride(), st));
+    HIP_TRY(pgemm(ctx, p, dt, f.out, st));
+    TR(HH_TRACE_ELEMENTWISE, 2.0 * T * H * es, rmsnorm_fwd(dt, h, w->g_mlp, p.each(at(saved, sl.hn)), p.each(at(saved, sl.r2)), p.n, T, H,
+                                                           cfg->rms_eps, st));
+    HIP_TRY(pgemm(ctx, p, dt, f.gu, f.n_gu, st));
+    TR(HH_TRACE_ELEMENTWISE, 3.0 * T * F * es, swiglu_fwd(dt, p.each(at(saved, sl.gu)), m, p.n, T, F, st));
+    HIP_TRY(pgemm(ctx, p, dt, f.down, st));
     return HH_OK;
 }
 
@@ -494,7 +558,7 @@ extern "C" int hh_layer_fwd(hh_ctx* ctx, const hh_layer_cfg* cfg, const hh_layer
         sv = workspace;
         wsp = at(workspace, saved_layout(d).total);
     }
-    return layer_fwd_impl(ctx, d, cfg, w, x, y, sv, wsp, (hipStream_t)stream);
+    return layer_fwd_impl(ctx, ONE, d, cfg, w, x, y, sv, wsp, nullptr, (hipStream_t)stream);
 }
 
 extern "C" int hh_layer_fwd_noalloc(hh_ctx* ctx, const hh_layer_cfg* cfg, const hh_layer_weights* w, const void* x, void* y,
@@ -515,41 +579,35 @@ extern "C" int hh_layer_fwd_noalloc(hh_ctx* ctx, const hh_layer_cfg* cfg, const 
     void* base = static_scratch(ctx->device);
     if (!base) return fail(HH_ERR_DEVICE, "hh_layer_fwd_noalloc: the scratch array of device %d was never looked up", ctx->device);
     // same carving as hh_layer_fwd with saved == NULL: the saved block first, the workspace behind it
-    return layer_fwd_impl(ctx, d, cfg, w, x, y, base, at(base, saved_b), (hipStream_t)stream);
+    return layer_fwd_impl(ctx, ONE, d, cfg, w, x, y, base, at(base, saved_b), nullptr, (hipStream_t)stream);
 }
 
 // ----------------------------------------------------------- layer backward
-static int layer_bwd_impl(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, const hh_layer_weights* w, const void* x,
-                          const void* saved, const void* dy, void* dx, const hh_layer_grads* g, int acc, void* ws,
-                          hipStream_t st) {
-    (void)cfg;
+// The GEMMs of a backward pass: dm, and three groups of independent ones -- the weight gradients that use an operand of an
+// input gradient, and that input gradient last.
+struct BwdGemms {
+    GemmDesc dm, group[3][4], dw[7];
+    int n[3], n_dw;
+    bool defer;   // all the weight gradients (dw) in one launch after the last input gradient: predicted to be faster
+};
+static void bwd_gemms(const Dims& d, const hh_layer_weights* w, const hh_layer_grads* g, const void* saved, const void* dy, void* ws, int acc,
+                      BwdGemms& b) {
     const SavedLayout sl = saved_layout(d);
     const WorkLayout wl = work_layout(d);
-    const int T = d.T, H = d.H, A = d.A, F = d.F, dt = d.dt;
+    const int T = d.T, H = d.H, A = d.A, F = d.F, Akv = d.Akv, Q3 = d.Q3;
     const size_t es = d.es;
-    const void* xn = at(saved, sl.xn); const void* qkv = at(saved, sl.qkv); const void* a = at(saved, sl.a);
-    const void* h = at(saved, sl.h); const void* hn = at(saved, sl.hn); const void* gu = at(saved, sl.gu);
-    const float* lse = (const float*)at(saved, sl.lse);
-    const float* r1 = (const float*)at(saved, sl.r1); const float* r2 = (const float*)at(saved, sl.r2);
+    const void* xn = at(saved, sl.xn); const void* a = at(saved, sl.a); const void* hn = at(saved, sl.hn);
     void* m = at(ws, wl.m); void* dgu = at(ws, wl.dgu); void* dhn = at(ws, wl.dhn); void* dh = at(ws, wl.dh);
     void* da = at(ws, wl.da); void* dqkv = at(ws, wl.dqkv);
-    float* dvec = (float*)at(ws, wl.dvec);
-    acc = acc ? 1 : 0;
-    ctx->gemm_ws = d.dt == DT_BF16 ? at(ws, wl.gemm_ws) : nullptr;
     void* dxn = dhn;
-
-    // The GEMMs after dm, in three groups of independent ones: the weight gradients that use an operand of an input
-    // gradient, and that input gradient last.
-    const int Akv = d.Akv, Q3 = d.Q3;
     const int part_w[3] = {A, Akv, Akv}, part_c[3] = {0, A, A + Akv};
-    const bool gu_packed = (const char*)w->w_up == (const char*)w->w_gate + (size_t)F * H * es;
     const bool dgu_packed = (char*)g->w_up == (char*)g->w_gate + (size_t)F * H * 4 && (size_t)2 * F * H * 4 < ((size_t)1 << 31);
-    const bool qkv_packed = (const char*)w->wk == (const char*)w->wq + (size_t)A * H * es &&
-                            (const char*)w->wv == (const char*)w->wk + (size_t)Akv * H * es;
     const bool dqkv_packed = (char*)g->wk == (char*)g->wq + (size_t)A * H * 4 && (char*)g->wv == (char*)g->wk + (size_t)Akv * H * 4 &&
                              (size_t)Q3 * H * 4 < ((size_t)1 << 31);
-    GemmDesc group[3][4];
-    int n[3] = {0, 0, 0};
+    GemmDesc (&group)[3][4] = b.group;
+    int (&n)[3] = b.n;
+    n[0] = n[1] = n[2] = 0;
+    b.dm = desc(GEMM_NN, T, F, H, dy, H, w->w_down, F, m, F);
     group[0][n[0]++] = desc(GEMM_TN, H, F, T, dy, H, m, F, g->w_down, F, nullptr, 0, 1, acc);
     if (dgu_packed) {
         group[0][n[0]++] = desc(GEMM_TN, 2 * F, H, T, dgu, 2 * F, hn, H, g->w_gate, H, nullptr, 0, 1, acc);
@@ -558,7 +616,7 @@ static int layer_bwd_impl(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, c
         group[0][n[0]++] = desc(GEMM_TN, F, H, T, at(dgu, (size_t)F * es), 2 * F, hn, H, g->w_up, H, nullptr, 0, 1, acc);
     }
     GemmDesc& to_hn = group[0][n[0]++] = desc(GEMM_NN, T, H, 2 * F, dgu, 2 * F, w->w_gate, H, dhn, H);
-    if (!gu_packed) { to_hn.B1 = w->w_up; to_hn.k1 = F; }
+    if (!gate_up_in_one(d, w)) { to_hn.B1 = w->w_up; to_hn.k1 = F; }
     group[1][n[1]++] = desc(GEMM_TN, H, A, T, dh, H, a, A, g->wo, A, nullptr, 0, 1, acc);
     group[1][n[1]++] = desc(GEMM_NN, T, A, H, dh, H, w->wo, A, da, A);
     if (dqkv_packed) {
@@ -569,18 +627,32 @@ static int layer_bwd_impl(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, c
             group[2][n[2]++] = desc(GEMM_TN, part_w[i], H, T, at(dqkv, (size_t)part_c[i] * es), Q3, xn, H, gs[i], H, nullptr, 0, 1, acc);
     }
     GemmDesc& to_xn = group[2][n[2]++] = desc(GEMM_NN, T, H, Q3, dqkv, Q3, w->wq, H, dxn, H);
-    if (!qkv_packed) { to_xn.B1 = w->wk; to_xn.k1 = A; to_xn.B2 = w->wv; to_xn.k2 = A + Akv; }
-    // Or all the weight gradients in one launch after the last input gradient, where that is predicted to be faster.
-    GemmDesc dw[7];
-    int n_dw = 0;
+    if (!qkv_in_one(d, w)) { to_xn.B1 = w->wk; to_xn.k1 = A; to_xn.B2 = w->wv; to_xn.k2 = A + Akv; }
+}
+static void plan_deferral(const hh_ctx* ctx, const Dims& d, BwdGemms& b) {
+    b.n_dw = 0;
     for (int i = 0; i < 3; i++)
-        for (int j = 0; j < n[i]; j++) {
-            gemm_scratch(ctx, group[i][j]);
-            if (j + 1 < n[i]) dw[n_dw++] = group[i][j];
+        for (int j = 0; j < b.n[i]; j++) {
+            gemm_scratch(ctx, b.group[i][j]);
+            if (j + 1 < b.n[i]) b.dw[b.n_dw++] = b.group[i][j];
         }
-    const GemmDesc* const groups[3] = {group[0], group[1], group[2]};
-    const bool defer = dt == DT_BF16 && gemm_bf16_defer(dw, n_dw, groups, n);
-    auto run_group = [&](int i) { return defer ? tgemm(ctx, dt, &group[i][n[i] - 1], 1, st) : tgemm(ctx, dt, group[i], n[i], st); };
+    const GemmDesc* const groups[3] = {b.group[0], b.group[1], b.group[2]};
+    b.defer = d.dt == DT_BF16 && gemm_bf16_defer(b.dw, b.n_dw, groups, b.n);
+}
+
+static int layer_bwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_layer_weights* w, const void* x, const void* saved,
+                          const void* dy, void* dx, const hh_layer_grads* g, int acc, void* ws, void* gemm_ws, hipStream_t st) {
+    const SavedLayout sl = saved_layout(d);
+    const WorkLayout wl = work_layout(d);
+    const int T = d.T, H = d.H, F = d.F, dt = d.dt;
+    const size_t es = d.es;
+    acc = acc ? 1 : 0;
+    ctx->gemm_ws = d.dt != DT_BF16 ? nullptr : gemm_ws ? gemm_ws : at(ws, wl.gemm_ws);
+    BwdGemms b;
+    bwd_gemms(d, w, g, saved, dy, ws, acc, b);
+    plan_deferral(ctx, d, b);
+    const bool defer = b.defer;
+    auto run_group = [&](int i) { return defer ? pgemm(ctx, p, dt, &b.group[i][b.n[i] - 1], 1, st) : pgemm(ctx, p, dt, b.group[i], b.n[i], st); };
 
     // Partial column sums of the two gain gradients.  Those of the MLP norm go to the front of the m | dgate|dup stretch
     // if nobody needs that any more by then and it holds a row per workgroup, otherwise to `partial`; those of the
@@ -590,18 +662,19 @@ static int layer_bwd_impl(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, c
     const bool mlp_in = !defer && stretch >= want;
     const size_t taken = mlp_in ? up256(want) : 0;
     const bool attn_in = stretch - taken >= want;
-    float* part2 = (float*)at(ws, mlp_in ? wl.m : wl.partial);
-    float* part1 = (float*)at(ws, attn_in ? wl.m + taken : wl.partial);
+    const Each part2 = p.each(at(ws, mlp_in ? wl.m : wl.partial)), part1 = p.each(at(ws, attn_in ? wl.m + taken : wl.partial));
     const size_t part2_b = mlp_in ? want : partial_b, part1_b = attn_in ? want : partial_b;
     const ColSum sums[2] = {{part2, rmsnorm_bwd_blocks(T, H, part2_b), g->g_mlp}, {part1, rmsnorm_bwd_blocks(T, H, part1_b), g->g_attn}};
-    const bool sum_both = part1 != part2;
+    const bool sum_both = part1.p[0] != part2.p[0];
 
     // MLP branch: y = h + m Wd^T
-    HIP_TRY(tgemm(ctx, dt, desc(GEMM_NN, T, F, H, dy, H, w->w_down, F, m, F), st));                 // dm (in the m buffer)
-    TR(HH_TRACE_ELEMENTWISE, 6.0 * T * F * es, swiglu_bwd(dt, m, gu, dgu, m, T, F, st));                                          // dgate|dup, m
+    const Each m = p.each(at(ws, wl.m)), dgu = p.each(at(ws, wl.dgu)), dhn = p.each(at(ws, wl.dhn)), dh = p.each(at(ws, wl.dh));
+    HIP_TRY(pgemm(ctx, p, dt, b.dm, st));                                                           // dm (in the m buffer)
+    TR(HH_TRACE_ELEMENTWISE, 6.0 * T * F * es, swiglu_bwd(dt, m, p.each(at(saved, sl.gu)), dgu, m, p.n, T, F, st));               // dgate|dup, m
     HIP_TRY(run_group(0));
-    TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dhn, h, r2, w->g_mlp, dy, dh, part2, part2_b, T, H, st));          // dh = dy + norm-bwd
-    if (!sum_both) TR(HH_TRACE_ELEMENTWISE, 4.0 * sums[0].rows * H, colsum_reduce(sums, 1, H, acc, st));
+    TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dhn, p.each(at(saved, sl.h)), p.each(at(saved, sl.r2)), w->g_mlp, p.each(dy), dh,
+                                                           part2, part2_b, p.n, T, H, st));         // dh = dy + norm-bwd
+    if (!sum_both) TR(HH_TRACE_ELEMENTWISE, 4.0 * sums[0].rows * H, colsum_reduce(sums, 1, p.n, H, acc, st));
 
     // attention branch: h = x + a Wo^T
     HIP_TRY(run_group(1));
@@ -609,13 +682,15 @@ static int layer_bwd_impl(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, c
     // scratch is the m | dgate|dup | dhn stretch of the workspace behind the partial sums above, whose contents nobody
     // needs any more by now.
     const size_t part_at = dt == DT_BF16 ? wl.dkv_part : wl.m + taken, part_end = dt == DT_BF16 ? wl.partial : wl.dh;
-    TR(HH_TRACE_ATTN_BWD, 2.0 * attn_flop(d), attn_bwd(dt, qkv, Q3, a, da, lse, dvec, dqkv, at(ws, part_at), part_end - part_at, d.B, d.S,
-                                                       d.nh, d.nkv, d.d, ctx->rope_table, ctx->rope_seq, st));
+    TR(HH_TRACE_ATTN_BWD, 2.0 * attn_flop(d), attn_bwd(dt, at(saved, sl.qkv), d.Q3, at(saved, sl.a), at(ws, wl.da), (const float*)at(saved, sl.lse),
+                                                       (float*)at(ws, wl.dvec), at(ws, wl.dqkv), at(ws, part_at), part_end - part_at, d.B, d.S,
+                                                       d.nh, d.nkv, d.d, ctx->rope_table, ctx->rope_seq, p.stride(), st));
     HIP_TRY(run_group(2));
-    if (defer) HIP_TRY(tgemm(ctx, dt, dw, n_dw, st));
-    TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dxn, x, r1, w->g_attn, dh, dx, part1, part1_b, T, H, st));         // dx = dh + norm-bwd
-    if (sum_both) TR(HH_TRACE_ELEMENTWISE, 4.0 * (sums[0].rows + sums[1].rows) * H, colsum_reduce(sums, 2, H, acc, st));
-    else TR(HH_TRACE_ELEMENTWISE, 4.0 * sums[1].rows * H, colsum_reduce(sums + 1, 1, H, acc, st));
+    if (defer) HIP_TRY(pgemm(ctx, p, dt, b.dw, b.n_dw, st));
+    TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dhn, p.each(x), p.each(at(saved, sl.r1)), w->g_attn, dh, p.each(dx),
+                                                           part1, part1_b, p.n, T, H, st));         // d(xn) in dhn; dx = dh + norm-bwd
+    if (sum_both) TR(HH_TRACE_ELEMENTWISE, 4.0 * (sums[0].rows + sums[1].rows) * H, colsum_reduce(sums, 2, p.n, H, acc, st));
+    else TR(HH_TRACE_ELEMENTWISE, 4.0 * sums[1].rows * H, colsum_reduce(sums + 1, 1, p.n, H, acc, st));
     return HH_OK;
 }
 
@@ -630,7 +705,7 @@ extern "C" int hh_layer_bwd(hh_ctx* ctx, const hh_layer_cfg* cfg, const hh_layer
     if (!ctx) return fail(HH_ERR_INVALID_ARG, "ctx is NULL");
     TRY(ensure_rope(ctx, cfg));
     const Dims d = dims_of(cfg);
-    return layer_bwd_impl(ctx, d, cfg, w, x, saved, dy, dx, grads, accumulate, workspace, (hipStream_t)stream);
+    return layer_bwd_impl(ctx, ONE, d, w, x, saved, dy, dx, grads, accumulate, workspace, nullptr, (hipStream_t)stream);
 }
 
 // --------------------------------------------------------------- stage step
@@ -661,32 +736,92 @@ static int check_stage_args(const hh_layer_cfg* cfg, int n_layers, const hh_laye
     return HH_OK;
 }
 
-// Forward of micro-batch m through the stage, activations into pool slot `slot`.
-static int stage_fwd(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, int k, const hh_layer_weights* w, const StagePool& p,
-                     int slot, const void* x, void* y, void* workspace, hipStream_t st) {
+// Forward of a pass's micro-batches through the stage, activations into the pool slots from `slot` on.
+static int stage_fwd(hh_ctx* ctx, const Pass& ps, const Dims& d, const hh_layer_cfg* cfg, int k, const hh_layer_weights* w, const StagePool& p,
+                     int slot, const void* x, void* y, void* workspace, void* gemm_ws, hipStream_t st) {
     for (int l = 0; l < k; l++) {
         const void* in = l == 0 ? x : p.act(slot, l - 1);
         void* out = l == k - 1 ? y : p.act(slot, l);
-        TRY(layer_fwd_impl(ctx, d, cfg, &w[l], in, out, p.saved(slot, l), workspace, st));
+        TRY(layer_fwd_impl(ctx, ps, d, cfg, &w[l], in, out, p.saved(slot, l), workspace, gemm_ws, st));
     }
     return HH_OK;
 }
-// Backward of the micro-batch whose activations sit in pool slot `slot`.
-static int stage_bwd(hh_ctx* ctx, const Dims& d, const hh_layer_cfg* cfg, int k, const hh_layer_weights* w, const hh_layer_grads* g,
-                     const StagePool& p, int slot, const void* x, const void* dy, void* dx, int acc, void* workspace, hipStream_t st) {
-    void* gbuf = at(workspace, work_layout(d).total);  // gradient flowing between layers, updated in place
+// Backward of the micro-batches whose activations sit in the pool slots from `slot` on; gbuf: gradient flowing between layers,
+// updated in place.
+static int stage_bwd(hh_ctx* ctx, const Pass& ps, const Dims& d, int k, const hh_layer_weights* w, const hh_layer_grads* g,
+                     const StagePool& p, int slot, const void* x, const void* dy, void* dx, int acc, void* workspace, void* gbuf, void* gemm_ws,
+                     hipStream_t st) {
     for (int l = k - 1; l >= 0; l--) {
         const void* in = l == 0 ? x : p.act(slot, l - 1);
         const void* gin = l == k - 1 ? dy : gbuf;
         void* gout = l == 0 ? dx : gbuf;
-        TRY(layer_bwd_impl(ctx, d, cfg, &w[l], in, p.saved(slot, l), gin, gout, &g[l], acc, workspace, st));
+        TRY(layer_bwd_impl(ctx, ps, d, &w[l], in, p.saved(slot, l), gin, gout, &g[l], acc, workspace, gemm_ws, st));
     }
     return HH_OK;
+}
+
+// How many micro-batches (of at most n_live) go through the launches side by side: as many as the workspace holds, whose
+// size is that of one.  Side by side each has its own tensors (`unit` bytes, the gradient between layers behind them) where
+// one alone leaves room for the GEMMs' partial sums, and those partial sums behind the last one's.  Only small micro-batches fit, which
+// are also the ones whose launches leave most of the chip idle; and only where every GEMM goes to the ring kernel (bf16),
+// with the tile and split of a micro-batch by itself.
+static size_t side_unit(const Dims& d) { return work_layout(d).gemm_ws + act_bytes(d); }
+static int side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weights* w, const hh_layer_grads* g, int n_live, void* workspace) {
+    const size_t unit = side_unit(d), total = work_layout(d).total + act_bytes(d);
+    int n = std::min(n_live, MICRO_MAX);
+    if (d.dt != DT_BF16 || n < 2 || 2 * unit > total) return 1;
+    size_t partial = 0;   // of one micro-batch, the launch that has most
+    ctx->gemm_ws = workspace;   // plans ask for sizes and for whether there is scratch, not where anything is
+    for (int l = 0; l < k; l++) {
+        FwdGemms f;
+        fwd_gemms(d, &w[l], workspace, workspace, workspace, workspace, f);
+        BwdGemms b;
+        bwd_gemms(d, &w[l], &g[l], workspace, workspace, workspace, 1, b);
+        plan_deferral(ctx, d, b);
+        if (b.defer) return 1;
+        auto take = [&](GemmDesc* q, int m) {
+            size_t bytes = 0;
+            for (int i = 0; i < m; i++) gemm_scratch(ctx, q[i]);
+            if (!gemm_bf16_micro_bytes(q, m, &bytes)) return false;
+            partial = std::max(partial, bytes);
+            return true;
+        };
+        if (!take(f.qkv, f.n_qkv) || !take(&f.out, 1) || !take(f.gu, f.n_gu) || !take(&f.down, 1) || !take(&b.dm, 1)) return 1;
+        for (int i = 0; i < 3; i++)
+            if (!take(b.group[i], b.n[i])) return 1;
+    }
+    while (n > 1 && (size_t)n * (unit + partial) > total) n--;
+    return n;
+}
+
+// Whether the micro-batches' boundary tensors are buffers of their own (dx[m] may be dy[m], in all of them or none): only then
+// does it not matter in which order micro-batches touch them.
+static bool separate_buffers(const Dims& d, int n, const void* const* x, void* const* y, const void* const* dy, void* const* dx) {
+    struct Buf { uintptr_t at; int kind, m; };   // 0: x, 1: y, 2: dy, 3: dx
+    std::vector<Buf> v;
+    v.reserve((size_t)4 * n);
+    const bool in_place = dx[0] == dy[0];
+    for (int m = 0; m < n; m++) {
+        if ((dx[m] == dy[m]) != in_place) return false;
+        v.push_back({(uintptr_t)x[m], 0, m}); v.push_back({(uintptr_t)y[m], 1, m}); v.push_back({(uintptr_t)dy[m], 2, m});
+        if (!in_place) v.push_back({(uintptr_t)dx[m], 3, m});
+    }
+    std::sort(v.begin(), v.end(), [](const Buf& a, const Buf& b) { return a.at < b.at; });
+    const uintptr_t bytes = (uintptr_t)d.T * d.H * d.es;
+    for (size_t i = 1; i < v.size(); i++) {   // all of one length: if any two overlap, two neighbours do
+        if (v[i].at - v[i - 1].at >= bytes) continue;
+        const bool shared_input = v[i].at == v[i - 1].at && v[i].kind == v[i - 1].kind && (v[i].kind == 0 || (v[i].kind == 2 && !in_place));
+        if (!shared_input) return false;
+    }
+    return true;
 }
 
 // Both schedules: forward of the first n_live micro-batches, then backward of m followed by forward of
 // m + n_live.  n_live == n_micro is "all forwards, then all backwards".  Backward always visits the
 // micro-batches in ascending order, so the fp32 sums are formed in the same order for every n_live.
+// Small micro-batches go through the launches side by side, a pass of up to n_live of them after the other: forward of all
+// of a pass, then backward of all of it, which is the same results with no more activations alive.  Such launches are bound by
+// latency and by the one chain of work of a workgroup, not by a unit of the chip.
 static int stage_run(hh_ctx* ctx, const hh_layer_cfg* cfg, int n_layers, const hh_layer_weights* w, int n_micro, int n_live,
                      const void* const* x, void* const* y, const void* const* dy, void* const* dx, const hh_layer_grads* g,
                      int zero_grads_first, void* saved_pool, void* workspace, void* stream) {
@@ -704,15 +839,38 @@ static int stage_run(hh_ctx* ctx, const hh_layer_cfg* cfg, int n_layers, const h
     const Dims d = dims_of(cfg);
     const StagePool p = stage_pool(d, n_layers, saved_pool);
     hipStream_t st = (hipStream_t)stream;
-    for (int m = 0; m < n_live; m++) TRY(stage_fwd(ctx, d, cfg, n_layers, w, p, m, x[m], y[m], workspace, st));
+    const WorkLayout wl = work_layout(d);
+    const size_t unit = side_unit(d);
+    const int side = n_live > 1 && separate_buffers(d, n_micro, x, y, dy, dx) ? side_by_side(ctx, d, n_layers, w, g, n_live, workspace) : 1;
+    if (side > 1) {
+        for (int m = 0; m < n_micro; m += side) {
+            const Pass ps{std::min(side, n_micro - m), p.base, p.per_micro, (const char*)workspace, unit, x + m, y + m, dy + m, dx + m};
+            void* gemm_ws = at(workspace, (size_t)side * unit);
+            TRY(stage_fwd(ctx, ps, d, cfg, n_layers, w, p, 0, x[m], y[m], workspace, gemm_ws, st));
+            TRY(stage_bwd(ctx, ps, d, n_layers, w, g, p, 0, x[m], dy[m], dx[m], m > 0 || !zero_grads_first, workspace, at(workspace, wl.gemm_ws),
+                          gemm_ws, st));
+        }
+        return HH_OK;
+    }
+    void* gbuf = at(workspace, wl.total);
+    for (int m = 0; m < n_live; m++) TRY(stage_fwd(ctx, ONE, d, cfg, n_layers, w, p, m, x[m], y[m], workspace, nullptr, st));
     for (int m = 0; m < n_micro; m++) {
         const int acc = (m > 0 || !zero_grads_first) ? 1 : 0;
         const int slot = m % n_live;
-        TRY(stage_bwd(ctx, d, cfg, n_layers, w, g, p, slot, x[m], dy[m], dx[m], acc, workspace, st));
+        TRY(stage_bwd(ctx, ONE, d, n_layers, w, g, p, slot, x[m], dy[m], dx[m], acc, workspace, gbuf, nullptr, st));
         const int nxt = m + n_live;   // its activations take the slot just released
-        if (nxt < n_micro) TRY(stage_fwd(ctx, d, cfg, n_layers, w, p, slot, x[nxt], y[nxt], workspace, st));
+        if (nxt < n_micro) TRY(stage_fwd(ctx, ONE, d, cfg, n_layers, w, p, slot, x[nxt], y[nxt], workspace, nullptr, st));
     }
     return HH_OK;
+}
+
+// For tests, not part of the public interface: how many micro-batches such a call takes through its launches side by side.
+extern "C" int hh_internal_side_by_side(const hh_layer_cfg* cfg, int n_layers, const hh_layer_weights* w, const hh_layer_grads* g, int n_micro,
+                                        int n_live, const void* const* x, void* const* y, const void* const* dy, void* const* dx) {
+    const Dims d = dims_of(cfg);
+    hh_ctx ctx{0, nullptr, 0, 0, 0.f, {}, 0, false, 0u, nullptr, {}};
+    if (n_live < 2 || !separate_buffers(d, n_micro, x, y, dy, dx)) return 1;
+    return side_by_side(&ctx, d, n_layers, w, g, n_live, (void*)(uintptr_t)4096);
 }
 
 extern "C" int hh_stage_step(hh_ctx* ctx, const hh_layer_cfg* cfg, int n_layers, const hh_layer_weights* w, int n_micro,
@@ -765,14 +923,14 @@ extern "C" int hh_layer_profile(hh_ctx* ctx, const hh_layer_cfg* cfg, int n_laye
             const void* in = l == 0 ? x : p.act(0, l - 1);
             void* o = l == k - 1 ? gbuf : p.act(0, l);
             (void)hipEventRecord(ev[4 * l], st);
-            rc = layer_fwd_impl(ctx, d, cfg, &w[l], in, o, p.saved(0, l), workspace, st);
+            rc = layer_fwd_impl(ctx, ONE, d, cfg, &w[l], in, o, p.saved(0, l), workspace, nullptr, st);
             (void)hipEventRecord(ev[4 * l + 1], st);
         }
         for (int l = k - 1; l >= 0 && rc == HH_OK; l--) {
             const void* in = l == 0 ? x : p.act(0, l - 1);
             const void* gin = l == k - 1 ? dy : gbuf;
             (void)hipEventRecord(ev[4 * l + 2], st);
-            rc = layer_bwd_impl(ctx, d, cfg, &w[l], in, p.saved(0, l), gin, gbuf, &g[l], 1, workspace, st);
+            rc = layer_bwd_impl(ctx, ONE, d, &w[l], in, p.saved(0, l), gin, gbuf, &g[l], 1, workspace, nullptr, st);
             (void)hipEventRecord(ev[4 * l + 3], st);
         }
         if (rc != HH_OK) break;

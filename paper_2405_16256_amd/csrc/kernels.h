@@ -10,11 +10,18 @@ namespace hh {
 enum { DT_F32 = 0, DT_BF16 = 1 };
 inline size_t dt_size(int dt) { return dt == DT_BF16 ? 2 : 4; }
 
+// One operand of up to MICRO_MAX micro-batches that a launch takes side by side: its address in each of them.
+constexpr int MICRO_MAX = 8;
+struct Each { void* p[MICRO_MAX]; };
+
 // C[M,N] (=|+=) op(A) op(B) (+ R), leading dimensions in elements.
 //   GEMM_NT: A[M,K] row-major, B[N,K] row-major   (y = x W^T)
 //   GEMM_NN: A[M,K] row-major, B[K,N] row-major   (dX = dY W)
 //   GEMM_TN: A[K,M] row-major, B[K,N] row-major   (dW = dY^T X)
 enum { GEMM_NT = 0, GEMM_NN = 1, GEMM_TN = 2 };
+// The operands of a problem that the launch repeats for several micro-batches (weight gradients: C is the same in all of
+// them and their products are added in the order of the micro-batches, each as a launch of its own would add it).
+struct GemmMicro { Each A, B, C, R; };
 struct GemmDesc {
     int kind;
     int M, N, K;
@@ -28,7 +35,9 @@ struct GemmDesc {
     const void* B1; int k1;
     const void* B2; int k2;
     void* ws;                // optional scratch for k-split partial sums (bf16 path), may be NULL
-    size_t ws_bytes;
+    size_t ws_bytes;         // of one micro-batch: what a plan may use
+    int micro;               // micro-batches; above 1 (bf16, gemm_bf16_micro_bytes) their operands are in `each`
+    const GemmMicro* each;
 };
 constexpr size_t GEMM_WS_BYTES = (size_t)64 << 20;   // enough for 256 partial tiles of 256x256 fp32
 
@@ -43,33 +52,38 @@ hipError_t gemm(int dtype, const GemmDesc* g, int n, hipStream_t st);
 bool gemm_shares_launch(int dtype, const GemmDesc* g, int n);
 
 // xn = x * r * g, r = 1/sqrt(mean(x^2)+eps) per row.
-hipError_t rmsnorm_fwd(int dtype, const void* x, const void* g, void* xn, float* r,
-                       int T, int H, float eps, hipStream_t st);
+// Here and below: micro-batches 0 .. n-1 side by side, an operand's address in each of them; the result of a micro-batch
+// does not depend on n.
+hipError_t rmsnorm_fwd(int dtype, const Each& x, const void* g, const Each& xn, const Each& r,
+                       int n, int T, int H, float eps, hipStream_t st);
 // dx = dres + r*(w - u*mean(w*u)), u = x*r, w = dxn*g; per-workgroup column sums of
 // dxn*u go to partial[rmsnorm_bwd_blocks(T, H, partial_bytes)][H].
 int rmsnorm_bwd_blocks(int T, int H, size_t partial_bytes);
-hipError_t rmsnorm_bwd(int dtype, const void* dxn, const void* x, const float* r, const void* g,
-                       const void* dres, void* dx, float* partial, size_t partial_bytes, int T, int H, hipStream_t st);
-// out[H] (=|+=) column sums of partial[rows][H], one or two of them in one launch
-struct ColSum { const float* partial; int rows; float* out; };
-hipError_t colsum_reduce(const ColSum* jobs, int n, int H, int accumulate, hipStream_t st);
+hipError_t rmsnorm_bwd(int dtype, const Each& dxn, const Each& x, const Each& r, const void* g,
+                       const Each& dres, const Each& dx, const Each& partial, size_t partial_bytes, int n, int T, int H, hipStream_t st);
+// out[H] (=|+=) column sums of partial[rows][H], of one micro-batch after the other; one or two such sums in one launch
+struct ColSum { Each partial; int rows; float* out; };
+hipError_t colsum_reduce(const ColSum* jobs, int n_jobs, int n, int H, int accumulate, hipStream_t st);
 
 // In-place rotary embedding of the first nrot heads (query heads, then key heads) of every row of a
 // [T, ld] buffer.  table = cos[table_seq][d/2] followed by sin[table_seq][d/2], table_seq >= S.  (The backward rotation is
 // part of attn_bwd.)
-hipError_t rope(int dtype, void* qkv, int ld, int T, int S, int nrot, int d, const float* table, int table_seq,
+hipError_t rope(int dtype, const Each& qkv, int ld, int n, int T, int S, int nrot, int d, const float* table, int table_seq,
                 hipStream_t st);
 
 // gu[T,2F] = (gate | up);  m = silu(gate)*up
-hipError_t swiglu_fwd(int dtype, const void* gu, void* m, int T, int F, hipStream_t st);
+hipError_t swiglu_fwd(int dtype, const Each& gu, const Each& m, int n, int T, int F, hipStream_t st);
 // dgu[T,2F] = (dgate | dup), and m recomputed
-hipError_t swiglu_bwd(int dtype, const void* dm, const void* gu, void* dgu, void* m, int T, int F, hipStream_t st);
+hipError_t swiglu_bwd(int dtype, const Each& dm, const Each& gu, const Each& dgu, const Each& m, int n, int T, int F, hipStream_t st);
 
 // Causal attention over a [T, ld] buffer holding q | k | v column blocks of width nh*d, nkv*d, nkv*d;
 // query head h uses key/value head h / (nh / nkv).  o [T, nh*d]; lse [B, nh, S] natural-log sum-exp of
 // the scaled scores.
+// bf16: micro.n micro-batches side by side, micro.saved bytes apart in qkv, o and lse, micro.ws bytes in dout, dvec, dqkv and
+// scratch (fp32: one); how a micro-batch is split over workgroups does not depend on micro.n.
+struct MicroStride { int n; size_t saved, ws; };
 hipError_t attn_fwd(int dtype, const void* qkv, int ld, void* o, float* lse,
-                    int B, int S, int nh, int nkv, int d, hipStream_t st);
+                    int B, int S, int nh, int nkv, int d, const MicroStride& micro, hipStream_t st);
 // dqkv [T, ld] receives dq | dk | dv in the same layout.  dvec: scratch [B, nh, S] floats.  scratch: device
 // memory of scratch_bytes, at least attn_bwd_scratch_bytes() (partial dK, dV sums when the query heads that share a
 // key/value head are spread over several workgroups; may be null when it has no bytes; the fp32 path needs none and
@@ -79,6 +93,6 @@ hipError_t attn_fwd(int dtype, const void* qkv, int ld, void* o, float* lse,
 size_t attn_bwd_scratch_bytes(int dtype, int B, int S, int nh, int nkv, int d);
 hipError_t attn_bwd(int dtype, const void* qkv, int ld, const void* o, const void* dout, const float* lse,
                     float* dvec, void* dqkv, void* scratch, size_t scratch_bytes, int B, int S, int nh, int nkv, int d,
-                    const float* rope_table, int rope_seq, hipStream_t st);
+                    const float* rope_table, int rope_seq, const MicroStride& micro, hipStream_t st);
 
 }  // namespace hh

@@ -1,0 +1,105 @@
+"""Small micro-batches of a stage step go through the launches side by side: every result must be what one micro-batch after
+the other gives, bit for bit, and buffers that micro-batches share must keep their order."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2405_16256_amd import inputs as I
+from tests import stage_plans
+
+TINY = I.LayerShape(256, 4, 64, 704, 128, 1)
+# shape, packed, layers, micro-batches, alive, added to the gradients, dx over dy; the number side by side
+CASES = [
+    (TINY, True, 2, 5, 2, False, False, 2),                                             # a last pass of one
+    (TINY, True, 1, 9, 9, True, True, 8),                                               # more than one launch takes
+    (I.LayerShape(128, 2, 64, 128, 1, 1), True, 1, 3, 3, False, False, 3),              # one token
+    (I.LayerShape(128, 1, 128, 192, 37, 3, n_kv_heads=1), False, 2, 4, 3, True, False, 3),
+    (I.LayerShape(512, 8, 64, 768, 1100, 2, n_kv_heads=2), False, 2, 3, 3, False, False, 2),   # split weight gradients
+    (I.LayerShape(512, 4, 128, 64, 2049, 1, n_kv_heads=1), True, 1, 2, 2, True, True, 2),      # split ones, partial dK and dV
+    (I.LayerShape(1024, 8, 128, 2048, 700, 1, n_kv_heads=2), True, 1, 4, 4, True, False, 2),   # larger tiles
+    (I.LayerShape(192, 3, 64, 64, 65, 40), True, 1, 2, 2, False, False, 2),                     # rows past a tile, many samples
+]
+IDS = ["%dx%d T%d" % (c[0].hidden, c[0].ffn, c[0].seq * c[0].micro_batch) for c in CASES]
+
+
+@pytest.mark.parametrize("shape,packed,k,M,n_live,acc,in_place,side", CASES, ids=IDS)
+def test_rule(shape, packed, k, M, n_live, acc, in_place, side):
+    buffers = stage_plans.boundary(shape, 2, M, in_place)
+    assert stage_plans.side_by_side(shape, k, M, n_live, packed, buffers=buffers) == side
+    assert stage_plans.side_by_side(shape, k, M, 1, packed, buffers=buffers) == 1
+
+
+def test_rule_leaves_out():
+    assert stage_plans.side_by_side(TINY, 2, 4, 4, bf16=False) == 1                    # fp32
+    assert stage_plans.side_by_side(I.CFG2, 1, 4, 4) == 1                              # no room in the workspace, tiles of 256
+    x, y, dy, dx = stage_plans.boundary(TINY, 2, 3)
+    bytes_ = 2 * 128 * 256
+
+    def side(x=x, y=y, dy=dy, dx=dx):
+        return stage_plans.side_by_side(TINY, 1, 3, 3, buffers=[x, y, dy, dx])
+    assert side() == 3 and side(x=x[:1] * 3) == 3 and side(dy=dy[:1] * 3) == 3 and side(dx=dy) == 3
+    for shared in (dict(y=y[:1] * 3), dict(dx=dx[:1] * 3), dict(dx=[dy[1], dy[2], dx[0]]), dict(dx=[dy[0], dx[1], dx[2]]),
+                   dict(dy=y), dict(dy=dy[:1] * 3, dx=dy[:1] * 3), dict(y=[x[1], y[1], y[2]]), dict(dx=x),
+                   dict(y=[y[0], y[0] + bytes_ - 16, y[2]]), dict(dy=x)):
+        assert side(**shared) == 1, shared
+    assert side(y=[y[0], y[0] + bytes_, y[2]]) == 3                                    # right behind one another
+
+
+def _stage(hh, L, ctx, cfg, layers, n_live, xs, ys, dys, dxs, zero_first):
+    pool_b, ws_b = hh.hh_stage_sizes(cfg, len(layers), n_live)
+    pool = torch.full((pool_b + 4096,), 0xFF, dtype=torch.uint8, device=L.DEV)         # bf16 NaN wherever nothing is written
+    ws = torch.full((ws_b + 4096,), 0xFF, dtype=torch.uint8, device=L.DEV)
+    hh.hh_stage_step_1f1b(ctx, cfg, [l.wstruct for l in layers], n_live, xs, ys, dys, dxs, [l.gstruct for l in layers], zero_first,
+                          pool[:pool_b], ws[:ws_b], L.stream_ptr())
+    torch.cuda.synchronize()
+    assert (pool[pool_b:] == 0xFF).all() and (ws[ws_b:] == 0xFF).all()
+
+
+def _inputs(L, shape, packed, k, M):
+    layers = [[L.DeviceLayer(I.layer_weights(811, l, shape, True), shape, True, packed) for l in range(k)] for _ in range(2)]
+    acts = [I.activations(811, shape, m, True) for m in range(M)]
+    return layers, [L.to_dev(a[0], True) for a in acts], [L.to_dev(a[1], True) for a in acts]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,packed,k,M,n_live,acc,in_place,side", CASES, ids=IDS)
+def test_same_bits_as_one_by_one(shape, packed, k, M, n_live, acc, in_place, side):
+    from paper_2405_16256_amd import binding as hh
+    from paper_2405_16256_amd import glue as L
+    ctx = hh.hh_ctx_create(0)
+    cfg = L.cfg_of(shape, True)
+    (side_layers, one_layers), xs, dys = _inputs(L, shape, packed, k, M)
+    out = []
+    for layers, live in ((side_layers, n_live), (one_layers, 1)):
+        for l in layers:
+            for n in I.WEIGHT_NAMES:
+                l.g[n].fill_(0.75 if acc else float("nan"))
+        ys = [torch.full_like(t, float("nan")) for t in xs]
+        g_in = [t.clone() for t in dys]
+        dxs = g_in if in_place else [torch.full_like(t, float("nan")) for t in xs]
+        _stage(hh, L, ctx, cfg, layers, live, xs, ys, g_in, dxs, not acc)
+        out.append((ys, dxs))
+    for m in range(M):
+        assert torch.isfinite(out[0][0][m]).all() and torch.isfinite(out[0][1][m]).all()
+        assert torch.equal(out[0][0][m], out[1][0][m]) and torch.equal(out[0][1][m], out[1][1][m]), m
+    for a, b in zip(side_layers, one_layers):
+        for n in I.WEIGHT_NAMES:
+            assert torch.isfinite(a.g[n]).all() and torch.equal(a.g[n], b.g[n]), n
+    hh.hh_ctx_destroy(ctx)
+
+
+@pytest.mark.gpu
+def test_micro_batches_that_share_an_output_keep_their_order():
+    from paper_2405_16256_amd import binding as hh
+    from paper_2405_16256_amd import glue as L
+    ctx = hh.hh_ctx_create(0)
+    cfg = L.cfg_of(TINY, True)
+    (layers, ref), xs, dys = _inputs(L, TINY, True, 1, 3)
+    y, dx = torch.empty_like(xs[0]), torch.empty_like(xs[0])
+    _stage(hh, L, ctx, cfg, layers, 3, xs, [y] * 3, dys, [dx] * 3, True)
+    ys, dxs = [torch.empty_like(t) for t in xs], [torch.empty_like(t) for t in xs]
+    _stage(hh, L, ctx, cfg, ref, 1, xs, ys, dys, dxs, True)
+    assert torch.equal(y, ys[2]) and torch.equal(dx, dxs[2])
+    for n in I.WEIGHT_NAMES:
+        assert np.array_equal(L.to_np(layers[0].g[n]), L.to_np(ref[0].g[n])), n
+    hh.hh_ctx_destroy(ctx)
