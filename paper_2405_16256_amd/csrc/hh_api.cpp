@@ -10,6 +10,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <vector>
 
@@ -797,18 +798,19 @@ static int side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weight
 // Whether the micro-batches' boundary tensors are buffers of their own (dx[m] may be dy[m], in all of them or none): only then
 // does it not matter in which order micro-batches touch them.
 static bool separate_buffers(const Dims& d, int n, const void* const* x, void* const* y, const void* const* dy, void* const* dx) {
-    struct Buf { uintptr_t at; int kind, m; };   // 0: x, 1: y, 2: dy, 3: dx
-    std::vector<Buf> v;
-    v.reserve((size_t)4 * n);
+    struct Buf { uintptr_t at; int kind; };   // 0: x, 1: y, 2: dy, 3: dx
+    const std::unique_ptr<Buf[]> v(new (std::nothrow) Buf[(size_t)4 * n]);
+    if (!v) return false;
     const bool in_place = dx[0] == dy[0];
+    size_t k = 0;
     for (int m = 0; m < n; m++) {
         if ((dx[m] == dy[m]) != in_place) return false;
-        v.push_back({(uintptr_t)x[m], 0, m}); v.push_back({(uintptr_t)y[m], 1, m}); v.push_back({(uintptr_t)dy[m], 2, m});
-        if (!in_place) v.push_back({(uintptr_t)dx[m], 3, m});
+        v[k++] = {(uintptr_t)x[m], 0}; v[k++] = {(uintptr_t)y[m], 1}; v[k++] = {(uintptr_t)dy[m], 2};
+        if (!in_place) v[k++] = {(uintptr_t)dx[m], 3};
     }
-    std::sort(v.begin(), v.end(), [](const Buf& a, const Buf& b) { return a.at < b.at; });
+    std::sort(v.get(), v.get() + k, [](const Buf& a, const Buf& b) { return a.at < b.at; });
     const uintptr_t bytes = (uintptr_t)d.T * d.H * d.es;
-    for (size_t i = 1; i < v.size(); i++) {   // all of one length: if any two overlap, two neighbours do
+    for (size_t i = 1; i < k; i++) {   // all of one length: if any two overlap, two neighbours do
         if (v[i].at - v[i - 1].at >= bytes) continue;
         const bool shared_input = v[i].at == v[i - 1].at && v[i].kind == v[i - 1].kind && (v[i].kind == 0 || (v[i].kind == 2 && !in_place));
         if (!shared_input) return false;
