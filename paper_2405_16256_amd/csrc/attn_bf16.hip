@@ -195,7 +195,7 @@ __device__ __forceinline__ void mfma_stream(L load, M mma, W side) {
 // The operand of micro-batch m (blockIdx.y) where consecutive ones lie `stride` bytes apart.
 template <typename T>
 __device__ __forceinline__ T* micro_at(T* p, size_t stride) {
-    return (T*)((uintptr_t)p + blockIdx.y * stride);
+    return (T*)((const char*)p + blockIdx.y * stride);
 }
 
 // ------------------------------------------------------------------ forward
