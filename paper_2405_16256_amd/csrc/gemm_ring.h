@@ -102,8 +102,7 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB>& g) {
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
     const int kseg0 = g.kseg[0], kseg1 = g.kseg[1];
     int kissue = kbeg, missue = micro;   // k tile and micro-batch that `issue` fetches next
-    auto issue = [&](int slot) {
-        const uint32_t base = lds0 + slot * STAGE;
+    auto next_tile = [&]() {
         if (KIND == GEMM_NN && (kissue == kseg0 || kissue == kseg1)) rsB = rsrc_b(micro, kissue);
         if (SUMS && kissue == kbeg + nk) {   // the next micro-batch's product
             kissue = kbeg;
@@ -116,11 +115,33 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB>& g) {
             for (int i = 0; i < DB::PER_WAVE; i++) voB[i] -= (uint32_t)nk * stepB;
         }
         kissue++;
-#pragma unroll
-        for (int i = 0; i < DA::PER_WAVE; i++) { dma16(base + (wave * DA::PER_WAVE + i) * 1024, voA[i], rsA); voA[i] += stepA; }
-#pragma unroll
-        for (int i = 0; i < DB::PER_WAVE; i++) { dma16(base + DA::BYTES + (wave * DB::PER_WAVE + i) * 1024, voB[i], rsB); voB[i] += stepB; }
     };
+    // quarter Q of the DMA instructions that fetch a k tile (-1: all of them)
+    auto issue_part = [&](int slot, auto quarter) {
+        constexpr int Q = decltype(quarter)::value;
+        const uint32_t base = lds0 + slot * STAGE;
+#pragma unroll
+        for (int i = 0; i < DA::PER_WAVE; i++)
+            if (Q < 0 || i * 4 / PW == Q) { dma16(base + (wave * DA::PER_WAVE + i) * 1024, voA[i], rsA); voA[i] += stepA; }
+#pragma unroll
+        for (int i = 0; i < DB::PER_WAVE; i++)
+            if (Q < 0 || (DA::PER_WAVE + i) * 4 / PW == Q) {
+                dma16(base + DA::BYTES + (wave * DB::PER_WAVE + i) * 1024, voB[i], rsB);
+                voB[i] += stepB;
+            }
+    };
+    auto issue = [&](int slot) {
+        next_tile();
+        issue_part(slot, std::integral_constant<int, -1>{});
+    };
+    // The memory pipe takes 16 cycles over a DMA instruction of 1 KB, and a wave whose instruction has to wait for it issues
+    // no MFMA meanwhile.  NT problems on the larger tiles spread the instructions that refill a slot over the four k steps
+    // that follow its release, a quarter behind each step's MFMAs: 333x22016x4096 (192x192 tiles) 81 -> 72 us, 333x12288x4096
+    // (192x128) 52 -> 50, 333x4096x4096 (128x128) 24.2 -> 23.1.  Not with two stages, where the tile would be waited for right
+    // after its last quarter (3300x8192x4096, 192x256 tiles: 87 -> 106), not on the smallest tiles, whose loops are short
+    // chains (nine launches of a 700-token forward pass 67.4 -> 69.3), and not beside the transposing fragment reads of NN
+    // and TN (backward of hidden 448, 3348 tokens: 176 -> 182).
+    constexpr bool SPREAD = KIND == GEMM_NT && NS > 2 && BM * BN >= 128 * 128;
 #pragma unroll
     for (int s = 0; s < NS; s++)
         if (s < nt) issue(s);
@@ -241,15 +262,20 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB>& g) {
                 for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0);
         };
         fetch(0, 0, 0);
-        int slot = 0;
+        int slot = 0, freed = 0;
+        bool refill = false;   // the slot freed last is still being refilled
         for (int kt = 0; kt < nt; kt++) {
             const int next = slot + 1 == NS ? 0 : slot + 1;
-#pragma unroll
-            for (int kk = 0; kk < 3; kk++) {
+            auto step = [&](auto k) {
+                constexpr int kk = decltype(k)::value;
                 fetch((kk + 1) & 1, slot, kk + 1);
                 mma(kk & 1);
+                if (SPREAD && refill) issue_part(freed, std::integral_constant<int, kk + 1>{});
                 __builtin_amdgcn_sched_barrier(0);
-            }
+            };
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
+            step(std::integral_constant<int, 2>{});
             // Every wave holds its last fragments of k tile kt, so its slot is free once all waves are here; k tile kt + 1
             // must have landed for everyone, the NS - 2 tiles after it may still be on their way.
             if (kt + NS <= nt) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * PW) : "memory");
@@ -257,11 +283,15 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB>& g) {
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             __builtin_amdgcn_sched_barrier(0);
-            if (kt + NS < nt) issue(slot);
+            refill = kt + NS < nt;
+            if (refill) next_tile();
+            if (!SPREAD && refill) issue_part(slot, std::integral_constant<int, -1>{});
             if (kt + 1 < nt) fetch(0, next, 0);
             mma(1);
+            if (SPREAD && refill) issue_part(slot, std::integral_constant<int, 0>{});
             __builtin_amdgcn_sched_barrier(0);
             fold();
+            freed = slot;
             slot = next;
         }
     }
