@@ -251,7 +251,7 @@ typedef enum {
     HH_TRACE_GEMM_TN = 2,      /* weight gradients          dW = dY^T X  */
     HH_TRACE_ATTN_FWD = 3,
     HH_TRACE_ATTN_BWD = 4,
-    HH_TRACE_ELEMENTWISE = 5,  /* RMSNorm, RoPE, SwiGLU, gain-gradient reduction */
+    HH_TRACE_ELEMENTWISE = 5,  /* RMSNorm, RoPE, SwiGLU (unless a small layer's GEMM does the latter two), gain-gradient reduction */
     HH_TRACE_KINDS = 6
 } hh_trace_kind;
 typedef struct {

@@ -79,6 +79,22 @@ struct Ops {
     __device__ __forceinline__ void* at(int m) const { return p[N == 1 ? 0 : m]; }
 };
 
+// ---- the arithmetic of the elementwise kernels, which GEMM epilogues share ----
+// (a, b) rotated by the angle of cosine c and sine s
+__device__ __forceinline__ void rotate_pair(float& a, float& b, float c, float s) {
+    const float x = fmaf(a, c, -(b * s));   // spelled out: the same bits wherever it is inlined
+    b = fmaf(b, c, a * s);
+    a = x;
+}
+__device__ __forceinline__ float swiglu(float gate, float up) { return gate / (1.0f + expf(-gate)) * up; }
+__device__ __forceinline__ void swiglu_grad(float gate, float up, float dm, float& dgate, float& dup, float& m) {
+    const float sg = 1.0f / (1.0f + expf(-gate));
+    const float sl = gate * sg;
+    m = sl * up;
+    dgate = dm * up * sg * fmaf(gate, 1.0f - sg, 1.0f);
+    dup = dm * sl;
+}
+
 // ---- dynamic LDS above the 48 KB default -------------------------------------
 // The limit is an attribute of the (kernel, device) pair.  `done` is the calling launcher's own record (one
 // bit per device, one record per kernel instantiation) of where it has been raised already.

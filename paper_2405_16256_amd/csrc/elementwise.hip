@@ -301,17 +301,13 @@ __global__ __launch_bounds__(TPB) void k_rope(Ops<N> qkv, int ld, int Ttok, int 
     T* p = (T*)qkv.at(blockIdx.y) + (size_t)t * ld + (size_t)head * d + iv * V;
     const float* cs = table + ((size_t)pos * half + iv * V);
     const float* sn = cs + (size_t)table_seq * half;
-    float a[V], b[V], oa[V], ob[V];
+    float a[V], b[V];
     Vec<T>::load(p, a);
     Vec<T>::load(p + half, b);
 #pragma unroll
-    for (int e = 0; e < V; e++) {
-        const float c = cs[e], s = sn[e];
-        oa[e] = a[e] * c - b[e] * s;
-        ob[e] = b[e] * c + a[e] * s;
-    }
-    Vec<T>::store(p, oa);
-    Vec<T>::store(p + half, ob);
+    for (int e = 0; e < V; e++) rotate_pair(a[e], b[e], cs[e], sn[e]);
+    Vec<T>::store(p, a);
+    Vec<T>::store(p + half, b);
 }
 
 // ------------------------------------------------------------------- SwiGLU
@@ -328,7 +324,7 @@ __global__ __launch_bounds__(TPB) void k_swiglu_fwd(Ops<N> gu_, Ops<N> m_, int T
     Vec<T>::load(gu + (size_t)t * 2 * F + c, gt);
     Vec<T>::load(gu + (size_t)t * 2 * F + F + c, u);
 #pragma unroll
-    for (int e = 0; e < V; e++) o[e] = gt[e] / (1.0f + expf(-gt[e])) * u[e];
+    for (int e = 0; e < V; e++) o[e] = swiglu(gt[e], u[e]);
     Vec<T>::store(m + (size_t)t * F + c, o);
 }
 
@@ -346,13 +342,7 @@ __global__ __launch_bounds__(TPB) void k_swiglu_bwd(Ops<N> dm_, Ops<N> gu_, Ops<
     Vec<T>::load(gu + (size_t)t * 2 * F + F + c, u);
     Vec<T>::load(dm + (size_t)t * F + c, d);
 #pragma unroll
-    for (int e = 0; e < V; e++) {
-        const float sg = 1.0f / (1.0f + expf(-gt[e]));
-        const float sl = gt[e] * sg;
-        om[e] = sl * u[e];
-        og[e] = d[e] * u[e] * sg * (1.0f + gt[e] * (1.0f - sg));
-        ou[e] = d[e] * sl;
-    }
+    for (int e = 0; e < V; e++) swiglu_grad(gt[e], u[e], d[e], og[e], ou[e], om[e]);
     Vec<T>::store(dgu + (size_t)t * 2 * F + c, og);
     Vec<T>::store(dgu + (size_t)t * 2 * F + F + c, ou);
     Vec<T>::store(m + (size_t)t * F + c, om);

@@ -437,9 +437,11 @@ static hipError_t launch_ring_n(const GemmDesc* g, const int* order, const int* 
         const int nk = (q.K + DK - 1) / DK;
         if constexpr (MB == 1) {
             p.A.p[0] = const_cast<void*>(q.A); p.B.p[0] = const_cast<void*>(q.B); p.C.p[0] = q.C; p.R.p[0] = const_cast<void*>(q.R);
+            p.X.p[0] = q.fuse.X; p.Y.p[0] = q.fuse.Y;
         } else {
             for (int m = 0; m < MB; m++) {
                 p.A.p[m] = q.each->A.p[m]; p.B.p[m] = q.each->B.p[m]; p.C.p[m] = q.each->C.p[m]; p.R.p[m] = q.each->R.p[m];
+                p.X.p[m] = q.each->X.p[m]; p.Y.p[m] = q.each->Y.p[m];
             }
         }
         p.kseg[0] = q.k1 ? q.k1 / DK : INT_MAX; p.kseg[1] = q.k2 ? q.k2 / DK : INT_MAX;
@@ -449,6 +451,8 @@ static hipError_t launch_ring_n(const GemmDesc* g, const int* order, const int* 
         p.accumulate = q.accumulate;
         p.tiles = ((q.M + BM - 1) / BM) * ((q.N + BN - 1) / BN);
         p.ksplit = s;
+        p.fuse = q.fuse.kind; p.period = q.fuse.period; p.rot = q.fuse.rot; p.tokens = q.fuse.seq; p.table_seq = q.fuse.table_seq; p.table = q.fuse.table;
+        p.shift = q.fuse.kind == FUSE_ROPE ? (q.fuse.period == 128 ? 7 : 6) : 31;
         p.first = first;
         p.micro = q.micro;
         p.seq = q.kind == GEMM_TN && s == 1 ? q.micro : 1;
@@ -457,8 +461,9 @@ static hipError_t launch_ring_n(const GemmDesc* g, const int* order, const int* 
             if (nk < s) return hipErrorInvalidValue;
             p.partial = partial;
             partial += (size_t)p.tiles * s * q.micro * BM * BN;
-            const int blocks = (int)(((long)q.M * (q.N / 4) + 255) / 256);
-            red.j[red.n++] = typename RingReduce<MB>::Job{p.C, p.R, p.partial, s, q.ldc, q.ldr, q.M, q.N, q.accumulate, q.out_f32, red_first, q.micro, blocks};
+            const int blocks = (int)(((long)q.M * (q.N / (p.fuse == FUSE_ROPE || p.fuse == FUSE_SWIGLU ? 8 : 4)) + 255) / 256);
+            red.j[red.n++] = typename RingReduce<MB>::Job{p.C, p.R, p.X, p.Y, p.partial, s, q.ldc, q.ldr, q.M, q.N, q.accumulate, q.out_f32, red_first,
+                                                               q.micro, blocks, p.fuse, p.period, p.shift, p.rot, p.tokens, p.table_seq, p.table};
             red_first += blocks * (q.out_f32 ? 1 : q.micro);
         }
     }
@@ -513,6 +518,7 @@ static double stage_us(const Variant& q, long busy, double ks) {
 static double out_bytes(const GemmDesc& g) { return (double)g.M * g.N * (g.out_f32 ? 8 : 2); }
 static double floor_us(const GemmDesc& g) { return (2.0 * g.K * ((double)g.M + g.N) + out_bytes(g)) / 5.0e6; }
 static long tiles_of(const GemmDesc& g, const Variant& q) { return (long)((g.M + q.bm - 1) / q.bm) * ((g.N + q.bn - 1) / q.bn); }
+static int tile_size(int v) { return VARIANTS[v].bm * VARIANTS[v].bn; }
 static bool may_split(const GemmDesc& g, const Variant& q, int s) {
     const long tiles = tiles_of(g, q);
     return s == 1 || (g.ws && (g.K + DK - 1) / DK / s >= 2 && tiles * (s - 1) <= 700 &&
@@ -696,6 +702,13 @@ static hipError_t check(const GemmDesc& g) {
     if ((g.out_f32 != 0) != (g.kind == GEMM_TN) || (g.out_f32 && g.R)) return hipErrorInvalidValue;
     // segments of B: rows of an NN problem, in order, each a whole number of k tiles
     if (g.k1 && (g.kind != GEMM_NN || !g.B1 || g.k1 % DK || g.k1 >= g.K)) return hipErrorInvalidValue;
+    // fusions: whole heads of 64 or 128 columns, a whole gate|up row, a whole dm row; nothing is added
+    const GemmFuse& f = g.fuse;
+    if (f.kind && (g.R || g.accumulate)) return hipErrorInvalidValue;
+    if (f.kind == FUSE_ROPE && (g.kind != GEMM_NT || (f.period != 64 && f.period != 128) || g.N % f.period || f.rot % f.period || f.rot > g.N ||
+                                !f.table || f.seq <= 0 || f.table_seq < f.seq)) return hipErrorInvalidValue;
+    if (f.kind == FUSE_SWIGLU && (g.kind != GEMM_NT || f.period != g.N || g.N % 64 || g.ldc != g.N || !f.X)) return hipErrorInvalidValue;
+    if (f.kind == FUSE_SWIGLU_BWD && (g.kind != GEMM_NN || !f.X || !f.Y || (long)g.M * g.N * 4 >= (1L << 31))) return hipErrorInvalidValue;
     if (g.k2 && (!g.k1 || !g.B2 || g.k2 % DK || g.k2 <= g.k1 || g.k2 >= g.K)) return hipErrorInvalidValue;
     return hipSuccess;
 }
@@ -766,22 +779,23 @@ bool gemm_bf16_shares_launch(const GemmDesc* g, int n) {
     return r.how != Route::APART;
 }
 
-// Whether the launches that `n` problems take can take them for several micro-batches at once (only the ring kernel does),
-// and what partial sums those launches keep for each micro-batch.
-bool gemm_bf16_micro_bytes(const GemmDesc* g, int n, size_t* bytes) {
+bool gemm_bf16_on_ring(const GemmDesc* g, int n, RingUse* use) {
     if (n < 1 || n > RING_MAX) return false;
     Route r;
     route(g, n, r);
     if (r.how == Route::TILES256 || (r.how == Route::RING && r.group.v >= V_DMA)) return false;
-    size_t total = 0;
+    *use = RingUse{0, 0, 0};
     for (int i = 0; i < n; i++) {
-        const Plan& p = r.how == Route::RING ? r.group : r.each[i];
+        const bool ring = r.how == Route::RING;
+        const Plan& p = ring ? r.group : r.each[i];
         if (p.v >= V_DMA) return false;
-        const int s = p.ksplit[r.how == Route::RING ? i : 0];
-        const size_t b = s > 1 ? (size_t)tiles_of(g[i], VARIANTS[p.v]) * s * VARIANTS[p.v].bm * VARIANTS[p.v].bn * sizeof(float) : 0;
-        total = r.how == Route::RING ? total + b : std::max(total, b);
+        const int s = p.ksplit[ring ? i : 0], tile = tile_size(p.v);
+        const long w = tiles_of(g[i], VARIANTS[p.v]) * s;
+        const size_t b = s > 1 ? (size_t)w * tile * sizeof(float) : 0;
+        use->partial = ring ? use->partial + b : std::max(use->partial, b);
+        use->workgroups = ring ? use->workgroups + w : std::max(use->workgroups, w);
+        use->tile = std::max(use->tile, tile);
     }
-    *bytes = total;
     return true;
 }
 
@@ -795,8 +809,10 @@ hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st) {
     }
     Route r;
     route(g, n, r);
-    for (int i = 0; i < n; i++)   // several micro-batches: what gemm_bf16_micro_bytes allows
-        if (g[i].micro < 1 || g[i].micro > MICRO_MAX || g[i].micro != g[0].micro || (g[i].micro > 1 && (!g[i].each || r.how == Route::TILES256 || (r.how == Route::RING ? r.group.v : r.each[i].v) >= V_DMA)))
+    for (int i = 0; i < n; i++)   // several micro-batches, fusions: where gemm_bf16_on_ring says so
+        if (g[i].micro < 1 || g[i].micro > MICRO_MAX || g[i].micro != g[0].micro || (g[i].micro > 1 && !g[i].each) ||
+            ((g[i].micro > 1 || g[i].fuse.kind) && (r.how == Route::TILES256 || (r.how == Route::RING ? r.group.v : r.each[i].v) >= V_DMA)) ||
+            (g[i].fuse.kind && tile_size(r.how == Route::RING ? r.group.v : r.each[i].v) > fuse_tile(g[i].fuse.kind)))
             return hipErrorInvalidValue;
     if (r.how == Route::RING) return launch_planned(g, n, r.group, st);
     if (r.how == Route::TILES256) return launch_tiles256(g, n, st);

@@ -27,15 +27,32 @@ namespace hh {
 // micro-batch by itself, so every result is what a launch per micro-batch gives, bit for bit.  Bound as before by one
 // workgroup's chain and by launch latency, of which there are fewer: a 4-layer stage of hidden 256, 128 tokens and 8
 // micro-batches, two at a time, 2671 -> 1485 us; 2 layers of hidden 512, 2200 tokens, 3 micro-batches, two and one, 1092 -> 899 us.
+//
+// Fused problems (GemmFuse).  The rotary embedding and SwiGLU combine columns far apart: (c, c + period/2) of a head or of a
+// gate|up row.  The workgroup's columns are therefore taken from B's rows in another order (any order is free: each lane
+// asks for its own row): a 32-column block holds 16 columns of the first half and their 16 partners, which an accumulator
+// lane then both owns, 4q + e and 4(q + 2) + e.  C is written back in its own order, in runs of 16 columns.  Bound by launch
+// latency, of which two launches of nine forward and one of ten backward go: forward of hidden 1024, 700 tokens 67.6 -> 65.9 us,
+// of hidden 192, 22 tokens 35.6 -> 34.1.  (Cosines asked for before the k loop, so that they need not be waited for behind it,
+// hold up the first tiles: 67.0.)
 constexpr int RING_MAX = 4;
+// the column of C that column c (of N) of the workgroups' order stands for; period 2^shift, or N (shift 31)
+__device__ __forceinline__ int pair_column(int c, int period, int shift, int N) {
+    if (c >= N) return c;
+    const int first = (c >> shift) * period, r = c - first;
+    return first + (r >> 5) * 16 + (r & 15) + ((r & 16) ? period / 2 : 0);
+}
+__device__ __forceinline__ float as_bf(float v) { return lo_bf(pack_bf2(v, 0.f)); }
 template <int MB>             // how many micro-batches a launch may stand for: 1 or MICRO_MAX
 struct RingProblem {
-    Ops<MB> A, B, C, R;
+    Ops<MB> A, B, C, R, X, Y;
     const bf16_t* Bseg[2];     // NN: where the rows of B from k tile kseg[0] (kseg[1]) on are; INT_MAX: no such segment
     float* partial;            // k shares: [tile][micro-batch][share][BM*BN] fp32 sums
     uint32_t a_bytes, b_bytes; // extent of A, and of B up to the first segment's end
     int kseg[2];
     int kind, lda, ldb, ldc, ldr, M, N, K, accumulate, tiles, ksplit, first, micro, seq;
+    int fuse, period, shift, rot, tokens, table_seq;   // tokens of a sample
+    const float* table;
 };
 template <int MB>
 struct RingGroup {
@@ -50,6 +67,7 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB>& g) {
     using DA = DmaTile<(KIND != GEMM_TN), BM, NW>;
     using DB = DmaTile<(KIND == GEMM_NT), BN, NW>;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+    constexpr bool FUSES = KIND != GEMM_TN && BM * BN <= fuse_tile(KIND == GEMM_NT ? FUSE_SWIGLU : FUSE_SWIGLU_BWD);
     constexpr int STAGE = DA::BYTES + DB::BYTES;
     constexpr int PW = DA::PER_WAVE + DB::PER_WAVE;       // DMA instructions per wave and stage
     static_assert(NS * STAGE >= NW * 4096, "the epilogue patches reuse the ring");
@@ -98,7 +116,14 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB>& g) {
 #pragma unroll
     for (int i = 0; i < DA::PER_WAVE; i++) voA[i] = DA::voff(wave, i, m0, lda) + kbeg * stepA;
 #pragma unroll
-    for (int i = 0; i < DB::PER_WAVE; i++) voB[i] = DB::voff(wave, i, n0, ldb) + kbeg * stepB;
+    for (int i = 0; i < DB::PER_WAVE; i++) {
+        int row0 = n0;
+        if (KIND == GEMM_NT && FUSES && g.fuse) {   // voff adds the lane's row of the tile
+            const int r = DB::row(wave, i);
+            row0 = pair_column(n0 + r, g.period, g.shift, N) - r;
+        }
+        voB[i] = DB::voff(wave, i, row0, ldb) + kbeg * stepB;
+    }
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
     const int kseg0 = g.kseg[0], kseg1 = g.kseg[1];
     int kissue = kbeg, missue = micro;   // k tile and micro-batch that `issue` fetches next
@@ -327,18 +352,68 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB>& g) {
     char* const patch = smem + wave * 4096;
     const int r_w = lane & 31;                       // row written, chunks 2g + hf
     const int r_r = lane >> 3, c_r = lane & 7;       // row (+ 8t) and chunk read back
+    const int fuse = FUSES ? g.fuse : FUSE_NONE;
+    const bool gates = FUSES && fuse > FUSE_ROPE;
+    const __amdgpu_buffer_rsrc_t rsX = make_rsrc(KIND == GEMM_NN && gates ? g.X.at(micro) : Cv, KIND == GEMM_NN && gates ? (uint32_t)((size_t)M * 2 * N * 2u) : 0u);
+    const __amdgpu_buffer_rsrc_t rsM = make_rsrc(KIND == GEMM_NT && gates ? g.X.at(micro) : Cv, KIND == GEMM_NT && gates ? (uint32_t)((size_t)M * N) : 0u);
+    const __amdgpu_buffer_rsrc_t rsY = make_rsrc(KIND == GEMM_NN && gates ? g.Y.at(micro) : Cv, KIND == GEMM_NN && gates ? (uint32_t)((size_t)M * 2 * N * 2u) : 0u);
 #pragma unroll
-    for (int i = 0; i < TM; i++)
+    for (int i = 0; i < TM; i++) {
+        int pos = 0;
+        if (KIND == GEMM_NT && fuse == FUSE_ROPE) pos = (m0 + wm + 32 * i + r_w) % g.tokens;
 #pragma unroll
         for (int j = 0; j < TN; j++) {
-            const int col = n0 + wn + 32 * j + 4 * c_r;
+            const int block = n0 + wn + 32 * j;
+            int col = block + 4 * c_r;
+            if (KIND == GEMM_NT && fuse) {
+                const int half = g.period / 2, base = pair_column(block, g.period, g.shift, N);
+                col = block >= N ? block : base + (c_r < 4 ? 4 * c_r : half + 4 * (c_r - 4));
+                if (fuse == FUSE_SWIGLU || block < g.rot) {
+                    float4 cs[2], sn[2];
+                    if (fuse == FUSE_ROPE) {
+                        const float* t = g.table + (size_t)pos * half + (base & (g.period - 1)) + 4 * hf;
+#pragma unroll
+                        for (int q = 0; q < 2; q++) {
+                            cs[q] = *reinterpret_cast<const float4*>(t + 8 * q);
+                            sn[q] = *reinterpret_cast<const float4*>(t + 8 * q + (size_t)g.table_seq * half);
+                        }
+                    }
+#pragma unroll
+                    for (int q = 0; q < 2; q++) {
+                        float o[4];
+                        const float c[4] = {cs[q].x, cs[q].y, cs[q].z, cs[q].w}, sv[4] = {sn[q].x, sn[q].y, sn[q].z, sn[q].w};
+#pragma unroll
+                        for (int e = 0; e < 4; e++) {
+                            float a = as_bf(acc[i][j][4 * q + e]), b = as_bf(acc[i][j][4 * (q + 2) + e]);
+                            if (fuse == FUSE_SWIGLU) {
+                                o[e] = swiglu(a, b);
+                            } else {
+                                rotate_pair(a, b, c[e], sv[e]);
+                                acc[i][j][4 * q + e] = a;
+                                acc[i][j][4 * (q + 2) + e] = b;
+                            }
+                        }
+                        if (fuse == FUSE_SWIGLU) {
+                            const uint32_t row = (uint32_t)(m0 + wm + 32 * i + r_w);
+                            const uint32_t off = block < N ? (row * (uint32_t)half + (uint32_t)(base + 8 * q + 4 * hf)) * 2u : OUT_OF_RANGE;
+                            __builtin_amdgcn_raw_buffer_store_b64(i32x2{(int)pack_bf2(o[0], o[1]), (int)pack_bf2(o[2], o[3])}, rsM, off, 0, 0);
+                        }
+                    }
+                }
+            }
             float4 add[4];
+            i32x2 gate[4], up[4];   // beside dm
             uint32_t off_c[4];
 #pragma unroll
             for (int t = 0; t < 4; t++) {
                 const uint32_t row = (uint32_t)(m0 + wm + 32 * i + r_r + 8 * t);
                 off_c[t] = col < N ? (row * (uint32_t)ldc + (uint32_t)col) * CES : OUT_OF_RANGE;
                 add[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (KIND == GEMM_NN && fuse) {
+                    const uint32_t at = (row * (uint32_t)(2 * N) + (uint32_t)col) * 2u;
+                    gate[t] = __builtin_amdgcn_raw_buffer_load_b64(rsX, col < N ? at : OUT_OF_RANGE, 0, 0);
+                    up[t] = __builtin_amdgcn_raw_buffer_load_b64(rsX, col < N ? at + (uint32_t)N * 2u : OUT_OF_RANGE, 0, 0);
+                }
                 if (OUT_F32) {
                     if (accumulate) {
                         const i32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsC, off_c[t], 0, 0);
@@ -359,6 +434,20 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB>& g) {
                 const int rr = 8 * t + r_r;
                 float4 v = *reinterpret_cast<const float4*>(patch + rr * 128 + ((c_r ^ ((rr >> 1) & 7)) << 4));
                 v.x += add[t].x; v.y += add[t].y; v.z += add[t].z; v.w += add[t].w;
+                if (KIND == GEMM_NN && fuse) {   // v: dm
+                    const uint32_t row = (uint32_t)(m0 + wm + 32 * i + r_r + 8 * t);
+                    const uint32_t off_g = col < N ? (row * (uint32_t)(2 * N) + (uint32_t)col) * 2u : OUT_OF_RANGE;
+                    const uint32_t off_u = col < N ? off_g + (uint32_t)N * 2u : OUT_OF_RANGE;
+                    const float gt[4] = {lo_bf((uint32_t)gate[t][0]), hi_bf((uint32_t)gate[t][0]), lo_bf((uint32_t)gate[t][1]), hi_bf((uint32_t)gate[t][1])};
+                    const float uu[4] = {lo_bf((uint32_t)up[t][0]), hi_bf((uint32_t)up[t][0]), lo_bf((uint32_t)up[t][1]), hi_bf((uint32_t)up[t][1])};
+                    const float dm[4] = {v.x, v.y, v.z, v.w};
+                    float dg[4], du[4], mm[4];
+#pragma unroll
+                    for (int e = 0; e < 4; e++) swiglu_grad(gt[e], uu[e], as_bf(dm[e]), dg[e], du[e], mm[e]);
+                    __builtin_amdgcn_raw_buffer_store_b64(i32x2{(int)pack_bf2(dg[0], dg[1]), (int)pack_bf2(dg[2], dg[3])}, rsY, off_g, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b64(i32x2{(int)pack_bf2(du[0], du[1]), (int)pack_bf2(du[2], du[3])}, rsY, off_u, 0, 0);
+                    v = make_float4(mm[0], mm[1], mm[2], mm[3]);
+                }
                 if (OUT_F32) {
                     const i32x4 o = {__float_as_int(v.x), __float_as_int(v.y), __float_as_int(v.z), __float_as_int(v.w)};
                     __builtin_amdgcn_raw_buffer_store_b128(o, rsC, off_c[t], 0, 0);
@@ -368,6 +457,7 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB>& g) {
                 }
             }
         }
+    }
 }
 
 // BWD: NN and TN problems, otherwise NT
@@ -387,9 +477,11 @@ __global__ __launch_bounds__(WM * WN * 64, BM * BN / (WM * WN) > 64 * 128 ? 1 : 
 template <int MB>
 struct RingReduce {
     struct Job {
-        Ops<MB> C, R;
+        Ops<MB> C, R, X, Y;
         const float* partial;
         int ksplit, ldc, ldr, M, N, accumulate, out_f32, first, micro, blocks;   // blocks: workgroups of one micro-batch
+        int fuse, period, shift, rot, tokens, table_seq;
+        const float* table;
     } j[RING_MAX];
     int n, bm, bn;
 };
@@ -398,11 +490,13 @@ __global__ __launch_bounds__(256) void k_ring_reduce(RingReduce<MB> grp) {
     int i = 0;
     while (i + 1 < grp.n && (int)blockIdx.x >= grp.j[i + 1].first) i++;
     const typename RingReduce<MB>::Job& j = grp.j[i];
-    const int bm = grp.bm, bn = grp.bn, vpr = j.N / 4;
+    const bool pairs = j.fuse == FUSE_ROPE || j.fuse == FUSE_SWIGLU;   // 4 columns and their 4 partners, 16 further in the tiles
+    const int bm = grp.bm, bn = grp.bn, vpr = j.N / (pairs ? 8 : 4);
     const int micro = MB == 1 ? 0 : ((int)blockIdx.x - j.first) / j.blocks, micros = MB == 1 ? 1 : j.micro;
     const long idx = (long)((int)blockIdx.x - j.first - micro * j.blocks) * 256 + threadIdx.x;
     if (idx >= (long)j.M * vpr) return;
-    const int m = (int)(idx / vpr), n = (int)(idx - (long)m * vpr) * 4;
+    const int m = (int)(idx / vpr), v4 = (int)(idx - (long)m * vpr);
+    const int n = pairs ? (v4 >> 2) * 32 + (v4 & 3) * 4 : v4 * 4;
     const int tiles_n = (j.N + bn - 1) / bn;
     const int tm = m / bm, tn = n / bn;
     const float* p = j.partial + ((size_t)(tm * tiles_n + tn) * micros + micro) * j.ksplit * (bm * bn) + (m - tm * bm) * bn + (n - tn * bn);
@@ -424,8 +518,42 @@ __global__ __launch_bounds__(256) void k_ring_reduce(RingReduce<MB> grp) {
             sum = make_float4(v[0], v[1], v[2], v[3]);
         }
         *reinterpret_cast<float4*>(c) = sum;
+    } else if (pairs) {
+        const float* const p0 = p;
+        shares(v);
+        p = p0 + 16;
+        float u[4] = {0.f, 0.f, 0.f, 0.f};
+        shares(u);
+        const int half = j.period / 2, col = pair_column(n, j.period, j.shift, j.N);
+#pragma unroll
+        for (int e = 0; e < 4; e++) { v[e] = as_bf(v[e]); u[e] = as_bf(u[e]); }
+        if (j.fuse == FUSE_SWIGLU) {
+            uint2 o;
+            o.x = pack_bf2(swiglu(v[0], u[0]), swiglu(v[1], u[1]));
+            o.y = pack_bf2(swiglu(v[2], u[2]), swiglu(v[3], u[3]));
+            *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(j.X.at(micro)) + (size_t)m * half + col) = o;
+        } else if (n < j.rot) {
+            const float* cs = j.table + (size_t)(m % j.tokens) * half + (col & (j.period - 1));
+            const float* sn = cs + (size_t)j.table_seq * half;
+#pragma unroll
+            for (int e = 0; e < 4; e++) rotate_pair(v[e], u[e], cs[e], sn[e]);
+        }
+        bf16_t* const c = reinterpret_cast<bf16_t*>(j.C.at(micro)) + (size_t)m * j.ldc + col;
+        *reinterpret_cast<uint2*>(c) = make_uint2(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]));
+        *reinterpret_cast<uint2*>(c + half) = make_uint2(pack_bf2(u[0], u[1]), pack_bf2(u[2], u[3]));
     } else {
         shares(v);
+        if (j.fuse == FUSE_SWIGLU_BWD) {
+            const bf16_t* gu = (const bf16_t*)j.X.at(micro) + (size_t)m * 2 * j.N + n;
+            bf16_t* dgu = (bf16_t*)j.Y.at(micro) + (size_t)m * 2 * j.N + n;
+            const uint2 gw = *reinterpret_cast<const uint2*>(gu), uw = *reinterpret_cast<const uint2*>(gu + j.N);
+            const float gt[4] = {lo_bf(gw.x), hi_bf(gw.x), lo_bf(gw.y), hi_bf(gw.y)}, up[4] = {lo_bf(uw.x), hi_bf(uw.x), lo_bf(uw.y), hi_bf(uw.y)};
+            float dg[4], du[4];
+#pragma unroll
+            for (int e = 0; e < 4; e++) swiglu_grad(gt[e], up[e], as_bf(v[e]), dg[e], du[e], v[e]);
+            *reinterpret_cast<uint2*>(dgu) = make_uint2(pack_bf2(dg[0], dg[1]), pack_bf2(dg[2], dg[3]));
+            *reinterpret_cast<uint2*>(dgu + j.N) = make_uint2(pack_bf2(du[0], du[1]), pack_bf2(du[2], du[3]));
+        }
         const bf16_t* R = (const bf16_t*)j.R.at(micro);
         if (R) {
             const uint2 rr = *reinterpret_cast<const uint2*>(R + (size_t)m * j.ldr + n);

@@ -44,6 +44,8 @@ struct DmaTile {
     static constexpr int PITCH = ROWS * 2;               // bytes of a k row (k strided)
     // slot swizzle of k row k: four consecutive k rows must fall into four different 64-byte slots of 256 bytes
     __device__ static __forceinline__ int slot(int k) { return ROWS == 64 ? ((k >> 1) & 1) << 6 : (k & 3) << 6; }
+    // k contiguous: the tile row that this lane fetches with instruction i of wave w
+    __device__ static __forceinline__ int row(int wave, int i) { return 8 * (wave * PER_WAVE + i) + ((threadIdx.x & 63) >> 3); }
     // source byte offset of instruction i of wave w: the global address picks the logical chunk that the swizzle
     // places at the physical slot the lane writes
     __device__ static __forceinline__ uint32_t voff(int wave, int i, int row0, int ld) {

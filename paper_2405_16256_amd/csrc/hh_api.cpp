@@ -20,7 +20,6 @@ namespace hh {
 hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st);
 bool gemm_bf16_shares_launch(const GemmDesc* g, int n);
 bool gemm_bf16_defer(const GemmDesc* dw, int n_dw, const GemmDesc* const groups[3], const int n[3]);
-bool gemm_bf16_micro_bytes(const GemmDesc* g, int n, size_t* bytes);
 hipError_t gemm_f32(const GemmDesc* g, int n, hipStream_t st);
 hipError_t attn_bf16_fwd(const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, const MicroStride& micro,
                          hipStream_t st);
@@ -437,6 +436,7 @@ static GemmDesc desc(int kind, int M, int N, int K, const void* A, int lda, cons
     g.kind = kind; g.M = M; g.N = N; g.K = K; g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc;
     g.R = R; g.ldr = ldr; g.out_f32 = out_f32; g.accumulate = acc; g.ws = nullptr; g.ws_bytes = 0;
     g.B1 = g.B2 = nullptr; g.k1 = g.k2 = 0;
+    g.fuse = GemmFuse{};
     g.micro = 1; g.each = nullptr;
     return g;
 }
@@ -476,7 +476,7 @@ static hipError_t pgemm(hh_ctx* ctx, const Pass& p, int dt, GemmDesc* g, int n, 
     if (n > 8) return hipErrorInvalidValue;
     if (p.n > 1)
         for (int i = 0; i < n; i++) {
-            ops[i] = GemmMicro{p.each(g[i].A), p.each(g[i].B), p.each(g[i].C), p.each(g[i].R)};
+            ops[i] = GemmMicro{p.each(g[i].A), p.each(g[i].B), p.each(g[i].C), p.each(g[i].R), p.each(g[i].fuse.X), p.each(g[i].fuse.Y)};
             g[i].micro = p.n; g[i].each = ops + i;
         }
     return tgemm(ctx, dt, g, n, st);
@@ -487,6 +487,17 @@ static bool qkv_in_one(const Dims& d, const hh_layer_weights* w) {
     return (const char*)w->wk == (const char*)w->wq + (size_t)d.A * d.H * d.es && (const char*)w->wv == (const char*)w->wk + (size_t)d.Akv * d.H * d.es;
 }
 static bool gate_up_in_one(const Dims& d, const hh_layer_weights* w) { return (const char*)w->w_up == (const char*)w->w_gate + (size_t)d.F * d.H * d.es; }
+
+// Whether the launches of these GEMMs do what follows them on their way out: on the ring kernel's smaller tiles, and where a
+// workgroup has a CU of its own.  That saves a launch of 3 to 5 us and costs the workgroups 1 to 2 us each, one after the
+// other on a CU that has several (forward of hidden 512, 3798 tokens: 96.6 us, 98.5 with the rotation fused; backward of hidden
+// 1984, 3820 tokens, 128x256 tiles: 510 us, 521 with the SwiGLU gradient fused).  Nor on k_gemm_dma, whose 256 workgroups
+// all have their epilogues at once.
+static bool can_fuse(const hh_ctx* ctx, const Dims& d, int kind, GemmDesc* g, int n) {
+    RingUse use;
+    for (int i = 0; i < n; i++) gemm_scratch(ctx, g[i]);
+    return d.dt == DT_BF16 && gemm_bf16_on_ring(g, n, &use) && use.tile <= fuse_tile(kind) && use.workgroups <= 256;
+}
 
 // The projections of a forward pass: q|k|v (one problem or three), out, gate|up (one or two), down.
 struct FwdGemms {
@@ -527,18 +538,23 @@ static int layer_fwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_la
     ctx->gemm_ws = d.dt != DT_BF16 ? nullptr : gemm_ws ? gemm_ws : at(ws, wl.gemm_ws);
     FwdGemms f;
     fwd_gemms(d, w, x, y, saved, m.p[0], f);
+    const bool rotates = can_fuse(ctx, d, FUSE_ROPE, f.qkv, f.n_qkv), gates = f.n_gu == 1 && can_fuse(ctx, d, FUSE_SWIGLU, f.gu, 1);
+    if (rotates)
+        for (int i = 0; i < f.n_qkv; i++)   // all but v
+            f.qkv[i].fuse = GemmFuse{FUSE_ROPE, d.d, f.n_qkv == 1 ? A + Akv : i < 2 ? f.qkv[i].N : 0, d.S, ctx->rope_seq, ctx->rope_table, nullptr, nullptr};
+    if (gates) f.gu[0].fuse = GemmFuse{FUSE_SWIGLU, 2 * F, 0, 0, 0, nullptr, m.p[0], nullptr};
 
     TR(HH_TRACE_ELEMENTWISE, 2.0 * T * H * es, rmsnorm_fwd(dt, p.each(x), w->g_attn, p.each(at(saved, sl.xn)), p.each(at(saved, sl.r1)), p.n, T, H,
                                                            cfg->rms_eps, st));
     HIP_TRY(pgemm(ctx, p, dt, f.qkv, f.n_qkv, st));
-    TR(HH_TRACE_ELEMENTWISE, 2.0 * T * (A + Akv) * es, rope(dt, qkv, Q3, p.n, T, d.S, d.nh + d.nkv, d.d, ctx->rope_table, ctx->rope_seq, st));
+    if (!rotates) TR(HH_TRACE_ELEMENTWISE, 2.0 * T * (A + Akv) * es, rope(dt, qkv, Q3, p.n, T, d.S, d.nh + d.nkv, d.d, ctx->rope_table, ctx->rope_seq, st));
     TR(HH_TRACE_ATTN_FWD, attn_flop(d), attn_fwd(dt, qkv.p[0], Q3, at(saved, sl.a), (float*)at(saved, sl.lse), d.B, d.S, d.nh, d.nkv, d.d,
                                                  p.stride(), st));
     HIP_TRY(pgemm(ctx, p, dt, f.out, st));
     TR(HH_TRACE_ELEMENTWISE, 2.0 * T * H * es, rmsnorm_fwd(dt, h, w->g_mlp, p.each(at(saved, sl.hn)), p.each(at(saved, sl.r2)), p.n, T, H,
                                                            cfg->rms_eps, st));
     HIP_TRY(pgemm(ctx, p, dt, f.gu, f.n_gu, st));
-    TR(HH_TRACE_ELEMENTWISE, 3.0 * T * F * es, swiglu_fwd(dt, p.each(at(saved, sl.gu)), m, p.n, T, F, st));
+    if (!gates) TR(HH_TRACE_ELEMENTWISE, 3.0 * T * F * es, swiglu_fwd(dt, p.each(at(saved, sl.gu)), m, p.n, T, F, st));
     HIP_TRY(pgemm(ctx, p, dt, f.down, st));
     return HH_OK;
 }
@@ -670,8 +686,10 @@ static int layer_bwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_la
 
     // MLP branch: y = h + m Wd^T
     const Each m = p.each(at(ws, wl.m)), dgu = p.each(at(ws, wl.dgu)), dhn = p.each(at(ws, wl.dhn)), dh = p.each(at(ws, wl.dh));
-    HIP_TRY(pgemm(ctx, p, dt, b.dm, st));                                                           // dm (in the m buffer)
-    TR(HH_TRACE_ELEMENTWISE, 6.0 * T * F * es, swiglu_bwd(dt, m, p.each(at(saved, sl.gu)), dgu, m, p.n, T, F, st));               // dgate|dup, m
+    const bool gates = can_fuse(ctx, d, FUSE_SWIGLU_BWD, &b.dm, 1);                                                   // dgate|dup, m ...
+    if (gates) b.dm.fuse = GemmFuse{FUSE_SWIGLU_BWD, 0, 0, 0, 0, nullptr, const_cast<char*>(at(saved, sl.gu)), at(ws, wl.dgu)};
+    HIP_TRY(pgemm(ctx, p, dt, b.dm, st));                                                           // ... or dm (in the m buffer)
+    if (!gates) TR(HH_TRACE_ELEMENTWISE, 6.0 * T * F * es, swiglu_bwd(dt, m, p.each(at(saved, sl.gu)), dgu, m, p.n, T, F, st));   // dgate|dup, m
     HIP_TRY(run_group(0));
     TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dhn, p.each(at(saved, sl.h)), p.each(at(saved, sl.r2)), w->g_mlp, p.each(dy), dh,
                                                            part2, part2_b, p.n, T, H, st));         // dh = dy + norm-bwd
@@ -781,10 +799,10 @@ static int side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weight
         plan_deferral(ctx, d, b);
         if (b.defer) return 1;
         auto take = [&](GemmDesc* q, int m) {
-            size_t bytes = 0;
+            RingUse use;
             for (int i = 0; i < m; i++) gemm_scratch(ctx, q[i]);
-            if (!gemm_bf16_micro_bytes(q, m, &bytes)) return false;
-            partial = std::max(partial, bytes);
+            if (!gemm_bf16_on_ring(q, m, &use)) return false;
+            partial = std::max(partial, use.partial);
             return true;
         };
         if (!take(f.qkv, f.n_qkv) || !take(&f.out, 1) || !take(f.gu, f.n_gu) || !take(&f.down, 1) || !take(&b.dm, 1)) return 1;

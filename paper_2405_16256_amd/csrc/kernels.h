@@ -21,7 +21,21 @@ struct Each { void* p[MICRO_MAX]; };
 enum { GEMM_NT = 0, GEMM_NN = 1, GEMM_TN = 2 };
 // The operands of a problem that the launch repeats for several micro-batches (weight gradients: C is the same in all of
 // them and their products are added in the order of the micro-batches, each as a launch of its own would add it).
-struct GemmMicro { Each A, B, C, R; };
+struct GemmMicro { Each A, B, C, R, X, Y; };
+// What the ring kernel (bf16) can do with a product before it is written, in place of a launch of its own:
+//   FUSE_ROPE       NT, C = q|k|v rows or a part of them: the rotary embedding of the first `rot` columns, heads of `period`
+//   FUSE_SWIGLU     NT, C = gate|up rows [M, period]: X [M, period/2] = silu(gate) * up
+//   FUSE_SWIGLU_BWD NN, the product is dm [M, N]: with X = gate|up, C = m and Y = dgate|dup
+// Each on the product rounded to bf16, as the launch would read it.
+enum { FUSE_NONE = 0, FUSE_ROPE, FUSE_SWIGLU, FUSE_SWIGLU_BWD };
+// The largest tile (rows x columns) on which the kernel does it.
+constexpr int fuse_tile(int kind) { return kind == FUSE_SWIGLU ? 128 * 128 : 64 * 128; }
+struct GemmFuse {
+    int kind;
+    int period, rot;
+    int seq, table_seq; const float* table;   // FUSE_ROPE: as for rope()
+    void* X; void* Y;
+};
 struct GemmDesc {
     int kind;
     int M, N, K;
@@ -36,7 +50,8 @@ struct GemmDesc {
     const void* B2; int k2;
     void* ws;                // optional scratch for k-split partial sums (bf16 path), may be NULL
     size_t ws_bytes;         // of one micro-batch: what a plan may use
-    int micro;               // micro-batches; above 1 (bf16, gemm_bf16_micro_bytes) their operands are in `each`
+    GemmFuse fuse;
+    int micro;               // micro-batches; above 1 (bf16, gemm_bf16_on_ring) their operands are in `each`
     const GemmMicro* each;
 };
 constexpr size_t GEMM_WS_BYTES = (size_t)64 << 20;   // enough for 256 partial tiles of 256x256 fp32
@@ -48,6 +63,10 @@ void* static_scratch(int device);             // that address (null before a suc
 // Up to 4 problems (8 weight gradients in bf16) of which none reads what another writes, either all NT or none; they share launches where that is
 // predicted to be faster.
 hipError_t gemm(int dtype, const GemmDesc* g, int n, hipStream_t st);
+// Whether all launches of these problems (bf16) are the ring kernel's, and if so: the bytes of partial sums that the largest of
+// those launches keeps, its workgroups, and the largest tile.
+struct RingUse { size_t partial; long workgroups; int tile; };
+bool gemm_bf16_on_ring(const GemmDesc* g, int n, RingUse* use);
 // Whether they do; if not, gemm() on each of them alone launches the same.
 bool gemm_shares_launch(int dtype, const GemmDesc* g, int n);
 
