@@ -270,6 +270,25 @@ static WorkLayout work_layout(const Dims& d) {
     return w;
 }
 
+// The same for one of several micro-batches that go side by side, packed closer: what the attention branch's backward needs
+// takes the place of m and dgate|dup, which nobody reads any more by then; both sets of gain-gradient partials have a place of
+// their own (`partial`, two times gain_bytes).  The GEMMs' scratch is not part of it.
+static size_t gain_bytes(const Dims& d) { return (size_t)std::min(d.T, 256) * d.H * 4; }
+static WorkLayout side_layout(const Dims& d) {
+    const WorkLayout one = work_layout(d);
+    WorkLayout w;
+    w.m = one.m; w.dgu = one.dgu;
+    w.da = w.m;
+    w.dqkv = w.da + (one.dqkv - one.da);
+    w.dvec = w.dqkv + (one.dvec - one.dqkv);
+    w.dkv_part = w.dvec + (one.dkv_part - one.dvec);
+    w.dhn = std::max(one.dhn, w.dkv_part + (one.partial - one.dkv_part));
+    w.dh = w.dhn + (one.dh - one.dhn);
+    w.partial = w.dh + (one.da - one.dh);
+    w.gemm_ws = w.total = w.partial + 2 * up256(gain_bytes(d));
+    return w;
+}
+
 extern "C" int hh_layer_sizes(const hh_layer_cfg* cfg, size_t* saved_bytes, size_t* workspace_bytes) {
     TRY(check_cfg(cfg));
     const Dims d = dims_of(cfg);
@@ -446,6 +465,7 @@ static GemmDesc desc(int kind, int M, int N, int K, const void* A, int lda, cons
 // the first micro-batch; at() gives those of the others.
 struct Pass {
     int n;
+    bool side;   // workspaces laid out by side_layout
     const char* pool; size_t pool_stride;
     const char* ws; size_t ws_stride;
     const void* const* x; void* const* y;
@@ -468,7 +488,7 @@ struct Pass {
     }
     MicroStride stride() const { return MicroStride{n, pool_stride, ws_stride}; }
 };
-static const Pass ONE{1, nullptr, 0, nullptr, 0, nullptr, nullptr, nullptr, nullptr};
+static const Pass ONE{1, false, nullptr, 0, nullptr, 0, nullptr, nullptr, nullptr, nullptr};
 
 // GEMMs of a pass: in every micro-batch of it.
 static hipError_t pgemm(hh_ctx* ctx, const Pass& p, int dt, GemmDesc* g, int n, hipStream_t st) {
@@ -531,7 +551,7 @@ static void fwd_gemms(const Dims& d, const hh_layer_weights* w, const void* x, v
 static int layer_fwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_layer_cfg* cfg, const hh_layer_weights* w, const void* x,
                           void* y, void* saved, void* ws, void* gemm_ws, hipStream_t st) {
     const SavedLayout sl = saved_layout(d);
-    const WorkLayout wl = work_layout(d);
+    const WorkLayout wl = p.side ? side_layout(d) : work_layout(d);
     const int T = d.T, H = d.H, A = d.A, F = d.F, dt = d.dt, Akv = d.Akv, Q3 = d.Q3;
     const size_t es = d.es;
     const Each qkv = p.each(at(saved, sl.qkv)), h = p.each(at(saved, sl.h)), m = p.each(at(ws, wl.m));
@@ -607,10 +627,9 @@ struct BwdGemms {
     int n[3], n_dw;
     bool defer;   // all the weight gradients (dw) in one launch after the last input gradient: predicted to be faster
 };
-static void bwd_gemms(const Dims& d, const hh_layer_weights* w, const hh_layer_grads* g, const void* saved, const void* dy, void* ws, int acc,
-                      BwdGemms& b) {
+static void bwd_gemms(const Dims& d, const WorkLayout& wl, const hh_layer_weights* w, const hh_layer_grads* g, const void* saved, const void* dy,
+                      void* ws, int acc, BwdGemms& b) {
     const SavedLayout sl = saved_layout(d);
-    const WorkLayout wl = work_layout(d);
     const int T = d.T, H = d.H, A = d.A, F = d.F, Akv = d.Akv, Q3 = d.Q3;
     const size_t es = d.es;
     const void* xn = at(saved, sl.xn); const void* a = at(saved, sl.a); const void* hn = at(saved, sl.hn);
@@ -660,13 +679,13 @@ static void plan_deferral(const hh_ctx* ctx, const Dims& d, BwdGemms& b) {
 static int layer_bwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_layer_weights* w, const void* x, const void* saved,
                           const void* dy, void* dx, const hh_layer_grads* g, int acc, void* ws, void* gemm_ws, hipStream_t st) {
     const SavedLayout sl = saved_layout(d);
-    const WorkLayout wl = work_layout(d);
+    const WorkLayout one = work_layout(d), wl = p.side ? side_layout(d) : one;
     const int T = d.T, H = d.H, F = d.F, dt = d.dt;
     const size_t es = d.es;
     acc = acc ? 1 : 0;
     ctx->gemm_ws = d.dt != DT_BF16 ? nullptr : gemm_ws ? gemm_ws : at(ws, wl.gemm_ws);
     BwdGemms b;
-    bwd_gemms(d, w, g, saved, dy, ws, acc, b);
+    bwd_gemms(d, wl, w, g, saved, dy, ws, acc, b);
     plan_deferral(ctx, d, b);
     const bool defer = b.defer;
     auto run_group = [&](int i) { return defer ? pgemm(ctx, p, dt, &b.group[i][b.n[i] - 1], 1, st) : pgemm(ctx, p, dt, b.group[i], b.n[i], st); };
@@ -674,12 +693,13 @@ static int layer_bwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_la
     // Partial column sums of the two gain gradients.  Those of the MLP norm go to the front of the m | dgate|dup stretch
     // if nobody needs that any more by then and it holds a row per workgroup, otherwise to `partial`; those of the
     // attention norm to the stretch (behind the others) or to `partial` likewise.  Unless both have to take `partial`,
-    // one launch at the end reduces both.
-    const size_t want = (size_t)std::min(T, 256) * H * 4, stretch = wl.dhn - wl.m, partial_b = wl.gemm_ws - wl.partial;
+    // one launch at the end reduces both.  (Side by side both have a place of their own, of as many rows.)
+    const size_t want = gain_bytes(d), stretch = one.dhn - one.m, partial_b = one.gemm_ws - one.partial;
     const bool mlp_in = !defer && stretch >= want;
     const size_t taken = mlp_in ? up256(want) : 0;
     const bool attn_in = stretch - taken >= want;
-    const Each part2 = p.each(at(ws, mlp_in ? wl.m : wl.partial)), part1 = p.each(at(ws, attn_in ? wl.m + taken : wl.partial));
+    const Each part2 = p.each(at(ws, p.side || !mlp_in ? wl.partial : wl.m));
+    const Each part1 = p.each(at(ws, p.side ? wl.partial + up256(want) : attn_in ? wl.m + taken : wl.partial));
     const size_t part2_b = mlp_in ? want : partial_b, part1_b = attn_in ? want : partial_b;
     const ColSum sums[2] = {{part2, rmsnorm_bwd_blocks(T, H, part2_b), g->g_mlp}, {part1, rmsnorm_bwd_blocks(T, H, part1_b), g->g_attn}};
     const bool sum_both = part1.p[0] != part2.p[0];
@@ -780,11 +800,11 @@ static int stage_bwd(hh_ctx* ctx, const Pass& ps, const Dims& d, int k, const hh
 }
 
 // How many micro-batches (of at most n_live) go through the launches side by side: as many as the workspace holds, whose
-// size is that of one.  Side by side each has its own tensors (`unit` bytes, the gradient between layers behind them) where
+// size is that of one.  Side by side each has its own tensors (side_layout and the gradient between layers behind them) where
 // one alone leaves room for the GEMMs' partial sums, and those partial sums behind the last one's.  Only small micro-batches fit, which
 // are also the ones whose launches leave most of the chip idle; and only where every GEMM goes to the ring kernel (bf16),
 // with the tile and split of a micro-batch by itself.
-static size_t side_unit(const Dims& d) { return work_layout(d).gemm_ws + act_bytes(d); }
+static size_t side_unit(const Dims& d) { return side_layout(d).total + act_bytes(d); }
 static int side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weights* w, const hh_layer_grads* g, int n_live, void* workspace) {
     const size_t unit = side_unit(d), total = work_layout(d).total + act_bytes(d);
     int n = std::min(n_live, MICRO_MAX);
@@ -795,7 +815,7 @@ static int side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weight
         FwdGemms f;
         fwd_gemms(d, &w[l], workspace, workspace, workspace, workspace, f);
         BwdGemms b;
-        bwd_gemms(d, &w[l], &g[l], workspace, workspace, workspace, 1, b);
+        bwd_gemms(d, side_layout(d), &w[l], &g[l], workspace, workspace, workspace, 1, b);
         plan_deferral(ctx, d, b);
         if (b.defer) return 1;
         auto take = [&](GemmDesc* q, int m) {
@@ -863,12 +883,15 @@ static int stage_run(hh_ctx* ctx, const hh_layer_cfg* cfg, int n_layers, const h
     const size_t unit = side_unit(d);
     const int side = n_live > 1 && separate_buffers(d, n_micro, x, y, dy, dx) ? side_by_side(ctx, d, n_layers, w, g, n_live, workspace) : 1;
     if (side > 1) {
-        for (int m = 0; m < n_micro; m += side) {
-            const Pass ps{std::min(side, n_micro - m), p.base, p.per_micro, (const char*)workspace, unit, x + m, y + m, dy + m, dx + m};
+        const int passes = (n_micro + side - 1) / side;
+        for (int i = 0, m = 0; i < passes; i++) {   // as alike as they can be
+            const int n = (n_micro - m + passes - i - 1) / (passes - i);
+            const Pass ps{n, true, p.base, p.per_micro, (const char*)workspace, unit, x + m, y + m, dy + m, dx + m};
             void* gemm_ws = at(workspace, (size_t)side * unit);
             TRY(stage_fwd(ctx, ps, d, cfg, n_layers, w, p, 0, x[m], y[m], workspace, gemm_ws, st));
-            TRY(stage_bwd(ctx, ps, d, n_layers, w, g, p, 0, x[m], dy[m], dx[m], m > 0 || !zero_grads_first, workspace, at(workspace, wl.gemm_ws),
+            TRY(stage_bwd(ctx, ps, d, n_layers, w, g, p, 0, x[m], dy[m], dx[m], m > 0 || !zero_grads_first, workspace, at(workspace, unit - act_bytes(d)),
                           gemm_ws, st));
+            m += n;
         }
         return HH_OK;
     }

@@ -14,9 +14,9 @@ CASES = [
     (TINY, True, 1, 9, 9, True, True, 8),                                               # more than one launch takes
     (I.LayerShape(128, 2, 64, 128, 1, 1), True, 1, 3, 3, False, False, 3),              # one token
     (I.LayerShape(128, 1, 128, 192, 37, 3, n_kv_heads=1), False, 2, 4, 3, True, False, 3),
-    (I.LayerShape(512, 8, 64, 768, 1100, 2, n_kv_heads=2), False, 2, 3, 3, False, False, 2),   # split weight gradients
+    (I.LayerShape(512, 8, 64, 768, 1100, 2, n_kv_heads=2), False, 2, 3, 3, False, False, 3),   # split weight gradients
     (I.LayerShape(512, 4, 128, 64, 2049, 1, n_kv_heads=1), True, 1, 2, 2, True, True, 2),      # split ones, partial dK and dV
-    (I.LayerShape(1024, 8, 128, 2048, 700, 1, n_kv_heads=2), True, 1, 4, 4, True, False, 2),   # larger tiles
+    (I.LayerShape(1024, 8, 128, 2048, 700, 1, n_kv_heads=2), True, 1, 4, 4, True, False, 3),   # larger tiles, passes of two
     (I.LayerShape(192, 3, 64, 64, 65, 40), True, 1, 2, 2, False, False, 2),                     # rows past a tile, many samples
 ]
 IDS = ["%dx%d T%d" % (c[0].hidden, c[0].ffn, c[0].seq * c[0].micro_batch) for c in CASES]
