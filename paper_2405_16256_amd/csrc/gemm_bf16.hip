@@ -417,15 +417,15 @@ static hipError_t launch_dma(const GemmDesc* g, int n, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <bool BWD, int MB, int BM, int BN, int WM, int WN, int NS>
+template <bool BWD, int MB, bool F, int BM, int BN, int WM, int WN, int NS>
 static hipError_t launch_ring_n(const GemmDesc* g, const int* order, const int* ksplit, int n, hipStream_t st) {
     constexpr int LDS = NS * (BM + BN) * DK * 2;
     static std::atomic<uint64_t> lds_ok{0};
-    auto kern = k_gemm_ring<BWD, MB, BM, BN, WM, WN, NS>;
+    auto kern = k_gemm_ring<BWD, MB, F, BM, BN, WM, WN, NS>;
     const hipError_t e = allow_lds((const void*)kern, LDS, lds_ok);
     if (e != hipSuccess) return e;
-    RingGroup<MB> grp{};
-    RingReduce<MB> red{};
+    RingGroup<MB, F> grp{};
+    RingReduce<MB, F> red{};
     grp.n = n;
     red.bm = BM; red.bn = BN;
     int first = 0, red_first = 0;
@@ -433,15 +433,13 @@ static hipError_t launch_ring_n(const GemmDesc* g, const int* order, const int* 
     for (int i = 0; i < n; i++) {
         const GemmDesc& q = g[order[i]];
         const int s = ksplit[order[i]];
-        RingProblem<MB>& p = grp.p[i];
+        RingProblem<MB, F>& p = grp.p[i];
         const int nk = (q.K + DK - 1) / DK;
         if constexpr (MB == 1) {
             p.A.p[0] = const_cast<void*>(q.A); p.B.p[0] = const_cast<void*>(q.B); p.C.p[0] = q.C; p.R.p[0] = const_cast<void*>(q.R);
-            p.X.p[0] = q.fuse.X; p.Y.p[0] = q.fuse.Y;
         } else {
             for (int m = 0; m < MB; m++) {
                 p.A.p[m] = q.each->A.p[m]; p.B.p[m] = q.each->B.p[m]; p.C.p[m] = q.each->C.p[m]; p.R.p[m] = q.each->R.p[m];
-                p.X.p[m] = q.each->X.p[m]; p.Y.p[m] = q.each->Y.p[m];
             }
         }
         p.kseg[0] = q.k1 ? q.k1 / DK : INT_MAX; p.kseg[1] = q.k2 ? q.k2 / DK : INT_MAX;
@@ -451,8 +449,15 @@ static hipError_t launch_ring_n(const GemmDesc* g, const int* order, const int* 
         p.accumulate = q.accumulate;
         p.tiles = ((q.M + BM - 1) / BM) * ((q.N + BN - 1) / BN);
         p.ksplit = s;
-        p.fuse = q.fuse.kind; p.period = q.fuse.period; p.rot = q.fuse.rot; p.tokens = q.fuse.seq; p.table_seq = q.fuse.table_seq; p.table = q.fuse.table;
-        p.shift = q.fuse.kind == FUSE_ROPE ? (q.fuse.period == 128 ? 7 : 6) : 31;
+        if constexpr (F) {
+            const GemmFuse& f = q.fuse;
+            for (int m = 0; m < MB; m++) {
+                p.X.p[m] = MB == 1 ? f.X : q.each->X.p[m];
+                p.Y.p[m] = MB == 1 ? f.Y : q.each->Y.p[m];
+            }
+            p.fuse = f.kind; p.period = f.period; p.rot = f.rot; p.tokens = f.seq; p.table_seq = f.table_seq; p.table = f.table;
+            p.shift = f.kind == FUSE_ROPE ? (f.period == 128 ? 7 : 6) : 31;
+        }
         p.first = first;
         p.micro = q.micro;
         p.seq = q.kind == GEMM_TN && s == 1 ? q.micro : 1;
@@ -461,21 +466,29 @@ static hipError_t launch_ring_n(const GemmDesc* g, const int* order, const int* 
             if (nk < s) return hipErrorInvalidValue;
             p.partial = partial;
             partial += (size_t)p.tiles * s * q.micro * BM * BN;
-            const int blocks = (int)(((long)q.M * (q.N / (p.fuse == FUSE_ROPE || p.fuse == FUSE_SWIGLU ? 8 : 4)) + 255) / 256);
-            red.j[red.n++] = typename RingReduce<MB>::Job{p.C, p.R, p.X, p.Y, p.partial, s, q.ldc, q.ldr, q.M, q.N, q.accumulate, q.out_f32, red_first,
-                                                               q.micro, blocks, p.fuse, p.period, p.shift, p.rot, p.tokens, p.table_seq, p.table};
+            const int blocks = (int)(((long)q.M * (q.N / (q.fuse.kind == FUSE_ROPE || q.fuse.kind == FUSE_SWIGLU ? 8 : 4)) + 255) / 256);
+            auto& j = red.j[red.n++];
+            static_cast<RingFuse<MB, F>&>(j) = p;
+            j.C = p.C; j.R = p.R; j.partial = p.partial;
+            j.ksplit = s; j.ldc = q.ldc; j.ldr = q.ldr; j.M = q.M; j.N = q.N; j.accumulate = q.accumulate; j.out_f32 = q.out_f32;
+            j.first = red_first; j.micro = q.micro; j.blocks = blocks;
             red_first += blocks * (q.out_f32 ? 1 : q.micro);
         }
     }
     kern<<<first, WM * WN * 64, LDS, st>>>(grp);
-    if (red.n) k_ring_reduce<MB><<<red_first, 256, 0, st>>>(red);
+    if (red.n) k_ring_reduce<MB, F><<<red_first, 256, 0, st>>>(red);
     return hipGetLastError();
 }
 
 template <bool BWD, int BM, int BN, int WM, int WN, int NS>
 static hipError_t launch_ring(const GemmDesc* g, const int* order, const int* ksplit, int n, hipStream_t st) {
-    return g[0].micro == 1 ? launch_ring_n<BWD, 1, BM, BN, WM, WN, NS>(g, order, ksplit, n, st)
-                           : launch_ring_n<BWD, MICRO_MAX, BM, BN, WM, WN, NS>(g, order, ksplit, n, st);
+    constexpr bool CAN = BM * BN <= (BWD ? fuse_tile(FUSE_SWIGLU_BWD) : fuse_tile(FUSE_ROPE));
+    if constexpr (CAN)
+        if (g[0].fuse.kind)
+            return g[0].micro == 1 ? launch_ring_n<BWD, 1, true, BM, BN, WM, WN, NS>(g, order, ksplit, n, st)
+                                   : launch_ring_n<BWD, MICRO_MAX, true, BM, BN, WM, WN, NS>(g, order, ksplit, n, st);
+    return g[0].micro == 1 ? launch_ring_n<BWD, 1, false, BM, BN, WM, WN, NS>(g, order, ksplit, n, st)
+                           : launch_ring_n<BWD, MICRO_MAX, false, BM, BN, WM, WN, NS>(g, order, ksplit, n, st);
 }
 
 // Which kernel, tile and k split: the smallest predicted time over the variants below.  A launch of W workgroups runs
@@ -812,6 +825,7 @@ hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st) {
     for (int i = 0; i < n; i++)   // several micro-batches, fusions: where gemm_bf16_on_ring says so
         if (g[i].micro < 1 || g[i].micro > MICRO_MAX || g[i].micro != g[0].micro || (g[i].micro > 1 && !g[i].each) ||
             ((g[i].micro > 1 || g[i].fuse.kind) && (r.how == Route::TILES256 || (r.how == Route::RING ? r.group.v : r.each[i].v) >= V_DMA)) ||
+            (g[i].fuse.kind == FUSE_SWIGLU_BWD && n > 1) || (g[i].fuse.kind != g[0].fuse.kind) ||
             (g[i].fuse.kind && tile_size(r.how == Route::RING ? r.group.v : r.each[i].v) > fuse_tile(g[i].fuse.kind)))
             return hipErrorInvalidValue;
     if (r.how == Route::RING) return launch_planned(g, n, r.group, st);

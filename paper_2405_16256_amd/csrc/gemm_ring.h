@@ -26,14 +26,14 @@ namespace hh {
 // sum of those before it (`seq` of them), so that the gradient is read and written once.  Tile and split are those of a
 // micro-batch by itself, so every result is what a launch per micro-batch gives, bit for bit.  Bound as before by one
 // workgroup's chain and by launch latency, of which there are fewer: a 4-layer stage of hidden 256, 128 tokens and 8
-// micro-batches, two at a time, 2671 -> 1485 us; 2 layers of hidden 512, 2200 tokens, 3 micro-batches, two and one, 1092 -> 899 us.
+// micro-batches, two at a time, 2671 -> 1485 us; 2 layers of hidden 512, 2200 tokens, 3 micro-batches, 1092 -> 744 us.
 //
 // Fused problems (GemmFuse).  The rotary embedding and SwiGLU combine columns far apart: (c, c + period/2) of a head or of a
 // gate|up row.  The workgroup's columns are therefore taken from B's rows in another order (any order is free: each lane
 // asks for its own row): a 32-column block holds 16 columns of the first half and their 16 partners, which an accumulator
 // lane then both owns, 4q + e and 4(q + 2) + e.  C is written back in its own order, in runs of 16 columns.  Bound by launch
 // latency, of which two launches of nine forward and one of ten backward go: forward of hidden 1024, 700 tokens 67.6 -> 65.9 us,
-// of hidden 192, 22 tokens 35.6 -> 34.1.  (Cosines asked for before the k loop, so that they need not be waited for behind it,
+// of hidden 512, 48 tokens 35.6 -> 34.1.  (Cosines asked for before the k loop, so that they need not be waited for behind it,
 // hold up the first tiles: 67.0.)
 constexpr int RING_MAX = 4;
 // the column of C that column c (of N) of the workgroups' order stands for; period 2^shift, or N (shift 31)
@@ -43,31 +43,38 @@ __device__ __forceinline__ int pair_column(int c, int period, int shift, int N) 
     return first + (r >> 5) * 16 + (r & 15) + ((r & 16) ? period / 2 : 0);
 }
 __device__ __forceinline__ float as_bf(float v) { return lo_bf(pack_bf2(v, 0.f)); }
-template <int MB>             // how many micro-batches a launch may stand for: 1 or MICRO_MAX
-struct RingProblem {
-    Ops<MB> A, B, C, R, X, Y;
+// A launch that fuses is an instantiation of its own (F): its arguments and code in the others cost each of them 0.5 us.
+template <int MB, bool F>
+struct RingFuse {};
+template <int MB>
+struct RingFuse<MB, true> {
+    Ops<MB> X, Y;
+    int fuse, period, shift, rot, tokens, table_seq;   // tokens of a sample
+    const float* table;
+};
+template <int MB, bool F>     // MB: how many micro-batches a launch may stand for, 1 or MICRO_MAX
+struct RingProblem : RingFuse<MB, F> {
+    Ops<MB> A, B, C, R;
     const bf16_t* Bseg[2];     // NN: where the rows of B from k tile kseg[0] (kseg[1]) on are; INT_MAX: no such segment
     float* partial;            // k shares: [tile][micro-batch][share][BM*BN] fp32 sums
     uint32_t a_bytes, b_bytes; // extent of A, and of B up to the first segment's end
     int kseg[2];
     int kind, lda, ldb, ldc, ldr, M, N, K, accumulate, tiles, ksplit, first, micro, seq;
-    int fuse, period, shift, rot, tokens, table_seq;   // tokens of a sample
-    const float* table;
 };
-template <int MB>
+template <int MB, bool F>
 struct RingGroup {
     int n;
-    RingProblem<MB> p[RING_MAX];
+    RingProblem<MB, F> p[RING_MAX];
 };
 
-template <int KIND, int MB, int BM, int BN, int WM, int WN, int NS>
-__device__ __forceinline__ void ring_body(const RingProblem<MB>& g) {
+template <int KIND, int MB, bool F, int BM, int BN, int WM, int WN, int NS>
+__device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
     constexpr bool OUT_F32 = KIND == GEMM_TN;
     constexpr int NW = WM * WN;
     using DA = DmaTile<(KIND != GEMM_TN), BM, NW>;
     using DB = DmaTile<(KIND == GEMM_NT), BN, NW>;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
-    constexpr bool FUSES = KIND != GEMM_TN && BM * BN <= fuse_tile(KIND == GEMM_NT ? FUSE_SWIGLU : FUSE_SWIGLU_BWD);
+    constexpr bool FUSES = F && KIND != GEMM_TN;
     constexpr int STAGE = DA::BYTES + DB::BYTES;
     constexpr int PW = DA::PER_WAVE + DB::PER_WAVE;       // DMA instructions per wave and stage
     static_assert(NS * STAGE >= NW * 4096, "the epilogue patches reuse the ring");
@@ -118,7 +125,7 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB>& g) {
 #pragma unroll
     for (int i = 0; i < DB::PER_WAVE; i++) {
         int row0 = n0;
-        if (KIND == GEMM_NT && FUSES && g.fuse) {   // voff adds the lane's row of the tile
+        if constexpr (KIND == GEMM_NT && FUSES) {   // voff adds the lane's row of the tile
             const int r = DB::row(wave, i);
             row0 = pair_column(n0 + r, g.period, g.shift, N) - r;
         }
@@ -352,20 +359,25 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB>& g) {
     char* const patch = smem + wave * 4096;
     const int r_w = lane & 31;                       // row written, chunks 2g + hf
     const int r_r = lane >> 3, c_r = lane & 7;       // row (+ 8t) and chunk read back
-    const int fuse = FUSES ? g.fuse : FUSE_NONE;
+    const int fuse = [&] { if constexpr (FUSES) return g.fuse; else return (int)FUSE_NONE; }();
+    // NN: gate|up beside dm and dgate|dup; NT: silu(gate) * up
     const bool gates = FUSES && fuse > FUSE_ROPE;
-    const __amdgpu_buffer_rsrc_t rsX = make_rsrc(KIND == GEMM_NN && gates ? g.X.at(micro) : Cv, KIND == GEMM_NN && gates ? (uint32_t)((size_t)M * 2 * N * 2u) : 0u);
-    const __amdgpu_buffer_rsrc_t rsM = make_rsrc(KIND == GEMM_NT && gates ? g.X.at(micro) : Cv, KIND == GEMM_NT && gates ? (uint32_t)((size_t)M * N) : 0u);
-    const __amdgpu_buffer_rsrc_t rsY = make_rsrc(KIND == GEMM_NN && gates ? g.Y.at(micro) : Cv, KIND == GEMM_NN && gates ? (uint32_t)((size_t)M * 2 * N * 2u) : 0u);
+    __amdgpu_buffer_rsrc_t rsX = rsC, rsY = rsC;
+    if constexpr (FUSES) {
+        const uint32_t row = (KIND == GEMM_NN ? 4u : 1u) * (uint32_t)N;   // bytes
+        if (gates) rsX = make_rsrc(g.X.at(micro), (uint32_t)M * row);
+        if (KIND == GEMM_NN) rsY = make_rsrc(g.Y.at(micro), (uint32_t)M * row);
+    }
 #pragma unroll
     for (int i = 0; i < TM; i++) {
         int pos = 0;
-        if (KIND == GEMM_NT && fuse == FUSE_ROPE) pos = (m0 + wm + 32 * i + r_w) % g.tokens;
+        if constexpr (KIND == GEMM_NT && FUSES)
+            if (fuse == FUSE_ROPE) pos = (m0 + wm + 32 * i + r_w) % g.tokens;
 #pragma unroll
         for (int j = 0; j < TN; j++) {
             const int block = n0 + wn + 32 * j;
             int col = block + 4 * c_r;
-            if (KIND == GEMM_NT && fuse) {
+            if constexpr (KIND == GEMM_NT && FUSES) {
                 const int half = g.period / 2, base = pair_column(block, g.period, g.shift, N);
                 col = block >= N ? block : base + (c_r < 4 ? 4 * c_r : half + 4 * (c_r - 4));
                 if (fuse == FUSE_SWIGLU || block < g.rot) {
@@ -396,7 +408,7 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB>& g) {
                         if (fuse == FUSE_SWIGLU) {
                             const uint32_t row = (uint32_t)(m0 + wm + 32 * i + r_w);
                             const uint32_t off = block < N ? (row * (uint32_t)half + (uint32_t)(base + 8 * q + 4 * hf)) * 2u : OUT_OF_RANGE;
-                            __builtin_amdgcn_raw_buffer_store_b64(i32x2{(int)pack_bf2(o[0], o[1]), (int)pack_bf2(o[2], o[3])}, rsM, off, 0, 0);
+                            __builtin_amdgcn_raw_buffer_store_b64(i32x2{(int)pack_bf2(o[0], o[1]), (int)pack_bf2(o[2], o[3])}, rsX, off, 0, 0);
                         }
                     }
                 }
@@ -409,7 +421,7 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB>& g) {
                 const uint32_t row = (uint32_t)(m0 + wm + 32 * i + r_r + 8 * t);
                 off_c[t] = col < N ? (row * (uint32_t)ldc + (uint32_t)col) * CES : OUT_OF_RANGE;
                 add[t] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (KIND == GEMM_NN && fuse) {
+                if constexpr (KIND == GEMM_NN && FUSES) {
                     const uint32_t at = (row * (uint32_t)(2 * N) + (uint32_t)col) * 2u;
                     gate[t] = __builtin_amdgcn_raw_buffer_load_b64(rsX, col < N ? at : OUT_OF_RANGE, 0, 0);
                     up[t] = __builtin_amdgcn_raw_buffer_load_b64(rsX, col < N ? at + (uint32_t)N * 2u : OUT_OF_RANGE, 0, 0);
@@ -434,7 +446,7 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB>& g) {
                 const int rr = 8 * t + r_r;
                 float4 v = *reinterpret_cast<const float4*>(patch + rr * 128 + ((c_r ^ ((rr >> 1) & 7)) << 4));
                 v.x += add[t].x; v.y += add[t].y; v.z += add[t].z; v.w += add[t].w;
-                if (KIND == GEMM_NN && fuse) {   // v: dm
+                if constexpr (KIND == GEMM_NN && FUSES) {   // v: dm
                     const uint32_t row = (uint32_t)(m0 + wm + 32 * i + r_r + 8 * t);
                     const uint32_t off_g = col < N ? (row * (uint32_t)(2 * N) + (uint32_t)col) * 2u : OUT_OF_RANGE;
                     const uint32_t off_u = col < N ? off_g + (uint32_t)N * 2u : OUT_OF_RANGE;
@@ -461,36 +473,35 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB>& g) {
 }
 
 // BWD: NN and TN problems, otherwise NT
-template <bool BWD, int MB, int BM, int BN, int WM, int WN, int NS>
-__global__ __launch_bounds__(WM * WN * 64, BM * BN / (WM * WN) > 64 * 128 ? 1 : 2) void k_gemm_ring(RingGroup<MB> grp) {
+template <bool BWD, int MB, bool F, int BM, int BN, int WM, int WN, int NS>
+__global__ __launch_bounds__(WM * WN * 64, BM * BN / (WM * WN) > 64 * 128 ? 1 : 2) void k_gemm_ring(RingGroup<MB, F> grp) {
     int i = 0;
     while (i + 1 < grp.n && (int)blockIdx.x >= grp.p[i + 1].first) i++;
-    const RingProblem<MB>& g = grp.p[i];
-    if (!BWD) ring_body<GEMM_NT, MB, BM, BN, WM, WN, NS>(g);
-    else if (g.kind == GEMM_NN) ring_body<GEMM_NN, MB, BM, BN, WM, WN, NS>(g);
-    else ring_body<GEMM_TN, MB, BM, BN, WM, WN, NS>(g);
+    const RingProblem<MB, F>& g = grp.p[i];
+    if (!BWD) ring_body<GEMM_NT, MB, F, BM, BN, WM, WN, NS>(g);
+    else if (F || g.kind == GEMM_NN) ring_body<GEMM_NN, MB, F, BM, BN, WM, WN, NS>(g);
+    else ring_body<GEMM_TN, MB, F, BM, BN, WM, WN, NS>(g);
 }
 
 // Sums the ksplit fp32 shares of every BM x BN tile of the group's split problems in a fixed order and applies the
 // epilogue.  A thread owns 4 consecutive columns of one row of C: of one micro-batch's (NT, NN), or of the gradient, to
 // which it adds the micro-batches' products one after the other.
-template <int MB>
+template <int MB, bool F>
 struct RingReduce {
-    struct Job {
-        Ops<MB> C, R, X, Y;
+    struct Job : RingFuse<MB, F> {
+        Ops<MB> C, R;
         const float* partial;
         int ksplit, ldc, ldr, M, N, accumulate, out_f32, first, micro, blocks;   // blocks: workgroups of one micro-batch
-        int fuse, period, shift, rot, tokens, table_seq;
-        const float* table;
     } j[RING_MAX];
     int n, bm, bn;
 };
-template <int MB>
-__global__ __launch_bounds__(256) void k_ring_reduce(RingReduce<MB> grp) {
+template <int MB, bool F>
+__global__ __launch_bounds__(256) void k_ring_reduce(RingReduce<MB, F> grp) {
     int i = 0;
     while (i + 1 < grp.n && (int)blockIdx.x >= grp.j[i + 1].first) i++;
-    const typename RingReduce<MB>::Job& j = grp.j[i];
-    const bool pairs = j.fuse == FUSE_ROPE || j.fuse == FUSE_SWIGLU;   // 4 columns and their 4 partners, 16 further in the tiles
+    const typename RingReduce<MB, F>::Job& j = grp.j[i];
+    const int fuse = [&] { if constexpr (F) return j.fuse; else return (int)FUSE_NONE; }();
+    const bool pairs = fuse == FUSE_ROPE || fuse == FUSE_SWIGLU;   // 4 columns and their 4 partners, 16 further in the tiles
     const int bm = grp.bm, bn = grp.bn, vpr = j.N / (pairs ? 8 : 4);
     const int micro = MB == 1 ? 0 : ((int)blockIdx.x - j.first) / j.blocks, micros = MB == 1 ? 1 : j.micro;
     const long idx = (long)((int)blockIdx.x - j.first - micro * j.blocks) * 256 + threadIdx.x;
@@ -518,42 +529,45 @@ __global__ __launch_bounds__(256) void k_ring_reduce(RingReduce<MB> grp) {
             sum = make_float4(v[0], v[1], v[2], v[3]);
         }
         *reinterpret_cast<float4*>(c) = sum;
-    } else if (pairs) {
-        const float* const p0 = p;
-        shares(v);
-        p = p0 + 16;
-        float u[4] = {0.f, 0.f, 0.f, 0.f};
-        shares(u);
-        const int half = j.period / 2, col = pair_column(n, j.period, j.shift, j.N);
-#pragma unroll
-        for (int e = 0; e < 4; e++) { v[e] = as_bf(v[e]); u[e] = as_bf(u[e]); }
-        if (j.fuse == FUSE_SWIGLU) {
-            uint2 o;
-            o.x = pack_bf2(swiglu(v[0], u[0]), swiglu(v[1], u[1]));
-            o.y = pack_bf2(swiglu(v[2], u[2]), swiglu(v[3], u[3]));
-            *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(j.X.at(micro)) + (size_t)m * half + col) = o;
-        } else if (n < j.rot) {
-            const float* cs = j.table + (size_t)(m % j.tokens) * half + (col & (j.period - 1));
-            const float* sn = cs + (size_t)j.table_seq * half;
-#pragma unroll
-            for (int e = 0; e < 4; e++) rotate_pair(v[e], u[e], cs[e], sn[e]);
-        }
-        bf16_t* const c = reinterpret_cast<bf16_t*>(j.C.at(micro)) + (size_t)m * j.ldc + col;
-        *reinterpret_cast<uint2*>(c) = make_uint2(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]));
-        *reinterpret_cast<uint2*>(c + half) = make_uint2(pack_bf2(u[0], u[1]), pack_bf2(u[2], u[3]));
     } else {
-        shares(v);
-        if (j.fuse == FUSE_SWIGLU_BWD) {
-            const bf16_t* gu = (const bf16_t*)j.X.at(micro) + (size_t)m * 2 * j.N + n;
-            bf16_t* dgu = (bf16_t*)j.Y.at(micro) + (size_t)m * 2 * j.N + n;
-            const uint2 gw = *reinterpret_cast<const uint2*>(gu), uw = *reinterpret_cast<const uint2*>(gu + j.N);
-            const float gt[4] = {lo_bf(gw.x), hi_bf(gw.x), lo_bf(gw.y), hi_bf(gw.y)}, up[4] = {lo_bf(uw.x), hi_bf(uw.x), lo_bf(uw.y), hi_bf(uw.y)};
-            float dg[4], du[4];
+        if constexpr (F) if (pairs) {
+            const float* const p0 = p;
+            shares(v);
+            p = p0 + 16;
+            float u[4] = {0.f, 0.f, 0.f, 0.f};
+            shares(u);
+            const int half = j.period / 2, col = pair_column(n, j.period, j.shift, j.N);
 #pragma unroll
-            for (int e = 0; e < 4; e++) swiglu_grad(gt[e], up[e], as_bf(v[e]), dg[e], du[e], v[e]);
-            *reinterpret_cast<uint2*>(dgu) = make_uint2(pack_bf2(dg[0], dg[1]), pack_bf2(dg[2], dg[3]));
-            *reinterpret_cast<uint2*>(dgu + j.N) = make_uint2(pack_bf2(du[0], du[1]), pack_bf2(du[2], du[3]));
+            for (int e = 0; e < 4; e++) { v[e] = as_bf(v[e]); u[e] = as_bf(u[e]); }
+            if (fuse == FUSE_SWIGLU) {
+                uint2 o;
+                o.x = pack_bf2(swiglu(v[0], u[0]), swiglu(v[1], u[1]));
+                o.y = pack_bf2(swiglu(v[2], u[2]), swiglu(v[3], u[3]));
+                *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(j.X.at(micro)) + (size_t)m * half + col) = o;
+            } else if (n < j.rot) {
+                const float* cs = j.table + (size_t)(m % j.tokens) * half + (col & (j.period - 1));
+                const float* sn = cs + (size_t)j.table_seq * half;
+#pragma unroll
+                for (int e = 0; e < 4; e++) rotate_pair(v[e], u[e], cs[e], sn[e]);
+            }
+            bf16_t* const c = reinterpret_cast<bf16_t*>(j.C.at(micro)) + (size_t)m * j.ldc + col;
+            *reinterpret_cast<uint2*>(c) = make_uint2(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]));
+            *reinterpret_cast<uint2*>(c + half) = make_uint2(pack_bf2(u[0], u[1]), pack_bf2(u[2], u[3]));
+            return;
         }
+        shares(v);
+        if constexpr (F)
+            if (fuse == FUSE_SWIGLU_BWD) {
+                const bf16_t* gu = (const bf16_t*)j.X.at(micro) + (size_t)m * 2 * j.N + n;
+                bf16_t* dgu = (bf16_t*)j.Y.at(micro) + (size_t)m * 2 * j.N + n;
+                const uint2 gw = *reinterpret_cast<const uint2*>(gu), uw = *reinterpret_cast<const uint2*>(gu + j.N);
+                const float gt[4] = {lo_bf(gw.x), hi_bf(gw.x), lo_bf(gw.y), hi_bf(gw.y)}, up[4] = {lo_bf(uw.x), hi_bf(uw.x), lo_bf(uw.y), hi_bf(uw.y)};
+                float dg[4], du[4];
+#pragma unroll
+                for (int e = 0; e < 4; e++) swiglu_grad(gt[e], up[e], as_bf(v[e]), dg[e], du[e], v[e]);
+                *reinterpret_cast<uint2*>(dgu) = make_uint2(pack_bf2(dg[0], dg[1]), pack_bf2(dg[2], dg[3]));
+                *reinterpret_cast<uint2*>(dgu + j.N) = make_uint2(pack_bf2(du[0], du[1]), pack_bf2(du[2], du[3]));
+            }
         const bf16_t* R = (const bf16_t*)j.R.at(micro);
         if (R) {
             const uint2 rr = *reinterpret_cast<const uint2*>(R + (size_t)m * j.ldr + n);

@@ -29,7 +29,7 @@ struct GemmMicro { Each A, B, C, R, X, Y; };
 // Each on the product rounded to bf16, as the launch would read it.
 enum { FUSE_NONE = 0, FUSE_ROPE, FUSE_SWIGLU, FUSE_SWIGLU_BWD };
 // The largest tile (rows x columns) on which the kernel does it.
-constexpr int fuse_tile(int kind) { return kind == FUSE_SWIGLU ? 128 * 128 : 64 * 128; }
+constexpr int fuse_tile(int kind) { return kind == FUSE_ROPE ? 192 * 128 : kind == FUSE_SWIGLU ? 128 * 128 : 64 * 128; }
 struct GemmFuse {
     int kind;
     int period, rot;
