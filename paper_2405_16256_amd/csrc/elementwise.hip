@@ -17,9 +17,31 @@ constexpr int NWAVES = TPB / WAVE;
 // output pass (RC raw 16-byte vectors per thread); longer rows are re-read (from L2).
 constexpr int RC = 6;
 
-template <typename T>
-__device__ __forceinline__ void rmsnorm_fwd_body(const T* __restrict__ x, const T* __restrict__ g, T* __restrict__ xn,
-                                                 float* __restrict__ r, int H, float eps) {
+// The norms read a GEMM's product right behind it.  Where the GEMM has cut k into shares, they add the shares themselves
+// (SPLIT) in place of a reduction kernel of 4 to 5 us and a pass over the product: every thread its own columns, in the order
+// and with the rounding of k_ring_reduce.
+__device__ __forceinline__ uint4 sum_shares(const GemmSplit& sp, int n_micro, int row, int c, const bf16_t* res) {
+    const int tm = row / sp.bm, tn = c / sp.bn, tile = sp.bm * sp.bn;
+    const float* p = sp.partial + ((size_t)(tm * sp.tiles_n + tn) * n_micro + blockIdx.y) * sp.ksplit * tile + (row - tm * sp.bm) * sp.bn + (c - tn * sp.bn);
+    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int s = 0; s < sp.ksplit; s++, p += tile) {
+        const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
+        v[0] += a.x; v[1] += a.y; v[2] += a.z; v[3] += a.w;
+        v[4] += b.x; v[5] += b.y; v[6] += b.z; v[7] += b.w;
+    }
+    if (res) {
+        float f[8];
+        Vec<bf16_t>::load(res, f);
+#pragma unroll
+        for (int e = 0; e < 8; e++) v[e] += f[e];
+    }
+    return make_uint4(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7]));
+}
+
+template <typename T, bool SPLIT>
+__device__ __forceinline__ void rmsnorm_fwd_body(T* __restrict__ x, const T* __restrict__ g, T* __restrict__ xn, float* __restrict__ r,
+                                                 int H, float eps, const GemmSplit& sp, int n_micro, const T* __restrict__ res) {
     constexpr int V = Vec<T>::N;
     typedef typename Vec<T>::Raw Raw;
     __shared__ float red[NWAVES];
@@ -32,7 +54,12 @@ __device__ __forceinline__ void rmsnorm_fwd_body(const T* __restrict__ x, const 
         for (int i = 0; i < RC; i++) {
             const int c = (threadIdx.x + i * TPB) * V;
             if (c < H) {
-                keep[i] = Vec<T>::raw(x + base + c);
+                if constexpr (SPLIT) {
+                    keep[i] = sum_shares(sp, n_micro, blockIdx.x, c, res + base + c);
+                    *reinterpret_cast<Raw*>(x + base + c) = keep[i];
+                } else {
+                    keep[i] = Vec<T>::raw(x + base + c);
+                }
                 float f[V];
                 Vec<T>::widen(keep[i], f);
 #pragma unroll
@@ -42,7 +69,13 @@ __device__ __forceinline__ void rmsnorm_fwd_body(const T* __restrict__ x, const 
     } else {
         for (int c = threadIdx.x * V; c < H; c += TPB * V) {
             float f[V];
-            Vec<T>::load(x + base + c, f);
+            if constexpr (SPLIT) {
+                const Raw w = sum_shares(sp, n_micro, blockIdx.x, c, res + base + c);
+                *reinterpret_cast<Raw*>(x + base + c) = w;
+                Vec<T>::widen(w, f);
+            } else {
+                Vec<T>::load(x + base + c, f);
+            }
 #pragma unroll
             for (int e = 0; e < V; e++) ss += f[e] * f[e];
         }
@@ -85,7 +118,13 @@ static Ops<N> ops(const Each& e) {
 template <typename T, int N>
 __global__ __launch_bounds__(TPB) void k_rmsnorm_fwd(Ops<N> x, const T* g, Ops<N> xn, Ops<N> r, int H, float eps) {
     const int m = blockIdx.y;
-    rmsnorm_fwd_body<T>((const T*)x.at(m), g, (T*)xn.at(m), (float*)r.at(m), H, eps);
+    rmsnorm_fwd_body<T, false>((T*)x.at(m), g, (T*)xn.at(m), (float*)r.at(m), H, eps, GemmSplit{}, 1, nullptr);
+}
+template <int N>
+__global__ __launch_bounds__(TPB) void k_rmsnorm_fwd_split(GemmSplit sp, int n, Ops<N> res, Ops<N> x, const bf16_t* g, Ops<N> xn, Ops<N> r, int H,
+                                                           float eps) {
+    const int m = blockIdx.y;
+    rmsnorm_fwd_body<bf16_t, true>((bf16_t*)x.at(m), g, (bf16_t*)xn.at(m), (float*)r.at(m), H, eps, sp, N == 1 ? 1 : n, (const bf16_t*)res.at(m));
 }
 
 // The operands of the backward kernels, one per micro-batch but for the gain.
@@ -94,6 +133,7 @@ struct NormBwd {
     Ops<N> dxn, x, r, dres, dx, partial;
     const void* g;
     int T, H, rpb, nblk, n;
+    GemmSplit split;
 };
 
 // RMSNorm backward, rows too long for registers: one workgroup walks `rpb` consecutive rows and reads each twice.
@@ -158,10 +198,11 @@ __global__ __launch_bounds__(TPB) void k_rmsnorm_bwd(NormBwd<N> a) {
 // 128 rows of 256 and 20.8 us for 2200 rows of 512 (bf16); this kernel with one to nine rows a workgroup takes
 // 3.0-4.2 and 4.8 us.
 constexpr int RW = 8;   // waves per workgroup
-template <typename T, int NV>
+template <typename T, int NV, bool SPLIT>
 __device__ __forceinline__ void rmsnorm_bwd_wave_body(const T* __restrict__ dxn, const T* __restrict__ x, const float* __restrict__ r, const T* __restrict__ g,
                                                       const T* __restrict__ dres, T* __restrict__ dx, float* __restrict__ partial,
-                                                      int T_rows, int H, int rpb) {
+                                                      int T_rows, int H, int rpb,
+                                                      const GemmSplit& sp, int n_micro) {
     constexpr int V = Vec<T>::N;
     extern __shared__ float colsum[];  // [RW][H]
     const int wave = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
@@ -184,7 +225,8 @@ __device__ __forceinline__ void rmsnorm_bwd_wave_body(const T* __restrict__ dxn,
         for (int i = 0; i < NV; i++) {
             const int c = (lane + i * WAVE) * V;
             if (c < H) {
-                Vec<T>::load(dxn + base + c, d[i]);
+                if constexpr (SPLIT) Vec<T>::widen(sum_shares(sp, n_micro, row, c, nullptr), d[i]);
+                else Vec<T>::load(dxn + base + c, d[i]);
                 Vec<T>::load(x + base + c, xx[i]);
                 Vec<T>::load(dres + base + c, rr[i]);
 #pragma unroll
@@ -224,11 +266,11 @@ __device__ __forceinline__ void rmsnorm_bwd_wave_body(const T* __restrict__ dxn,
     }
 }
 
-template <typename T, int NV, int N>
+template <typename T, int NV, int N, bool SPLIT>
 __global__ __launch_bounds__(RW * WAVE) void k_rmsnorm_bwd_wave(NormBwd<N> a) {
     const int m = blockIdx.y;
-    rmsnorm_bwd_wave_body<T, NV>((const T*)a.dxn.at(m), (const T*)a.x.at(m), (const float*)a.r.at(m), (const T*)a.g, (const T*)a.dres.at(m),
-                                 (T*)a.dx.at(m), (float*)a.partial.at(m), a.T, a.H, a.rpb);
+    rmsnorm_bwd_wave_body<T, NV, SPLIT>((const T*)a.dxn.at(m), (const T*)a.x.at(m), (const float*)a.r.at(m), (const T*)a.g, (const T*)a.dres.at(m),
+                                 (T*)a.dx.at(m), (float*)a.partial.at(m), a.T, a.H, a.rpb, a.split, N == 1 ? 1 : a.n);
 }
 
 // out[j] (=|+=) sum_b partial[b][j] of one or two gain gradients (blockIdx.y).  A workgroup covers 64 columns (a float4
@@ -357,8 +399,19 @@ static void rmsnorm_fwd_t(const Each& x, const void* g, const Each& xn, const Ea
     else if constexpr (sizeof(T) == 2)   // fp32 micro-batches come one by one
         k_rmsnorm_fwd<T, MICRO_MAX><<<dim3(T_, n), TPB, 0, st>>>(ops<MICRO_MAX>(x), (const T*)g, ops<MICRO_MAX>(xn), ops<MICRO_MAX>(r), H, eps);
 }
+template <int N>
+static void rmsnorm_fwd_split(const GemmSplit& sp, const Each& res, const Each& x, const void* g, const Each& xn, const Each& r, int n, int T, int H,
+                              float eps, hipStream_t st) {
+    k_rmsnorm_fwd_split<N><<<dim3(T, n), TPB, 0, st>>>(sp, n, ops<N>(res), ops<N>(x), (const bf16_t*)g, ops<N>(xn), ops<N>(r), H, eps);
+}
 hipError_t rmsnorm_fwd(int dtype, const Each& x, const void* g, const Each& xn, const Each& r, int n, int T, int H, float eps,
-                       hipStream_t st) {
+                       hipStream_t st, const GemmSplit* split, const Each* res) {
+    if (split) {
+        if (dtype != DT_BF16 || !res) return hipErrorInvalidValue;
+        if (n == 1) rmsnorm_fwd_split<1>(*split, *res, x, g, xn, r, n, T, H, eps, st);
+        else rmsnorm_fwd_split<MICRO_MAX>(*split, *res, x, g, xn, r, n, T, H, eps, st);
+        return hipGetLastError();
+    }
     if (dtype == DT_BF16) rmsnorm_fwd_t<bf16_t>(x, g, xn, r, n, T, H, eps, st);
     else rmsnorm_fwd_t<float>(x, g, xn, r, n, T, H, eps, st);
     return hipGetLastError();
@@ -370,10 +423,11 @@ hipError_t rmsnorm_fwd(int dtype, const Each& x, const void* g, const Each& xn, 
 __device__ __forceinline__ void keep_raw(uint4& v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
 __device__ __forceinline__ void keep_raw(float4& v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
 
-template <typename T, int NV, bool GUARD>
+template <typename T, int NV, bool GUARD, bool SPLIT>
 __device__ __forceinline__ void rmsnorm_bwd_rows_body(const T* __restrict__ dxn, const T* __restrict__ x, const float* __restrict__ r, const T* __restrict__ g,
                                                       const T* __restrict__ dres, T* __restrict__ dx, float* __restrict__ partial,
-                                                      int T_rows, int H_, int rpb) {
+                                                      int T_rows, int H_, int rpb,
+                                                      const GemmSplit& sp, int n_micro) {
     constexpr int V = Vec<T>::N;
     const int H = GUARD ? H_ : NV * TPB * V;
     typedef typename Vec<T>::Raw Raw;
@@ -386,7 +440,8 @@ __device__ __forceinline__ void rmsnorm_bwd_rows_body(const T* __restrict__ dxn,
         for (int i = 0; i < NV; i++) {
             const int c = (threadIdx.x + i * TPB) * V;
             if (GUARD && c >= H) break;
-            w.d[i] = Vec<T>::raw(dxn + base + c);
+            if constexpr (SPLIT) w.d[i] = sum_shares(sp, n_micro, row, c, nullptr);
+            else w.d[i] = Vec<T>::raw(dxn + base + c);
             w.x[i] = Vec<T>::raw(x + base + c);
             w.res[i] = Vec<T>::raw(dres + base + c);
         }
@@ -471,23 +526,33 @@ __device__ __forceinline__ void rmsnorm_bwd_rows_body(const T* __restrict__ dxn,
     }
 }
 
-template <typename T, int NV, bool GUARD, int N>
+template <typename T, int NV, bool GUARD, int N, bool SPLIT>
 __global__ __launch_bounds__(TPB, 2) void k_rmsnorm_bwd_rows(NormBwd<N> a) {
     const int m = blockIdx.y;
-    rmsnorm_bwd_rows_body<T, NV, GUARD>((const T*)a.dxn.at(m), (const T*)a.x.at(m), (const float*)a.r.at(m), (const T*)a.g, (const T*)a.dres.at(m),
-                                        (T*)a.dx.at(m), (float*)a.partial.at(m), a.T, a.H, a.rpb);
+    rmsnorm_bwd_rows_body<T, NV, GUARD, SPLIT>((const T*)a.dxn.at(m), (const T*)a.x.at(m), (const float*)a.r.at(m), (const T*)a.g, (const T*)a.dres.at(m),
+                                        (T*)a.dx.at(m), (float*)a.partial.at(m), a.T, a.H, a.rpb, a.split, N == 1 ? 1 : a.n);
 }
 
 template <typename T, int NV, bool GUARD, int N>
 static hipError_t launch_rows(const NormBwd<N>& a, hipStream_t st) {
     const int lds = a.H * (int)sizeof(float);   // at most 48 KB
-    k_rmsnorm_bwd_rows<T, NV, GUARD, N><<<dim3(a.nblk, a.n), TPB, lds, st>>>(a);
+    if constexpr (sizeof(T) == 2)
+        if (a.split.partial) {
+            k_rmsnorm_bwd_rows<T, NV, GUARD, N, true><<<dim3(a.nblk, a.n), TPB, lds, st>>>(a);
+            return hipGetLastError();
+        }
+    k_rmsnorm_bwd_rows<T, NV, GUARD, N, false><<<dim3(a.nblk, a.n), TPB, lds, st>>>(a);
     return hipGetLastError();
 }
 template <typename T, int NV, int N>
 static hipError_t launch_wave(const NormBwd<N>& a, hipStream_t st) {
     const int lds = RW * a.H * (int)sizeof(float);   // at most 32 KB
-    k_rmsnorm_bwd_wave<T, NV, N><<<dim3(a.nblk, a.n), RW * WAVE, lds, st>>>(a);
+    if constexpr (sizeof(T) == 2)
+        if (a.split.partial) {
+            k_rmsnorm_bwd_wave<T, NV, N, true><<<dim3(a.nblk, a.n), RW * WAVE, lds, st>>>(a);
+            return hipGetLastError();
+        }
+    k_rmsnorm_bwd_wave<T, NV, N, false><<<dim3(a.nblk, a.n), RW * WAVE, lds, st>>>(a);
     return hipGetLastError();
 }
 
@@ -519,6 +584,7 @@ static hipError_t rmsnorm_bwd_t(const NormBwd<N>& a, hipStream_t st) {
         case 5: return whole ? launch_rows<T, 5, false>(a, st) : launch_rows<T, 5, true>(a, st);
         case 6: return whole ? launch_rows<T, 6, false>(a, st) : launch_rows<T, 6, true>(a, st);
     }
+    if (a.split.partial) return hipErrorInvalidValue;   // a GEMM leaves its shares only for rows that stay in registers
     const int lds = a.H * (int)sizeof(float);
     static std::atomic<uint64_t> lds_ok{0};
     const hipError_t e = allow_lds((const void*)k_rmsnorm_bwd<T, N>, 32768 * (int)sizeof(float), lds_ok);
@@ -529,17 +595,18 @@ static hipError_t rmsnorm_bwd_t(const NormBwd<N>& a, hipStream_t st) {
 
 template <int N>
 static hipError_t rmsnorm_bwd_n(int dtype, const Each& dxn, const Each& x, const Each& r, const void* g, const Each& dres,
-                                const Each& dx, const Each& partial, size_t partial_bytes, int n, int T, int H, hipStream_t st) {
+                                const Each& dx, const Each& partial, size_t partial_bytes, int n, int T, int H, hipStream_t st,
+                                const GemmSplit* split) {
     NormBwd<N> a{ops<N>(dxn), ops<N>(x), ops<N>(r), ops<N>(dres), ops<N>(dx), ops<N>(partial), g, T, H, rms_rows_per_block(T, H, partial_bytes),
-                 0, n};
+                 0, n, split ? *split : GemmSplit{}};
     a.nblk = (T + a.rpb - 1) / a.rpb;
     if constexpr (N == 1) if (dtype != DT_BF16) return rmsnorm_bwd_t<float>(a, st);
     return rmsnorm_bwd_t<bf16_t>(a, st);
 }
 hipError_t rmsnorm_bwd(int dtype, const Each& dxn, const Each& x, const Each& r, const void* g, const Each& dres,
-                       const Each& dx, const Each& partial, size_t partial_bytes, int n, int T, int H, hipStream_t st) {
-    return n == 1 ? rmsnorm_bwd_n<1>(dtype, dxn, x, r, g, dres, dx, partial, partial_bytes, n, T, H, st)
-                  : rmsnorm_bwd_n<MICRO_MAX>(dtype, dxn, x, r, g, dres, dx, partial, partial_bytes, n, T, H, st);
+                       const Each& dx, const Each& partial, size_t partial_bytes, int n, int T, int H, hipStream_t st, const GemmSplit* split) {
+    return n == 1 ? rmsnorm_bwd_n<1>(dtype, dxn, x, r, g, dres, dx, partial, partial_bytes, n, T, H, st, split)
+                  : rmsnorm_bwd_n<MICRO_MAX>(dtype, dxn, x, r, g, dres, dx, partial, partial_bytes, n, T, H, st, split);
 }
 
 template <int N>

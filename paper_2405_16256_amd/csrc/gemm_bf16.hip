@@ -417,6 +417,10 @@ static hipError_t launch_dma(const GemmDesc* g, int n, hipStream_t st) {
     return hipGetLastError();
 }
 
+// Whether a problem's shares are left to the norm that reads its result, which then gathers them with one workgroup (or wave) a
+// row: not more than 64 KB a row, which takes it about as long as the reduction kernel's launch.
+static bool leaves_shares(const GemmDesc& g, int ksplit) { return (long)g.N * ksplit <= 16384 && g.N % 8 == 0; }
+
 template <bool BWD, int MB, bool F, int BM, int BN, int WM, int WN, int NS>
 static hipError_t launch_ring_n(const GemmDesc* g, const int* order, const int* ksplit, int n, hipStream_t st) {
     constexpr int LDS = NS * (BM + BN) * DK * 2;
@@ -462,10 +466,16 @@ static hipError_t launch_ring_n(const GemmDesc* g, const int* order, const int* 
         p.micro = q.micro;
         p.seq = q.kind == GEMM_TN && s == 1 ? q.micro : 1;
         first += p.tiles * s * (q.micro / p.seq);
+        if (q.split) *q.split = GemmSplit{nullptr, 1, BM, BN, (q.N + BN - 1) / BN};
         if (s > 1) {
             if (nk < s) return hipErrorInvalidValue;
             p.partial = partial;
             partial += (size_t)p.tiles * s * q.micro * BM * BN;
+            if (q.split && leaves_shares(q, s)) {
+                q.split->partial = p.partial;
+                q.split->ksplit = s;
+                continue;
+            }
             const int blocks = (int)(((long)q.M * (q.N / (q.fuse.kind == FUSE_ROPE || q.fuse.kind == FUSE_SWIGLU ? 8 : 4)) + 255) / 256);
             auto& j = red.j[red.n++];
             static_cast<RingFuse<MB, F>&>(j) = p;
@@ -692,7 +702,7 @@ static int segments(const GemmDesc& g, GemmDesc out[3]) {
     for (int i = 0; i < 3 && at[i] < g.K; i++) {
         GemmDesc& o = out[n++];
         o = g;
-        o.k1 = o.k2 = 0; o.B1 = o.B2 = nullptr;
+        o.k1 = o.k2 = 0; o.B1 = o.B2 = nullptr; o.split = nullptr;
         o.A = (const bf16_t*)g.A + at[i];
         o.B = b[i];
         o.K = at[i + 1] - at[i];

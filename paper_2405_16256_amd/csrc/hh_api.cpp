@@ -455,7 +455,7 @@ static GemmDesc desc(int kind, int M, int N, int K, const void* A, int lda, cons
     g.kind = kind; g.M = M; g.N = N; g.K = K; g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc;
     g.R = R; g.ldr = ldr; g.out_f32 = out_f32; g.accumulate = acc; g.ws = nullptr; g.ws_bytes = 0;
     g.B1 = g.B2 = nullptr; g.k1 = g.k2 = 0;
-    g.fuse = GemmFuse{};
+    g.fuse = GemmFuse{}; g.split = nullptr;
     g.micro = 1; g.each = nullptr;
     return g;
 }
@@ -570,9 +570,13 @@ static int layer_fwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_la
     if (!rotates) TR(HH_TRACE_ELEMENTWISE, 2.0 * T * (A + Akv) * es, rope(dt, qkv, Q3, p.n, T, d.S, d.nh + d.nkv, d.d, ctx->rope_table, ctx->rope_seq, st));
     TR(HH_TRACE_ATTN_FWD, attn_flop(d), attn_fwd(dt, qkv.p[0], Q3, at(saved, sl.a), (float*)at(saved, sl.lse), d.B, d.S, d.nh, d.nkv, d.d,
                                                  p.stride(), st));
+    GemmSplit left{};   // the second norm takes h's shares as they are where they are few
+    if (dt == DT_BF16) f.out.split = &left;
     HIP_TRY(pgemm(ctx, p, dt, f.out, st));
+    const bool sums = left.ksplit > 1;
+    const Each res = p.each(x);
     TR(HH_TRACE_ELEMENTWISE, 2.0 * T * H * es, rmsnorm_fwd(dt, h, w->g_mlp, p.each(at(saved, sl.hn)), p.each(at(saved, sl.r2)), p.n, T, H,
-                                                           cfg->rms_eps, st));
+                                                           cfg->rms_eps, st, sums ? &left : nullptr, &res));
     HIP_TRY(pgemm(ctx, p, dt, f.gu, f.n_gu, st));
     if (!gates) TR(HH_TRACE_ELEMENTWISE, 3.0 * T * F * es, swiglu_fwd(dt, p.each(at(saved, sl.gu)), m, p.n, T, F, st));
     HIP_TRY(pgemm(ctx, p, dt, f.down, st));
@@ -688,6 +692,10 @@ static int layer_bwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_la
     bwd_gemms(d, wl, w, g, saved, dy, ws, acc, b);
     plan_deferral(ctx, d, b);
     const bool defer = b.defer;
+    // The norms take the shares of d(hn) and d(xn) as they are where those are few and nothing else uses the scratch before.
+    GemmSplit left[3] = {};
+    if (dt == DT_BF16 && !defer && H <= 12288)
+        for (int i = 0; i < 3; i += 2) b.group[i][b.n[i] - 1].split = left + i;
     auto run_group = [&](int i) { return defer ? pgemm(ctx, p, dt, &b.group[i][b.n[i] - 1], 1, st) : pgemm(ctx, p, dt, b.group[i], b.n[i], st); };
 
     // Partial column sums of the two gain gradients.  Those of the MLP norm go to the front of the m | dgate|dup stretch
@@ -712,7 +720,7 @@ static int layer_bwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_la
     if (!gates) TR(HH_TRACE_ELEMENTWISE, 6.0 * T * F * es, swiglu_bwd(dt, m, p.each(at(saved, sl.gu)), dgu, m, p.n, T, F, st));   // dgate|dup, m
     HIP_TRY(run_group(0));
     TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dhn, p.each(at(saved, sl.h)), p.each(at(saved, sl.r2)), w->g_mlp, p.each(dy), dh,
-                                                           part2, part2_b, p.n, T, H, st));         // dh = dy + norm-bwd
+                                                           part2, part2_b, p.n, T, H, st, left[0].ksplit > 1 ? left : nullptr));   // dh = dy + norm-bwd
     if (!sum_both) TR(HH_TRACE_ELEMENTWISE, 4.0 * sums[0].rows * H, colsum_reduce(sums, 1, p.n, H, acc, st));
 
     // attention branch: h = x + a Wo^T
@@ -727,7 +735,7 @@ static int layer_bwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_la
     HIP_TRY(run_group(2));
     if (defer) HIP_TRY(pgemm(ctx, p, dt, b.dw, b.n_dw, st));
     TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dhn, p.each(x), p.each(at(saved, sl.r1)), w->g_attn, dh, p.each(dx),
-                                                           part1, part1_b, p.n, T, H, st));         // d(xn) in dhn; dx = dh + norm-bwd
+                                                           part1, part1_b, p.n, T, H, st, left[2].ksplit > 1 ? left + 2 : nullptr));   // d(xn) in dhn; dx = dh + norm-bwd
     if (sum_both) TR(HH_TRACE_ELEMENTWISE, 4.0 * (sums[0].rows + sums[1].rows) * H, colsum_reduce(sums, 2, p.n, H, acc, st));
     else TR(HH_TRACE_ELEMENTWISE, 4.0 * sums[1].rows * H, colsum_reduce(sums + 1, 1, p.n, H, acc, st));
     return HH_OK;

@@ -36,6 +36,9 @@ struct GemmFuse {
     int seq, table_seq; const float* table;   // FUSE_ROPE: as for rope()
     void* X; void* Y;
 };
+// Partial sums of an NT or NN problem that its launch has left to the kernel that reads the result: fp32 tiles
+// [tile][micro-batch][share][bm*bn], to be added in the order of the shares (then the residual) and rounded.
+struct GemmSplit { const float* partial; int ksplit, bm, bn, tiles_n; };
 struct GemmDesc {
     int kind;
     int M, N, K;
@@ -51,6 +54,7 @@ struct GemmDesc {
     void* ws;                // optional scratch for k-split partial sums (bf16 path), may be NULL
     size_t ws_bytes;         // of one micro-batch: what a plan may use
     GemmFuse fuse;
+    GemmSplit* split;        // not null: the launch may leave its partial sums (ksplit > 1 then, else C is complete)
     int micro;               // micro-batches; above 1 (bf16, gemm_bf16_on_ring) their operands are in `each`
     const GemmMicro* each;
 };
@@ -73,13 +77,15 @@ bool gemm_shares_launch(int dtype, const GemmDesc* g, int n);
 // xn = x * r * g, r = 1/sqrt(mean(x^2)+eps) per row.
 // Here and below: micro-batches 0 .. n-1 side by side, an operand's address in each of them; the result of a micro-batch
 // does not depend on n.
+// split (bf16): x has yet to be summed (with the residual `res`) and written.
 hipError_t rmsnorm_fwd(int dtype, const Each& x, const void* g, const Each& xn, const Each& r,
-                       int n, int T, int H, float eps, hipStream_t st);
+                       int n, int T, int H, float eps, hipStream_t st, const GemmSplit* split = nullptr, const Each* res = nullptr);
 // dx = dres + r*(w - u*mean(w*u)), u = x*r, w = dxn*g; per-workgroup column sums of
 // dxn*u go to partial[rmsnorm_bwd_blocks(T, H, partial_bytes)][H].
 int rmsnorm_bwd_blocks(int T, int H, size_t partial_bytes);
 hipError_t rmsnorm_bwd(int dtype, const Each& dxn, const Each& x, const Each& r, const void* g,
-                       const Each& dres, const Each& dx, const Each& partial, size_t partial_bytes, int n, int T, int H, hipStream_t st);
+                       const Each& dres, const Each& dx, const Each& partial, size_t partial_bytes, int n, int T, int H, hipStream_t st,
+                       const GemmSplit* split = nullptr);   // split (bf16): in place of dxn
 // out[H] (=|+=) column sums of partial[rows][H], of one micro-batch after the other; one or two such sums in one launch
 struct ColSum { Each partial; int rows; float* out; };
 hipError_t colsum_reduce(const ColSum* jobs, int n_jobs, int n, int H, int accumulate, hipStream_t st);
