@@ -65,7 +65,18 @@ struct FTile {
 // k stages on a few dozen workgroups.  dWdown | dWgate|up | d(hn) of hidden 256, ffn 688 and 128 tokens in three launches
 // 22.3 us, in one 15.5; of hidden 1024, ffn 2048 and 700 tokens 171 -> 137; dWo | da there 39.5 -> 32.
 constexpr int F32_MAX = 4;
-struct F32Problem {
+// F: the launch does what GemmFuse says on its way out (an instantiation of its own, as in gemm_ring.h).  A step of hidden 256,
+// ffn 688 and 128 tokens is 19 launches of 3 to 16 us, three of which are spared: 95.6 -> 89.8 us; of hidden 1024, ffn 2048 and
+// 700 tokens 507 -> 499.
+template <bool F>
+struct F32Fuse {};
+template <>
+struct F32Fuse<true> {
+    GemmFuse fuse;
+    int shift;
+};
+template <bool F>
+struct F32Problem : F32Fuse<F> {
     const float* A;
     const float* B;
     float* C;
@@ -73,13 +84,14 @@ struct F32Problem {
     uint32_t a_bytes, b_bytes;
     int kind, lda, ldb, ldc, ldr, M, N, K, accumulate, tiles, first;
 };
+template <bool F>
 struct F32Group {
     int n;
-    F32Problem p[F32_MAX];
+    F32Problem<F> p[F32_MAX];
 };
 
-template <int KIND, int BT, int NS>
-__device__ __forceinline__ void f32_body(const F32Problem& g) {
+template <int KIND, int BT, int NS, bool F>
+__device__ __forceinline__ void f32_body(const F32Problem<F>& g) {
     constexpr bool A_KC = KIND != GEMM_TN, B_KC = KIND == GEMM_NT;
     using TA = FTile<A_KC, BT>;
     using TB = FTile<B_KC, BT>;
@@ -107,7 +119,14 @@ __device__ __forceinline__ void f32_body(const F32Problem& g) {
 #pragma unroll
     for (int i = 0; i < TA::PER_WAVE; i++) sa[i] = TA::src(wave, i, m0, lda);
 #pragma unroll
-    for (int i = 0; i < TB::PER_WAVE; i++) sb[i] = TB::src(wave, i, n0, ldb);
+    for (int i = 0; i < TB::PER_WAVE; i++) {
+        int row0 = n0;
+        if constexpr (KIND == GEMM_NT && F) {   // src adds the lane's row of the tile
+            const int r = 8 * (wave * TB::PER_WAVE + i) + (lane >> 3);
+            row0 = pair_column(n0 + r, g.fuse.period, g.shift, N) - r;
+        }
+        sb[i] = TB::src(wave, i, row0, ldb);
+    }
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
     auto issue = [&](int slot, int kt) {
         const uint32_t base = lds0 + slot * STAGE;
@@ -173,8 +192,47 @@ __device__ __forceinline__ void f32_body(const F32Problem& g) {
             const float4 u = *reinterpret_cast<const float4*>(smem + q * 4096 + at);
             v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
         }
-        const int m = m0 + wm + rr, n = n0 + wn + 4 * c_r;
+        const int m = m0 + wm + rr;
+        int n = n0 + wn + 4 * c_r;
+        if constexpr (KIND == GEMM_NT && F) {
+            // the partners are 16 columns on, four lanes: lanes 0..3 of a row hold the first half's columns
+            const float4 u = make_float4(__shfl_xor(v.x, 4, WAVE), __shfl_xor(v.y, 4, WAVE), __shfl_xor(v.z, 4, WAVE), __shfl_xor(v.w, 4, WAVE));
+            if (m >= M || n >= N) continue;
+            const bool second = c_r & 4;
+            const int block = n0 + wn, half = g.fuse.period / 2, col = pair_column(block, g.fuse.period, g.shift, N) + 4 * (c_r & 3);
+            float a[4] = {v.x, v.y, v.z, v.w}, b[4] = {u.x, u.y, u.z, u.w};
+            if (g.fuse.kind == FUSE_SWIGLU) {
+                if (!second)
+                    *reinterpret_cast<float4*>((float*)g.fuse.X + (size_t)m * half + col) =
+                        make_float4(swiglu(a[0], b[0]), swiglu(a[1], b[1]), swiglu(a[2], b[2]), swiglu(a[3], b[3]));
+            } else if (block < g.fuse.rot) {
+                const float* cs = g.fuse.table + (size_t)(m % g.fuse.seq) * half + (col & (g.fuse.period - 1));
+                const float4 c4 = *reinterpret_cast<const float4*>(cs), s4 = *reinterpret_cast<const float4*>(cs + (size_t)g.fuse.table_seq * half);
+                const float c[4] = {c4.x, c4.y, c4.z, c4.w}, sn[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    float x = second ? b[e] : a[e], y = second ? a[e] : b[e];
+                    rotate_pair(x, y, c[e], sn[e]);
+                    a[e] = second ? y : x;
+                }
+                v = make_float4(a[0], a[1], a[2], a[3]);
+            }
+            n = col + (second ? half : 0);
+        }
         if (m >= M || n >= N) continue;
+        if constexpr (KIND == GEMM_NN && F) {   // v: dm
+            const float* gu = (const float*)g.fuse.X + (size_t)m * 2 * N + n;
+            float* dgu = (float*)g.fuse.Y + (size_t)m * 2 * N + n;
+            const float4 g4 = *reinterpret_cast<const float4*>(gu), u4 = *reinterpret_cast<const float4*>(gu + N);
+            float4 dg, du, mm;
+            swiglu_grad(g4.x, u4.x, v.x, dg.x, du.x, mm.x);
+            swiglu_grad(g4.y, u4.y, v.y, dg.y, du.y, mm.y);
+            swiglu_grad(g4.z, u4.z, v.z, dg.z, du.z, mm.z);
+            swiglu_grad(g4.w, u4.w, v.w, dg.w, du.w, mm.w);
+            *reinterpret_cast<float4*>(dgu) = dg;
+            *reinterpret_cast<float4*>(dgu + N) = du;
+            v = mm;
+        }
         if (R) {
             const float4 u = *reinterpret_cast<const float4*>(R + (size_t)m * ldr + n);
             v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
@@ -189,29 +247,29 @@ __device__ __forceinline__ void f32_body(const F32Problem& g) {
 }
 
 // BWD: NN and TN problems, otherwise NT
-template <bool BWD, int BT, int NS>
-__global__ __launch_bounds__(256) void k_gemm_f32(F32Group grp) {
+template <bool BWD, int BT, int NS, bool F>
+__global__ __launch_bounds__(256) void k_gemm_f32(F32Group<F> grp) {
     int i = 0;
     while (i + 1 < grp.n && (int)blockIdx.x >= grp.p[i + 1].first) i++;
-    const F32Problem& g = grp.p[i];
-    if (!BWD) f32_body<GEMM_NT, BT, NS>(g);
-    else if (g.kind == GEMM_NN) f32_body<GEMM_NN, BT, NS>(g);
-    else f32_body<GEMM_TN, BT, NS>(g);
+    const F32Problem<F>& g = grp.p[i];
+    if (!BWD) f32_body<GEMM_NT, BT, NS, F>(g);
+    else if (F || g.kind == GEMM_NN) f32_body<GEMM_NN, BT, NS, F>(g);
+    else f32_body<GEMM_TN, BT, NS, F>(g);
 }
 
-template <bool BWD, int BT, int NS>
-static hipError_t launch(F32Group& grp, hipStream_t st) {
+template <bool BWD, int BT, int NS, bool F>
+static hipError_t launch(F32Group<F>& grp, hipStream_t st) {
     constexpr int LDS = NS * 2 * BT * FK * 4;
     static_assert(LDS >= 4 * 4096, "the epilogue patches reuse the ring");
     static_assert(LDS <= 48 * 1024, "no raised LDS limit");
     int first = 0;
     for (int i = 0; i < grp.n; i++) {
-        F32Problem& p = grp.p[i];
+        F32Problem<F>& p = grp.p[i];
         p.tiles = ((p.M + BT - 1) / BT) * ((p.N + BT - 1) / BT);
         p.first = first;
         first += p.tiles;
     }
-    k_gemm_f32<BWD, BT, NS><<<first, 256, LDS, st>>>(grp);
+    k_gemm_f32<BWD, BT, NS, F><<<first, 256, LDS, st>>>(grp);
     return hipGetLastError();
 }
 
@@ -219,11 +277,11 @@ static hipError_t launch(F32Group& grp, hipStream_t st) {
 // places, have to last a quarter longer than the longest tile.  700x4096x1024 NT, 704 tiles: 53.6 us against 55.3 with
 // 32x32 tiles; 2048x8192x1024: 270 against 302; 700x1536x1024, 264 of them: 39.0 against 27.7; dWdown | dWgate|up | d(hn)
 // of hidden 1024, 700 tokens, 1712 tiles of which 176 six times as long as the others: 149 against 137.
-template <bool BWD>
-static hipError_t pick(F32Group& grp, hipStream_t st) {
+template <bool BWD, bool F>
+static hipError_t pick(F32Group<F>& grp, hipStream_t st) {
     long stages = 0, longest = 0, small = 0;
     for (int i = 0; i < grp.n; i++) {
-        const F32Problem& p = grp.p[i];
+        const F32Problem<F>& p = grp.p[i];
         const long nk = (p.K + FK - 1) / FK;
         stages += (long)((p.M + 63) / 64) * ((p.N + 63) / 64) * nk;
         longest = std::max(longest, nk);
@@ -232,17 +290,17 @@ static hipError_t pick(F32Group& grp, hipStream_t st) {
     // longest k loop first: the launch then ends with the short ones
     for (int i = 1; i < grp.n; i++)
         for (int j = i; j > 0 && grp.p[j].K > grp.p[j - 1].K; j--) std::swap(grp.p[j], grp.p[j - 1]);
-    if (stages >= 640 * longest) return launch<BWD, 64, 2>(grp, st);
+    if (stages >= 640 * longest) return launch<BWD, 64, 2, F>(grp, st);
     // Up to three 32x32 tiles per CU: six stages, because few workgroups hide little of the latency of operands that
     // another kernel has just written.  128x256x688 NT of a step of hidden 256
     // and 128 tokens: 11.3 us with two stages, 8.0 with six (704 tiles: alike).
-    if (small <= 768) return launch<BWD, 32, 6>(grp, st);
-    return launch<BWD, 32, 2>(grp, st);
+    if (small <= 768) return launch<BWD, 32, 6, F>(grp, st);
+    return launch<BWD, 32, 2, F>(grp, st);
 }
 
-hipError_t gemm_f32(const GemmDesc* d, int n, hipStream_t st) {
-    if (n < 1 || n > F32_MAX) return hipErrorInvalidValue;
-    F32Group grp{};
+template <bool F>
+static hipError_t gemm_f32_f(const GemmDesc* d, int n, hipStream_t st) {
+    F32Group<F> grp{};
     grp.n = n;
     for (int i = 0; i < n; i++) {
         const GemmDesc& g = d[i];
@@ -254,10 +312,28 @@ hipError_t gemm_f32(const GemmDesc* d, int n, hipStream_t st) {
         if (a_bytes >= (1L << 32) - (1L << 25) || b_bytes >= (1L << 32) - (1L << 25)) return hipErrorInvalidValue;
         if (g.lda > 65535 || g.ldb > 65535 || g.N % 4 != 0) return hipErrorInvalidValue;
         if (g.kind != GEMM_TN && g.K % 4 != 0) return hipErrorInvalidValue;
-        grp.p[i] = F32Problem{(const float*)g.A, (const float*)g.B, (float*)g.C, (const float*)g.R, (uint32_t)a_bytes, (uint32_t)b_bytes,
-                              g.kind, g.lda, g.ldb, g.ldc, g.ldr, g.M, g.N, g.K, g.accumulate, 0, 0};
+        F32Problem<F>& p = grp.p[i];
+        p.A = (const float*)g.A; p.B = (const float*)g.B; p.C = (float*)g.C; p.R = (const float*)g.R;
+        p.a_bytes = (uint32_t)a_bytes; p.b_bytes = (uint32_t)b_bytes;
+        p.kind = g.kind; p.lda = g.lda; p.ldb = g.ldb; p.ldc = g.ldc; p.ldr = g.ldr; p.M = g.M; p.N = g.N; p.K = g.K;
+        p.accumulate = g.accumulate;
+        if constexpr (F) {
+            // whole heads, or a whole gate|up row of two whole 16-column pieces and more; a whole dm row; nothing is added
+            const GemmFuse& f = g.fuse;
+            if (g.R || g.accumulate || f.kind != d[0].fuse.kind) return hipErrorInvalidValue;
+            if (f.kind == FUSE_ROPE && (g.kind != GEMM_NT || (f.period != 64 && f.period != 128) || g.N % f.period || f.rot % f.period ||
+                                        !f.table || f.seq <= 0 || f.table_seq < f.seq)) return hipErrorInvalidValue;
+            if (f.kind == FUSE_SWIGLU && (g.kind != GEMM_NT || f.period != g.N || g.N % 32 || !f.X)) return hipErrorInvalidValue;
+            if (f.kind == FUSE_SWIGLU_BWD && (g.kind != GEMM_NN || n != 1 || !f.X || !f.Y)) return hipErrorInvalidValue;
+            p.fuse = f;
+            p.shift = f.kind == FUSE_ROPE ? (f.period == 128 ? 7 : 6) : 31;
+        }
     }
-    return d[0].kind == GEMM_NT ? pick<false>(grp, st) : pick<true>(grp, st);
+    return d[0].kind == GEMM_NT ? pick<false, F>(grp, st) : pick<true, F>(grp, st);
+}
+hipError_t gemm_f32(const GemmDesc* d, int n, hipStream_t st) {
+    if (n < 1 || n > F32_MAX) return hipErrorInvalidValue;
+    return d[0].fuse.kind ? gemm_f32_f<true>(d, n, st) : gemm_f32_f<false>(d, n, st);
 }
 
 }  // namespace hh

@@ -28,20 +28,12 @@ namespace hh {
 // workgroup's chain and by launch latency, of which there are fewer: a 4-layer stage of hidden 256, 128 tokens and 8
 // micro-batches, two at a time, 2671 -> 1485 us; 2 layers of hidden 512, 2200 tokens, 3 micro-batches, 1092 -> 744 us.
 //
-// Fused problems (GemmFuse).  The rotary embedding and SwiGLU combine columns far apart: (c, c + period/2) of a head or of a
-// gate|up row.  The workgroup's columns are therefore taken from B's rows in another order (any order is free: each lane
-// asks for its own row): a 32-column block holds 16 columns of the first half and their 16 partners, which an accumulator
-// lane then both owns, 4q + e and 4(q + 2) + e.  C is written back in its own order, in runs of 16 columns.  Bound by launch
+// Fused problems (GemmFuse): the workgroup's columns come in pair_column's order, so that an accumulator lane owns a column
+// and its partner, 4q + e and 4(q + 2) + e of a block.  C is written back in its own order, in runs of 16 columns.  Bound by launch
 // latency, of which two launches of nine forward and one of ten backward go: forward of hidden 1024, 700 tokens 67.6 -> 65.9 us,
 // of hidden 512, 48 tokens 35.6 -> 34.1.  (Cosines asked for before the k loop, so that they need not be waited for behind it,
 // hold up the first tiles: 67.0.)
 constexpr int RING_MAX = 4;
-// the column of C that column c (of N) of the workgroups' order stands for; period 2^shift, or N (shift 31)
-__device__ __forceinline__ int pair_column(int c, int period, int shift, int N) {
-    if (c >= N) return c;
-    const int first = (c >> shift) * period, r = c - first;
-    return first + (r >> 5) * 16 + (r & 15) + ((r & 16) ? period / 2 : 0);
-}
 __device__ __forceinline__ float as_bf(float v) { return lo_bf(pack_bf2(v, 0.f)); }
 // A launch that fuses is an instantiation of its own (F): its arguments and code in the others cost each of them 0.5 us.
 template <int MB, bool F>

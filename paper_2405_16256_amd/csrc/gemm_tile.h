@@ -22,6 +22,16 @@ __device__ __forceinline__ void tile_of_index(int id, int tiles_m, int tiles_n, 
     tn = within / gsz;
 }
 
+// The rotary embedding and SwiGLU combine columns far apart: (c, c + period/2) of a head or of a gate|up row.  A GEMM that
+// does them on its way out takes its columns from B's rows in another order (any order is free: each lane asks for its own
+// row): a 32-column block holds 16 columns of the first half and their 16 partners.
+// the column of C that column c (of N) of the workgroups' order stands for; period 2^shift, or N (shift 31)
+__device__ __forceinline__ int pair_column(int c, int period, int shift, int N) {
+    if (c >= N) return c;
+    const int first = (c >> shift) * period, r = c - first;
+    return first + (r >> 5) * 16 + (r & 15) + ((r & 16) ? period / 2 : 0);
+}
+
 constexpr int DK = 64;           // k values per LDS stage
 
 __device__ __forceinline__ void dma16(uint32_t lds_addr, uint32_t voff, i32x4 rs) {

@@ -514,9 +514,10 @@ static bool gate_up_in_one(const Dims& d, const hh_layer_weights* w) { return (c
 // 1984, 3820 tokens, 128x256 tiles: 510 us, 521 with the SwiGLU gradient fused).  Nor on k_gemm_dma, whose 256 workgroups
 // all have their epilogues at once.
 static bool can_fuse(const hh_ctx* ctx, const Dims& d, int kind, GemmDesc* g, int n) {
+    if (d.dt != DT_BF16) return kind != FUSE_SWIGLU || d.F % 16 == 0;   // its column order is in pieces of 16
     RingUse use;
     for (int i = 0; i < n; i++) gemm_scratch(ctx, g[i]);
-    return d.dt == DT_BF16 && gemm_bf16_on_ring(g, n, &use) && use.tile <= fuse_tile(kind) && use.workgroups <= 256;
+    return gemm_bf16_on_ring(g, n, &use) && use.tile <= fuse_tile(kind) && use.workgroups <= 256;
 }
 
 // The projections of a forward pass: q|k|v (one problem or three), out, gate|up (one or two), down.

@@ -38,3 +38,17 @@ def test_against_the_oracle(shape, packed, shares):
     ctx = hh.hh_ctx_create(0)
     check_layer(ctx, shape, True, 931, packed=packed, label="fused %s" % (shape,))
     hh.hh_ctx_destroy(ctx)
+
+
+# fp32: tiles of 32 with deep and shallow rings and of 64; an ffn in whole pieces of 16 columns and one that is not
+@pytest.mark.parametrize("shape,packed", [
+    (S(8, 1, 64, 8, 1, 1), True), (S(40, 3, 64, 48, 33, 2, n_kv_heads=1), True), (S(72, 1, 128, 40, 65, 1), False),
+    (S(256, 4, 64, 688, 128, 1), True), (S(256, 2, 128, 336, 900, 1, n_kv_heads=1), True), (S(512, 8, 128, 1536, 1100, 1), False),
+    (S(512, 8, 128, 1536, 1100, 1), True),
+])
+def test_fp32_against_the_oracle(shape, packed):
+    from paper_2405_16256_amd import binding as hh
+    from tests.test_gpu_parity import check_layer
+    ctx = hh.hh_ctx_create(0)
+    check_layer(ctx, shape, False, 932, packed=packed, label="fused fp32 %s" % (shape,))
+    hh.hh_ctx_destroy(ctx)
