@@ -720,9 +720,11 @@ static int layer_bwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_la
     HIP_TRY(pgemm(ctx, p, dt, b.dm, st));                                                           // ... or dm (in the m buffer)
     if (!gates) TR(HH_TRACE_ELEMENTWISE, 6.0 * T * F * es, swiglu_bwd(dt, m, p.each(at(saved, sl.gu)), dgu, m, p.n, T, F, st));   // dgate|dup, m
     HIP_TRY(run_group(0));
+    const GemmSplit* const split2 = left[0].ksplit > 1 ? left : nullptr;
+    const bool gain2 = rmsnorm_bwd_sums_gain(T, H, split2);
     TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dhn, p.each(at(saved, sl.h)), p.each(at(saved, sl.r2)), w->g_mlp, p.each(dy), dh,
-                                                           part2, part2_b, p.n, T, H, st, left[0].ksplit > 1 ? left : nullptr));   // dh = dy + norm-bwd
-    if (!sum_both) TR(HH_TRACE_ELEMENTWISE, 4.0 * sums[0].rows * H, colsum_reduce(sums, 1, p.n, H, acc, st));
+                                                           part2, part2_b, p.n, T, H, st, split2, gain2 ? g->g_mlp : nullptr, acc));   // dh = dy + norm-bwd
+    if (!sum_both && !gain2) TR(HH_TRACE_ELEMENTWISE, 4.0 * sums[0].rows * H, colsum_reduce(sums, 1, p.n, H, acc, st));
 
     // attention branch: h = x + a Wo^T
     HIP_TRY(run_group(1));
@@ -735,10 +737,15 @@ static int layer_bwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_la
                                                        d.nh, d.nkv, d.d, ctx->rope_table, ctx->rope_seq, p.stride(), st));
     HIP_TRY(run_group(2));
     if (defer) HIP_TRY(pgemm(ctx, p, dt, b.dw, b.n_dw, st));
+    // (A caller may write dx over x: the gain's gradient then comes from partial sums, as no other workgroup may read x.)
+    const GemmSplit* const split1 = left[2].ksplit > 1 ? left + 2 : nullptr;
+    const size_t act = (size_t)T * H * es;
+    const bool apart = (const char*)x + act <= (const char*)dx || (const char*)dx + act <= (const char*)x;
+    const bool gain1 = apart && gain2 && rmsnorm_bwd_sums_gain(T, H, split1);   // with sums to do anyway, in that launch
     TR(HH_TRACE_ELEMENTWISE, 4.0 * T * H * es, rmsnorm_bwd(dt, dhn, p.each(x), p.each(at(saved, sl.r1)), w->g_attn, dh, p.each(dx),
-                                                           part1, part1_b, p.n, T, H, st, left[2].ksplit > 1 ? left + 2 : nullptr));   // d(xn) in dhn; dx = dh + norm-bwd
-    if (sum_both) TR(HH_TRACE_ELEMENTWISE, 4.0 * (sums[0].rows + sums[1].rows) * H, colsum_reduce(sums, 2, p.n, H, acc, st));
-    else TR(HH_TRACE_ELEMENTWISE, 4.0 * sums[1].rows * H, colsum_reduce(sums + 1, 1, p.n, H, acc, st));
+                                                           part1, part1_b, p.n, T, H, st, split1, gain1 ? g->g_attn : nullptr, acc));   // d(xn) in dhn; dx = dh + norm-bwd
+    const int first = gain2 || !sum_both ? 1 : 0;   // of the sums left to do
+    if (!gain1) TR(HH_TRACE_ELEMENTWISE, 4.0 * ((first ? 0 : sums[0].rows) + sums[1].rows) * H, colsum_reduce(sums + first, 2 - first, p.n, H, acc, st));
     return HH_OK;
 }
 

@@ -85,7 +85,10 @@ hipError_t rmsnorm_fwd(int dtype, const Each& x, const void* g, const Each& xn, 
 int rmsnorm_bwd_blocks(int T, int H, size_t partial_bytes);
 hipError_t rmsnorm_bwd(int dtype, const Each& dxn, const Each& x, const Each& r, const void* g,
                        const Each& dres, const Each& dx, const Each& partial, size_t partial_bytes, int n, int T, int H, hipStream_t st,
-                       const GemmSplit* split = nullptr);   // split (bf16): in place of dxn
+                       const GemmSplit* split = nullptr,   // bf16: in place of dxn
+                       float* gain = nullptr, int accumulate = 0);   // gain: gradient of g, written (+=) here; no partial sums then
+// Whether rmsnorm_bwd had better write the gain's gradient itself (where nothing it reads is written by it).
+bool rmsnorm_bwd_sums_gain(int T, int H, const GemmSplit* split);
 // out[H] (=|+=) column sums of partial[rows][H], of one micro-batch after the other; one or two such sums in one launch
 struct ColSum { Each partial; int rows; float* out; };
 hipError_t colsum_reduce(const ColSum* jobs, int n_jobs, int n, int H, int accumulate, hipStream_t st);
