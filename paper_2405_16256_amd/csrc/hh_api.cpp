@@ -817,16 +817,18 @@ static int stage_bwd(hh_ctx* ctx, const Pass& ps, const Dims& d, int k, const hh
     return HH_OK;
 }
 
-// How many micro-batches (of at most n_live) go through the launches side by side: as many as the workspace holds, whose
-// size is that of one.  Side by side each has its own tensors (side_layout and the gradient between layers behind them) where
-// one alone leaves room for the GEMMs' partial sums, and those partial sums behind the last one's.  Only small micro-batches fit, which
-// are also the ones whose launches leave most of the chip idle; and only where every GEMM goes to the ring kernel (bf16),
-// with the tile and split of a micro-batch by itself.
+// How many micro-batches (of at most n_live) go through the launches side by side: as many as there is room for, in buffers that
+// are sized for one after the other.  Side by side each has its own tensors (side_layout and the gradient between layers behind
+// them), one after the other where a single one has its tensors and the GEMMs' partial sums, or in the pool's slots that a pass
+// leaves free; the partial sums of all of them lie behind the tensors, or alone in the workspace.  Only where every GEMM goes to
+// the ring kernel (bf16), with the tile and split of a micro-batch by itself, which larger micro-batches do not.
+struct Side { int n; bool in_pool; };
 static size_t side_unit(const Dims& d) { return side_layout(d).total + act_bytes(d); }
-static int side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weights* w, const hh_layer_grads* g, int n_live, void* workspace) {
-    const size_t unit = side_unit(d), total = work_layout(d).total + act_bytes(d);
-    int n = std::min(n_live, MICRO_MAX);
-    if (d.dt != DT_BF16 || n < 2 || 2 * unit > total) return 1;
+static Side side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weights* w, const hh_layer_grads* g, int n_live, void* workspace) {
+    const size_t unit = side_unit(d), total = work_layout(d).total + act_bytes(d), slot = stage_pool(d, k, nullptr).per_micro;
+    if (d.dt != DT_BF16 || n_live < 2) return {1, false};
+    auto in_pool = [&](int n) { return (size_t)n * unit <= (size_t)(n_live - n) * slot; };
+    if (2 * unit > total && !(n_live > 2 && in_pool(2))) return {1, false};
     size_t partial = 0;   // of one micro-batch, the launch that has most
     ctx->gemm_ws = workspace;   // plans ask for sizes and for whether there is scratch, not where anything is
     for (int l = 0; l < k; l++) {
@@ -835,7 +837,7 @@ static int side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weight
         BwdGemms b;
         bwd_gemms(d, side_layout(d), &w[l], &g[l], workspace, workspace, workspace, 1, b);
         plan_deferral(ctx, d, b);
-        if (b.defer) return 1;
+        if (b.defer) return {1, false};
         auto take = [&](GemmDesc* q, int m) {
             RingUse use;
             for (int i = 0; i < m; i++) gemm_scratch(ctx, q[i]);
@@ -843,12 +845,14 @@ static int side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weight
             partial = std::max(partial, use.partial);
             return true;
         };
-        if (!take(f.qkv, f.n_qkv) || !take(&f.out, 1) || !take(f.gu, f.n_gu) || !take(&f.down, 1) || !take(&b.dm, 1)) return 1;
+        if (!take(f.qkv, f.n_qkv) || !take(&f.out, 1) || !take(f.gu, f.n_gu) || !take(&f.down, 1) || !take(&b.dm, 1)) return {1, false};
         for (int i = 0; i < 3; i++)
-            if (!take(b.group[i], b.n[i])) return 1;
+            if (!take(b.group[i], b.n[i])) return {1, false};
     }
-    while (n > 1 && (size_t)n * (unit + partial) > total) n--;
-    return n;
+    int ws = std::min(n_live, MICRO_MAX), pool = std::min(n_live - 1, MICRO_MAX);
+    while (ws > 1 && (size_t)ws * (unit + partial) > total) ws--;
+    while (pool > 1 && !(in_pool(pool) && pool * partial <= total)) pool--;
+    return pool > ws ? Side{pool, true} : Side{ws, false};
 }
 
 // Whether the micro-batches' boundary tensors are buffers of their own (dx[m] may be dy[m], in all of them or none): only then
@@ -899,16 +903,17 @@ static int stage_run(hh_ctx* ctx, const hh_layer_cfg* cfg, int n_layers, const h
     hipStream_t st = (hipStream_t)stream;
     const WorkLayout wl = work_layout(d);
     const size_t unit = side_unit(d);
-    const int side = n_live > 1 && separate_buffers(d, n_micro, x, y, dy, dx) ? side_by_side(ctx, d, n_layers, w, g, n_live, workspace) : 1;
-    if (side > 1) {
-        const int passes = (n_micro + side - 1) / side;
+    const Side side = n_live > 1 && separate_buffers(d, n_micro, x, y, dy, dx) ? side_by_side(ctx, d, n_layers, w, g, n_live, workspace) : Side{1, false};
+    if (side.n > 1) {
+        const int passes = (n_micro + side.n - 1) / side.n;
+        char* const ws = side.in_pool ? p.base + (size_t)side.n * p.per_micro : (char*)workspace;
+        void* const gbuf = ws + unit - act_bytes(d);
+        void* const gemm_ws = side.in_pool ? workspace : ws + (size_t)side.n * unit;
         for (int i = 0, m = 0; i < passes; i++) {   // as alike as they can be
             const int n = (n_micro - m + passes - i - 1) / (passes - i);
-            const Pass ps{n, true, p.base, p.per_micro, (const char*)workspace, unit, x + m, y + m, dy + m, dx + m};
-            void* gemm_ws = at(workspace, (size_t)side * unit);
-            TRY(stage_fwd(ctx, ps, d, cfg, n_layers, w, p, 0, x[m], y[m], workspace, gemm_ws, st));
-            TRY(stage_bwd(ctx, ps, d, n_layers, w, g, p, 0, x[m], dy[m], dx[m], m > 0 || !zero_grads_first, workspace, at(workspace, unit - act_bytes(d)),
-                          gemm_ws, st));
+            const Pass ps{n, true, p.base, p.per_micro, ws, unit, x + m, y + m, dy + m, dx + m};
+            TRY(stage_fwd(ctx, ps, d, cfg, n_layers, w, p, 0, x[m], y[m], ws, gemm_ws, st));
+            TRY(stage_bwd(ctx, ps, d, n_layers, w, g, p, 0, x[m], dy[m], dx[m], m > 0 || !zero_grads_first, ws, gbuf, gemm_ws, st));
             m += n;
         }
         return HH_OK;
@@ -931,7 +936,7 @@ extern "C" int hh_internal_side_by_side(const hh_layer_cfg* cfg, int n_layers, c
     const Dims d = dims_of(cfg);
     hh_ctx ctx{0, nullptr, 0, 0, 0.f, {}, 0, false, 0u, nullptr, {}};
     if (n_live < 2 || !separate_buffers(d, n_micro, x, y, dy, dx)) return 1;
-    return side_by_side(&ctx, d, n_layers, w, g, n_live, (void*)(uintptr_t)4096);
+    return side_by_side(&ctx, d, n_layers, w, g, n_live, (void*)(uintptr_t)4096).n;
 }
 
 extern "C" int hh_stage_step(hh_ctx* ctx, const hh_layer_cfg* cfg, int n_layers, const hh_layer_weights* w, int n_micro,

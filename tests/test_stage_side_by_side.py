@@ -17,9 +17,11 @@ CASES = [
     (I.LayerShape(512, 8, 64, 768, 1100, 2, n_kv_heads=2), False, 2, 3, 3, False, False, 3),   # split weight gradients
     (I.LayerShape(512, 4, 128, 64, 2049, 1, n_kv_heads=1), True, 1, 2, 2, True, True, 2),      # split ones, partial dK and dV
     (I.LayerShape(1024, 8, 128, 2048, 700, 1, n_kv_heads=2), True, 1, 4, 4, True, False, 3),   # larger tiles, passes of two
+    (I.LayerShape(512, 8, 64, 768, 1100, 2, n_kv_heads=2), False, 2, 8, 8, True, True, 5),     # tensors in the pool's free slots
+    (I.LayerShape(2048, 4, 128, 1408, 130, 1), True, 2, 7, 4, False, False, 4),
     (I.LayerShape(192, 3, 64, 64, 65, 40), True, 1, 2, 2, False, False, 2),                     # rows past a tile, many samples
 ]
-IDS = ["%dx%d T%d" % (c[0].hidden, c[0].ffn, c[0].seq * c[0].micro_batch) for c in CASES]
+IDS = ["%dx%d T%d M%d" % (c[0].hidden, c[0].ffn, c[0].seq * c[0].micro_batch, c[3]) for c in CASES]
 
 
 @pytest.mark.parametrize("shape,packed,k,M,n_live,acc,in_place,side", CASES, ids=IDS)
