@@ -607,12 +607,27 @@ __global__ __launch_bounds__(TPB, 2) void k_rmsnorm_bwd_rows(NormBwd<N> a) {
                                         (T*)a.dx.at(m), a.gain ? nullptr : (float*)a.partial.at(m), a.T, a.H, a.rpb, a.split, N == 1 ? 1 : a.n);
 }
 
+// One micro-batch, partial sums, no shares: the large launches.  Pointers as arguments of their own, of which the compiler knows
+// that they do not overlap: 4096 rows of 8192 58.8 us, 61.5 with the pointers in a struct.
+template <typename T, int NV, bool GUARD>
+__global__ __launch_bounds__(TPB, 2) void k_rmsnorm_bwd_rows_one(const T* __restrict__ dxn, const T* __restrict__ x, const float* __restrict__ r,
+                                                                 const T* __restrict__ g, const T* __restrict__ dres, T* __restrict__ dx,
+                                                                 float* __restrict__ partial, int T_rows, int H, int rpb) {
+    rmsnorm_bwd_rows_body<T, NV, GUARD, false>(dxn, x, r, g, dres, dx, partial, T_rows, H, rpb, GemmSplit{}, 1);
+}
+
 template <typename T, int NV, bool GUARD, int N>
 static hipError_t launch_rows(const NormBwd<N>& a, hipStream_t st) {
     const int lds = a.H * (int)sizeof(float);   // at most 48 KB
     if constexpr (sizeof(T) == 2)
         if (a.split.partial) {
             k_rmsnorm_bwd_rows<T, NV, GUARD, N, true><<<dim3(a.nblk, a.n), TPB, lds, st>>>(a);
+            return hipGetLastError();
+        }
+    if constexpr (N == 1)
+        if (!a.gain) {
+            k_rmsnorm_bwd_rows_one<T, NV, GUARD><<<a.nblk, TPB, lds, st>>>((const T*)a.dxn.p[0], (const T*)a.x.p[0], (const float*)a.r.p[0], (const T*)a.g,
+                                                                           (const T*)a.dres.p[0], (T*)a.dx.p[0], (float*)a.partial.p[0], a.T, a.H, a.rpb);
             return hipGetLastError();
         }
     k_rmsnorm_bwd_rows<T, NV, GUARD, N, false><<<dim3(a.nblk + a.gain_blocks(), a.n), TPB, lds, st>>>(a);
