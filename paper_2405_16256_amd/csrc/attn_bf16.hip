@@ -192,12 +192,6 @@ __device__ __forceinline__ void mfma_stream(L load, M mma, W side) {
     }
 }
 
-// The operand of micro-batch m (blockIdx.y) where consecutive ones lie `stride` bytes apart.
-template <typename T>
-__device__ __forceinline__ T* micro_at(T* p, size_t stride) {
-    return (T*)((const char*)p + blockIdx.y * stride);
-}
-
 // ------------------------------------------------------------------ forward
 // QW waves, each 32 queries of the block's 32 * QW, walk the key tiles; NPAR groups of them repeat the same queries and
 // take every NPAR-th tile each (NPAR tiles per step), so the longest job of the launch -- the last query block -- is

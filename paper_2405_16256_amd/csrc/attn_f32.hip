@@ -172,7 +172,8 @@ __device__ __forceinline__ float col_sum(float v) { v += __shfl_xor(v, 16, WAVE)
 
 template <int D>
 __global__ __launch_bounds__(AW* WAVE, 2) void k_attn_f32_fwd(const float* __restrict__ qkv, int ld, float* __restrict__ o,
-                                                              float* __restrict__ lse, int B, int S, int nh, int nkv) {
+                                                              float* __restrict__ lse, int B, int S, int nh, int nkv, MicroStride micro) {
+    qkv = micro_at(qkv, micro.saved); o = micro_at(o, micro.saved); lse = micro_at(lse, micro.saved);
     __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
     __shared__ float ms[AW][AT], ls[AW][AT];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4;
@@ -241,7 +242,9 @@ __global__ __launch_bounds__(AW* WAVE, 2) void k_attn_f32_bwd_q(const float* __r
                                                                 const float* __restrict__ o, const float* __restrict__ dout,
                                                                 const float* __restrict__ lse, float* __restrict__ dvec,
                                                                 float* __restrict__ dqkv, int B, int S, int nh, int nkv,
-                                                                const float* __restrict__ table, int table_seq) {
+                                                                const float* __restrict__ table, int table_seq, MicroStride micro) {
+    qkv = micro_at(qkv, micro.saved); o = micro_at(o, micro.saved); lse = micro_at(lse, micro.saved);
+    dout = micro_at(dout, micro.ws); dvec = micro_at(dvec, micro.ws); dqkv = micro_at(dqkv, micro.ws);
     __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4;
     const int nhb = nh * B, tiles = (S + AT - 1) / AT;
@@ -298,7 +301,9 @@ __global__ __launch_bounds__(AW* WAVE, 1) void k_attn_f32_bwd_kv(const float* __
                                                                  const float* __restrict__ dout, const float* __restrict__ lse,
                                                                  const float* __restrict__ dvec, float* __restrict__ dqkv,
                                                                  float* __restrict__ partial, int parts, int B, int S, int nh, int nkv,
-                                                                 const float* __restrict__ table, int table_seq) {
+                                                                 const float* __restrict__ table, int table_seq, MicroStride micro) {
+    qkv = micro_at(qkv, micro.saved); lse = micro_at(lse, micro.saved);
+    dout = micro_at(dout, micro.ws); dvec = micro_at(dvec, micro.ws); dqkv = micro_at(dqkv, micro.ws); partial = micro_at(partial, micro.ws);
     __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4;
     const int tiles = (S + AT - 1) / AT, jobs = B * nkv * parts;
@@ -374,7 +379,8 @@ __global__ __launch_bounds__(AW* WAVE, 1) void k_attn_f32_bwd_kv(const float* __
 // dk | dv of a token = the sum of its `parts` partial rows in order, dk rotated back.  A thread owns 4 channel pairs.
 template <int D>
 __global__ __launch_bounds__(256) void k_attn_f32_kv_reduce(const float* __restrict__ partial, int parts, float* __restrict__ dqkv, int ld,
-                                                            int T, int S, int nh, int nkv, const float* __restrict__ table, int table_seq) {
+                                                            int T, int S, int nh, int nkv, const float* __restrict__ table, int table_seq, MicroStride micro) {
+    partial = micro_at(partial, micro.ws); dqkv = micro_at(dqkv, micro.ws);
     constexpr int HALF = D / 2, VPH = HALF / 4;
     const int per_row = 2 * nkv * VPH;
     const long idx = (long)blockIdx.x * 256 + threadIdx.x;
@@ -401,7 +407,7 @@ __global__ __launch_bounds__(256) void k_attn_f32_kv_reduce(const float* __restr
 template <int D>
 static hipError_t launch_bwd(const float* qkv, int ld, const float* o, const float* dout, const float* lse, float* dvec, float* dqkv,
                              float* scratch, size_t scratch_bytes, int B, int S, int nh, int nkv, const float* table, int table_seq,
-                             hipStream_t st) {
+                             const MicroStride& micro, hipStream_t st) {
     const int tiles = (S + AT - 1) / AT, G = nh / nkv;
     // The query heads that share a key/value head run one after the other in a workgroup, unless that leaves fewer than
     // two workgroups per CU and the scratch holds their partial sums.  dq, dk and dv together, kept together -> dealt
@@ -411,31 +417,34 @@ static hipError_t launch_bwd(const float* qkv, int ld, const float* o, const flo
     const size_t part_bytes = (size_t)B * S * 2 * nkv * D * sizeof(float);
     for (int p = 2; p <= G; p++)
         if (G % p == 0 && (long)tiles * B * nkv * parts < 512 && p * part_bytes <= scratch_bytes) parts = p;
-    k_attn_f32_bwd_q<D><<<tiles * B * nh, AW * WAVE, 0, st>>>(qkv, ld, o, dout, lse, dvec, dqkv, B, S, nh, nkv, table, table_seq);
-    k_attn_f32_bwd_kv<D><<<tiles * B * nkv * parts, AW * WAVE, 0, st>>>(qkv, ld, dout, lse, dvec, dqkv, scratch, parts, B, S, nh, nkv,
-                                                                       table, table_seq);
+    k_attn_f32_bwd_q<D><<<dim3(tiles * B * nh, micro.n), AW * WAVE, 0, st>>>(qkv, ld, o, dout, lse, dvec, dqkv, B, S, nh, nkv, table, table_seq, micro);
+    k_attn_f32_bwd_kv<D><<<dim3(tiles * B * nkv * parts, micro.n), AW * WAVE, 0, st>>>(qkv, ld, dout, lse, dvec, dqkv, scratch, parts, B, S, nh, nkv,
+                                                                       table, table_seq, micro);
     if (parts > 1) {
         const long n = (long)B * S * 2 * nkv * (D / 8);
-        k_attn_f32_kv_reduce<D><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(scratch, parts, dqkv, ld, B * S, S, nh, nkv, table, table_seq);
+        k_attn_f32_kv_reduce<D><<<dim3((unsigned)((n + 255) / 256), micro.n), 256, 0, st>>>(scratch, parts, dqkv, ld, B * S, S, nh, nkv, table, table_seq,
+                                                                                            micro);
     }
     return hipGetLastError();
 }
 
-hipError_t attn_f32_fwd(const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, hipStream_t st) {
-    const int grid = (S + AT - 1) / AT * B * nh;
-    if (d == 64) k_attn_f32_fwd<64><<<grid, AW * WAVE, 0, st>>>((const float*)qkv, ld, (float*)o, lse, B, S, nh, nkv);
-    else if (d == 128) k_attn_f32_fwd<128><<<grid, AW * WAVE, 0, st>>>((const float*)qkv, ld, (float*)o, lse, B, S, nh, nkv);
+hipError_t attn_f32_fwd(const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, const MicroStride& micro,
+                        hipStream_t st) {
+    const int tiles = (S + AT - 1) / AT * B * nh;
+    const dim3 grid(tiles, micro.n);
+    if (d == 64) k_attn_f32_fwd<64><<<grid, AW * WAVE, 0, st>>>((const float*)qkv, ld, (float*)o, lse, B, S, nh, nkv, micro);
+    else if (d == 128) k_attn_f32_fwd<128><<<grid, AW * WAVE, 0, st>>>((const float*)qkv, ld, (float*)o, lse, B, S, nh, nkv, micro);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
 hipError_t attn_f32_bwd(const void* qkv, int ld, const void* o, const void* dout, const float* lse, float* dvec,
                         void* dqkv, float* scratch, size_t scratch_bytes, int B, int S, int nh, int nkv, int d,
-                        const float* table, int table_seq, hipStream_t st) {
+                        const float* table, int table_seq, const MicroStride& micro, hipStream_t st) {
     if (d == 64) return launch_bwd<64>((const float*)qkv, ld, (const float*)o, (const float*)dout, lse, dvec, (float*)dqkv, scratch,
-                                       scratch_bytes, B, S, nh, nkv, table, table_seq, st);
+                                       scratch_bytes, B, S, nh, nkv, table, table_seq, micro, st);
     if (d == 128) return launch_bwd<128>((const float*)qkv, ld, (const float*)o, (const float*)dout, lse, dvec, (float*)dqkv, scratch,
-                                         scratch_bytes, B, S, nh, nkv, table, table_seq, st);
+                                         scratch_bytes, B, S, nh, nkv, table, table_seq, micro, st);
     return hipErrorInvalidValue;
 }
 

@@ -95,6 +95,12 @@ __device__ __forceinline__ void swiglu_grad(float gate, float up, float dm, floa
     dup = dm * sl;
 }
 
+// ---- the operand of micro-batch m (blockIdx.y) where consecutive ones lie `stride` bytes apart.
+template <typename T>
+__device__ __forceinline__ T* micro_at(T* p, size_t stride) {
+    return (T*)((const char*)p + blockIdx.y * stride);
+}
+
 // ---- dynamic LDS above the 48 KB default -------------------------------------
 // The limit is an attribute of the (kernel, device) pair.  `done` is the calling launcher's own record (one
 // bit per device, one record per kernel instantiation) of where it has been raised already.

@@ -464,7 +464,7 @@ static inline unsigned nblocks(long n) { return (unsigned)((n + TPB - 1) / TPB);
 template <typename T>
 static void rmsnorm_fwd_t(const Each& x, const void* g, const Each& xn, const Each& r, int n, int T_, int H, float eps, hipStream_t st) {
     if (n == 1) k_rmsnorm_fwd<T, 1><<<T_, TPB, 0, st>>>(ops<1>(x), (const T*)g, ops<1>(xn), ops<1>(r), H, eps);
-    else if constexpr (sizeof(T) == 2)   // fp32 micro-batches come one by one
+    else
         k_rmsnorm_fwd<T, MICRO_MAX><<<dim3(T_, n), TPB, 0, st>>>(ops<MICRO_MAX>(x), (const T*)g, ops<MICRO_MAX>(xn), ops<MICRO_MAX>(r), H, eps);
 }
 template <int N>
@@ -701,8 +701,7 @@ static hipError_t rmsnorm_bwd_n(int dtype, const Each& dxn, const Each& x, const
     NormBwd<N> a{ops<N>(dxn), ops<N>(x), ops<N>(r), ops<N>(dres), ops<N>(dx), ops<N>(partial), g, T, H, rms_rows_per_block(T, H, partial_bytes),
                  0, n, split ? *split : GemmSplit{}, gain, accumulate};
     a.nblk = (T + a.rpb - 1) / a.rpb;
-    if constexpr (N == 1) if (dtype != DT_BF16) return rmsnorm_bwd_t<float>(a, st);
-    return rmsnorm_bwd_t<bf16_t>(a, st);
+    return dtype == DT_BF16 ? rmsnorm_bwd_t<bf16_t>(a, st) : rmsnorm_bwd_t<float>(a, st);
 }
 hipError_t rmsnorm_bwd(int dtype, const Each& dxn, const Each& x, const Each& r, const void* g, const Each& dres,
                        const Each& dx, const Each& partial, size_t partial_bytes, int n, int T, int H, hipStream_t st, const GemmSplit* split, float* gain, int accumulate) {
@@ -733,7 +732,8 @@ static void rope_t(const Each& qkv, int ld, int n, int Ttok, int S, int nrot, in
 }
 hipError_t rope(int dtype, const Each& qkv, int ld, int n, int T, int S, int nrot, int d, const float* table, int table_seq,
                 hipStream_t st) {
-    if (dtype != DT_BF16) rope_t<float, 1>(qkv, ld, 1, T, S, nrot, d, table, table_seq, st);
+    if (dtype != DT_BF16 && n == 1) rope_t<float, 1>(qkv, ld, n, T, S, nrot, d, table, table_seq, st);
+    else if (dtype != DT_BF16) rope_t<float, MICRO_MAX>(qkv, ld, n, T, S, nrot, d, table, table_seq, st);
     else if (n == 1) rope_t<bf16_t, 1>(qkv, ld, n, T, S, nrot, d, table, table_seq, st);
     else rope_t<bf16_t, MICRO_MAX>(qkv, ld, n, T, S, nrot, d, table, table_seq, st);
     return hipGetLastError();
@@ -744,7 +744,8 @@ static void swiglu_fwd_t(const Each& gu, const Each& m, int n, int Ttok, int F, 
     k_swiglu_fwd<T, N><<<dim3(nblocks((long)Ttok * (F / Vec<T>::N)), n), TPB, 0, st>>>(ops<N>(gu), ops<N>(m), Ttok, F);
 }
 hipError_t swiglu_fwd(int dtype, const Each& gu, const Each& m, int n, int T, int F, hipStream_t st) {
-    if (dtype != DT_BF16) swiglu_fwd_t<float, 1>(gu, m, 1, T, F, st);
+    if (dtype != DT_BF16 && n == 1) swiglu_fwd_t<float, 1>(gu, m, n, T, F, st);
+    else if (dtype != DT_BF16) swiglu_fwd_t<float, MICRO_MAX>(gu, m, n, T, F, st);
     else if (n == 1) swiglu_fwd_t<bf16_t, 1>(gu, m, n, T, F, st);
     else swiglu_fwd_t<bf16_t, MICRO_MAX>(gu, m, n, T, F, st);
     return hipGetLastError();
@@ -755,7 +756,8 @@ static void swiglu_bwd_t(const Each& dm, const Each& gu, const Each& dgu, const 
     k_swiglu_bwd<T, N><<<dim3(nblocks((long)Ttok * (F / Vec<T>::N)), n), TPB, 0, st>>>(ops<N>(dm), ops<N>(gu), ops<N>(dgu), ops<N>(m), Ttok, F);
 }
 hipError_t swiglu_bwd(int dtype, const Each& dm, const Each& gu, const Each& dgu, const Each& m, int n, int T, int F, hipStream_t st) {
-    if (dtype != DT_BF16) swiglu_bwd_t<float, 1>(dm, gu, dgu, m, 1, T, F, st);
+    if (dtype != DT_BF16 && n == 1) swiglu_bwd_t<float, 1>(dm, gu, dgu, m, n, T, F, st);
+    else if (dtype != DT_BF16) swiglu_bwd_t<float, MICRO_MAX>(dm, gu, dgu, m, n, T, F, st);
     else if (n == 1) swiglu_bwd_t<bf16_t, 1>(dm, gu, dgu, m, n, T, F, st);
     else swiglu_bwd_t<bf16_t, MICRO_MAX>(dm, gu, dgu, m, n, T, F, st);
     return hipGetLastError();

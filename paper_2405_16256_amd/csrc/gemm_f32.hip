@@ -75,23 +75,22 @@ struct F32Fuse<true> {
     GemmFuse fuse;
     int shift;
 };
-template <bool F>
+// MB: 1 or MICRO_MAX micro-batches, as in gemm_ring.h: NT and NN problems own that many times the workgroups, a workgroup of a TN
+// one adds the products of all of them, in order, to the gradient it reads and writes once.
+template <bool F, int MB>
 struct F32Problem : F32Fuse<F> {
-    const float* A;
-    const float* B;
-    float* C;
-    const float* R;
+    Ops<MB> A, B, C, R, X, Y;
     uint32_t a_bytes, b_bytes;
-    int kind, lda, ldb, ldc, ldr, M, N, K, accumulate, tiles, first;
+    int kind, lda, ldb, ldc, ldr, M, N, K, accumulate, tiles, first, micro;
 };
-template <bool F>
+template <bool F, int MB>
 struct F32Group {
     int n;
-    F32Problem<F> p[F32_MAX];
+    F32Problem<F, MB> p[F32_MAX];
 };
 
-template <int KIND, int BT, int NS, bool F>
-__device__ __forceinline__ void f32_body(const F32Problem<F>& g) {
+template <int KIND, int BT, int NS, bool F, int MB>
+__device__ __forceinline__ void f32_body(const F32Problem<F, MB>& g) {
     constexpr bool A_KC = KIND != GEMM_TN, B_KC = KIND == GEMM_NT;
     using TA = FTile<A_KC, BT>;
     using TB = FTile<B_KC, BT>;
@@ -100,176 +99,183 @@ __device__ __forceinline__ void f32_body(const F32Problem<F>& g) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int M = g.M, N = g.N, K = g.K, lda = g.lda, ldb = g.ldb, ldc = g.ldc, ldr = g.ldr, accumulate = g.accumulate;
     const uint32_t a_bytes = g.a_bytes, b_bytes = g.b_bytes;
-    const float* const R = g.R;
-    float* const C = g.C;
+    const int item = (int)blockIdx.x - g.first, micro = MB == 1 ? 0 : item / g.tiles;
+    const int seq = KIND == GEMM_TN && MB > 1 ? g.micro : 1;   // products summed here
+    const float* const R = (const float*)g.R.at(micro);
+    float* const C = (float*)g.C.at(micro);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, hf = lane >> 5;
     const int tiles_n = (N + BT - 1) / BT;
     int tm, tn;
-    tile_of_index((int)blockIdx.x - g.first, (M + BT - 1) / BT, tiles_n, tm, tn);
+    tile_of_index(item - micro * g.tiles, (M + BT - 1) / BT, tiles_n, tm, tn);
     const int m0 = tm * BT, n0 = tn * BT;
     const int wm = KG == 1 ? (wave >> 1) * 32 : 0, wn = KG == 1 ? (wave & 1) * 32 : 0;
     const int nk = (K + FK - 1) / FK;
 
-    const uint64_t pa = (uint64_t)g.A, pb = (uint64_t)g.B;
-    const i32x4 rsA = {(int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), (int)a_bytes, 0x00020000};
-    const i32x4 rsB = {(int)(uint32_t)pb, (int)(uint32_t)(pb >> 32), (int)b_bytes, 0x00020000};
-    const uint32_t stepA = TA::kstep_bytes(lda), stepB = TB::kstep_bytes(ldb);
-    typename TA::Src sa[TA::PER_WAVE];
-    typename TB::Src sb[TB::PER_WAVE];
+    float4 sum[4 / KG];
+    for (int mi = 0; mi < seq; mi++) {
+        const uint64_t pa = (uint64_t)g.A.at(micro + mi), pb = (uint64_t)g.B.at(micro + mi);
+        const i32x4 rsA = {(int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), (int)a_bytes, 0x00020000};
+        const i32x4 rsB = {(int)(uint32_t)pb, (int)(uint32_t)(pb >> 32), (int)b_bytes, 0x00020000};
+        const uint32_t stepA = TA::kstep_bytes(lda), stepB = TB::kstep_bytes(ldb);
+        typename TA::Src sa[TA::PER_WAVE];
+        typename TB::Src sb[TB::PER_WAVE];
 #pragma unroll
-    for (int i = 0; i < TA::PER_WAVE; i++) sa[i] = TA::src(wave, i, m0, lda);
-#pragma unroll
-    for (int i = 0; i < TB::PER_WAVE; i++) {
-        int row0 = n0;
-        if constexpr (KIND == GEMM_NT && F) {   // src adds the lane's row of the tile
-            const int r = 8 * (wave * TB::PER_WAVE + i) + (lane >> 3);
-            row0 = pair_column(n0 + r, g.fuse.period, g.shift, N) - r;
-        }
-        sb[i] = TB::src(wave, i, row0, ldb);
-    }
-    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
-    auto issue = [&](int slot, int kt) {
-        const uint32_t base = lds0 + slot * STAGE;
-        // k values at or past K read as zero: they lie past the end of a k-strided operand by themselves, in a
-        // k-contiguous one (4 values per lane, K a multiple of 8) the lane's offset is put out of range
-        const int k0 = kt * FK;
-#pragma unroll
-        for (int i = 0; i < TA::PER_WAVE; i++) {
-            const uint32_t off = sa[i].off + (uint32_t)kt * stepA;
-            dma16(base + (wave * TA::PER_WAVE + i) * 1024, A_KC && k0 + sa[i].k >= K ? a_bytes : off, rsA);
-        }
+        for (int i = 0; i < TA::PER_WAVE; i++) sa[i] = TA::src(wave, i, m0, lda);
 #pragma unroll
         for (int i = 0; i < TB::PER_WAVE; i++) {
-            const uint32_t off = sb[i].off + (uint32_t)kt * stepB;
-            dma16(base + TA::BYTES + (wave * TB::PER_WAVE + i) * 1024, B_KC && k0 + sb[i].k >= K ? b_bytes : off, rsB);
-        }
-    };
-#pragma unroll
-    for (int s = 0; s < NS - 1; s++)
-        if (s < nk) issue(s, s);
-
-    f32x16 acc;
-#pragma unroll
-    for (int r = 0; r < 16; r++) acc[r] = 0.f;
-    int slot = 0, fill = NS - 1;
-    for (int kt = 0; kt < nk; kt++) {
-        // k tile kt has landed, and everyone has read k tile kt - 1, whose slot is filled next
-        if (nk - 1 - kt >= NS - 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * PW) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        if (kt + NS - 1 < nk) issue(fill, kt + NS - 1);
-        const char* cA = smem + slot * STAGE;
-        const char* cB = cA + TA::BYTES;
-#pragma unroll
-        for (int q = 0; q < 4 / KG; q++) {
-            const int kk = KG == 1 ? q : wave;
-            const f32x4 fa = TA::frag(cA, wm, kk), fb = TB::frag(cB, wn, kk);
-#pragma unroll
-            for (int e = 0; e < 4; e++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[e], fa[e], acc, 0, 0, 0);
-        }
-        slot = slot + 1 == NS ? 0 : slot + 1;
-        fill = fill + 1 == NS ? 0 : fill + 1;
-    }
-    __syncthreads();   // nobody reads the ring any more
-    // A lane owns row lane%32 of its block and runs of 4 columns 8g + 4hf; through an LDS patch of 4 KB per block the
-    // stores cover 128-byte row segments.  With KG = 4 the patches of the waves that share a block are its partial sums.
-    char* const patch = smem + wave * 4096;
-    const int r_w = lane & 31;
-#pragma unroll
-    for (int g = 0; g < 4; g++)
-        *reinterpret_cast<float4*>(patch + r_w * 128 + (((2 * g + hf) ^ ((r_w >> 1) & 7)) << 4)) =
-            make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
-    if (KG > 1) __syncthreads();
-    const int r_r = lane >> 3, c_r = lane & 7;
-#pragma unroll
-    for (int t = 0; t < 4 / KG; t++) {
-        const int rr = 8 * (KG == 1 ? t : wave) + r_r;
-        const int at = rr * 128 + ((c_r ^ ((rr >> 1) & 7)) << 4);
-        float4 v = *reinterpret_cast<const float4*>((KG == 1 ? patch : smem) + at);
-#pragma unroll
-        for (int q = 1; q < KG; q++) {
-            const float4 u = *reinterpret_cast<const float4*>(smem + q * 4096 + at);
-            v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
-        }
-        const int m = m0 + wm + rr;
-        int n = n0 + wn + 4 * c_r;
-        if constexpr (KIND == GEMM_NT && F) {
-            // the partners are 16 columns on, four lanes: lanes 0..3 of a row hold the first half's columns
-            const float4 u = make_float4(__shfl_xor(v.x, 4, WAVE), __shfl_xor(v.y, 4, WAVE), __shfl_xor(v.z, 4, WAVE), __shfl_xor(v.w, 4, WAVE));
-            if (m >= M || n >= N) continue;
-            const bool second = c_r & 4;
-            const int block = n0 + wn, half = g.fuse.period / 2, col = pair_column(block, g.fuse.period, g.shift, N) + 4 * (c_r & 3);
-            float a[4] = {v.x, v.y, v.z, v.w}, b[4] = {u.x, u.y, u.z, u.w};
-            if (g.fuse.kind == FUSE_SWIGLU) {
-                if (!second)
-                    *reinterpret_cast<float4*>((float*)g.fuse.X + (size_t)m * half + col) =
-                        make_float4(swiglu(a[0], b[0]), swiglu(a[1], b[1]), swiglu(a[2], b[2]), swiglu(a[3], b[3]));
-            } else if (block < g.fuse.rot) {
-                const float* cs = g.fuse.table + (size_t)(m % g.fuse.seq) * half + (col & (g.fuse.period - 1));
-                const float4 c4 = *reinterpret_cast<const float4*>(cs), s4 = *reinterpret_cast<const float4*>(cs + (size_t)g.fuse.table_seq * half);
-                const float c[4] = {c4.x, c4.y, c4.z, c4.w}, sn[4] = {s4.x, s4.y, s4.z, s4.w};
-#pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    float x = second ? b[e] : a[e], y = second ? a[e] : b[e];
-                    rotate_pair(x, y, c[e], sn[e]);
-                    a[e] = second ? y : x;
-                }
-                v = make_float4(a[0], a[1], a[2], a[3]);
+            int row0 = n0;
+            if constexpr (KIND == GEMM_NT && F) {   // src adds the lane's row of the tile
+                const int r = 8 * (wave * TB::PER_WAVE + i) + (lane >> 3);
+                row0 = pair_column(n0 + r, g.fuse.period, g.shift, N) - r;
             }
-            n = col + (second ? half : 0);
+            sb[i] = TB::src(wave, i, row0, ldb);
         }
-        if (m >= M || n >= N) continue;
-        if constexpr (KIND == GEMM_NN && F) {   // v: dm
-            const float* gu = (const float*)g.fuse.X + (size_t)m * 2 * N + n;
-            float* dgu = (float*)g.fuse.Y + (size_t)m * 2 * N + n;
-            const float4 g4 = *reinterpret_cast<const float4*>(gu), u4 = *reinterpret_cast<const float4*>(gu + N);
-            float4 dg, du, mm;
-            swiglu_grad(g4.x, u4.x, v.x, dg.x, du.x, mm.x);
-            swiglu_grad(g4.y, u4.y, v.y, dg.y, du.y, mm.y);
-            swiglu_grad(g4.z, u4.z, v.z, dg.z, du.z, mm.z);
-            swiglu_grad(g4.w, u4.w, v.w, dg.w, du.w, mm.w);
-            *reinterpret_cast<float4*>(dgu) = dg;
-            *reinterpret_cast<float4*>(dgu + N) = du;
-            v = mm;
+        const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
+        auto issue = [&](int slot, int kt) {
+            const uint32_t base = lds0 + slot * STAGE;
+            // k values at or past K read as zero: they lie past the end of a k-strided operand by themselves, in a
+            // k-contiguous one (4 values per lane, K a multiple of 8) the lane's offset is put out of range
+            const int k0 = kt * FK;
+#pragma unroll
+            for (int i = 0; i < TA::PER_WAVE; i++) {
+                const uint32_t off = sa[i].off + (uint32_t)kt * stepA;
+                dma16(base + (wave * TA::PER_WAVE + i) * 1024, A_KC && k0 + sa[i].k >= K ? a_bytes : off, rsA);
+            }
+#pragma unroll
+            for (int i = 0; i < TB::PER_WAVE; i++) {
+                const uint32_t off = sb[i].off + (uint32_t)kt * stepB;
+                dma16(base + TA::BYTES + (wave * TB::PER_WAVE + i) * 1024, B_KC && k0 + sb[i].k >= K ? b_bytes : off, rsB);
+            }
+        };
+#pragma unroll
+        for (int s = 0; s < NS - 1; s++)
+            if (s < nk) issue(s, s);
+
+        f32x16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; r++) acc[r] = 0.f;
+        int slot = 0, fill = NS - 1;
+        for (int kt = 0; kt < nk; kt++) {
+            // k tile kt has landed, and everyone has read k tile kt - 1, whose slot is filled next
+            if (nk - 1 - kt >= NS - 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * PW) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (kt + NS - 1 < nk) issue(fill, kt + NS - 1);
+            const char* cA = smem + slot * STAGE;
+            const char* cB = cA + TA::BYTES;
+#pragma unroll
+            for (int q = 0; q < 4 / KG; q++) {
+                const int kk = KG == 1 ? q : wave;
+                const f32x4 fa = TA::frag(cA, wm, kk), fb = TB::frag(cB, wn, kk);
+#pragma unroll
+                for (int e = 0; e < 4; e++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[e], fa[e], acc, 0, 0, 0);
+            }
+            slot = slot + 1 == NS ? 0 : slot + 1;
+            fill = fill + 1 == NS ? 0 : fill + 1;
         }
-        if (R) {
-            const float4 u = *reinterpret_cast<const float4*>(R + (size_t)m * ldr + n);
-            v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+        __syncthreads();   // nobody reads the ring any more
+        // A lane owns row lane%32 of its block and runs of 4 columns 8g + 4hf; through an LDS patch of 4 KB per block the
+        // stores cover 128-byte row segments.  With KG = 4 the patches of the waves that share a block are its partial sums.
+        char* const patch = smem + wave * 4096;
+        const int r_w = lane & 31;
+#pragma unroll
+        for (int g = 0; g < 4; g++)
+            *reinterpret_cast<float4*>(patch + r_w * 128 + (((2 * g + hf) ^ ((r_w >> 1) & 7)) << 4)) =
+                make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
+        if (KG > 1) __syncthreads();
+        const int r_r = lane >> 3, c_r = lane & 7;
+#pragma unroll
+        for (int t = 0; t < 4 / KG; t++) {
+            const int rr = 8 * (KG == 1 ? t : wave) + r_r;
+            const int at = rr * 128 + ((c_r ^ ((rr >> 1) & 7)) << 4);
+            float4 v = *reinterpret_cast<const float4*>((KG == 1 ? patch : smem) + at);
+#pragma unroll
+            for (int q = 1; q < KG; q++) {
+                const float4 u = *reinterpret_cast<const float4*>(smem + q * 4096 + at);
+                v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+            }
+            const int m = m0 + wm + rr;
+            int n = n0 + wn + 4 * c_r;
+            if constexpr (KIND == GEMM_NT && F) {
+                // the partners are 16 columns on, four lanes: lanes 0..3 of a row hold the first half's columns
+                const float4 u = make_float4(__shfl_xor(v.x, 4, WAVE), __shfl_xor(v.y, 4, WAVE), __shfl_xor(v.z, 4, WAVE), __shfl_xor(v.w, 4, WAVE));
+                if (m >= M || n >= N) continue;
+                const bool second = c_r & 4;
+                const int block = n0 + wn, half = g.fuse.period / 2, col = pair_column(block, g.fuse.period, g.shift, N) + 4 * (c_r & 3);
+                float a[4] = {v.x, v.y, v.z, v.w}, b[4] = {u.x, u.y, u.z, u.w};
+                if (g.fuse.kind == FUSE_SWIGLU) {
+                    if (!second)
+                        *reinterpret_cast<float4*>((float*)g.X.at(micro) + (size_t)m * half + col) =
+                            make_float4(swiglu(a[0], b[0]), swiglu(a[1], b[1]), swiglu(a[2], b[2]), swiglu(a[3], b[3]));
+                } else if (block < g.fuse.rot) {
+                    const float* cs = g.fuse.table + (size_t)(m % g.fuse.seq) * half + (col & (g.fuse.period - 1));
+                    const float4 c4 = *reinterpret_cast<const float4*>(cs), s4 = *reinterpret_cast<const float4*>(cs + (size_t)g.fuse.table_seq * half);
+                    const float c[4] = {c4.x, c4.y, c4.z, c4.w}, sn[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+                    for (int e = 0; e < 4; e++) {
+                        float x = second ? b[e] : a[e], y = second ? a[e] : b[e];
+                        rotate_pair(x, y, c[e], sn[e]);
+                        a[e] = second ? y : x;
+                    }
+                    v = make_float4(a[0], a[1], a[2], a[3]);
+                }
+                n = col + (second ? half : 0);
+            }
+            if (m >= M || n >= N) continue;
+            if constexpr (KIND == GEMM_NN && F) {   // v: dm
+                const float* gu = (const float*)g.X.at(micro) + (size_t)m * 2 * N + n;
+                float* dgu = (float*)g.Y.at(micro) + (size_t)m * 2 * N + n;
+                const float4 g4 = *reinterpret_cast<const float4*>(gu), u4 = *reinterpret_cast<const float4*>(gu + N);
+                float4 dg, du, mm;
+                swiglu_grad(g4.x, u4.x, v.x, dg.x, du.x, mm.x);
+                swiglu_grad(g4.y, u4.y, v.y, dg.y, du.y, mm.y);
+                swiglu_grad(g4.z, u4.z, v.z, dg.z, du.z, mm.z);
+                swiglu_grad(g4.w, u4.w, v.w, dg.w, du.w, mm.w);
+                *reinterpret_cast<float4*>(dgu) = dg;
+                *reinterpret_cast<float4*>(dgu + N) = du;
+                v = mm;
+            }
+            if (R) {
+                const float4 u = *reinterpret_cast<const float4*>(R + (size_t)m * ldr + n);
+                v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+            }
+            float4* c = reinterpret_cast<float4*>(C + (size_t)m * ldc + n);
+            if (accumulate || mi) {
+                const float4 u = mi ? sum[t] : *c;
+                v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+            }
+            if (mi + 1 < seq) sum[t] = v;
+            else *c = v;
         }
-        float4* c = reinterpret_cast<float4*>(C + (size_t)m * ldc + n);
-        if (accumulate) {
-            const float4 u = *c;
-            v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
-        }
-        *c = v;
+        if (mi + 1 < seq) __syncthreads();   // the patches become the ring again
     }
 }
 
 // BWD: NN and TN problems, otherwise NT
-template <bool BWD, int BT, int NS, bool F>
-__global__ __launch_bounds__(256) void k_gemm_f32(F32Group<F> grp) {
+template <bool BWD, int BT, int NS, bool F, int MB>
+__global__ __launch_bounds__(256) void k_gemm_f32(F32Group<F, MB> grp) {
     int i = 0;
     while (i + 1 < grp.n && (int)blockIdx.x >= grp.p[i + 1].first) i++;
-    const F32Problem<F>& g = grp.p[i];
-    if (!BWD) f32_body<GEMM_NT, BT, NS, F>(g);
-    else if (F || g.kind == GEMM_NN) f32_body<GEMM_NN, BT, NS, F>(g);
-    else f32_body<GEMM_TN, BT, NS, F>(g);
+    const F32Problem<F, MB>& g = grp.p[i];
+    if (!BWD) f32_body<GEMM_NT, BT, NS, F, MB>(g);
+    else if (F || g.kind == GEMM_NN) f32_body<GEMM_NN, BT, NS, F, MB>(g);
+    else f32_body<GEMM_TN, BT, NS, F, MB>(g);
 }
 
-template <bool BWD, int BT, int NS, bool F>
-static hipError_t launch(F32Group<F>& grp, hipStream_t st) {
+template <bool BWD, int BT, int NS, bool F, int MB>
+static hipError_t launch(F32Group<F, MB>& grp, hipStream_t st) {
     constexpr int LDS = NS * 2 * BT * FK * 4;
     static_assert(LDS >= 4 * 4096, "the epilogue patches reuse the ring");
     static_assert(LDS <= 48 * 1024, "no raised LDS limit");
     int first = 0;
     for (int i = 0; i < grp.n; i++) {
-        F32Problem<F>& p = grp.p[i];
+        F32Problem<F, MB>& p = grp.p[i];
         p.tiles = ((p.M + BT - 1) / BT) * ((p.N + BT - 1) / BT);
         p.first = first;
-        first += p.tiles;
+        first += p.tiles * (p.kind == GEMM_TN ? 1 : p.micro);
     }
-    k_gemm_f32<BWD, BT, NS, F><<<first, 256, LDS, st>>>(grp);
+    k_gemm_f32<BWD, BT, NS, F, MB><<<first, 256, LDS, st>>>(grp);
     return hipGetLastError();
 }
 
@@ -277,11 +283,11 @@ static hipError_t launch(F32Group<F>& grp, hipStream_t st) {
 // places, have to last a quarter longer than the longest tile.  700x4096x1024 NT, 704 tiles: 53.6 us against 55.3 with
 // 32x32 tiles; 2048x8192x1024: 270 against 302; 700x1536x1024, 264 of them: 39.0 against 27.7; dWdown | dWgate|up | d(hn)
 // of hidden 1024, 700 tokens, 1712 tiles of which 176 six times as long as the others: 149 against 137.
-template <bool BWD, bool F>
-static hipError_t pick(F32Group<F>& grp, hipStream_t st) {
+template <bool BWD, bool F, int MB>
+static hipError_t pick(F32Group<F, MB>& grp, hipStream_t st) {
     long stages = 0, longest = 0, small = 0;
     for (int i = 0; i < grp.n; i++) {
-        const F32Problem<F>& p = grp.p[i];
+        const F32Problem<F, MB>& p = grp.p[i];
         const long nk = (p.K + FK - 1) / FK;
         stages += (long)((p.M + 63) / 64) * ((p.N + 63) / 64) * nk;
         longest = std::max(longest, nk);
@@ -290,17 +296,17 @@ static hipError_t pick(F32Group<F>& grp, hipStream_t st) {
     // longest k loop first: the launch then ends with the short ones
     for (int i = 1; i < grp.n; i++)
         for (int j = i; j > 0 && grp.p[j].K > grp.p[j - 1].K; j--) std::swap(grp.p[j], grp.p[j - 1]);
-    if (stages >= 640 * longest) return launch<BWD, 64, 2, F>(grp, st);
+    if (stages >= 640 * longest) return launch<BWD, 64, 2, F, MB>(grp, st);
     // Up to three 32x32 tiles per CU: six stages, because few workgroups hide little of the latency of operands that
     // another kernel has just written.  128x256x688 NT of a step of hidden 256
     // and 128 tokens: 11.3 us with two stages, 8.0 with six (704 tiles: alike).
-    if (small <= 768) return launch<BWD, 32, 6, F>(grp, st);
-    return launch<BWD, 32, 2, F>(grp, st);
+    if (small <= 768) return launch<BWD, 32, 6, F, MB>(grp, st);
+    return launch<BWD, 32, 2, F, MB>(grp, st);
 }
 
-template <bool F>
+template <bool F, int MB>
 static hipError_t gemm_f32_f(const GemmDesc* d, int n, hipStream_t st) {
-    F32Group<F> grp{};
+    F32Group<F, MB> grp{};
     grp.n = n;
     for (int i = 0; i < n; i++) {
         const GemmDesc& g = d[i];
@@ -312,8 +318,14 @@ static hipError_t gemm_f32_f(const GemmDesc* d, int n, hipStream_t st) {
         if (a_bytes >= (1L << 32) - (1L << 25) || b_bytes >= (1L << 32) - (1L << 25)) return hipErrorInvalidValue;
         if (g.lda > 65535 || g.ldb > 65535 || g.N % 4 != 0) return hipErrorInvalidValue;
         if (g.kind != GEMM_TN && g.K % 4 != 0) return hipErrorInvalidValue;
-        F32Problem<F>& p = grp.p[i];
-        p.A = (const float*)g.A; p.B = (const float*)g.B; p.C = (float*)g.C; p.R = (const float*)g.R;
+        F32Problem<F, MB>& p = grp.p[i];
+        if (g.micro < 1 || g.micro > MB || g.micro != d[0].micro || (MB > 1 && !g.each)) return hipErrorInvalidValue;
+        for (int m = 0; m < MB; m++) {
+            p.A.p[m] = MB == 1 ? const_cast<void*>(g.A) : g.each->A.p[m]; p.B.p[m] = MB == 1 ? const_cast<void*>(g.B) : g.each->B.p[m];
+            p.C.p[m] = MB == 1 ? g.C : g.each->C.p[m]; p.R.p[m] = MB == 1 ? const_cast<void*>(g.R) : g.each->R.p[m];
+            p.X.p[m] = MB == 1 ? g.fuse.X : g.each->X.p[m]; p.Y.p[m] = MB == 1 ? g.fuse.Y : g.each->Y.p[m];
+        }
+        p.micro = g.micro;
         p.a_bytes = (uint32_t)a_bytes; p.b_bytes = (uint32_t)b_bytes;
         p.kind = g.kind; p.lda = g.lda; p.ldb = g.ldb; p.ldc = g.ldc; p.ldr = g.ldr; p.M = g.M; p.N = g.N; p.K = g.K;
         p.accumulate = g.accumulate;
@@ -329,11 +341,12 @@ static hipError_t gemm_f32_f(const GemmDesc* d, int n, hipStream_t st) {
             p.shift = f.kind == FUSE_ROPE ? (f.period == 128 ? 7 : 6) : 31;
         }
     }
-    return d[0].kind == GEMM_NT ? pick<false, F>(grp, st) : pick<true, F>(grp, st);
+    return d[0].kind == GEMM_NT ? pick<false, F, MB>(grp, st) : pick<true, F, MB>(grp, st);
 }
 hipError_t gemm_f32(const GemmDesc* d, int n, hipStream_t st) {
     if (n < 1 || n > F32_MAX) return hipErrorInvalidValue;
-    return d[0].fuse.kind ? gemm_f32_f<true>(d, n, st) : gemm_f32_f<false>(d, n, st);
+    if (d[0].micro > 1) return d[0].fuse.kind ? gemm_f32_f<true, MICRO_MAX>(d, n, st) : gemm_f32_f<false, MICRO_MAX>(d, n, st);
+    return d[0].fuse.kind ? gemm_f32_f<true, 1>(d, n, st) : gemm_f32_f<false, 1>(d, n, st);
 }
 
 }  // namespace hh

@@ -26,7 +26,8 @@ namespace hh {
 // sum of those before it (`seq` of them), so that the gradient is read and written once.  Tile and split are those of a
 // micro-batch by itself, so every result is what a launch per micro-batch gives, bit for bit.  Bound as before by one
 // workgroup's chain and by launch latency, of which there are fewer: a 4-layer stage of hidden 256, 128 tokens and 8
-// micro-batches, two at a time, 2671 -> 1485 us; 2 layers of hidden 512, 2200 tokens, 3 micro-batches, 1092 -> 744 us.
+// micro-batches, two at a time, 2671 -> 1485 us; 2 layers of hidden 512, 2200 tokens, 3 micro-batches, 1092 -> 744 us (1391 and 718
+// with what came after).
 //
 // Fused problems (GemmFuse): the workgroup's columns come in pair_column's order, so that an accumulator lane owns a column
 // and its partner, 4q + e and 4(q + 2) + e of a block.  C is written back in its own order, in runs of 16 columns.  Bound by launch
@@ -34,6 +35,7 @@ namespace hh {
 // of hidden 512, 48 tokens 35.6 -> 34.1.  (Cosines asked for before the k loop, so that they need not be waited for behind it,
 // hold up the first tiles: 67.0.)
 constexpr int RING_MAX = 4;
+// rounded to bf16
 __device__ __forceinline__ float as_bf(float v) { return lo_bf(pack_bf2(v, 0.f)); }
 // A launch that fuses is an instantiation of its own (F): its arguments and code in the others cost each of them 0.5 us.
 template <int MB, bool F>

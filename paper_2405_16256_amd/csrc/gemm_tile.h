@@ -24,8 +24,8 @@ __device__ __forceinline__ void tile_of_index(int id, int tiles_m, int tiles_n, 
 
 // The rotary embedding and SwiGLU combine columns far apart: (c, c + period/2) of a head or of a gate|up row.  A GEMM that
 // does them on its way out takes its columns from B's rows in another order (any order is free: each lane asks for its own
-// row): a 32-column block holds 16 columns of the first half and their 16 partners.
-// the column of C that column c (of N) of the workgroups' order stands for; period 2^shift, or N (shift 31)
+// row): a 32-column block holds 16 columns of the first half and their 16 partners.  This is the column of C that column c (of
+// N) of that order stands for; period 2^shift, or N (shift 31).
 __device__ __forceinline__ int pair_column(int c, int period, int shift, int N) {
     if (c >= N) return c;
     const int first = (c >> shift) * period, r = c - first;

@@ -27,10 +27,11 @@ hipError_t attn_bf16_bwd(const void* qkv, int ld, const void* o, const void* dou
                          void* dqkv, float* scratch, int B, int S, int nh, int nkv, int d,
                          const float* rope, int rope_seq, const MicroStride& micro, hipStream_t st);
 size_t attn_bf16_bwd_scratch_bytes(int B, int S, int nh, int nkv, int d);
-hipError_t attn_f32_fwd(const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, hipStream_t st);
+hipError_t attn_f32_fwd(const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, const MicroStride& micro,
+                        hipStream_t st);
 hipError_t attn_f32_bwd(const void* qkv, int ld, const void* o, const void* dout, const float* lse, float* dvec,
                         void* dqkv, float* scratch, size_t scratch_bytes, int B, int S, int nh, int nkv, int d,
-                        const float* rope, int rope_seq, hipStream_t st);
+                        const float* rope, int rope_seq, const MicroStride& micro, hipStream_t st);
 
 hipError_t gemm(int dtype, const GemmDesc* g, int n, hipStream_t st) {
     if (dtype == DT_BF16) return gemm_bf16(g, n, st);
@@ -46,6 +47,7 @@ hipError_t gemm(int dtype, const GemmDesc* g, int n, hipStream_t st) {
     for (int i = 0; i < n; i++) {
         const int at[3] = {g[i].k1, g[i].k2 ? g[i].k2 : g[i].K, g[i].K};
         const void* const b[2] = {g[i].B1, g[i].B2};
+        if (g[i].k1 && g[i].micro > 1) return hipErrorInvalidValue;
         for (int s = 0; s < 2 && g[i].k1 && at[s] < g[i].K && e == hipSuccess; s++) {
             q[i].A = (const float*)g[i].A + at[s];
             q[i].B = b[s];
@@ -59,7 +61,7 @@ hipError_t gemm(int dtype, const GemmDesc* g, int n, hipStream_t st) {
 bool gemm_shares_launch(int dtype, const GemmDesc* g, int n) { return dtype == DT_BF16 ? gemm_bf16_shares_launch(g, n) : n > 1; }
 hipError_t attn_fwd(int dtype, const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, const MicroStride& micro,
                     hipStream_t st) {
-    return dtype == DT_BF16 ? attn_bf16_fwd(qkv, ld, o, lse, B, S, nh, nkv, d, micro, st) : attn_f32_fwd(qkv, ld, o, lse, B, S, nh, nkv, d, st);
+    return dtype == DT_BF16 ? attn_bf16_fwd(qkv, ld, o, lse, B, S, nh, nkv, d, micro, st) : attn_f32_fwd(qkv, ld, o, lse, B, S, nh, nkv, d, micro, st);
 }
 size_t attn_bwd_scratch_bytes(int dtype, int B, int S, int nh, int nkv, int d) {
     return dtype == DT_BF16 ? attn_bf16_bwd_scratch_bytes(B, S, nh, nkv, d) : 0;
@@ -68,7 +70,7 @@ hipError_t attn_bwd(int dtype, const void* qkv, int ld, const void* o, const voi
                     void* dqkv, void* scratch, size_t scratch_bytes, int B, int S, int nh, int nkv, int d,
                     const float* rope_table, int rope_seq, const MicroStride& micro, hipStream_t st) {
     if (dtype == DT_BF16) return attn_bf16_bwd(qkv, ld, o, dout, lse, dvec, dqkv, (float*)scratch, B, S, nh, nkv, d, rope_table, rope_seq, micro, st);
-    return attn_f32_bwd(qkv, ld, o, dout, lse, dvec, dqkv, (float*)scratch, scratch_bytes, B, S, nh, nkv, d, rope_table, rope_seq, st);
+    return attn_f32_bwd(qkv, ld, o, dout, lse, dvec, dqkv, (float*)scratch, scratch_bytes, B, S, nh, nkv, d, rope_table, rope_seq, micro, st);
 }
 }  // namespace hh
 
@@ -276,6 +278,7 @@ static WorkLayout work_layout(const Dims& d) {
 static size_t gain_bytes(const Dims& d) { return (size_t)std::min(d.T, 256) * d.H * 4; }
 static WorkLayout side_layout(const Dims& d) {
     const WorkLayout one = work_layout(d);
+    if (d.dt != DT_BF16) return one;   // whose attention keeps its partial sums in m | dgate|dup | d(hn)
     WorkLayout w;
     w.m = one.m; w.dgu = one.dgu;
     w.da = w.m;
@@ -821,12 +824,13 @@ static int stage_bwd(hh_ctx* ctx, const Pass& ps, const Dims& d, int k, const hh
 // are sized for one after the other.  Side by side each has its own tensors (side_layout and the gradient between layers behind
 // them), one after the other where a single one has its tensors and the GEMMs' partial sums, or in the pool's slots that a pass
 // leaves free; the partial sums of all of them lie behind the tensors, or alone in the workspace.  Only where every GEMM goes to
-// the ring kernel (bf16), with the tile and split of a micro-batch by itself, which larger micro-batches do not.
+// the ring kernel, with the tile and split of a micro-batch by itself, which larger bf16 micro-batches do not; fp32 ones with packed
+// weights.
 struct Side { int n; bool in_pool; };
 static size_t side_unit(const Dims& d) { return side_layout(d).total + act_bytes(d); }
 static Side side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weights* w, const hh_layer_grads* g, int n_live, void* workspace) {
     const size_t unit = side_unit(d), total = work_layout(d).total + act_bytes(d), slot = stage_pool(d, k, nullptr).per_micro;
-    if (d.dt != DT_BF16 || n_live < 2) return {1, false};
+    if (n_live < 2) return {1, false};
     auto in_pool = [&](int n) { return (size_t)n * unit <= (size_t)(n_live - n) * slot; };
     if (2 * unit > total && !(n_live > 2 && in_pool(2))) return {1, false};
     size_t partial = 0;   // of one micro-batch, the launch that has most
@@ -838,6 +842,10 @@ static Side side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weigh
         bwd_gemms(d, side_layout(d), &w[l], &g[l], workspace, workspace, workspace, 1, b);
         plan_deferral(ctx, d, b);
         if (b.defer) return {1, false};
+        if (d.dt != DT_BF16) {
+            if (f.n_qkv == 3 || f.n_gu == 2) return {1, false};   // its input gradients take B in segments, one call after the other
+            continue;
+        }
         auto take = [&](GemmDesc* q, int m) {
             RingUse use;
             for (int i = 0; i < m; i++) gemm_scratch(ctx, q[i]);
@@ -911,7 +919,7 @@ static int stage_run(hh_ctx* ctx, const hh_layer_cfg* cfg, int n_layers, const h
         void* const gemm_ws = side.in_pool ? workspace : ws + (size_t)side.n * unit;
         for (int i = 0, m = 0; i < passes; i++) {   // as alike as they can be
             const int n = (n_micro - m + passes - i - 1) / (passes - i);
-            const Pass ps{n, true, p.base, p.per_micro, ws, unit, x + m, y + m, dy + m, dx + m};
+            const Pass ps{n, d.dt == DT_BF16, p.base, p.per_micro, ws, unit, x + m, y + m, dy + m, dx + m};
             TRY(stage_fwd(ctx, ps, d, cfg, n_layers, w, p, 0, x[m], y[m], ws, gemm_ws, st));
             TRY(stage_bwd(ctx, ps, d, n_layers, w, g, p, 0, x[m], dy[m], dx[m], m > 0 || !zero_grads_first, ws, gbuf, gemm_ws, st));
             m += n;

@@ -55,7 +55,7 @@ struct GemmDesc {
     size_t ws_bytes;         // of one micro-batch: what a plan may use
     GemmFuse fuse;
     GemmSplit* split;        // not null: the launch may leave its partial sums (ksplit > 1 then, else C is complete)
-    int micro;               // micro-batches; above 1 (bf16, gemm_bf16_on_ring) their operands are in `each`
+    int micro;               // micro-batches; above 1 (bf16: where gemm_bf16_on_ring) their operands are in `each`
     const GemmMicro* each;
 };
 constexpr size_t GEMM_WS_BYTES = (size_t)64 << 20;   // enough for 256 partial tiles of 256x256 fp32
@@ -107,8 +107,8 @@ hipError_t swiglu_bwd(int dtype, const Each& dm, const Each& gu, const Each& dgu
 // Causal attention over a [T, ld] buffer holding q | k | v column blocks of width nh*d, nkv*d, nkv*d;
 // query head h uses key/value head h / (nh / nkv).  o [T, nh*d]; lse [B, nh, S] natural-log sum-exp of
 // the scaled scores.
-// bf16: micro.n micro-batches side by side, micro.saved bytes apart in qkv, o and lse, micro.ws bytes in dout, dvec, dqkv and
-// scratch (fp32: one); how a micro-batch is split over workgroups does not depend on micro.n.
+// micro.n micro-batches side by side, micro.saved bytes apart in qkv, o and lse, micro.ws bytes in dout, dvec, dqkv and
+// scratch; how a micro-batch is split over workgroups does not depend on micro.n.
 struct MicroStride { int n; size_t saved, ws; };
 hipError_t attn_fwd(int dtype, const void* qkv, int ld, void* o, float* lse,
                     int B, int S, int nh, int nkv, int d, const MicroStride& micro, hipStream_t st);

@@ -21,18 +21,26 @@ CASES = [
     (I.LayerShape(2048, 4, 128, 1408, 130, 1), True, 2, 7, 4, False, False, 4),
     (I.LayerShape(192, 3, 64, 64, 65, 40), True, 1, 2, 2, False, False, 2),                     # rows past a tile, many samples
 ]
-IDS = ["%dx%d T%d M%d" % (c[0].hidden, c[0].ffn, c[0].seq * c[0].micro_batch, c[3]) for c in CASES]
+F32_CASES = [
+    (I.LayerShape(256, 4, 64, 688, 128, 1), True, 2, 5, 5, False, False, 3),
+    (I.LayerShape(72, 1, 128, 40, 33, 2), True, 1, 8, 8, True, True, 3),                  # no whole pieces of 16 columns
+    (I.LayerShape(128, 4, 64, 256, 300, 1, n_kv_heads=1), True, 3, 8, 5, False, False, 3),     # partial dK and dV
+    (I.LayerShape(512, 4, 128, 1536, 700, 1), True, 2, 4, 4, True, False, 2),             # tiles of 64
+]
+CASES = [c + (True,) for c in CASES] + [c + (False,) for c in F32_CASES]
+IDS = ["%s%dx%d T%d M%d" % ("" if c[8] else "fp32 ", c[0].hidden, c[0].ffn, c[0].seq * c[0].micro_batch, c[3]) for c in CASES]
 
 
-@pytest.mark.parametrize("shape,packed,k,M,n_live,acc,in_place,side", CASES, ids=IDS)
-def test_rule(shape, packed, k, M, n_live, acc, in_place, side):
-    buffers = stage_plans.boundary(shape, 2, M, in_place)
-    assert stage_plans.side_by_side(shape, k, M, n_live, packed, buffers=buffers) == side
-    assert stage_plans.side_by_side(shape, k, M, 1, packed, buffers=buffers) == 1
+@pytest.mark.parametrize("shape,packed,k,M,n_live,acc,in_place,side,bf16", CASES, ids=IDS)
+def test_rule(shape, packed, k, M, n_live, acc, in_place, side, bf16):
+    buffers = stage_plans.boundary(shape, 2 if bf16 else 4, M, in_place)
+    assert stage_plans.side_by_side(shape, k, M, n_live, packed, bf16, buffers=buffers) == side
+    assert stage_plans.side_by_side(shape, k, M, 1, packed, bf16, buffers=buffers) == 1
 
 
 def test_rule_leaves_out():
-    assert stage_plans.side_by_side(TINY, 2, 4, 4, bf16=False) == 1                    # fp32
+    assert stage_plans.side_by_side(TINY, 2, 2, 2, bf16=False) == 1                    # fp32: no room for a second one's tensors
+    assert stage_plans.side_by_side(TINY, 2, 8, 8, packed=False, bf16=False) == 1      # fp32: weights in three parts
     assert stage_plans.side_by_side(I.CFG2, 1, 4, 4) == 1                              # no room in the workspace, tiles of 256
     x, y, dy, dx = stage_plans.boundary(TINY, 2, 3)
     bytes_ = 2 * 128 * 256
@@ -57,20 +65,20 @@ def _stage(hh, L, ctx, cfg, layers, n_live, xs, ys, dys, dxs, zero_first):
     assert (pool[pool_b:] == 0xFF).all() and (ws[ws_b:] == 0xFF).all()
 
 
-def _inputs(L, shape, packed, k, M):
-    layers = [[L.DeviceLayer(I.layer_weights(811, l, shape, True), shape, True, packed) for l in range(k)] for _ in range(2)]
-    acts = [I.activations(811, shape, m, True) for m in range(M)]
-    return layers, [L.to_dev(a[0], True) for a in acts], [L.to_dev(a[1], True) for a in acts]
+def _inputs(L, shape, packed, k, M, bf16=True):
+    layers = [[L.DeviceLayer(I.layer_weights(811, l, shape, bf16), shape, bf16, packed) for l in range(k)] for _ in range(2)]
+    acts = [I.activations(811, shape, m, bf16) for m in range(M)]
+    return layers, [L.to_dev(a[0], bf16) for a in acts], [L.to_dev(a[1], bf16) for a in acts]
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape,packed,k,M,n_live,acc,in_place,side", CASES, ids=IDS)
-def test_same_bits_as_one_by_one(shape, packed, k, M, n_live, acc, in_place, side):
+@pytest.mark.parametrize("shape,packed,k,M,n_live,acc,in_place,side,bf16", CASES, ids=IDS)
+def test_same_bits_as_one_by_one(shape, packed, k, M, n_live, acc, in_place, side, bf16):
     from paper_2405_16256_amd import binding as hh
     from paper_2405_16256_amd import glue as L
     ctx = hh.hh_ctx_create(0)
-    cfg = L.cfg_of(shape, True)
-    (side_layers, one_layers), xs, dys = _inputs(L, shape, packed, k, M)
+    cfg = L.cfg_of(shape, bf16)
+    (side_layers, one_layers), xs, dys = _inputs(L, shape, packed, k, M, bf16)
     out = []
     for layers, live in ((side_layers, n_live), (one_layers, 1)):
         for l in layers:
