@@ -802,18 +802,28 @@ bool gemm_bf16_shares_launch(const GemmDesc* g, int n) {
     return r.how != Route::APART;
 }
 
+// Weight gradients that 256x256 tiles would take, of too few tokens for those to be cut along k: several micro-batches go to the
+// ring kernel all the same, which forms the same bits (whole k loops in order) and reads and writes a gradient once for all
+// of them.  One micro-batch at a time that traffic is most of such a launch: TODO.
+constexpr int WHOLE_DW = V_128x256;
+static bool whole_dw(const GemmDesc& g) { return g.kind == GEMM_TN && (g.K + DK - 1) / DK < 8; }   // see tail_shares
+
 bool gemm_bf16_on_ring(const GemmDesc* g, int n, RingUse* use) {
-    if (n < 1 || n > RING_MAX) return false;
+    if (n < 1 || n > DMA_MAX) return false;
     Route r;
     route(g, n, r);
-    if (r.how == Route::TILES256 || (r.how == Route::RING && r.group.v >= V_DMA)) return false;
+    const bool ring = r.how == Route::RING;
+    if (ring && r.group.v >= V_DMA) return false;
     *use = RingUse{0, 0, 0};
     for (int i = 0; i < n; i++) {
-        const bool ring = r.how == Route::RING;
         const Plan& p = ring ? r.group : r.each[i];
-        if (p.v >= V_DMA) return false;
-        const int s = p.ksplit[ring ? i : 0], tile = tile_size(p.v);
-        const long w = tiles_of(g[i], VARIANTS[p.v]) * s;
+        int v = p.v, s = p.ksplit[ring ? i : 0];
+        if (r.how == Route::TILES256 || v == V_DMA) {
+            if (!whole_dw(g[i])) return false;
+            v = WHOLE_DW; s = 1;
+        } else if (v > V_DMA) return false;
+        const int tile = tile_size(v);
+        const long w = tiles_of(g[i], VARIANTS[v]) * s;
         const size_t b = s > 1 ? (size_t)w * tile * sizeof(float) : 0;
         use->partial = ring ? use->partial + b : std::max(use->partial, b);
         use->workgroups = ring ? use->workgroups + w : std::max(use->workgroups, w);
@@ -834,11 +844,18 @@ hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st) {
     route(g, n, r);
     for (int i = 0; i < n; i++)   // several micro-batches, fusions: where gemm_bf16_on_ring says so
         if (g[i].micro < 1 || g[i].micro > MICRO_MAX || g[i].micro != g[0].micro || (g[i].micro > 1 && !g[i].each) ||
-            ((g[i].micro > 1 || g[i].fuse.kind) && (r.how == Route::TILES256 || (r.how == Route::RING ? r.group.v : r.each[i].v) >= V_DMA)) ||
+            ((g[i].micro > 1 || g[i].fuse.kind) && (r.how == Route::TILES256 || (r.how == Route::RING ? r.group.v : r.each[i].v) >= V_DMA) &&
+             !(g[i].micro > 1 && whole_dw(g[i]))) ||
             (g[i].fuse.kind == FUSE_SWIGLU_BWD && n > 1) || (g[i].fuse.kind != g[0].fuse.kind) ||
             (g[i].fuse.kind && tile_size(r.how == Route::RING ? r.group.v : r.each[i].v) > fuse_tile(g[i].fuse.kind)))
             return hipErrorInvalidValue;
     if (r.how == Route::RING) return launch_planned(g, n, r.group, st);
+    const Plan whole{WHOLE_DW, {1, 1, 1, 1}, {0, 1, 2, 3}, 0.0};
+    if (r.how == Route::TILES256 && g[0].micro > 1) {
+        hipError_t e = hipSuccess;
+        for (int i = 0; i < n && e == hipSuccess; i += RING_MAX) e = launch_planned(g + i, std::min(n - i, RING_MAX), whole, st);
+        return e;
+    }
     if (r.how == Route::TILES256) return launch_tiles256(g, n, st);
     for (int i = 0; i < n; i++) {
         hipError_t e = hipSuccess;
@@ -846,7 +863,7 @@ hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st) {
             GemmDesc seg[3];
             const int m = segments(g[i], seg);
             for (int j = 0; j < m && e == hipSuccess; j++) e = launch_planned(seg + j, 1, plan(seg + j, 1, false), st);
-        } else e = launch_planned(g + i, 1, r.each[i], st);
+        } else e = launch_planned(g + i, 1, g[i].micro > 1 && r.each[i].v == V_DMA ? whole : r.each[i], st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

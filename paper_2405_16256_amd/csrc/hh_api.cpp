@@ -47,12 +47,18 @@ hipError_t gemm(int dtype, const GemmDesc* g, int n, hipStream_t st) {
     for (int i = 0; i < n; i++) {
         const int at[3] = {g[i].k1, g[i].k2 ? g[i].k2 : g[i].K, g[i].K};
         const void* const b[2] = {g[i].B1, g[i].B2};
-        if (g[i].k1 && g[i].micro > 1) return hipErrorInvalidValue;
         for (int s = 0; s < 2 && g[i].k1 && at[s] < g[i].K && e == hipSuccess; s++) {
+            GemmMicro each{};
             q[i].A = (const float*)g[i].A + at[s];
             q[i].B = b[s];
             q[i].K = at[s + 1] - at[s];
             q[i].R = g[i].C; q[i].ldr = g[i].ldc;
+            for (int m = 0; m < g[i].micro && g[i].micro > 1; m++) {
+                each.A.p[m] = (float*)g[i].each->A.p[m] + at[s];
+                each.B.p[m] = const_cast<void*>(b[s]);
+                each.C.p[m] = each.R.p[m] = g[i].each->C.p[m];
+                q[i].each = &each;
+            }
             e = gemm_f32(q + i, 1, st);
         }
     }
@@ -824,8 +830,7 @@ static int stage_bwd(hh_ctx* ctx, const Pass& ps, const Dims& d, int k, const hh
 // are sized for one after the other.  Side by side each has its own tensors (side_layout and the gradient between layers behind
 // them), one after the other where a single one has its tensors and the GEMMs' partial sums, or in the pool's slots that a pass
 // leaves free; the partial sums of all of them lie behind the tensors, or alone in the workspace.  Only where every GEMM goes to
-// the ring kernel, with the tile and split of a micro-batch by itself, which larger bf16 micro-batches do not; fp32 ones with packed
-// weights.
+// the ring kernel, with the tile and split of a micro-batch by itself, which larger bf16 micro-batches do not.
 struct Side { int n; bool in_pool; };
 static size_t side_unit(const Dims& d) { return side_layout(d).total + act_bytes(d); }
 static Side side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weights* w, const hh_layer_grads* g, int n_live, void* workspace) {
@@ -841,11 +846,7 @@ static Side side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weigh
         BwdGemms b;
         bwd_gemms(d, side_layout(d), &w[l], &g[l], workspace, workspace, workspace, 1, b);
         plan_deferral(ctx, d, b);
-        if (b.defer) return {1, false};
-        if (d.dt != DT_BF16) {
-            if (f.n_qkv == 3 || f.n_gu == 2) return {1, false};   // its input gradients take B in segments, one call after the other
-            continue;
-        }
+        if (d.dt != DT_BF16) continue;   // any
         auto take = [&](GemmDesc* q, int m) {
             RingUse use;
             for (int i = 0; i < m; i++) gemm_scratch(ctx, q[i]);
@@ -855,7 +856,8 @@ static Side side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weigh
         };
         if (!take(f.qkv, f.n_qkv) || !take(&f.out, 1) || !take(f.gu, f.n_gu) || !take(&f.down, 1) || !take(&b.dm, 1)) return {1, false};
         for (int i = 0; i < 3; i++)
-            if (!take(b.group[i], b.n[i])) return {1, false};
+            if (!take(b.defer ? &b.group[i][b.n[i] - 1] : b.group[i], b.defer ? 1 : b.n[i])) return {1, false};
+        if (b.defer && !take(b.dw, b.n_dw)) return {1, false};
     }
     int ws = std::min(n_live, MICRO_MAX), pool = std::min(n_live - 1, MICRO_MAX);
     while (ws > 1 && (size_t)ws * (unit + partial) > total) ws--;

@@ -19,6 +19,7 @@ CASES = [
     (I.LayerShape(1024, 8, 128, 2048, 700, 1, n_kv_heads=2), True, 1, 4, 4, True, False, 3),   # larger tiles, passes of two
     (I.LayerShape(512, 8, 64, 768, 1100, 2, n_kv_heads=2), False, 2, 8, 8, True, True, 5),     # tensors in the pool's free slots
     (I.LayerShape(2048, 4, 128, 1408, 130, 1), True, 2, 7, 4, False, False, 4),
+    (I.LayerShape(2048, 16, 128, 5632, 64, 1), True, 1, 4, 3, True, False, 3),                 # weight gradients that alone take 256x256
     (I.LayerShape(192, 3, 64, 64, 65, 40), True, 1, 2, 2, False, False, 2),                     # rows past a tile, many samples
 ]
 F32_CASES = [
@@ -26,6 +27,7 @@ F32_CASES = [
     (I.LayerShape(72, 1, 128, 40, 33, 2), True, 1, 8, 8, True, True, 3),                  # no whole pieces of 16 columns
     (I.LayerShape(128, 4, 64, 256, 300, 1, n_kv_heads=1), True, 3, 8, 5, False, False, 3),     # partial dK and dV
     (I.LayerShape(512, 4, 128, 1536, 700, 1), True, 2, 4, 4, True, False, 2),             # tiles of 64
+    (I.LayerShape(128, 4, 64, 192, 77, 1, n_kv_heads=2), False, 1, 6, 6, True, False, 3),   # B of the input gradients in segments
 ]
 CASES = [c + (True,) for c in CASES] + [c + (False,) for c in F32_CASES]
 IDS = ["%s%dx%d T%d M%d" % ("" if c[8] else "fp32 ", c[0].hidden, c[0].ffn, c[0].seq * c[0].micro_batch, c[3]) for c in CASES]
@@ -40,7 +42,6 @@ def test_rule(shape, packed, k, M, n_live, acc, in_place, side, bf16):
 
 def test_rule_leaves_out():
     assert stage_plans.side_by_side(TINY, 2, 2, 2, bf16=False) == 1                    # fp32: no room for a second one's tensors
-    assert stage_plans.side_by_side(TINY, 2, 8, 8, packed=False, bf16=False) == 1      # fp32: weights in three parts
     assert stage_plans.side_by_side(I.CFG2, 1, 4, 4) == 1                              # no room in the workspace, tiles of 256
     x, y, dy, dx = stage_plans.boundary(TINY, 2, 3)
     bytes_ = 2 * 128 * 256
