@@ -27,7 +27,7 @@ F32_CASES = [
     (I.LayerShape(72, 1, 128, 40, 33, 2), True, 1, 8, 8, True, True, 3),                  # no whole pieces of 16 columns
     (I.LayerShape(128, 4, 64, 256, 300, 1, n_kv_heads=1), True, 3, 8, 5, False, False, 3),     # partial dK and dV
     (I.LayerShape(512, 4, 128, 1536, 700, 1), True, 2, 4, 4, True, False, 2),             # tiles of 64
-    (I.LayerShape(128, 4, 64, 192, 77, 1, n_kv_heads=2), False, 1, 6, 6, True, False, 3),   # B of the input gradients in segments
+    (I.LayerShape(128, 4, 64, 192, 77, 1, n_kv_heads=2), False, 1, 6, 6, True, False, 2),   # B of the input gradients in segments
 ]
 CASES = [c + (True,) for c in CASES] + [c + (False,) for c in F32_CASES]
 IDS = ["%s%dx%d T%d M%d" % ("" if c[8] else "fp32 ", c[0].hidden, c[0].ffn, c[0].seq * c[0].micro_batch, c[3]) for c in CASES]
