@@ -179,7 +179,8 @@ int hh_layer_bwd(hh_ctx *ctx, const hh_layer_cfg *cfg, const hh_layer_weights *w
 
 /* Sizes for a stage of n_layers layers over n_micro micro-batches: the pool
  * keeps every layer's saved block and the activations between layers for all
- * micro-batches (forward of all micro-batches precedes backward). */
+ * micro-batches (forward of all micro-batches precedes backward).  What pool
+ * and workspace hold after a stage call is unspecified. */
 int hh_stage_sizes(const hh_layer_cfg *cfg, int n_layers, int n_micro,
                    size_t *saved_pool_bytes, size_t *workspace_bytes);
 
