@@ -278,22 +278,24 @@ static WorkLayout work_layout(const Dims& d) {
     return w;
 }
 
-// The same for one of several micro-batches that go side by side, packed closer: what the attention branch's backward needs
-// takes the place of m and dgate|dup, which nobody reads any more by then; both sets of gain-gradient partials have a place of
-// their own (`partial`, two times gain_bytes).  The GEMMs' scratch is not part of it.
+// The same for one of several micro-batches that go side by side: both sets of gain-gradient partials have a place of their own
+// (`partial`, two times gain_bytes), and the GEMMs' scratch is not part of it.  Packed closer unless a layer defers its weight
+// gradients: what the attention branch's backward needs takes the place of m and dgate|dup, whose last readers are the weight
+// gradients of the MLP, and deferred ones read them at the very end.
 static size_t gain_bytes(const Dims& d) { return (size_t)std::min(d.T, 256) * d.H * 4; }
-static WorkLayout side_layout(const Dims& d) {
+static WorkLayout side_layout(const Dims& d, bool defers) {
     const WorkLayout one = work_layout(d);
     if (d.dt != DT_BF16) return one;   // whose attention keeps its partial sums in m | dgate|dup | d(hn)
-    WorkLayout w;
-    w.m = one.m; w.dgu = one.dgu;
-    w.da = w.m;
-    w.dqkv = w.da + (one.dqkv - one.da);
-    w.dvec = w.dqkv + (one.dvec - one.dqkv);
-    w.dkv_part = w.dvec + (one.dkv_part - one.dvec);
-    w.dhn = std::max(one.dhn, w.dkv_part + (one.partial - one.dkv_part));
-    w.dh = w.dhn + (one.dh - one.dhn);
-    w.partial = w.dh + (one.da - one.dh);
+    WorkLayout w = one;
+    if (!defers) {
+        w.da = w.m;
+        w.dqkv = w.da + (one.dqkv - one.da);
+        w.dvec = w.dqkv + (one.dvec - one.dqkv);
+        w.dkv_part = w.dvec + (one.dkv_part - one.dvec);
+        w.dhn = std::max(one.dhn, w.dkv_part + (one.partial - one.dkv_part));
+        w.dh = w.dhn + (one.dh - one.dhn);
+        w.partial = w.dh + (one.da - one.dh);
+    }
     w.gemm_ws = w.total = w.partial + 2 * up256(gain_bytes(d));
     return w;
 }
@@ -474,7 +476,7 @@ static GemmDesc desc(int kind, int M, int N, int K, const void* A, int lda, cons
 // the first micro-batch; at() gives those of the others.
 struct Pass {
     int n;
-    bool side;   // workspaces laid out by side_layout
+    const WorkLayout* side;   // how the workspaces are laid out (null: work_layout)
     const char* pool; size_t pool_stride;
     const char* ws; size_t ws_stride;
     const void* const* x; void* const* y;
@@ -497,7 +499,7 @@ struct Pass {
     }
     MicroStride stride() const { return MicroStride{n, pool_stride, ws_stride}; }
 };
-static const Pass ONE{1, false, nullptr, 0, nullptr, 0, nullptr, nullptr, nullptr, nullptr};
+static const Pass ONE{1, nullptr, nullptr, 0, nullptr, 0, nullptr, nullptr, nullptr, nullptr};
 
 // GEMMs of a pass: in every micro-batch of it.
 static hipError_t pgemm(hh_ctx* ctx, const Pass& p, int dt, GemmDesc* g, int n, hipStream_t st) {
@@ -561,7 +563,7 @@ static void fwd_gemms(const Dims& d, const hh_layer_weights* w, const void* x, v
 static int layer_fwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_layer_cfg* cfg, const hh_layer_weights* w, const void* x,
                           void* y, void* saved, void* ws, void* gemm_ws, hipStream_t st) {
     const SavedLayout sl = saved_layout(d);
-    const WorkLayout wl = p.side ? side_layout(d) : work_layout(d);
+    const WorkLayout wl = p.side ? *p.side : work_layout(d);
     const int T = d.T, H = d.H, A = d.A, F = d.F, dt = d.dt, Akv = d.Akv, Q3 = d.Q3;
     const size_t es = d.es;
     const Each qkv = p.each(at(saved, sl.qkv)), h = p.each(at(saved, sl.h)), m = p.each(at(ws, wl.m));
@@ -693,7 +695,7 @@ static void plan_deferral(const hh_ctx* ctx, const Dims& d, BwdGemms& b) {
 static int layer_bwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_layer_weights* w, const void* x, const void* saved,
                           const void* dy, void* dx, const hh_layer_grads* g, int acc, void* ws, void* gemm_ws, hipStream_t st) {
     const SavedLayout sl = saved_layout(d);
-    const WorkLayout one = work_layout(d), wl = p.side ? side_layout(d) : one;
+    const WorkLayout one = work_layout(d), wl = p.side ? *p.side : one;
     const int T = d.T, H = d.H, F = d.F, dt = d.dt;
     const size_t es = d.es;
     acc = acc ? 1 : 0;
@@ -831,20 +833,22 @@ static int stage_bwd(hh_ctx* ctx, const Pass& ps, const Dims& d, int k, const hh
 // them), one after the other where a single one has its tensors and the GEMMs' partial sums, or in the pool's slots that a pass
 // leaves free; the partial sums of all of them lie behind the tensors, or alone in the workspace.  Only where every GEMM goes to
 // the ring kernel, with the tile and split of a micro-batch by itself, which larger bf16 micro-batches do not.
-struct Side { int n; bool in_pool; };
-static size_t side_unit(const Dims& d) { return side_layout(d).total + act_bytes(d); }
+struct Side { int n; bool in_pool, defers; };
+static size_t side_unit(const Dims& d, bool defers) { return side_layout(d, defers).total + act_bytes(d); }
 static Side side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weights* w, const hh_layer_grads* g, int n_live, void* workspace) {
-    const size_t unit = side_unit(d), total = work_layout(d).total + act_bytes(d), slot = stage_pool(d, k, nullptr).per_micro;
-    if (n_live < 2) return {1, false};
+    const size_t total = work_layout(d).total + act_bytes(d), slot = stage_pool(d, k, nullptr).per_micro;
+    size_t unit = side_unit(d, false);
+    const Side one{1, false, false};
     auto in_pool = [&](int n) { return (size_t)n * unit <= (size_t)(n_live - n) * slot; };
-    if (2 * unit > total && !(n_live > 2 && in_pool(2))) return {1, false};
+    if (n_live < 2 || (2 * unit > total && !(n_live > 2 && in_pool(2)))) return one;
+    bool defers = false;
     size_t partial = 0;   // of one micro-batch, the launch that has most
     ctx->gemm_ws = workspace;   // plans ask for sizes and for whether there is scratch, not where anything is
     for (int l = 0; l < k; l++) {
         FwdGemms f;
         fwd_gemms(d, &w[l], workspace, workspace, workspace, workspace, f);
         BwdGemms b;
-        bwd_gemms(d, side_layout(d), &w[l], &g[l], workspace, workspace, workspace, 1, b);
+        bwd_gemms(d, work_layout(d), &w[l], &g[l], workspace, workspace, workspace, 1, b);
         plan_deferral(ctx, d, b);
         if (d.dt != DT_BF16) continue;   // any
         auto take = [&](GemmDesc* q, int m) {
@@ -854,15 +858,17 @@ static Side side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weigh
             partial = std::max(partial, use.partial);
             return true;
         };
-        if (!take(f.qkv, f.n_qkv) || !take(&f.out, 1) || !take(f.gu, f.n_gu) || !take(&f.down, 1) || !take(&b.dm, 1)) return {1, false};
+        if (!take(f.qkv, f.n_qkv) || !take(&f.out, 1) || !take(f.gu, f.n_gu) || !take(&f.down, 1) || !take(&b.dm, 1)) return one;
         for (int i = 0; i < 3; i++)
-            if (!take(b.defer ? &b.group[i][b.n[i] - 1] : b.group[i], b.defer ? 1 : b.n[i])) return {1, false};
-        if (b.defer && !take(b.dw, b.n_dw)) return {1, false};
+            if (!take(b.defer ? &b.group[i][b.n[i] - 1] : b.group[i], b.defer ? 1 : b.n[i])) return one;
+        if (b.defer && !take(b.dw, b.n_dw)) return one;
+        defers = defers || b.defer;
     }
+    unit = side_unit(d, defers);
     int ws = std::min(n_live, MICRO_MAX), pool = std::min(n_live - 1, MICRO_MAX);
     while (ws > 1 && (size_t)ws * (unit + partial) > total) ws--;
     while (pool > 1 && !(in_pool(pool) && pool * partial <= total)) pool--;
-    return pool > ws ? Side{pool, true} : Side{ws, false};
+    return pool > ws ? Side{pool, true, defers} : Side{ws, false, defers};
 }
 
 // Whether the micro-batches' boundary tensors are buffers of their own (dx[m] may be dy[m], in all of them or none): only then
@@ -912,16 +918,17 @@ static int stage_run(hh_ctx* ctx, const hh_layer_cfg* cfg, int n_layers, const h
     const StagePool p = stage_pool(d, n_layers, saved_pool);
     hipStream_t st = (hipStream_t)stream;
     const WorkLayout wl = work_layout(d);
-    const size_t unit = side_unit(d);
-    const Side side = n_live > 1 && separate_buffers(d, n_micro, x, y, dy, dx) ? side_by_side(ctx, d, n_layers, w, g, n_live, workspace) : Side{1, false};
+    const Side side = n_live > 1 && separate_buffers(d, n_micro, x, y, dy, dx) ? side_by_side(ctx, d, n_layers, w, g, n_live, workspace) : Side{1, false, false};
     if (side.n > 1) {
+        const WorkLayout sl = side_layout(d, side.defers);
+        const size_t unit = side_unit(d, side.defers);
         const int passes = (n_micro + side.n - 1) / side.n;
         char* const ws = side.in_pool ? p.base + (size_t)side.n * p.per_micro : (char*)workspace;
         void* const gbuf = ws + unit - act_bytes(d);
         void* const gemm_ws = side.in_pool ? workspace : ws + (size_t)side.n * unit;
         for (int i = 0, m = 0; i < passes; i++) {   // as alike as they can be
             const int n = (n_micro - m + passes - i - 1) / (passes - i);
-            const Pass ps{n, d.dt == DT_BF16, p.base, p.per_micro, ws, unit, x + m, y + m, dy + m, dx + m};
+            const Pass ps{n, d.dt == DT_BF16 ? &sl : nullptr, p.base, p.per_micro, ws, unit, x + m, y + m, dy + m, dx + m};
             TRY(stage_fwd(ctx, ps, d, cfg, n_layers, w, p, 0, x[m], y[m], ws, gemm_ws, st));
             TRY(stage_bwd(ctx, ps, d, n_layers, w, g, p, 0, x[m], dy[m], dx[m], m > 0 || !zero_grads_first, ws, gbuf, gemm_ws, st));
             m += n;
@@ -947,6 +954,19 @@ extern "C" int hh_internal_side_by_side(const hh_layer_cfg* cfg, int n_layers, c
     hh_ctx ctx{0, nullptr, 0, 0, 0.f, {}, 0, false, 0u, nullptr, {}};
     if (n_live < 2 || !separate_buffers(d, n_micro, x, y, dy, dx)) return 1;
     return side_by_side(&ctx, d, n_layers, w, g, n_live, (void*)(uintptr_t)4096).n;
+}
+
+// Likewise: where the tensors of one of them lie (m, dgate|dup, d(hn), dh, da, dqkv, delta, partial dK and dV, gain partials, the
+// gradient between layers, and the end), and the bytes of the partial dK and dV.
+extern "C" void hh_internal_side_layout(const hh_layer_cfg* cfg, int n_layers, const hh_layer_weights* w, const hh_layer_grads* g, size_t at[11],
+                                        size_t* dkv_part_bytes) {
+    const Dims d = dims_of(cfg);
+    hh_ctx ctx{0, nullptr, 0, 0, 0.f, {}, 0, false, 0u, nullptr, {}};
+    const bool defers = side_by_side(&ctx, d, n_layers, w, g, 1 << 20, (void*)(uintptr_t)4096).defers;
+    const WorkLayout s = side_layout(d, defers);
+    const size_t all[11] = {s.m, s.dgu, s.dhn, s.dh, s.da, s.dqkv, s.dvec, s.dkv_part, s.partial, s.total, side_unit(d, defers)};
+    std::copy(all, all + 11, at);
+    *dkv_part_bytes = attn_bwd_scratch_bytes(d.dt, d.B, d.S, d.nh, d.nkv, d.d);
 }
 
 extern "C" int hh_stage_step(hh_ctx* ctx, const hh_layer_cfg* cfg, int n_layers, const hh_layer_weights* w, int n_micro,

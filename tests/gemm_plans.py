@@ -19,8 +19,8 @@ def plan(problems):
     return [(how, tile, int(shares)) for how, tile, shares in rows]
 
 
-def layer_launches(s, packed=True):
-    """{name of the GEMM: (how, tile, k shares)} of a forward and a backward pass of a layer."""
+def _calls(s, packed):
+    """The GEMMs of a layer, [(name, problem)] of each call: those up to d(m), and the three groups of the backward pass."""
     T, H, F, A, Akv = s.tokens, s.hidden, s.ffn, s.n_heads * s.head_dim, s.kv_heads * s.head_dim
     Q3 = A + 2 * Akv
     qkv, gu = ({"qkv": Q3}, {"gate|up": 2 * F}) if packed else ({"q": A, "k": Akv, "v": Akv}, {"gate": F, "up": F})
@@ -30,9 +30,21 @@ def layer_launches(s, packed=True):
               + [("d gate|up", (NN, T, H, 2 * F, 0 if packed else F))],
               [("dW out", (TN, H, A, T)), ("d out", (NN, T, A, H))],
               [("dW " + n, (TN, w, H, T)) for n, w in qkv.items()] + [("d qkv", (NN, T, H, Q3) + (() if packed else (A, A + Akv)))]]
+    return calls, groups
+
+
+def defers(s, packed=True):
+    """Whether the layer leaves its weight gradients to one launch at the end of its backward pass."""
+    groups = _calls(s, packed)[1]
     defer = hh.lib.hh_internal_gemm_defer(_ints([p for g in groups for _, p in g]), (C.c_int * 3)(*[len(g) for g in groups]))
     assert defer in (0, 1)
-    if defer:
+    return bool(defer)
+
+
+def layer_launches(s, packed=True):
+    """{name of the GEMM: (how, tile, k shares)} of a forward and a backward pass of a layer."""
+    calls, groups = _calls(s, packed)
+    if defers(s, packed):
         calls += [g[-1:] for g in groups] + [[q for g in groups for q in g[:-1]]]
     else:
         calls += groups

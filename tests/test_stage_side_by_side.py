@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2405_16256_amd import inputs as I
-from tests import stage_plans
+from tests import gemm_plans, stage_plans
 
 TINY = I.LayerShape(256, 4, 64, 704, 128, 1)
 # shape, packed, layers, micro-batches, alive, added to the gradients, dx over dy; the number side by side
@@ -22,6 +22,15 @@ CASES = [
     (I.LayerShape(2048, 16, 128, 5632, 64, 1), True, 1, 4, 3, True, False, 3),                 # weight gradients that alone take 256x256
     (I.LayerShape(192, 3, 64, 64, 65, 40), True, 1, 2, 2, False, False, 2),                     # rows past a tile, many samples
 ]
+# layers that leave their weight gradients to one launch at the end, of tensors that the attention branch must not overwrite before
+DEFERRING = [
+    (I.LayerShape(1536, 12, 128, 768, 400, 1), True, 1, 4, 4, False, False, 3),                        # passes of two, in the workspace
+    (I.LayerShape(2176, 17, 128, 768, 426, 1, n_kv_heads=1), True, 2, 8, 8, True, True, 4),            # in the pool's free slots; partial dK and dV
+    (I.LayerShape(2240, 35, 64, 2368, 397, 1, n_kv_heads=5), False, 1, 3, 2, True, False, 2),          # seven problems in two launches
+    (I.LayerShape(1664, 26, 64, 704, 424, 1, n_kv_heads=1), False, 2, 3, 3, False, False, 3),
+    (I.LayerShape(3392, 26, 128, 9536, 33, 1), False, 1, 2, 2, False, False, 2),                       # one k tile
+]
+CASES += DEFERRING
 F32_CASES = [
     (I.LayerShape(256, 4, 64, 688, 128, 1), True, 2, 5, 5, False, False, 3),
     (I.LayerShape(72, 1, 128, 40, 33, 2), True, 1, 8, 8, True, True, 3),                  # no whole pieces of 16 columns
@@ -38,6 +47,35 @@ def test_rule(shape, packed, k, M, n_live, acc, in_place, side, bf16):
     buffers = stage_plans.boundary(shape, 2 if bf16 else 4, M, in_place)
     assert stage_plans.side_by_side(shape, k, M, n_live, packed, bf16, buffers=buffers) == side
     assert stage_plans.side_by_side(shape, k, M, 1, packed, bf16, buffers=buffers) == 1
+
+
+def _random_shapes(n):
+    rng = np.random.default_rng(17)
+    for _ in range(n):
+        d, hidden = int(rng.choice((64, 128))), 64 * int(np.exp(rng.uniform(np.log(2), np.log(192))))
+        heads = max(1, int(hidden / d * rng.choice((0.125, 0.25, 0.5, 1.0))))
+        kv = int(rng.choice([k for k in range(1, heads + 1) if heads % k == 0]))
+        yield I.LayerShape(hidden, heads, d, 64 * int(rng.integers(max(1, hidden // 192), max(2, hidden // 20))), int(np.exp(rng.uniform(0, np.log(2500)))),
+                           int(rng.choice((1, 1, 2))), n_kv_heads=kv), bool(rng.random() < 0.7)
+
+
+def test_nothing_is_overwritten_before_its_last_reader():
+    for case in DEFERRING:
+        assert gemm_plans.defers(case[0], case[1])
+    assert not any(gemm_plans.defers(c[0], c[1]) for c in CASES if c[8] and c[:8] not in DEFERRING)
+    shapes = [(c[0], c[1]) for c in CASES if c[8]] + list(_random_shapes(300))
+    for shape, packed in shapes:
+        tensors, unit = stage_plans.side_tensors(shape, 2, packed)
+        ends = sorted(e for _, e in tensors.values())
+        assert ends[-1] <= unit, shape
+        defer = gemm_plans.defers(shape, packed) and stage_plans.side_by_side(shape, 2, 16, 16, packed) > 1
+        assert stage_plans.overwritten(tensors, stage_plans.backward_steps(defer)) == [], (shape, packed, defer)
+
+
+def test_the_check_finds_a_tensor_overwritten():
+    # a layer that does not defer, whose tensors are packed closer, run as if it did
+    tensors, _ = stage_plans.side_tensors(TINY, 2)
+    assert {t for _, t, _ in stage_plans.overwritten(tensors, stage_plans.backward_steps(True))} == {"m", "dgu"}
 
 
 def test_rule_leaves_out():
