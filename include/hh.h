@@ -207,9 +207,10 @@ int hh_stage_step(hh_ctx *ctx, const hh_layer_cfg *cfg, int n_layers, const hh_l
  * stage of rank r uses n_live = min(n_micro, P - r).  1 <= n_live <= n_micro;
  * n_live == n_micro is hh_stage_step.  Backward visits the micro-batches in
  * ascending order in both, so the results are bit-identical to hh_stage_step.
- * (Both calls take small micro-batches whose boundary buffers are all separate
- * through their launches side by side, up to 8 and up to n_live of them, forward
- * of all of these and then backward: the same results, no more of them alive.)
+ * (Where no two buffers overlap of which one is written, other than dx[m] and
+ * dy[m], both calls take small micro-batches through their launches side by
+ * side, up to 8 and up to n_live of them, forward of all of these and then
+ * backward: the same results, no more of them alive.)
  * y[m + n_live] is written while dy[m + 1 ...] are still to be read: y and dy
  * arrays must not share buffers across micro-batches. */
 int hh_stage_step_1f1b(hh_ctx *ctx, const hh_layer_cfg *cfg, int n_layers, const hh_layer_weights *w,

@@ -871,25 +871,44 @@ static Side side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weigh
     return pool > ws ? Side{pool, true, defers} : Side{ws, false, defers};
 }
 
-// Whether the micro-batches' boundary tensors are buffers of their own (dx[m] may be dy[m], in all of them or none): only then
-// does it not matter in which order micro-batches touch them.
-static bool separate_buffers(const Dims& d, int n, const void* const* x, void* const* y, const void* const* dy, void* const* dx) {
-    struct Buf { uintptr_t at; int kind; };   // 0: x, 1: y, 2: dy, 3: dx
-    const std::unique_ptr<Buf[]> v(new (std::nothrow) Buf[(size_t)4 * n]);
+// Whether it does not matter in which order micro-batches and layers touch the buffers of a call: none that is written overlaps
+// another one (but dx[m] may be dy[m], in all of them or none); inputs and weights may be shared, as wholes.
+static bool separate_buffers(const Dims& d, int k, const hh_layer_weights* w, const hh_layer_grads* g, int n, const void* const* x, void* const* y,
+                             const void* const* dy, void* const* dx, const StagePool& pool, int n_live, const void* workspace) {
+    enum { X, DY, WEIGHT, WRITTEN };   // only buffers of one of the first three kinds may be one buffer
+    struct Buf { uintptr_t at, end; int kind; };
+    const size_t most = 4 * (size_t)n + 18 * (size_t)k + 2;
+    const std::unique_ptr<Buf[]> v(new (std::nothrow) Buf[most]);
     if (!v) return false;
+    size_t count = 0;
+    auto add = [&](const void* p, size_t bytes, int kind) { v[count++] = {(uintptr_t)p, (uintptr_t)p + bytes, kind}; };
     const bool in_place = dx[0] == dy[0];
-    size_t k = 0;
+    const size_t act = (size_t)d.T * d.H * d.es;
     for (int m = 0; m < n; m++) {
         if ((dx[m] == dy[m]) != in_place) return false;
-        v[k++] = {(uintptr_t)x[m], 0}; v[k++] = {(uintptr_t)y[m], 1}; v[k++] = {(uintptr_t)dy[m], 2};
-        if (!in_place) v[k++] = {(uintptr_t)dx[m], 3};
+        add(x[m], act, X);
+        add(y[m], act, WRITTEN);
+        add(dy[m], act, in_place ? WRITTEN : DY);
+        if (!in_place) add(dx[m], act, WRITTEN);
     }
-    std::sort(v.get(), v.get() + k, [](const Buf& a, const Buf& b) { return a.at < b.at; });
-    const uintptr_t bytes = (uintptr_t)d.T * d.H * d.es;
-    for (size_t i = 1; i < k; i++) {   // all of one length: if any two overlap, two neighbours do
-        if (v[i].at - v[i - 1].at >= bytes) continue;
-        const bool shared_input = v[i].at == v[i - 1].at && v[i].kind == v[i - 1].kind && (v[i].kind == 0 || (v[i].kind == 2 && !in_place));
-        if (!shared_input) return false;
+    for (int l = 0; l < k; l++) {
+        auto layer = [&](const auto& q, size_t gain, size_t es, int kind) {
+            const size_t col = (size_t)d.H * es;
+            add(q.g_attn, gain, kind); add(q.g_mlp, gain, kind);
+            add(q.wq, d.A * col, kind); add(q.wk, d.Akv * col, kind); add(q.wv, d.Akv * col, kind); add(q.wo, d.A * col, kind);
+            add(q.w_gate, d.F * col, kind); add(q.w_up, d.F * col, kind); add(q.w_down, d.F * col, kind);
+        };
+        layer(w[l], d.H * d.es, d.es, WEIGHT);
+        layer(g[l], d.H * sizeof(float), sizeof(float), WRITTEN);
+    }
+    add(pool.base, pool.per_micro * (size_t)n_live, WRITTEN);
+    add(workspace, work_layout(d).total + act_bytes(d), WRITTEN);
+    std::sort(v.get(), v.get() + count, [](const Buf& a, const Buf& b) { return a.at < b.at; });
+    uintptr_t end = v[0].end;
+    for (size_t i = 1; i < count; i++) {
+        const bool one = v[i].at == v[i - 1].at && v[i].kind == v[i - 1].kind && v[i].kind != WRITTEN;
+        if (v[i].at < end && !one) return false;
+        end = std::max(end, v[i].end);
     }
     return true;
 }
@@ -918,8 +937,8 @@ static int stage_run(hh_ctx* ctx, const hh_layer_cfg* cfg, int n_layers, const h
     const StagePool p = stage_pool(d, n_layers, saved_pool);
     hipStream_t st = (hipStream_t)stream;
     const WorkLayout wl = work_layout(d);
-    const Side side = n_live > 1 && separate_buffers(d, n_micro, x, y, dy, dx) ? side_by_side(ctx, d, n_layers, w, g, n_live, workspace) : Side{1, false, false};
-    if (side.n > 1) {
+    const Side side = side_by_side(ctx, d, n_layers, w, g, n_live, workspace);
+    if (side.n > 1 && separate_buffers(d, n_layers, w, g, n_micro, x, y, dy, dx, p, n_live, workspace)) {
         const WorkLayout sl = side_layout(d, side.defers);
         const size_t unit = side_unit(d, side.defers);
         const int passes = (n_micro + side.n - 1) / side.n;
@@ -949,11 +968,12 @@ static int stage_run(hh_ctx* ctx, const hh_layer_cfg* cfg, int n_layers, const h
 
 // For tests, not part of the public interface: how many micro-batches such a call takes through its launches side by side.
 extern "C" int hh_internal_side_by_side(const hh_layer_cfg* cfg, int n_layers, const hh_layer_weights* w, const hh_layer_grads* g, int n_micro,
-                                        int n_live, const void* const* x, void* const* y, const void* const* dy, void* const* dx) {
+                                        int n_live, const void* const* x, void* const* y, const void* const* dy, void* const* dx, void* saved_pool,
+                                        void* workspace) {
     const Dims d = dims_of(cfg);
     hh_ctx ctx{0, nullptr, 0, 0, 0.f, {}, 0, false, 0u, nullptr, {}};
-    if (n_live < 2 || !separate_buffers(d, n_micro, x, y, dy, dx)) return 1;
-    return side_by_side(&ctx, d, n_layers, w, g, n_live, (void*)(uintptr_t)4096).n;
+    const int n = side_by_side(&ctx, d, n_layers, w, g, n_live, workspace).n;
+    return n > 1 && separate_buffers(d, n_layers, w, g, n_micro, x, y, dy, dx, stage_pool(d, n_layers, saved_pool), n_live, workspace) ? n : 1;
 }
 
 // Likewise: where the tensors of one of them lie (m, dgate|dup, d(hn), dh, da, dqkv, delta, partial dK and dV, gain partials, the

@@ -15,26 +15,31 @@ def boundary(s, es, n_micro, in_place=False, base=1 << 40):
 
 def _stage(s, n_layers, packed, bf16):
     """cfg and the layers' weights and gradients, at addresses of their own."""
-    es = 2 if bf16 else 4
     cfg = hh.make_cfg(s.hidden, s.n_heads, s.head_dim, s.ffn, s.seq, s.micro_batch, s.rms_eps, s.rope_base,
                       hh.HH_BF16 if bf16 else hh.HH_F32, n_kv_heads=s.kv_heads)
     rows = {"wq": s.attn, "wk": s.attn_kv, "wv": s.attn_kv, "w_gate": s.ffn, "w_up": s.ffn}
 
-    def layer(struct, es):
-        out, at = struct(), 1 << 36
+    def layer(struct, es, at):
+        out = struct()
         for n in NAMES:
             setattr(out, n, at)
-            at += rows[n] * s.hidden * es + (0 if packed else 256) if n in rows else 1 << 30
+            at += rows[n] * s.hidden * es + (0 if packed else 256) if n in rows else 1 << 32
         return out
-    ws = (hh.hh_layer_weights * n_layers)(*[layer(hh.hh_layer_weights, es)] * n_layers)
-    gs = (hh.hh_layer_grads * n_layers)(*[layer(hh.hh_layer_grads, 4)] * n_layers)
+    ws = (hh.hh_layer_weights * n_layers)(*[layer(hh.hh_layer_weights, 2 if bf16 else 4, (1 << 44) + (l << 36)) for l in range(n_layers)])
+    gs = (hh.hh_layer_grads * n_layers)(*[layer(hh.hh_layer_grads, 4, (1 << 45) + (l << 36)) for l in range(n_layers)])
     return cfg, ws, gs
 
 
-def side_by_side(s, n_layers, n_micro, n_live, packed=True, bf16=True, buffers=None):
+POOL, WORKSPACE = 1 << 46, 1 << 47
+
+
+def side_by_side(s, n_layers, n_micro, n_live, packed=True, bf16=True, buffers=None, change=None):
+    """change(weights, gradients): what to make of the layers' structs before."""
     cfg, ws, gs = _stage(s, n_layers, packed, bf16)
+    if change:
+        change(ws, gs)
     ptrs = [(C.c_void_p * n_micro)(*b) for b in buffers or boundary(s, 2 if bf16 else 4, n_micro)]
-    return hh.lib.hh_internal_side_by_side(C.byref(cfg), n_layers, ws, gs, n_micro, n_live, *ptrs)
+    return hh.lib.hh_internal_side_by_side(C.byref(cfg), n_layers, ws, gs, n_micro, n_live, *ptrs, C.c_void_p(POOL), C.c_void_p(WORKSPACE))
 
 
 TENSORS = ("m", "dgu", "dhn", "dh", "da", "dqkv", "dvec", "dkv_part", "partial", "gbuf")

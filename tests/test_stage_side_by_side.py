@@ -92,6 +92,53 @@ def test_rule_leaves_out():
                    dict(y=[y[0], y[0] + bytes_ - 16, y[2]]), dict(dy=x)):
         assert side(**shared) == 1, shared
     assert side(y=[y[0], y[0] + bytes_, y[2]]) == 3                                    # right behind one another
+    pool_b, ws_b = [hh_sizes(TINY, 1, 3)[i] for i in (0, 1)]
+    for inside in (stage_plans.POOL, stage_plans.POOL + pool_b - 256, stage_plans.WORKSPACE + ws_b - 256):
+        assert side(y=[y[0], inside, y[2]]) == 1 and side(dx=[dx[0], dx[1], inside]) == 1 and side(dy=[inside] + dy[1:]) == 1
+    assert side(y=[y[0], stage_plans.POOL + pool_b, stage_plans.WORKSPACE + ws_b]) == 3
+
+
+def hh_sizes(shape, layers, live):
+    from paper_2405_16256_amd import binding as hh
+    from paper_2405_16256_amd import glue as L
+    return hh.hh_stage_sizes(L.cfg_of(shape, True), layers, live)
+
+
+def _tie(*names, layers=(0, 1)):
+    def change(ws, gs):
+        for n in names:
+            setattr(gs[layers[1]], n, getattr(gs[layers[0]], n))
+    return change
+
+
+def test_rule_leaves_out_shared_gradients():
+    def side(change):
+        return stage_plans.side_by_side(TINY, 2, 3, 3, change=change)
+
+    def tied_weights(ws, gs):
+        for n in stage_plans.NAMES:
+            setattr(ws[1], n, getattr(ws[0], n))
+
+    def two_of_a_layer(ws, gs):
+        gs[0].g_mlp = gs[0].g_attn
+
+    def partly(ws, gs):
+        gs[1].wo = gs[0].w_down + 4 * 256 * 704 - 256
+
+    def behind(ws, gs):
+        gs[1].wo = gs[0].w_down + 4 * 256 * 704
+
+    def over_a_weight(ws, gs):
+        gs[0].g_mlp = ws[0].g_mlp
+
+    def input_is_a_weight(ws, gs):
+        ws[0].wq = stage_plans.boundary(TINY, 2, 3)[0][0]
+
+    def in_the_workspace(ws, gs):
+        gs[1].g_attn = stage_plans.WORKSPACE
+    assert side(None) == side(tied_weights) == side(behind) == 3
+    for change in (_tie(*stage_plans.NAMES), _tie("wo"), _tie("g_mlp"), two_of_a_layer, partly, over_a_weight, input_is_a_weight, in_the_workspace):
+        assert side(change) == 1, change
 
 
 def _stage(hh, L, ctx, cfg, layers, n_live, xs, ys, dys, dxs, zero_first):
@@ -151,4 +198,26 @@ def test_micro_batches_that_share_an_output_keep_their_order():
     assert torch.equal(y, ys[2]) and torch.equal(dx, dxs[2])
     for n in I.WEIGHT_NAMES:
         assert np.array_equal(L.to_np(layers[0].g[n]), L.to_np(ref[0].g[n])), n
+    hh.hh_ctx_destroy(ctx)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("names", [I.WEIGHT_NAMES, ("wo", "g_mlp")], ids=["all", "two"])
+@pytest.mark.parametrize("zero_first", [False, True])
+def test_layers_that_share_gradients_keep_their_order(names, zero_first):
+    from paper_2405_16256_amd import binding as hh
+    from paper_2405_16256_amd import glue as L
+    ctx = hh.hh_ctx_create(0)
+    cfg = L.cfg_of(TINY, True)
+    (layers, ref), xs, dys = _inputs(L, TINY, True, 2, 3)
+    out = []
+    for both, live in ((layers, 3), (ref, 1)):
+        for l in both:
+            for n in I.WEIGHT_NAMES:
+                l.g[n].fill_(0.75)
+        both[1].gstruct = hh.make_grads({n: both[0 if n in names else 1].g[n] for n in I.WEIGHT_NAMES})
+        ys, dxs = [torch.empty_like(t) for t in xs], [torch.empty_like(t) for t in xs]
+        _stage(hh, L, ctx, cfg, both, live, xs, ys, dys, dxs, zero_first)
+        out.append(dxs + [l.g[n] for l in both for n in I.WEIGHT_NAMES])
+    assert all(torch.equal(a, b) for a, b in zip(*out))
     hh.hh_ctx_destroy(ctx)
