@@ -30,7 +30,8 @@ def rel_err(got: np.ndarray, ref: np.ndarray) -> float:
 
 class DeviceLayer:
     """Device copies of one layer's parameters and fp32 gradient buffers.
-    packed=True keeps wq|wk|wv and w_gate|w_up (and their gradients) in single allocations."""
+    packed=True keeps wq|wk|wv and w_gate|w_up (and their gradients) in single allocations; packed=False leaves a gap behind each
+    tensor: the allocator may put separate ones right behind one another, and the library would take those for a single allocation."""
 
     def __init__(self, w: dict, s: I.LayerShape, bf16: bool, packed: bool = True):
         self.s, self.bf16 = s, bf16
@@ -51,11 +52,11 @@ class DeviceLayer:
             self._keep = (wqkv, wgu, gqkv, ggu)
         for n in hh.WEIGHT_FIELDS:
             src = to_dev(w[n], bf16)
-            if n in self.w:
-                self.w[n].copy_(src)
-            else:
-                self.w[n] = src
-                self.g[n] = torch.zeros(w[n].shape, dtype=torch.float32, device=DEV)
+            if n not in self.w:
+                gap = 256
+                self.w[n] = torch.empty(src.numel() + gap, dtype=dt, device=DEV)[:-gap].view(src.shape)
+                self.g[n] = torch.zeros(src.numel() + gap, dtype=torch.float32, device=DEV)[:-gap].view(src.shape)
+            self.w[n].copy_(src)
         self.wstruct = hh.make_weights(self.w)
         self.gstruct = hh.make_grads(self.g)
 

@@ -153,6 +153,10 @@ def _stage(hh, L, ctx, cfg, layers, n_live, xs, ys, dys, dxs, zero_first):
 
 def _inputs(L, shape, packed, k, M, bf16=True):
     layers = [[L.DeviceLayer(I.layer_weights(811, l, shape, bf16), shape, bf16, packed) for l in range(k)] for _ in range(2)]
+    for l in layers[0] + layers[1]:   # which GEMMs a layer has depends on whether these are one allocation
+        for t in (l.w, l.g):
+            for a, b in (("wq", "wk"), ("wk", "wv"), ("w_gate", "w_up")):
+                assert (t[a].data_ptr() + t[a].numel() * t[a].element_size() == t[b].data_ptr()) == packed, (a, b)
     acts = [I.activations(811, shape, m, bf16) for m in range(M)]
     return layers, [L.to_dev(a[0], bf16) for a in acts], [L.to_dev(a[1], bf16) for a in acts]
 
