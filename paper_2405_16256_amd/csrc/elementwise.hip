@@ -46,7 +46,8 @@ __device__ __forceinline__ void rmsnorm_fwd_body(T* __restrict__ x, const T* __r
     typedef typename Vec<T>::Raw Raw;
     __shared__ float red[NWAVES];
     const size_t base = (size_t)blockIdx.x * H;
-    const bool cached = H <= RC * TPB * V;
+    const bool cached = SPLIT || H <= RC * TPB * V;
+    static_assert(!SPLIT || SPLIT_COLUMNS <= RC * TPB * V, "a row of shares stays in registers");
     Raw keep[RC];
     float ss = 0.f;
     if (cached) {
@@ -69,13 +70,7 @@ __device__ __forceinline__ void rmsnorm_fwd_body(T* __restrict__ x, const T* __r
     } else {
         for (int c = threadIdx.x * V; c < H; c += TPB * V) {
             float f[V];
-            if constexpr (SPLIT) {
-                const Raw w = sum_shares(sp, n_micro, blockIdx.x, c, res + base + c);
-                *reinterpret_cast<Raw*>(x + base + c) = w;
-                Vec<T>::widen(w, f);
-            } else {
-                Vec<T>::load(x + base + c, f);
-            }
+            Vec<T>::load(x + base + c, f);
 #pragma unroll
             for (int e = 0; e < V; e++) ss += f[e] * f[e];
         }
@@ -144,6 +139,7 @@ struct NormBwd {
 // workgroups that norm them, which spares the launch that sums partial rows: up to GAIN_ROWS rows a micro-batch, beyond which
 // these workgroups would take longer than the others.  fp32 step of hidden 256, 128 tokens: 89.8 -> 87.9 us.
 constexpr int GAIN_ROWS = 256;
+constexpr int GAIN_COLUMNS = 6 * TPB * Vec<float>::N;
 template <typename T> struct Quad;
 template <> struct Quad<float> {
     __device__ static __forceinline__ float4 load(const float* p) { return *reinterpret_cast<const float4*>(p); }
@@ -475,7 +471,7 @@ static void rmsnorm_fwd_split(const GemmSplit& sp, const Each& res, const Each& 
 hipError_t rmsnorm_fwd(int dtype, const Each& x, const void* g, const Each& xn, const Each& r, int n, int T, int H, float eps,
                        hipStream_t st, const GemmSplit* split, const Each* res) {
     if (split) {
-        if (dtype != DT_BF16 || !res) return hipErrorInvalidValue;
+        if (dtype != DT_BF16 || !res || H > SPLIT_COLUMNS) return hipErrorInvalidValue;
         if (n == 1) rmsnorm_fwd_split<1>(*split, *res, x, g, xn, r, n, T, H, eps, st);
         else rmsnorm_fwd_split<MICRO_MAX>(*split, *res, x, g, xn, r, n, T, H, eps, st);
         return hipGetLastError();
@@ -619,7 +615,8 @@ __global__ __launch_bounds__(TPB, 2) void k_rmsnorm_bwd_rows_one(const T* __rest
 template <typename T, int NV, bool GUARD, int N>
 static hipError_t launch_rows(const NormBwd<N>& a, hipStream_t st) {
     const int lds = a.H * (int)sizeof(float);   // at most 48 KB
-    if constexpr (sizeof(T) == 2)
+    constexpr int FEWER = (NV - 1) * TPB * Vec<T>::N;   // columns, and rows have more than that
+    if constexpr (sizeof(T) == 2 && FEWER < SPLIT_COLUMNS)
         if (a.split.partial) {
             k_rmsnorm_bwd_rows<T, NV, GUARD, N, true><<<dim3(a.nblk, a.n), TPB, lds, st>>>(a);
             return hipGetLastError();
@@ -630,7 +627,7 @@ static hipError_t launch_rows(const NormBwd<N>& a, hipStream_t st) {
                                                                            (const T*)a.dres.p[0], (T*)a.dx.p[0], (float*)a.partial.p[0], a.T, a.H, a.rpb);
             return hipGetLastError();
         }
-    k_rmsnorm_bwd_rows<T, NV, GUARD, N, false><<<dim3(a.nblk + a.gain_blocks(), a.n), TPB, lds, st>>>(a);
+    if constexpr (N > 1 || FEWER < GAIN_COLUMNS) k_rmsnorm_bwd_rows<T, NV, GUARD, N, false><<<dim3(a.nblk + a.gain_blocks(), a.n), TPB, lds, st>>>(a);
     return hipGetLastError();
 }
 template <typename T, int NV, int N>
@@ -682,7 +679,6 @@ static hipError_t rmsnorm_bwd_t(const NormBwd<N>& a, hipStream_t st) {
         case 5: return whole ? launch_rows<T, 5, false>(a, st) : launch_rows<T, 5, true>(a, st);
         case 6: return whole ? launch_rows<T, 6, false>(a, st) : launch_rows<T, 6, true>(a, st);
     }
-    if (a.split.partial || a.gain) return hipErrorInvalidValue;   // a GEMM leaves its shares only for rows that stay in registers
     const int lds = a.H * (int)sizeof(float);
     static std::atomic<uint64_t> lds_ok{0};
     const hipError_t e = allow_lds((const void*)k_rmsnorm_bwd<T, N>, 32768 * (int)sizeof(float), lds_ok);
@@ -692,7 +688,7 @@ static hipError_t rmsnorm_bwd_t(const NormBwd<N>& a, hipStream_t st) {
 }
 
 // Not from shares: the columns' workgroups would have to add them up as well.
-bool rmsnorm_bwd_sums_gain(int T, int H, const GemmSplit* split) { return T <= GAIN_ROWS && H <= 6 * TPB * Vec<float>::N && !split; }
+bool rmsnorm_bwd_sums_gain(int T, int H, const GemmSplit* split) { return T <= GAIN_ROWS && H <= GAIN_COLUMNS && !split; }
 
 template <int N>
 static hipError_t rmsnorm_bwd_n(int dtype, const Each& dxn, const Each& x, const Each& r, const void* g, const Each& dres,
@@ -705,7 +701,8 @@ static hipError_t rmsnorm_bwd_n(int dtype, const Each& dxn, const Each& x, const
 }
 hipError_t rmsnorm_bwd(int dtype, const Each& dxn, const Each& x, const Each& r, const void* g, const Each& dres,
                        const Each& dx, const Each& partial, size_t partial_bytes, int n, int T, int H, hipStream_t st, const GemmSplit* split, float* gain, int accumulate) {
-    if (gain && split) return hipErrorInvalidValue;
+    if (split && (gain || dtype != DT_BF16 || H > SPLIT_COLUMNS)) return hipErrorInvalidValue;
+    if (gain && H > GAIN_COLUMNS) return hipErrorInvalidValue;
     return n == 1 ? rmsnorm_bwd_n<1>(dtype, dxn, x, r, g, dres, dx, partial, partial_bytes, n, T, H, st, split, gain, accumulate)
                   : rmsnorm_bwd_n<MICRO_MAX>(dtype, dxn, x, r, g, dres, dx, partial, partial_bytes, n, T, H, st, split, gain, accumulate);
 }

@@ -419,7 +419,7 @@ static hipError_t launch_dma(const GemmDesc* g, int n, hipStream_t st) {
 
 // Whether a problem's shares are left to the norm that reads its result, which then gathers them with one workgroup (or wave) a
 // row: not more than 64 KB a row, which takes it about as long as the reduction kernel's launch.
-static bool leaves_shares(const GemmDesc& g, int ksplit) { return (long)g.N * ksplit <= 16384 && g.N % 8 == 0; }
+static bool leaves_shares(const GemmDesc& g, int ksplit) { return (long)g.N * ksplit <= SPLIT_ROW && g.N % 8 == 0; }
 
 template <bool BWD, int MB, bool F, int BM, int BN, int WM, int WN, int NS>
 static hipError_t launch_ring_n(const GemmDesc* g, const int* order, const int* ksplit, int n, hipStream_t st) {

@@ -721,7 +721,7 @@ static int layer_bwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_la
     // The norms take the shares of d(hn) and d(xn) as they are where those are few, nothing else uses the scratch before, and the
     // norm has a workgroup for every row or two (333 rows of 1280 in 42 workgroups: 6.8 + 4.5 us, 10.7 with eight shares).
     GemmSplit left[3] = {};
-    if (dt == DT_BF16 && !defer && H <= 12288)
+    if (dt == DT_BF16 && !defer)
         for (int i = 0; i < 3; i += 2)
             if (2 * sums[i / 2].rows >= T) b.group[i][b.n[i] - 1].split = left + i;
     auto run_group = [&](int i) { return defer ? pgemm(ctx, p, dt, &b.group[i][b.n[i] - 1], 1, st) : pgemm(ctx, p, dt, b.group[i], b.n[i], st); };

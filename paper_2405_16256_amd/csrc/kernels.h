@@ -39,6 +39,8 @@ struct GemmFuse {
 // Partial sums of an NT or NN problem that its launch has left to the kernel that reads the result: fp32 tiles
 // [tile][micro-batch][share][bm*bn], to be added in the order of the shares (then the residual) and rounded.
 struct GemmSplit { const float* partial; int ksplit, bm, bn, tiles_n; };
+// The launch leaves at most SPLIT_ROW of them for a row, in two shares or more: rows of at most SPLIT_COLUMNS columns.
+constexpr int SPLIT_ROW = 16384, SPLIT_COLUMNS = SPLIT_ROW / 2;
 struct GemmDesc {
     int kind;
     int M, N, K;

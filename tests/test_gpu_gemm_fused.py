@@ -22,6 +22,9 @@ CASES = [
     (S(512, 32, 128, 64, 41, 1, n_kv_heads=1), True, (1, 1, 8, 1, 1, 8)),           # h from shares, of one tile row
     (S(2048, 16, 128, 1024, 300, 1, n_kv_heads=1), True, (1, 1, 1, 3, 3, 4)),         # two rows a workgroup
     (S(4096, 32, 128, 1024, 333, 1, n_kv_heads=1), True, (2, 4, 2, 4, 1, 2)),         # h from shares, larger tiles
+    (S(6144, 16, 128, 512, 17, 1, n_kv_heads=8), True, (3, 8, 2, 8, 1, 1)),           # the longest rows whose gains' gradients the norm sums itself
+    (S(6208, 16, 128, 512, 17, 1, n_kv_heads=8), True, (3, 8, 2, 8, 1, 1)),           # longer ones
+    (S(8192, 32, 128, 4096, 17, 1, n_kv_heads=8), True, (2, 2, 2, 3, 2, 1)),          # the longest rows of shares, both norms
 ]
 
 
