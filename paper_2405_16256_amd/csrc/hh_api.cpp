@@ -831,8 +831,9 @@ static int stage_bwd(hh_ctx* ctx, const Pass& ps, const Dims& d, int k, const hh
 // How many micro-batches (of at most n_live) go through the launches side by side: as many as there is room for, in buffers that
 // are sized for one after the other.  Side by side each has its own tensors (side_layout and the gradient between layers behind
 // them), one after the other where a single one has its tensors and the GEMMs' partial sums, or in the pool's slots that a pass
-// leaves free; the partial sums of all of them lie behind the tensors, or alone in the workspace.  Only where every GEMM goes to
-// the ring kernel, with the tile and split of a micro-batch by itself, which larger bf16 micro-batches do not.
+// leaves free; the partial sums of all of them lie behind the tensors, or alone in the workspace.  In bf16 only where every
+// GEMM goes to the ring kernel, with the tile and split of a micro-batch by itself, which larger micro-batches do not, or is a weight
+// gradient of so few tokens that the ring kernel forms the same bits.
 struct Side { int n; bool in_pool, defers; };
 static size_t side_unit(const Dims& d, bool defers) { return side_layout(d, defers).total + act_bytes(d); }
 static Side side_by_side(hh_ctx* ctx, const Dims& d, int k, const hh_layer_weights* w, const hh_layer_grads* g, int n_live, void* workspace) {

@@ -22,13 +22,13 @@ enum { GEMM_NT = 0, GEMM_NN = 1, GEMM_TN = 2 };
 // The operands of a problem that the launch repeats for several micro-batches (weight gradients: C is the same in all of
 // them and their products are added in the order of the micro-batches, each as a launch of its own would add it).
 struct GemmMicro { Each A, B, C, R, X, Y; };
-// What the ring kernel (bf16) can do with a product before it is written, in place of a launch of its own:
+// What a GEMM (in bf16 the ring kernel) can do with a product before it is written, in place of a launch of its own:
 //   FUSE_ROPE       NT, C = q|k|v rows or a part of them: the rotary embedding of the first `rot` columns, heads of `period`
 //   FUSE_SWIGLU     NT, C = gate|up rows [M, period]: X [M, period/2] = silu(gate) * up
 //   FUSE_SWIGLU_BWD NN, the product is dm [M, N]: with X = gate|up, C = m and Y = dgate|dup
-// Each on the product rounded to bf16, as the launch would read it.
+// Each on the product rounded to the storage type, as the launch would read it.
 enum { FUSE_NONE = 0, FUSE_ROPE, FUSE_SWIGLU, FUSE_SWIGLU_BWD };
-// The largest tile (rows x columns) on which the kernel does it.
+// The largest tile (rows x columns) on which the ring kernel does it.
 constexpr int fuse_tile(int kind) { return kind == FUSE_ROPE ? 192 * 128 : kind == FUSE_SWIGLU ? 128 * 128 : 64 * 128; }
 struct GemmFuse {
     int kind;
