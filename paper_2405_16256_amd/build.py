@@ -11,9 +11,11 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libhh.so")
 SOURCES = ["hh_api.cpp", "predictor.cpp", "elementwise.hip", "gemm_f32.hip", "gemm_bf16.hip", "attn_f32.hip", "attn_bf16.hip", "scratch.hip"]
-# packed fp32 instructions are kept out of the generated code on purpose
+# Packed fp32 instructions are kept out of the generated code on purpose.  The first 14 words of a kernel's arguments arrive in
+# registers instead of being loaded by every workgroup (a GEMM of 128x768x256: 3.40 -> 3.35 us, of 333x4096x4096 24.1 -> 23.3).
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=14",
+         "-Wno-unused-command-line-argument"]
 
 
 def _hipcc() -> str:

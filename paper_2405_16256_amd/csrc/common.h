@@ -70,6 +70,26 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
 }
 
+// ---- division of 0 <= n < 2^31 by a divisor that the launch knows: one high product ----
+// With 2^(l-1) < d <= 2^l and mul = ceil(2^(31+l) / d), floor(n mul / 2^(31+l)) is exact (Granlund and Montgomery, "Division by
+// invariant integers using multiplication", 1994).  A division of two numbers that only the kernel knows is a chain of about
+// 35 scalar instructions through a float reciprocal, a 64-bit one of more than 100: with seven of them (two of 64 bits) a GEMM
+// workgroup spent 1.0 us before it asked for its first operand.
+struct Divisor { int d; uint32_t mul; int shift; };
+inline Divisor divisor(int d) {
+    const int l = d > 1 ? 32 - __builtin_clz((unsigned)d - 1u) : 0;
+    return Divisor{d, (uint32_t)(((1ull << (31 + l)) + (uint64_t)d - 1) / (uint64_t)d), l};
+}
+__host__ __device__ __forceinline__ int quotient(int n, const Divisor& v) {
+    return (int)((uint32_t)((uint64_t)(2u * (uint32_t)n) * v.mul >> 32) >> v.shift);
+}
+// n becomes the quotient, the remainder is returned
+__device__ __forceinline__ int split_off(int& n, const Divisor& v) {
+    const int q = quotient(n, v), r = n - q * v.d;
+    n = q;
+    return r;
+}
+
 // ---- an operand's address in each of up to N micro-batches, as a kernel argument ----
 // N is 1 for a launch of one micro-batch: a table of one, whose entry is asked for with the other arguments, where an index
 // would have to be formed first (nine launches of a small layer's forward pass: 67.7 us, 70.7 with tables of 8).

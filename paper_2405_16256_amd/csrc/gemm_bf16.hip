@@ -63,20 +63,24 @@ struct DmaProblem {
     void* C;
     const bf16_t* R;
     uint32_t a_bytes, b_bytes;
-    int lda, ldb, ldc, ldr, M, N, accumulate, first;
+    int lda, ldb, ldc, ldr, M, N, accumulate;
+    TileMap map;
 };
 struct DmaGroup {
-    int n, K;
+    int first[DMA_MAX];   // first tile of each problem, INT_MAX behind the last one
+    int K;
+    Divisor ksplit;       // k shares of a tile of the last round
     DmaProblem p[DMA_MAX];
     __device__ __forceinline__ int problem_of(int tile) const {
         int i = 0;
-        while (i + 1 < n && tile >= p[i + 1].first) i++;
+#pragma unroll
+        for (int q = 1; q < DMA_MAX; q++) i += tile >= first[q];
         return i;
     }
 };
 
 template <int KIND, bool OUT_F32>
-__global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_items, int ksplit, float* __restrict__ partial) {
+__global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_items, float* __restrict__ partial) {
     // The workgroup walks work items blockIdx.x, + gridDim.x, ... < n_items.  Items below `full` are whole tiles
     // (all of k, written out through the epilogue).  Item full + q is the (q % ksplit)-th share of the k range of
     // tile full + q / ksplit; its fp32 sums go to partial[q][256][256] and k_splitk_reduce finishes those tiles.
@@ -99,16 +103,16 @@ __global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_
         int tix;
         if (item < full) { tix = item; kbeg = 0; nk = nk_all; slot = -1; }
         else {
-            const int q = item - full, chunk = q % ksplit;
-            tix = full + q / ksplit;
-            kbeg = (int)((long)chunk * nk_all / ksplit);
-            nk = (int)((long)(chunk + 1) * nk_all / ksplit) - kbeg;
-            slot = q;
+            int tile = slot = item - full;
+            const int chunk = split_off(tile, grp.ksplit);
+            tix = full + tile;
+            kbeg = quotient(chunk * nk_all, grp.ksplit);
+            nk = quotient((chunk + 1) * nk_all, grp.ksplit) - kbeg;
         }
         prob = grp.problem_of(tix);
         const DmaProblem& g = grp.p[prob];
         int tm, tn;
-        tile_of_index(tix - g.first, (g.M + DTILE - 1) / DTILE, (g.N + DTILE - 1) / DTILE, tm, tn);
+        g.map.tile(tix - grp.first[prob], tm, tn);
         m0 = tm * DTILE; n0 = tn * DTILE;
         const uint64_t pa = (uint64_t)g.A, pb = (uint64_t)g.B;
         rsA = i32x4{(int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), (int)g.a_bytes, 0x00020000};
@@ -314,14 +318,15 @@ __global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_
 // Sums the ksplit fp32 partial tiles of each split tile in a fixed order and applies the epilogue.
 // 64 workgroups per tile; a thread owns 4 consecutive columns of one row.
 template <bool OUT_F32>
-__global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__ partial, int ksplit, int block0, DmaGroup grp) {
+__global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__ partial, int block0, DmaGroup grp) {
     const int r = blockIdx.x >> 6, sub = blockIdx.x & 63;
-    const DmaProblem& g = grp.p[grp.problem_of(block0 + r)];
+    const int prob = grp.problem_of(block0 + r), ksplit = grp.ksplit.d;
+    const DmaProblem& g = grp.p[prob];
     const int M = g.M, N = g.N, ldc = g.ldc, ldr = g.ldr, accumulate = g.accumulate;
     void* const Cv = g.C;
     const bf16_t* const R = g.R;
     int tm, tn;
-    tile_of_index(block0 + r - g.first, (M + DTILE - 1) / DTILE, (N + DTILE - 1) / DTILE, tm, tn);
+    g.map.tile(block0 + r - grp.first[prob], tm, tn);
     const int q = sub * 256 + threadIdx.x;
     const int row = q >> 6, col = (q & 63) * 4;
     const float* p = partial + (size_t)r * ksplit * (DTILE * DTILE) + row * DTILE + col;
@@ -400,20 +405,23 @@ static hipError_t launch_dma(const GemmDesc* g, int n, hipStream_t st) {
     const int NUM_CU = device_cus(ce);
     if (ce != hipSuccess) return ce;
     DmaGroup grp{};
-    grp.n = n; grp.K = g[0].K;
+    grp.K = g[0].K;
     int tiles = 0;
+    for (int i = 0; i < DMA_MAX; i++) grp.first[i] = INT_MAX;
     for (int i = 0; i < n; i++) {
         const GemmDesc& q = g[i];
         grp.p[i] = DmaProblem{(const bf16_t*)q.A, (const bf16_t*)q.B, q.C, (const bf16_t*)q.R, (uint32_t)extent_a(q), (uint32_t)extent_b(q, q.K),
-                              q.lda, q.ldb, q.ldc, q.ldr, q.M, q.N, q.accumulate, tiles};
-        tiles += ((q.M + DTILE - 1) / DTILE) * ((q.N + DTILE - 1) / DTILE);
+                              q.lda, q.ldb, q.ldc, q.ldr, q.M, q.N, q.accumulate, tile_map(q.M, q.N, DTILE, DTILE)};
+        grp.first[i] = tiles;
+        tiles += grp.p[i].map.tiles();
     }
     const int ksplit = tail_shares(g[0], tiles, NUM_CU);
     const int tail = ksplit > 1 ? tiles % NUM_CU : 0, full = tiles - tail;
+    grp.ksplit = divisor(ksplit);
     // one launch: a persistent workgroup per CU walks the whole tiles and then the k shares of the tail tiles
     const int n_items = full + tail * ksplit;
-    kern<<<n_items < NUM_CU ? n_items : NUM_CU, 512, LDS, st>>>(grp, full, n_items, ksplit, (float*)g[0].ws);
-    if (tail > 0) k_splitk_reduce<OUT_F32><<<tail * 64, 256, 0, st>>>((const float*)g[0].ws, ksplit, full, grp);
+    kern<<<n_items < NUM_CU ? n_items : NUM_CU, 512, LDS, st>>>(grp, full, n_items, (float*)g[0].ws);
+    if (tail > 0) k_splitk_reduce<OUT_F32><<<tail * 64, 256, 0, st>>>((const float*)g[0].ws, full, grp);
     return hipGetLastError();
 }
 
@@ -421,18 +429,19 @@ static hipError_t launch_dma(const GemmDesc* g, int n, hipStream_t st) {
 // row: not more than 64 KB a row, which takes it about as long as the reduction kernel's launch.
 static bool leaves_shares(const GemmDesc& g, int ksplit) { return (long)g.N * ksplit <= SPLIT_ROW && g.N % 8 == 0; }
 
-template <bool BWD, int MB, bool F, int BM, int BN, int WM, int WN, int NS>
+template <bool BWD, int MB, bool F, int NP, int BM, int BN, int WM, int WN, int NS>
 static hipError_t launch_ring_n(const GemmDesc* g, const int* order, const int* ksplit, int n, hipStream_t st) {
     constexpr int LDS = NS * (BM + BN) * DK * 2;
     static std::atomic<uint64_t> lds_ok{0};
-    auto kern = k_gemm_ring<BWD, MB, F, BM, BN, WM, WN, NS>;
+    auto kern = k_gemm_ring<BWD, MB, F, NP, BM, BN, WM, WN, NS>;
     const hipError_t e = allow_lds((const void*)kern, LDS, lds_ok);
     if (e != hipSuccess) return e;
-    RingGroup<MB, F> grp{};
-    RingReduce<MB, F> red{};
-    grp.n = n;
-    red.bm = BM; red.bn = BN;
-    int first = 0, red_first = 0;
+    RingGroup<MB, F, NP> grp;
+    RingReduce<MB, F, NP> red;
+    red.bm = divisor(BM); red.bn = divisor(BN);
+    int starts[RING_MAX], red_starts[RING_MAX];
+    for (int i = 0; i < RING_MAX; i++) starts[i] = red_starts[i] = INT_MAX;
+    int first = 0, red_first = 0, n_red = 0, tn = 0;
     float* partial = (float*)g[0].ws;
     for (int i = 0; i < n; i++) {
         const GemmDesc& q = g[order[i]];
@@ -449,56 +458,65 @@ static hipError_t launch_ring_n(const GemmDesc* g, const int* order, const int* 
         p.kseg[0] = q.k1 ? q.k1 / DK : INT_MAX; p.kseg[1] = q.k2 ? q.k2 / DK : INT_MAX;
         p.Bseg[0] = (const bf16_t*)q.B1; p.Bseg[1] = (const bf16_t*)q.B2;
         p.a_bytes = (uint32_t)extent_a(q); p.b_bytes = (uint32_t)extent_b(q, q.k1 ? q.k1 : q.K);
-        p.kind = q.kind; p.lda = q.lda; p.ldb = q.ldb; p.ldc = q.ldc; p.ldr = q.ldr; p.M = q.M; p.N = q.N; p.K = q.K;
+        tn |= (q.kind == GEMM_TN) << i;
+        p.lda = q.lda; p.ldb = q.ldb; p.ldc = q.ldc; p.ldr = q.ldr; p.M = q.M; p.N = q.N; p.K = q.K;
         p.accumulate = q.accumulate;
-        p.tiles = ((q.M + BM - 1) / BM) * ((q.N + BN - 1) / BN);
-        p.ksplit = s;
+        p.map = tile_map(q.M, q.N, BM, BN);
+        p.nk = nk;
+        const int tiles = p.map.tiles();
+        p.tiles = divisor(tiles); p.items = divisor(tiles * s); p.ksplit = divisor(s);
         if constexpr (F) {
             const GemmFuse& f = q.fuse;
             for (int m = 0; m < MB; m++) {
                 p.X.p[m] = MB == 1 ? f.X : q.each->X.p[m];
                 p.Y.p[m] = MB == 1 ? f.Y : q.each->Y.p[m];
             }
-            p.fuse = f.kind; p.period = f.period; p.rot = f.rot; p.tokens = f.seq; p.table_seq = f.table_seq; p.table = f.table;
+            p.fuse = f.kind; p.period = f.period; p.rot = f.rot; p.tokens = divisor(f.seq > 0 ? f.seq : 1); p.table_seq = f.table_seq; p.table = f.table;
             p.shift = f.kind == FUSE_ROPE ? (f.period == 128 ? 7 : 6) : 31;
         }
-        p.first = first;
+        starts[i] = p.first = first;
         p.micro = q.micro;
         p.seq = q.kind == GEMM_TN && s == 1 ? q.micro : 1;
-        first += p.tiles * s * (q.micro / p.seq);
+        first += tiles * s * (q.micro / p.seq);
         if (q.split) *q.split = GemmSplit{nullptr, 1, BM, BN, (q.N + BN - 1) / BN};
+        p.partial = partial;
         if (s > 1) {
             if (nk < s) return hipErrorInvalidValue;
-            p.partial = partial;
-            partial += (size_t)p.tiles * s * q.micro * BM * BN;
+            partial += (size_t)tiles * s * q.micro * BM * BN;
             if (q.split && leaves_shares(q, s)) {
                 q.split->partial = p.partial;
                 q.split->ksplit = s;
                 continue;
             }
-            const int blocks = (int)(((long)q.M * (q.N / (q.fuse.kind == FUSE_ROPE || q.fuse.kind == FUSE_SWIGLU ? 8 : 4)) + 255) / 256);
-            auto& j = red.j[red.n++];
+            const int vectors = q.N / (q.fuse.kind == FUSE_ROPE || q.fuse.kind == FUSE_SWIGLU ? 8 : 4);
+            const int blocks = (int)(((long)q.M * vectors + 255) / 256);
+            red_starts[n_red] = red_first;
+            auto& j = red.j[n_red++];
+            j.first = red_first;
             static_cast<RingFuse<MB, F>&>(j) = p;
             j.C = p.C; j.R = p.R; j.partial = p.partial;
             j.ksplit = s; j.ldc = q.ldc; j.ldr = q.ldr; j.M = q.M; j.N = q.N; j.accumulate = q.accumulate; j.out_f32 = q.out_f32;
-            j.first = red_first; j.micro = q.micro; j.blocks = blocks;
+            j.micro = q.micro; j.tiles_n = p.map.tiles_n; j.blocks = divisor(blocks); j.vectors = divisor(vectors);
             red_first += blocks * (q.out_f32 ? 1 : q.micro);
         }
     }
-    kern<<<first, WM * WN * 64, LDS, st>>>(grp);
-    if (red.n) k_ring_reduce<MB, F><<<red_first, 256, 0, st>>>(red);
+    kern<<<first, WM * WN * 64, LDS, st>>>(starts[1], starts[2], starts[3], tn, grp);
+    if (n_red) k_ring_reduce<MB, F, NP><<<red_first, 256, 0, st>>>(red_starts[1], red_starts[2], red_starts[3], red);
     return hipGetLastError();
 }
 
+template <bool BWD, bool F, int BM, int BN, int WM, int WN, int NS>
+static hipError_t launch_ring_f(const GemmDesc* g, const int* order, const int* ksplit, int n, hipStream_t st) {
+    if (g[0].micro > 1) return launch_ring_n<BWD, MICRO_MAX, F, RING_MAX, BM, BN, WM, WN, NS>(g, order, ksplit, n, st);
+    return n == 1 ? launch_ring_n<BWD, 1, F, 1, BM, BN, WM, WN, NS>(g, order, ksplit, n, st)
+                  : launch_ring_n<BWD, 1, F, RING_MAX, BM, BN, WM, WN, NS>(g, order, ksplit, n, st);
+}
 template <bool BWD, int BM, int BN, int WM, int WN, int NS>
 static hipError_t launch_ring(const GemmDesc* g, const int* order, const int* ksplit, int n, hipStream_t st) {
     constexpr bool CAN = BM * BN <= (BWD ? fuse_tile(FUSE_SWIGLU_BWD) : fuse_tile(FUSE_ROPE));
     if constexpr (CAN)
-        if (g[0].fuse.kind)
-            return g[0].micro == 1 ? launch_ring_n<BWD, 1, true, BM, BN, WM, WN, NS>(g, order, ksplit, n, st)
-                                   : launch_ring_n<BWD, MICRO_MAX, true, BM, BN, WM, WN, NS>(g, order, ksplit, n, st);
-    return g[0].micro == 1 ? launch_ring_n<BWD, 1, false, BM, BN, WM, WN, NS>(g, order, ksplit, n, st)
-                           : launch_ring_n<BWD, MICRO_MAX, false, BM, BN, WM, WN, NS>(g, order, ksplit, n, st);
+        if (g[0].fuse.kind) return launch_ring_f<BWD, true, BM, BN, WM, WN, NS>(g, order, ksplit, n, st);
+    return launch_ring_f<BWD, false, BM, BN, WM, WN, NS>(g, order, ksplit, n, st);
 }
 
 // Which kernel, tile and k split: the smallest predicted time over the variants below.  A launch of W workgroups runs
@@ -913,6 +931,8 @@ extern "C" int hh_internal_gemm_plan(const int* problems, int n, char* out, size
     }
     return 0;
 }
+// n / d as the kernels form it
+extern "C" int hh_internal_quotient(int n, int d) { return hh::quotient(n, hh::divisor(d)); }
 // Whether the weight gradients of a layer are left to one launch at the end: the problems of its three groups, n of each.
 extern "C" int hh_internal_gemm_defer(const int* problems, const int* n) {
     using namespace hh;

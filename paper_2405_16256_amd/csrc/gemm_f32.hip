@@ -15,6 +15,7 @@
 // Rings of two stages on full launches, so that ten workgroups of 32x32 (five of 64x64) share a CU and their barriers and loads overlap:
 // 700x1536x1024 NT 30.0 us with four stages, 27.7 with two; 2048x8192x1024 329 and 270; eight are slower still.
 #include <algorithm>
+#include <climits>
 #include <utility>
 
 #include "gemm_tile.h"
@@ -74,6 +75,7 @@ template <>
 struct F32Fuse<true> {
     GemmFuse fuse;
     int shift;
+    Divisor tokens;   // of a sample
 };
 // MB: 1 or MICRO_MAX micro-batches, as in gemm_ring.h: NT and NN problems own that many times the workgroups, a workgroup of a TN
 // one adds the products of all of them, in order, to the gradient it reads and writes once.
@@ -81,7 +83,9 @@ template <bool F, int MB>
 struct F32Problem : F32Fuse<F> {
     Ops<MB> A, B, C, R, X, Y;
     uint32_t a_bytes, b_bytes;
-    int kind, lda, ldb, ldc, ldr, M, N, K, accumulate, tiles, first, micro;
+    int kind, lda, ldb, ldc, ldr, M, N, K, accumulate, first, micro;
+    TileMap map;
+    Divisor tiles;   // of a micro-batch
 };
 template <bool F, int MB>
 struct F32Group {
@@ -90,7 +94,7 @@ struct F32Group {
 };
 
 template <int KIND, int BT, int NS, bool F, int MB>
-__device__ __forceinline__ void f32_body(const F32Problem<F, MB>& g) {
+__device__ __forceinline__ void f32_body(const F32Problem<F, MB>& g, int item) {   // item: workgroup of the problem
     constexpr bool A_KC = KIND != GEMM_TN, B_KC = KIND == GEMM_NT;
     using TA = FTile<A_KC, BT>;
     using TB = FTile<B_KC, BT>;
@@ -99,14 +103,14 @@ __device__ __forceinline__ void f32_body(const F32Problem<F, MB>& g) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int M = g.M, N = g.N, K = g.K, lda = g.lda, ldb = g.ldb, ldc = g.ldc, ldr = g.ldr, accumulate = g.accumulate;
     const uint32_t a_bytes = g.a_bytes, b_bytes = g.b_bytes;
-    const int item = (int)blockIdx.x - g.first, micro = MB == 1 ? 0 : item / g.tiles;
+    int micro = 0;
+    if (MB > 1) { micro = item; item = split_off(micro, g.tiles); }
     const int seq = KIND == GEMM_TN && MB > 1 ? g.micro : 1;   // products summed here
     const float* const R = (const float*)g.R.at(micro);
     float* const C = (float*)g.C.at(micro);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, hf = lane >> 5;
-    const int tiles_n = (N + BT - 1) / BT;
     int tm, tn;
-    tile_of_index(item - micro * g.tiles, (M + BT - 1) / BT, tiles_n, tm, tn);
+    g.map.tile(item, tm, tn);
     const int m0 = tm * BT, n0 = tn * BT;
     const int wm = KG == 1 ? (wave >> 1) * 32 : 0, wn = KG == 1 ? (wave & 1) * 32 : 0;
     const int nk = (K + FK - 1) / FK;
@@ -209,7 +213,8 @@ __device__ __forceinline__ void f32_body(const F32Problem<F, MB>& g) {
                         *reinterpret_cast<float4*>((float*)g.X.at(micro) + (size_t)m * half + col) =
                             make_float4(swiglu(a[0], b[0]), swiglu(a[1], b[1]), swiglu(a[2], b[2]), swiglu(a[3], b[3]));
                 } else if (block < g.fuse.rot) {
-                    const float* cs = g.fuse.table + (size_t)(m % g.fuse.seq) * half + (col & (g.fuse.period - 1));
+                    int sample = m;
+                    const float* cs = g.fuse.table + (size_t)split_off(sample, g.tokens) * half + (col & (g.fuse.period - 1));
                     const float4 c4 = *reinterpret_cast<const float4*>(cs), s4 = *reinterpret_cast<const float4*>(cs + (size_t)g.fuse.table_seq * half);
                     const float c[4] = {c4.x, c4.y, c4.z, c4.w}, sn[4] = {s4.x, s4.y, s4.z, s4.w};
 #pragma unroll
@@ -252,15 +257,14 @@ __device__ __forceinline__ void f32_body(const F32Problem<F, MB>& g) {
     }
 }
 
-// BWD: NN and TN problems, otherwise NT
+// BWD: NN and TN problems (bit i of `tn`: problem i is TN), otherwise NT
 template <bool BWD, int BT, int NS, bool F, int MB>
-__global__ __launch_bounds__(256) void k_gemm_f32(F32Group<F, MB> grp) {
-    int i = 0;
-    while (i + 1 < grp.n && (int)blockIdx.x >= grp.p[i + 1].first) i++;
+__global__ __launch_bounds__(256) void k_gemm_f32(int second, int third, int fourth, int tn, F32Group<F, MB> grp) {
+    const int i = own_problem(Firsts{second, third, fourth}), item = (int)blockIdx.x - grp.p[i].first;
     const F32Problem<F, MB>& g = grp.p[i];
-    if (!BWD) f32_body<GEMM_NT, BT, NS, F, MB>(g);
-    else if (F || g.kind == GEMM_NN) f32_body<GEMM_NN, BT, NS, F, MB>(g);
-    else f32_body<GEMM_TN, BT, NS, F, MB>(g);
+    if (!BWD) f32_body<GEMM_NT, BT, NS, F, MB>(g, item);
+    else if (F || !(tn >> i & 1)) f32_body<GEMM_NN, BT, NS, F, MB>(g, item);
+    else f32_body<GEMM_TN, BT, NS, F, MB>(g, item);
 }
 
 template <bool BWD, int BT, int NS, bool F, int MB>
@@ -268,14 +272,17 @@ static hipError_t launch(F32Group<F, MB>& grp, hipStream_t st) {
     constexpr int LDS = NS * 2 * BT * FK * 4;
     static_assert(LDS >= 4 * 4096, "the epilogue patches reuse the ring");
     static_assert(LDS <= 48 * 1024, "no raised LDS limit");
-    int first = 0;
+    int first = 0, tn = 0, starts[F32_MAX];
+    for (int i = 0; i < F32_MAX; i++) starts[i] = INT_MAX;
     for (int i = 0; i < grp.n; i++) {
         F32Problem<F, MB>& p = grp.p[i];
-        p.tiles = ((p.M + BT - 1) / BT) * ((p.N + BT - 1) / BT);
-        p.first = first;
-        first += p.tiles * (p.kind == GEMM_TN ? 1 : p.micro);
+        p.map = tile_map(p.M, p.N, BT, BT);
+        p.tiles = divisor(p.map.tiles());
+        starts[i] = p.first = first;
+        tn |= (p.kind == GEMM_TN) << i;
+        first += p.map.tiles() * (p.kind == GEMM_TN ? 1 : p.micro);
     }
-    k_gemm_f32<BWD, BT, NS, F, MB><<<first, 256, LDS, st>>>(grp);
+    k_gemm_f32<BWD, BT, NS, F, MB><<<first, 256, LDS, st>>>(starts[1], starts[2], starts[3], tn, grp);
     return hipGetLastError();
 }
 
@@ -338,6 +345,7 @@ static hipError_t gemm_f32_f(const GemmDesc* d, int n, hipStream_t st) {
             if (f.kind == FUSE_SWIGLU && (g.kind != GEMM_NT || f.period != g.N || g.N % 32 || !f.X)) return hipErrorInvalidValue;
             if (f.kind == FUSE_SWIGLU_BWD && (g.kind != GEMM_NN || n != 1 || !f.X || !f.Y)) return hipErrorInvalidValue;
             p.fuse = f;
+            p.tokens = divisor(f.seq > 0 ? f.seq : 1);
             p.shift = f.kind == FUSE_ROPE ? (f.period == 128 ? 7 : 6) : 31;
         }
     }

@@ -43,7 +43,8 @@ struct RingFuse {};
 template <int MB>
 struct RingFuse<MB, true> {
     Ops<MB> X, Y;
-    int fuse, period, shift, rot, tokens, table_seq;   // tokens of a sample
+    int fuse, period, shift, rot, table_seq;
+    Divisor tokens;            // of a sample
     const float* table;
 };
 template <int MB, bool F>     // MB: how many micro-batches a launch may stand for, 1 or MICRO_MAX
@@ -53,16 +54,22 @@ struct RingProblem : RingFuse<MB, F> {
     float* partial;            // k shares: [tile][micro-batch][share][BM*BN] fp32 sums
     uint32_t a_bytes, b_bytes; // extent of A, and of B up to the first segment's end
     int kseg[2];
-    int kind, lda, ldb, ldc, ldr, M, N, K, accumulate, tiles, ksplit, first, micro, seq;
+    int lda, ldb, ldc, ldr, M, N, K, accumulate, first, micro, seq, nk;   // nk: k tiles
+    TileMap map;
+    Divisor items, tiles, ksplit;   // workgroups of a micro-batch, of a share; shares
 };
-template <int MB, bool F>
+// NP: how many problems a launch may have, RING_MAX or 1 where MB is: what a launch costs the host grows with its arguments.
+template <int MB, bool F, int NP>
 struct RingGroup {
-    int n;
-    RingProblem<MB, F> p[RING_MAX];
+    RingProblem<MB, F> p[NP];
 };
 
 template <int KIND, int MB, bool F, int BM, int BN, int WM, int WN, int NS>
 __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
+    // what the first operand requests need, loaded at once
+    asm volatile("" ::"s"(g.A.p[0]), "s"(g.B.p[0]), "s"(g.a_bytes), "s"(g.b_bytes), "s"(g.lda), "s"(g.ldb), "s"(g.first), "s"(g.nk),
+                 "s"(g.map.tiles_m), "s"(g.map.tiles_n), "s"(g.map.width.d), "s"(g.map.width.mul), "s"(g.map.width.shift), "s"(g.map.last.d),
+                 "s"(g.map.last.mul), "s"(g.map.last.shift), "s"(g.tiles.d), "s"(g.tiles.mul), "s"(g.tiles.shift), "s"(g.ksplit.mul), "s"(g.ksplit.shift));
     constexpr bool OUT_F32 = KIND == GEMM_TN;
     constexpr int NW = WM * WN;
     using DA = DmaTile<(KIND != GEMM_TN), BM, NW>;
@@ -73,22 +80,22 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
     constexpr int PW = DA::PER_WAVE + DB::PER_WAVE;       // DMA instructions per wave and stage
     static_assert(NS * STAGE >= NW * 4096, "the epilogue patches reuse the ring");
     extern __shared__ __attribute__((aligned(1024))) char smem[];   // [stage][A | B]
-    const int M = g.M, N = g.N, K = g.K, lda = g.lda, ldb = g.ldb, ldc = g.ldc, ldr = g.ldr, tiles = g.tiles, ksplit = g.ksplit;
+    const int M = g.M, N = g.N, K = g.K, lda = g.lda, ldb = g.ldb, ldc = g.ldc, ldr = g.ldr, ksplit = g.ksplit.d;
     bool accumulate = g.accumulate != 0;
 
-    const int item = (int)blockIdx.x - g.first;
-    const int micro = MB == 1 ? 0 : item / (tiles * ksplit), rest = item - micro * (tiles * ksplit);
-    const int share = rest / tiles, tix = rest - share * tiles;
+    int micro = 0, share = (int)blockIdx.x - g.first, tix = share;
+    if (MB > 1) { micro = share; tix = share = split_off(micro, g.items); }
+    tix = split_off(share, g.tiles);
     const bf16_t* const R = (const bf16_t*)g.R.at(micro);
     void* const Cv = g.C.at(micro);
     constexpr bool SUMS = KIND == GEMM_TN && MB > 1;
     const int seq = SUMS ? g.seq : 1;   // products summed here
-    const int tiles_n = (N + BN - 1) / BN;
+    const int tiles_n = g.map.tiles_n;
     int tm, tn;
-    tile_of_index(tix, (M + BM - 1) / BM, tiles_n, tm, tn);
+    g.map.tile(tix, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
-    const int nk_all = (K + DK - 1) / DK;
-    const int kbeg = (int)((long)share * nk_all / ksplit), nk = (int)((long)(share + 1) * nk_all / ksplit) - kbeg;
+    const int nk_all = g.nk;
+    const int kbeg = quotient(share * nk_all, g.ksplit), nk = quotient((share + 1) * nk_all, g.ksplit) - kbeg;
     const int nt = nk * seq;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, hf = lane >> 5;
     const int wm = (wave / WN) * (BM / WM), wn = (wave % WN) * (BN / WN);
@@ -366,7 +373,7 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
     for (int i = 0; i < TM; i++) {
         int pos = 0;
         if constexpr (KIND == GEMM_NT && FUSES)
-            if (fuse == FUSE_ROPE) pos = (m0 + wm + 32 * i + r_w) % g.tokens;
+            if (fuse == FUSE_ROPE) { int sample = m0 + wm + 32 * i + r_w; pos = split_off(sample, g.tokens); }
 #pragma unroll
         for (int j = 0; j < TN; j++) {
             const int block = n0 + wn + 32 * j;
@@ -466,45 +473,47 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
     }
 }
 
-// BWD: NN and TN problems, otherwise NT
-template <bool BWD, int MB, bool F, int BM, int BN, int WM, int WN, int NS>
-__global__ __launch_bounds__(WM * WN * 64, BM * BN / (WM * WN) > 64 * 128 ? 1 : 2) void k_gemm_ring(RingGroup<MB, F> grp) {
-    int i = 0;
-    while (i + 1 < grp.n && (int)blockIdx.x >= grp.p[i + 1].first) i++;
+// BWD: NN and TN problems (bit i of `tn`: problem i is TN), otherwise NT
+template <bool BWD, int MB, bool F, int NP, int BM, int BN, int WM, int WN, int NS>
+__global__ __launch_bounds__(WM * WN * 64, BM * BN / (WM * WN) > 64 * 128 ? 1 : 2) void k_gemm_ring(int second, int third, int fourth, int tn,
+                                                                                                RingGroup<MB, F, NP> grp) {
+    const int i = NP == 1 ? 0 : own_problem(Firsts{second, third, fourth});
     const RingProblem<MB, F>& g = grp.p[i];
     if (!BWD) ring_body<GEMM_NT, MB, F, BM, BN, WM, WN, NS>(g);
-    else if (F || g.kind == GEMM_NN) ring_body<GEMM_NN, MB, F, BM, BN, WM, WN, NS>(g);
+    else if (F || !(tn >> i & 1)) ring_body<GEMM_NN, MB, F, BM, BN, WM, WN, NS>(g);
     else ring_body<GEMM_TN, MB, F, BM, BN, WM, WN, NS>(g);
 }
 
 // Sums the ksplit fp32 shares of every BM x BN tile of the group's split problems in a fixed order and applies the
 // epilogue.  A thread owns 4 consecutive columns of one row of C: of one micro-batch's (NT, NN), or of the gradient, to
 // which it adds the micro-batches' products one after the other.
-template <int MB, bool F>
+template <int MB, bool F, int NP>
 struct RingReduce {
     struct Job : RingFuse<MB, F> {
         Ops<MB> C, R;
         const float* partial;
-        int ksplit, ldc, ldr, M, N, accumulate, out_f32, first, micro, blocks;   // blocks: workgroups of one micro-batch
-    } j[RING_MAX];
-    int n, bm, bn;
+        int ksplit, ldc, ldr, M, N, accumulate, out_f32, micro, tiles_n, first;
+        Divisor blocks, vectors;   // workgroups of one micro-batch; threads of a row
+    } j[NP];
+    Divisor bm, bn;
 };
-template <int MB, bool F>
-__global__ __launch_bounds__(256) void k_ring_reduce(RingReduce<MB, F> grp) {
-    int i = 0;
-    while (i + 1 < grp.n && (int)blockIdx.x >= grp.j[i + 1].first) i++;
-    const typename RingReduce<MB, F>::Job& j = grp.j[i];
+template <int MB, bool F, int NP>
+__global__ __launch_bounds__(256) void k_ring_reduce(int second, int third, int fourth, RingReduce<MB, F, NP> grp) {
+    const int i = NP == 1 ? 0 : own_problem(Firsts{second, third, fourth});
+    const typename RingReduce<MB, F, NP>::Job& j = grp.j[i];
     const int fuse = [&] { if constexpr (F) return j.fuse; else return (int)FUSE_NONE; }();
     const bool pairs = fuse == FUSE_ROPE || fuse == FUSE_SWIGLU;   // 4 columns and their 4 partners, 16 further in the tiles
-    const int bm = grp.bm, bn = grp.bn, vpr = j.N / (pairs ? 8 : 4);
-    const int micro = MB == 1 ? 0 : ((int)blockIdx.x - j.first) / j.blocks, micros = MB == 1 ? 1 : j.micro;
-    const long idx = (long)((int)blockIdx.x - j.first - micro * j.blocks) * 256 + threadIdx.x;
-    if (idx >= (long)j.M * vpr) return;
-    const int m = (int)(idx / vpr), v4 = (int)(idx - (long)m * vpr);
+    const int bm = grp.bm.d, bn = grp.bn.d;
+    const int micros = MB == 1 ? 1 : j.micro;
+    int micro = 0, m = (int)blockIdx.x - j.first;
+    if (MB > 1) { micro = m; m = split_off(micro, j.blocks); }
+    m = m * 256 + (int)threadIdx.x;   // below 2^31: M rows of up to 65535 columns are checked to be under 2 GB
+    const int v4 = split_off(m, j.vectors);
+    if (m >= j.M) return;
     const int n = pairs ? (v4 >> 2) * 32 + (v4 & 3) * 4 : v4 * 4;
-    const int tiles_n = (j.N + bn - 1) / bn;
-    const int tm = m / bm, tn = n / bn;
-    const float* p = j.partial + ((size_t)(tm * tiles_n + tn) * micros + micro) * j.ksplit * (bm * bn) + (m - tm * bm) * bn + (n - tn * bn);
+    int tm = m, tn = n;
+    const int row = split_off(tm, grp.bm), col_in = split_off(tn, grp.bn);
+    const float* p = j.partial + ((size_t)(tm * j.tiles_n + tn) * micros + micro) * j.ksplit * (bm * bn) + row * bn + col_in;
     auto shares = [&](float (&v)[4]) {   // the next ksplit shares
         for (int c = 0; c < j.ksplit; c++, p += bm * bn) {
             const float4 t = *reinterpret_cast<const float4*>(p);
@@ -539,7 +548,8 @@ __global__ __launch_bounds__(256) void k_ring_reduce(RingReduce<MB, F> grp) {
                 o.y = pack_bf2(swiglu(v[2], u[2]), swiglu(v[3], u[3]));
                 *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(j.X.at(micro)) + (size_t)m * half + col) = o;
             } else if (n < j.rot) {
-                const float* cs = j.table + (size_t)(m % j.tokens) * half + (col & (j.period - 1));
+                int sample = m;
+                const float* cs = j.table + (size_t)split_off(sample, j.tokens) * half + (col & (j.period - 1));
                 const float* sn = cs + (size_t)j.table_seq * half;
 #pragma unroll
                 for (int e = 0; e < 4; e++) rotate_pair(v[e], u[e], cs[e], sn[e]);

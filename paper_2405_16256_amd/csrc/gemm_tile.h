@@ -8,18 +8,38 @@ namespace hh {
 // Workgroup -> tile mapping.  Consecutive workgroup ids land on different XCDs
 // (8 of them, each with its own L2), so ids are first regrouped per XCD and each
 // XCD then walks a compact block of tiles, GROUP_M tile rows at a time.
-__device__ __forceinline__ void tile_of_index(int id, int tiles_m, int tiles_n, int& tm, int& tn) {
-    const int nb = tiles_m * tiles_n;
-    const int per = nb >> 3;
-    if (id < per * 8) id = (id & 7) * per + (id >> 3);
-    constexpr int GROUP_M = 8;
-    const int width = GROUP_M * tiles_n;
-    const int grp = id / width;
-    const int first_m = grp * GROUP_M;
-    const int gsz = min(tiles_m - first_m, GROUP_M);
-    const int within = id - grp * width;
-    tm = first_m + within % gsz;
-    tn = within / gsz;
+constexpr int GROUP_M = 8;
+struct TileMap {
+    int tiles_m, tiles_n;
+    Divisor width, last;   // tiles of a whole group of rows; rows of the last, smaller one
+    int tiles() const { return tiles_m * tiles_n; }
+    // Without a branch, so that the fields are loaded together and not each group of them behind the branch before it.
+    __device__ __forceinline__ void tile(int id, int& tm, int& tn) const {
+        const int per = (tiles_m * tiles_n) >> 3, there = (id & 7) * per + (id >> 3);
+        id = id < per * 8 ? there : id;
+        const int within = split_off(id, width);   // id: the group
+        const int first_m = id * GROUP_M;
+        const bool whole = tiles_m - first_m >= GROUP_M;
+        const Divisor rows = {whole ? GROUP_M : last.d, whole ? 1u << 31 : last.mul, whole ? 3 : last.shift};
+        tn = within;
+        tm = first_m + split_off(tn, rows);
+    }
+};
+inline TileMap tile_map(int M, int N, int bm, int bn) {
+    const int tiles_m = (M + bm - 1) / bm, tiles_n = (N + bn - 1) / bn;
+    return TileMap{tiles_m, tiles_n, divisor(GROUP_M * tiles_n), divisor(tiles_m % GROUP_M ? tiles_m % GROUP_M : GROUP_M)};
+}
+
+// Which of up to four problems a workgroup belongs to, from the first workgroup of the second, third and fourth (INT_MAX: no
+// such problem).  The index is hidden from the compiler, which otherwise chooses between the addresses of every single field
+// instead of loading the problem's fields from one base, up to 16 words at a time.
+struct Firsts { int second, third, fourth; };
+__device__ __forceinline__ int own_problem(const Firsts& f) {
+    const int b = (int)blockIdx.x;
+    auto from = [&](int first) { return (int)((uint32_t)(first - 1 - b) >> 31); };   // b >= first
+    int i = from(f.second) + from(f.third) + from(f.fourth);
+    asm("" : "+s"(i));
+    return i;
 }
 
 // The rotary embedding and SwiGLU combine columns far apart: (c, c + period/2) of a head or of a gate|up row.  A GEMM that
