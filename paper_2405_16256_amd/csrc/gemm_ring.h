@@ -168,7 +168,10 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
         issue_part(slot, std::integral_constant<int, -1>{});
     };
     // The memory pipe takes 16 cycles over a DMA instruction of 1 KB, and a wave whose instruction has to wait for it issues
-    // no MFMA meanwhile.  NT problems on the larger tiles spread the instructions that refill a slot over the four k steps
+    // no MFMA and no fragment read meanwhile.  So the requests that refill a slot come behind the next k tile's first fragment
+    // reads and the MFMAs that need no others (64x64 tiles: behind the third of four): in front of them, 700x1024x1024 took 7.0 us
+    // (NN) and 7.2 (NT with residual) where it takes 6.4 and 6.8, 333x4096x4096 NN 25.7 (24.6), 200x2048x2048 10.2 (9.7).
+    // NT problems on the larger tiles spread the instructions that refill a slot over the four k steps
     // that follow its release, a quarter behind each step's MFMAs: 333x22016x4096 (192x192 tiles) 81 -> 72 us, 333x12288x4096
     // (192x128) 52 -> 50, 333x4096x4096 (128x128) 24.2 -> 23.1.  Not with two stages, where the tile would be waited for right
     // after its last quarter (3300x8192x4096, 192x256 tiles: 87 -> 106), not on the smallest tiles, whose loops are short
@@ -257,11 +260,15 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             __builtin_amdgcn_sched_barrier(0);
-            if (kt + NS < nt) issue(slot);
             const bool more = kt + 1 < nt;
+            if (more) {
+#pragma unroll
+                for (int kk = 0; kk < 4; kk++) fetch(Q, next, kk);
+            }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int kk = 0; kk < 4; kk++) {
-                if (more) fetch(Q, next, kk);
+                if (kk == 3 && kt + NS < nt) issue(slot);
 #pragma unroll
                 for (int i = 0; i < TM; i++)
 #pragma unroll
@@ -318,9 +325,11 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
             __builtin_amdgcn_sched_barrier(0);
             refill = kt + NS < nt;
             if (refill) next_tile();
-            if (!SPREAD && refill) issue_part(slot, std::integral_constant<int, -1>{});
             if (kt + 1 < nt) fetch(0, next, 0);
+            __builtin_amdgcn_sched_barrier(0);
             mma(1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (!SPREAD && refill) issue_part(slot, std::integral_constant<int, -1>{});
             if (SPREAD && refill) issue_part(slot, std::integral_constant<int, 0>{});
             __builtin_amdgcn_sched_barrier(0);
             fold();
