@@ -32,8 +32,7 @@ namespace hh {
 // Fused problems (GemmFuse): the workgroup's columns come in pair_column's order, so that an accumulator lane owns a column
 // and its partner, 4q + e and 4(q + 2) + e of a block.  C is written back in its own order, in runs of 16 columns.  Bound by launch
 // latency, of which two launches of nine forward and one of ten backward go: forward of hidden 1024, 700 tokens 67.6 -> 65.9 us,
-// of hidden 512, 48 tokens 35.6 -> 34.1.  (Cosines asked for before the k loop, so that they need not be waited for behind it,
-// hold up the first tiles: 67.0.)
+// of hidden 512, 48 tokens 35.6 -> 34.1.
 constexpr int RING_MAX = 4;
 // rounded to bf16
 __device__ __forceinline__ float as_bf(float v) { return lo_bf(pack_bf2(v, 0.f)); }
@@ -181,6 +180,66 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
 #pragma unroll
     for (int s = 0; s < NS; s++)
         if (s < nt) issue(s);
+
+    constexpr uint32_t CES = OUT_F32 ? 4u : 2u;
+    constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
+    const __amdgpu_buffer_rsrc_t rsC = make_rsrc(Cv, (uint32_t)(((size_t)(M - 1) * ldc + N) * CES));
+    const __amdgpu_buffer_rsrc_t rsR = make_rsrc(R ? (const void*)R : (const void*)Cv, R ? (uint32_t)(((size_t)(M - 1) * ldr + N) * 2u) : 0u);
+    const int r_w = lane & 31;                       // row written, chunks 2g + hf
+    const int r_r = lane >> 3, c_r = lane & 7;       // row (+ 8t) and chunk read back
+    const int fuse = [&] { if constexpr (FUSES) return g.fuse; else return (int)FUSE_NONE; }();
+    // NN: gate|up beside dm and dgate|dup; NT: silu(gate) * up
+    const bool gates = FUSES && fuse > FUSE_ROPE;
+    __amdgpu_buffer_rsrc_t rsX = rsC, rsY = rsC;
+    if constexpr (FUSES) {
+        const uint32_t row = (KIND == GEMM_NN ? 4u : 1u) * (uint32_t)N;   // bytes
+        if (gates) rsX = make_rsrc(g.X.at(micro), (uint32_t)M * row);
+        if (KIND == GEMM_NN) rsY = make_rsrc(g.Y.at(micro), (uint32_t)M * row);
+    }
+    // What the epilogue reads beside the product of block (i, j): the residual, the sum so far or gate|up, and the angles of the
+    // rotary embedding.
+    struct Beside { i32x2 res[KIND == GEMM_TN ? 1 : 4], up[KIND == GEMM_NN && FUSES ? 4 : 1]; i32x4 sum[OUT_F32 ? 4 : 1]; float4 cs[2], sn[2]; };
+    auto ask = [&](int i, int j, Beside& s) {
+        const int block = n0 + wn + 32 * j, col = block + 4 * c_r;
+        if constexpr (KIND == GEMM_NT && FUSES) {
+            if (fuse == FUSE_ROPE && block < g.rot) {
+                int sample = m0 + wm + 32 * i + r_w;
+                const int pos = split_off(sample, g.tokens), half = g.period / 2, base = pair_column(block, g.period, g.shift, N);
+                const float* t = g.table + (size_t)pos * half + (base & (g.period - 1)) + 4 * hf;
+#pragma unroll
+                for (int q = 0; q < 2; q++) {
+                    s.cs[q] = *reinterpret_cast<const float4*>(t + 8 * q);
+                    s.sn[q] = *reinterpret_cast<const float4*>(t + 8 * q + (size_t)g.table_seq * half);
+                }
+            }
+            return;
+        }
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+            const uint32_t row = (uint32_t)(m0 + wm + 32 * i + r_r + 8 * t);
+            if constexpr (OUT_F32) {
+                if (accumulate) s.sum[t] = __builtin_amdgcn_raw_buffer_load_b128(rsC, col < N ? (row * (uint32_t)ldc + (uint32_t)col) * CES : OUT_OF_RANGE, 0, 0);
+            } else if constexpr (FUSES) {
+                const uint32_t at = (row * (uint32_t)(2 * N) + (uint32_t)col) * 2u;
+                s.res[t] = __builtin_amdgcn_raw_buffer_load_b64(rsX, col < N ? at : OUT_OF_RANGE, 0, 0);
+                s.up[t] = __builtin_amdgcn_raw_buffer_load_b64(rsX, col < N ? at + (uint32_t)N * 2u : OUT_OF_RANGE, 0, 0);
+            } else if (R) {
+                s.res[t] = __builtin_amdgcn_raw_buffer_load_b64(rsR, col < N ? (row * (uint32_t)ldr + (uint32_t)col) * 2u : OUT_OF_RANGE, 0, 0);
+            }
+        }
+    };
+    // Asked for behind the requests of the first k tiles on the smaller tiles, whose epilogue would otherwise be a round trip to
+    // memory: 128x768x256 with rotary embedding 4.2 -> 4.0 us, 700x1536x1024 10.6 -> 10.1, 128x256x256 with residual 3.33 -> 3.30.
+    // Of three or four blocks a wave, 64 registers, it costs more than it gives (1100x3072x3072 with residual 27.4 -> 28.2), and
+    // gate|up, two tiles as large as the product, hold up the k tiles behind them (700x2048x1024 12.2 -> 12.6).
+    constexpr bool EARLY = TM * TN <= 2 && !(KIND == GEMM_NN && FUSES);
+    Beside beside[EARLY ? TM : 1][EARLY ? TN : 1];
+    if (EARLY && ksplit == 1 && !(SUMS && seq > 1)) {
+#pragma unroll
+        for (int i = 0; i < TM; i++)
+#pragma unroll
+            for (int j = 0; j < TN; j++) ask(i, j, beside[EARLY ? i : 0][EARLY ? j : 0]);
+    }
 
     f32x16 acc[TM][TN];
 #pragma unroll
@@ -361,58 +420,33 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
 
     // Epilogue as in k_gemm_dma: every 32x32 block goes through a wave-private LDS patch, so that loads of what is
     // added and stores cover whole row segments.
-    constexpr uint32_t CES = OUT_F32 ? 4u : 2u;
-    constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
-    const __amdgpu_buffer_rsrc_t rsC = make_rsrc(Cv, (uint32_t)(((size_t)(M - 1) * ldc + N) * CES));
-    const __amdgpu_buffer_rsrc_t rsR = make_rsrc(R ? (const void*)R : (const void*)Cv, R ? (uint32_t)(((size_t)(M - 1) * ldr + N) * 2u) : 0u);
     __syncthreads();   // nobody reads the ring any more: each wave takes 4 KB of it as its patch
     char* const patch = smem + wave * 4096;
-    const int r_w = lane & 31;                       // row written, chunks 2g + hf
-    const int r_r = lane >> 3, c_r = lane & 7;       // row (+ 8t) and chunk read back
-    const int fuse = [&] { if constexpr (FUSES) return g.fuse; else return (int)FUSE_NONE; }();
-    // NN: gate|up beside dm and dgate|dup; NT: silu(gate) * up
-    const bool gates = FUSES && fuse > FUSE_ROPE;
-    __amdgpu_buffer_rsrc_t rsX = rsC, rsY = rsC;
-    if constexpr (FUSES) {
-        const uint32_t row = (KIND == GEMM_NN ? 4u : 1u) * (uint32_t)N;   // bytes
-        if (gates) rsX = make_rsrc(g.X.at(micro), (uint32_t)M * row);
-        if (KIND == GEMM_NN) rsY = make_rsrc(g.Y.at(micro), (uint32_t)M * row);
-    }
 #pragma unroll
     for (int i = 0; i < TM; i++) {
-        int pos = 0;
-        if constexpr (KIND == GEMM_NT && FUSES)
-            if (fuse == FUSE_ROPE) { int sample = m0 + wm + 32 * i + r_w; pos = split_off(sample, g.tokens); }
 #pragma unroll
         for (int j = 0; j < TN; j++) {
             const int block = n0 + wn + 32 * j;
             int col = block + 4 * c_r;
+            Beside& b = beside[EARLY ? i : 0][EARLY ? j : 0];
+            if (!EARLY) ask(i, j, b);
             if constexpr (KIND == GEMM_NT && FUSES) {
                 const int half = g.period / 2, base = pair_column(block, g.period, g.shift, N);
                 col = block >= N ? block : base + (c_r < 4 ? 4 * c_r : half + 4 * (c_r - 4));
                 if (fuse == FUSE_SWIGLU || block < g.rot) {
-                    float4 cs[2], sn[2];
-                    if (fuse == FUSE_ROPE) {
-                        const float* t = g.table + (size_t)pos * half + (base & (g.period - 1)) + 4 * hf;
-#pragma unroll
-                        for (int q = 0; q < 2; q++) {
-                            cs[q] = *reinterpret_cast<const float4*>(t + 8 * q);
-                            sn[q] = *reinterpret_cast<const float4*>(t + 8 * q + (size_t)g.table_seq * half);
-                        }
-                    }
 #pragma unroll
                     for (int q = 0; q < 2; q++) {
                         float o[4];
-                        const float c[4] = {cs[q].x, cs[q].y, cs[q].z, cs[q].w}, sv[4] = {sn[q].x, sn[q].y, sn[q].z, sn[q].w};
+                        const float c[4] = {b.cs[q].x, b.cs[q].y, b.cs[q].z, b.cs[q].w}, sv[4] = {b.sn[q].x, b.sn[q].y, b.sn[q].z, b.sn[q].w};
 #pragma unroll
                         for (int e = 0; e < 4; e++) {
-                            float a = as_bf(acc[i][j][4 * q + e]), b = as_bf(acc[i][j][4 * (q + 2) + e]);
+                            float u = as_bf(acc[i][j][4 * q + e]), v = as_bf(acc[i][j][4 * (q + 2) + e]);
                             if (fuse == FUSE_SWIGLU) {
-                                o[e] = swiglu(a, b);
+                                o[e] = swiglu(u, v);
                             } else {
-                                rotate_pair(a, b, c[e], sv[e]);
-                                acc[i][j][4 * q + e] = a;
-                                acc[i][j][4 * (q + 2) + e] = b;
+                                rotate_pair(u, v, c[e], sv[e]);
+                                acc[i][j][4 * q + e] = u;
+                                acc[i][j][4 * (q + 2) + e] = v;
                             }
                         }
                         if (fuse == FUSE_SWIGLU) {
@@ -424,27 +458,16 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
                 }
             }
             float4 add[4];
-            i32x2 gate[4], up[4];   // beside dm
             uint32_t off_c[4];
 #pragma unroll
             for (int t = 0; t < 4; t++) {
                 const uint32_t row = (uint32_t)(m0 + wm + 32 * i + r_r + 8 * t);
                 off_c[t] = col < N ? (row * (uint32_t)ldc + (uint32_t)col) * CES : OUT_OF_RANGE;
                 add[t] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if constexpr (KIND == GEMM_NN && FUSES) {
-                    const uint32_t at = (row * (uint32_t)(2 * N) + (uint32_t)col) * 2u;
-                    gate[t] = __builtin_amdgcn_raw_buffer_load_b64(rsX, col < N ? at : OUT_OF_RANGE, 0, 0);
-                    up[t] = __builtin_amdgcn_raw_buffer_load_b64(rsX, col < N ? at + (uint32_t)N * 2u : OUT_OF_RANGE, 0, 0);
-                }
-                if (OUT_F32) {
-                    if (accumulate) {
-                        const i32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsC, off_c[t], 0, 0);
-                        add[t] = make_float4(__int_as_float(v[0]), __int_as_float(v[1]), __int_as_float(v[2]), __int_as_float(v[3]));
-                    }
-                } else if (R) {
-                    const uint32_t off_r = col < N ? (row * (uint32_t)ldr + (uint32_t)col) * 2u : OUT_OF_RANGE;
-                    const i32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsR, off_r, 0, 0);
-                    add[t] = make_float4(lo_bf((uint32_t)v[0]), hi_bf((uint32_t)v[0]), lo_bf((uint32_t)v[1]), hi_bf((uint32_t)v[1]));
+                if constexpr (OUT_F32) {
+                    if (accumulate) add[t] = make_float4(__int_as_float(b.sum[t][0]), __int_as_float(b.sum[t][1]), __int_as_float(b.sum[t][2]), __int_as_float(b.sum[t][3]));
+                } else if (!FUSES && R) {
+                    add[t] = make_float4(lo_bf((uint32_t)b.res[t][0]), hi_bf((uint32_t)b.res[t][0]), lo_bf((uint32_t)b.res[t][1]), hi_bf((uint32_t)b.res[t][1]));
                 }
             }
 #pragma unroll
@@ -460,8 +483,8 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
                     const uint32_t row = (uint32_t)(m0 + wm + 32 * i + r_r + 8 * t);
                     const uint32_t off_g = col < N ? (row * (uint32_t)(2 * N) + (uint32_t)col) * 2u : OUT_OF_RANGE;
                     const uint32_t off_u = col < N ? off_g + (uint32_t)N * 2u : OUT_OF_RANGE;
-                    const float gt[4] = {lo_bf((uint32_t)gate[t][0]), hi_bf((uint32_t)gate[t][0]), lo_bf((uint32_t)gate[t][1]), hi_bf((uint32_t)gate[t][1])};
-                    const float uu[4] = {lo_bf((uint32_t)up[t][0]), hi_bf((uint32_t)up[t][0]), lo_bf((uint32_t)up[t][1]), hi_bf((uint32_t)up[t][1])};
+                    const float gt[4] = {lo_bf((uint32_t)b.res[t][0]), hi_bf((uint32_t)b.res[t][0]), lo_bf((uint32_t)b.res[t][1]), hi_bf((uint32_t)b.res[t][1])};
+                    const float uu[4] = {lo_bf((uint32_t)b.up[t][0]), hi_bf((uint32_t)b.up[t][0]), lo_bf((uint32_t)b.up[t][1]), hi_bf((uint32_t)b.up[t][1])};
                     const float dm[4] = {v.x, v.y, v.z, v.w};
                     float dg[4], du[4], mm[4];
 #pragma unroll
