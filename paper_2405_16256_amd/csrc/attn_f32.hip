@@ -15,8 +15,8 @@
 // The next tile of each operand is requested as soon as its registers are free.
 //
 // Measured on one MI355X against one wave per row with scalar dot products (us per call, 8 query heads on 2 key/value
-// heads of 128, 700 tokens): forward 401 -> 28, dq 424 -> 42, dk|dv 1246 -> 53; 4 heads of 64, 128 tokens: 39.7 -> 6.4,
-// 26.3 -> 7.6, 33.3 -> 8.9.
+// heads of 128, 700 tokens): forward 401 -> 27, dq 424 -> 40, dk|dv 1246 -> 51; 4 heads of 64, 128 tokens: 39.7 -> 4.9,
+// dq and dk|dv in one launch 59.6 -> 8.3.
 #include "common.h"
 #include "kernels.h"
 
@@ -166,20 +166,31 @@ template <int D> struct Merge {
     }
 };
 
+// The shape of a launch, with the divisors that take a workgroup's index apart.
+struct F32Shape {
+    int B, S, nh, nkv, tiles, parts;
+    Divisor heads, nh_, group;        // heads of all samples, of one; query heads of a key/value head
+    Divisor kv_jobs, kv, parts_, level;   // dk | dv jobs of a key tile, of one sample; workgroups a key/value head's query heads are dealt to;
+                                          // jobs of both passes of a tile
+    int G;                            // query heads of one of those workgroups
+};
+
 // reductions over the four lanes that share a column
 __device__ __forceinline__ float col_max(float v) { v = fmaxf(v, __shfl_xor(v, 16, WAVE)); return fmaxf(v, __shfl_xor(v, 32, WAVE)); }
 __device__ __forceinline__ float col_sum(float v) { v += __shfl_xor(v, 16, WAVE); return v + __shfl_xor(v, 32, WAVE); }
 
 template <int D>
 __global__ __launch_bounds__(AW* WAVE, 2) void k_attn_f32_fwd(const float* __restrict__ qkv, int ld, float* __restrict__ o,
-                                                              float* __restrict__ lse, int B, int S, int nh, int nkv, MicroStride micro) {
+                                                              float* __restrict__ lse, F32Shape sh, MicroStride micro) {
     qkv = micro_at(qkv, micro.saved); o = micro_at(o, micro.saved); lse = micro_at(lse, micro.saved);
+    const int B = sh.B, S = sh.S, nh = sh.nh, nkv = sh.nkv;
     __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
     __shared__ float ms[AW][AT], ls[AW][AT];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4;
-    const int nhb = nh * B, tiles = (S + AT - 1) / AT;
-    const int qt = tiles - 1 - (int)blockIdx.x / nhb, h = (blockIdx.x % nhb) % nh, b = (blockIdx.x % nhb) / nh;   // longest first
-    const int A = nh * D, kcol = A + (h / (nh / nkv)) * D;
+    int qt = (int)blockIdx.x, b = split_off(qt, sh.heads);
+    qt = sh.tiles - 1 - qt;   // longest first
+    const int h = split_off(b, sh.nh_);
+    const int A = nh * D, kcol = A + quotient(h, sh.group) * D;
     const size_t extent = (size_t)B * S * ld, row0 = (size_t)b * S * ld;
     const Operand oq = operand(qkv, extent, row0 + h * D, ld, S), ok = operand(qkv, extent, row0 + kcol, ld, S),
                   ov = operand(qkv, extent, row0 + kcol + nkv * D, ld, S);
@@ -236,20 +247,17 @@ __global__ __launch_bounds__(AW* WAVE, 2) void k_attn_f32_fwd(const float* __res
     if ((threadIdx.x & 15) == 0) lse[((size_t)b * nh + h) * S + s] = M + logf(L);
 }
 
-// Per 16 queries: delta = <do, o>, and dq = sum_t dZ[s,t] k[t] / sqrt(d).
+// Per 16 queries (tile qt of head and sample hb): delta = <do, o>, which is also left in dvec unless that is null, and
+// dq = sum_t dZ[s,t] k[t] / sqrt(d).
 template <int D>
-__global__ __launch_bounds__(AW* WAVE, 2) void k_attn_f32_bwd_q(const float* __restrict__ qkv, int ld,
-                                                                const float* __restrict__ o, const float* __restrict__ dout,
-                                                                const float* __restrict__ lse, float* __restrict__ dvec,
-                                                                float* __restrict__ dqkv, int B, int S, int nh, int nkv,
-                                                                const float* __restrict__ table, int table_seq, MicroStride micro) {
-    qkv = micro_at(qkv, micro.saved); o = micro_at(o, micro.saved); lse = micro_at(lse, micro.saved);
-    dout = micro_at(dout, micro.ws); dvec = micro_at(dvec, micro.ws); dqkv = micro_at(dqkv, micro.ws);
-    __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
+__device__ __forceinline__ void bwd_q_body(float* buf, const int qt, const int hb, const float* __restrict__ qkv, int ld, const float* __restrict__ o,
+                                           const float* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ dvec,
+                                           float* __restrict__ dqkv, const F32Shape& sh, const float* __restrict__ table, int table_seq) {
+    const int B = sh.B, S = sh.S, nh = sh.nh, nkv = sh.nkv;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4;
-    const int nhb = nh * B, tiles = (S + AT - 1) / AT;
-    const int qt = tiles - 1 - (int)blockIdx.x / nhb, h = (blockIdx.x % nhb) % nh, b = (blockIdx.x % nhb) / nh;
-    const int A = nh * D, kcol = A + (h / (nh / nkv)) * D;
+    int b = hb;
+    const int h = split_off(b, sh.nh_);
+    const int A = nh * D, kcol = A + quotient(h, sh.group) * D;
     const size_t extent = (size_t)B * S * ld, row0 = (size_t)b * S * ld;
     const size_t extent_o = (size_t)B * S * A, row0_o = (size_t)b * S * A;
     const Operand oq = operand(qkv, extent, row0 + h * D, ld, S), ok = operand(qkv, extent, row0 + kcol, ld, S),
@@ -269,7 +277,7 @@ __global__ __launch_bounds__(AW* WAVE, 2) void k_attn_f32_bwd_q(const float* __r
     const int s = qt * AT + (lane & 15);
     const size_t at_s = ((size_t)b * nh + h) * S + s;
     const float L = s < S ? lse[at_s] : 0.f;
-    if (wave == 0 && g == 0 && s < S) dvec[at_s] = delta;
+    if (dvec && wave == 0 && g == 0 && s < S) dvec[at_s] = delta;
     const float scale = 1.0f / sqrtf((float)D);
     f32x4 acc[D / 16];
 #pragma unroll
@@ -293,28 +301,27 @@ __global__ __launch_bounds__(AW* WAVE, 2) void k_attn_f32_bwd_q(const float* __r
     Merge<D>::write(buf, dqkv + ((size_t)b * S + qt * AT) * ld + h * D, ld, qt * AT, S, scale, table, table_seq);
 }
 
-// Per 16 keys of one key/value head: dv[t] = sum over its query heads and s >= t of P[s,t] do[s]; dk[t] = the same sum
-// of dZ[s,t] q[s] / sqrt(d).  With parts > 1 the query heads are dealt out to `parts` workgroups, whose sums go to
-// partial[part][token][dk | dv of every key/value head] and are finished by k_attn_f32_kv_reduce.
-template <int D>
-__global__ __launch_bounds__(AW* WAVE, 1) void k_attn_f32_bwd_kv(const float* __restrict__ qkv, int ld,
-                                                                 const float* __restrict__ dout, const float* __restrict__ lse,
-                                                                 const float* __restrict__ dvec, float* __restrict__ dqkv,
-                                                                 float* __restrict__ partial, int parts, int B, int S, int nh, int nkv,
-                                                                 const float* __restrict__ table, int table_seq, MicroStride micro) {
-    qkv = micro_at(qkv, micro.saved); lse = micro_at(lse, micro.saved);
-    dout = micro_at(dout, micro.ws); dvec = micro_at(dvec, micro.ws); dqkv = micro_at(dqkv, micro.ws); partial = micro_at(partial, micro.ws);
-    __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
+// Per 16 keys (tile kt) of one key/value head: dv[t] = sum over its query heads and s >= t of P[s,t] do[s]; dk[t] = the same
+// sum of dZ[s,t] q[s] / sqrt(d).  With parts > 1 the query heads are dealt out to `parts` workgroups, whose sums go to
+// partial[part][token][dk | dv of every key/value head] and are finished by k_attn_f32_kv_reduce.  Unless DELTA_GIVEN (in
+// dvec), delta of each query tile is formed here, as the dq jobs form it.
+template <int D, bool DELTA_GIVEN>
+__device__ __forceinline__ void bwd_kv_body(float* buf, const int kt, const int rest, const float* __restrict__ qkv, int ld, const float* __restrict__ o,
+                                            const float* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ dvec,
+                                            float* __restrict__ dqkv, float* __restrict__ partial, const F32Shape& sh,
+                                            const float* __restrict__ table, int table_seq) {
+    const int B = sh.B, S = sh.S, nh = sh.nh, nkv = sh.nkv, parts = sh.parts, tiles = sh.tiles;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4;
-    const int tiles = (S + AT - 1) / AT, jobs = B * nkv * parts;
-    const int kt = (int)blockIdx.x / jobs, rest = blockIdx.x % jobs;   // the first keys see the most queries: longest first
-    const int part = rest % parts, hk = (rest / parts) % nkv, b = rest / (parts * nkv);
-    const int A = nh * D, kcol = A + hk * D, heads = nh / nkv / parts, h0 = hk * (nh / nkv) + part * heads;
+    int b = rest, hk = split_off(b, sh.kv);
+    const int part = split_off(hk, sh.parts_);
+    const int A = nh * D, kcol = A + hk * D, heads = sh.G, h0 = hk * sh.group.d + part * heads;
     const size_t extent = (size_t)B * S * ld, row0 = (size_t)b * S * ld;
     const size_t extent_o = (size_t)B * S * A, row0_o = (size_t)b * S * A;
     Operand oq = operand(qkv, extent, row0 + (size_t)h0 * D, ld, S), od = operand(dout, extent_o, row0_o + (size_t)h0 * D, A, S);
+    Operand oo = od;
+    if (!DELTA_GIVEN) oo.rs = make_rsrc(o, (uint32_t)(extent_o * 4));
     const uint32_t base_q = oq.base, base_d = od.base;
-    RowsF<D> kf, vf, qf, df;
+    RowsF<D> kf, vf, qf, df, of;
     ColsF<D> qc, dc;
     operand(qkv, extent, row0 + kcol, ld, S).rows(kf, kt * AT);
     operand(qkv, extent, row0 + kcol + nkv * D, ld, S).rows(vf, kt * AT);
@@ -323,18 +330,21 @@ __global__ __launch_bounds__(AW* WAVE, 1) void k_attn_f32_bwd_kv(const float* __
     for (int i = 0; i < D / 16; i++) dk[i] = dv[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float scale = 1.0f / sqrtf((float)D);
     const int per_head = tiles - kt, n = heads * per_head;   // (head, query tile) pairs, dealt out to the waves in turn
-    auto point = [&](int i) {   // the operands' head of pair i; its query tile
-        const int hd = i / per_head;
-        oq.base = base_q + (uint32_t)(hd * D) * 4u;
-        od.base = base_d + (uint32_t)(hd * D) * 4u;
-        return kt + i - hd * per_head;
+    int head = 0, tile = wave;   // query head and tile (from kt on) of the pair that is asked for
+    auto point = [&]() {         // the operands at that head; its query tile
+        while (tile >= per_head) { tile -= per_head; head++; }
+        oq.base = base_q + (uint32_t)(head * D) * 4u;
+        oo.base = od.base = base_d + (uint32_t)(head * D) * 4u;
+        return kt + tile;
     };
     if (wave < n) {
-        const int t = point(wave);
-        oq.rows(qf, t * AT); od.rows(df, t * AT); od.cols(dc, t * AT); oq.cols(qc, t * AT);
+        const int t = point();
+        oq.rows(qf, t * AT); od.rows(df, t * AT);
+        if (!DELTA_GIVEN) oo.rows(of, t * AT);
+        od.cols(dc, t * AT); oq.cols(qc, t * AT);
     }
     for (int i = wave; i < n; i += AW) {
-        const int qt = point(i), hd = h0 + i / per_head;
+        const int qt = kt + tile, hd = h0 + head;
         const Operand cq = oq, cd = od;
         const size_t stat = ((size_t)b * nh + hd) * S;
         float L[4], dl[4];
@@ -342,10 +352,22 @@ __global__ __launch_bounds__(AW* WAVE, 1) void k_attn_f32_bwd_kv(const float* __
         for (int r = 0; r < 4; r++) {
             const int s = min(qt * AT + 4 * g + r, S - 1);
             L[r] = lse[stat + s];
-            dl[r] = dvec[stat + s];
+            if (DELTA_GIVEN) dl[r] = dvec[stat + s];
         }
         const bool more = i + AW < n;
-        const int nt = more ? point(i + AW) : 0;
+        tile += AW;
+        const int nt = more ? point() : 0;
+        if (!DELTA_GIVEN) {
+            float delta = 0.f;
+#pragma unroll
+            for (int j = 0; j < D / 16; j++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) delta = fmaf(df.v[j][e], of.v[j][e], delta);
+            delta = col_sum(delta);   // of query lane % 16
+#pragma unroll
+            for (int r = 0; r < 4; r++) dl[r] = __shfl(delta, 4 * g + r, WAVE);
+            if (more) oo.rows(of, nt * AT);
+        }
         const f32x4 z = dot_tiles<D>(qf, kf) * scale;   // row = query, column = key
         if (more) oq.rows(qf, nt * AT);
         const f32x4 dp = dot_tiles<D>(df, vf);
@@ -376,16 +398,58 @@ __global__ __launch_bounds__(AW* WAVE, 1) void k_attn_f32_bwd_kv(const float* __
     Merge<D>::write(buf, out + nkv * D, ldo, kt * AT, S, 1.0f, nullptr, 0);
 }
 
+template <int D>
+__global__ __launch_bounds__(AW* WAVE, 2) void k_attn_f32_bwd_q(const float* __restrict__ qkv, int ld,
+                                                                const float* __restrict__ o, const float* __restrict__ dout,
+                                                                const float* __restrict__ lse, float* __restrict__ dvec,
+                                                                float* __restrict__ dqkv, const float* __restrict__ table, int table_seq,
+                                                                F32Shape sh, MicroStride micro) {
+    qkv = micro_at(qkv, micro.saved); o = micro_at(o, micro.saved); lse = micro_at(lse, micro.saved);
+    dout = micro_at(dout, micro.ws); dvec = micro_at(dvec, micro.ws); dqkv = micro_at(dqkv, micro.ws);
+    __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
+    int qt = (int)blockIdx.x;
+    const int hb = split_off(qt, sh.heads);
+    bwd_q_body<D>(buf, sh.tiles - 1 - qt, hb, qkv, ld, o, dout, lse, dvec, dqkv, sh, table, table_seq);
+}
+template <int D>
+__global__ __launch_bounds__(AW* WAVE, 1) void k_attn_f32_bwd_kv(const float* __restrict__ qkv, int ld,
+                                                                 const float* __restrict__ dout, const float* __restrict__ lse,
+                                                                 const float* __restrict__ dvec, float* __restrict__ dqkv,
+                                                                 float* __restrict__ partial, const float* __restrict__ table, int table_seq,
+                                                                 F32Shape sh, MicroStride micro) {
+    qkv = micro_at(qkv, micro.saved); lse = micro_at(lse, micro.saved);
+    dout = micro_at(dout, micro.ws); dvec = micro_at(dvec, micro.ws); dqkv = micro_at(dqkv, micro.ws); partial = micro_at(partial, micro.ws);
+    __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
+    int kt = (int)blockIdx.x;   // the first keys see the most queries: longest first
+    const int rest = split_off(kt, sh.kv_jobs);
+    bwd_kv_body<D, true>(buf, kt, rest, qkv, ld, nullptr, dout, lse, dvec, dqkv, partial, sh, table, table_seq);
+}
+// Both passes in one launch: the dk | dv jobs of key tile l and the dq jobs of query tile n-1-l, longest first.
+template <int D>
+__global__ __launch_bounds__(AW* WAVE, D == 64 ? 2 : 1) void k_attn_f32_bwd_both(const float* __restrict__ qkv, int ld,
+                                                                const float* __restrict__ o, const float* __restrict__ dout,
+                                                                const float* __restrict__ lse, float* __restrict__ dqkv,
+                                                                float* __restrict__ partial, const float* __restrict__ table, int table_seq,
+                                                                F32Shape sh, MicroStride micro) {
+    qkv = micro_at(qkv, micro.saved); o = micro_at(o, micro.saved); lse = micro_at(lse, micro.saved);
+    dout = micro_at(dout, micro.ws); dqkv = micro_at(dqkv, micro.ws); partial = micro_at(partial, micro.ws);
+    __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
+    int level = (int)blockIdx.x;
+    const int r = split_off(level, sh.level), kv_jobs = sh.kv_jobs.d;
+    if (r < kv_jobs) bwd_kv_body<D, false>(buf, level, r, qkv, ld, o, dout, lse, nullptr, dqkv, partial, sh, table, table_seq);
+    else bwd_q_body<D>(buf, sh.tiles - 1 - level, r - kv_jobs, qkv, ld, o, dout, lse, nullptr, dqkv, sh, table, table_seq);
+}
+
 // dk | dv of a token = the sum of its `parts` partial rows in order, dk rotated back.  A thread owns 4 channel pairs.
 template <int D>
 __global__ __launch_bounds__(256) void k_attn_f32_kv_reduce(const float* __restrict__ partial, int parts, float* __restrict__ dqkv, int ld,
-                                                            int T, int S, int nh, int nkv, const float* __restrict__ table, int table_seq, MicroStride micro) {
+                                                            int T, Divisor S, int nh, int nkv, Divisor per_row, const float* __restrict__ table,
+                                                            int table_seq, MicroStride micro) {
     partial = micro_at(partial, micro.ws); dqkv = micro_at(dqkv, micro.ws);
     constexpr int HALF = D / 2, VPH = HALF / 4;
-    const int per_row = 2 * nkv * VPH;
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (long)T * per_row) return;
-    const int t = (int)(idx / per_row), w = (int)(idx % per_row), head = w / VPH, c = (w % VPH) * 4, pos = t % S;
+    int t = (int)(blockIdx.x * 256 + threadIdx.x), sample;
+    const int w = split_off(t, per_row), head = w / VPH, c = (w % VPH) * 4, pos = split_off(sample = t, S);
+    if (t >= T) return;
     const int width = 2 * nkv * D;
     const float* p = partial + (size_t)t * width + head * D + c;
     f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
@@ -404,6 +468,14 @@ __global__ __launch_bounds__(256) void k_attn_f32_kv_reduce(const float* __restr
     *reinterpret_cast<f32x4*>(out + HALF) = b;
 }
 
+static F32Shape f32_shape(int B, int S, int nh, int nkv, int parts) {
+    F32Shape s;
+    s.B = B; s.S = S; s.nh = nh; s.nkv = nkv; s.tiles = (S + AT - 1) / AT; s.parts = parts; s.G = nh / nkv / parts;
+    s.heads = divisor(nh * B); s.nh_ = divisor(nh); s.group = divisor(nh / nkv);
+    s.kv_jobs = divisor(B * nkv * parts); s.kv = divisor(nkv * parts); s.parts_ = divisor(parts); s.level = divisor(B * nkv * parts + nh * B);
+    return s;
+}
+
 template <int D>
 static hipError_t launch_bwd(const float* qkv, int ld, const float* o, const float* dout, const float* lse, float* dvec, float* dqkv,
                              float* scratch, size_t scratch_bytes, int B, int S, int nh, int nkv, const float* table, int table_seq,
@@ -417,23 +489,33 @@ static hipError_t launch_bwd(const float* qkv, int ld, const float* o, const flo
     const size_t part_bytes = (size_t)B * S * 2 * nkv * D * sizeof(float);
     for (int p = 2; p <= G; p++)
         if (G % p == 0 && (long)tiles * B * nkv * parts < 512 && p * part_bytes <= scratch_bytes) parts = p;
-    k_attn_f32_bwd_q<D><<<dim3(tiles * B * nh, micro.n), AW * WAVE, 0, st>>>(qkv, ld, o, dout, lse, dvec, dqkv, B, S, nh, nkv, table, table_seq, micro);
-    k_attn_f32_bwd_kv<D><<<dim3(tiles * B * nkv * parts, micro.n), AW * WAVE, 0, st>>>(qkv, ld, dout, lse, dvec, dqkv, scratch, parts, B, S, nh, nkv,
-                                                                       table, table_seq, micro);
+    const F32Shape sh = f32_shape(B, S, nh, nkv, parts);
+    const unsigned jobs_q = tiles * B * nh, jobs_kv = tiles * B * nkv * parts;
+    // Both passes in one launch while its jobs are few: each pass alone is bound by its longest job, and the second waits for
+    // the first.  Every dk | dv job then reads o as well, and at head_dim 128 a workgroup has its CU to itself (406
+    // registers), the dq jobs too.  us apart -> together, head_dim 64: 4 heads, 128 tokens (64 jobs) 14.2 -> 8.3; 16 on 2, 2 x 1024
+    // (4096) 256 -> 217; 8, 4 x 1000 (4032) 211 -> 209; 16, 4 x 1000 (8064) 404 -> 425.  128: 1 head, 44 tokens 14.8 -> 8.6; 8, 500
+    // (512) 56.5 -> 46.9; 8, 620 (624) 73.3 -> 72.0; 8 on 2, 700 (704) 86 -> 88.5; 8, 1024 (1024) 128 -> 152.
+    if (jobs_q + jobs_kv <= (D == 64 ? 4096u : 640u)) {
+        k_attn_f32_bwd_both<D><<<dim3(jobs_q + jobs_kv, micro.n), AW * WAVE, 0, st>>>(qkv, ld, o, dout, lse, dqkv, scratch, table, table_seq, sh, micro);
+    } else {
+        k_attn_f32_bwd_q<D><<<dim3(jobs_q, micro.n), AW * WAVE, 0, st>>>(qkv, ld, o, dout, lse, dvec, dqkv, table, table_seq, sh, micro);
+        k_attn_f32_bwd_kv<D><<<dim3(jobs_kv, micro.n), AW * WAVE, 0, st>>>(qkv, ld, dout, lse, dvec, dqkv, scratch, table, table_seq, sh, micro);
+    }
     if (parts > 1) {
         const long n = (long)B * S * 2 * nkv * (D / 8);
-        k_attn_f32_kv_reduce<D><<<dim3((unsigned)((n + 255) / 256), micro.n), 256, 0, st>>>(scratch, parts, dqkv, ld, B * S, S, nh, nkv, table, table_seq,
-                                                                                            micro);
+        k_attn_f32_kv_reduce<D><<<dim3((unsigned)((n + 255) / 256), micro.n), 256, 0, st>>>(scratch, parts, dqkv, ld, B * S, divisor(S), nh, nkv, divisor(2 * nkv * (D / 8)),
+                                                                                            table, table_seq, micro);
     }
     return hipGetLastError();
 }
 
 hipError_t attn_f32_fwd(const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, const MicroStride& micro,
                         hipStream_t st) {
-    const int tiles = (S + AT - 1) / AT * B * nh;
-    const dim3 grid(tiles, micro.n);
-    if (d == 64) k_attn_f32_fwd<64><<<grid, AW * WAVE, 0, st>>>((const float*)qkv, ld, (float*)o, lse, B, S, nh, nkv, micro);
-    else if (d == 128) k_attn_f32_fwd<128><<<grid, AW * WAVE, 0, st>>>((const float*)qkv, ld, (float*)o, lse, B, S, nh, nkv, micro);
+    const dim3 grid((S + AT - 1) / AT * B * nh, micro.n);
+    const F32Shape sh = f32_shape(B, S, nh, nkv, 1);
+    if (d == 64) k_attn_f32_fwd<64><<<grid, AW * WAVE, 0, st>>>((const float*)qkv, ld, (float*)o, lse, sh, micro);
+    else if (d == 128) k_attn_f32_fwd<128><<<grid, AW * WAVE, 0, st>>>((const float*)qkv, ld, (float*)o, lse, sh, micro);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

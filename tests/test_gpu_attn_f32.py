@@ -32,6 +32,13 @@ def test_heads_that_share_keys_in_one_workgroup(ctx):
     check_layer(ctx, I.LayerShape(64, 8, 64, 64, 1024, 2, n_kv_heads=4), False, 502, label="attn f32 wide")
 
 
+@pytest.mark.parametrize("heads,kv_heads,head_dim,seq,batch", [(5, 1, 128, 1000, 1), (8, 8, 128, 650, 1), (16, 16, 64, 1001, 2), (16, 8, 64, 1030, 2)])
+def test_backward_passes_together_and_apart(ctx, heads, kv_heads, head_dim, seq, batch):
+    # 630 and 656 jobs of head_dim 128, 4032 and 4160 of head_dim 64: both sides of where the two passes share a launch
+    from tests.test_gpu_parity import check_layer
+    check_layer(ctx, I.LayerShape(64, heads, head_dim, 64, seq, batch, n_kv_heads=kv_heads), False, 504, label="attn f32 passes")
+
+
 @pytest.mark.parametrize("seq,at", [(50, 5), (50, 20), (33, 32)])
 def test_values_that_are_not_finite_stay_behind_the_mask(ctx, seq, at):
     # the tile that holds the bad row is summed pair by pair, in another order: equal up to fp32 rounding of sums of at
