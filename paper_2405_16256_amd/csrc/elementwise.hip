@@ -48,7 +48,7 @@ __device__ __forceinline__ void rmsnorm_fwd_body(T* __restrict__ x, const T* __r
     const size_t base = (size_t)blockIdx.x * H;
     const bool cached = SPLIT || H <= RC * TPB * V;
     static_assert(!SPLIT || SPLIT_COLUMNS <= RC * TPB * V, "a row of shares stays in registers");
-    Raw keep[RC];
+    Raw keep[RC], gain[RC];   // the gain is asked for with the row and not behind the barriers of its sum
     float ss = 0.f;
     if (cached) {
 #pragma unroll
@@ -61,6 +61,7 @@ __device__ __forceinline__ void rmsnorm_fwd_body(T* __restrict__ x, const T* __r
                 } else {
                     keep[i] = Vec<T>::raw(x + base + c);
                 }
+                gain[i] = Vec<T>::raw(g + c);
                 float f[V];
                 Vec<T>::widen(keep[i], f);
 #pragma unroll
@@ -85,7 +86,7 @@ __device__ __forceinline__ void rmsnorm_fwd_body(T* __restrict__ x, const T* __r
             if (c < H) {
                 float f[V], gg[V];
                 Vec<T>::widen(keep[i], f);
-                Vec<T>::load(g + c, gg);
+                Vec<T>::widen(gain[i], gg);
 #pragma unroll
                 for (int e = 0; e < V; e++) f[e] = f[e] * rs * gg[e];
                 Vec<T>::store(xn + base + c, f);
@@ -391,19 +392,15 @@ __global__ __launch_bounds__(CSW * WAVE) void k_colsum_reduce(ColSums<N> sums, i
 // One thread rotates V pairs (i, i + d/2) of one of the nrot heads that start at column 0 of a token's row
 // (the query heads followed by the key heads).
 template <typename T, int N>
-__global__ __launch_bounds__(TPB) void k_rope(Ops<N> qkv, int ld, int Ttok, int S, int nrot, int d,
+__global__ __launch_bounds__(TPB) void k_rope(Ops<N> qkv, int ld, int Ttok, Divisor S, Divisor nrot, int d, Divisor vph,   // vph: vectors of a head-half
                                               const float* __restrict__ table, int table_seq) {
     constexpr int V = Vec<T>::N;
     const int half = d / 2;
-    const int vph = half / V;               // vectors per head-half
-    const long total = (long)Ttok * nrot * vph;
-    const long idx = (long)blockIdx.x * TPB + threadIdx.x;
-    if (idx >= total) return;
-    const int iv = (int)(idx % vph);
-    long rest = idx / vph;
-    const int head = (int)(rest % nrot);
-    const int t = (int)(rest / nrot);
-    const int pos = t % S;
+    int t = (int)(blockIdx.x * TPB + threadIdx.x);
+    const int iv = split_off(t, vph), head = split_off(t, nrot);
+    if (t >= Ttok) return;
+    int sample = t;
+    const int pos = split_off(sample, S);
     T* p = (T*)qkv.at(blockIdx.y) + (size_t)t * ld + (size_t)head * d + iv * V;
     const float* cs = table + ((size_t)pos * half + iv * V);
     const float* sn = cs + (size_t)table_seq * half;
@@ -418,14 +415,13 @@ __global__ __launch_bounds__(TPB) void k_rope(Ops<N> qkv, int ld, int Ttok, int 
 
 // ------------------------------------------------------------------- SwiGLU
 template <typename T, int N>
-__global__ __launch_bounds__(TPB) void k_swiglu_fwd(Ops<N> gu_, Ops<N> m_, int Ttok, int F) {
+__global__ __launch_bounds__(TPB) void k_swiglu_fwd(Ops<N> gu_, Ops<N> m_, int Ttok, int F, Divisor vpr) {
     constexpr int V = Vec<T>::N;
     const T* gu = (const T*)gu_.at(blockIdx.y);
     T* m = (T*)m_.at(blockIdx.y);
-    const int vpr = F / V;
-    const long idx = (long)blockIdx.x * TPB + threadIdx.x;
-    if (idx >= (long)Ttok * vpr) return;
-    const int t = (int)(idx / vpr), c = (int)(idx % vpr) * V;
+    int t = (int)(blockIdx.x * TPB + threadIdx.x);
+    const int c = split_off(t, vpr) * V;
+    if (t >= Ttok) return;
     float gt[V], u[V], o[V];
     Vec<T>::load(gu + (size_t)t * 2 * F + c, gt);
     Vec<T>::load(gu + (size_t)t * 2 * F + F + c, u);
@@ -435,14 +431,13 @@ __global__ __launch_bounds__(TPB) void k_swiglu_fwd(Ops<N> gu_, Ops<N> m_, int T
 }
 
 template <typename T, int N>
-__global__ __launch_bounds__(TPB) void k_swiglu_bwd(Ops<N> dm_, Ops<N> gu_, Ops<N> dgu_, Ops<N> m_, int Ttok, int F) {
+__global__ __launch_bounds__(TPB) void k_swiglu_bwd(Ops<N> dm_, Ops<N> gu_, Ops<N> dgu_, Ops<N> m_, int Ttok, int F, Divisor vpr) {
     constexpr int V = Vec<T>::N;
     const T *dm = (const T*)dm_.at(blockIdx.y), *gu = (const T*)gu_.at(blockIdx.y);
     T *dgu = (T*)dgu_.at(blockIdx.y), *m = (T*)m_.at(blockIdx.y);
-    const int vpr = F / V;
-    const long idx = (long)blockIdx.x * TPB + threadIdx.x;
-    if (idx >= (long)Ttok * vpr) return;
-    const int t = (int)(idx / vpr), c = (int)(idx % vpr) * V;
+    int t = (int)(blockIdx.x * TPB + threadIdx.x);
+    const int c = split_off(t, vpr) * V;
+    if (t >= Ttok) return;
     float gt[V], u[V], d[V], og[V], ou[V], om[V];
     Vec<T>::load(gu + (size_t)t * 2 * F + c, gt);
     Vec<T>::load(gu + (size_t)t * 2 * F + F + c, u);
@@ -725,7 +720,8 @@ hipError_t colsum_reduce(const ColSum* jobs, int n_jobs, int n, int H, int accum
 template <typename T, int N>
 static void rope_t(const Each& qkv, int ld, int n, int Ttok, int S, int nrot, int d, const float* table, int table_seq, hipStream_t st) {
     const long vecs = (long)Ttok * nrot * (d / 2 / Vec<T>::N);
-    k_rope<T, N><<<dim3(nblocks(vecs), n), TPB, 0, st>>>(ops<N>(qkv), ld, Ttok, S, nrot, d, table, table_seq);
+    k_rope<T, N><<<dim3(nblocks(vecs), n), TPB, 0, st>>>(ops<N>(qkv), ld, Ttok, divisor(S), divisor(nrot), d, divisor(d / 2 / Vec<T>::N), table,
+                                                           table_seq);
 }
 hipError_t rope(int dtype, const Each& qkv, int ld, int n, int T, int S, int nrot, int d, const float* table, int table_seq,
                 hipStream_t st) {
@@ -738,7 +734,7 @@ hipError_t rope(int dtype, const Each& qkv, int ld, int n, int T, int S, int nro
 
 template <typename T, int N>
 static void swiglu_fwd_t(const Each& gu, const Each& m, int n, int Ttok, int F, hipStream_t st) {
-    k_swiglu_fwd<T, N><<<dim3(nblocks((long)Ttok * (F / Vec<T>::N)), n), TPB, 0, st>>>(ops<N>(gu), ops<N>(m), Ttok, F);
+    k_swiglu_fwd<T, N><<<dim3(nblocks((long)Ttok * (F / Vec<T>::N)), n), TPB, 0, st>>>(ops<N>(gu), ops<N>(m), Ttok, F, divisor(F / Vec<T>::N));
 }
 hipError_t swiglu_fwd(int dtype, const Each& gu, const Each& m, int n, int T, int F, hipStream_t st) {
     if (dtype != DT_BF16 && n == 1) swiglu_fwd_t<float, 1>(gu, m, n, T, F, st);
@@ -750,7 +746,8 @@ hipError_t swiglu_fwd(int dtype, const Each& gu, const Each& m, int n, int T, in
 
 template <typename T, int N>
 static void swiglu_bwd_t(const Each& dm, const Each& gu, const Each& dgu, const Each& m, int n, int Ttok, int F, hipStream_t st) {
-    k_swiglu_bwd<T, N><<<dim3(nblocks((long)Ttok * (F / Vec<T>::N)), n), TPB, 0, st>>>(ops<N>(dm), ops<N>(gu), ops<N>(dgu), ops<N>(m), Ttok, F);
+    k_swiglu_bwd<T, N><<<dim3(nblocks((long)Ttok * (F / Vec<T>::N)), n), TPB, 0, st>>>(ops<N>(dm), ops<N>(gu), ops<N>(dgu), ops<N>(m), Ttok, F,
+                                                                                         divisor(F / Vec<T>::N));
 }
 hipError_t swiglu_bwd(int dtype, const Each& dm, const Each& gu, const Each& dgu, const Each& m, int n, int T, int F, hipStream_t st) {
     if (dtype != DT_BF16 && n == 1) swiglu_bwd_t<float, 1>(dm, gu, dgu, m, n, T, F, st);
