@@ -47,7 +47,7 @@ namespace hh {
 // VGPR staging, no ds_write).  A k-contiguous operand row is 128 bytes per stage,
 // i.e. one full cache line per request.
 constexpr int DSTAGES = 2;
-constexpr int DTILE = 256;
+constexpr int DTILE = 256, DHALF = 128;
 constexpr int DSTAGE_BYTES = DTILE * DK * 2;   // one operand, one stage: 32 KB
 // Of the 8 DMA instructions a wave issues per stage, the last DMA_LATE wait until k step 0 of the next stage
 // (their buffer is free from the barrier on and the data is not needed before the next barrier): spreading the
@@ -315,6 +315,230 @@ __global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_
 #undef SB
 }
 
+// The same for TN problems (fp32 C, optional +=), with another k loop.  The tile is worked off as 2x2 quadrants of 128x128, of which
+// a wave has 64x32 each, one quadrant after the other over all k of a stage, so that each half of an operand's tile is read in one go
+// and its place refilled from then on: a request is on its way for 1.25 to 1.5 stages where k_gemm_dma leaves it 0.5 to 1, for a
+// second barrier per stage.  Half the fragments of both operands stay in registers (96).  4096x16384xK, four rounds of tiles,
+// k_gemm_dma's loop -> this one: K 2048 317 -> 303 us, 4096 510 -> 496, 8192 888 -> 877; 57344x8192x4096 3435 -> 3298.  NT and NN gain 1
+// to 2.5 % where the loop is long and the chip full, and lose as much or more elsewhere (NN 3300x4096x8192, 208 tiles, 175 -> 183):
+// they are at the power limit or bound by barriers.  Four waves of 128x128 (a third fewer LDS reads) take the same.
+__global__ __launch_bounds__(512) void k_gemm_dma_tn(DmaGroup grp, int full, int n_items, float* __restrict__ partial) {
+    using DT = DmaTile<false, DHALF, 8>;
+    constexpr int TM = 4, TN = 2, PW = DT::PER_WAVE, HALF_BYTES = DT::BYTES;   // 2 instructions a wave, 16 KB
+    constexpr int B_LDS = DSTAGES * DSTAGE_BYTES;
+    extern __shared__ __attribute__((aligned(1024))) char smem[];   // A [stage][half] | B [stage][half] | patches
+
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = (wave >> 2) * 64, wn = (wave & 3) * 32;          // in each half
+    const int nk_all = (grp.K + DK - 1) / DK;
+    int prob, m0, n0, kbeg, nk, slot;                               // of a work item, as in k_gemm_dma
+    auto decode = [&](int item) {
+        int tix;
+        if (item < full) { tix = item; kbeg = 0; nk = nk_all; slot = -1; }
+        else {
+            int tile = slot = item - full;
+            const int chunk = split_off(tile, grp.ksplit);
+            tix = full + tile;
+            kbeg = quotient(chunk * nk_all, grp.ksplit);
+            nk = quotient((chunk + 1) * nk_all, grp.ksplit) - kbeg;
+        }
+        prob = grp.problem_of(tix);
+        int tm, tn;
+        grp.p[prob].map.tile(tix - grp.first[prob], tm, tn);
+        m0 = tm * DTILE; n0 = tn * DTILE;
+    };
+    int item = (int)blockIdx.x;
+    decode(item);
+
+    constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem) + wave * (PW * 1024);
+    // A half's buffer begins at its first byte of the k tile asked for next, so that a lane's offset is the same in every k tile.
+    struct Half { uint64_t at; int left; };   // left: elements up to the operand's end
+    Half hA[2], hB[2];
+    uint32_t voA[PW], voB[PW], stepA, stepB;
+    // instruction p of a half; the last one moves on to the next k tile
+    auto dma_half = [&](Half& h, const uint32_t (&vo)[PW], uint32_t step, int lds, int p) {
+        const i32x4 rs = {(int)(uint32_t)h.at, (int)(uint32_t)(h.at >> 32), max(h.left, 0) << 1, 0x00020000};
+        dma16(lds0 + lds + p * 1024, vo[p], rs);
+        if (p == PW - 1) {
+            h.at += step;
+            h.left -= (int)(step >> 1);
+        }
+    };
+    auto dma_a = [&](int st, int half, int p) { dma_half(hA[half], voA, stepA, st * DSTAGE_BYTES + half * HALF_BYTES, p); };
+    auto dma_b = [&](int st, int half, int p) { dma_half(hB[half], voB, stepB, B_LDS + st * DSTAGE_BYTES + half * HALF_BYTES, p); };
+    // point the DMA at the decoded tile and put its first two k tiles on their way
+    auto start_tile = [&]() {
+        const DmaProblem& g = grp.p[prob];
+        stepA = DT::kstep_bytes(g.lda); stepB = DT::kstep_bytes(g.ldb);
+#pragma unroll
+        for (int i = 0; i < PW; i++) { voA[i] = DT::voff(wave, i, 0, g.lda); voB[i] = DT::voff(wave, i, 0, g.ldb); }
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const uint32_t skip_a = (uint32_t)(m0 + h * DHALF) * 2u + (uint32_t)kbeg * stepA;
+            const uint32_t skip_b = (uint32_t)(n0 + h * DHALF) * 2u + (uint32_t)kbeg * stepB;
+            hA[h] = Half{(uint64_t)g.A + skip_a, (int)(g.a_bytes >> 1) - (int)(skip_a >> 1)};
+            hB[h] = Half{(uint64_t)g.B + skip_b, (int)(g.b_bytes >> 1) - (int)(skip_b >> 1)};
+        }
+#pragma unroll
+        for (int s = 0; s < 2; s++)
+            if (s < nk) {
+#pragma unroll
+                for (int p = 0; p < PW; p++) dma_a(s, 0, p);
+#pragma unroll
+                for (int p = 0; p < PW; p++) dma_b(s, 0, p);
+#pragma unroll
+                for (int p = 0; p < PW; p++) dma_b(s, 1, p);
+#pragma unroll
+                for (int p = 0; p < PW; p++) dma_a(s, 1, p);
+            }
+    };
+#define SB() __builtin_amdgcn_sched_barrier(0)
+    auto sync = [&]() {
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        SB();
+    };
+    start_tile();
+    bool fresh = true;   // no stores of an earlier tile are in flight behind the DMAs
+
+    for (;;) {
+        f32x16 acc[TM][TN];
+#pragma unroll
+        for (int i = 0; i < TM; i++)
+#pragma unroll
+            for (int j = 0; j < TN; j++)
+#pragma unroll
+                for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
+
+        // k tile 0 has landed, as in k_gemm_dma
+        if (fresh && nk > 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * PW) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        sync();
+        bf16x8 a[2][2][4], b[2][4];   // A: half, row block, k step; B: register set, k step
+        // fragment f of a half, in the order in which the MFMAs take them
+        auto read_a = [&](int st, int half, int f) {
+            a[half][f & 1][f >> 1] = DT::frag(smem + st * DSTAGE_BYTES + half * HALF_BYTES, wm + 32 * (f & 1), f >> 1);
+        };
+        auto read_b = [&](int set, int st, int half, int f) { b[set][f] = DT::frag(smem + B_LDS + st * DSTAGE_BYTES + half * HALF_BYTES, wn, f); };
+#pragma unroll
+        for (int f = 0; f < 8; f++) read_a(0, 0, f);
+#pragma unroll
+        for (int f = 0; f < 4; f++) read_b(0, 0, 0, f);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        sync();
+
+        // The 8 MFMAs of quadrant (ha, hb), B from register set `set`; meanwhile the fragments of a half that is needed later are read
+        // and the two DMA instructions of one whose place is free are issued.
+        auto quadrant = [&](int ha, int hb, int set, auto read, int n_reads, auto dma, bool more) {
+#pragma unroll
+            for (int q = 0; q < 8; q++) {
+                f32x16& c = acc[2 * ha + (q & 1)][hb];
+                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[set][q >> 1], a[ha][q & 1][q >> 1], c, 0, 0, 0);
+#pragma unroll
+                for (int f = 0; f < 8; f++)
+                    if (f < n_reads && f * 4 / n_reads == q) read(f);
+#pragma unroll
+                for (int p = 0; p < PW; p++)
+                    if (q == 4 * p + 2 && more) dma(p);
+                SB();
+            }
+        };
+        // Stage S of k tile kt: the fragments of A half 0 and B half 0 (in register set S) are there, those of B half 1 and A half 1
+        // are read in the first two quadrants, the next k tile's A half 0 and B half 0 in the last two.  The waits leave the DMA
+        // instructions behind the halves that are read next on their way.
+        auto stage = [&](auto parity, int kt) {
+            constexpr int S = decltype(parity)::value, O = S ^ 1;
+            const bool more = kt + 2 < nk;
+            quadrant(0, 0, S, [&](int f) { read_b(O, S, 1, f); }, 4, [&](int p) { dma_a(S, 0, p); }, more);
+            quadrant(0, 1, O, [&](int f) { read_a(S, 1, f); }, 8, [&](int p) { dma_b(S, 0, p); }, more);
+            if (more) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(4 * PW) : "memory");
+            else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * PW) : "memory");
+            sync();
+            quadrant(1, 1, O, [&](int f) { read_a(O, 0, f); }, 8, [&](int p) { dma_b(S, 1, p); }, more);
+            quadrant(1, 0, S, [&](int f) { read_b(O, O, 0, f); }, 4, [&](int p) { dma_a(S, 1, p); }, more);
+            if (more) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(4 * PW) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            sync();
+        };
+        for (int kt = 0; kt < nk; kt += 2) {
+            stage(std::integral_constant<int, 0>{}, kt);
+            if (kt + 1 < nk) stage(std::integral_constant<int, 1>{}, kt + 1);
+        }
+
+        // next piece of work of this workgroup: start its loads before writing this one out (the stages have been read)
+        const int cm0 = m0, cn0 = n0, cslot = slot, cprob = prob;
+        item += (int)gridDim.x;
+        const bool has_next = item < n_items;
+        if (has_next) {
+            decode(item);
+            start_tile();
+            fresh = false;
+        }
+        // formed here, out of the compiler's sight: it would keep what it derives from them through the k loop
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));
+        const int hf = lane >> 5, r_w = lane & 31;
+        auto block_row = [&](int i) { return DHALF * (i >> 1) + wm + 32 * (i & 1); };
+        if (cslot >= 0) {   // a share of the k range
+            float* pt = partial + (size_t)cslot * (DTILE * DTILE);
+#pragma unroll
+            for (int i = 0; i < TM; i++)
+#pragma unroll
+                for (int j = 0; j < TN; j++)
+#pragma unroll
+                    for (int q = 0; q < 4; q++)
+                        *reinterpret_cast<float4*>(pt + (block_row(i) + r_w) * DTILE + DHALF * j + wn + 8 * q + 4 * hf) =
+                            make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+            if (!has_next) return;
+            continue;
+        }
+        // epilogue as in k_gemm_dma
+        const DmaProblem& g = grp.p[cprob];
+        const int M = g.M, N = g.N, ldc = g.ldc;
+        const bool cacc = g.accumulate != 0;
+        const __amdgpu_buffer_rsrc_t rsC = make_rsrc(g.C, (uint32_t)(((size_t)(M - 1) * ldc + N) * 4u));
+        char* const patch = smem + DSTAGES * 2 * DSTAGE_BYTES + wave * 4096;
+        const int r_r = lane >> 3, c_r = lane & 7;
+#pragma unroll
+        for (int i = 0; i < TM; i++) {
+            const uint32_t row_base = (uint32_t)(cm0 + block_row(i) + r_r);
+            float4 add[TN][4];
+            uint32_t off_c[TN][4];
+#pragma unroll
+            for (int j = 0; j < TN; j++) {
+                const int col = cn0 + DHALF * j + wn + 4 * c_r;
+#pragma unroll
+                for (int t = 0; t < 4; t++) {
+                    off_c[j][t] = col < N ? ((row_base + 8 * t) * (uint32_t)ldc + (uint32_t)col) * 4u : OUT_OF_RANGE;
+                    add[j][t] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (cacc) {
+                        const i32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsC, off_c[j][t], 0, 0);
+                        add[j][t] = make_float4(__int_as_float(v[0]), __int_as_float(v[1]), __int_as_float(v[2]), __int_as_float(v[3]));
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < TN; j++) {
+#pragma unroll
+                for (int q = 0; q < 4; q++)
+                    *reinterpret_cast<float4*>(patch + r_w * 128 + (((2 * q + hf) ^ ((r_w >> 1) & 7)) << 4)) =
+                        make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+#pragma unroll
+                for (int t = 0; t < 4; t++) {
+                    const int rr = 8 * t + r_r;
+                    const float4 v = *reinterpret_cast<const float4*>(patch + rr * 128 + ((c_r ^ ((rr >> 1) & 7)) << 4));
+                    const i32x4 o = {__float_as_int(v.x + add[j][t].x), __float_as_int(v.y + add[j][t].y), __float_as_int(v.z + add[j][t].z),
+                                     __float_as_int(v.w + add[j][t].w)};
+                    __builtin_amdgcn_raw_buffer_store_b128(o, rsC, off_c[j][t], 0, 0);
+                }
+            }
+        }
+        if (!has_next) return;
+    }
+#undef SB
+}
+
 // Sums the ksplit fp32 partial tiles of each split tile in a fixed order and applies the epilogue.
 // 64 workgroups per tile; a thread owns 4 consecutive columns of one row.
 template <bool OUT_F32>
@@ -394,11 +618,16 @@ static int tail_shares(const GemmDesc& g, int tiles, int cus) {
 // Full rounds of one tile per compute unit run as one persistent workgroup per unit.  A last, partial round of R
 // tiles would leave most units idle, so it is cut along k into floor(units / R) shares per tile, which the same
 // workgroups take up after their whole tiles (fp32 partials in `ws`, summed in a fixed order by a small second kernel).
+template <int KIND>
+static auto dma_kernel() {
+    if constexpr (KIND == GEMM_TN) return &k_gemm_dma_tn;
+    else return &k_gemm_dma<KIND, false>;
+}
 template <int KIND, bool OUT_F32>
 static hipError_t launch_dma(const GemmDesc* g, int n, hipStream_t st) {
     constexpr int LDS = DSTAGES * 2 * DSTAGE_BYTES + 8 * 4096;   // two stages + the epilogue patches of the 8 waves
     static std::atomic<uint64_t> lds_ok{0};
-    auto kern = k_gemm_dma<KIND, OUT_F32>;
+    auto kern = dma_kernel<KIND>();
     const hipError_t e = allow_lds((const void*)kern, LDS, lds_ok);
     if (e != hipSuccess) return e;
     hipError_t ce = hipSuccess;
