@@ -79,16 +79,15 @@ struct DmaGroup {
     }
 };
 
-template <int KIND, bool OUT_F32>
+// NT or NN; RES: a problem has a residual, which is added to C.  A kernel of its own: what it holds costs the others registers.
+template <int KIND, bool RES>
 __global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_items, float* __restrict__ partial) {
     // The workgroup walks work items blockIdx.x, + gridDim.x, ... < n_items.  Items below `full` are whole tiles
     // (all of k, written out through the epilogue).  Item full + q is the (q % ksplit)-th share of the k range of
     // tile full + q / ksplit; its fp32 sums go to partial[q][256][256] and k_splitk_reduce finishes those tiles.
     // The first DMA stages of the next item are issued before the current one is written out.
-    constexpr bool A_KC = (KIND != GEMM_TN);
-    constexpr bool B_KC = (KIND == GEMM_NT);
-    using DA = DmaTile<A_KC, DTILE, 8>;
-    using DB = DmaTile<B_KC, DTILE, 8>;
+    using DA = DmaTile<true, DTILE, 8>;
+    using DB = DmaTile<(KIND == GEMM_NT), DTILE, 8>;
     constexpr int TM = 4, TN = 2;
     extern __shared__ __attribute__((aligned(1024))) char smem[];   // [stage][A 32 KB | B 32 KB]
 
@@ -126,7 +125,6 @@ __global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_
     const uint32_t lds0 = (uint32_t)(uintptr_t)smem;   // LDS byte address of the dynamic segment
     const uint32_t wave_lds = __builtin_amdgcn_readfirstlane(lds0 + wave * 4096);
 
-    constexpr uint32_t CES = OUT_F32 ? 4u : 2u;
     constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
 
 #define SB() __builtin_amdgcn_sched_barrier(0)
@@ -225,10 +223,11 @@ __global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_
         const int cm0 = m0, cn0 = n0, cslot = slot, cprob = prob;
         item += (int)gridDim.x;
         const bool has_next = item < n_items;
+        const bf16_t* const R = RES && cslot < 0 ? grp.p[cprob].R : nullptr;
         if (has_next) {
             decode(item);
             __syncthreads();   // every wave has finished reading the LDS stages
-            start_tile();
+            if (!RES || !R) start_tile();
             fresh = false;
         }
 
@@ -247,66 +246,59 @@ __global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_
         }
 
         // Epilogue.  In the accumulators a lane owns one row and 4-column pieces of it, which would make every
-        // store instruction touch 32 rows with 16 or 32 bytes each.  Each 32x32 block therefore goes through a
+        // store instruction touch 32 rows with 16 bytes each.  Each 32x32 block therefore goes through a
         // wave-private 4 KB LDS patch (fp32, 16-byte chunks XOR-swizzled by the row) and comes back with 8
-        // lanes per row: loads of what is added (old fp32 sums or the bf16 residual) and stores then cover
-        // whole 128-byte (fp32) or 64-byte (bf16) row segments.  C and R are reached through bounds-checked
-        // buffers: rows past M fall behind the buffer's end, columns past N get an out-of-range offset.
+        // lanes per row: loads of the residual and stores then cover whole 64-byte row segments.  C and R are reached
+        // through bounds-checked buffers: rows past M fall behind the buffer's end, columns past N get an
+        // out-of-range offset.
+        // The residual is asked for two block rows ahead, and ahead of the next tile's DMA, which it would wait behind: block
+        // row by block row behind the DMA it was four round trips (4096x16384xK: K 1024 187 -> 162 us, 4096 507 -> 485).
         {
             const DmaProblem& g = grp.p[cprob];
             const int M = g.M, N = g.N, ldc = g.ldc, ldr = g.ldr;
-            const bool cacc = g.accumulate != 0;
-            void* const Cv = g.C;
-            const bf16_t* const R = g.R;
-            const __amdgpu_buffer_rsrc_t rsC = make_rsrc(Cv, (uint32_t)(((size_t)(M - 1) * ldc + N) * CES));
-            const __amdgpu_buffer_rsrc_t rsR = make_rsrc(R ? (const void*)R : (const void*)Cv, R ? (uint32_t)(((size_t)(M - 1) * ldr + N) * 2u) : 0u);
+            const __amdgpu_buffer_rsrc_t rsC = make_rsrc(g.C, (uint32_t)(((size_t)(M - 1) * ldc + N) * 2u));
+            const __amdgpu_buffer_rsrc_t rsR = make_rsrc(R ? (const void*)R : g.C, R ? (uint32_t)(((size_t)(M - 1) * ldr + N) * 2u) : 0u);
             char* const patch = smem + DSTAGES * 2 * DSTAGE_BYTES + wave * 4096;
             const int r_w = lane & 31;                       // row written, chunks 2g + hf
             const int r_r = lane >> 3, c_r = lane & 7;       // row (+ 8t) and chunk read back
-#pragma unroll
-            for (int i = 0; i < TM; i++) {
-                const uint32_t row_base = (uint32_t)(cm0 + wm + 32 * i + r_r);
-                float4 add[TN][4];
-                uint32_t off_c[TN][4];
+            const uint32_t row0 = (uint32_t)(cm0 + wm + r_r);
+            i32x2 res[2][TN][4];
+            auto ask = [&](int i) {
 #pragma unroll
                 for (int j = 0; j < TN; j++) {
                     const int col = cn0 + wn + 32 * j + 4 * c_r;
 #pragma unroll
-                    for (int t = 0; t < 4; t++) {
-                        const uint32_t row = row_base + 8 * t;
-                        off_c[j][t] = col < N ? (row * (uint32_t)ldc + (uint32_t)col) * CES : OUT_OF_RANGE;
-                        add[j][t] = make_float4(0.f, 0.f, 0.f, 0.f);
-                        if (OUT_F32) {
-                            if (cacc) {
-                                const i32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsC, off_c[j][t], 0, 0);
-                                add[j][t] = make_float4(__int_as_float(v[0]), __int_as_float(v[1]), __int_as_float(v[2]), __int_as_float(v[3]));
-                            }
-                        } else if (R) {
-                            const uint32_t off_r = col < N ? (row * (uint32_t)ldr + (uint32_t)col) * 2u : OUT_OF_RANGE;
-                            const i32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsR, off_r, 0, 0);
-                            add[j][t] = make_float4(lo_bf((uint32_t)v[0]), hi_bf((uint32_t)v[0]), lo_bf((uint32_t)v[1]), hi_bf((uint32_t)v[1]));
-                        }
-                    }
+                    for (int t = 0; t < 4; t++)
+                        res[i & 1][j][t] = __builtin_amdgcn_raw_buffer_load_b64(
+                            rsR, col < N ? ((row0 + 32 * i + 8 * t) * (uint32_t)ldr + (uint32_t)col) * 2u : OUT_OF_RANGE, 0, 0);
                 }
+            };
+            if (RES && R) { ask(0); ask(1); }
+#pragma unroll
+            for (int i = 0; i < TM; i++) {
 #pragma unroll
                 for (int j = 0; j < TN; j++) {
+                    const int col = cn0 + wn + 32 * j + 4 * c_r;
 #pragma unroll
-                    for (int g = 0; g < 4; g++)
-                        *reinterpret_cast<float4*>(patch + r_w * 128 + (((2 * g + hf) ^ ((r_w >> 1) & 7)) << 4)) =
-                            make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+                    for (int q = 0; q < 4; q++)
+                        *reinterpret_cast<float4*>(patch + r_w * 128 + (((2 * q + hf) ^ ((r_w >> 1) & 7)) << 4)) =
+                            make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
 #pragma unroll
                     for (int t = 0; t < 4; t++) {
                         const int rr = 8 * t + r_r;
                         float4 v = *reinterpret_cast<const float4*>(patch + rr * 128 + ((c_r ^ ((rr >> 1) & 7)) << 4));
-                        v.x += add[j][t].x; v.y += add[j][t].y; v.z += add[j][t].z; v.w += add[j][t].w;
-                        if (OUT_F32) {
-                            const i32x4 o = {__float_as_int(v.x), __float_as_int(v.y), __float_as_int(v.z), __float_as_int(v.w)};
-                            __builtin_amdgcn_raw_buffer_store_b128(o, rsC, off_c[j][t], 0, 0);
-                        } else {
-                            const i32x2 o = {(int)pack_bf2(v.x, v.y), (int)pack_bf2(v.z, v.w)};
-                            __builtin_amdgcn_raw_buffer_store_b64(o, rsC, off_c[j][t], 0, 0);
+                        if (RES && R) {
+                            const i32x2 u = res[i & 1][j][t];
+                            v.x += lo_bf((uint32_t)u[0]); v.y += hi_bf((uint32_t)u[0]); v.z += lo_bf((uint32_t)u[1]); v.w += hi_bf((uint32_t)u[1]);
                         }
+                        const i32x2 o = {(int)pack_bf2(v.x, v.y), (int)pack_bf2(v.z, v.w)};
+                        __builtin_amdgcn_raw_buffer_store_b64(
+                            o, rsC, col < N ? ((row0 + 32 * i + 8 * t) * (uint32_t)ldc + (uint32_t)col) * 2u : OUT_OF_RANGE, 0, 0);
                     }
+                }
+                if (RES && R) {
+                    if (i + 2 < TM) ask(i + 2);
+                    if (i == 1 && has_next) start_tile();
                 }
             }
         }
@@ -618,16 +610,16 @@ static int tail_shares(const GemmDesc& g, int tiles, int cus) {
 // Full rounds of one tile per compute unit run as one persistent workgroup per unit.  A last, partial round of R
 // tiles would leave most units idle, so it is cut along k into floor(units / R) shares per tile, which the same
 // workgroups take up after their whole tiles (fp32 partials in `ws`, summed in a fixed order by a small second kernel).
-template <int KIND>
+template <int KIND, bool RES>
 static auto dma_kernel() {
     if constexpr (KIND == GEMM_TN) return &k_gemm_dma_tn;
-    else return &k_gemm_dma<KIND, false>;
+    else return &k_gemm_dma<KIND, RES>;
 }
-template <int KIND, bool OUT_F32>
+template <int KIND, bool RES = false>
 static hipError_t launch_dma(const GemmDesc* g, int n, hipStream_t st) {
     constexpr int LDS = DSTAGES * 2 * DSTAGE_BYTES + 8 * 4096;   // two stages + the epilogue patches of the 8 waves
     static std::atomic<uint64_t> lds_ok{0};
-    auto kern = dma_kernel<KIND>();
+    auto kern = dma_kernel<KIND, RES>();
     const hipError_t e = allow_lds((const void*)kern, LDS, lds_ok);
     if (e != hipSuccess) return e;
     hipError_t ce = hipSuccess;
@@ -650,7 +642,7 @@ static hipError_t launch_dma(const GemmDesc* g, int n, hipStream_t st) {
     // one launch: a persistent workgroup per CU walks the whole tiles and then the k shares of the tail tiles
     const int n_items = full + tail * ksplit;
     kern<<<n_items < NUM_CU ? n_items : NUM_CU, 512, LDS, st>>>(grp, full, n_items, (float*)g[0].ws);
-    if (tail > 0) k_splitk_reduce<OUT_F32><<<tail * 64, 256, 0, st>>>((const float*)g[0].ws, full, grp);
+    if (tail > 0) k_splitk_reduce<KIND == GEMM_TN><<<tail * 64, 256, 0, st>>>((const float*)g[0].ws, full, grp);
     return hipGetLastError();
 }
 
@@ -913,10 +905,12 @@ static Plan plan(const GemmDesc* g, int n, bool whole_only) {
 }
 
 static hipError_t launch_tiles256(const GemmDesc* g, int n, hipStream_t st) {
+    bool res = false;
+    for (int i = 0; i < n; i++) res |= g[i].R != nullptr;
     switch (g[0].kind) {
-        case GEMM_NT: return launch_dma<GEMM_NT, false>(g, n, st);
-        case GEMM_NN: return launch_dma<GEMM_NN, false>(g, n, st);
-        default: return launch_dma<GEMM_TN, true>(g, n, st);
+        case GEMM_NT: return res ? launch_dma<GEMM_NT, true>(g, n, st) : launch_dma<GEMM_NT>(g, n, st);
+        case GEMM_NN: return res ? launch_dma<GEMM_NN, true>(g, n, st) : launch_dma<GEMM_NN>(g, n, st);
+        default: return launch_dma<GEMM_TN>(g, n, st);
     }
 }
 template <bool BWD>
