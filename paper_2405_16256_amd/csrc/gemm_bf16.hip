@@ -79,6 +79,15 @@ struct DmaGroup {
     }
 };
 
+// Instructions are fetched 32 bytes at a time, and where an 8-byte MFMA or the target of a branch lies in its 32 bytes decides whether
+// the two waves of a SIMD are fed in time: the same k loop takes up to 2.4 % longer 16 bytes further on (NT 4096x8192x12288 by 4-byte
+// steps from a 32-byte line: 627 627 630 622 636 628 629 623 us).  So the loops don't begin where the code before them happens to end
+// but WORDS instructions behind such a line; each kernel's number is the best of the eight for its loop as it stands.
+template <int WORDS>
+__device__ __forceinline__ void place_loop() {
+    asm volatile(".p2align 5\n\t.fill %0, 4, 0xbf800000" ::"n"(WORDS));   // s_nop
+}
+
 // NT or NN; RES: a problem has a residual, which is added to C.  A kernel of its own: what it holds costs the others registers.
 template <int KIND, bool RES>
 __global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_items, float* __restrict__ partial) {
@@ -170,6 +179,7 @@ __global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_
 #pragma unroll
         for (int j = 0; j < TN; j++) b0[j] = DB::frag(smem + DSTAGE_BYTES, wn + 32 * j, 0);
 
+        place_loop<KIND == GEMM_NT ? 3 : 7>();
         for (int kt = 0; kt < nk; kt++) {
             const char* cA = smem + (kt & 1) * (2 * DSTAGE_BYTES);
             const char* cB = cA + DSTAGE_BYTES;
@@ -311,7 +321,7 @@ __global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_
 // a wave has 64x32 each, one quadrant after the other over all k of a stage, so that each half of an operand's tile is read in one go
 // and its place refilled from then on: a request is on its way for 1.25 to 1.5 stages where k_gemm_dma leaves it 0.5 to 1, for a
 // second barrier per stage.  Half the fragments of both operands stay in registers (96).  4096x16384xK, four rounds of tiles,
-// k_gemm_dma's loop -> this one: K 2048 317 -> 303 us, 4096 510 -> 496, 8192 888 -> 877; 57344x8192x4096 3435 -> 3298.  NT and NN gain 1
+// k_gemm_dma's loop -> this one: K 2048 315 -> 296 us, 4096 502 -> 479, 8192 908 -> 897; 57344x8192x4096 3508 -> 3456.  NT and NN gain 1
 // to 2.5 % where the loop is long and the chip full, and lose as much or more elsewhere (NN 3300x4096x8192, 208 tiles, 175 -> 183):
 // they are at the power limit or bound by barriers.  Four waves of 128x128 (a third fewer LDS reads) take the same.
 __global__ __launch_bounds__(512) void k_gemm_dma_tn(DmaGroup grp, int full, int n_items, float* __restrict__ partial) {
@@ -453,6 +463,7 @@ __global__ __launch_bounds__(512) void k_gemm_dma_tn(DmaGroup grp, int full, int
             else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
             sync();
         };
+        place_loop<4>();
         for (int kt = 0; kt < nk; kt += 2) {
             stage(std::integral_constant<int, 0>{}, kt);
             if (kt + 1 < nk) stage(std::integral_constant<int, 1>{}, kt + 1);
