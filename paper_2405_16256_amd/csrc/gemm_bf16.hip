@@ -661,8 +661,12 @@ static hipError_t launch_dma(const GemmDesc* g, int n, hipStream_t st) {
 // row: not more than 64 KB a row, which takes it about as long as the reduction kernel's launch.
 static bool leaves_shares(const GemmDesc& g, int ksplit) { return (long)g.N * ksplit <= SPLIT_ROW && g.N % 8 == 0; }
 
+// Plan of one problem or of a group: the kernel variant, k splits, the order of the problems (longest k loop first), the
+// predicted time and, for several micro-batches, the problems (bits) whose sums over them are not formed one after the other.
+struct Plan { int v, ksplit[RING_MAX], order[RING_MAX]; double t; unsigned apart; };
+
 template <bool BWD, int MB, bool F, int NP, int BM, int BN, int WM, int WN, int NS>
-static hipError_t launch_ring_n(const GemmDesc* g, const int* order, const int* ksplit, int n, hipStream_t st) {
+static hipError_t launch_ring_n(const GemmDesc* g, const int* order, const int* ksplit, unsigned apart, int n, hipStream_t st) {
     constexpr int LDS = NS * (BM + BN) * DK * 2;
     static std::atomic<uint64_t> lds_ok{0};
     auto kern = k_gemm_ring<BWD, MB, F, NP, BM, BN, WM, WN, NS>;
@@ -708,14 +712,14 @@ static hipError_t launch_ring_n(const GemmDesc* g, const int* order, const int* 
         }
         starts[i] = p.first = first;
         p.micro = q.micro;
-        p.seq = q.kind == GEMM_TN && s == 1 ? q.micro : 1;
+        p.seq = q.kind == GEMM_TN && s == 1 && !(apart >> order[i] & 1) ? q.micro : 1;
         first += tiles * s * (q.micro / p.seq);
         if (q.split) *q.split = GemmSplit{nullptr, 1, BM, BN, (q.N + BN - 1) / BN};
         p.partial = partial;
-        if (s > 1) {
+        if (s > 1 || (q.kind == GEMM_TN && p.seq < q.micro)) {
             if (nk < s) return hipErrorInvalidValue;
             partial += (size_t)tiles * s * q.micro * BM * BN;
-            if (q.split && leaves_shares(q, s)) {
+            if (s > 1 && q.split && leaves_shares(q, s)) {
                 q.split->partial = p.partial;
                 q.split->ksplit = s;
                 continue;
@@ -732,23 +736,24 @@ static hipError_t launch_ring_n(const GemmDesc* g, const int* order, const int* 
             red_first += blocks * (q.out_f32 ? 1 : q.micro);
         }
     }
+    if (MB > 1 && (size_t)(partial - (float*)g[0].ws) * sizeof(float) > g[0].ws_room) return hipErrorInvalidValue;
     kern<<<first, WM * WN * 64, LDS, st>>>(starts[1], starts[2], starts[3], tn, grp);
     if (n_red) k_ring_reduce<MB, F, NP><<<red_first, 256, 0, st>>>(red_starts[1], red_starts[2], red_starts[3], red);
     return hipGetLastError();
 }
 
 template <bool BWD, bool F, int BM, int BN, int WM, int WN, int NS>
-static hipError_t launch_ring_f(const GemmDesc* g, const int* order, const int* ksplit, int n, hipStream_t st) {
-    if (g[0].micro > 1) return launch_ring_n<BWD, MICRO_MAX, F, RING_MAX, BM, BN, WM, WN, NS>(g, order, ksplit, n, st);
-    return n == 1 ? launch_ring_n<BWD, 1, F, 1, BM, BN, WM, WN, NS>(g, order, ksplit, n, st)
-                  : launch_ring_n<BWD, 1, F, RING_MAX, BM, BN, WM, WN, NS>(g, order, ksplit, n, st);
+static hipError_t launch_ring_f(const GemmDesc* g, const int* order, const int* ksplit, unsigned apart, int n, hipStream_t st) {
+    if (g[0].micro > 1) return launch_ring_n<BWD, MICRO_MAX, F, RING_MAX, BM, BN, WM, WN, NS>(g, order, ksplit, apart, n, st);
+    return n == 1 ? launch_ring_n<BWD, 1, F, 1, BM, BN, WM, WN, NS>(g, order, ksplit, apart, n, st)
+                  : launch_ring_n<BWD, 1, F, RING_MAX, BM, BN, WM, WN, NS>(g, order, ksplit, apart, n, st);
 }
 template <bool BWD, int BM, int BN, int WM, int WN, int NS>
-static hipError_t launch_ring(const GemmDesc* g, const int* order, const int* ksplit, int n, hipStream_t st) {
+static hipError_t launch_ring(const GemmDesc* g, const Plan& p, int n, hipStream_t st) {
     constexpr bool CAN = BM * BN <= (BWD ? fuse_tile(FUSE_SWIGLU_BWD) : fuse_tile(FUSE_ROPE));
     if constexpr (CAN)
-        if (g[0].fuse.kind) return launch_ring_f<BWD, true, BM, BN, WM, WN, NS>(g, order, ksplit, n, st);
-    return launch_ring_f<BWD, false, BM, BN, WM, WN, NS>(g, order, ksplit, n, st);
+        if (g[0].fuse.kind) return launch_ring_f<BWD, true, BM, BN, WM, WN, NS>(g, p.order, p.ksplit, p.apart, n, st);
+    return launch_ring_f<BWD, false, BM, BN, WM, WN, NS>(g, p.order, p.ksplit, p.apart, n, st);
 }
 
 // Which kernel, tile and k split: the smallest predicted time over the variants below.  A launch of W workgroups runs
@@ -774,9 +779,6 @@ static constexpr Variant VARIANTS[V_COUNT] = {
     {192, 192, 1, true, 1.81, 4.58, 0.960, 1.067},  {192, 256, 1, true, 2.07, 4.57, 1.085, 1.305},
     {256, 256, 1, false, 0.97, 5.44, 1.587, 1.639},
 };
-// Plan of one problem or of a group: the kernel variant, k splits, the order of the problems (longest k loop first) and
-// the predicted time.
-struct Plan { int v, ksplit[RING_MAX], order[RING_MAX]; double t; };
 static constexpr int SPLITS[] = {1, 2, 3, 4, 6, 8};
 
 // Time of a k stage in a last round of `busy` workgroups, one per CU.  Where each CU holds one workgroup at most anyway,
@@ -842,9 +844,16 @@ static Plan plan_one(const GemmDesc& g, bool whole_only) {
     return best;
 }
 
-// Several problems in one launch of one variant.  Its workgroups are handed out longest first; the launch ends with the
-// longest of them if all fit the chip at once, otherwise when the work is spent, give or take half a short one.  The
-// splits tried are those that bring every problem's k loop below a common length.
+// w workgroups of `least` to `most` k stages, `sum` in all, in one launch.  They are handed out longest first; the launch ends with the
+// longest of them if all fit the chip at once, otherwise when the work is spent, give or take half a short one.
+static double group_us(const Variant& q, long w, double most, double least, double sum) {
+    const double slots = 256.0 * q.per_cu;
+    if (w <= 256) return q.e + most * stage_us(q, w, most);
+    if (w <= slots) return q.e + most * q.t_full;
+    return std::max(q.e + most * q.t_full, (w * q.e + sum * q.t_full) / slots + 0.5 * (q.e + least * q.t_full));
+}
+
+// Several problems in one launch of one variant.  The splits tried are those that bring every problem's k loop below a common length.
 static Plan plan_group(const GemmDesc* g, int n) {
     double floor = 0.0;
     for (int i = 0; i < n; i++) floor += floor_us(g[i]);
@@ -877,14 +886,8 @@ static Plan plan_group(const GemmDesc* g, int n) {
                     most = std::max(most, ks); least = std::min(least, ks); sum += tiles * s * ks;
                 }
                 if (ws > g[0].ws_bytes) continue;
-                const double slots = 256.0 * q.per_cu;
-                double t;
-                if (w <= 256) t = q.e + most * stage_us(q, w, most);
-                else if (w <= slots) t = q.e + most * q.t_full;
-                else t = std::max(q.e + most * q.t_full, (w * q.e + sum * q.t_full) / slots + 0.5 * (q.e + least * q.t_full));
-                t = std::max(t, floor) + q.t0 + (ws ? 3.0 + reduce : 0.0);
-                p.t = t;
-                if (t < best.t) best = p;
+                p.t = std::max(group_us(q, w, most, least, sum), floor) + q.t0 + (ws ? 3.0 + reduce : 0.0);
+                if (p.t < best.t) best = p;
             }
     }
     auto len = [&](int i) { return (double)g[i].K / best.ksplit[i]; };
@@ -927,23 +930,67 @@ static hipError_t launch_tiles256(const GemmDesc* g, int n, hipStream_t st) {
 template <bool BWD>
 static hipError_t launch_variant(const GemmDesc* g, int n, const Plan& p, hipStream_t st) {
     switch (p.v) {
-        case V_64x64: return launch_ring<BWD, 64, 64, 2, 2, 4>(g, p.order, p.ksplit, n, st);
-        case V_64x128: return launch_ring<BWD, 64, 128, 2, 2, 3>(g, p.order, p.ksplit, n, st);
-        case V_128x128: return launch_ring<BWD, 128, 128, 2, 4, 4>(g, p.order, p.ksplit, n, st);
-        case V_128x128_2: return launch_ring<BWD, 128, 128, 2, 2, 2>(g, p.order, p.ksplit, n, st);
-        case V_128x256: return launch_ring<BWD, 128, 256, 2, 4, 3>(g, p.order, p.ksplit, n, st);
+        case V_64x64: return launch_ring<BWD, 64, 64, 2, 2, 4>(g, p, n, st);
+        case V_64x128: return launch_ring<BWD, 64, 128, 2, 2, 3>(g, p, n, st);
+        case V_128x128: return launch_ring<BWD, 128, 128, 2, 4, 4>(g, p, n, st);
+        case V_128x128_2: return launch_ring<BWD, 128, 128, 2, 2, 2>(g, p, n, st);
+        case V_128x256: return launch_ring<BWD, 128, 256, 2, 4, 3>(g, p, n, st);
     }
     if constexpr (!BWD) {
         switch (p.v) {
-            case V_192x128: return launch_ring<false, 192, 128, 2, 4, 4>(g, p.order, p.ksplit, n, st);
-            case V_192x192: return launch_ring<false, 192, 192, 2, 2, 3>(g, p.order, p.ksplit, n, st);
-            case V_192x256: return launch_ring<false, 192, 256, 2, 4, 2>(g, p.order, p.ksplit, n, st);
+            case V_192x128: return launch_ring<false, 192, 128, 2, 4, 4>(g, p, n, st);
+            case V_192x192: return launch_ring<false, 192, 192, 2, 2, 3>(g, p, n, st);
+            case V_192x256: return launch_ring<false, 192, 256, 2, 4, 2>(g, p, n, st);
         }
     }
     return launch_tiles256(g, n, st);
 }
+// A plan for several micro-batches: the tile and the k splits stay those of one, so that the bits do.  A workgroup forms a tile of a
+// weight gradient for one micro-batch after the other, or each micro-batch's product has a workgroup of its own and the reduction
+// adds them, in the same order: shorter k loops for the traffic of the partial sums.  The latter where it is predicted to take
+// under 0.85 of the time: on 130 launches (hidden 256 to 2048, 64 to 3000 tokens, 2 to 8 micro-batches) it takes 0.63 to 0.98 of it
+// there (three of 768x512 and 1536x512 over 2200 tokens with their input gradient 58.6 -> 49.6 us, eight of 768x768 over 1500
+// 81 -> 55), and 1.13 at most where it is predicted to take less at all.
+static Plan micro_plan(const GemmDesc* g, int n, const Plan& p) {
+    const Variant& q = VARIANTS[p.v];
+    const int micro = g[0].micro;
+    Plan best = p;
+    best.t = 1e30;
+    for (int apart = 0; apart < 2; apart++) {
+        Plan o = p;
+        double len[RING_MAX], most = 0.0, least = 1e30, sum = 0.0, reduce = 0.0, floor = 0.0;
+        long w = 0;
+        size_t ws = 0;
+        bool reduces = false;
+        for (int i = 0; i < n; i++) {
+            const int s = p.ksplit[i];
+            const long tiles = tiles_of(g[i], q);
+            const bool one = g[i].kind == GEMM_TN && s == 1, sums = one && !apart;   // whether a workgroup works for all micro-batches
+            len[i] = (double)((g[i].K + DK - 1) / DK) / s * (sums ? micro : 1);
+            if (one && apart) o.apart |= 1u << i;
+            const long wgs = tiles * s * (sums ? 1 : micro);
+            w += wgs;
+            most = std::max(most, len[i]); least = std::min(least, len[i]); sum += wgs * len[i];
+            floor += g[i].kind == GEMM_TN ? (2.0 * g[i].K * micro * ((double)g[i].M + g[i].N) + out_bytes(g[i])) / 5.0e6 : 0.0;
+            if (s == 1 && !(one && apart)) continue;
+            const size_t bytes = (size_t)wgs * q.bm * q.bn * sizeof(float);
+            ws += bytes;
+            if (s > 1 && g[i].split && leaves_shares(g[i], s)) continue;
+            reduces = true;
+            reduce += 2.0 * bytes / 6.5e6;
+        }
+        if (apart && (!o.apart || ws > g[0].ws_room)) break;
+        o.t = std::max(group_us(q, w, most, least, sum), floor) + (reduces ? 3.0 + reduce : 0.0);
+        for (int i = 1; i < n; i++)   // longest first
+            for (int j = i; j > 0 && len[o.order[j]] > len[o.order[j - 1]]; j--) std::swap(o.order[j], o.order[j - 1]);
+        if (o.t < 0.85 * best.t) best = o;
+    }
+    return best;
+}
+
 static hipError_t launch_planned(const GemmDesc* g, int n, const Plan& p, hipStream_t st) {
-    return g[0].kind == GEMM_NT ? launch_variant<false>(g, n, p, st) : launch_variant<true>(g, n, p, st);
+    if (g[0].kind == GEMM_NT) return launch_variant<false>(g, n, p, st);
+    return launch_variant<true>(g, n, g[0].micro > 1 ? micro_plan(g, n, p) : p, st);
 }
 
 // The segments of a segmented problem one after the other, each adding to what the ones before it have left in C.
@@ -1164,6 +1211,20 @@ extern "C" int hh_internal_gemm_plan(const int* problems, int n, char* out, size
         at += (size_t)w;
     }
     return 0;
+}
+// The weight gradients (bits) of a launch of several micro-batches whose products are apart, with that much room for partial sums.
+extern "C" int hh_internal_products_apart(const int* problems, int n, int micro, size_t room) {
+    using namespace hh;
+    if (n < 1 || n > RING_MAX) return -1;
+    GemmDesc g[RING_MAX];
+    for (int i = 0; i < n; i++) {
+        g[i] = sizes_of(problems + 6 * i);
+        g[i].micro = micro; g[i].ws_room = room;
+    }
+    Route r;
+    route(g, n, r);
+    const Plan& p = n > 1 ? r.group : r.each[0];
+    return (n > 1) != (r.how == Route::RING) || p.v >= V_DMA ? -1 : (int)micro_plan(g, n, p).apart;
 }
 // n / d as the kernels form it
 extern "C" int hh_internal_quotient(int n, int d) { return hh::quotient(n, hh::divisor(d)); }

@@ -234,7 +234,7 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
     // gate|up, two tiles as large as the product, hold up the k tiles behind them (700x2048x1024 12.2 -> 12.6).
     constexpr bool EARLY = TM * TN <= 2 && !(KIND == GEMM_NN && FUSES);
     Beside beside[EARLY ? TM : 1][EARLY ? TN : 1];
-    if (EARLY && ksplit == 1 && !(SUMS && seq > 1)) {
+    if (EARLY && ksplit == 1 && !SUMS) {
 #pragma unroll
         for (int i = 0; i < TM; i++)
 #pragma unroll
@@ -397,7 +397,8 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
         }
     }
 
-    if (ksplit > 1) {   // a share of the k range: raw fp32 sums, finished by k_ring_reduce
+    // a share of the k range, or one micro-batch's product of several: raw fp32 sums, finished by k_ring_reduce
+    if (ksplit > 1 || (SUMS && seq == 1)) {
         float* pt = g.partial + (((size_t)(tm * tiles_n + tn) * (MB == 1 ? 1 : g.micro) + micro) * ksplit + share) * (BM * BN);
 #pragma unroll
         for (int i = 0; i < TM; i++)

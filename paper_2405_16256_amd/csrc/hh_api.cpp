@@ -127,6 +127,7 @@ struct hh_ctx {
     bool trace_on;
     uint32_t trace_mask;          // families recorded while trace_on
     void* gemm_ws;                // k-split scratch inside the caller's workspace, set by each hot call
+    size_t gemm_room;             // its bytes where several micro-batches go side by side, set by each such call
     std::vector<float*> retired_tables;   // rotary tables replaced by a larger one: freed with the context
 };
 
@@ -394,7 +395,7 @@ struct Traced {
     } while (0)
 static double attn_flop(const Dims& d) { return 4.0 * d.d * d.B * d.nh * ((double)d.S * (d.S + 1) / 2); }
 static double gemm_flop(const GemmDesc& g) { return 2.0 * g.M * g.N * g.K * g.micro; }
-static void gemm_scratch(const hh_ctx* ctx, GemmDesc& g) { g.ws = ctx->gemm_ws; g.ws_bytes = ctx->gemm_ws ? GEMM_WS_BYTES : 0; }
+static void gemm_scratch(const hh_ctx* ctx, GemmDesc& g) { g.ws = ctx->gemm_ws; g.ws_bytes = ctx->gemm_ws ? GEMM_WS_BYTES : 0; g.ws_room = ctx->gemm_room; }
 // A group of GEMMs in one call.  Where they share a launch it is bracketed once and its time shared out to the members by
 // their flops; members with launches of their own are traced (and launched, in the same way) one by one.
 static hipError_t tgemm(hh_ctx* ctx, int dt, GemmDesc* g, int n, hipStream_t st) {
@@ -947,6 +948,7 @@ static int stage_run(hh_ctx* ctx, const hh_layer_cfg* cfg, int n_layers, const h
         char* const ws = side.in_pool ? p.base + (size_t)side.n * p.per_micro : (char*)workspace;
         void* const gbuf = ws + unit - act_bytes(d);
         void* const gemm_ws = side.in_pool ? workspace : ws + (size_t)side.n * unit;
+        ctx->gemm_room = wl.total + act_bytes(d) - (side.in_pool ? 0 : (size_t)side.n * unit);
         for (int i = 0, m = 0; i < passes; i++) {   // as alike as they can be
             const int n = (n_micro - m + passes - i - 1) / (passes - i);
             const Pass ps{n, d.dt == DT_BF16 ? &sl : nullptr, p.base, p.per_micro, ws, unit, x + m, y + m, dy + m, dx + m};

@@ -55,6 +55,7 @@ struct GemmDesc {
     const void* B2; int k2;
     void* ws;                // optional scratch for k-split partial sums (bf16 path), may be NULL
     size_t ws_bytes;         // of one micro-batch: what a plan may use
+    size_t ws_room;          // micro > 1: what there is for all of them
     GemmFuse fuse;
     GemmSplit* split;        // not null: the launch may leave its partial sums (ksplit > 1 then, else C is complete)
     int micro;               // micro-batches; above 1 (bf16: where gemm_bf16_on_ring) their operands are in `each`
