@@ -63,8 +63,25 @@ struct RingGroup {
     RingProblem<MB, F> p[NP];
 };
 
-template <int KIND, int MB, bool F, int BM, int BN, int WM, int WN, int NS>
-__device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
+// A launch whose problems (NT, one A) norm the rows of A on the way in: A holds x, and the product is that of xn = x * r * gain.
+template <int MB>
+struct RingNorm {
+    Ops<MB> xn, r;
+    const bf16_t* gain;
+    float eps;
+    int writer;   // the problem whose first column of tiles writes xn and r
+};
+
+// v of the lane N before it of its 16, in a circle
+template <int N>
+__device__ __forceinline__ float rotated(float v) { return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x120 + N, 0xf, 0xf, true)); }
+
+// NORM (K up to NORM_K): the tile's rows of x come into registers, are normed as k_rmsnorm_fwd norms them, to the same bits, and lie in
+// LDS for all of k; only B goes through the ring.  Bound by latency: the launch before it (3.6 us with the gap behind it, of rows of 256)
+// goes, and the workgroups get 1.2 to 1.9 us longer, for about 500 instructions between x and its place in LDS.
+template <int KIND, int MB, bool F, int BM, int BN, int WM, int WN, int NS, bool NORM = false>
+__device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g, const RingNorm<MB>* norm = nullptr, bool writer = false) {
+    if constexpr (NORM) asm volatile("" ::"s"(norm->gain), "s"(norm->eps), "s"(g.K), "s"(g.M), "s"(g.N));
     // what the first operand requests need, loaded at once
     asm volatile("" ::"s"(g.A.p[0]), "s"(g.B.p[0]), "s"(g.a_bytes), "s"(g.b_bytes), "s"(g.lda), "s"(g.ldb), "s"(g.first), "s"(g.nk),
                  "s"(g.map.tiles_m), "s"(g.map.tiles_n), "s"(g.map.width.d), "s"(g.map.width.mul), "s"(g.map.width.shift), "s"(g.map.last.d),
@@ -75,8 +92,9 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
     using DB = DmaTile<(KIND == GEMM_NT), BN, NW>;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr bool FUSES = F && KIND != GEMM_TN;
-    constexpr int STAGE = DA::BYTES + DB::BYTES;
-    constexpr int PW = DA::PER_WAVE + DB::PER_WAVE;       // DMA instructions per wave and stage
+    constexpr int STAGE = (NORM ? 0 : DA::BYTES) + DB::BYTES;
+    constexpr int PW = (NORM ? 0 : DA::PER_WAVE) + DB::PER_WAVE;       // DMA instructions per wave and stage
+    static_assert(!NORM || (KIND == GEMM_NT && BM / NW % 4 == 0 && BM * BN == 64 * 64), "16 lanes a row, one MFMA a k step");
     static_assert(NS * STAGE >= NW * 4096, "the epilogue patches reuse the ring");
     extern __shared__ __attribute__((aligned(1024))) char smem[];   // [stage][A | B]
     const int M = g.M, N = g.N, K = g.K, lda = g.lda, ldb = g.ldb, ldc = g.ldc, ldr = g.ldr, ksplit = g.ksplit.d;
@@ -131,7 +149,8 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
         }
         voB[i] = DB::voff(wave, i, row0, ldb) + kbeg * stepB;
     }
-    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
+    const int ring = NORM ? nk_all * DA::BYTES : 0;   // LDS: x's k tiles, then the ring
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem + ring);
     const int kseg0 = g.kseg[0], kseg1 = g.kseg[1];
     int kissue = kbeg, missue = micro;   // k tile and micro-batch that `issue` fetches next
     auto next_tile = [&]() {
@@ -153,12 +172,12 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
         constexpr int Q = decltype(quarter)::value;
         const uint32_t base = lds0 + slot * STAGE;
 #pragma unroll
-        for (int i = 0; i < DA::PER_WAVE; i++)
+        for (int i = 0; i < (NORM ? 0 : DA::PER_WAVE); i++)
             if (Q < 0 || i * 4 / PW == Q) { dma16(base + (wave * DA::PER_WAVE + i) * 1024, voA[i], rsA); voA[i] += stepA; }
 #pragma unroll
         for (int i = 0; i < DB::PER_WAVE; i++)
             if (Q < 0 || (DA::PER_WAVE + i) * 4 / PW == Q) {
-                dma16(base + DA::BYTES + (wave * DB::PER_WAVE + i) * 1024, voB[i], rsB);
+                dma16(base + (NORM ? 0 : DA::BYTES) + (wave * DB::PER_WAVE + i) * 1024, voB[i], rsB);
                 voB[i] += stepB;
             }
     };
@@ -177,6 +196,24 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
     // chains (nine launches of a 700-token forward pass 67.4 -> 69.3), and not beside the transposing fragment reads of NN
     // and TN (backward of hidden 448, 3348 tokens: 176 -> 182).
     constexpr bool SPREAD = KIND == GEMM_NT && NS > 2 && BM * BN >= 128 * 128;
+    // NORM: lane `sub` of 16 has the 16-byte pieces sub, sub + 16, .. of four of the wave's rows
+    constexpr int ROWS = NORM ? BM / NW / 4 : 1, PIECES = NORM ? NORM_K / 128 : 1;
+    i32x4 row[ROWS][PIECES], gain[PIECES];
+    float rstd[ROWS];
+    const int sub = lane & 15, row0 = wave * (BM / NW) + (lane >> 4);
+    if constexpr (NORM) {
+        // past a row's or the gain's end: an offset that is out of range
+        const __amdgpu_buffer_rsrc_t rsX = make_rsrc(g.A.at(micro), g.a_bytes), rsG = make_rsrc(norm->gain, (uint32_t)K * 2u);
+#pragma unroll
+        for (int p = 0; p < PIECES; p++) {
+            const int col = 128 * p + 8 * sub;
+#pragma unroll
+            for (int q = 0; q < ROWS; q++)
+                row[q][p] = __builtin_amdgcn_raw_buffer_load_b128(
+                    rsX, col < K ? ((uint32_t)(m0 + row0 + 4 * q) * (uint32_t)lda + (uint32_t)col) * 2u : 0x80000000u, 0, 0);
+            gain[p] = __builtin_amdgcn_raw_buffer_load_b128(rsG, (uint32_t)col * 2u, 0, 0);
+        }
+    }
 #pragma unroll
     for (int s = 0; s < NS; s++)
         if (s < nt) issue(s);
@@ -228,6 +265,57 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
             }
         }
     };
+    if constexpr (NORM) {
+        auto widen = [](const i32x4& v, float (&f)[8]) {
+#pragma unroll
+            for (int e = 0; e < 4; e++) { f[2 * e] = lo_bf((uint32_t)v[e]); f[2 * e + 1] = hi_bf((uint32_t)v[e]); }
+        };
+        float ss[ROWS];
+#pragma unroll
+        for (int q = 0; q < ROWS; q++) {
+            float sum[PIECES];
+#pragma unroll
+            for (int p = 0; p < PIECES; p++) {
+                float f[8];
+                widen(row[q][p], f);
+                sum[p] = 0.f;
+#pragma unroll
+                for (int e = 0; e < 8; e++) sum[p] += f[e] * f[e];
+            }
+            static_assert(PIECES == 2, "added up as a wave's lanes with a piece each do it");
+            ss[q] = sum[0] + sum[1];
+        }
+#pragma unroll
+        for (int q = 0; q < ROWS; q++) { ss[q] += rotated<8>(ss[q]); ss[q] += rotated<4>(ss[q]); ss[q] += rotated<2>(ss[q]); ss[q] += rotated<1>(ss[q]); }
+        static_assert(ROWS == 4, "a lane of every four forms the factor of one of the four rows");
+        const float mine = (sub & 2) ? ((sub & 1) ? ss[3] : ss[2]) : ((sub & 1) ? ss[1] : ss[0]);
+        const int factor = __float_as_int(1.0f / sqrtf(mine / (float)K + norm->eps));
+        rstd[0] = __int_as_float(__builtin_amdgcn_mov_dpp(factor, 0x00, 0xf, 0xf, true));   // lane 0 of its four, 1, 2, 3
+        rstd[1] = __int_as_float(__builtin_amdgcn_mov_dpp(factor, 0x55, 0xf, 0xf, true));
+        rstd[2] = __int_as_float(__builtin_amdgcn_mov_dpp(factor, 0xaa, 0xf, 0xf, true));
+        rstd[3] = __int_as_float(__builtin_amdgcn_mov_dpp(factor, 0xff, 0xf, 0xf, true));
+#pragma unroll
+        for (int p = 0; p < PIECES; p++) {
+            float gg[8];
+            widen(gain[p], gg);
+#pragma unroll
+            for (int q = 0; q < ROWS; q++) {
+                float f[8];
+                widen(row[q][p], f);
+#pragma unroll
+                for (int e = 0; e < 8; e++) f[e] = f[e] * rstd[q] * gg[e];
+                row[q][p] = i32x4{(int)pack_bf2(f[0], f[1]), (int)pack_bf2(f[2], f[3]), (int)pack_bf2(f[4], f[5]), (int)pack_bf2(f[6], f[7])};
+            }
+            if (128 * p + 8 * sub < K) {   // DmaTile's place of row r, piece sub % 8 of k tile 2p + sub / 8
+#pragma unroll
+                for (int q = 0; q < ROWS; q++) {
+                    const int r = row0 + 4 * q;
+                    *reinterpret_cast<i32x4*>(smem + (2 * p + (sub >> 3)) * DA::BYTES + r * 128 + (((sub & 7) ^ ((r >> 1) & 7)) << 4)) = row[q][p];
+                }
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
     // Asked for behind the requests of the first k tiles on the smaller tiles, whose epilogue would otherwise be a round trip to
     // memory: 128x768x256 with rotary embedding 4.2 -> 4.0 us, 700x1536x1024 10.6 -> 10.1, 128x256x256 with residual 3.33 -> 3.30.
     // Of three or four blocks a wave, 64 registers, it costs more than it gives (1100x3072x3072 with residual 27.4 -> 28.2), and
@@ -300,9 +388,9 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
         // step the loop is bound by its loads from L2 and the registers of a second k tile only cost (64x128 tiles 3 %
         // slower, 192x192 ones 20 %).
         bf16x8 fa[2][4][TM], fb[2][4][TN];
-        auto fetch = [&](int set, int slot, int kk) {
-            const char* cA = smem + slot * STAGE;
-            const char* cB = cA + DA::BYTES;
+        auto fetch = [&](int set, int slot, int kt, int kk) {
+            const char* cA = smem + (NORM ? kt * DA::BYTES : slot * STAGE);
+            const char* cB = NORM ? smem + ring + slot * STAGE : cA + DA::BYTES;
 #pragma unroll
             for (int i = 0; i < TM; i++) fa[set][kk][i] = DA::frag(cA, wm + 32 * i, kk);
 #pragma unroll
@@ -322,7 +410,7 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
             const bool more = kt + 1 < nt;
             if (more) {
 #pragma unroll
-                for (int kk = 0; kk < 4; kk++) fetch(Q, next, kk);
+                for (int kk = 0; kk < 4; kk++) fetch(Q, next, kt + 1, kk);
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -339,7 +427,7 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
             slot = next;
         };
 #pragma unroll
-        for (int kk = 0; kk < 4; kk++) fetch(0, 0, kk);
+        for (int kk = 0; kk < 4; kk++) fetch(0, 0, 0, kk);
         for (int kt = 0; kt < nt; kt += 2) {
             step(std::integral_constant<int, 0>{}, kt);
             if (kt + 1 < nt) step(std::integral_constant<int, 1>{}, kt + 1);
@@ -394,6 +482,23 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g) {
             fold();
             freed = slot;
             slot = next;
+        }
+    }
+
+    if constexpr (NORM) {
+        if (writer && tn == 0) {
+            bf16_t* const xn = (bf16_t*)norm->xn.at(micro);
+            float* const rr = (float*)norm->r.at(micro);
+#pragma unroll
+            for (int q = 0; q < ROWS; q++) {
+                const int r = m0 + row0 + 4 * q;
+                if (r < M) {
+                    if (sub == 0) rr[r] = rstd[q];
+#pragma unroll
+                    for (int p = 0; p < PIECES; p++)
+                        if (128 * p + 8 * sub < K) *reinterpret_cast<i32x4*>(xn + (size_t)r * K + 128 * p + 8 * sub) = row[q][p];
+                }
+            }
         }
     }
 
@@ -515,6 +620,13 @@ __global__ __launch_bounds__(WM * WN * 64, BM * BN / (WM * WN) > 64 * 128 ? 1 : 
     if (!BWD) ring_body<GEMM_NT, MB, F, BM, BN, WM, WN, NS>(g);
     else if (F || !(tn >> i & 1)) ring_body<GEMM_NN, MB, F, BM, BN, WM, WN, NS>(g);
     else ring_body<GEMM_TN, MB, F, BM, BN, WM, WN, NS>(g);
+}
+
+// NT problems that norm the rows of A, which they share
+template <int MB, bool F, int NP, int BM, int BN, int WM, int WN, int NS>
+__global__ __launch_bounds__(WM * WN * 64, 2) void k_gemm_ring_norm(int second, int third, int fourth, RingNorm<MB> norm, RingGroup<MB, F, NP> grp) {
+    const int i = NP == 1 ? 0 : own_problem(Firsts{second, third, fourth});
+    ring_body<GEMM_NT, MB, F, BM, BN, WM, WN, NS, true>(grp.p[i], &norm, i == norm.writer);
 }
 
 // Sums the ksplit fp32 shares of every BM x BN tile of the group's split problems in a fixed order and applies the

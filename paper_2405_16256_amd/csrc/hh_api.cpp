@@ -467,7 +467,7 @@ static GemmDesc desc(int kind, int M, int N, int K, const void* A, int lda, cons
     g.kind = kind; g.M = M; g.N = N; g.K = K; g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc;
     g.R = R; g.ldr = ldr; g.out_f32 = out_f32; g.accumulate = acc; g.ws = nullptr; g.ws_bytes = 0;
     g.B1 = g.B2 = nullptr; g.k1 = g.k2 = 0;
-    g.fuse = GemmFuse{}; g.split = nullptr;
+    g.fuse = GemmFuse{}; g.split = nullptr; g.norm = nullptr;
     g.micro = 1; g.each = nullptr;
     return g;
 }
@@ -577,8 +577,16 @@ static int layer_fwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_la
             f.qkv[i].fuse = GemmFuse{FUSE_ROPE, d.d, f.n_qkv == 1 ? A + Akv : i < 2 ? f.qkv[i].N : 0, d.S, ctx->rope_seq, ctx->rope_table, nullptr, nullptr};
     if (gates) f.gu[0].fuse = GemmFuse{FUSE_SWIGLU, 2 * F, 0, 0, 0, nullptr, m.p[0], nullptr};
 
-    TR(HH_TRACE_ELEMENTWISE, 2.0 * T * H * es, rmsnorm_fwd(dt, p.each(x), w->g_attn, p.each(at(saved, sl.xn)), p.each(at(saved, sl.r1)), p.n, T, H,
-                                                           cfg->rms_eps, st));
+    // a norm is a launch of its own, or the first thing in its projections'
+    auto norms = [&](GemmDesc* g, int n, const GemmNorm& q, const void* from) {
+        for (int i = 0; i < n; i++) gemm_scratch(ctx, g[i]);
+        if (dt != DT_BF16 || !gemm_bf16_norms(g, n)) return false;
+        for (int i = 0; i < n; i++) { g[i].A = from; g[i].norm = &q; }
+        return true;
+    };
+    const GemmNorm first{p.each(at(saved, sl.xn)), p.each(at(saved, sl.r1)), w->g_attn, cfg->rms_eps};
+    if (!norms(f.qkv, f.n_qkv, first, x))
+        TR(HH_TRACE_ELEMENTWISE, 2.0 * T * H * es, rmsnorm_fwd(dt, p.each(x), w->g_attn, first.xn, first.r, p.n, T, H, cfg->rms_eps, st));
     HIP_TRY(pgemm(ctx, p, dt, f.qkv, f.n_qkv, st));
     if (!rotates) TR(HH_TRACE_ELEMENTWISE, 2.0 * T * (A + Akv) * es, rope(dt, qkv, Q3, p.n, T, d.S, d.nh + d.nkv, d.d, ctx->rope_table, ctx->rope_seq, st));
     TR(HH_TRACE_ATTN_FWD, attn_flop(d), attn_fwd(dt, qkv.p[0], Q3, at(saved, sl.a), (float*)at(saved, sl.lse), d.B, d.S, d.nh, d.nkv, d.d,
@@ -588,8 +596,10 @@ static int layer_fwd_impl(hh_ctx* ctx, const Pass& p, const Dims& d, const hh_la
     HIP_TRY(pgemm(ctx, p, dt, f.out, st));
     const bool sums = left.ksplit > 1;
     const Each res = p.each(x);
-    TR(HH_TRACE_ELEMENTWISE, 2.0 * T * H * es, rmsnorm_fwd(dt, h, w->g_mlp, p.each(at(saved, sl.hn)), p.each(at(saved, sl.r2)), p.n, T, H,
-                                                           cfg->rms_eps, st, sums ? &left : nullptr, &res));
+    const GemmNorm second{p.each(at(saved, sl.hn)), p.each(at(saved, sl.r2)), w->g_mlp, cfg->rms_eps};
+    if (sums || !norms(f.gu, f.n_gu, second, h.p[0]))
+        TR(HH_TRACE_ELEMENTWISE, 2.0 * T * H * es, rmsnorm_fwd(dt, h, w->g_mlp, second.xn, second.r, p.n, T, H, cfg->rms_eps, st, sums ? &left : nullptr,
+                                                               &res));
     HIP_TRY(pgemm(ctx, p, dt, f.gu, f.n_gu, st));
     if (!gates) TR(HH_TRACE_ELEMENTWISE, 3.0 * T * F * es, swiglu_fwd(dt, p.each(at(saved, sl.gu)), m, p.n, T, F, st));
     HIP_TRY(pgemm(ctx, p, dt, f.down, st));

@@ -41,6 +41,9 @@ struct GemmFuse {
 struct GemmSplit { const float* partial; int ksplit, bm, bn, tiles_n; };
 // The launch leaves at most SPLIT_ROW of them for a row, in two shares or more: rows of at most SPLIT_COLUMNS columns.
 constexpr int SPLIT_ROW = 16384, SPLIT_COLUMNS = SPLIT_ROW / 2;
+// The RMSNorm of the rows of A on the way into an NT launch: xn and r (of each micro-batch) are written beside the product.
+struct GemmNorm { Each xn, r; const void* gain; float eps; };
+constexpr int NORM_K = 256;
 struct GemmDesc {
     int kind;
     int M, N, K;
@@ -58,6 +61,7 @@ struct GemmDesc {
     size_t ws_room;          // micro > 1: what there is for all of them
     GemmFuse fuse;
     GemmSplit* split;        // not null: the launch may leave its partial sums (ksplit > 1 then, else C is complete)
+    const GemmNorm* norm;    // not null (bf16, where gemm_bf16_norms): A holds x, and xn takes its place; one for a launch
     int micro;               // micro-batches; above 1 (bf16: where gemm_bf16_on_ring) their operands are in `each`
     const GemmMicro* each;
 };
@@ -74,6 +78,8 @@ hipError_t gemm(int dtype, const GemmDesc* g, int n, hipStream_t st);
 // those launches keeps, its workgroups, and the largest tile.
 struct RingUse { size_t partial; long workgroups; int tile; };
 bool gemm_bf16_on_ring(const GemmDesc* g, int n, RingUse* use);
+// Whether one launch of these problems (NT, one A) can norm the rows of A, and had better.
+bool gemm_bf16_norms(const GemmDesc* g, int n);
 // Whether they do; if not, gemm() on each of them alone launches the same.
 bool gemm_shares_launch(int dtype, const GemmDesc* g, int n);
 
