@@ -420,12 +420,6 @@ struct RopeRow {
             }
     }
 };
-// everyone's LDS accesses are done; loads into registers stay in flight
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
 
 // --------------------------------------------------------------- backward: dQ
 // The job of query block qb of (head, sample) hb = h + nh*b.  NPAR as in k_attn_fwd: with 2, the even and the

@@ -136,6 +136,14 @@ inline hipError_t allow_lds(const void* kern, int bytes, std::atomic<uint64_t>& 
     return e;
 }
 
+// ---- barriers -----------------------------------------------------------------
+// everyone's LDS accesses are done; loads into registers stay in flight
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 // ---- wave / block reductions -----------------------------------------------
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

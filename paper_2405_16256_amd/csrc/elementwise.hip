@@ -357,23 +357,39 @@ __global__ __launch_bounds__(CSW * WAVE) void k_colsum_reduce(ColSums<N> sums, i
     float4* const out = reinterpret_cast<float4*>(j.out + col);
     float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
     if (owner && accumulate) sum = *out;
+    // A thread's first rows of the next micro-batch, all of them with up to 256 rows, are asked for before this one's are combined: a round
+    // trip to memory less for each (2 layers of hidden 512, three micro-batches of 2200 tokens 714 -> 707 us; 4 of hidden 256 1181 -> 1172).
+    constexpr int GROUPS = CSW * WAVE / 16, AHEAD = 4;
+    float4 next[AHEAD];
+    auto ask = [&](int m) {
+        const float* p = (const float*)j.partial.at(m) + col;
+#pragma unroll
+        for (int q = 0; q < AHEAD; q++) {
+            const int i = threadIdx.x / 16 + q * GROUPS;
+            next[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (col < H && i < j.rows) next[q] = *reinterpret_cast<const float4*>(p + (size_t)i * H);
+        }
+    };
+    ask(0);
     for (int m = 0; m < (N == 1 ? 1 : n); m++) {   // each micro-batch's sum is added to those before it, as n calls would
         float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int q = 0; q < AHEAD; q++) { s.x += next[q].x; s.y += next[q].y; s.z += next[q].z; s.w += next[q].w; }
         if (col < H) {
             const float* p = (const float*)j.partial.at(m) + col;
-#pragma unroll 4
-            for (int i = threadIdx.x / 16; i < j.rows; i += CSW * WAVE / 16) {
+            for (int i = threadIdx.x / 16 + AHEAD * GROUPS; i < j.rows; i += GROUPS) {
                 const float4 v = *reinterpret_cast<const float4*>(p + (size_t)i * H);
                 s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
             }
         }
+        if (N > 1 && m + 1 < n) ask(m + 1);
 #pragma unroll
         for (int o = 16; o < WAVE; o *= 2) {
             s.x += __shfl_xor(s.x, o, WAVE); s.y += __shfl_xor(s.y, o, WAVE);
             s.z += __shfl_xor(s.z, o, WAVE); s.w += __shfl_xor(s.w, o, WAVE);
         }
         if ((threadIdx.x & (WAVE - 1)) < 16) red[m & 1][wave][cx] = s;
-        __syncthreads();   // red[m & 1] is written again two barriers after its readers
+        lds_barrier();   // red[m & 1] is written again two barriers after its readers
         if (owner) {
             float4 t = red[m & 1][0][cx];
 #pragma unroll
