@@ -12,7 +12,7 @@
 //     one whole 128-byte line per stage.  The loop is laid out by hand: MFMAs of one k step
 //     interleaved with the LDS fragment reads of the next, one barrier per stage placed
 //     before its last k step, after which the other stage's first fragments and the DMA of
-//     the stage after that are issued.
+//     the stage after that are issued.  TN problems have the same tile with another loop (k_gemm_dma_tn).
 //   * k_gemm_ring (gemm_ring.h): tiles of 64x64 to 192x256 with rings of 2 to 4 stages, for
 //     problems that 256x256 tiles would leave most of the chip idle on.
 // plan() picks kernel, tile and k split, and whether problems share a launch, by a cost model fitted to measured times.

@@ -23,11 +23,11 @@ namespace hh {
 //
 // A problem may stand for the same product in `micro` micro-batches.  NT, NN and split TN ones then own that many times the
 // workgroups; a workgroup of an unsplit TN problem walks the k loops of all of them, in order, and adds each product to the
-// sum of those before it (`seq` of them), so that the gradient is read and written once.  Tile and split are those of a
-// micro-batch by itself, so every result is what a launch per micro-batch gives, bit for bit.  Bound as before by one
-// workgroup's chain and by launch latency, of which there are fewer: a 4-layer stage of hidden 256, 128 tokens and 8
-// micro-batches, two at a time, 2671 -> 1485 us; 2 layers of hidden 512, 2200 tokens, 3 micro-batches, 1092 -> 744 us (1385 and
-// 706 to 758 by run, with what came after).
+// sum of those before it (`seq` of them), so that the gradient is read and written once; or each product has a workgroup of its
+// own (seq 1) and the reduction adds them in that order.  Tile and split are those of a micro-batch by itself, so every result is
+// what a launch per micro-batch gives, bit for bit.  Bound as before by one workgroup's chain and by launch latency, of which
+// there are fewer: a 4-layer stage of hidden 256, 128 tokens and 8 micro-batches, two at a time, 2671 -> 1485 us; 2 layers of
+// hidden 512, 2200 tokens, 3 micro-batches, 1092 -> 744 us (1172 and 665 to 707 by run, with what came after).
 //
 // Fused problems (GemmFuse): the workgroup's columns come in pair_column's order, so that an accumulator lane owns a column
 // and its partner, 4q + e and 4(q + 2) + e of a block.  C is written back in its own order, in runs of 16 columns.  Bound by launch
