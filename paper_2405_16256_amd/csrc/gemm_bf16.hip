@@ -1120,9 +1120,11 @@ bool gemm_bf16_shares_launch(const GemmDesc* g, int n) {
 // Weight gradients that 256x256 tiles would take, of too few tokens for those to be cut along k: several micro-batches go to the
 // ring kernel all the same, which forms the same bits (whole k loops in order) and reads and writes a gradient once for all
 // of them, which is most of the traffic of such a launch.  2 layers of hidden 4096, ffn 11008, 64 tokens, 8 micro-batches:
-// 10.6 -> 4.4 ms.  One tile for all of them: 16 such stages (hidden 3584 to 12160, 3 to 122 tokens) take 0.4 to 6 % longer with
-// 128x128 tiles, one workgroup a CU, 6 % less to 3 % more with 64x128 ones, and 2 to 10 % less with two 128x128 workgroups a CU.
-constexpr int WHOLE_DW = V_128x256;
+// 10.6 -> 4.4 ms.  One tile for all of them: two 128x128 workgroups a CU, of which one loads while the other writes.  24 random
+// stages (hidden 2112 to 11776, 4 to 431 tokens, 2 to 8 micro-batches) take 0.90 to 1.00 of what they do with one workgroup of
+// 128x256 (hidden 9856, 38 tokens, 8 micro-batches 6893 -> 6220 us; from 128 tokens on no change); with one of 128x128 16 others
+// took 0.4 to 6 % longer, with 64x128 ones 6 % less to 3 % more.
+constexpr int WHOLE_DW = V_128x128_2;
 static bool whole_dw(const GemmDesc& g) { return g.kind == GEMM_TN && (g.K + DK - 1) / DK < 8; }   // see tail_shares
 
 bool gemm_bf16_on_ring(const GemmDesc* g, int n, RingUse* use) {
