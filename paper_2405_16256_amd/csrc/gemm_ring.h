@@ -189,6 +189,9 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g, const Rin
     // no MFMA and no fragment read meanwhile.  So the requests that refill a slot come behind the next k tile's first fragment
     // reads and the MFMAs that need no others (64x64 tiles: behind the third of four): in front of them, 700x1024x1024 took 7.0 us
     // (NN) and 7.2 (NT with residual) where it takes 6.4 and 6.8, 333x4096x4096 NN 25.7 (24.6), 200x2048x2048 10.2 (9.7).
+    // With two stages they stay in front: the tile is waited for at the end of the next k tile, and the reads they hold up are the
+    // other workgroup's time to multiply (steps of hidden 4224, four layers of two micro-batches of 439 tokens: 7628 us behind, 7510 in
+    // front; hidden 10816, two of 621 tokens, 9013 and 8863).
     // NT problems on the larger tiles spread the instructions that refill a slot over the four k steps
     // that follow its release, a quarter behind each step's MFMAs: 333x22016x4096 (192x192 tiles) 81 -> 72 us, 333x12288x4096
     // (192x128) 52 -> 50, 333x4096x4096 (128x128) 24.2 -> 23.1.  Not with two stages, where the tile would be waited for right
@@ -472,11 +475,12 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g, const Rin
             __builtin_amdgcn_sched_barrier(0);
             refill = kt + NS < nt;
             if (refill) next_tile();
+            if (NS == 2 && refill) issue_part(slot, std::integral_constant<int, -1>{});
             if (kt + 1 < nt) fetch(0, next, 0);
             __builtin_amdgcn_sched_barrier(0);
             mma(1);
             __builtin_amdgcn_sched_barrier(0);
-            if (!SPREAD && refill) issue_part(slot, std::integral_constant<int, -1>{});
+            if (NS > 2 && !SPREAD && refill) issue_part(slot, std::integral_constant<int, -1>{});
             if (SPREAD && refill) issue_part(slot, std::integral_constant<int, 0>{});
             __builtin_amdgcn_sched_barrier(0);
             fold();
