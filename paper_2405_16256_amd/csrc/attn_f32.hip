@@ -172,6 +172,8 @@ struct F32Shape {
     Divisor heads, nh_, group;        // heads of all samples, of one; query heads of a key/value head
     Divisor kv_jobs, kv, parts_, level;   // dk | dv jobs of a key tile, of one sample; workgroups a key/value head's query heads are dealt to;
                                           // jobs of both passes of a tile
+    Divisor micro;                    // micro-batches
+    int turn;                         // jobs of a tile in all of them, where that is a multiple of 8, otherwise 0
     int G;                            // query heads of one of those workgroups
 };
 
@@ -398,16 +400,20 @@ __device__ __forceinline__ void bwd_kv_body(float* buf, const int kt, const int 
     Merge<D>::write(buf, out + nkv * D, ldo, kt * AT, S, 1.0f, nullptr, 0);
 }
 
+// The backward kernels deal out the jobs of several micro-batches as they do those of several samples, the longest of all of them
+// first: micro-batch by micro-batch the last one's long jobs start when the others are done (8 heads of 64, 500 tokens, 8 micro-batches,
+// together 156 us and 131, apart 149 and 134).
 template <int D>
 __global__ __launch_bounds__(AW* WAVE, 2) void k_attn_f32_bwd_q(const float* __restrict__ qkv, int ld,
                                                                 const float* __restrict__ o, const float* __restrict__ dout,
                                                                 const float* __restrict__ lse, float* __restrict__ dvec,
                                                                 float* __restrict__ dqkv, const float* __restrict__ table, int table_seq,
                                                                 F32Shape sh, MicroStride micro) {
-    qkv = micro_at(qkv, micro.saved); o = micro_at(o, micro.saved); lse = micro_at(lse, micro.saved);
-    dout = micro_at(dout, micro.ws); dvec = micro_at(dvec, micro.ws); dqkv = micro_at(dqkv, micro.ws);
-    __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
     int qt = (int)blockIdx.x;
+    const int m = split_off(qt, sh.micro);
+    qkv = micro_at(qkv, micro.saved, m); o = micro_at(o, micro.saved, m); lse = micro_at(lse, micro.saved, m);
+    dout = micro_at(dout, micro.ws, m); dvec = micro_at(dvec, micro.ws, m); dqkv = micro_at(dqkv, micro.ws, m);
+    __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
     const int hb = split_off(qt, sh.heads);
     bwd_q_body<D>(buf, sh.tiles - 1 - qt, hb, qkv, ld, o, dout, lse, dvec, dqkv, sh, table, table_seq);
 }
@@ -417,25 +423,35 @@ __global__ __launch_bounds__(AW* WAVE, 1) void k_attn_f32_bwd_kv(const float* __
                                                                  const float* __restrict__ dvec, float* __restrict__ dqkv,
                                                                  float* __restrict__ partial, const float* __restrict__ table, int table_seq,
                                                                  F32Shape sh, MicroStride micro) {
-    qkv = micro_at(qkv, micro.saved); lse = micro_at(lse, micro.saved);
-    dout = micro_at(dout, micro.ws); dvec = micro_at(dvec, micro.ws); dqkv = micro_at(dqkv, micro.ws); partial = micro_at(partial, micro.ws);
-    __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
     int kt = (int)blockIdx.x;   // the first keys see the most queries: longest first
+    const int m = split_off(kt, sh.micro);
+    qkv = micro_at(qkv, micro.saved, m); lse = micro_at(lse, micro.saved, m);
+    dout = micro_at(dout, micro.ws, m); dvec = micro_at(dvec, micro.ws, m); dqkv = micro_at(dqkv, micro.ws, m); partial = micro_at(partial, micro.ws, m);
+    __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
     const int rest = split_off(kt, sh.kv_jobs);
     bwd_kv_body<D, true>(buf, kt, rest, qkv, ld, nullptr, dout, lse, dvec, dqkv, partial, sh, table, table_seq);
 }
-// Both passes in one launch: the dk | dv jobs of key tile l and the dq jobs of query tile n-1-l, longest first.
+// Both passes in one launch: the dk | dv jobs of key tile l and the dq jobs of query tile n-1-l, longest first.  Workgroups go to the
+// 8 XCDs in turn, and in each of them to its 4 shader engines in turn.  Where the jobs of a tile are a multiple of 8, an engine would be
+// given those of one pass again and again, so every 32 workgroups the passes change places: 8 heads of 64, 2000 tokens 222 -> 187 us,
+// 16, 700 71 -> 61; 8 of 128, 600 tokens 69 -> 57, 500 47 -> 43.
 template <int D>
 __global__ __launch_bounds__(AW* WAVE, D == 64 ? 2 : 1) void k_attn_f32_bwd_both(const float* __restrict__ qkv, int ld,
                                                                 const float* __restrict__ o, const float* __restrict__ dout,
                                                                 const float* __restrict__ lse, float* __restrict__ dqkv,
                                                                 float* __restrict__ partial, const float* __restrict__ table, int table_seq,
                                                                 F32Shape sh, MicroStride micro) {
-    qkv = micro_at(qkv, micro.saved); o = micro_at(o, micro.saved); lse = micro_at(lse, micro.saved);
-    dout = micro_at(dout, micro.ws); dqkv = micro_at(dqkv, micro.ws); partial = micro_at(partial, micro.ws);
-    __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
     int level = (int)blockIdx.x;
-    const int r = split_off(level, sh.level), kv_jobs = sh.kv_jobs.d;
+    const int m = split_off(level, sh.micro);
+    qkv = micro_at(qkv, micro.saved, m); o = micro_at(o, micro.saved, m); lse = micro_at(lse, micro.saved, m);
+    dout = micro_at(dout, micro.ws, m); dqkv = micro_at(dqkv, micro.ws, m); partial = micro_at(partial, micro.ws, m);
+    __shared__ __attribute__((aligned(16))) float buf[Merge<D>::FLOATS];
+    int r = split_off(level, sh.level);
+    const int kv_jobs = sh.kv_jobs.d;
+    if ((uint32_t)(level * sh.turn) >> 5 & 1u) {
+        r += kv_jobs;
+        if (r >= sh.level.d) r -= sh.level.d;
+    }
     if (r < kv_jobs) bwd_kv_body<D, false>(buf, level, r, qkv, ld, o, dout, lse, nullptr, dqkv, partial, sh, table, table_seq);
     else bwd_q_body<D>(buf, sh.tiles - 1 - level, r - kv_jobs, qkv, ld, o, dout, lse, nullptr, dqkv, sh, table, table_seq);
 }
@@ -468,39 +484,49 @@ __global__ __launch_bounds__(256) void k_attn_f32_kv_reduce(const float* __restr
     *reinterpret_cast<f32x4*>(out + HALF) = b;
 }
 
-static F32Shape f32_shape(int B, int S, int nh, int nkv, int parts) {
+static F32Shape f32_shape(int B, int S, int nh, int nkv, int parts, int micro) {
     F32Shape s;
     s.B = B; s.S = S; s.nh = nh; s.nkv = nkv; s.tiles = (S + AT - 1) / AT; s.parts = parts; s.G = nh / nkv / parts;
+    s.micro = divisor(micro); s.turn = (B * (nkv * parts + nh) * micro) % 8 ? 0 : B * (nkv * parts + nh) * micro;
     s.heads = divisor(nh * B); s.nh_ = divisor(nh); s.group = divisor(nh / nkv);
     s.kv_jobs = divisor(B * nkv * parts); s.kv = divisor(nkv * parts); s.parts_ = divisor(parts); s.level = divisor(B * nkv * parts + nh * B);
     return s;
 }
 
+// The query heads that share a key/value head run one after the other in a workgroup, unless that leaves fewer than
+// two workgroups per CU and the scratch holds their partial sums.  dq, dk and dv together, kept together -> dealt
+// out: 8 heads of 128 on 2, 700 tokens, 202 -> 92 us; 350 tokens 101 -> 50; 16 heads of 64 on 2, 2 x 1024 tokens,
+// 349 -> 261; 4 heads of 64 on 1, 128 tokens, 27 -> 30 (the reduction's launch).  A micro-batch by itself decides, so that the
+// order of its sums does not depend on those beside it.
+static int kv_parts(int B, int S, int nh, int nkv, size_t part_bytes, size_t scratch_bytes) {
+    const int tiles = (S + AT - 1) / AT, G = nh / nkv;
+    int parts = 1;
+    for (int p = 2; p <= G; p++)
+        if (G % p == 0 && (long)tiles * B * nkv * parts < 512 && p * part_bytes <= scratch_bytes) parts = p;
+    return parts;
+}
+
+// Both passes in one launch while its jobs, those of all samples and micro-batches, are few: each pass alone is bound by its longest
+// job, and the second waits for the first.  But every dk | dv job then reads o as well, and the dq jobs get the dk | dv jobs' registers,
+// so that fewer of them share a CU (head_dim 64: two workgroups for three; 128: one for two).  us apart -> together, head_dim 64:
+// 4 heads, 128 tokens (64 jobs) 14.2 -> 8.4; 8, 2000 (2000) 191 -> 187; 16 on 2, 2 x 1024 (2560) 257 -> 217; 32, 1000 (4032) 212 -> 209;
+// 11, 2 x 1500 (4136) 300 -> 315; 24, 2000 (6000) 535 -> 554.  128: 1 head, 44 tokens 15.9 -> 8.9; 8, 500 (512) 56.5 -> 42.7; 10, 500 (640)
+// 63 -> 58; 9, 700 (792) 87.7 -> 85.1, but 11, 500 (704) 66 -> 68; 16, 17 x 13 (832) 21.5 -> 22.7; 8, 1000 (1008) 126 -> 130.
+static bool together(int D, long jobs) { return jobs <= (D == 64 ? 4096 : 640); }
+
 template <int D>
 static hipError_t launch_bwd(const float* qkv, int ld, const float* o, const float* dout, const float* lse, float* dvec, float* dqkv,
                              float* scratch, size_t scratch_bytes, int B, int S, int nh, int nkv, const float* table, int table_seq,
                              const MicroStride& micro, hipStream_t st) {
-    const int tiles = (S + AT - 1) / AT, G = nh / nkv;
-    // The query heads that share a key/value head run one after the other in a workgroup, unless that leaves fewer than
-    // two workgroups per CU and the scratch holds their partial sums.  dq, dk and dv together, kept together -> dealt
-    // out: 8 heads of 128 on 2, 700 tokens, 202 -> 92 us; 350 tokens 101 -> 50; 16 heads of 64 on 2, 2 x 1024 tokens,
-    // 349 -> 261; 4 heads of 64 on 1, 128 tokens, 27 -> 30 (the reduction's launch).
-    int parts = 1;
     const size_t part_bytes = (size_t)B * S * 2 * nkv * D * sizeof(float);
-    for (int p = 2; p <= G; p++)
-        if (G % p == 0 && (long)tiles * B * nkv * parts < 512 && p * part_bytes <= scratch_bytes) parts = p;
-    const F32Shape sh = f32_shape(B, S, nh, nkv, parts);
-    const unsigned jobs_q = tiles * B * nh, jobs_kv = tiles * B * nkv * parts;
-    // Both passes in one launch while its jobs are few: each pass alone is bound by its longest job, and the second waits for
-    // the first.  Every dk | dv job then reads o as well, and at head_dim 128 a workgroup has its CU to itself (406
-    // registers), the dq jobs too.  us apart -> together, head_dim 64: 4 heads, 128 tokens (64 jobs) 14.2 -> 8.3; 16 on 2, 2 x 1024
-    // (4096) 256 -> 217; 8, 4 x 1000 (4032) 211 -> 209; 16, 4 x 1000 (8064) 404 -> 425.  128: 1 head, 44 tokens 14.8 -> 8.6; 8, 500
-    // (512) 56.5 -> 46.9; 8, 620 (624) 73.3 -> 72.0; 8 on 2, 700 (704) 86 -> 88.5; 8, 1024 (1024) 128 -> 152.
-    if (jobs_q + jobs_kv <= (D == 64 ? 4096u : 640u)) {
-        k_attn_f32_bwd_both<D><<<dim3(jobs_q + jobs_kv, micro.n), AW * WAVE, 0, st>>>(qkv, ld, o, dout, lse, dqkv, scratch, table, table_seq, sh, micro);
+    const int parts = kv_parts(B, S, nh, nkv, part_bytes, scratch_bytes);
+    const F32Shape sh = f32_shape(B, S, nh, nkv, parts, micro.n);
+    const unsigned jobs_q = (unsigned)sh.tiles * B * nh * micro.n, jobs_kv = (unsigned)sh.tiles * B * nkv * parts * micro.n;
+    if (together(D, (long)jobs_q + jobs_kv)) {
+        k_attn_f32_bwd_both<D><<<jobs_q + jobs_kv, AW * WAVE, 0, st>>>(qkv, ld, o, dout, lse, dqkv, scratch, table, table_seq, sh, micro);
     } else {
-        k_attn_f32_bwd_q<D><<<dim3(jobs_q, micro.n), AW * WAVE, 0, st>>>(qkv, ld, o, dout, lse, dvec, dqkv, table, table_seq, sh, micro);
-        k_attn_f32_bwd_kv<D><<<dim3(jobs_kv, micro.n), AW * WAVE, 0, st>>>(qkv, ld, dout, lse, dvec, dqkv, scratch, table, table_seq, sh, micro);
+        k_attn_f32_bwd_q<D><<<jobs_q, AW * WAVE, 0, st>>>(qkv, ld, o, dout, lse, dvec, dqkv, table, table_seq, sh, micro);
+        k_attn_f32_bwd_kv<D><<<jobs_kv, AW * WAVE, 0, st>>>(qkv, ld, dout, lse, dvec, dqkv, scratch, table, table_seq, sh, micro);
     }
     if (parts > 1) {
         const long n = (long)B * S * 2 * nkv * (D / 8);
@@ -513,7 +539,7 @@ static hipError_t launch_bwd(const float* qkv, int ld, const float* o, const flo
 hipError_t attn_f32_fwd(const void* qkv, int ld, void* o, float* lse, int B, int S, int nh, int nkv, int d, const MicroStride& micro,
                         hipStream_t st) {
     const dim3 grid((S + AT - 1) / AT * B * nh, micro.n);
-    const F32Shape sh = f32_shape(B, S, nh, nkv, 1);
+    const F32Shape sh = f32_shape(B, S, nh, nkv, 1, micro.n);
     if (d == 64) k_attn_f32_fwd<64><<<grid, AW * WAVE, 0, st>>>((const float*)qkv, ld, (float*)o, lse, sh, micro);
     else if (d == 128) k_attn_f32_fwd<128><<<grid, AW * WAVE, 0, st>>>((const float*)qkv, ld, (float*)o, lse, sh, micro);
     else return hipErrorInvalidValue;
@@ -531,3 +557,9 @@ hipError_t attn_f32_bwd(const void* qkv, int ld, const void* o, const void* dout
 }
 
 }  // namespace hh
+
+// For tests, not part of the public interface: whether the backward passes of that many micro-batches share a launch.
+extern "C" int hh_internal_attn_f32_together(int B, int S, int nh, int nkv, int d, int micro) {
+    using namespace hh;
+    return together(d, (long)((S + AT - 1) / AT) * B * (nh + nkv * kv_parts(B, S, nh, nkv, 0, 0)) * micro);
+}

@@ -115,11 +115,13 @@ __device__ __forceinline__ void swiglu_grad(float gate, float up, float dm, floa
     dup = dm * sl;
 }
 
-// ---- the operand of micro-batch m (blockIdx.y) where consecutive ones lie `stride` bytes apart.
+// ---- the operand of micro-batch m (blockIdx.y unless given) where consecutive ones lie `stride` bytes apart.
 template <typename T>
-__device__ __forceinline__ T* micro_at(T* p, size_t stride) {
-    return (T*)((const char*)p + blockIdx.y * stride);
+__device__ __forceinline__ T* micro_at(T* p, size_t stride, uint32_t m) {
+    return (T*)((const char*)p + m * stride);
 }
+template <typename T>
+__device__ __forceinline__ T* micro_at(T* p, size_t stride) { return micro_at(p, stride, blockIdx.y); }
 
 // ---- dynamic LDS above the 48 KB default -------------------------------------
 // The limit is an attribute of the (kernel, device) pair.  `done` is the calling launcher's own record (one
