@@ -261,8 +261,10 @@ __global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_
         // lanes per row: loads of the residual and stores then cover whole 64-byte row segments.  C and R are reached
         // through bounds-checked buffers: rows past M fall behind the buffer's end, columns past N get an
         // out-of-range offset.
-        // The residual is asked for two block rows ahead, and ahead of the next tile's DMA, which it would wait behind: block
-        // row by block row behind the DMA it was four round trips (4096x16384xK: K 1024 187 -> 162 us, 4096 507 -> 485).
+        // The residual is asked for AHEAD blocks ahead, STEP at a time, and ahead of the next tile's DMA, which it would wait behind:
+        // block row by block row behind the DMA it was four round trips (NT 4096x16384xK: K 1024 187 -> 162 us, 4096 507 -> 485; NN
+        // 8192x8192x512 105 -> 98).  NN, whose fragment reads keep more addresses, has registers for three: with four, ten
+        // of them went to scratch memory, and NN 8192x8192x512 took 103.
         {
             const DmaProblem& g = grp.p[cprob];
             const int M = g.M, N = g.N, ldc = g.ldc, ldr = g.ldr;
@@ -272,18 +274,19 @@ __global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_
             const int r_w = lane & 31;                       // row written, chunks 2g + hf
             const int r_r = lane >> 3, c_r = lane & 7;       // row (+ 8t) and chunk read back
             const uint32_t row0 = (uint32_t)(cm0 + wm + r_r);
-            i32x2 res[2][TN][4];
-            auto ask = [&](int i) {
+            constexpr int AHEAD = KIND == GEMM_NT ? 2 * TN : 3, STEP = KIND == GEMM_NT ? TN : 1;
+            i32x2 res[AHEAD][4];
+            auto ask = [&](int from, int to) {   // blocks, row by row
 #pragma unroll
-                for (int j = 0; j < TN; j++) {
-                    const int col = cn0 + wn + 32 * j + 4 * c_r;
+                for (int b = from; b < to; b++) {
+                    const int col = cn0 + wn + 32 * (b % TN) + 4 * c_r;
 #pragma unroll
                     for (int t = 0; t < 4; t++)
-                        res[i & 1][j][t] = __builtin_amdgcn_raw_buffer_load_b64(
-                            rsR, col < N ? ((row0 + 32 * i + 8 * t) * (uint32_t)ldr + (uint32_t)col) * 2u : OUT_OF_RANGE, 0, 0);
+                        res[b % AHEAD][t] = __builtin_amdgcn_raw_buffer_load_b64(
+                            rsR, col < N ? ((row0 + 32 * (b / TN) + 8 * t) * (uint32_t)ldr + (uint32_t)col) * 2u : OUT_OF_RANGE, 0, 0);
                 }
             };
-            if (RES && R) { ask(0); ask(1); }
+            if (RES && R) ask(0, AHEAD);
 #pragma unroll
             for (int i = 0; i < TM; i++) {
 #pragma unroll
@@ -298,17 +301,18 @@ __global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_
                         const int rr = 8 * t + r_r;
                         float4 v = *reinterpret_cast<const float4*>(patch + rr * 128 + ((c_r ^ ((rr >> 1) & 7)) << 4));
                         if (RES && R) {
-                            const i32x2 u = res[i & 1][j][t];
+                            const i32x2 u = res[(TN * i + j) % AHEAD][t];
                             v.x += lo_bf((uint32_t)u[0]); v.y += hi_bf((uint32_t)u[0]); v.z += lo_bf((uint32_t)u[1]); v.w += hi_bf((uint32_t)u[1]);
                         }
                         const i32x2 o = {(int)pack_bf2(v.x, v.y), (int)pack_bf2(v.z, v.w)};
                         __builtin_amdgcn_raw_buffer_store_b64(
                             o, rsC, col < N ? ((row0 + 32 * i + 8 * t) * (uint32_t)ldc + (uint32_t)col) * 2u : OUT_OF_RANGE, 0, 0);
                     }
-                }
-                if (RES && R) {
-                    if (i + 2 < TM) ask(i + 2);
-                    if (i == 1 && has_next) start_tile();
+                    const int asked = TN * i + j + 1 + AHEAD;   // up to here when this block's step is done
+                    if (RES && R && (j + 1) % STEP == 0 && asked <= TM * TN) {
+                        ask(asked - STEP, asked);
+                        if (asked == TM * TN && has_next) start_tile();
+                    }
                 }
             }
         }
