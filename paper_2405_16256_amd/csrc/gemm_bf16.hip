@@ -328,6 +328,11 @@ __global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_
 // k_gemm_dma's loop -> this one: K 2048 315 -> 296 us, 4096 502 -> 479, 8192 908 -> 897; 57344x8192x4096 3508 -> 3456.  NT and NN gain 1
 // to 2.5 % where the loop is long and the chip full, and lose as much or more elsewhere (NN 3300x4096x8192, 208 tiles, 175 -> 183):
 // they are at the power limit or bound by barriers.  Four waves of 128x128 (a third fewer LDS reads) take the same.
+// Every workgroup writes its tile's halves of 128 rows one after the other, all at about the same time, and where a row of C is a power
+// of two bytes, rows 64 apart lie in the same memory channels.  So in every other row of tiles A's halves change places.  += with K 17,
+// k_gemm_dma's loop -> halves in order -> in turn: 16384x2048 51 -> 61 -> 44 us, 8192x4096 67 -> 58 -> 49, 12288x4096 71 -> 75 -> 64;
+// 16384x2112 48 -> 49 -> 49.  K 700 6144x16384 253 -> 246 -> 229.  What the longer prologue costs shows where the sums are short
+// and there is one round of tiles: 4096x4096 by 64 14.6 -> 15.2, by 512 24.4 -> 25.1.
 __global__ __launch_bounds__(512) void k_gemm_dma_tn(DmaGroup grp, int full, int n_items, float* __restrict__ partial) {
     using DT = DmaTile<false, DHALF, 8>;
     constexpr int TM = 4, TN = 2, PW = DT::PER_WAVE, HALF_BYTES = DT::BYTES;   // 2 instructions a wave, 16 KB
@@ -338,6 +343,7 @@ __global__ __launch_bounds__(512) void k_gemm_dma_tn(DmaGroup grp, int full, int
     const int wm = (wave >> 2) * 64, wn = (wave & 3) * 32;          // in each half
     const int nk_all = (grp.K + DK - 1) / DK;
     int prob, m0, n0, kbeg, nk, slot;                               // of a work item, as in k_gemm_dma
+    int turn;                                                       // A's halves change places
     auto decode = [&](int item) {
         int tix;
         if (item < full) { tix = item; kbeg = 0; nk = nk_all; slot = -1; }
@@ -351,7 +357,7 @@ __global__ __launch_bounds__(512) void k_gemm_dma_tn(DmaGroup grp, int full, int
         prob = grp.problem_of(tix);
         int tm, tn;
         grp.p[prob].map.tile(tix - grp.first[prob], tm, tn);
-        m0 = tm * DTILE; n0 = tn * DTILE;
+        m0 = tm * DTILE; n0 = tn * DTILE; turn = tm & 1;
     };
     int item = (int)blockIdx.x;
     decode(item);
@@ -381,7 +387,7 @@ __global__ __launch_bounds__(512) void k_gemm_dma_tn(DmaGroup grp, int full, int
         for (int i = 0; i < PW; i++) { voA[i] = DT::voff(wave, i, 0, g.lda); voB[i] = DT::voff(wave, i, 0, g.ldb); }
 #pragma unroll
         for (int h = 0; h < 2; h++) {
-            const uint32_t skip_a = (uint32_t)(m0 + h * DHALF) * 2u + (uint32_t)kbeg * stepA;
+            const uint32_t skip_a = (uint32_t)(m0 + (h ^ turn) * DHALF) * 2u + (uint32_t)kbeg * stepA;
             const uint32_t skip_b = (uint32_t)(n0 + h * DHALF) * 2u + (uint32_t)kbeg * stepB;
             hA[h] = Half{(uint64_t)g.A + skip_a, (int)(g.a_bytes >> 1) - (int)(skip_a >> 1)};
             hB[h] = Half{(uint64_t)g.B + skip_b, (int)(g.b_bytes >> 1) - (int)(skip_b >> 1)};
@@ -474,7 +480,7 @@ __global__ __launch_bounds__(512) void k_gemm_dma_tn(DmaGroup grp, int full, int
         }
 
         // next piece of work of this workgroup: start its loads before writing this one out (the stages have been read)
-        const int cm0 = m0, cn0 = n0, cslot = slot, cprob = prob;
+        const int cm0 = m0, cn0 = n0, cslot = slot, cprob = prob, cturn = turn;
         item += (int)gridDim.x;
         const bool has_next = item < n_items;
         if (has_next) {
@@ -486,7 +492,7 @@ __global__ __launch_bounds__(512) void k_gemm_dma_tn(DmaGroup grp, int full, int
         int lane = threadIdx.x & 63;
         asm volatile("" : "+v"(lane));
         const int hf = lane >> 5, r_w = lane & 31;
-        auto block_row = [&](int i) { return DHALF * (i >> 1) + wm + 32 * (i & 1); };
+        auto block_row = [&](int i) { return DHALF * ((i >> 1) ^ cturn) + wm + 32 * (i & 1); };
         if (cslot >= 0) {   // a share of the k range
             float* pt = partial + (size_t)cslot * (DTILE * DTILE);
 #pragma unroll
