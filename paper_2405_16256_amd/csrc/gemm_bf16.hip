@@ -1182,6 +1182,18 @@ bool gemm_bf16_norms(const GemmDesc* g, int n) {
     return can_norm(g, n, r);
 }
 
+// The launches of problems of several micro-batches: launch(first problem, problems, plan) of each, until one fails.
+template <typename L>
+static hipError_t micro_launches(const GemmDesc* g, int n, const Route& r, L launch) {
+    if (r.how == Route::RING) return launch(0, n, r.group);
+    const Plan whole{WHOLE_DW, {1, 1, 1, 1}, {0, 1, 2, 3}, 0.0, 0};
+    hipError_t e = hipSuccess;
+    const int step = r.how == Route::TILES256 ? RING_MAX : 1;
+    for (int i = 0; i < n && e == hipSuccess; i += step)
+        e = launch(i, std::min(n - i, step), r.how == Route::TILES256 || r.each[i].v == V_DMA ? whole : r.each[i]);
+    return e;
+}
+
 hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st) {
     if (n < 1 || n > DMA_MAX) return hipErrorInvalidValue;
     for (int i = 0; i < n; i++) {
@@ -1201,13 +1213,8 @@ hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st) {
             g[i].norm != g[0].norm)
             return hipErrorInvalidValue;
     if (g[0].norm && !can_norm(g, n, r)) return hipErrorInvalidValue;
+    if (g[0].micro > 1) return micro_launches(g, n, r, [&](int i, int m, const Plan& p) { return launch_planned(g + i, m, p, st); });
     if (r.how == Route::RING) return launch_planned(g, n, r.group, st);
-    const Plan whole{WHOLE_DW, {1, 1, 1, 1}, {0, 1, 2, 3}, 0.0};
-    if (r.how == Route::TILES256 && g[0].micro > 1) {
-        hipError_t e = hipSuccess;
-        for (int i = 0; i < n && e == hipSuccess; i += RING_MAX) e = launch_planned(g + i, std::min(n - i, RING_MAX), whole, st);
-        return e;
-    }
     if (r.how == Route::TILES256) return launch_tiles256(g, n, st);
     for (int i = 0; i < n; i++) {
         hipError_t e = hipSuccess;
@@ -1215,7 +1222,7 @@ hipError_t gemm_bf16(const GemmDesc* g, int n, hipStream_t st) {
             GemmDesc seg[3];
             const int m = segments(g[i], seg);
             for (int j = 0; j < m && e == hipSuccess; j++) e = launch_planned(seg + j, 1, plan(seg + j, 1, false), st);
-        } else e = launch_planned(g + i, 1, g[i].micro > 1 && r.each[i].v == V_DMA ? whole : r.each[i], st);
+        } else e = launch_planned(g + i, 1, r.each[i], st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -1263,19 +1270,26 @@ extern "C" int hh_internal_gemm_plan(const int* problems, int n, char* out, size
     }
     return 0;
 }
-// The weight gradients (bits) of a launch of several micro-batches whose products are apart, with that much room for partial sums.
+// The weight gradients (bits) of a call for several micro-batches whose products are apart, with that much room for partial sums; -1
+// where such a call is refused.
 extern "C" int hh_internal_products_apart(const int* problems, int n, int micro, size_t room) {
     using namespace hh;
-    if (n < 1 || n > RING_MAX) return -1;
-    GemmDesc g[RING_MAX];
+    if (n < 1 || n > DMA_MAX) return -1;
+    GemmDesc g[DMA_MAX];
     for (int i = 0; i < n; i++) {
         g[i] = sizes_of(problems + 6 * i);
         g[i].micro = micro; g[i].ws_room = room;
     }
+    RingUse use;
+    if (!gemm_bf16_on_ring(g, n, &use)) return -1;
     Route r;
     route(g, n, r);
-    const Plan& p = n > 1 ? r.group : r.each[0];
-    return (n > 1) != (r.how == Route::RING) || p.v >= V_DMA ? -1 : (int)micro_plan(g, n, p).apart;
+    int apart = 0;
+    (void)micro_launches(g, n, r, [&](int i, int m, const Plan& p) {
+        if (g[i].kind != GEMM_NT) apart |= (int)(micro_plan(g + i, m, p).apart << i);
+        return hipSuccess;
+    });
+    return apart;
 }
 // Whether one launch of these problems, all NT on one A, norms its rows itself.
 extern "C" int hh_internal_gemm_norms(const int* problems, int n) {

@@ -1,13 +1,14 @@
 """Several micro-batches in one launch: a weight gradient's products one after the other in a workgroup, or each in a workgroup of
 its own, added by the reduction in the same order.  The bits are those of one micro-batch after the other."""
 import ctypes as C
+import random
 
 import pytest
 
 from paper_2405_16256_amd import binding as hh
 from paper_2405_16256_amd import inputs as I
 from tests import gemm_plans, stage_plans
-from tests.test_stage_side_by_side import hh_sizes
+from tests.test_stage_side_by_side import DEFERRING, hh_sizes
 from tests.test_stage_side_by_side import test_same_bits_as_one_by_one as same_bits
 
 MB = 1 << 20
@@ -42,6 +43,26 @@ def test_rule_leaves_short_sums():
     for tokens in (64, 128, 333):
         for g in groups(I.LayerShape(1024, 8, 128, 2752, tokens, 1)):
             assert apart(g, 8, 512 * MB) in (0, -1), tokens
+
+
+def test_gradients_of_few_tokens_stay_in_one_workgroup():
+    # those that 256x256 tiles would take alone: they are bound by the traffic of the gradients, which partial sums would add to
+    rng, seen = random.Random(9), set()
+    shapes = [(I.LayerShape(64 * rng.randint(24, 192), rng.choice((4, 8, 16, 32, 64)), 128, 64 * rng.randint(16, 448), rng.randint(1, 448), 1),
+               rng.random() < 0.7) for _ in range(600)] + [c[:2] for c in DEFERRING]
+    for shape, packed in shapes:
+        M = rng.randint(2, 8)
+        calls = gemm_plans._calls(shape, packed)[1]
+        if gemm_plans.defers(shape, packed):
+            calls = [[q for g in calls for q in g[:-1]]]
+        for problems in ([p for _, p in c] for c in calls):
+            plans = gemm_plans.plan(problems)
+            of = sum(1 << i for i, (r, p) in enumerate(zip(plans, problems)) if r[1] == "256x256" and p[0] == gemm_plans.TN)
+            bits = apart(problems, M, 1 << 40)
+            if of and bits >= 0:
+                assert bits & of == 0, (shape, packed, M)
+                seen.add((plans[0][0], len(problems)))
+    assert {("alone", 2), ("alone", 4), ("tiles256", 4), ("tiles256", 7)} <= seen
 
 
 @pytest.mark.gpu
