@@ -82,7 +82,8 @@ struct DmaGroup {
 // Instructions are fetched 32 bytes at a time, and where an 8-byte MFMA or the target of a branch lies in its 32 bytes decides whether
 // the two waves of a SIMD are fed in time: the same k loop takes up to 2.4 % longer 16 bytes further on (NT 4096x8192x12288 by 4-byte
 // steps from a 32-byte line: 627 627 630 622 636 628 629 623 us).  So the loops don't begin where the code before them happens to end
-// but WORDS instructions behind such a line; each kernel's number is the best of the eight for its loop as it stands.
+// but WORDS instructions behind such a line.  NT, NN and TN have a number each, the best of the eight for the loop as it stands or within
+// 0.5 % of it, with a residual as without (NT with one 4096x8192x12288: 638 640 640 635 649 643 639 635); another compiler's may be others.
 template <int WORDS>
 __device__ __forceinline__ void place_loop() {
     asm volatile(".p2align 5\n\t.fill %0, 4, 0xbf800000" ::"n"(WORDS));   // s_nop
@@ -325,9 +326,10 @@ __global__ __launch_bounds__(512) void k_gemm_dma(DmaGroup grp, int full, int n_
 // a wave has 64x32 each, one quadrant after the other over all k of a stage, so that each half of an operand's tile is read in one go
 // and its place refilled from then on: a request is on its way for 1.25 to 1.5 stages where k_gemm_dma leaves it 0.5 to 1, for a
 // second barrier per stage.  Half the fragments of both operands stay in registers (96).  4096x16384xK, four rounds of tiles,
-// k_gemm_dma's loop -> this one: K 2048 315 -> 296 us, 4096 502 -> 479, 8192 908 -> 897; 57344x8192x4096 3508 -> 3456.  NT and NN gain 1
-// to 2.5 % where the loop is long and the chip full, and lose as much or more elsewhere (NN 3300x4096x8192, 208 tiles, 175 -> 183):
-// they are at the power limit or bound by barriers.  Four waves of 128x128 (a third fewer LDS reads) take the same.
+// k_gemm_dma's loop -> this one, the halves written in order: K 2048 315 -> 296 us, 4096 502 -> 479, 8192 908 -> 897; 57344x8192x4096
+// 3508 -> 3456.  NT and NN gain 1 to 2.5 % where the loop is long and the chip full, and lose as much or more elsewhere (NN
+// 3300x4096x8192, 208 tiles, 175 -> 183): they are at the power limit or bound by barriers.  Four waves of 128x128 (a third fewer LDS
+// reads) take the same.
 // Every workgroup writes its tile's halves of 128 rows one after the other, all at about the same time, and where a row of C is a power
 // of two bytes, rows 64 apart lie in the same memory channels.  So in every other row of tiles A's halves change places.  += with K 17,
 // k_gemm_dma's loop -> halves in order -> in turn: 16384x2048 51 -> 61 -> 44 us, 8192x4096 67 -> 58 -> 49, 12288x4096 71 -> 75 -> 64;
@@ -1161,9 +1163,10 @@ bool gemm_bf16_on_ring(const GemmDesc* g, int n, RingUse* use) {
     return true;
 }
 
-// Whether the launch of these projections norms its rows itself: where it is one of whole 64x64 tiles, one workgroup a CU at most, and
-// a row has up to NORM_K columns.  Forward passes of hidden 128 and 256, 17 to 1100 tokens, take 6 to 18 % less, steps of four
-// micro-batches 2 to 7 %.  Rows of 320 to 512 columns (twice the registers and instructions): 0 to 3 % less where a micro-batch is
+// Whether the launch of these projections norms its rows itself: where it is one of whole 64x64 tiles, one workgroup a CU at most for
+// a micro-batch, and a row has up to NORM_K columns.  Forward passes of hidden 128 and 256, 17 to 1100 tokens, take 6 to 18 % less.
+// Several micro-batches, up to eight workgroups a CU, don't move the line: each of 48 steps of 2, 4 and 8 (hidden 128 to 256, 32 to 2000
+// tokens, up to 256 workgroups a micro-batch) takes 1 to 8 % less.  Rows of 320 to 512 columns (twice the registers and instructions): 0 to 3 % less where a micro-batch is
 // alone, up to 11 % more for four of 200 and more tokens.
 static bool can_norm(const GemmDesc* g, int n, const Route& r) {
     const bool ring = r.how == Route::RING;

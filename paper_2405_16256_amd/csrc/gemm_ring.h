@@ -78,7 +78,8 @@ __device__ __forceinline__ float rotated(float v) { return __int_as_float(__buil
 
 // NORM (K up to NORM_K): the tile's rows of x come into registers, are normed as k_rmsnorm_fwd norms them, to the same bits, and lie in
 // LDS for all of k; only B goes through the ring.  Bound by latency: the launch before it (3.6 us with the gap behind it, of rows of 256)
-// goes, and the workgroups get 1.2 to 1.9 us longer, for about 500 instructions between x and its place in LDS.
+// goes, and the workgroups get 1.2 to 1.9 us longer, for about 500 instructions between x and its place in LDS and because what waits for
+// x and the gain, which the compiler counts, waits for the requests of B behind them too.
 template <int KIND, int MB, bool F, int BM, int BN, int WM, int WN, int NS, bool NORM = false>
 __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g, const RingNorm<MB>* norm = nullptr, bool writer = false) {
     if constexpr (NORM) asm volatile("" ::"s"(norm->gain), "s"(norm->eps), "s"(g.K), "s"(g.M), "s"(g.N));
@@ -322,7 +323,8 @@ __device__ __forceinline__ void ring_body(const RingProblem<MB, F>& g, const Rin
     // Asked for behind the requests of the first k tiles on the smaller tiles, whose epilogue would otherwise be a round trip to
     // memory: 128x768x256 with rotary embedding 4.2 -> 4.0 us, 700x1536x1024 10.6 -> 10.1, 128x256x256 with residual 3.33 -> 3.30.
     // Of three or four blocks a wave, 64 registers, it costs more than it gives (1100x3072x3072 with residual 27.4 -> 28.2), and
-    // gate|up, two tiles as large as the product, hold up the k tiles behind them (700x2048x1024 12.2 -> 12.6).
+    // gate|up, two tiles as large as the product, hold up the k tiles behind them (700x2048x1024 12.2 -> 12.6).  The wait for k tile 0
+    // leaves as many requests on their way as the later tiles have, so it covers as many of those as are asked for here.
     constexpr bool EARLY = TM * TN <= 2 && !(KIND == GEMM_NN && FUSES);
     Beside beside[EARLY ? TM : 1][EARLY ? TN : 1];
     if (EARLY && ksplit == 1 && !SUMS) {
