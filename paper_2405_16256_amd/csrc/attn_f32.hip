@@ -511,7 +511,8 @@ static int kv_parts(int B, int S, int nh, int nkv, size_t part_bytes, size_t scr
 // so that fewer of them share a CU (head_dim 64: two workgroups for three; 128: one for two).  us apart -> together, head_dim 64:
 // 4 heads, 128 tokens (64 jobs) 14.2 -> 8.4; 8, 2000 (2000) 191 -> 187; 16 on 2, 2 x 1024 (2560) 257 -> 217; 32, 1000 (4032) 212 -> 209;
 // 11, 2 x 1500 (4136) 300 -> 315; 24, 2000 (6000) 535 -> 554.  128: 1 head, 44 tokens 15.9 -> 8.9; 8, 500 (512) 56.5 -> 42.7; 10, 500 (640)
-// 63 -> 58; 9, 700 (792) 87.7 -> 85.1, but 11, 500 (704) 66 -> 68; 16, 17 x 13 (832) 21.5 -> 22.7; 8, 1000 (1008) 126 -> 130.
+// 63 -> 58.  From there on it depends on the heads: 8 on 2, 700 (704) 87 -> 75, 11, 500 (704) 66 -> 68, 16, 13 x 17 (832) 21.5 -> 22.7, 8, 1000
+// (1008) 126 -> 130.
 static bool together(int D, long jobs) { return jobs <= (D == 64 ? 4096 : 640); }
 
 template <int D>
